@@ -48,22 +48,24 @@ __device__ inline int share_owner(const ShareTable& tb, int K, int id) {
 
 // Partial sums of (a) x and x^2, or (b) dy and dy*xhat, over one split of one worker's positions.
 // grid (total splits, ceil(C/64)); block = 8 channel pieces x 32 position lanes; four
-// positions per lane in flight.
+// positions per lane in flight.  A split is `per` positions, a whole number of trips of 128: splits of
+// equal shares instead made most of them end in a trip for one to three positions (129 positions each for
+// 128 32x32 images over 1016 workgroups: two trips where one does).
 template <bool BWD>
 __global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                          const float* __restrict__ stats, int C, int hw,
-                                                         Segments seg, ShareTable tb, double* __restrict__ partial) {
+                                                         Segments seg, ShareTable tb, int per,
+                                                         double* __restrict__ partial) {
   __shared__ double red[32][8][17];
   const int tid = threadIdx.x;
   const int c8 = tid & 7, pl = tid >> 3;
   const int wk = share_owner(tb, seg.K, blockIdx.x);
-  const int split = blockIdx.x - tb.first[wk], nsplit = tb.first[wk + 1] - tb.first[wk];
+  const int split = blockIdx.x - tb.first[wk];
   const int c0 = blockIdx.y * 64 + c8 * 8;
   const bool cok = c0 < C;
   const int cl = cok ? c0 : 0;   // a piece past the last channel shadows piece 0 and is not stored
   const long pbeg = (long)seg.off[wk] * hw, pend = (long)seg.off[wk + 1] * hw;
-  const long per = (pend - pbeg + nsplit - 1) / nsplit;
-  const long sbeg = pbeg + split * per, send = min(pend, sbeg + per);
+  const long sbeg = pbeg + (long)split * per, send = min(pend, sbeg + per);
   // Sums run in double: this kernel waits on memory, and statistics good to fp32
   // rounding keep the normalised values from landing on the other side of a bf16
   // rounding boundary more often than the arithmetic forces.
@@ -117,39 +119,41 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restric
   }
 }
 
-// Sum of worker wk's split partials for 64 channels: 4 lanes per channel walk the splits
-// (stride 4, fixed order), then the 4 lane sums are added in lane order.
+// Sum of worker wk's split partials for 16 channels: 16 lanes per channel walk the splits (stride 16, fixed
+// order), then the 16 lane sums are added in lane order.  Bound by the chain of dependent round trips, not
+// by bytes: with 4 lanes per channel and 64 channels per workgroup it was eight trips and 10 us for the 254
+// splits of the largest layers, with 16 it is two.
+constexpr int kFinLanes = 16, kFinChannels = 16;
 __device__ inline void bn_sum_splits(const double* __restrict__ partial, int C, const ShareTable& tb, int wk,
-                                     int c, int sg, double (*red)[64][2], double& a, double& b) {
+                                     int c, int sg, double (*red)[kFinChannels][2], double& a, double& b) {
   a = 0.0; b = 0.0;
-  if (c < C) {
-    int s = tb.first[wk] + sg;
-    const int s_end = tb.first[wk + 1];
-    for (; s + 28 < s_end; s += 32) {   // eight loads in flight; the additions keep their order
-      double2 v[8];
+  const int cl = c < C ? c : C - 1;
+  const int s_end = tb.first[wk + 1];
+  for (int s = tb.first[wk] + sg; s < s_end; s += 8 * kFinLanes) {   // eight loads in flight, added in order
+    double2 v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const double2*>(partial + ((size_t)(s + 4 * u) * C + c) * 2);
+    for (int u = 0; u < 8; ++u)
+      v[u] = *reinterpret_cast<const double2*>(partial + ((size_t)min(s + kFinLanes * u, s_end - 1) * C + cl) * 2);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { a += v[u].x; b += v[u].y; }
-    }
-    for (; s < s_end; s += 4) {
-      const double2 v = *reinterpret_cast<const double2*>(partial + ((size_t)s * C + c) * 2);
-      a += v.x; b += v.y;
-    }
+    for (int u = 0; u < 8; ++u)
+      if (s + kFinLanes * u < s_end) { a += v[u].x; b += v[u].y; }
   }
-  red[sg][threadIdx.x & 63][0] = a;
-  red[sg][threadIdx.x & 63][1] = b;
+  const int cc = threadIdx.x % kFinChannels;
+  red[sg][cc][0] = a;
+  red[sg][cc][1] = b;
   __syncthreads();
-  const int cc = threadIdx.x & 63;
-  a = (red[0][cc][0] + red[1][cc][0]) + (red[2][cc][0] + red[3][cc][0]);
-  b = (red[0][cc][1] + red[1][cc][1]) + (red[2][cc][1] + red[3][cc][1]);
+  a = 0.0; b = 0.0;
+  if (sg == 0) {
+#pragma unroll
+    for (int l = 0; l < kFinLanes; ++l) { a += red[l][cc][0]; b += red[l][cc][1]; }
+  }
 }
 
-// Forward: mean and 1/sqrt(var + eps) per (worker, channel).  grid (K, ceil(C/64)).
+// Forward: mean and 1/sqrt(var + eps) per (worker, channel).  grid (K, ceil(C/16)).
 __global__ __launch_bounds__(256) void bn_finalize_fwd_kernel(const double* __restrict__ partial, int C, int hw,
                                                               Segments seg, ShareTable tb, float* __restrict__ stats) {
-  __shared__ double red[4][64][2];
-  const int wk = blockIdx.x, c = blockIdx.y * 64 + (threadIdx.x & 63), sg = threadIdx.x >> 6;
+  __shared__ double red[kFinLanes][kFinChannels][2];
+  const int wk = blockIdx.x, c = blockIdx.y * kFinChannels + threadIdx.x % kFinChannels, sg = threadIdx.x / kFinChannels;
   double a, b;
   bn_sum_splits(partial, C, tb, wk, c, sg, red, a, b);
   if (sg != 0 || c >= C) return;
@@ -166,8 +170,8 @@ __global__ __launch_bounds__(256) void bn_finalize_bwd_kernel(const double* __re
                                                               Segments seg, ShareTable tb, float* __restrict__ means,
                                                               float* __restrict__ g_gamma, float* __restrict__ g_beta,
                                                               size_t worker_stride) {
-  __shared__ double red[4][64][2];
-  const int wk = blockIdx.x, c = blockIdx.y * 64 + (threadIdx.x & 63), sg = threadIdx.x >> 6;
+  __shared__ double red[kFinLanes][kFinChannels][2];
+  const int wk = blockIdx.x, c = blockIdx.y * kFinChannels + threadIdx.x % kFinChannels, sg = threadIdx.x / kFinChannels;
   double a, b;
   bn_sum_splits(partial, C, tb, wk, c, sg, red, a, b);
   if (sg != 0 || c >= C) return;
@@ -372,20 +376,34 @@ ShareTable deal_shares(const Segments& seg, long total) {
   return tb;
 }
 
-ShareTable bn_splits(const Segments& seg, int C) {
+// Splits of the statistics pass: about 2048 workgroups in all, every split `per` positions of one worker
+// (a multiple of the 128 positions of a trip), never more records than the scratch holds.
+ShareTable bn_splits(const Segments& seg, int C, int hw, int& per) {
   const int groups = (C + 63) / 64;
-  // about 2048 workgroups, never more splits than the scratch holds (K * kBnMaxSplits in all)
-  long total = std::max<long>(seg.K, 2048 / groups);
-  total = std::min<long>(total, (long)seg.K * (kBnMaxSplits - 2));
-  return deal_shares(seg, total);
+  const long positions = (long)seg.off[seg.K] * hw;
+  const long most = (long)seg.K * (kBnMaxSplits - 2);
+  long trips = std::max<long>(1, (positions * groups + 2048 * 64) / (2048L * 128));
+  while (positions / (128 * trips) + seg.K > most) ++trips;
+  per = (int)(128 * trips);
+  ShareTable tb{};
+  int acc = 0;
+  for (int k = 0; k < seg.K; ++k) {
+    tb.first[k] = acc;
+    acc += (int)(((long)(seg.off[k + 1] - seg.off[k]) * hw + per - 1) / per);
+  }
+  tb.first[seg.K] = acc;
+  return tb;
 }
 
 ShareTable bn_chunks(const Segments& seg, int C, int hw) {
   const long positions = (long)seg.off[seg.K] * hw;
   const int ppar = 256 / (C / 8);
-  // about 4096 workgroups, at least 8 trips each
-  long total = std::min<long>(4096, std::max<long>(seg.K, positions / (32L * ppar)));
-  return deal_shares(seg, total);
+  // At most about 4096 workgroups with at least eight trips each (a trip is four positions per thread) where
+  // there is that much; a smaller tensor is spread over up to 2048 workgroups, one trip being the least (128
+  // images of 32x32x64: 1024 workgroups 6 us, 128 with eight trips each 25 us).
+  const long trips = positions / (4L * ppar);
+  long total = std::min<long>(4096, std::max(trips / 8, std::min<long>(trips, 2048)));
+  return deal_shares(seg, std::max<long>(seg.K, total));
 }
 
 }  // namespace
@@ -395,12 +413,13 @@ bool bn_shape_supported(int C) { return C % 8 == 0 && C >= 8 && C <= 2048; }
 void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* gamma, const float* beta, int C, int hw,
                      const Segments& seg, bool relu, float* stats, double* partial, const bf16_t* skip,
                      bool relu_add, const ShareTable* presummed, uint8_t* sign_bits) {
-  const ShareTable sp = presummed ? *presummed : bn_splits(seg, C);
-  const int groups = (C + 63) / 64;
+  int per = 0;
+  const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
+  const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
   if (!presummed)
     hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(sp.first[seg.K], groups), dim3(256), 0, st, x, nullptr,
-                       nullptr, C, hw, seg, sp, partial);
-  hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, groups), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
+                       nullptr, C, hw, seg, sp, per, partial);
+  hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
   const ShareTable ch = bn_chunks(seg, C, hw);
   hipLaunchKernelGGL(bn_apply_kernel<false>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, nullptr, stats, nullptr,
                      gamma, beta, C, hw, seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
@@ -409,11 +428,12 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
                       const Segments& seg, const float* stats, float* means, double* partial, float* g_gamma,
                       float* g_beta, size_t worker_stride) {
-  const ShareTable sp = bn_splits(seg, C);
-  const int groups = (C + 63) / 64;
+  int per = 0;
+  const ShareTable sp = bn_splits(seg, C, hw, per);
+  const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
   hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(sp.first[seg.K], groups), dim3(256), 0, st, x, dy, stats, C, hw,
-                     seg, sp, partial);
-  hipLaunchKernelGGL(bn_finalize_bwd_kernel, dim3(seg.K, groups), dim3(256), 0, st, partial, C, hw, seg, sp, means,
+                     seg, sp, per, partial);
+  hipLaunchKernelGGL(bn_finalize_bwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, means,
                      g_gamma, g_beta, worker_stride);
   const ShareTable ch = bn_chunks(seg, C, hw);
   hipLaunchKernelGGL(bn_apply_kernel<true>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, dy, stats, means, gamma,
