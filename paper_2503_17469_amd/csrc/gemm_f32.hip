@@ -15,34 +15,37 @@
 // steps are staged through LDS with register prefetch of the next slab
 // (double-buffered LDS, one barrier per slab).
 //
-// Filling 256 compute units when the batch is small:
-//   * forward / dgrad split the reduction over gridDim.y workgroups per tile;
-//     each writes its partial tile, the last one to arrive (a per-tile counter)
-//     adds the partials in split order and runs the epilogue, so the sum order
-//     is fixed and results repeat bit for bit;
-//   * wgrad gives every workgroup one output tile position and lets it walk
-//     through ALL workers' row ranges one after the other, flushing the
-//     accumulator into worker k's gradient when k's rows end.  Every workgroup
-//     then does the same amount of work however ragged the b_k are.  The
-//     weight gradients of several layers can share one launch
-//     (linear_wgrad_f32_batch): their workgroups follow each other in one grid.
+// Products with too few tiles to fill the chip are those of gemm_f32_direct.hip and gemm_f32_small.hip.
+//
+// wgrad gives every workgroup one output tile position and lets it walk through
+// ALL workers' row ranges one after the other, flushing the accumulator into
+// worker k's gradient when k's rows end.  Every workgroup then does the same
+// amount of work however ragged the b_k are, and, holding all workers' gradients
+// of its tile in turn, it can apply the SGD update of the tile's parameters at
+// the end.  The weight gradients of all layers share one launch
+// (linear_wgrad_f32_batch): their workgroups follow each other in one grid.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
 #include <algorithm>
 
 #include "common.h"
+#include "head_device.h"
 #include "kernels.h"
+#include "update_device.h"
 
 namespace omni {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTile = 64;
+// Weight gradients come here with this many 64 x 64 tiles in the launch (one per compute unit), whatever the rows; fewer
+// go to gemm_f32_small.hip (its time against this kernel's: 164 tiles, 333 rows 16 / 21 us; 136 tiles, 1000 rows 31 / 39;
+// 1024 tiles, 32 rows 10.6 / 9.9, 480 rows 64 / 54).
+constexpr long kTiledWgradTiles = 256;
 
 // Staging of one operand slab: R rows x BK reduction steps.
 template <int R, int BK, bool MC>
@@ -55,82 +58,34 @@ struct Slab {
   static constexpr int kStride = MC ? (R + 8) : (BK + 4);
   static constexpr int kFloats = MC ? BK * (R + 8) : R * (BK + 4);
 
-  // Loads never branch: an element outside the operand is fetched from the
-  // operand's first element instead and zeroed when the slab is written to LDS
-  // (`ok` carries validity bits).  Branch-free loads let the compiler keep them
-  // in flight across the whole MFMA section of the current slab.
-  // VEC requires the contiguous extent (kk for k-contiguous, rows for
-  // row-contiguous operands) to be a multiple of 4 and 16-byte aligned rows, so a
-  // 4-element piece is either wholly inside or wholly outside (one bit per piece).
+  // Loads never branch, so that the compiler keeps them in flight across the whole MFMA section of the
+  // current slab.  Requires at least BK reduction steps and at least 4 rows in a row-contiguous operand; rows may start at
+  // any multiple of 4 bytes (16-byte loads need no more).  A row-contiguous piece that would run past the last
+  // row is moved back to end there: its place in the tile then holds other rows than its index says (piece_start).
   // Everything that does not change from slab to slab is worked out once per
   // thread (`Pre`): the per-slab address is one 64-bit add per piece.  The vector
   // ALU shares issue slots with the matrix pipe, so every instruction saved here
   // is matrix time gained.
   struct Pre {
-    int koff[kPerThread];     // reduction offset of the piece inside a slab
     long cpart[kPerThread];   // element offset of the piece for slab start 0
-    uint32_t rowok;           // bit i: the piece's rows lie inside the operand
   };
   __device__ static inline Pre prepare(int ld, int row0, int rows, int tid) {
     Pre pre;
-    pre.rowok = 0;
 #pragma unroll
     for (int i = 0; i < kPerThread; ++i) {
       const int c = tid + kThreads * i;
       if (!MC) {
         const int r = row0 + c / (BK / 4), kc = (c % (BK / 4)) * 4;
-        pre.koff[i] = kc + 3;
         pre.cpart[i] = r < rows ? (long)r * ld + kc : (long)kc;      // absent row: row 0 stands in
-        pre.rowok |= (r < rows ? 1u : 0u) << i;
       } else {
         const int kk = c / (R / 4), r = row0 + (c % (R / 4)) * 4;
-        pre.koff[i] = kk;
-        pre.cpart[i] = r + 3 < rows ? (long)kk * ld + r : (long)kk * ld;   // absent rows: rows 0..3 stand in
-        pre.rowok |= (r + 3 < rows ? 1u : 0u) << i;
+        pre.cpart[i] = (long)kk * ld + max(min(r, rows - 4), 0);
       }
     }
     return pre;
   }
 
-  template <bool VEC>
-  __device__ static inline void load(v4f (&reg)[kPerThread], uint32_t& ok, const float* __restrict__ base, int ld,
-                                     int row0, int rows, int k0, int kend, int tid, const Pre& pre) {
-    ok = 0;
-    if (VEC) {
-      const long kbase = MC ? (long)k0 * ld : (long)k0;
-      const int klen = kend - k0;
-#pragma unroll
-      for (int i = 0; i < kPerThread; ++i) {
-        const bool in = ((pre.rowok >> i) & 1u) && pre.koff[i] < klen;
-        reg[i] = *reinterpret_cast<const v4f*>(base + (in ? pre.cpart[i] + kbase : 0));
-        ok |= (in ? 1u : 0u) << i;
-      }
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) {
-      const int c = tid + kThreads * i;
-      int gr, gk;
-      if (!MC) {
-        gr = row0 + c / (BK / 4);
-        gk = k0 + (c % (BK / 4)) * 4;
-      } else {
-        gk = k0 + c / (R / 4);
-        gr = row0 + (c % (R / 4)) * 4;
-      }
-      v4f v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool in = MC ? (gk < kend && gr + e < rows) : (gr < rows && gk + e < kend);
-        const size_t o = MC ? (size_t)gk * ld + gr + e : (size_t)gr * ld + gk + e;
-        v[e] = base[in ? o : 0];
-        ok |= (in ? 1u : 0u) << (4 * i + e);
-      }
-      reg[i] = v;
-    }
-  }
-
-  // The mask-free form used with VEC.  A slab whose BK reduction steps all lie inside the
+  // A slab whose BK reduction steps all lie inside the
   // range is loaded as it is.  A slab that would run past the end of its range is moved
   // back so that it ENDS at the end of the range (start ks = max(kend - BK, 0): the caller
   // guarantees at least BK reduction steps in the operand, so this stays in bounds); the
@@ -142,7 +97,7 @@ struct Slab {
                                           const Pre& pre) {
     const float* sbase = base + (MC ? (long)ks * ld : (long)ks);
 #pragma unroll
-    for (int i = 0; i < kPerThread; ++i) reg[i] = *reinterpret_cast<const v4f*>(sbase + pre.cpart[i]);
+    for (int i = 0; i < kPerThread; ++i) reg[i] = *reinterpret_cast<const v4f_a4*>(sbase + pre.cpart[i]);
   }
   __device__ static inline void store_fast(const v4f (&reg)[kPerThread], float* lds, int tid, int i) {
     const int c = tid + kThreads * i;
@@ -163,33 +118,8 @@ struct Slab {
     }
   }
 
-  // piece i of the thread's share of the slab
-  template <bool VEC>
-  __device__ static inline void store_one(const v4f (&reg)[kPerThread], uint32_t ok, float* lds, int tid, int i) {
-    const int c = tid + kThreads * i;
-    v4f v = reg[i];
-    if (VEC) {
-      const bool in = (ok >> i) & 1u;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : 0.f;
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = ((ok >> (4 * i + e)) & 1u) ? v[e] : 0.f;
-    }
-    if (!MC) {
-      const int r = c / (BK / 4), kc = (c % (BK / 4)) * 4;
-      *reinterpret_cast<v4f*>(lds + r * kStride + kc) = v;
-    } else {
-      const int kk = c / (R / 4), rc = (c % (R / 4)) * 4;
-      *reinterpret_cast<v4f*>(lds + kk * kStride + rc) = v;
-    }
-  }
-
-  template <bool VEC>
-  __device__ static inline void store(const v4f (&reg)[kPerThread], uint32_t ok, float* lds, int tid) {
-#pragma unroll
-    for (int i = 0; i < kPerThread; ++i) store_one<VEC>(reg, ok, lds, tid, i);
-  }
+  // First operand row of the four-row piece that tile index i belongs to (row-contiguous operands, see above).
+  __device__ static inline int piece_start(int row0, int i, int rows) { return min(row0 + (i & ~3), rows - 4); }
 
   // Operand registers for the 4 MFMA steps covering kk = ks*8 .. ks*8+7 of the
   // slab, for the 32-row block starting at `row`.  Lane l supplies row l%32 and
@@ -210,6 +140,12 @@ struct Slab {
 
 enum { MODE_FWD = 0, MODE_DGRAD = 1, MODE_WGRAD = 2 };
 
+// LDS of one workgroup, in floats: two stages of both slabs and, for WGRAD, the bias-gradient partial sums.
+template <int BK, bool A_MC, bool B_MC, int MODE>
+constexpr int gemm_lds_floats() {
+  return 2 * (Slab<kTile, BK, A_MC>::kFloats + Slab<kTile, BK, B_MC>::kFloats) + (MODE == MODE_WGRAD ? 4 * kTile : 0);
+}
+
 struct GemmParams {
   const float* A;
   const float* B;
@@ -222,30 +158,29 @@ struct GemmParams {
   int relu;            // FWD
   int accumulate;      // DGRAD: C += result
   int xcd_remap;       // FWD / DGRAD: 1 if the workgroups are re-ordered per XCD
-  int splits;          // FWD / DGRAD: reduction splits per tile
-  float* partial;      // FWD / DGRAD split-K: [tiles][splits][16][256] floats
-  uint32_t* counters;  // FWD / DGRAD split-K: one per tile, zero between launches
   size_t c_worker_stride;  // WGRAD: floats between consecutive workers' outputs
   float* bias_grad;        // WGRAD: per worker column sums of A (at + worker*c_worker_stride), may be null
-  int c_vec;               // WGRAD: every worker's output rows are 16-byte aligned (16-byte stores allowed)
-  int ngroups;             // WGRAD: consecutive workers are dealt to this many workgroups per tile (gridDim.y)
-  int gfirst[9];           // WGRAD: first worker of every group; gfirst[ngroups] = K
+  float* theta;            // WGRAD with the update: this layer's weights and bias (and velocities), null without
+  float* theta_bias;
+  float* velocity;
+  float* velocity_bias;
 };
 
 // (The second launch bound caps the kernel at 256 registers: the compiler then issues the MFMAs on
 // ordinary vector registers.  With accumulation registers it copied all 32 accumulator registers in
 // and out around the MFMAs of every step, 64 extra vector instructions per 16 MFMAs, because the
 // per-worker flush inside the loop reads and zeroes them.)
-// The whole workgroup program; (bx, by) is the workgroup's place in a launch of nbx workgroups along x.
-template <int BK, bool A_MC, bool B_MC, int MODE, bool VEC>
-__device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segments& seg, const int bx, const int by,
-                                              const int nbx) {
+// The whole workgroup program; bx is the workgroup's place among nbx workgroups.
+// UPD (WGRAD): 1 / 2 if the workgroups, having walked through ALL workers, also apply the SGD / momentum update to
+// the parameters of their tile (lam, opt).
+template <int BK, bool A_MC, bool B_MC, int MODE, int UPD>
+__device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segments& seg, const int bx, const int nbx, float* lds,
+                                              const Lambdas* lam = nullptr, const Optim* opt = nullptr) {
   using SA = Slab<kTile, BK, A_MC>;
   using SB = Slab<kTile, BK, B_MC>;
   constexpr int kStage = SA::kFloats + SB::kFloats;
-  __shared__ __attribute__((aligned(16))) float lds[2 * kStage];
-  __shared__ uint32_t arrival;
-  __shared__ float bred[4][kTile];                 // WGRAD: the four wavefronts' bias-gradient partial sums
+  // WGRAD: the four wavefronts' bias-gradient partial sums
+  float (*bred)[kTile] = reinterpret_cast<float (*)[kTile]>(lds + 2 * kStage);
   constexpr int kFlushStride = kTile + 4;          // WGRAD: row stride of the output tile staged for the flush
   static_assert(kTile * kFlushStride <= kStage, "the staged output tile must fit one LDS stage");
   auto sA = [&](int stage) { return lds + stage * kStage; };
@@ -254,23 +189,10 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tiles_n = (p.N + kTile - 1) / kTile;
   const int tiles_m = (p.M + kTile - 1) / kTile;
-  int tile = bx, split = 0;
-  const int splits = (MODE == MODE_WGRAD) ? 1 : p.splits;
-  if (MODE != MODE_WGRAD) {
-    // Forward / dgrad launch tiles*splits workgroups in one dimension.  They are
-    // dealt to the 8 XCDs round-robin by index; re-order them so that each XCD
-    // owns a contiguous run of (split, tile) pairs, split-major: an XCD then
-    // works on ONE slice of the reduction, and that slice of both operands
-    // (a few MB) stays in its own L2 while all its tiles sweep over it.
-    int g = bx;
-    if (p.xcd_remap) {
-      const int per = nbx >> 3;
-      g = (bx & 7) * per + (bx >> 3);
-    }
-    const int tiles = tiles_m * tiles_n;
-    split = g / tiles;
-    tile = g - split * tiles;
-  }
+  int tile = bx;
+  // Forward / dgrad workgroups are dealt to the 8 XCDs round-robin by index; re-ordered so that each XCD owns a
+  // contiguous run of tiles, whose columns of B its own L2 then holds.
+  if (MODE != MODE_WGRAD && p.xcd_remap) tile = (bx & 7) * (nbx >> 3) + (bx >> 3);
   // tile_n major: consecutive tiles share the same rows of B
   const int tile_n = (MODE == MODE_WGRAD) ? tile % tiles_n : tile / tiles_m;
   const int tile_m = (MODE == MODE_WGRAD) ? tile / tiles_n : tile % tiles_m;
@@ -280,17 +202,14 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   // The reduction is a stream of slabs over one or more consecutive ranges
   // ("workers"); the accumulator is flushed whenever a range ends.  A slab is
   // (range index w, start k0, end of its range kend); w == nrange marks the end.
-  const int nrange = (MODE == MODE_WGRAD) ? p.gfirst[by + 1] : 1;
+  const int nrange = (MODE == MODE_WGRAD) ? seg.K : 1;
   int w0 = 0, k00, kend0;
   if (MODE == MODE_WGRAD) {
-    w0 = p.gfirst[by];
-    k00 = seg.off[w0];
-    kend0 = seg.off[w0 + 1];
+    k00 = seg.off[0];
+    kend0 = seg.off[1];
   } else {
-    const int slabs = (p.kred + BK - 1) / BK;
-    const int per = (slabs + splits - 1) / splits;
-    k00 = min(split * per * BK, p.kred);
-    kend0 = min((split + 1) * per * BK, p.kred);
+    k00 = 0;
+    kend0 = p.kred;
   }
 #define OMNI_NEXT_SLAB(W, K0, KEND, NW, NK0, NKEND)       \
   int NW = W, NK0 = K0 + BK, NKEND = KEND;                \
@@ -302,10 +221,18 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     }                                                     \
   }
 
-  // Two accumulator chains (even / odd reduction steps) keep consecutive MFMAs independent.
+  // Two accumulator chains (even / odd reduction steps) keep consecutive MFMAs independent.  WGRAD runs four
+  // wavefronts per SIMD, which hide the dependence, and uses the second set of registers for gsum.
+  constexpr bool kTwo = MODE != MODE_WGRAD;
   v16f acc, acc2;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = acc2[v] = 0.f;
+  // WGRAD with the update: sum_k lambda_k G[k] of the 16-byte pieces this thread stores, in the order of the update
+  // kernel, so that the gradient rows are never fetched again
+  v4f gsum[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) gsum[q] = v4f{0.f, 0.f, 0.f, 0.f};
+  float bgsum = 0.f;
   const bool want_bias_grad = (MODE == MODE_WGRAD) && p.bias_grad != nullptr && tile_n == 0;
   float bsum = 0.f;
 
@@ -319,7 +246,6 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   const typename SA::Pre preA = SA::prepare(p.lda, row0, p.M, tid);
   const typename SB::Pre preB = SB::prepare(p.ldb, col0, p.N, tid);
   v4f ra0[SA::kPerThread], rb0[SB::kPerThread], ra1[SA::kPerThread], rb1[SB::kPerThread];
-  uint32_t oka0 = 0, okb0 = 0, oka1 = 0, okb1 = 0;
   OMNI_NEXT_SLAB(w0, k00, kend0, w1, k01, kend1)
   // start of the slab as it is fetched (see Slab::load_fast)
 #define OMNI_KSTART(K0, KEND) ((K0) + BK <= (KEND) ? (K0) : max((KEND) - BK, 0))
@@ -327,28 +253,19 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   // first slab and are discarded): a load that is issued on one path only would force
   // every later wait to assume it is not there and drain the whole queue.
   if (w1 >= nrange) { k01 = 0; kend1 = 0; }
-  if (VEC) {
-    SA::load_fast(ra0, p.A, p.lda, OMNI_KSTART(k00, kend0), preA);
-    SB::load_fast(rb0, p.B, p.ldb, OMNI_KSTART(k00, kend0), preB);
-    SA::load_fast(ra1, p.A, p.lda, OMNI_KSTART(k01, kend1), preA);
-    SB::load_fast(rb1, p.B, p.ldb, OMNI_KSTART(k01, kend1), preB);
+  SA::load_fast(ra0, p.A, p.lda, OMNI_KSTART(k00, kend0), preA);
+  SB::load_fast(rb0, p.B, p.ldb, OMNI_KSTART(k00, kend0), preB);
+  SA::load_fast(ra1, p.A, p.lda, OMNI_KSTART(k01, kend1), preA);
+  SB::load_fast(rb1, p.B, p.ldb, OMNI_KSTART(k01, kend1), preB);
 #pragma unroll
-    for (int i = 0; i < SA::kPerThread; ++i) SA::store_fast(ra0, sA(0), tid, i);
+  for (int i = 0; i < SA::kPerThread; ++i) SA::store_fast(ra0, sA(0), tid, i);
 #pragma unroll
-    for (int i = 0; i < SB::kPerThread; ++i) SB::store_fast(rb0, sB(0), tid, i);
-    if (k00 + BK > kend0) {
-      const int ks = OMNI_KSTART(k00, kend0);
-      __syncthreads();
-      SA::zero_outside(sA(0), k00 - ks, kend0 - ks, tid);
-      SB::zero_outside(sB(0), k00 - ks, kend0 - ks, tid);
-    }
-  } else {
-    SA::template load<VEC>(ra0, oka0, p.A, p.lda, row0, p.M, k00, kend0, tid, preA);
-    SB::template load<VEC>(rb0, okb0, p.B, p.ldb, col0, p.N, k00, kend0, tid, preB);
-    SA::template load<VEC>(ra1, oka1, p.A, p.lda, row0, p.M, k01, kend1, tid, preA);
-    SB::template load<VEC>(rb1, okb1, p.B, p.ldb, col0, p.N, k01, kend1, tid, preB);
-    SA::template store<VEC>(ra0, oka0, sA(0), tid);
-    SB::template store<VEC>(rb0, okb0, sB(0), tid);
+  for (int i = 0; i < SB::kPerThread; ++i) SB::store_fast(rb0, sB(0), tid, i);
+  if (k00 + BK > kend0) {
+    const int ks = OMNI_KSTART(k00, kend0);
+    __syncthreads();
+    SA::zero_outside(sA(0), k00 - ks, kend0 - ks, tid);
+    SB::zero_outside(sB(0), k00 - ks, kend0 - ks, tid);
   }
   __syncthreads();
 
@@ -356,7 +273,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   // copies of the step, so that every LDS address is an immediate offset), fetch the
   // slab two ahead into the free register set (LA/LB), then move the slab one
   // ahead from its register set (NA/NB) into the other LDS stage.
-#define OMNI_STEP(CUR, LA, LB, LOKA, LOKB, NA, NB, NOKA, NOKB)                                               \
+#define OMNI_STEP(CUR, LA, LB, NA, NB)                                                               \
   {                                                                                                     \
     int w2 = nrange, k02 = 0, kend2 = 0;                                                                \
     if (w1 < nrange) {                                                                                  \
@@ -364,13 +281,10 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
       w2 = tw; k02 = tk0; kend2 = tkend;                                                                \
     }                                                                                                   \
     if (w2 >= nrange) { k02 = 0; kend2 = 0; }                                                           \
-    if (VEC) {                                                                                          \
+    {                                                                                                   \
       const int ks2 = OMNI_KSTART(k02, kend2);                                                          \
       SA::load_fast(LA, p.A, p.lda, ks2, preA);                                                         \
       SB::load_fast(LB, p.B, p.ldb, ks2, preB);                                                         \
-    } else {                                                                                            \
-      SA::template load<VEC>(LA, LOKA, p.A, p.lda, row0, p.M, k02, kend2, tid, preA);                    \
-      SB::template load<VEC>(LB, LOKB, p.B, p.ldb, col0, p.N, k02, kend2, tid, preB);                    \
     }                                                                                                   \
     __builtin_amdgcn_sched_barrier(0); /* keep the fetches ahead of the MFMA section */                 \
     /* The slab one step ahead has been in flight for a whole step: its pieces go to the other LDS */  \
@@ -386,21 +300,17 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
           fb[(ks + 1) & 1] = SB::frag(sB(CUR), wcol, ks + 1, lane);                                     \
         }                                                                                               \
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][0], fb[ks & 1][0], acc, 0, 0, 0);         \
-        acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][1], fb[ks & 1][1], acc2, 0, 0, 0);       \
+        if (kTwo) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][1], fb[ks & 1][1], acc2, 0, 0, 0); \
+        else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][1], fb[ks & 1][1], acc, 0, 0, 0);    \
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][2], fb[ks & 1][2], acc, 0, 0, 0);         \
-        acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][3], fb[ks & 1][3], acc2, 0, 0, 0);       \
-        if (VEC) {                                                                                      \
-          if (ks < SA::kPerThread) SA::store_fast(NA, sA(1 - CUR), tid, ks);                            \
-          else if (ks - SA::kPerThread < SB::kPerThread) SB::store_fast(NB, sB(1 - CUR), tid, ks - SA::kPerThread); \
-        } else {                                                                                        \
-          if (ks < SA::kPerThread) SA::template store_one<VEC>(NA, NOKA, sA(1 - CUR), tid, ks);         \
-          else if (ks - SA::kPerThread < SB::kPerThread)                                                \
-            SB::template store_one<VEC>(NB, NOKB, sB(1 - CUR), tid, ks - SA::kPerThread);               \
-        }                                                                                               \
+        if (kTwo) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][3], fb[ks & 1][3], acc2, 0, 0, 0); \
+        else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][3], fb[ks & 1][3], acc, 0, 0, 0);    \
+        if (ks < SA::kPerThread) SA::store_fast(NA, sA(1 - CUR), tid, ks);                              \
+        else if (ks - SA::kPerThread < SB::kPerThread) SB::store_fast(NB, sB(1 - CUR), tid, ks - SA::kPerThread); \
         __builtin_amdgcn_sched_barrier(0);                                                              \
       }                                                                                                 \
     }                                                                                                   \
-    if (VEC && w1 < nrange && k01 + BK > kend1) {                                                       \
+    if (w1 < nrange && k01 + BK > kend1) {                                                              \
       /* the slab just staged runs past the end of its range: it was fetched moved back; clear the */  \
       /* reduction steps that are not its own (once per range; all its pieces must have landed)     */  \
       const int ks1 = OMNI_KSTART(k01, kend1);                                                          \
@@ -417,38 +327,29 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     if (MODE == MODE_WGRAD && w1 != w0) {                                                               \
       /* this worker's rows are done: its tile goes out (stores only; the prefetch stays in flight) */ \
       float* C = p.C + (size_t)w0 * p.c_worker_stride;                                                  \
-      if (VEC && p.c_vec) {                                                                             \
-        /* through the LDS stage that was just multiplied, so that every thread writes 16-byte pieces */ \
-        /* of whole 256-byte rows (scattered 4-byte stores, 16 per lane, cost 3 us per launch)        */ \
-        float* tile = sA(CUR);                                                                          \
-        __syncthreads(); /* every wavefront is done reading this stage */                               \
-        _Pragma("unroll") for (int v = 0; v < 16; ++v)                                                  \
-          tile[(wrow + 4 * (lane >> 5) + 8 * (v / 4) + (v % 4)) * kFlushStride + wcol + (lane & 31)] = acc[v] + acc2[v]; \
-        if (want_bias_grad) bred[wave][lane] = bsum;                                                    \
-        __syncthreads();                                                                                \
-        _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                 \
-          const int idx = tid + kThreads * q, r = idx >> 4, c4 = (idx & 15) * 4;                         \
-          if (row0 + r < p.M && col0 + c4 < p.N)                                                        \
-            *reinterpret_cast<v4f*>(C + (size_t)(row0 + r) * p.ldc + col0 + c4) =                       \
-                *reinterpret_cast<const v4f*>(tile + r * kFlushStride + c4);                            \
-        }                                                                                               \
-      } else {                                                                                          \
-        if (j < p.N) {                                                                                  \
-          _Pragma("unroll") for (int v = 0; v < 16; ++v) {                                              \
-            const int i = ibase + 8 * (v / 4) + (v % 4);                                                \
-            if (i < p.M) C[(size_t)i * p.ldc + j] = acc[v] + acc2[v];                                   \
-          }                                                                                             \
-        }                                                                                               \
-        if (want_bias_grad) {                                                                           \
-          bred[wave][lane] = bsum;                                                                      \
-          __syncthreads();                                                                              \
-        }                                                                                               \
+      /* through the LDS stage that was just multiplied, so that every thread writes 16-byte pieces */   \
+      /* of whole 256-byte rows (scattered 4-byte stores, 16 per lane, cost 3 us per launch).  A piece */ \
+      /* moved back at the edge of the matrix writes a few elements a second time, with the same values. */ \
+      float* tile = sA(CUR);                                                                            \
+      __syncthreads(); /* every wavefront is done reading this stage */                                 \
+      _Pragma("unroll") for (int v = 0; v < 16; ++v)                                                    \
+        tile[(wrow + 4 * (lane >> 5) + 8 * (v / 4) + (v % 4)) * kFlushStride + wcol + (lane & 31)] = acc[v]; \
+      if (want_bias_grad) bred[wave][lane] = bsum;                                                      \
+      __syncthreads();                                                                                  \
+      _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                   \
+        const int idx = tid + kThreads * q, r = idx >> 4, c4 = (idx & 15) * 4;                          \
+        const v4f t = *reinterpret_cast<const v4f*>(tile + r * kFlushStride + c4);                      \
+        *reinterpret_cast<v4f_a4*>(C + (size_t)(SA::piece_start(row0, r, p.M) + (r & 3)) * p.ldc +      \
+                                   SB::piece_start(col0, c4, p.N)) = t;                                 \
+        if (UPD) gsum[q] += lam->v[w0] * t;                                                             \
       }                                                                                                 \
-      if (want_bias_grad && tid < kTile && row0 + tid < p.M)                                            \
-        p.bias_grad[(size_t)w0 * p.c_worker_stride + row0 + tid] =                                      \
-            ((bred[0][tid] + bred[1][tid]) + bred[2][tid]) + bred[3][tid];                              \
+      if (want_bias_grad && tid < kTile) {                                                              \
+        const float t = ((bred[0][tid] + bred[1][tid]) + bred[2][tid]) + bred[3][tid];                  \
+        p.bias_grad[(size_t)w0 * p.c_worker_stride + SA::piece_start(row0, tid, p.M) + (tid & 3)] = t;  \
+        if (UPD) bgsum += lam->v[w0] * t;                                                               \
+      }                                                                                                 \
       bsum = 0.f;                                                                                       \
-      _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[v] = acc2[v] = 0.f;                            \
+      _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[v] = 0.f;                                      \
     }                                                                                                   \
     if (w1 >= nrange) break;                                                                            \
     __syncthreads();                                                                                    \
@@ -456,54 +357,55 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     w1 = w2; k01 = k02; kend1 = kend2;                                                                  \
   }
   for (;;) {
-    OMNI_STEP(0, ra0, rb0, oka0, okb0, ra1, rb1, oka1, okb1)
-    OMNI_STEP(1, ra1, rb1, oka1, okb1, ra0, rb0, oka0, okb0)
+    OMNI_STEP(0, ra0, rb0, ra1, rb1)
+    OMNI_STEP(1, ra1, rb1, ra0, rb0)
   }
 #undef OMNI_STEP
 #undef OMNI_NEXT_SLAB
 #undef OMNI_KSTART
 
+  if (MODE == MODE_WGRAD && UPD != 0) {
+    constexpr bool MOM = UPD == 2;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int idx = tid + kThreads * q, r = idx >> 4, c4 = (idx & 15) * 4;
+      const int rs = SA::piece_start(row0, r, p.M), cs = SB::piece_start(col0, c4, p.N);
+      const size_t e0 = (size_t)(rs + (r & 3)) * p.ldc + cs;
+      v4f th = *reinterpret_cast<const v4f_a4*>(p.theta + e0), vel = {0.f, 0.f, 0.f, 0.f};
+      if (MOM) vel = *reinterpret_cast<const v4f_a4*>(p.velocity + e0);
+      apply_update<MOM>(th, vel, gsum[q], *opt);
+      if (rs + (r & 3) < row0 + (r & ~3)) continue;      // this row belongs to the piece before it
+      if (cs == col0 + c4) {
+        *reinterpret_cast<v4f_a4*>(p.theta + e0) = th;
+        if (MOM) *reinterpret_cast<v4f_a4*>(p.velocity + e0) = vel;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (cs + e >= col0 + c4) {
+            p.theta[e0 + e] = th[e];
+            if (MOM) p.velocity[e0 + e] = vel[e];
+          }
+      }
+    }
+    if (want_bias_grad && tid < kTile) {
+      const int i = SA::piece_start(row0, tid, p.M) + (tid & 3);
+      if (i >= row0 + (tid & ~3)) {
+        float th = p.theta_bias[i], vel = MOM ? p.velocity_bias[i] : 0.f;
+        apply_update<MOM>(th, vel, bgsum, *opt);
+        p.theta_bias[i] = th;
+        if (MOM) p.velocity_bias[i] = vel;
+      }
+    }
+  }
   if (MODE != MODE_WGRAD) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] += acc2[v];
-    bool finish = true;
-    if (splits > 1) {
-      // Park this split's partial tile; whoever arrives last adds them up.  The
-      // splits of a tile may run on different XCDs, whose L2s are not coherent
-      // with each other inside a kernel.  The partial tiles therefore travel
-      // through device-scope stores and loads (they bypass the XCD-private L2);
-      // every thread drains its own stores, the barrier collects the workgroup,
-      // and ONE wavefront then executes the device-scope release (an L2
-      // write-back: done by all four wavefronts, or paired with an acquire that
-      // invalidates the L2 under everybody else's feet, it cost 25 % of the
-      // step) before one thread bumps the tile's arrival counter.  Without that
-      // release the counter could overtake the data (seen as rare wrong tiles).
-      float* mine = p.partial + ((size_t)tile * splits + split) * (16 * kThreads);
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        __hip_atomic_store(mine + v * kThreads + tid, acc[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      __syncthreads();
-      if (wave == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        if (tid == 0)
-          arrival = __hip_atomic_fetch_add(&p.counters[tile], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      __syncthreads();
-      finish = (arrival == (uint32_t)splits - 1);
-      if (finish) {
-        const float* all = p.partial + (size_t)tile * splits * (16 * kThreads);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        for (int s = 0; s < splits; ++s)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            acc[v] += __hip_atomic_load(all + ((size_t)s * 16 + v) * kThreads + tid, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-        if (tid == 0) p.counters[tile] = 0u;   // ready for the next launch
-      }
-    }
-    if (finish && j < p.N) {
+    // dgrad: the column that sits at this lane's place in the tile; of a piece moved back, the columns that an
+    // earlier piece also holds are left to that one
+    const int jt = wcol + (lane & 31);
+    const int jc = B_MC ? SB::piece_start(col0, jt, p.N) + (jt & 3) : j;
+    const bool jok = B_MC ? jc >= col0 + (jt & ~3) : j < p.N;
+    if (jok) {
       float bj = 0.f;
       if (MODE == MODE_FWD && p.bias) bj = p.bias[j];
 #pragma unroll
@@ -511,7 +413,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
         const int i = ibase + 8 * (v / 4) + (v % 4);
         if (i >= p.M) continue;
         float val = acc[v];
-        const size_t idx = (size_t)i * p.ldc + j;
+        const size_t idx = (size_t)i * p.ldc + jc;
         if (MODE == MODE_FWD) {
           val += bj;
           if (p.relu) val = val > 0.f ? val : 0.f;
@@ -525,165 +427,168 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   }
 }
 
-template <int BK, bool A_MC, bool B_MC, int MODE, bool VEC>
-__global__ __launch_bounds__(kThreads, MODE == MODE_WGRAD ? 3 : 2) void gemm_f32_kernel(GemmParams p, Segments seg) {
-  gemm_f32_body<BK, A_MC, B_MC, MODE, VEC>(p, seg, (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x);
+template <int BK, bool A_MC, bool B_MC, int MODE>
+__global__ __launch_bounds__(kThreads, 2) void gemm_f32_kernel(GemmParams p) {
+  __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<BK, A_MC, B_MC, MODE>()];
+  gemm_f32_body<BK, A_MC, B_MC, MODE, 0>(p, Segments{}, (int)blockIdx.x, (int)gridDim.x, lds);
+}
+
+// An input gradient and, behind its tiles, the classifier's parameter gradients and losses (see HeadWgradParams): the
+// head's workgroups wait for memory most of the time and run beside the product's.
+__global__ __launch_bounds__(kThreads, 2) void gemm_f32_dgrad_head_kernel(GemmParams p, int tiles, HeadWgradParams h,
+                                                                          int head_gx, Segments seg) {
+  constexpr int kGemm = gemm_lds_floats<32, false, true, MODE_DGRAD>();
+  __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
+  if ((int)blockIdx.x < tiles) {
+    gemm_f32_body<32, false, true, MODE_DGRAD, 0>(p, seg, (int)blockIdx.x, tiles, lds);
+  } else {
+    const int hb = (int)blockIdx.x - tiles;
+    head_wgrad_loss_body<float>(h, seg, hb % head_gx, hb / head_gx, lds);
+  }
 }
 
 // Weight gradients of several layers in ONE launch: the workgroups of the problems follow each other
-// along x (problem i owns start[i] .. start[i+1]-1, tiles fastest, then worker groups).  A launch
+// along x (problem i owns start[i] .. start[i+1]-1, one per tile).  A launch
 // has a start-up and a drain during which the matrix pipes idle; run together, one problem's
-// workgroups start while another's finish.
+// workgroups start while another's finish.  With the update, the workgroups behind the last tile update the
+// classifier's parameters, whose gradients an earlier launch has left in G.
+// Four workgroups per compute unit: 1024 tiles (the 3072-1024-1024 net) are then resident at once; with three, the
+// last quarter of them ran by itself, one wavefront per SIMD (61 against 53 us at 480 rows).
 constexpr int kMaxBatch = 8;
 struct WgradBatch {
   int n;
   int start[kMaxBatch + 1];
+  size_t worker_stride;
+  long head_n;                 // classifier: parameters, where they start, and worker 0's gradients of them
+  float* head_theta;
+  float* head_velocity;
+  const float* head_grad;
   GemmParams prob[kMaxBatch];
 };
 
-template <int BK, bool VEC>
-__global__ __launch_bounds__(kThreads, 3) void gemm_f32_wgrad_batch_kernel(WgradBatch b, Segments seg) {
+template <int BK, int UPD>
+__global__ __launch_bounds__(kThreads, 4) void gemm_f32_wgrad_batch_kernel(WgradBatch b, Segments seg, Lambdas lam,
+                                                                           Optim opt) {
+  __shared__ __attribute__((aligned(16))) float lds[gemm_lds_floats<BK, true, true, MODE_WGRAD>()];
+  if (UPD != 0 && (int)blockIdx.x >= b.start[b.n]) {
+    const long j = (long)((int)blockIdx.x - b.start[b.n]) * kThreads + threadIdx.x;
+    if (j >= b.head_n) return;
+    float g = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < seg.K; ++k) g += lam.v[k] * b.head_grad[(size_t)k * b.worker_stride + j];
+    float th = b.head_theta[j], ve = UPD == 2 ? b.head_velocity[j] : 0.f;
+    apply_update<UPD == 2>(th, ve, g, opt);
+    b.head_theta[j] = th;
+    if (UPD == 2) b.head_velocity[j] = ve;
+    return;
+  }
   int pi = 0;
   for (int i = 1; i < b.n; ++i)
     if ((int)blockIdx.x >= b.start[i]) pi = i;
   const GemmParams& p = b.prob[pi];
   const int local = (int)blockIdx.x - b.start[pi];
   const int tiles = ((p.M + kTile - 1) / kTile) * ((p.N + kTile - 1) / kTile);
-  const int by = local / tiles;
-  gemm_f32_body<BK, true, true, MODE_WGRAD, VEC>(p, seg, local - by * tiles, by, tiles);
+  gemm_f32_body<BK, true, true, MODE_WGRAD, UPD>(p, seg, local, tiles, lds, &lam, &opt);
 }
 
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-// Deals the workers of a weight-gradient problem to workgroups per tile (p.gfirst, p.ngroups):
-// with few tiles, groups of consecutive workers with about equal row counts (each worker stays
-// whole, so nothing is summed across workgroups).  `want` is the number of workgroups to aim for.
-int plan_worker_groups(GemmParams& p, const Segments& seg, int tiles, int want) {
-  int G = tiles >= want ? 1 : std::min(std::min(8, seg.K), (want + tiles - 1) / tiles);
-  const int B = seg.off[seg.K];
-  p.gfirst[0] = 0;
-  int g = 1;
-  for (int w = 1; w < seg.K && g < G; ++w) {
-    // start group g at the first worker whose start reaches g/G of the rows (keeping every later group non-empty)
-    if ((long)seg.off[w] * G >= (long)g * B || seg.K - w <= G - g) p.gfirst[g++] = w;
-  }
-  G = g;
-  p.gfirst[G] = seg.K;
-  p.ngroups = G;
-  return G;
-}
-
-template <int BK, bool A_MC, bool B_MC, int MODE>
-void launch(hipStream_t st, GemmParams& p, const Segments& seg, int splits, bool vec) {
+template <bool A_MC, bool B_MC, int MODE>
+void launch(hipStream_t st, GemmParams& p) {
   const int tiles = ((p.M + kTile - 1) / kTile) * ((p.N + kTile - 1) / kTile);
-  p.splits = splits;
-  p.xcd_remap = (MODE != MODE_WGRAD && (tiles * splits) % 8 == 0) ? 1 : 0;
-  dim3 grid(tiles * splits, 1, 1);
-  if (MODE == MODE_WGRAD) grid = dim3(tiles, plan_worker_groups(p, seg, tiles, 512), 1);
-  if (vec)
-    hipLaunchKernelGGL((gemm_f32_kernel<BK, A_MC, B_MC, MODE, true>), grid, dim3(kThreads), 0, st, p, seg);
-  else
-    hipLaunchKernelGGL((gemm_f32_kernel<BK, A_MC, B_MC, MODE, false>), grid, dim3(kThreads), 0, st, p, seg);
+  p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
+  hipLaunchKernelGGL((gemm_f32_kernel<32, A_MC, B_MC, MODE>), dim3(tiles), dim3(kThreads), 0, st, p);
 }
 
-// Number of reduction splits that brings a forward / dgrad launch to roughly two
-// workgroups per compute unit, never leaving a split without at least 4 slabs.
-int pick_splits(int tiles, int kred, int bk, const SplitWorkspace& sw) {
-  if (!sw.partial || !sw.counters || tiles > kSplitMaxTiles) return 1;
-  int s = (512 + tiles - 1) / tiles;
-  const int slabs = (kred + bk - 1) / bk;
-  s = std::min(s, std::max(1, slabs / 4));
-  s = std::min(s, 16);
-  while (s > 1 && (size_t)tiles * s * 16 * kThreads > kSplitPartialFloats) --s;
-  // every split must own at least one slab
-  while (s > 1 && ((slabs + s - 1) / s) * (s - 1) >= slabs) --s;
-  return std::max(s, 1);
-}
+int gemm_tiles(int rows, int cols) { return ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile); }
 
 }  // namespace
 
-static int gemm_tiles(int rows, int cols) { return ((rows + kTile - 1) / kTile) * ((cols + kTile - 1) / kTile); }
-
 void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
-                    int rows, int cin, int cout, bool relu, const SplitWorkspace& sw) {
+                    int rows, int cin, int cout, bool relu) {
   if (linear_fwd_f32_direct(st, x, w, bias, y, rows, cin, cout, relu)) return;
+  if (linear_f32_small(rows, cout, cin)) {
+    linear_fwd_f32_small(st, x, w, bias, y, rows, cin, cout, relu);
+    return;
+  }
   GemmParams p{};
   p.A = x; p.B = w; p.C = y; p.M = rows; p.N = cout; p.lda = cin; p.ldb = cin; p.ldc = cout;
   p.kred = cin; p.bias = bias; p.relu = relu ? 1 : 0;
-  p.partial = sw.partial; p.counters = sw.counters;
-  Segments seg{};
-  // both operands k-contiguous; the mask-free loads need at least one whole slab of reduction steps
-  const bool vec = aligned16(x) && aligned16(w) && (cin % 4 == 0) && cin >= 32;
-  launch<32, false, false, MODE_FWD>(st, p, seg, pick_splits(gemm_tiles(rows, cout), cin, 32, sw), vec);
+  launch<false, false, MODE_FWD>(st, p);
 }
 
-void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                      int rows, int cin, int cout, bool accumulate, const SplitWorkspace& sw) {
-  if (linear_dgrad_f32_direct(st, dy, w, mask, dx, rows, cin, cout, accumulate)) return;
+bool linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
+                      int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg) {
+  if (linear_dgrad_f32_direct(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg)) return head != nullptr;
+  if (linear_f32_small(rows, cin, cout)) {
+    linear_dgrad_f32_small(st, dy, w, mask, dx, rows, cin, cout, accumulate);
+    return false;
+  }
   GemmParams p{};
   p.A = dy; p.B = w; p.C = dx; p.M = rows; p.N = cin; p.lda = cout; p.ldb = cin; p.ldc = cin;
   p.kred = cout; p.mask = mask; p.accumulate = accumulate ? 1 : 0;
-  p.partial = sw.partial; p.counters = sw.counters;
-  Segments seg{};
-  const bool vec = aligned16(dy) && aligned16(w) && (cout % 4 == 0) && (cin % 4 == 0) && cout >= 32;
-  launch<32, false, true, MODE_DGRAD>(st, p, seg, pick_splits(gemm_tiles(rows, cin), cout, 32, sw), vec);
+  if (!head) {
+    launch<false, true, MODE_DGRAD>(st, p);
+    return false;
+  }
+  const int tiles = gemm_tiles(p.M, p.N);
+  p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
+  const dim3 hg = head_wgrad_grid(head->cin, head->C, seg.K);
+  hipLaunchKernelGGL(gemm_f32_dgrad_head_kernel, dim3(tiles + hg.x * hg.y), dim3(kThreads), 0, st, p, tiles, *head,
+                     (int)hg.x, seg);
+  return true;
 }
 
-static bool wgrad_params(GemmParams& p, const LinearWgradJob& j, size_t worker_stride, const Segments& seg) {
-  p = GemmParams{};
-  p.A = j.dy; p.B = j.x; p.C = j.gw; p.M = j.cout; p.N = j.cin; p.lda = j.cout; p.ldb = j.cin; p.ldc = j.cin;
-  p.c_worker_stride = worker_stride; p.bias_grad = j.gb;
-  p.c_vec = (aligned16(j.gw) && j.cin % 4 == 0 && worker_stride % 4 == 0) ? 1 : 0;
-  return aligned16(j.dy) && aligned16(j.x) && (j.cout % 4 == 0) && (j.cin % 4 == 0) && seg.off[seg.K] >= 32;
-}
-
-void linear_wgrad_f32(hipStream_t st, const float* dy, const float* x, float* gw, float* gb,
-                      size_t worker_stride, const Segments& seg, int cin, int cout) {
-  GemmParams p;
-  const LinearWgradJob job{dy, x, gw, gb, cin, cout};
-  const bool vec = wgrad_params(p, job, worker_stride, seg);
-  launch<32, true, true, MODE_WGRAD>(st, p, seg, 1, vec);
+bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows) {
+  long tiles64 = 0;
+  bool tileable = rows >= 32;
+  for (int i = 0; i < n; ++i) {
+    tiles64 += gemm_tiles(jobs[i].cout, jobs[i].cin);
+    tileable = tileable && jobs[i].cout >= 4 && jobs[i].cin >= 4;
+  }
+  return tileable && tiles64 >= kTiledWgradTiles;
 }
 
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
-                            const Segments& seg, const KernelTimer* timer) {
-  // problems that can take the mask-free loads share launches of up to kMaxBatch; the others go alone
-  WgradBatch b{};
-  // exact timing needs everything in ONE launch of the shared kernel; otherwise the events go around the launches
-  bool one_launch = n >= 2 && n <= kMaxBatch;
-  for (int i = 0; i < n && one_launch; ++i) {
-    GemmParams p;
-    one_launch = wgrad_params(p, jobs[i], worker_stride, seg);
-  }
-  const bool bracket = timer && !one_launch;
-  if (bracket) (void)hipEventRecord(timer->start, st);
-  auto flush = [&]() {
-    if (b.n == 1) {
-      GemmParams p = b.prob[0];
-      launch<32, true, true, MODE_WGRAD>(st, p, seg, 1, true);
-    } else if (b.n > 1) {
-      if (timer && one_launch)
-        hipExtLaunchKernelGGL((gemm_f32_wgrad_batch_kernel<32, true>), dim3(b.start[b.n]), dim3(kThreads), 0, st,
-                              timer->start, timer->stop, 0, b, seg);
-      else
-        hipLaunchKernelGGL((gemm_f32_wgrad_batch_kernel<32, true>), dim3(b.start[b.n]), dim3(kThreads), 0, st, b, seg);
+                            const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
+                            const KernelTimer* timer) {
+  const int upd = sgd ? (sgd->velocity ? 2 : 1) : 0;
+  const Lambdas lam = lambdas_of(seg);
+  const Optim opt = sgd ? Optim{sgd->lr, sgd->momentum, sgd->weight_decay} : Optim{0.f, 0.f, 0.f};
+  const bool one = n <= kMaxBatch;
+  if (timer && !one) (void)hipEventRecord(timer->start, st);
+  for (int base = 0; base < n; base += kMaxBatch) {
+    WgradBatch b{};
+    b.n = std::min(n - base, kMaxBatch);
+    b.worker_stride = worker_stride;
+    for (int i = 0; i < b.n; ++i) {
+      const LinearWgradJob& j = jobs[base + i];
+      GemmParams& p = b.prob[i];
+      p.A = j.dy; p.B = j.x; p.C = j.gw; p.M = j.cout; p.N = j.cin; p.lda = j.cout; p.ldb = j.cin; p.ldc = j.cin;
+      p.c_worker_stride = worker_stride; p.bias_grad = j.gb;
+      if (sgd) {
+        p.theta = sgd->params + j.w_off; p.theta_bias = sgd->params + j.b_off;
+        if (sgd->velocity) { p.velocity = sgd->velocity + j.w_off; p.velocity_bias = sgd->velocity + j.b_off; }
+      }
+      b.start[i + 1] = b.start[i] + gemm_tiles(p.M, p.N);
     }
-    b.n = 0;
-  };
-  for (int i = 0; i < n; ++i) {
-    GemmParams p;
-    if (!wgrad_params(p, jobs[i], worker_stride, seg)) {
-      launch<32, true, true, MODE_WGRAD>(st, p, seg, 1, false);
-      continue;
+    if (sgd && head && base + kMaxBatch >= n) {
+      b.head_n = (long)head->cout * head->cin + (head->gb ? head->cout : 0);   // (the bias follows the weight)
+      b.head_theta = sgd->params + head->w_off;
+      if (sgd->velocity) b.head_velocity = sgd->velocity + head->w_off;
+      b.head_grad = head->gw;
     }
-    const int tiles = gemm_tiles(p.M, p.N);
-    const int G = plan_worker_groups(p, seg, tiles, 512);
-    b.start[b.n + 1] = b.start[b.n] + tiles * G;
-    b.prob[b.n++] = p;
-    if (b.n == kMaxBatch) flush();
+    const dim3 grid(b.start[b.n] + (unsigned)((b.head_n + kThreads - 1) / kThreads)), block(kThreads);
+#define OMNI_WGRAD(U)                                                                                              \
+  if (timer && one)                                                                                                \
+    hipExtLaunchKernelGGL((gemm_f32_wgrad_batch_kernel<32, U>), grid, block, 0, st, timer->start, timer->stop, 0,  \
+                          b, seg, lam, opt);                                                                       \
+  else                                                                                                             \
+    hipLaunchKernelGGL((gemm_f32_wgrad_batch_kernel<32, U>), grid, block, 0, st, b, seg, lam, opt)
+    if (upd == 0) { OMNI_WGRAD(0); }
+    else if (upd == 1) { OMNI_WGRAD(1); }
+    else { OMNI_WGRAD(2); }
+#undef OMNI_WGRAD
   }
-  flush();
-  if (bracket) (void)hipEventRecord(timer->stop, st);
+  if (timer && !one) (void)hipEventRecord(timer->stop, st);
 }
 
 }  // namespace omni

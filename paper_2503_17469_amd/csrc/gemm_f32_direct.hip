@@ -325,26 +325,22 @@ bool linear_dgrad_f32_direct_supported(const float* dy, const float* w, const fl
 }
 
 bool linear_dgrad_f32_direct(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                             int rows, int cin, int cout, bool accumulate) {
+                             int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head,
+                             const Segments& seg) {
   if (!linear_dgrad_f32_direct_supported(dy, w, mask, dx, rows, cin, cout)) return false;
   DirectParams p{};
   p.A = dy; p.B = w; p.C = dx; p.M = rows; p.N = cin; p.K = cout; p.lda = cout; p.ldb = cin; p.ldc = cin;
   p.mask = mask; p.accumulate = accumulate ? 1 : 0;
-  launch_direct<true>(st, p);
-  return true;
-}
-
-void linear_dgrad_f32_with_head_wgrad(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                                      int rows, int cin, int cout, bool accumulate, const HeadWgradParams& head,
-                                      const Segments& seg) {
-  DirectParams p{};
-  p.A = dy; p.B = w; p.C = dx; p.M = rows; p.N = cin; p.K = cout; p.lda = cout; p.ldb = cin; p.ldc = cin;
-  p.mask = mask; p.accumulate = accumulate ? 1 : 0;
+  if (!head) {
+    launch_direct<true>(st, p);
+    return true;
+  }
   const int tiles = ((p.M + 31) / 32) * ((p.N + 63) / 64);
   p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
-  const dim3 hg = head_wgrad_grid(head.cin, head.C, seg.K);
-  hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel, dim3(tiles + hg.x * hg.y), dim3(256), 0, st, p, tiles, head,
+  const dim3 hg = head_wgrad_grid(head->cin, head->C, seg.K);
+  hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel, dim3(tiles + hg.x * hg.y), dim3(256), 0, st, p, tiles, *head,
                      (int)hg.x, seg);
+  return true;
 }
 
 }  // namespace omni

@@ -12,10 +12,13 @@
 //      extra workgroup) L_k, the lambda-weighted total loss and the label check.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bf16.h"
 #include "common.h"
 #include "head_device.h"
 #include "kernels.h"
+#include "update_device.h"
 
 namespace omni {
 
@@ -28,8 +31,20 @@ __device__ inline int owner(const Segments& seg, int s) {
   while (k + 1 < seg.K && s >= seg.off[k + 1]) ++k;
   return k;
 }
-__device__ inline float dot4(v4f a, v4f b) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + a[3] * b[3]; }
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <typename T, bool AL>
+__device__ inline void load_piece(const T* p, float (&v)[Piece<T>::EL]) {
+  if constexpr (AL) {
+    Piece<T>::load(p, v);
+  } else {
+    const v4f t = *reinterpret_cast<const v4f_a4*>(p);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = t[e];
+  }
+}
 
+// AL = false (fp32 only): rows may start at any multiple of 4 bytes and have any length of at least one piece; the
+// last piece of a row is moved back to end there and the elements it shares with the piece before count once.
 // T is the storage type of the input rows, the weights and the input gradient
 // (fp32, or bf16 with fp32 arithmetic).  NV = 16-byte pieces of the input row
 // each lane keeps in registers; one piece per lane covers 64 * EL consecutive
@@ -39,7 +54,7 @@ __device__ inline float dot4(v4f a, v4f b) { return a[0] * b[0] + a[1] * b[1] + 
 // there.  A wavefront then waits for memory once instead of once per group of classes in each
 // pass; with one row per wavefront and two wavefronts per compute unit that chain of round
 // trips, not bandwidth, is what the kernel's time consists of.
-template <typename T, int NV, bool WLDS>
+template <typename T, int NV, bool WLDS, bool AL>
 __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
     const T* __restrict__ x, const T* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ labels, int cin, int C, Segments seg, float* __restrict__ z,
@@ -64,13 +79,16 @@ __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int k = (lane + 64 * i) * EL;
-    kk[i] = k < cin ? k : 0;
-    Piece<T>::load(xr + kk[i], a[i]);
+    kk[i] = k < cin ? (AL ? k : min(k, cin - EL)) : 0;
+    load_piece<T, AL>(xr + kk[i], a[i]);
   }
   if (WLDS) {
-    const int npieces = C * cin / EL;          // 16-byte pieces; cin is a multiple of EL
-    const u32x4* src = reinterpret_cast<const u32x4*>(w);
+    const int npieces = C * cin / EL;          // 16-byte pieces; with AL, cin is a multiple of EL
+    typedef typename std::conditional<AL, u32x4, u32x4_a4>::type src_t;
+    const src_t* src = reinterpret_cast<const src_t*>(w);
     u32x4* dst = reinterpret_cast<u32x4*>(wl_raw);
+    if (!AL && (int)threadIdx.x < C * cin - npieces * EL)
+      reinterpret_cast<T*>(wl_raw)[npieces * EL + threadIdx.x] = w[npieces * EL + threadIdx.x];
     // eight pieces per thread in flight at a time (a piece past the end re-reads the last one)
     for (int q0 = threadIdx.x; q0 < npieces; q0 += 256 * 8) {
       u32x4 t[8];
@@ -83,11 +101,12 @@ __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < NV; ++i)
-    if ((lane + 64 * i) * EL >= cin) {
+  for (int i = 0; i < NV; ++i) {
+    const int k = (lane + 64 * i) * EL;
 #pragma unroll
-      for (int e = 0; e < EL; ++e) a[i][e] = 0.f;
-    }
+    for (int e = 0; e < EL; ++e)
+      if (k >= cin || (!AL && kk[i] + e < k)) a[i][e] = 0.f;
+  }
   for (int c0 = 0; c0 < C; c0 += CH) {
     float acc[CH];
 #pragma unroll
@@ -97,7 +116,7 @@ __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         float wv_[EL];
-        Piece<T>::load(wp + (size_t)c * cin + kk[i], wv_);
+        load_piece<T, AL>(wp + (size_t)c * cin + kk[i], wv_);
 #pragma unroll
         for (int e = 0; e < EL; ++e) acc[j] += a[i][e] * wv_[e];
       }
@@ -149,7 +168,7 @@ __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         float wv_[EL];
-        Piece<T>::load(wp + (size_t)c * cin + kk[i], wv_);
+        load_piece<T, AL>(wp + (size_t)c * cin + kk[i], wv_);
 #pragma unroll
         for (int e = 0; e < EL; ++e) g[i][e] += d * wv_[e];
       }
@@ -158,18 +177,24 @@ __global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
     for (int i = 0; i < NV; ++i) {
       const int k = (lane + 64 * i) * EL;
       if (k >= cin) continue;
-      const size_t idx = (size_t)row * cin + k;
+      const size_t idx = (size_t)row * cin + kk[i];
       if (use_mask) {
 #pragma unroll
         for (int e = 0; e < EL; ++e) g[i][e] = a[i][e] > 0.f ? g[i][e] : 0.f;
       }
       if (accumulate) {
         float old[EL];
-        Piece<T>::load(dx + idx, old);
+        load_piece<T, AL>(dx + idx, old);
 #pragma unroll
         for (int e = 0; e < EL; ++e) g[i][e] += old[e];
       }
-      Piece<T>::store(dx + idx, g[i]);
+      if constexpr (AL) {
+        Piece<T>::store(dx + idx, g[i]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < EL; ++e)
+          if (kk[i] + e >= k) dx[idx + e] = g[i][e];
+      }
     }
   }
 }
@@ -183,9 +208,10 @@ __global__ __launch_bounds__(256) void head_wgrad_loss_kernel(HeadWgradParams h,
 }  // namespace
 
 bool head_supported(int cin, int classes, const void* x, const void* w, bool bf16) {
-  const int el = bf16 ? 8 : 4;
-  return classes >= 1 && classes <= kMaxClasses && cin % el == 0 && cin <= 2048 &&
-         (reinterpret_cast<uintptr_t>(x) & 15u) == 0 && (reinterpret_cast<uintptr_t>(w) & 15u) == 0;
+  if (classes < 1 || classes > kMaxClasses || cin > 2048) return false;
+  if (!bf16) return cin >= Piece<float>::EL;
+  return cin % Piece<bf16_t>::EL == 0 && (reinterpret_cast<uintptr_t>(x) & 15u) == 0 &&
+         (reinterpret_cast<uintptr_t>(w) & 15u) == 0;
 }
 
 template <typename T>
@@ -198,20 +224,27 @@ static void launch_head_fwd(hipStream_t st, const T* x, const T* w, const float*
   const int acc = accumulate ? 1 : 0, um = use_mask ? 1 : 0;
   const size_t wbytes = (size_t)classes * cin * sizeof(T);
   const bool wlds = wbytes <= 48 * 1024;
-#define OMNI_HEAD(NV)                                                                                              \
-  do {                                                                                                             \
-    if (wlds)                                                                                                      \
-      hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, NV, true>), grid, block, wbytes, st, x, w, bias, labels,   \
-                         cin, classes, seg, z, dz, loss_rows, um, dx, acc);                                        \
-    else                                                                                                           \
-      hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, NV, false>), grid, block, 0, st, x, w, bias, labels, cin,  \
-                         classes, seg, z, dz, loss_rows, um, dx, acc);                                             \
+  const bool aligned = cin % Piece<T>::EL == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w) |
+                                                    reinterpret_cast<uintptr_t>(dx)) & 15u) == 0;
+#define OMNI_HEAD2(NV, WL, AL)                                                                                        \
+  hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, NV, WL, AL>), grid, block, WL ? wbytes : 0, st, x, w, bias, labels, \
+                     cin, classes, seg, z, dz, loss_rows, um, dx, acc)
+#define OMNI_HEAD(NV)                                             \
+  do {                                                            \
+    if (aligned) {                                                \
+      if (wlds) OMNI_HEAD2(NV, true, true);                       \
+      else OMNI_HEAD2(NV, false, true);                           \
+    } else if constexpr (Piece<T>::EL == 4) {                     \
+      if (wlds) OMNI_HEAD2(NV, true, false);                      \
+      else OMNI_HEAD2(NV, false, false);                          \
+    }                                                             \
   } while (0)
   if (nv <= 1) OMNI_HEAD(1);
   else if (nv <= 2) OMNI_HEAD(2);
   else if (nv <= 4) OMNI_HEAD(4);
   else if constexpr (Piece<T>::EL == 4) OMNI_HEAD(8);
 #undef OMNI_HEAD
+#undef OMNI_HEAD2
 }
 
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
@@ -225,11 +258,8 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
                            seg, z, dz, loss_rows, use_mask, static_cast<float*>(dx), accumulate);
 }
 
-void head_wgrad_loss(hipStream_t st, bool bf16, const float* dz, const void* x, const int32_t* labels, int cin,
-                     int classes, const Segments& seg, float* gw, float* gb, size_t worker_stride,
-                     const float* loss_rows, float* loss_per_worker, float* loss, uint32_t* status) {
-  const HeadWgradParams h{dz, x, labels, cin, classes, gw, gb, worker_stride, loss_rows, loss_per_worker, loss, status};
-  const dim3 grid = head_wgrad_grid(cin, classes, seg.K);
+void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg) {
+  const dim3 grid = head_wgrad_grid(h.cin, h.C, seg.K);
   if (bf16)
     hipLaunchKernelGGL(head_wgrad_loss_kernel<bf16_t>, grid, dim3(256), 0, st, h, seg);
   else

@@ -37,6 +37,35 @@ __device__ inline float wave_max(float v) {
   v = fmaxf(v, dpp_move<0x140>(v));
   return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
+// Losses and label check, one workgroup of any number of wavefronts, one wavefront per worker:
+// L_k = mean of the worker's row losses, loss = sum_k lambda_k L_k, status bit 0 if a label lies outside [0, C).
+constexpr int kHeadLossLdsFloats = OMNI_MAX_WORKERS;
+__device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Segments& seg, float* part) {
+  const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid & 63;
+  const int rows = seg.off[seg.K];
+  const float invB = 1.0f / (float)rows;
+  for (int k = tid >> 6; k < seg.K; k += nthreads >> 6) {
+    float a = 0.f;
+    for (int s = seg.off[k] + lane; s < seg.off[k + 1]; s += 64) a += h.loss_rows[s];
+    a = wave_sum(a);
+    if (lane == 0) {
+      const float bk = (float)(seg.off[k + 1] - seg.off[k]);
+      const float Lk = a / bk;
+      h.loss_per_worker[k] = Lk;
+      part[k] = bk * invB * Lk;   // lambda_k L_k
+    }
+  }
+  int badl = 0;
+  for (int s = tid; s < rows; s += nthreads) badl |= (h.labels[s] < 0 || h.labels[s] >= h.C) ? 1 : 0;
+  const int anybad = __syncthreads_or(badl);
+  if (tid == 0) {
+    float total = 0.f;
+    for (int k = 0; k < seg.K; ++k) total += part[k];
+    h.loss[0] = total;
+    h.status[0] = anybad ? 1u : 0u;
+  }
+}
+
 constexpr int kHeadWgradLdsFloats = 16 * 16 * 17 + 256 * 16;
 inline dim3 head_wgrad_grid(int cin, int classes, int K) {
   return dim3(K * ((cin + 15) / 16) + 1, (classes + 15) / 16, 1);
@@ -55,45 +84,16 @@ __device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, c
   float (*dzs)[16] = reinterpret_cast<float (*)[16]>(smem + 16 * 16 * 17);
   const float* __restrict__ dz = h.dz;
   const T* __restrict__ x = static_cast<const T*>(h.x);
-  const int32_t* __restrict__ labels = h.labels;
   const int cin = h.cin, C = h.C;
   float* __restrict__ gw = h.gw;
   float* __restrict__ gb = h.gb;
   const size_t worker_stride = h.worker_stride;
-  const float* __restrict__ loss_rows = h.loss_rows;
-  float* __restrict__ loss_per_worker = h.loss_per_worker;
-  float* __restrict__ loss = h.loss;
-  uint32_t* __restrict__ status = h.status;
   const int tid = threadIdx.x;
   const int jchunks = (cin + 15) / 16;
 
   if (bx == seg.K * jchunks) {
-    // ---- the extra workgroup: losses and label check; one wavefront per worker
-    if (by != 0) return;
-    float* part = &red[0][0][0];
-    const int lane = tid & 63, wv = tid >> 6;
-    const int rows = seg.off[seg.K];
-    const float invB = 1.0f / (float)rows;
-    for (int k = wv; k < seg.K; k += 4) {
-      float a = 0.f;
-      for (int s = seg.off[k] + lane; s < seg.off[k + 1]; s += 64) a += loss_rows[s];
-      a = wave_sum(a);
-      if (lane == 0) {
-        const float bk = (float)(seg.off[k + 1] - seg.off[k]);
-        const float Lk = a / bk;
-        loss_per_worker[k] = Lk;
-        part[k] = bk * invB * Lk;   // lambda_k L_k
-      }
-    }
-    int badl = 0;
-    for (int s = tid; s < rows; s += 256) badl |= (labels[s] < 0 || labels[s] >= C) ? 1 : 0;
-    const int anybad = __syncthreads_or(badl);
-    if (tid == 0) {
-      float total = 0.f;
-      for (int k = 0; k < seg.K; ++k) total += part[k];
-      loss[0] = total;
-      status[0] = anybad ? 1u : 0u;
-    }
+    if (by == 0)
+      head_loss_body(HeadLossParams{h.labels, h.C, h.loss_rows, h.loss_per_worker, h.loss, h.status}, seg, smem);
     return;
   }
 

@@ -19,22 +19,16 @@ struct KernelTimer {
   hipEvent_t stop;
 };
 
-// Scratch for split reductions: partial tiles plus one arrival counter per tile.
-// Counters must be zero when a launch starts; every launch leaves them zero.
-struct SplitWorkspace {
-  float* partial = nullptr;      // kSplitPartialFloats floats
-  uint32_t* counters = nullptr;  // kSplitMaxTiles words
-};
-constexpr int kSplitMaxTiles = 512;
-constexpr size_t kSplitPartialFloats = (size_t)1024 * 16 * 256;  // tiles * splits <= 1024
-
 // ---- fp32 fully connected layers (gemm_f32.hip) ----
 // y[rows][cout] = x[rows][cin] * w[cout][cin]^T + bias, optional ReLU.
 void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
-                    int rows, int cin, int cout, bool relu, const SplitWorkspace& sw);
+                    int rows, int cin, int cout, bool relu);
 // dx[rows][cin] (+)= dy[rows][cout] * w[cout][cin], zeroed where mask[rows][cin] <= 0 (mask may be null).
-void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                      int rows, int cin, int cout, bool accumulate, const SplitWorkspace& sw);
+// head (may be null): the classifier's parameter gradients and losses, which need nothing of this product; where the
+// kernel taken can carry them they run in the same launch and the call returns true.
+struct HeadWgradParams;
+bool linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
+                      int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
 // Small-batch variants (gemm_f32_direct.hip): same results as the two above up to
 // summation order; return false without launching when the shape does not qualify.
 bool linear_fwd_f32_direct_supported(const float* x, const float* w, int rows, int cin, int cout);
@@ -43,22 +37,51 @@ bool linear_fwd_f32_direct(hipStream_t st, const float* x, const float* w, const
 bool linear_dgrad_f32_direct_supported(const float* dy, const float* w, const float* mask, const float* dx, int rows,
                                        int cin, int cout);
 bool linear_dgrad_f32_direct(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                             int rows, int cin, int cout, bool accumulate);
-// For every worker k: gw + k*worker_stride receives dy_k^T x_k ([cout][cin]) over rows
-// seg.off[k]..seg.off[k+1]-1, and gb + k*worker_stride the column sums of dy_k (gb may be null).
-void linear_wgrad_f32(hipStream_t st, const float* dy, const float* x, float* gw, float* gb,
-                      size_t worker_stride, const Segments& seg, int cin, int cout);
-// The same for several layers at once (same workers, same worker_stride): one launch where the
-// shapes allow it, so that the start-up and drain of one layer's workgroups overlap the others' work.
+                             int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head,
+                             const Segments& seg);
+// For every worker k and every job: gw + k*worker_stride receives dy_k^T x_k ([cout][cin]) over rows
+// seg.off[k]..seg.off[k+1]-1, and gb + k*worker_stride the column sums of dy_k (gb may be null).  All jobs share one
+// launch, so that the start-up and drain of one layer's workgroups overlap the others' work.
 struct LinearWgradJob {
   const float* dy;   // [rows][cout]
   const float* x;    // [rows][cin]
   float* gw;         // worker 0's [cout][cin]
   float* gb;         // worker 0's [cout], may be null
   int cin, cout;
+  size_t w_off, b_off;   // the layer's weight and bias in the parameter vector
 };
+// Losses of the classifier head: L_k, their lambda-weighted sum and the label check, from the row losses.
+struct HeadLossParams {
+  const int32_t* labels;      // [rows]
+  int C;
+  const float* loss_rows;     // [rows]
+  float* loss_per_worker;     // [K]
+  float* loss;                // [1]
+  uint32_t* status;           // [1]
+};
+// The update that the weight-gradient launch may apply itself (see linear_wgrad_f32_batch).
+struct SgdArgs {
+  float* params;
+  float* velocity;            // null: plain SGD
+  float lr, momentum, weight_decay;
+};
+// Whether the tiled kernel takes these weight gradients (else linear_wgrad_f32_small does).
+bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows);
+// sgd (may be null): the update of the jobs' weights and biases is applied as well, by the workgroups that have formed
+// all workers' gradients of a tile; with head (may be null), also that of the classifier's parameters, whose gradients
+// are in G already.
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
-                            const Segments& seg, const KernelTimer* timer = nullptr);
+                            const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
+                            const KernelTimer* timer = nullptr);
+// Products too small or too odd for the tiled kernels (gemm_f32_small.hip); any shape and 4-byte alignment.
+bool linear_f32_small(int rows, int cols, int kred);   // the rule for forward (cols = cout) and dgrad (cols = cin)
+void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows,
+                          int cin, int cout, bool relu);
+void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows,
+                            int cin, int cout, bool accumulate);
+// (loss, may be null: computed in the same launch.)
+void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+                            const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer);
 
 // ---- classifier head (head.hip): last fully connected layer with few outputs ----
 // `bf16` selects the storage type of x, w and dx (bf16 words) versus fp32; the
@@ -72,9 +95,7 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
                          float* loss_rows, bool use_mask, void* dx, bool accumulate);
 // Per worker: gw_k = dz_k^T x_k, gb_k = column sums of dz_k; plus L_k, the total
 // loss and the status word (bit 0: some label outside [0, classes)).
-void head_wgrad_loss(hipStream_t st, bool bf16, const float* dz, const void* x, const int32_t* labels, int cin,
-                     int classes, const Segments& seg, float* gw, float* gb, size_t worker_stride,
-                     const float* loss_rows, float* loss_per_worker, float* loss, uint32_t* status);
+void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg);
 // Arguments of the head's parameter-gradient kernel.  x has the storage type T of the body's
 // instantiation (fp32, or bf16 words); everything else is fp32.
 struct HeadWgradParams {
@@ -90,13 +111,6 @@ struct HeadWgradParams {
   float* loss;                // [1]
   uint32_t* status;           // [1]
 };
-// The input gradient of a fully connected fp32 layer (as linear_dgrad_f32) and the head's parameter
-// gradients (as head_wgrad_loss with fp32 x) in ONE launch; the two must not depend on each other.
-// Only for products that linear_dgrad_f32_direct_supported accepts (the caller asks first).
-void linear_dgrad_f32_with_head_wgrad(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
-                                      int rows, int cin, int cout, bool accumulate, const HeadWgradParams& head,
-                                      const Segments& seg);
-
 // ---- bf16 convolutions / fully connected layers as implicit GEMMs (conv_bf16.hip) ----
 typedef uint16_t bf16_t;   // raw bfloat16 bits
 // How the left operand of an implicit GEMM is gathered from a channels-last tensor.

@@ -60,7 +60,7 @@ struct omni_net {
   int dtype, K_max, B_max;
   size_t P = 0, P_stride = 0;
   size_t ws_bytes = 0;
-  size_t grads_off = 0, loss_rows_off = 0, status_off = 0, partial_off = 0, counters_off = 0;
+  size_t grads_off = 0, loss_rows_off = 0, status_off = 0;
   size_t shadow_off = 0, shadow_elems = 0, xpad_off = 0, conv_partial_off = 0, conv_counters_off = 0;
   size_t conv_partial2_off = 0;     // chunk scratch of the second side stream
   size_t bn_off = 0, bn_floats = 0, bn_partial_off = 0;
@@ -308,8 +308,6 @@ int omni_net_create(const omni_layer_desc* descs, int32_t n, int32_t in_h, int32
   net->reduced_off = take(net->P_stride * sizeof(float));
   net->loss_rows_off = take((size_t)B_max * sizeof(float));
   net->status_off = take(kAlign);
-  net->counters_off = take(omni::kSplitMaxTiles * sizeof(uint32_t));
-  net->partial_off = take(omni::kSplitPartialFloats * sizeof(float));
   if (bf) {
     net->conv_counters_off = take(omni::kZeroPageWords * sizeof(uint32_t));
     net->conv_partial_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
@@ -496,6 +494,8 @@ struct StepCtx {
   uint32_t* status;
   float* loss_per_worker;
   float* loss;
+  float lr;
+  bool fuse_update;      // fp32: the weight-gradient launch applies the update
 };
 
 // ------------------------------------------------------------------ fp32 path
@@ -510,21 +510,6 @@ void step_f32(StepCtx& c) {
   float* params = c.params;
   const int rows = c.rows;
 
-  omni::SplitWorkspace sw;
-  sw.partial = reinterpret_cast<float*>(c.ws + net->partial_off);
-  sw.counters = reinterpret_cast<uint32_t*>(c.ws + net->counters_off);
-  // The arrival counters of the split reductions must be zero when a launch that uses them starts.
-  // Every such launch leaves them zero, but the workspace is the caller's memory (fresh, re-allocated at
-  // the same address, shared with another network, written in between): the first launch of a step
-  // that may split its reduction is therefore preceded by a fill.  A step whose products all take the
-  // small-batch kernel never touches the counters and pays nothing.
-  bool counters_clear = false;
-  auto before_split_launch = [&]() {
-    if (counters_clear) return;
-    omni::fill_u32(st, sw.counters, omni::kSplitMaxTiles, 0u);
-    counters_clear = true;
-  };
-
   const int n_layers = (int)net->layers.size();
   const Layer& last = net->layers[n_layers - 1];
   const bool fused_head = last.d.op == OMNI_OP_LINEAR &&
@@ -534,18 +519,14 @@ void step_f32(StepCtx& c) {
   for (int i = 0; i < n_layers; ++i) {
     const Layer& L = net->layers[i];
     if (L.fused_away || (fused_head && i == n_layers - 1)) continue;
-    if (!omni::linear_fwd_f32_direct_supported(act(L.in0), params + L.w_off, rows, L.d.cin, L.d.cout))
-      before_split_launch();
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_FWD, i);
     omni::linear_fwd_f32(st, act(L.in0), params + L.w_off, L.has_b ? params + L.b_off : nullptr, actw(L.out), rows,
-                         L.d.cin, L.d.cout, net->tensors[L.out].relu, sw);
+                         L.d.cin, L.d.cout, net->tensors[L.out].relu);
   }
 
   // ---- loss: dz already carries 1/b_k, so everything downstream is a per-worker mean gradient
   const int logits = last.out;
   std::vector<char> written(net->tensors.size(), 0);
-  int merge_layer = -1;
-  omni::HeadWgradParams head_wgrad{};
   if (fused_head) {
     TimedScope ts(net, st, OMNI_KERNEL_LOSS, n_layers - 1);
     const bool need_dx = last.in0 >= 0;
@@ -554,24 +535,6 @@ void step_f32(StepCtx& c) {
                               actw(logits), grad(logits), c.loss_rows, need_dx && net->tensors[last.in0].relu,
                               need_dx ? grad(last.in0) : nullptr, false);
     if (need_dx) written[last.in0] = 1;
-    // The head's parameter gradients and the next layer's input gradient both wait for this kernel only:
-    // where the latter takes the small-batch kernel the two share a launch (below), reported as that layer's dgrad.
-    for (int i = n_layers - 2; i >= 0 && merge_layer < 0; --i) {
-      const Layer& L = net->layers[i];
-      if (L.fused_away) continue;
-      if (L.in0 >= 0 && omni::linear_dgrad_f32_direct_supported(grad(L.out), params + L.w_off,
-                                                                net->tensors[L.in0].relu ? act(L.in0) : nullptr,
-                                                                grad(L.in0), rows, L.d.cin, L.d.cout))
-        merge_layer = i;
-      break;
-    }
-    head_wgrad = omni::HeadWgradParams{grad(logits), act(last.in0), c.labels, last.d.cin, last.d.cout,
-                                       c.G + last.w_off, last.has_b ? c.G + last.b_off : nullptr, net->P_stride,
-                                       c.loss_rows, c.loss_per_worker, c.loss, c.status};
-    if (merge_layer < 0)
-      omni::head_wgrad_loss(st, false, head_wgrad.dz, head_wgrad.x, head_wgrad.labels, head_wgrad.cin, head_wgrad.C,
-                            c.seg, head_wgrad.gw, head_wgrad.gb, head_wgrad.worker_stride, head_wgrad.loss_rows,
-                            head_wgrad.loss_per_worker, head_wgrad.loss, head_wgrad.status);
   } else {
     TimedScope ts(net, st, OMNI_KERNEL_LOSS, n_layers - 1);
     omni::fill_u32(st, c.status, 1, 0u);
@@ -579,40 +542,53 @@ void step_f32(StepCtx& c) {
                            c.loss_per_worker, c.loss, c.status);
   }
 
-  // ---- backward: input gradients on all rows first, then the parameter gradients of ALL layers per
-  // worker in one launch (every layer's output gradient has a buffer of its own, so they can wait;
-  // one launch has one start-up and one drain instead of one per layer).
+  // ---- backward: input gradients on all rows first, then the parameter gradients of all layers per worker in one
+  // launch, which also applies the update where the step wants one and nothing asks for the update as a launch of its
+  // own (every layer's output gradient has a buffer of its own, so they can wait; one launch has one start-up and one
+  // drain instead of one per layer, and the update needs no second pass over the gradients).
   // (No side stream here: at this size a cross-stream fork and join each cost about 10 us of
   // idle GPU, more than the overlap returns; measured.)
-  std::vector<omni::LinearWgradJob> jobs;
+  std::vector<omni::LinearWgradJob> jobs;   // last layer first (measured 47.1 us against 48.8 us the other way round)
   int first_job_layer = -1;
   for (int i = n_layers - 1; i >= 0; --i) {
     const Layer& L = net->layers[i];
-    if (L.fused_away || (fused_head && i == n_layers - 1)) continue;
-    jobs.push_back({grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin, L.d.cout});
+    if (L.fused_away) continue;
+    jobs.push_back({grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin, L.d.cout,
+                    L.w_off, L.b_off});
     first_job_layer = i;
-    if (L.in0 >= 0) {
-      const Tensor& ti = net->tensors[L.in0];
-      const float* mask = ti.relu ? act(L.in0) : nullptr;
-      if (i != merge_layer &&
-          !omni::linear_dgrad_f32_direct_supported(grad(L.out), params + L.w_off, mask, grad(L.in0), rows, L.d.cin,
-                                                   L.d.cout))
-        before_split_launch();
-      TimedScope ts(net, st, OMNI_KERNEL_LINEAR_DGRAD, i);
-      if (i == merge_layer)   // (chosen above by the very test the shared launcher requires)
-        omni::linear_dgrad_f32_with_head_wgrad(st, grad(L.out), params + L.w_off, mask, grad(L.in0), rows, L.d.cin,
-                                               L.d.cout, written[L.in0] != 0, head_wgrad, c.seg);
-      else
-        omni::linear_dgrad_f32(st, grad(L.out), params + L.w_off, mask, grad(L.in0), rows, L.d.cin, L.d.cout,
-                               written[L.in0] != 0, sw);
-      written[L.in0] = 1;
-    }
   }
-  if (!jobs.empty()) {
+  // The classifier's own gradients are one more problem of that launch for the small kernels.  The tiled kernel would
+  // spend whole tiles on them: they run beside the input gradient of the layer below, or by themselves.
+  const int skip = fused_head ? 1 : 0;
+  const bool tiled = omni::linear_wgrad_f32_tiled(jobs.data() + skip, (int)jobs.size() - skip, rows);
+  const omni::HeadWgradParams head{grad(logits), act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
+                                   last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
+                                   c.loss_per_worker, c.loss, c.status};
+  bool head_pending = fused_head && tiled;
+  for (int i = n_layers - 1; i >= 0; --i) {
+    const Layer& L = net->layers[i];
+    if (L.fused_away || L.in0 < 0 || (fused_head && i == n_layers - 1)) continue;
+    TimedScope ts(net, st, OMNI_KERNEL_LINEAR_DGRAD, i);
+    if (omni::linear_dgrad_f32(st, grad(L.out), params + L.w_off, net->tensors[L.in0].relu ? act(L.in0) : nullptr,
+                               grad(L.in0), rows, L.d.cin, L.d.cout, written[L.in0] != 0, head_pending ? &head : nullptr,
+                               c.seg))
+      head_pending = false;
+    written[L.in0] = 1;
+  }
+  if (head_pending) omni::head_wgrad_loss(st, false, head, c.seg);
+  {
     // reported under the lowest layer it covers
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, first_job_layer, true);
-    // (last layer's problem first in the launch: measured 47.1 us against 48.8 us the other way round)
-    omni::linear_wgrad_f32_batch(st, jobs.data(), (int)jobs.size(), net->P_stride, c.seg, ts.timer());
+    const omni::SgdArgs sgd{params, net->velocity, c.lr, net->momentum, net->weight_decay};
+    const omni::SgdArgs* upd = c.fuse_update ? &sgd : nullptr;
+    if (tiled) {
+      omni::linear_wgrad_f32_batch(st, jobs.data() + skip, (int)jobs.size() - skip, net->P_stride, c.seg,
+                                   fused_head ? jobs.data() : nullptr, upd, ts.timer());
+    } else {
+      const omni::HeadLossParams hl{c.labels, last.d.cout, c.loss_rows, c.loss_per_worker, c.loss, c.status};
+      omni::linear_wgrad_f32_small(st, jobs.data(), (int)jobs.size(), net->P_stride, c.seg, fused_head ? &hl : nullptr,
+                                   upd, ts.timer());
+    }
   }
   for (size_t t = 0; t < net->tensors.size(); ++t)
     net->grad_view[t] = (written[t] || (int)t == logits) ? net->tensors[t].grad_off : kNoGrad;
@@ -787,9 +763,11 @@ void step_bf16(StepCtx& c) {
     if (need_dx) written[last.in0] = 1;
     c.fork();
     c.forked = true;
-    omni::head_wgrad_loss(c.side, true, dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.seg, c.G + last.w_off,
-                          last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows, c.loss_per_worker,
-                          c.loss, c.status);
+    omni::head_wgrad_loss(c.side, true,
+                          omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
+                                                last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
+                                                c.loss_per_worker, c.loss, c.status},
+                          c.seg);
   }
 
   // ---- backward
@@ -986,6 +964,11 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
   c.status = reinterpret_cast<uint32_t*>(c.ws + net->status_off);
   c.loss_per_worker = loss_per_worker;
   c.loss = loss;
+  c.lr = lr;
+  // (a caller that times the update, or wants the aggregated gradient stored, gets it as a launch of its own:
+  // the same sums in the same order, so the results are the same bit for bit)
+  c.fuse_update = net->dtype == OMNI_F32 && !(flags & (OMNI_STEP_NO_UPDATE | OMNI_STEP_KEEP_REDUCED_GRAD)) &&
+                  net->time_class != OMNI_KERNEL_UPDATE;
 
   // ---- a repeated step as a graph: replay, capture, or enqueue launch by launch
   bool capture = false;
@@ -1045,7 +1028,8 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
 
   // ---- weighted aggregation + update
   float* reduced = (flags & OMNI_STEP_KEEP_REDUCED_GRAD) ? reinterpret_cast<float*>(c.ws + net->reduced_off) : nullptr;
-  if (!(flags & OMNI_STEP_NO_UPDATE)) {
+  if (c.fuse_update) {
+  } else if (!(flags & OMNI_STEP_NO_UPDATE)) {
     TimedScope ts(net, c.st, OMNI_KERNEL_UPDATE, -1, true);
     omni::weighted_sgd_f32(c.st, params, c.G, net->P_stride, net->P, c.seg, lr, nullptr, net->velocity,
                            net->momentum, net->weight_decay, ts.timer(), reduced);

@@ -5,10 +5,9 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "update_device.h"
 
 namespace omni {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -99,10 +98,6 @@ __global__ __launch_bounds__(256) void loss_reduce_kernel(const float* __restric
   if (t == 0) loss[0] = total;
 }
 
-struct Lambdas {
-  float v[OMNI_MAX_WORKERS];
-};
-
 __device__ inline uint16_t bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
@@ -118,21 +113,6 @@ __device__ inline uint16_t bf16_rne(float f) {
 // MOM: the momentum / weight-decay update of the paper's experiments (velocity is read and
 // written beside the parameters: (K+4)*4 bytes per parameter instead of (K+2)*4):
 //   d = g + wd*theta;  v = mu*v + d;  theta -= lr*v.
-struct Optim {
-  float lr, momentum, weight_decay;
-};
-
-template <bool MOM>
-__device__ inline void apply_update(v4f& th, v4f& v, const v4f& g, const Optim& o) {
-  if (MOM) {
-    const v4f d = g + o.weight_decay * th;
-    v = o.momentum * v + d;
-    th = th - o.lr * v;
-  } else {
-    th = th - o.lr * g;
-  }
-}
-
 // KEEPG: the aggregated gradient g itself is also written to gout (4 more bytes per parameter; for
 // callers that want to look at it: the update alone never stores it).
 template <bool SHADOW, bool MOM, bool KEEPG>
@@ -238,13 +218,6 @@ void softmax_xent_f32(hipStream_t st, const float* z, const int32_t* labels, int
   hipLaunchKernelGGL(softmax_xent_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, z, labels, C, seg, dz,
                      loss_rows, status);
   hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(256), 0, st, loss_rows, seg, loss_per_worker, loss);
-}
-
-static Lambdas lambdas_of(const Segments& seg) {
-  Lambdas lam{};
-  const double B = (double)seg.off[seg.K];
-  for (int k = 0; k < seg.K; ++k) lam.v[k] = (float)((double)(seg.off[k + 1] - seg.off[k]) / B);
-  return lam;
 }
 
 void weighted_sgd_f32(hipStream_t st, float* params, const float* grads, size_t stride, size_t P,
