@@ -4,15 +4,13 @@
 // With 10 or 100 classes the last layer is far too thin for a matrix-core tile
 // and far too small to fill the chip; what it costs is launches and round trips
 // through HBM.  Two kernels replace six:
-//   1. one wavefront per row: logits z = x w^T + bias, loss_row = logsumexp(z) -
+//   1. sixteen rows per workgroup: logits z = x w^T + bias, loss_row = logsumexp(z) -
 //      z[y], dz = (softmax(z) - onehot(y)) / b_k  (the 1/|b_k| of equation
 //      bspweightedgrads: everything downstream is worker k's MEAN gradient), and
 //      the input gradient dx = dz w (masked by the folded ReLU);
 //   2. per worker: gw_k = dz_k^T x_k and gb_k = sum of dz_k rows, plus (in one
 //      extra workgroup) L_k, the lambda-weighted total loss and the label check.
 #include <hip/hip_runtime.h>
-
-#include <type_traits>
 
 #include "bf16.h"
 #include "common.h"
@@ -31,170 +29,252 @@ __device__ inline int owner(const Segments& seg, int s) {
   while (k + 1 < seg.K && s >= seg.off[k + 1]) ++k;
   return k;
 }
-typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
-template <typename T, bool AL>
-__device__ inline void load_piece(const T* p, float (&v)[Piece<T>::EL]) {
-  if constexpr (AL) {
-    Piece<T>::load(p, v);
-  } else {
-    const v4f t = *reinterpret_cast<const v4f_a4*>(p);
+// T is the storage type of the input rows, the weights and the input gradient (fp32, or bf16 with fp32 arithmetic);
+// CT = 16-class tiles, at least ceil(C / 16).  Sixteen rows per workgroup:
+//   * logits: the four wavefronts split the reduction; both operands arrive in 128-byte lines (8 lanes per row) and turn
+//     into the matrix instruction's layout through wavefront-private LDS, as in gemm_f32_small.hip; the four partial tiles
+//     are added in wavefront order;
+//   * softmax, loss and dz with 16 lanes per row;
+//   * dx = dz w on the fp32 matrix instruction (dz stays fp32), a wavefront taking 16 rows x 16 pieces of columns at a time.
+// One wavefront per row with a lane reduction per class took 8.7 us for 10 classes, 13 for 37 and 34 for 100 (480 rows of
+// 1024, 333 of 243, 2048 of 512 inputs), nearly all of it waiting: for the classes' weight rows and between the lanes.
+// Rows may start at any multiple of the element size (bf16: 16 bytes); a piece that would run past the end of a row is moved
+// back to end there, and elements it shares with the piece before count once.
+constexpr int kLineFloats = 36;   // a 128-byte line in LDS, padded: conflict-free writes and fragment reads
+
+template <typename T> struct HeadOps;
+template <> struct HeadOps<float> {
+  __device__ static inline v4f load(const float* p) { return *reinterpret_cast<const v4f_a4*>(p); }
+  __device__ static inline void zero_below(v4f& f, int lo) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = e < lo ? 0.f : f[e];
+  }
+  __device__ static inline v4f mma(v4f a, v4f b, v4f c) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], c, 0, 0, 0);
+    return c;
+  }
+  __device__ static inline void unpack(v4f t, float (&v)[4]) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = t[e];
   }
+  __device__ static inline void store(float* p, const float (&v)[4]) {
+    *reinterpret_cast<v4f_a4*>(p) = v4f{v[0], v[1], v[2], v[3]};
+  }
+};
+template <> struct HeadOps<bf16_t> {
+  typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+  __device__ static inline v4f load(const bf16_t* p) { return *reinterpret_cast<const v4f*>(p); }
+  __device__ static inline void zero_below(v4f& f, int lo) {   // (rows are whole pieces: all or nothing)
+    if (lo > 0) f = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ static inline v4f mma(v4f a, v4f b, v4f c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+  }
+  __device__ static inline void unpack(v4f t, float (&v)[8]) {
+    const u32x4 u = __builtin_bit_cast(u32x4, t);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      v[2 * d] = bf16_lo(u[d]);
+      v[2 * d + 1] = bf16_hi(u[d]);
+    }
+  }
+  __device__ static inline void store(bf16_t* p, const float (&v)[8]) { Piece<bf16_t>::store(p, v); }
+};
+
+// sums and maxima over the 16 lanes of a row, left in every one of them
+__device__ inline float row16_sum(float v) {
+  v += dpp_move<0xB1>(v);
+  v += dpp_move<0x4E>(v);
+  v += dpp_move<0x141>(v);
+  return v + dpp_move<0x140>(v);
+}
+__device__ inline float row16_max(float v) {
+  v = fmaxf(v, dpp_move<0xB1>(v));
+  v = fmaxf(v, dpp_move<0x4E>(v));
+  v = fmaxf(v, dpp_move<0x141>(v));
+  return fmaxf(v, dpp_move<0x140>(v));
 }
 
-// AL = false (fp32 only): rows may start at any multiple of 4 bytes and have any length of at least one piece; the
-// last piece of a row is moved back to end there and the elements it shares with the piece before count once.
-// T is the storage type of the input rows, the weights and the input gradient
-// (fp32, or bf16 with fp32 arithmetic).  NV = 16-byte pieces of the input row
-// each lane keeps in registers; one piece per lane covers 64 * EL consecutive
-// inputs across the wavefront, so cin <= 64 * EL * NV.
-// WLDS: the whole weight matrix (at most 48 KB) is copied into LDS once per workgroup, while
-// the input rows are on their way, and both passes over it (logits, input gradient) read it
-// there.  A wavefront then waits for memory once instead of once per group of classes in each
-// pass; with one row per wavefront and two wavefronts per compute unit that chain of round
-// trips, not bandwidth, is what the kernel's time consists of.
-template <typename T, int NV, bool WLDS, bool AL>
-__global__ __launch_bounds__(256) void head_fwd_loss_dgrad_kernel(
+// Few classes: eight wavefronts and four chunks in flight, since all of it is waiting; more classes fill the registers.
+template <int CT> constexpr int head_waves() { return CT == 1 ? 8 : 4; }
+
+template <typename T, int CT>
+__global__ __launch_bounds__(64 * head_waves<CT>()) void head_fwd_loss_dgrad_kernel(
     const T* __restrict__ x, const T* __restrict__ w, const float* __restrict__ bias,
     const int32_t* __restrict__ labels, int cin, int C, Segments seg, float* __restrict__ z,
-    float* __restrict__ dz, float* __restrict__ loss_rows, int use_mask, T* __restrict__ dx, int accumulate) {
-  constexpr int EL = Piece<T>::EL;
-  constexpr int CH = NV * EL <= 16 ? 8 : 4;   // classes whose weight rows are in flight together
-  __shared__ float zbuf[4][kMaxClasses];
-  extern __shared__ __attribute__((aligned(16))) unsigned char wl_raw[];
-  const T* wp = WLDS ? reinterpret_cast<const T*>(wl_raw) : w;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int rows = seg.off[seg.K];
-  const int row_raw = blockIdx.x * 4 + wv;
-  const bool live = row_raw < rows;
-  const int row = live ? row_raw : rows - 1;   // idle wavefronts shadow the last row and write nothing
-  const T* xr = x + (size_t)row * cin;
+    float* __restrict__ dz, float* __restrict__ loss_rows, int use_mask, T* __restrict__ dx) {
+  typedef HeadOps<T> Ops;
+  constexpr int EL = Piece<T>::EL, kLine = 8 * EL;      // elements per 16-byte piece, per 128-byte line
+  constexpr int NW = head_waves<CT>(), D = CT == 1 ? 4 : 2;
+  constexpr int kClasses = 16 * CT, kZ = kClasses + 1;
+  constexpr int kWave = (16 + kClasses) * kLineFloats;  // a wavefront's staging block
+  static_assert(kWave >= 16 * kZ, "the partial logits reuse the staging block");
+  __shared__ __attribute__((aligned(16))) float lds[NW * kWave];
+  __shared__ float zbuf[16][kZ];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4, lrow = lane >> 3, lp = lane & 7;
+  const int rows = seg.off[seg.K], row0 = (int)blockIdx.x * 16;
 
-  // ---- logits: the row stays in registers, weight rows stream past it.
-  // Loads are unconditional (an out-of-range piece re-reads piece 0 and is zeroed
-  // afterwards): guarded loads would serialise behind per-load waits.
-  float a[NV][EL];
-  int kk[NV];
+  // ---- logits
+  float* la = lds + wave * kWave;
+  float* lb = la + 16 * kLineFloats;
+  const T* xrow[2];
+  const T* wrow[2 * CT];
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int k = (lane + 64 * i) * EL;
-    kk[i] = k < cin ? (AL ? k : min(k, cin - EL)) : 0;
-    load_piece<T, AL>(xr + kk[i], a[i]);
-  }
-  if (WLDS) {
-    const int npieces = C * cin / EL;          // 16-byte pieces; with AL, cin is a multiple of EL
-    typedef typename std::conditional<AL, u32x4, u32x4_a4>::type src_t;
-    const src_t* src = reinterpret_cast<const src_t*>(w);
-    u32x4* dst = reinterpret_cast<u32x4*>(wl_raw);
-    if (!AL && (int)threadIdx.x < C * cin - npieces * EL)
-      reinterpret_cast<T*>(wl_raw)[npieces * EL + threadIdx.x] = w[npieces * EL + threadIdx.x];
-    // eight pieces per thread in flight at a time (a piece past the end re-reads the last one)
-    for (int q0 = threadIdx.x; q0 < npieces; q0 += 256 * 8) {
-      u32x4 t[8];
+  for (int i = 0; i < 2; ++i) xrow[i] = x + (size_t)min(row0 + lrow + 8 * i, rows - 1) * cin;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = src[min(q0 + 256 * u, npieces - 1)];
+  for (int i = 0; i < 2 * CT; ++i) wrow[i] = w + (size_t)min(lrow + 8 * i, C - 1) * cin;
+  v4f acc[CT];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (q0 + 256 * u < npieces) dst[q0 + 256 * u] = t[u];
+  for (int j = 0; j < CT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+  const int nc = (cin + kLine - 1) / kLine;
+  const int cb = wave * nc / NW, ce = (wave + 1) * nc / NW;
+  v4f xa[D][2], wa[D][2 * CT];
+  auto fetch = [&](int set, int ch) {
+    const int k = min(min(ch, nc - 1) * kLine + lp * EL, cin - EL);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) xa[set][i] = Ops::load(xrow[i] + k);
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) wa[set][i] = Ops::load(wrow[i] + k);
+  };
+  auto multiply = [&](int set, int ch) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *reinterpret_cast<v4f*>(la + (lrow + 8 * i) * kLineFloats + lp * 4) = xa[set][i];
+#pragma unroll
+    for (int i = 0; i < 2 * CT; ++i) *reinterpret_cast<v4f*>(lb + (lrow + 8 * i) * kLineFloats + lp * 4) = wa[set][i];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      v4f a = *reinterpret_cast<const v4f*>(la + r * kLineFloats + 16 * s + 4 * g);
+      const int k = ch * kLine + (4 * s + g) * EL;       // first element of this lane's piece, before it was moved back
+      if ((ch + 1) * kLine > cin) Ops::zero_below(a, k >= cin ? EL : k - min(k, cin - EL));
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        acc[j] = Ops::mma(a, *reinterpret_cast<const v4f*>(lb + (16 * j + r) * kLineFloats + 16 * s + 4 * g), acc[j]);
     }
-    __syncthreads();
-  }
+  };
+  if (ce > cb) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int k = (lane + 64 * i) * EL;
+    for (int d = 0; d < D; ++d) fetch(d, min(cb + d, ce - 1));
+    int ch = cb;
+    for (; ch + D < ce; ch += D) {
 #pragma unroll
-    for (int e = 0; e < EL; ++e)
-      if (k >= cin || (!AL && kk[i] + e < k)) a[i][e] = 0.f;
-  }
-  for (int c0 = 0; c0 < C; c0 += CH) {
-    float acc[CH];
-#pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      acc[j] = 0.f;
-      const int c = min(c0 + j, C - 1);
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        float wv_[EL];
-        load_piece<T, AL>(wp + (size_t)c * cin + kk[i], wv_);
-#pragma unroll
-        for (int e = 0; e < EL; ++e) acc[j] += a[i][e] * wv_[e];
+      for (int d = 0; d < D; ++d) {
+        multiply(d, ch + d);
+        fetch(d, min(ch + d + D, ce - 1));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
-    for (int j = 0; j < CH; ++j) {
-      const float s = wave_sum(acc[j]);
-      if (lane == j && c0 + j < C) zbuf[wv][c0 + j] = s + (bias ? bias[c0 + j] : 0.f);
-    }
+    for (int d = 0; d < D; ++d)
+      if (ch + d < ce) multiply(d, ch + d);
   }
+  // what the input gradient of this wavefront's first columns needs travels while the loss is computed
+  const int col_tiles = (cin + 16 * EL - 1) / (16 * EL);
+  auto column = [&](int ct) { return min((min(ct, col_tiles - 1) * 16 + r) * EL, cin - EL); };
+  v4f xm[4], wt[4];
+  auto fetch_cols = [&](int col) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xm[v] = Ops::load(x + (size_t)min(row0 + 4 * g + v, rows - 1) * cin + col);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) wt[t] = Ops::load(w + col + (size_t)min(4 * t + g, C - 1) * cin);
+  };
+  if (dx != nullptr) fetch_cols(column(wave));
+#pragma unroll
+  for (int j = 0; j < CT; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) la[(4 * g + v) * kZ + 16 * j + r] = acc[j][v];
   __syncthreads();
 
-  // ---- loss and dz
-  const int k_own = owner(seg, row);
-  const float inv_b = 1.0f / (float)(seg.off[k_own + 1] - seg.off[k_own]);
-  const int y = labels[row];
-  const bool bad = (y < 0 || y >= C);
-  float m = -INFINITY;
-  for (int c = lane; c < C; c += 64) m = fmaxf(m, zbuf[wv][c]);
-  m = wave_max(m);
-  float s = 0.f;
-  for (int c = lane; c < C; c += 64) s += expf(zbuf[wv][c] - m);
-  s = wave_sum(s);
-  const float lse = logf(s);
-  if (live && lane == 0) loss_rows[row] = bad ? 0.f : lse - (zbuf[wv][bad ? 0 : y] - m);
-  for (int c = lane; c < C; c += 64) {
-    const float zc = zbuf[wv][c];
-    float p = expf(zc - m - lse);
-    if (c == y) p -= 1.0f;
-    p = bad ? 0.f : p * inv_b;
-    if (live) {
-      z[(size_t)row * C + c] = zc;
-      dz[(size_t)row * C + c] = p;
+  // ---- loss and dz: lane group tid / 16 has row tid / 16, its lanes the classes lane, lane + 16, ...
+  if (tid < 256) {
+    const int lr = tid >> 4, row = row0 + lr, cl = tid & 15;
+    const bool live = row < rows;
+    const int rr = live ? row : rows - 1;
+    float zc[CT], m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int c = 16 * j + cl, at = lr * kZ + c;
+      zc[j] = lds[at];
+#pragma unroll
+      for (int ww = 1; ww < NW; ++ww) zc[j] += lds[ww * kWave + at];
+      if (c < C) {
+        if (bias) zc[j] += bias[c];
+        m = fmaxf(m, zc[j]);
+      }
     }
-    zbuf[wv][c] = p;        // the lane that read this slot overwrites it
+    m = row16_max(m);
+    const int y = labels[rr];
+    const bool bad = y < 0 || y >= C;
+    float s = 0.f, zy = 0.f;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int c = 16 * j + cl;
+      if (c < C) s += expf(zc[j] - m);
+      zy += c == y ? zc[j] : 0.f;
+    }
+    s = row16_sum(s);
+    zy = row16_sum(zy);
+    const float lse = logf(s);
+    const int k_own = owner(seg, rr);
+    const float inv_b = 1.0f / (float)(seg.off[k_own + 1] - seg.off[k_own]);
+    if (live && cl == 0) loss_rows[row] = bad ? 0.f : lse - (zy - m);
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int c = 16 * j + cl;
+      float p = 0.f;
+      if (c < C) {
+        p = expf(zc[j] - m - lse);
+        if (c == y) p -= 1.0f;
+        p = bad ? 0.f : p * inv_b;
+        if (live) {
+          z[(size_t)row * C + c] = zc[j];
+          dz[(size_t)row * C + c] = p;
+        }
+      }
+      zbuf[lr][c] = p;
+    }
   }
   __syncthreads();
+  if (dx == nullptr) return;
 
   // ---- input gradient dx = dz w, masked by the folded ReLU (the input row itself)
-  if (dx != nullptr && live) {
-    float g[NV][EL];
+  float da[4 * CT];      // dz of row r, class 4 t + g
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
+  for (int t = 0; t < 4 * CT; ++t) da[t] = zbuf[r][4 * t + g];
+  const int nt = (C + 3) / 4;
+  for (int ct = wave; ct < col_tiles; ct += NW) {
+    const int col = column(ct);
+    v4f o[EL];
 #pragma unroll
-      for (int e = 0; e < EL; ++e) g[i][e] = 0.f;
-#pragma unroll 4
-    for (int c = 0; c < C; ++c) {
-      const float d = zbuf[wv][c];
+    for (int e = 0; e < EL; ++e) o[e] = v4f{0.f, 0.f, 0.f, 0.f};
+    v4f mk[4];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        float wv_[EL];
-        load_piece<T, AL>(wp + (size_t)c * cin + kk[i], wv_);
+    for (int v = 0; v < 4; ++v) mk[v] = xm[v];
 #pragma unroll
-        for (int e = 0; e < EL; ++e) g[i][e] += d * wv_[e];
+    for (int t0 = 0; t0 < 4 * CT; t0 += 4) {
+      if (t0 >= nt) break;
+      if (t0 > 0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wt[t] = Ops::load(w + col + (size_t)min(4 * (t0 + t) + g, C - 1) * cin);
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        float b[EL];
+        Ops::unpack(wt[t], b);
+#pragma unroll
+        for (int e = 0; e < EL; ++e) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[t0 + t], b[e], o[e], 0, 0, 0);
       }
     }
+    if (ct + NW < col_tiles) fetch_cols(column(ct + NW));
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int k = (lane + 64 * i) * EL;
-      if (k >= cin) continue;
-      const size_t idx = (size_t)row * cin + kk[i];
-      if (use_mask) {
+    for (int v = 0; v < 4; ++v) {
+      const int row = row0 + 4 * g + v;
+      float t[EL], m[EL];
+      if (use_mask) Ops::unpack(mk[v], m);
 #pragma unroll
-        for (int e = 0; e < EL; ++e) g[i][e] = a[i][e] > 0.f ? g[i][e] : 0.f;
-      }
-      if (accumulate) {
-        float old[EL];
-        load_piece<T, AL>(dx + idx, old);
-#pragma unroll
-        for (int e = 0; e < EL; ++e) g[i][e] += old[e];
-      }
-      if constexpr (AL) {
-        Piece<T>::store(dx + idx, g[i]);
-      } else {
-#pragma unroll
-        for (int e = 0; e < EL; ++e)
-          if (kk[i] + e >= k) dx[idx + e] = g[i][e];
-      }
+      for (int e = 0; e < EL; ++e) t[e] = !use_mask || m[e] > 0.f ? o[e][v] : 0.f;
+      if (row < rows) Ops::store(dx + (size_t)row * cin + col, t);
     }
   }
 }
@@ -217,45 +297,27 @@ bool head_supported(int cin, int classes, const void* x, const void* w, bool bf1
 template <typename T>
 static void launch_head_fwd(hipStream_t st, const T* x, const T* w, const float* bias, const int32_t* labels, int cin,
                             int classes, const Segments& seg, float* z, float* dz, float* loss_rows, bool use_mask,
-                            T* dx, bool accumulate) {
-  const int rows = seg.off[seg.K];
-  const int nv = (cin + 64 * Piece<T>::EL - 1) / (64 * Piece<T>::EL);
-  const dim3 grid((rows + 3) / 4), block(256);
-  const int acc = accumulate ? 1 : 0, um = use_mask ? 1 : 0;
-  const size_t wbytes = (size_t)classes * cin * sizeof(T);
-  const bool wlds = wbytes <= 48 * 1024;
-  const bool aligned = cin % Piece<T>::EL == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w) |
-                                                    reinterpret_cast<uintptr_t>(dx)) & 15u) == 0;
-#define OMNI_HEAD2(NV, WL, AL)                                                                                        \
-  hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, NV, WL, AL>), grid, block, WL ? wbytes : 0, st, x, w, bias, labels, \
-                     cin, classes, seg, z, dz, loss_rows, um, dx, acc)
-#define OMNI_HEAD(NV)                                             \
-  do {                                                            \
-    if (aligned) {                                                \
-      if (wlds) OMNI_HEAD2(NV, true, true);                       \
-      else OMNI_HEAD2(NV, false, true);                           \
-    } else if constexpr (Piece<T>::EL == 4) {                     \
-      if (wlds) OMNI_HEAD2(NV, true, false);                      \
-      else OMNI_HEAD2(NV, false, false);                          \
-    }                                                             \
-  } while (0)
-  if (nv <= 1) OMNI_HEAD(1);
-  else if (nv <= 2) OMNI_HEAD(2);
-  else if (nv <= 4) OMNI_HEAD(4);
-  else if constexpr (Piece<T>::EL == 4) OMNI_HEAD(8);
+                            T* dx) {
+  const dim3 grid((seg.off[seg.K] + 15) / 16);
+  const int um = use_mask ? 1 : 0;
+#define OMNI_HEAD(CT)                                                                                                 \
+  hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, CT>), grid, dim3(64 * head_waves<CT>()), 0, st, x, w, bias, labels, cin, classes, seg, z, \
+                     dz, loss_rows, um, dx)
+  if (classes <= 16) OMNI_HEAD(1);
+  else if (classes <= 48) OMNI_HEAD(3);
+  else OMNI_HEAD(8);
 #undef OMNI_HEAD
-#undef OMNI_HEAD2
 }
 
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
                          const int32_t* labels, int cin, int classes, const Segments& seg, float* z, float* dz,
-                         float* loss_rows, bool use_mask, void* dx, bool accumulate) {
+                         float* loss_rows, bool use_mask, void* dx) {
   if (bf16)
     launch_head_fwd<bf16_t>(st, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias, labels, cin,
-                            classes, seg, z, dz, loss_rows, use_mask, static_cast<bf16_t*>(dx), accumulate);
+                            classes, seg, z, dz, loss_rows, use_mask, static_cast<bf16_t*>(dx));
   else
     launch_head_fwd<float>(st, static_cast<const float*>(x), static_cast<const float*>(w), bias, labels, cin, classes,
-                           seg, z, dz, loss_rows, use_mask, static_cast<float*>(dx), accumulate);
+                           seg, z, dz, loss_rows, use_mask, static_cast<float*>(dx));
 }
 
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg) {

@@ -89,10 +89,10 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
 // True if the fused head kernels can take this shape (else use the generic path).
 bool head_supported(int cin, int classes, const void* x, const void* w, bool bf16);
 // z = x w^T + bias; loss_rows, dz = (softmax(z) - onehot)/b_k; optionally
-// dx (+)= dz w, zeroed where x <= 0 if use_mask (dx may be null when the input needs no gradient).
+// dx = dz w, zeroed where x <= 0 if use_mask (dx may be null when the input needs no gradient).
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
                          const int32_t* labels, int cin, int classes, const Segments& seg, float* z, float* dz,
-                         float* loss_rows, bool use_mask, void* dx, bool accumulate);
+                         float* loss_rows, bool use_mask, void* dx);
 // Per worker: gw_k = dz_k^T x_k, gb_k = column sums of dz_k; plus L_k, the total
 // loss and the status word (bit 0: some label outside [0, classes)).
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg);

@@ -533,7 +533,7 @@ void step_f32(StepCtx& c) {
     omni::head_fwd_loss_dgrad(st, false, act(last.in0), params + last.w_off,
                               last.has_b ? params + last.b_off : nullptr, c.labels, last.d.cin, last.d.cout, c.seg,
                               actw(logits), grad(logits), c.loss_rows, need_dx && net->tensors[last.in0].relu,
-                              need_dx ? grad(last.in0) : nullptr, false);
+                              need_dx ? grad(last.in0) : nullptr);
     if (need_dx) written[last.in0] = 1;
   } else {
     TimedScope ts(net, st, OMNI_KERNEL_LOSS, n_layers - 1);
@@ -759,7 +759,7 @@ void step_bf16(StepCtx& c) {
     omni::head_fwd_loss_dgrad(st, true, act(last.in0), shadow + last.wsh_off,
                               last.has_b ? c.params + last.b_off : nullptr, c.labels, last.d.cin, last.d.cout, c.seg,
                               z, dz, c.loss_rows, need_dx && net->tensors[last.in0].relu,
-                              need_dx ? grad(last.in0) : nullptr, false);
+                              need_dx ? grad(last.in0) : nullptr);
     if (need_dx) written[last.in0] = 1;
     c.fork();
     c.forked = true;
