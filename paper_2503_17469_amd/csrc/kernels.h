@@ -148,6 +148,22 @@ struct BnStatRequest {
   ShareTable table;
   bool done;
 };
+// Hidden fully connected layers (gemm_bf16.hip); widths are multiples of 8.
+// c[M][N] = a[M][K] b[N][K]^T (+bias) (ReLU), zeroed where mask <= 0 (mask may be null): forward with b = the weight copy,
+// input gradient with b = the transposed copy.
+void linear_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* c, int M, int N, int K, const float* bias,
+                 bool relu, const bf16_t* mask);
+struct LinearWgradBf16Job {
+  const bf16_t* dy;      // [rows][cout]
+  const bf16_t* x;       // [rows][cin]
+  float* gw;             // worker 0's [cout][cin]
+  float* gb;             // worker 0's [cout], may be null
+  int cin, cout;
+  size_t w_off, b_off;   // the layer's weight and bias in the parameter vector
+};
+// As linear_wgrad_f32_batch.
+void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
+                       const LinearWgradBf16Job* head, const SgdArgs* sgd, const KernelTimer* timer = nullptr);
 size_t conv_wgrad_partial_floats();
 bool conv_shape_supported(const ConvGeom& g, long positions);
 // out[M][N] = gather(src)[M][K] * wgt[N][K]^T (+bias) (ReLU) (masked where mask <= 0) (+= out)

@@ -70,6 +70,7 @@ struct omni_net {
   // did not store it).  Two tensors may share a buffer: a residual add hands its output gradient on.
   std::vector<size_t> grad_view;
   int classes = 0;
+  bool linear_only = false;         // fully connected layers only
   const void* ws_ready = nullptr;   // workspace of the last step
   // optimiser: velocity == nullptr is plain SGD
   float* velocity = nullptr;
@@ -332,6 +333,8 @@ int omni_net_create(const omni_layer_desc* descs, int32_t n, int32_t in_h, int32
     for (Tensor& t : net->tensors)
       if (t.relu && t.esize == 2 && t.c % 64 == 0) t.bits_off = take((size_t)B_max * t.elems / 8);
   net->ws_bytes = pos;
+  net->linear_only = std::all_of(net->layers.begin(), net->layers.end(),
+                                 [](const Layer& L) { return L.fused_away || L.d.op == OMNI_OP_LINEAR; });
   net->grad_view.assign(net->tensors.size(), kNoGrad);
   *out = net;
   return OMNI_OK;
@@ -495,7 +498,7 @@ struct StepCtx {
   float* loss_per_worker;
   float* loss;
   float lr;
-  bool fuse_update;      // fp32: the weight-gradient launch applies the update
+  bool fuse_update;      // fully connected networks: the weight-gradient launch applies the update
 };
 
 // ------------------------------------------------------------------ fp32 path
@@ -705,6 +708,11 @@ void step_bf16(StepCtx& c) {
       // what it stores), which the kernels that hold a worker-pure group of positions take
       const bool bn_next = L.d.op == OMNI_OP_CONV && nx < n_layers - 1 && net->layers[nx].d.op == OMNI_OP_BN &&
                            net->layers[nx].in0 == L.out && !to.relu && !L.has_b;
+      if (L.d.op == OMNI_OP_LINEAR) {
+        omni::linear_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows, L.d.cout, L.d.cin,
+                          L.has_b ? c.params + L.b_off : nullptr, to.relu, nullptr);
+        continue;
+      }
       omni::BnStatRequest offer{bn_partial, &c.seg, {}, false};
       const bool pooled =
           omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g,
@@ -761,9 +769,11 @@ void step_bf16(StepCtx& c) {
                               z, dz, c.loss_rows, need_dx && net->tensors[last.in0].relu,
                               need_dx ? grad(last.in0) : nullptr);
     if (need_dx) written[last.in0] = 1;
-    c.fork();
-    c.forked = true;
-    omni::head_wgrad_loss(c.side, true,
+    if (!net->linear_only) {   // (a network of fully connected layers is too short a chain to fork from)
+      c.fork();
+      c.forked = true;
+    }
+    omni::head_wgrad_loss(net->linear_only ? st : c.side, true,
                           omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                                 last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
                                                 c.loss_per_worker, c.loss, c.status},
@@ -799,6 +809,11 @@ void step_bf16(StepCtx& c) {
     }
     return -1;
   };
+  std::vector<omni::LinearWgradBf16Job> linear_jobs;   // linear_only: every hidden layer's, in one launch at the end
+  auto linear_job = [&](const Layer& L) {
+    return omni::LinearWgradBf16Job{grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin,
+                                    L.d.cout, L.w_off, L.b_off};
+  };
   for (int i = n_layers - 2; i >= 0; --i) {
     const Layer& L = net->layers[i];
     if (L.fused_away) continue;
@@ -810,7 +825,7 @@ void step_bf16(StepCtx& c) {
       // them do, the first layer's included.  The point they wait for is recorded first, then the
       // input gradient goes to the main stream, and only then are the side stream's wait and
       // launches issued: the main chain (the longer one) never waits for those host calls.
-      hipEvent_t ready = c.fork_record();
+      hipEvent_t ready = net->linear_only ? nullptr : c.fork_record();
       const int takes_me = conv && L.in0 >= 0 ? entry_partner(i) : -1;
       if (takes_me >= 0) partner[takes_me] = i;   // (this projection's input gradient rides with that convolution's)
       bool dgrad_done = takes_me >= 0;
@@ -840,12 +855,19 @@ void step_bf16(StepCtx& c) {
         const int m_rows = conv ? rows * L.ih * L.iw : rows;
         const bf16_t* addend = pending_add[L.in0];
         pending_add[L.in0] = nullptr;
-        d.mask_bits = (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr;
-        omni::conv_gemm_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), m_rows, L.cin_pad, d, nullptr,
-                             ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend);
+        if (!conv && !addend && !written[L.in0]) {
+          omni::linear_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), rows, L.d.cin, L.d.cout, nullptr, false,
+                            ti.relu ? act(L.in0) : nullptr);
+        } else {
+          d.mask_bits = (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr;
+          omni::conv_gemm_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), m_rows, L.cin_pad, d, nullptr,
+                               ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend);
+        }
         written[L.in0] = 1;
       }
-      {
+      if (net->linear_only) {
+        linear_jobs.push_back(linear_job(L));
+      } else {
         const bool use2 = second && c.side2 != c.side;
         second = !second;
         c.fork_wait(use2 ? c.side2 : c.side, ready);
@@ -854,6 +876,11 @@ void step_bf16(StepCtx& c) {
         hipStream_t ws_ = use2 ? c.side2 : c.side;
         TimedScope ts(net, ws_, conv ? OMNI_KERNEL_CONV_WGRAD : OMNI_KERNEL_LINEAR_WGRAD, i);
         const int pl = pooled_from[i];
+        if (!conv) {
+          const omni::LinearWgradBf16Job job = linear_job(L);
+          omni::linear_wgrad_bf16(ws_, &job, 1, net->P_stride, c.seg, nullptr, nullptr);
+          continue;
+        }
         omni::conv_wgrad_bf16(ws_, grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr,
                               net->P_stride, L.d.cout, L.d.cin, g, c.seg, use2 ? conv_partial2 : conv_partial,
                               conv_counters,
@@ -908,6 +935,16 @@ void step_bf16(StepCtx& c) {
                          L.ih * L.iw, L.ic, written[L.in0] != 0);
       written[L.in0] = 1;
     }
+  }
+  if (net->linear_only && (!linear_jobs.empty() || c.fuse_update)) {
+    TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);
+    const omni::SgdArgs sgd{c.params, net->velocity, c.lr, net->momentum, net->weight_decay};
+    omni::LinearWgradBf16Job head{};
+    head.gw = c.G + last.w_off;
+    head.gb = last.has_b ? c.G + last.b_off : nullptr;
+    head.cin = last.d.cin; head.cout = last.d.cout; head.w_off = last.w_off; head.b_off = last.b_off;
+    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg, &head,
+                            c.fuse_update ? &sgd : nullptr, ts.timer());
   }
   for (size_t t = 0; t < net->tensors.size(); ++t) {
     const bool have = (written[t] && !not_stored[t]) || (int)t == last.out;
@@ -967,7 +1004,7 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
   c.lr = lr;
   // (a caller that times the update, or wants the aggregated gradient stored, gets it as a launch of its own:
   // the same sums in the same order, so the results are the same bit for bit)
-  c.fuse_update = net->dtype == OMNI_F32 && !(flags & (OMNI_STEP_NO_UPDATE | OMNI_STEP_KEEP_REDUCED_GRAD)) &&
+  c.fuse_update = net->linear_only && !(flags & (OMNI_STEP_NO_UPDATE | OMNI_STEP_KEEP_REDUCED_GRAD)) &&
                   net->time_class != OMNI_KERNEL_UPDATE;
 
   // ---- a repeated step as a graph: replay, capture, or enqueue launch by launch
