@@ -135,16 +135,24 @@ def _check(rc):
 
 
 def _i32(seq: Sequence[int]):
-    return (C.c_int32 * len(seq))(*[int(v) for v in seq])
+    try:
+        return (C.c_int32 * len(seq))(*seq)
+    except TypeError:               # entries that are no Python integers
+        return (C.c_int32 * len(seq))(*[int(v) for v in seq])
 
 
 def _stream():
+    """Handle of the current stream (a step of a small net is a few microseconds of host work: the stream object
+    torch.cuda.current_stream() builds cost three of them)."""
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 # ------------------------------------------------------------------ controller
