@@ -45,6 +45,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "kernels.h"
+#include "pool_device.h"
 
 namespace omni {
 
@@ -459,17 +460,6 @@ struct Conv3Params {
 };
 constexpr int kUnitD = 256;
 
-// Where the gradient of a 2 x 2 max pooling goes: the first of the four inputs (scan order (0,0),
-// (0,1), (1,0), (1,1)) that holds the maximum, or nowhere (4) when a ReLU folded into the pooled
-// tensor has zeroed the maximum.  The comparison is on the values as stored (bf16).
-__device__ inline uint32_t pool_code_of(float a, float b, float c, float d, bool relu, float& m) {
-  m = a;
-  uint32_t k = 0;
-  if (b > m) { m = b; k = 1; }
-  if (c > m) { m = c; k = 2; }
-  if (d > m) { m = d; k = 3; }
-  return (relu && !(m > 0.f)) ? 4u : k;
-}
 __device__ inline float as_stored(float v) { return bf16_to_f32(f32_to_bf16(v)); }
 constexpr int kRowD = 64 + 8;   // elements per LDS row (144 bytes): 16-byte reads land 4 banks apart
 constexpr int kMaxPatchPieces = 13;   // 16-byte pieces of the patch per thread (up to 416 patch positions)
@@ -2014,6 +2004,8 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
                     const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
                     bf16_t* pool_out, uint8_t* pool_code, const bf16_t* addend, BnStatRequest* stats) {
   bool pooled = false;
+  if (g.frag)
+    return conv_frag_bf16(st, src, wgt, out, N, g, bias, mask, relu, accumulate, pool_out, pool_code, addend, stats);
   // 3x3 / stride 1 / pad 1: the wide-tile kernel where the shape and the amount of work allow it (it has no
   // pooling epilogue), else the 256-position one
   if (!(pool_out && pool_code) &&

@@ -1,0 +1,498 @@
+// Convolutions of few positions in bf16 (fp32 accumulation): forward of 3x3 / pad-1 and 1x1 layers of stride 1 or 2 and
+// the input gradient of stride-1 layers, where the tiles of the large-batch kernels would leave most of the chip idle.
+//
+// What bounds such a launch is not arithmetic but how few workgroups it has and how long each one's serial walk
+// over the reduction is: 128 images of the 512-channel 4x4 layers are 64 workgroups of the wide kernel, 4608
+// reduction elements each (74 us for 9.7 GFLOP, 84 us as input gradient).  Here:
+//
+//   * a workgroup owns 64 positions x 64 output channels (a quarter of the wide kernel's tile: 256 workgroups
+//     for that layer), and its four wavefronts divide the REDUCTION: each holds the whole 64 x 64 tile for a
+//     quarter of the input channels (32 x 64 for half of them where there are only 32 or 96), so nothing is
+//     shared while the product runs and there is no barrier inside it;
+//   * the source positions are copied into LDS once, all channels of them (the positions of a tile and their
+//     halo are one contiguous piece of the channels-last tensor); every tap reads them there.  Positions
+//     outside the map are a row of zeros in LDS that the lane's address points at;
+//   * the weights come from the L2 straight into registers, 1 KB per instruction and nine taps ahead: the
+//     weight copy is laid out in the order the matrix instruction wants ([32 outputs][tap][16 channels] blocks of
+//     64 lanes x 8 elements, see frag_offset), which costs nothing as the copy is rewritten every step anyway;
+//   * at the end the partial tiles meet in LDS and are added in wavefront order; each wavefront finishes one 32 x 32
+//     block of the tile: bias, ReLU, mask, residual share, 2 x 2 max pooling, batch-norm sums.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "bf16.h"
+#include "common.h"
+#include "kernels.h"
+#include "pool_device.h"
+
+namespace omni {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+namespace {
+
+constexpr int kThreads = 256;
+constexpr int kTM = 64, kTN = 64;      // positions, output channels per workgroup
+constexpr int kBlock = 64 * 8;         // elements of a weight block: one matrix operand
+constexpr size_t kLdsLimit = 160 * 1024;
+
+struct FragParams {
+  const bf16_t* src;   // [rows][Hs][Ws][Cs]
+  const bf16_t* wgt;   // blocks [N/32][taps][Cs/16]
+  bf16_t* out;         // [rows*Hp*Wp][N]
+  int rows, Hs, Ws, Cs, N, Hp;
+  int wlog, rlog;      // Wp and R as powers of two
+  int nimg, upi;       // a tile is nimg images x R rows; tiles per image (1 where nimg > 1)
+  int PR, npatch;      // patch rows per image, patch positions in all
+  int stride, flip;    // flip: input gradient (mirrored taps)
+  int by_channel;      // which operand an XCD keeps to itself, see the kernel
+  int gK;              // entries of the table below: entry k owns the tiles tfirst[k] .. and the images ifirst[k] ..
+  int32_t tfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
+  const void* zero;
+  const float* bias;
+  const bf16_t* mask;
+  const uint8_t* mask_bits;
+  const bf16_t* addend;
+  int relu, accumulate;
+  bf16_t* pool;
+  uint8_t* pool_code;
+  double* stat_partial;   // [tile][N][2] or null
+};
+
+__device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+
+// One step of the statistics tree (see conv3_wide_bf16.hip): the lane keeps half of its list and adds what its
+// partner, DIST lanes away, holds of the same half.
+template <int DIST, int N, int LEN>
+__device__ inline void stat_exchange(float (&sv)[LEN], int j) {
+  const bool upper = (j & DIST) != 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float keep = upper ? sv[N + i] : sv[i];
+    const float send = upper ? sv[i] : sv[N + i];
+    const float recv = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), (DIST << 10) | 0x1F));
+    sv[i] = keep + recv;
+  }
+}
+
+// KS: shares of the reduction (4: a wavefront has 64 positions and a quarter of the channels; 2: 32 positions and
+// half).  TAPS: 9 or 1.  BWD: mask / addend / accumulate instead of bias / ReLU / pooling / statistics.
+template <int KS, int TAPS, bool BWD>
+__global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
+  constexpr int MA = KS == 4 ? 2 : 1;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 31, h = lane >> 5;
+  const int kg = KS == 4 ? wave : wave & 1;
+  const int pa = KS == 4 ? 0 : wave >> 1;          // first 32-position block of this wavefront
+
+  // Workgroup b runs on XCD b % 8, and every XCD has an L2 of its own: it takes a contiguous run of the tiles, counted
+  // channel tile by channel tile (by_channel: its L2 then holds few channel tiles' weights and most of the source) or
+  // position by position (all weights, few positions).
+  const int tiles = p.tfirst[p.gK], tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n;
+  const int per = (total + 7) / 8;
+  const int at = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+  if (at >= total || ((int)blockIdx.x >> 3) >= per) return;
+  const int tile = p.by_channel ? at % tiles : at / tiles_n;
+  const int col0 = (p.by_channel ? at / tiles : at % tiles_n) * kTN;
+  int gk = 0;
+  while (gk + 1 < p.gK && tile >= p.tfirst[gk + 1]) ++gk;
+  const int tl = tile - p.tfirst[gk];
+  const int R = 1 << p.rlog, Wp = 1 << p.wlog;
+  const int n0 = p.ifirst[gk] + (p.upi == 1 ? tl * p.nimg : tl / p.upi);
+  const int r0 = p.upi == 1 ? 0 : (tl % p.upi) << p.rlog;
+  const int nvalid = min(p.nimg, p.ifirst[gk + 1] - n0);
+  const int npos = nvalid << (p.rlog + p.wlog);
+  const int oc = p.Cs >> 3;
+  const int pitch = p.Cs * 2 + 16;                 // bytes of a patch position: neighbours start 4 banks apart
+  // first source row of the patch; whole maps need no halo rows
+  const int s0 = TAPS == 1 || p.upi == 1 ? 0 : max(r0 * p.stride - 1, 0);
+
+  // ---- the patch: pieces of 16 bytes, thread tid takes pieces tid, tid + 256, ...
+  const bf16_t* const sbase = p.src + (TAPS == 1 ? (size_t)n0 * p.Hs * p.Ws * p.Cs
+                                                 : ((size_t)n0 * p.Hs + s0) * p.Ws * p.Cs);
+  const int npieces = p.npatch * oc;
+  const int live = (p.upi == 1 ? nvalid * p.PR : min(p.PR, p.Hs - s0)) * p.Ws * oc;   // (9 taps) pieces that exist
+  int q = tid / oc, rem = tid - q * oc;            // patch position and octet of the piece
+  const int dq = kThreads / oc, dr = kThreads - dq * oc;
+  int x = tid;
+  u32x4 rp[8];
+  int dst[8];
+  auto load_batch = [&]() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      size_t off;
+      if (TAPS == 1) {
+        const int pq = min(q, p.npatch - 1);
+        const int w = pq & (Wp - 1), r = (pq >> p.wlog) & (R - 1), il = min(pq >> (p.wlog + p.rlog), nvalid - 1);
+        off = ((size_t)(il * p.Hs + (r0 + r) * p.stride) * p.Ws + w * p.stride) * p.Cs + rem * 8;
+      } else {
+        off = (size_t)min(x, live - 1) * 8;        // (what lies past the end is never read back)
+      }
+      rp[i] = *reinterpret_cast<const u32x4*>(sbase + off);
+      dst[i] = x < npieces ? q * pitch + rem * 16 : -1;
+      x += kThreads;
+      q += dq;
+      rem += dr;
+      if (rem >= oc) { rem -= oc; ++q; }
+    }
+  };
+  auto store_batch = [&]() {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (dst[i] >= 0) *reinterpret_cast<u32x4*>(smemF + dst[i]) = rp[i];
+  };
+  load_batch();
+
+  // ---- weights: the first nine taps are on their way while the patch is stored
+  const int c16n = p.Cs >> 4, nC = c16n / KS;
+  const int nb32 = p.N >> 5;
+  const bf16_t* wp[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+    wp[b] = p.wgt + ((size_t)min((col0 >> 5) + b, nb32 - 1) * TAPS * c16n + kg * nC) * kBlock + lane * 8;
+  bf16x8 fb[TAPS][2];
+#pragma unroll
+  for (int t = 0; t < TAPS; ++t)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      fb[t][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wp[b] + (size_t)t * c16n * kBlock));
+
+  // ---- where every tap of this lane's positions lies in the patch
+  const int zrow = p.npatch * pitch;
+  int aaddr[MA][TAPS];
+#pragma unroll
+  for (int a = 0; a < MA; ++a) {
+    const int pos = (pa + a) * 32 + j;
+    const int w = pos & (Wp - 1), r = (pos >> p.wlog) & (R - 1), il = pos >> (p.wlog + p.rlog);
+    if (TAPS == 1) {
+      aaddr[a][0] = pos * pitch + h * 16;
+    } else {
+      const int hh = (r0 + r) * p.stride - 1, ww = w * p.stride - 1;
+#pragma unroll
+      for (int t = 0; t < TAPS; ++t) {
+        const int u = t / 3, v = t - 3 * u;
+        const int sr = hh + (p.flip ? 2 - u : u), sc = ww + (p.flip ? 2 - v : v);
+        const bool in = (unsigned)sr < (unsigned)p.Hs && (unsigned)sc < (unsigned)p.Ws;
+        aaddr[a][t] = (in ? ((il * p.PR + sr - s0) * p.Ws + sc) * pitch : zrow) + h * 16;
+      }
+    }
+  }
+
+  for (int i = tid; i <= oc; i += kThreads) *reinterpret_cast<u32x4*>(smemF + zrow + i * 16) = u32x4{0u, 0u, 0u, 0u};
+  while (true) {
+    store_batch();
+    if (x - tid >= npieces) break;                 // (the same for all threads)
+    load_batch();
+  }
+  __syncthreads();
+
+  // ---- product, transposed (rows = output channels, columns = positions)
+  v16f acc[MA][2];
+#pragma unroll
+  for (int a = 0; a < MA; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+  bf16x8 fa[2][MA];
+  int cofs = kg * nC * 32;
+  auto read_a = [&](bf16x8 (&f)[MA], int t, int ofs) {
+#pragma unroll
+    for (int a = 0; a < MA; ++a) f[a] = as_bf16x8(*reinterpret_cast<const u32x4*>(smemF + aaddr[a][t] + ofs));
+  };
+  auto sixteen_channels = [&](auto more) {
+    constexpr bool MORE = decltype(more)::value;
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) {
+      if (t + 1 < TAPS) read_a(fa[(t + 1) & 1], t + 1, cofs);
+      else if (MORE) read_a(fa[(t + 1) & 1], 0, cofs + 32);
+#pragma unroll
+      for (int a = 0; a < MA; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[t][b], fa[t & 1][a], acc[a][b], 0, 0, 0);
+      if (MORE) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          fb[t][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wp[b] + ((size_t)t * c16n + 1) * kBlock));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (MORE) {
+      if (TAPS & 1) {
+#pragma unroll
+        for (int a = 0; a < MA; ++a) fa[0][a] = fa[1][a];
+      }
+      cofs += 32;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) wp[b] += kBlock;
+    }
+  };
+  read_a(fa[0], 0, cofs);
+  for (int c = 0; c + 1 < nC; ++c) sixteen_channels(std::true_type{});
+  sixteen_channels(std::false_type{});
+
+  // ---- epilogue: this wavefront finishes positions 32 a .. and channels 32 b .. of the tile
+  const int ea = wave >> 1, eb = wave & 1;
+  const int pos = ea * 32 + j;
+  const size_t out_pos = (((size_t)n0 * p.Hp + r0) << p.wlog) + pos;
+  const bool row_in = pos < npos && col0 + eb * 32 < p.N;      // (N is a multiple of 32)
+  const int cb = min(col0 + eb * 32, p.N - 32);
+  const size_t row = out_pos * p.N + cb;
+  const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
+  u32x4 em[2], ea4[2];
+  uint32_t ebits = 0;
+  if (BWD) {
+    const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
+    if (p.mask_bits) ebits = *reinterpret_cast<const uint32_t*>(row_in ? p.mask_bits + (row >> 3) : static_cast<const uint8_t*>(p.zero));
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq) {
+      const size_t idx = row + qq * 16 + h * 8;
+      em[qq] = *reinterpret_cast<const u32x4*>((row_in && p.mask && !p.mask_bits) ? p.mask + idx : zp);
+      ea4[qq] = *reinterpret_cast<const u32x4*>((row_in && other) ? other + idx : zp);
+    }
+  }
+  float bias8[2][8];
+  if (!BWD) {
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bias8[qq][e] = p.bias ? p.bias[cb + qq * 16 + h * 8 + e] : 0.f;
+  }
+  __syncthreads();                                 // nobody reads the patch any more
+  float* const ex = reinterpret_cast<float*>(smemF);   // [position block][channel block][share][v / 4][lane][4]
+#pragma unroll
+  for (int a = 0; a < MA; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        *reinterpret_cast<v4f*>(ex + (size_t)((((pa + a) * 2 + b) * KS + kg) * 4 + v) * 256 + lane * 4) =
+            v4f{acc[a][b][4 * v], acc[a][b][4 * v + 1], acc[a][b][4 * v + 2], acc[a][b][4 * v + 3]};
+  __syncthreads();
+  float s[16];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    v4f t = *reinterpret_cast<const v4f*>(ex + (size_t)((ea * 2 + eb) * KS * 4 + v) * 256 + lane * 4);
+#pragma unroll
+    for (int k = 1; k < KS; ++k)
+      t += *reinterpret_cast<const v4f*>(ex + (size_t)(((ea * 2 + eb) * KS + k) * 4 + v) * 256 + lane * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[4 * v + e] = t[e];
+  }
+  // Register v in lane (j, h) is channel 8 (v/4) + 4 h + v%4; swapping v and v + 4 between the wavefront's halves leaves
+  // runs of eight channels (see conv3_wide_bf16.hip).
+  u32x4 outp[2];
+#pragma unroll
+  for (int qq = 0; qq < 2; ++qq) {
+    float val[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[8 * qq + e]), __float_as_uint(s[8 * qq + 4 + e]),
+                                                        false, false);
+      val[e] = __uint_as_float(sw[0]);
+      val[4 + e] = __uint_as_float(sw[1]);
+    }
+    if (BWD) {
+      const u32x4 mk = em[qq], ad = ea4[qq];
+      if (p.addend) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+      }
+      if (p.mask_bits) {
+        const uint32_t byte = ebits >> (8 * (2 * qq + h));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
+      } else if (p.mask) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
+          val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
+        }
+      }
+      if (p.accumulate) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        val[e] += bias8[qq][e];
+        if (p.relu) val[e] = val[e] > 0.f ? val[e] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
+    if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
+  }
+  if (BWD) return;
+
+  if (p.stat_partial) {
+    // sums of the stored values and of their squares: fp32 over the 32 positions of a block (a fixed tree, entry
+    // which*16 + q*8 + e ends in lane j with bits which, q, e from the top), double over the two blocks
+    float sv[32];
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const float lo = row_in ? bf16_lo(outp[qq][d]) : 0.f, hi = row_in ? bf16_hi(outp[qq][d]) : 0.f;
+        sv[qq * 8 + 2 * d] = lo;
+        sv[qq * 8 + 2 * d + 1] = hi;
+        sv[16 + qq * 8 + 2 * d] = lo * lo;
+        sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
+      }
+    stat_exchange<16, 16>(sv, j);
+    stat_exchange<8, 8>(sv, j);
+    stat_exchange<4, 4>(sv, j);
+    stat_exchange<2, 2>(sv, j);
+    stat_exchange<1, 1>(sv, j);
+    __syncthreads();                               // the partial tiles have been read
+    float* const red = ex;                         // [position block][which][64]
+    red[(ea * 2 + (j >> 4)) * 64 + eb * 32 + ((j >> 3) & 1) * 16 + h * 8 + (j & 7)] = sv[0];
+    __syncthreads();
+    if (tid < 128 && col0 + (tid & 63) < p.N) {
+      const int c = tid & 63, which = tid >> 6;
+      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] =
+          (double)red[which * 64 + c] + (double)red[(2 + which) * 64 + c];
+    }
+  }
+  if (p.pool) {
+    // a tile is whole rows of whole images, an even number of them: its pooled positions are a contiguous run too
+    __syncthreads();
+    constexpr int kRow = kTN + 8;
+    bf16_t* const st = reinterpret_cast<bf16_t*>(smemF);   // [64 positions][kRow]
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+      *reinterpret_cast<u32x4*>(st + pos * kRow + eb * 32 + qq * 16 + h * 8) = outp[qq];
+    __syncthreads();
+    const int pq = tid >> 3, c = (tid & 7) * 8;    // pooled position (16 of them), channel octet
+    if (pq < (npos >> 2) && col0 + c < p.N) {
+      const int whlog = p.wlog - 1;
+      const int pr = pq >> whlog, pc = pq & ((1 << whlog) - 1);
+      const bf16_t* t = st + ((2 * pr << p.wlog) + 2 * pc) * kRow + c;
+      float a[8], b[8], cc[8], d[8], m[8];
+      Piece<bf16_t>::load(t, a);
+      Piece<bf16_t>::load(t + kRow, b);
+      Piece<bf16_t>::load(t + (kRow << p.wlog), cc);
+      Piece<bf16_t>::load(t + (kRow << p.wlog) + kRow, d);
+      u32x2 code = {0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        code[e >> 2] |= pool_code_of(a[e], b[e], cc[e], d[e], p.relu != 0, m[e]) << (8 * (e & 3));
+      const size_t po = (((((size_t)n0 * p.Hp + r0) << p.wlog) >> 2) + pq) * p.N + col0 + c;
+      Piece<bf16_t>::store(p.pool + po, m);
+      *reinterpret_cast<u32x2*>(p.pool_code + po) = code;
+    }
+  }
+}
+
+int log2_exact(int v) {
+  int l = 0;
+  while ((1 << l) < v) ++l;
+  return (1 << l) == v ? l : -1;
+}
+
+// Geometry of the tiles; false where the shape does not qualify.
+struct FragShape {
+  int R, nimg, upi, PR, npatch, ks;
+  size_t lds;
+};
+bool frag_shape(const ConvGeom& g, int N, FragShape& s) {
+  if (g.raw3 || (g.transposed && g.stride != 1) || g.stride > 2) return false;
+  if (!((g.ks == 3 && g.pad == 1) || (g.ks == 1 && g.pad == 0))) return false;
+  if (g.Cs % 32 != 0 || N % 32 != 0) return false;
+  if (g.Hp != (g.Hs + 2 * g.pad - g.ks) / g.stride + 1 || g.Wp != (g.Ws + 2 * g.pad - g.ks) / g.stride + 1) return false;
+  if (g.Wp < 4 || g.Wp > kTM || log2_exact(g.Wp) < 0) return false;
+  s.R = std::min(g.Hp, kTM / g.Wp);
+  if (g.Hp % s.R != 0 || kTM % (s.R * g.Wp) != 0 || log2_exact(s.R) < 0) return false;
+  s.nimg = kTM / (s.R * g.Wp);
+  s.upi = g.Hp / s.R;
+  if (s.nimg > 1 && s.upi != 1) return false;
+  s.PR = g.ks == 1 ? s.R : s.upi == 1 ? g.Hs : (s.R - 1) * g.stride + 3;
+  s.npatch = g.ks == 1 ? kTM : s.nimg * s.PR * g.Ws;
+  s.ks = g.Cs % 64 == 0 ? 4 : 2;
+  s.lds = std::max((size_t)(s.npatch + 1) * (g.Cs * 2 + 16), (size_t)4 * s.ks * 4096);
+  return s.lds <= kLdsLimit;
+}
+
+template <int KS, int TAPS, bool BWD>
+void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
+  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
+  if (lds > configured) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_frag_kernel<KS, TAPS, BWD>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    configured = lds;
+  }
+  hipLaunchKernelGGL((conv_frag_kernel<KS, TAPS, BWD>), dim3(grid), dim3(kThreads), lds, st, p);
+}
+
+}  // namespace
+
+bool conv_frag_supported(const ConvGeom& g, int N) {
+  FragShape s;
+  return frag_shape(g, N, s);
+}
+
+// Up to two workgroups per compute unit this kernel wins everywhere (1.1-5.5x over 16-512 images of the ResNet-18 and
+// three-layer shapes); beyond, its larger share of start-up and epilogue per tile tells, the sooner the shorter
+// the reduction.  Its rivals are weak at stride 2 (general kernel) and on 4-wide maps (units of 512 positions), and a
+// reduction of 2304 still breaks even at four workgroups per compute unit (8x8x256: 22.8 us against 23.9); with 4608
+// on 4-wide maps it stays ahead (2048 images: 129 us against 145, 1.2 PFLOP/s).
+bool conv_frag_takes(const ConvGeom& g, int N) {
+  FragShape s;
+  if (!frag_shape(g, N, s)) return false;
+  const long tiles = (s.upi == 1 ? (g.rows + s.nimg - 1) / s.nimg : (long)g.rows * s.upi) * ((N + kTN - 1) / kTN);
+  const int K = g.ks * g.ks * g.Cs;
+  if (g.Wp == 4 && g.stride == 1 && K >= 4608) return true;
+  const bool weak_rival = g.ks == 3 && (g.stride == 2 || g.Wp == 4);
+  return tiles <= (weak_rival || K >= 2304 ? 1024 : 512);
+}
+
+bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
+                    const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
+                    const bf16_t* addend, BnStatRequest* stats) {
+  FragShape s;
+  (void)frag_shape(g, N, s);
+  const bool bwd = g.transposed != 0;
+  FragParams p{};
+  p.src = src; p.wgt = wgt; p.out = out;
+  p.rows = g.rows; p.Hs = g.Hs; p.Ws = g.Ws; p.Cs = g.Cs; p.N = N; p.Hp = g.Hp;
+  p.wlog = log2_exact(g.Wp); p.rlog = log2_exact(s.R);
+  p.nimg = s.nimg; p.upi = s.upi; p.PR = s.PR; p.npatch = s.npatch;
+  p.stride = g.stride; p.flip = bwd ? 1 : 0; p.zero = g.zero;
+  p.bias = bias; p.mask = mask; p.addend = addend; p.relu = relu ? 1 : 0; p.accumulate = accumulate ? 1 : 0;
+  p.mask_bits = (mask && N % 64 == 0) ? g.mask_bits : nullptr;
+  if (!bwd && pool && pool_code && s.R % 2 == 0 && g.Hp % 2 == 0) { p.pool = pool; p.pool_code = pool_code; }
+  // tiles; one worker's each where their batch-norm sums are wanted and there is room for one record per tile
+  const bool want = !bwd && stats && stats->partial && stats->seg && !bias && !relu && stats->seg->off[stats->seg->K] == g.rows;
+  auto tiles_of = [&](int images) { return s.upi == 1 ? (images + s.nimg - 1) / s.nimg : images * s.upi; };
+  long records = 0;
+  if (want)
+    for (int k = 0; k < stats->seg->K; ++k) records += tiles_of(stats->seg->off[k + 1] - stats->seg->off[k]);
+  p.gK = 1;
+  p.ifirst[1] = g.rows;
+  if (want && records <= (long)stats->seg->K * kBnMaxSplits) {
+    p.gK = stats->seg->K;
+    for (int k = 0; k <= p.gK; ++k) p.ifirst[k] = stats->seg->off[k];
+    p.stat_partial = stats->partial;
+  }
+  for (int k = 0; k < p.gK; ++k) p.tfirst[k + 1] = p.tfirst[k] + tiles_of(p.ifirst[k + 1] - p.ifirst[k]);
+  const int taps = g.ks * g.ks, tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
+  // an XCD's L2 sees the whole of one operand and about an eighth of the other
+  p.by_channel = (long)N * taps * g.Cs > (long)g.rows * g.Hs * g.Ws * g.Cs ? 1 : 0;
+  const int grid = (tiles * tiles_n + 7) / 8 * 8;
+#define OMNI_FRAG(KS_, TAPS_) { if (bwd) launch<KS_, TAPS_, true>(st, p, grid, s.lds); else launch<KS_, TAPS_, false>(st, p, grid, s.lds); }
+  if (taps == 9) { if (s.ks == 4) OMNI_FRAG(4, 9) else OMNI_FRAG(2, 9) }
+  else { if (s.ks == 4) OMNI_FRAG(4, 1) else OMNI_FRAG(2, 1) }
+#undef OMNI_FRAG
+  if (p.stat_partial) {
+    for (int k = 0; k <= p.gK; ++k) stats->table.first[k] = p.tfirst[k];
+    stats->done = true;
+  }
+  return p.pool != nullptr;
+}
+
+}  // namespace omni

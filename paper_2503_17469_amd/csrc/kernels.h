@@ -127,6 +127,7 @@ struct ConvGeom {
   const uint8_t* mask_bits;   // may be null; with a mask [M][N], N a multiple of 64: the same information at one bit
                               // per element ([M][N/8] bytes, bit e of byte c/8 set where mask[m][c - c%8 + e] > 0).
                               // Kernels that know how read it instead of the mask (a sixteenth of the bytes).
+  int frag;             // 1: the weights are laid out for conv_frag_bf16 (CastEntry), which conv_gemm_bf16 then calls
 };
 // True if both the forward and the weight-gradient pass of a first layer with this shape can read a
 // 3-channel source as it is, so that no padded copy of the network input has to be made.
@@ -177,6 +178,14 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
                     const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
                     bf16_t* pool_out = nullptr, uint8_t* pool_code = nullptr, const bf16_t* addend = nullptr,
                     BnStatRequest* stats = nullptr);
+// The kernel for few positions (conv_frag_bf16.hip), on weights in operand order: blocks [N/32][taps][Cs/16] of 64 lanes x
+// 8 elements, output n % 32 and channels 8 * (lane / 32) .. + 7 of the sixteen in lane n % 32 + 32 * ((c % 16) / 8).
+// conv_frag_takes tells which launches it is for, conv_frag_supported which it could make at all.
+bool conv_frag_supported(const ConvGeom& g, int N);
+bool conv_frag_takes(const ConvGeom& g, int N);
+bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
+                    const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
+                    const bf16_t* addend, BnStatRequest* stats);
 // The wide-tile kernel for 3x3 / stride 1 / pad 1 layers (conv3_wide_bf16.hip): same arguments and result as
 // conv_gemm_bf16 without pooling; false, with nothing launched, if the shape does not qualify.
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
@@ -217,9 +226,11 @@ bool conv3_wgrad_tr_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* src, fl
 // if w_t is not null, the transposed copy [cin_pad][taps][cout] used by dgrad.
 // One layer's weight copy: fp32 [cout][taps][cin_real] at params + src -> bf16 [cout][taps][cin_pad] at
 // shadow + dst_fwd and, if dst_t >= 0, the transposed [cin_pad][taps][cout] at shadow + dst_t (offsets in elements).
+// frag_fwd / frag_t: that copy is laid out for conv_frag_bf16 instead (same size).
 struct CastEntry {
   long src, dst_fwd, dst_t;
   int cout, taps, cin_real, cin_pad;
+  int frag_fwd, frag_t;
   int first_block;   // filled by the launcher
 };
 constexpr int kCastMaxEntries = 64;

@@ -643,6 +643,18 @@ void step_bf16(StepCtx& c) {
     g.raw3 = (raw_input && L.in0 < 0) ? 1 : 0;
     return g;
   };
+  // ... and of its input gradient's: gathered from the output gradient, one GEMM row per input position
+  auto dgrad_geom = [&](const Layer& L) {
+    omni::ConvGeom d = fwd_geom(L);
+    const Tensor& to = net->tensors[L.out];
+    d.Hs = to.h; d.Ws = to.w; d.Cs = L.d.cout;
+    d.Hp = L.ih; d.Wp = L.iw;
+    if (L.d.op != OMNI_OP_CONV) { d.Hp = 1; d.Wp = 1; }
+    d.transposed = 1;
+    d.K = d.ks * d.ks * d.Cs;
+    d.raw3 = 0;
+    return d;
+  };
 
   // ---- the network input: channel counts that are no multiple of 8 are padded into a copy, unless
   // every layer that reads the input is a first-layer convolution whose kernels read 3 channels directly
@@ -664,6 +676,12 @@ void step_bf16(StepCtx& c) {
     }
   }
 
+  // Which convolutions run in the kernel for few positions, whose weights have a layout of their own
+  auto frag_fwd = [&](const Layer& L) { return L.d.op == OMNI_OP_CONV && omni::conv_frag_takes(fwd_geom(L), L.d.cout) ? 1 : 0; };
+  auto frag_dgrad = [&](const Layer& L) {
+    return L.d.op == OMNI_OP_CONV && L.need_dgrad && omni::conv_frag_takes(dgrad_geom(L), L.cin_pad) ? 1 : 0;
+  };
+
   // ---- bf16 copies of the weights (forward layout, and transposed for dgrad)
   {
     std::vector<omni::CastEntry> casts;
@@ -675,6 +693,10 @@ void step_bf16(StepCtx& c) {
       e.taps = L.d.op == OMNI_OP_CONV ? L.d.ksize * L.d.ksize : 1;
       e.cin_real = L.d.op == OMNI_OP_CONV ? L.d.cin : L.cin_pad;
       e.cin_pad = L.cin_pad;
+      if (L.d.op == OMNI_OP_CONV) {
+        e.frag_fwd = frag_fwd(L);
+        e.frag_t = L.need_dgrad && frag_dgrad(L);
+      }
       casts.push_back(e);
     }
     // (the same launch clears the few bytes of zeros that loads of absent pieces are pointed at: the workspace
@@ -697,7 +719,8 @@ void step_bf16(StepCtx& c) {
     if (L.fused_away) continue;
     if (is_param_op(L.d.op)) {
       TimedScope ts(net, st, L.d.op == OMNI_OP_CONV ? OMNI_KERNEL_CONV_FWD : OMNI_KERNEL_LINEAR_FWD, i);
-      const omni::ConvGeom g = fwd_geom(L);
+      omni::ConvGeom g = fwd_geom(L);
+      g.frag = frag_fwd(L);
       const Tensor& to = net->tensors[L.out];
       // the next layer that runs, if it pools this layer's output (its only consumer then)
       int nx = i + 1;
@@ -845,12 +868,8 @@ void step_bf16(StepCtx& c) {
       }
       if (L.in0 >= 0 && !dgrad_done) {
         TimedScope ts(net, st, conv ? OMNI_KERNEL_CONV_DGRAD : OMNI_KERNEL_LINEAR_DGRAD, i);
-        omni::ConvGeom d = g;
-        d.Hs = to.h; d.Ws = to.w; d.Cs = L.d.cout;      // gather from dY
-        d.Hp = L.ih; d.Wp = L.iw;                        // one GEMM row per input position
-        if (!conv) { d.Hp = 1; d.Wp = 1; }
-        d.transposed = 1;
-        d.K = d.ks * d.ks * d.Cs;
+        omni::ConvGeom d = dgrad_geom(L);
+        d.frag = frag_dgrad(L);
         const Tensor& ti = net->tensors[L.in0];
         const int m_rows = conv ? rows * L.ih * L.iw : rows;
         const bf16_t* addend = pending_add[L.in0];

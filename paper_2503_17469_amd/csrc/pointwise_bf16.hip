@@ -23,6 +23,12 @@ constexpr int kCastTile = 64;
 constexpr int kCastStride = kCastTile + 2;   // halfwords; odd in words, so a column of the tile spreads over the banks
 typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));   // parameters start anywhere
 
+// Offset of the piece of eight channels that starts at c of output n in a copy laid out as matrix operands
+// (conv_frag_bf16): blocks [n/32][tap][c/16] of 64 lanes x 8 elements.
+__device__ inline long frag_offset(int n, int tap, int c, int taps, int channels) {
+  return (((long)(n >> 5) * taps + tap) * (channels >> 4) + (c >> 4)) * 512 + ((n & 31) + 32 * ((c >> 3) & 1)) * 8;
+}
+
 __global__ __launch_bounds__(256) void cast_weights_kernel(CastTable tab, const float* __restrict__ params,
                                                            bf16_t* __restrict__ shadow, uint32_t* __restrict__ zero_page) {
   __shared__ __attribute__((aligned(16))) bf16_t tile[kCastTile * kCastStride];
@@ -59,7 +65,9 @@ __global__ __launch_bounds__(256) void cast_weights_kernel(CastTable tab, const 
     const int co = co0 + r + 16 * i;
     const u32x2 w = {pack_bf16(v[i][0], v[i][1]), pack_bf16(v[i][2], v[i][3])};
     if (co < t.cout && ci < t.cin_pad)
-      *reinterpret_cast<u32x2*>(shadow + t.dst_fwd + ((long)co * t.taps + tap) * t.cin_pad + ci) = w;
+      *reinterpret_cast<u32x2*>(shadow + t.dst_fwd +
+                                (t.frag_fwd ? frag_offset(co, tap, ci, t.taps, t.cin_pad) + (ci & 7)
+                                            : ((long)co * t.taps + tap) * t.cin_pad + ci)) = w;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       tile[(cl + q) * kCastStride + r + 16 * i] = (bf16_t)(w[q >> 1] >> (16 * (q & 1)));
@@ -70,11 +78,13 @@ __global__ __launch_bounds__(256) void cast_weights_kernel(CastTable tab, const 
   const int tr = tid >> 2, tc = (tid & 3) * 16;
   if (ci0 + tr >= t.cin_pad) return;
   const uint32_t* row = reinterpret_cast<const uint32_t*>(tile + tr * kCastStride + tc);
-  bf16_t* dst = shadow + t.dst_t + ((long)(ci0 + tr) * t.taps + tap) * t.cout + co0 + tc;
+  bf16_t* dst = shadow + t.dst_t + (t.frag_t ? frag_offset(ci0 + tr, tap, co0 + tc, t.taps, t.cout)
+                                             : ((long)(ci0 + tr) * t.taps + tap) * t.cout + co0 + tc);
+  const int second = t.frag_t ? 32 * 8 : 8;   // from one piece of eight channels to the next
 #pragma unroll
   for (int h = 0; h < 2; ++h)
     if (co0 + tc + 8 * h < t.cout)
-      *reinterpret_cast<u32x4*>(dst + 8 * h) = u32x4{row[4 * h], row[4 * h + 1], row[4 * h + 2], row[4 * h + 3]};
+      *reinterpret_cast<u32x4*>(dst + second * h) = u32x4{row[4 * h], row[4 * h + 1], row[4 * h + 2], row[4 * h + 3]};
 }
 
 __global__ __launch_bounds__(256) void pad_channels_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ xp,
