@@ -22,30 +22,27 @@
 //     in chunk order (no atomics: bit-reproducible).
 //
 // Layers with a bias are left to the generic kernel (the convolutions this is for are followed by a batch norm).
+#pragma once
 #include <hip/hip_runtime.h>
-
-#include <algorithm>
 
 #include "bf16.h"
 #include "common.h"
-#include "kernels.h"
+#include "conv_device.h"
+#include "wgrad_chunk.h"
 
 namespace omni {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kUnit = 64;          // output positions per unit
+constexpr int kTrUnit = 64;          // output positions per unit
 constexpr int kCo = 128;           // output channels per workgroup (32 per wavefront)
 constexpr int kCi = 32;            // input channels per workgroup
-constexpr int kSA = (kCo + 16) * 2;   // bytes per dY row in LDS: 72 banks, so four rows 8 banks apart start in different bank octets
-constexpr int kNA = kUnit * (kCo / 8) / kThreads;   // dY pieces per thread (4)
+constexpr int kTrSA = (kCo + 16) * 2;   // bytes per dY row in LDS: 72 banks, so four rows 8 banks apart start in different bank octets
+constexpr int kNA = kTrUnit * (kCo / 8) / kThreads;   // dY pieces per thread (4)
 constexpr int kNX = 6;             // patch pieces per thread (up to 384 patch positions x 4 pieces)
-constexpr int kTileFloats = 9 * 16 * kThreads;
+constexpr int kTrTileFloats = 9 * 16 * kThreads;
 
 struct TrParams {
   const bf16_t* dy;    // [rows*Ho*Wo][Cout]
@@ -60,7 +57,6 @@ struct TrParams {
   float* partial;      // [(tile * total_chunks + chunk)][144][256]
   const void* zero;    // zeros for absent pieces
 };
-struct TrChunks { int32_t first[OMNI_MAX_WORKERS + 1]; };   // first chunk of every worker; first[K] = total
 
 __device__ inline bf16x8 tr_pair(const unsigned char* lds_a, const unsigned char* lds_b) {
   typedef __attribute__((address_space(3))) v4s lds_v4s;
@@ -74,21 +70,17 @@ __device__ inline bf16x8 tr_pair(const unsigned char* lds_a, const unsigned char
 // S: stride of the forward convolution.  Bytes per patch position in LDS: 64 of data + padding such that the
 // four positions one transposing read covers (S patch positions apart) start 8 banks apart.
 template <int S>
-__global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p, Segments seg, TrChunks ct) {
+__device__ __forceinline__ void wgrad_tr_body(const TrParams& p, const Segments& seg, const Chunk& ck, int tile,
+                                              unsigned char* smemT) {
   constexpr int SX = S == 2 ? 80 : 96;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smemT[];
-  unsigned char* sA = smemT;                       // [64][kSA]
-  unsigned char* sX = smemT + kUnit * kSA;         // [npatch][SX]
+  unsigned char* sA = smemT;                       // [64][kTrSA]
+  unsigned char* sX = smemT + kTrUnit * kTrSA;         // [npatch][SX]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tiles_ci = (p.Cin + kCi - 1) / kCi;
-  const int tile = blockIdx.x;
   const int co0 = (tile / tiles_ci) * kCo, ci0 = (tile % tiles_ci) * kCi;
   const int Ho = p.Ho, Wo = p.Wo, H = p.H, W = p.W, R = p.R, PR = p.PR, PW = p.PW;
 
-  int wk = 0;
-  while (wk + 1 < seg.K && (int)blockIdx.y >= ct.first[wk + 1]) ++wk;
-  const int chunk_idx = blockIdx.y - ct.first[wk];
-  const int nchunks = ct.first[wk + 1] - ct.first[wk];
+  const int wk = ck.wk, chunk_idx = ck.idx, nchunks = ck.n;
   const int bk = seg.off[wk + 1] - seg.off[wk];
   const int upi = Ho / R;   // units per image when a unit is part of one image
   const int units_k = p.nimg == 1 ? bk * upi : (bk + p.nimg - 1) / p.nimg;
@@ -124,7 +116,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p,
   // 32 x 32 x 16 matrix instruction expects.
   const int g = lane >> 4, s = lane & 15;
   const int chan = 16 * (g & 1) + 4 * (s & 3);
-  const unsigned char* a_base = sA + (8 * (g >> 1) + (s >> 2)) * kSA + (wave * 32 + chan) * 2;
+  const unsigned char* a_base = sA + (8 * (g >> 1) + (s >> 2)) * kTrSA + (wave * 32 + chan) * 2;
   // patch byte offset of a position of the unit (tap (0, 0))
   auto patch_off = [&](int pos) {
     const int il = pos / (R * Wo), rem = pos - il * (R * Wo);
@@ -176,7 +168,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p,
 #pragma unroll
     for (int t = 0; t < kNA; ++t) {
       const int x = tid + t * kThreads;
-      *reinterpret_cast<u32x4*>(sA + (x >> 4) * kSA + (x & 15) * 16) = ra[t];
+      *reinterpret_cast<u32x4*>(sA + (x >> 4) * kTrSA + (x & 15) * 16) = ra[t];
     }
 #pragma unroll
     for (int t = 0; t < kNX; ++t) {
@@ -192,8 +184,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p,
     __syncthreads();
     load_unit(min(u + 1, uend - 1));   // always issued: in flight during the matrix instructions below
 #pragma unroll
-    for (int ks = 0; ks < kUnit / 16; ++ks) {
-      const bf16x8 fa = tr_pair(a_base + (16 * ks) * kSA, a_base + (16 * ks + 4) * kSA);
+    for (int ks = 0; ks < kTrUnit / 16; ++ks) {
+      const bf16x8 fa = tr_pair(a_base + (16 * ks) * kTrSA, a_base + (16 * ks + 4) * kTrSA);
       const int kofs = patch_off(16 * ks);
       const unsigned char* x0 = sX + xb[0] + kofs;
       const unsigned char* x1 = sX + xb[1] + kofs;
@@ -210,7 +202,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p,
   const int j = lane & 31, h = lane >> 5;
   const int ci = ci0 + j;
   if (nchunks > 1) {
-    float* mine = p.partial + ((size_t)tile * ct.first[seg.K] + blockIdx.y) * kTileFloats;
+    float* mine = p.partial + ((size_t)tile * ck.total + ck.row) * kTrTileFloats;
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -229,20 +221,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv3_wgrad_tr_kernel(TrParams p,
   }
 }
 
-// Second stage: grid (tiles, workers, 36); a thread adds one (tap, four registers, lane) entry of every chunk of
+// Second stage: one workgroup per (tile, worker, one of 36); a thread adds one (tap, four registers, lane) entry of every chunk of
 // the worker in chunk order.
-__global__ __launch_bounds__(kThreads) void conv3_wgrad_tr_reduce_kernel(TrParams p, Segments seg, TrChunks ct) {
-  const int tile = blockIdx.x, wk = blockIdx.y;
-  const int nchunks = ct.first[wk + 1] - ct.first[wk];
-  if (nchunks <= 1) return;   // written directly by the first stage
-  const int tap = blockIdx.z >> 2, vq = blockIdx.z & 3;
+__device__ __forceinline__ void wgrad_tr_reduce(const TrParams& p, const Chunk& ck, int tile, int z) {
+  const int wk = ck.wk, nchunks = ck.n;
+  const int tap = z >> 2, vq = z & 3;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 31, h = lane >> 5;
   const int tiles_ci = (p.Cin + kCi - 1) / kCi;
   const int co0 = (tile / tiles_ci) * kCo, ci0 = (tile % tiles_ci) * kCi;
   const int ci = ci0 + j;
   if (ci >= p.cin_real) return;
-  const float* mine = p.partial + ((size_t)tile * ct.first[seg.K] + ct.first[wk]) * kTileFloats +
+  const float* mine = p.partial + ((size_t)tile * ck.total + ck.row) * kTrTileFloats +
                       (size_t)(tap * 16 + vq * 4) * kThreads + tid;
   float sum[4] = {0.f, 0.f, 0.f, 0.f};
   int c = 0;
@@ -251,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void conv3_wgrad_tr_reduce_kernel(TrParam
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t[u][e] = mine[(size_t)(c + u) * kTileFloats + e * kThreads];
+      for (int e = 0; e < 4; ++e) t[u][e] = mine[(size_t)(c + u) * kTrTileFloats + e * kThreads];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -259,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void conv3_wgrad_tr_reduce_kernel(TrParam
   }
   for (; c < nchunks; ++c)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) sum[e] += mine[(size_t)c * kTileFloats + e * kThreads];
+    for (int e = 0; e < 4; ++e) sum[e] += mine[(size_t)c * kTrTileFloats + e * kThreads];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int v = vq * 4 + e;
@@ -269,63 +259,4 @@ __global__ __launch_bounds__(kThreads) void conv3_wgrad_tr_reduce_kernel(TrParam
 }
 
 }  // namespace
-
-bool conv3_wgrad_tr_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* src, float* gw, float* gb,
-                         size_t worker_stride, int Cout, int cin_real, const ConvGeom& g, const Segments& seg,
-                         float* partial) {
-  const int S = g.stride, Ho = g.Hp, Wo = g.Wp, H = g.Hs, W = g.Ws;
-  // (the kernel is written for any stride; stride-1 layers are not sent here: the transposed-patch kernel of
-  // conv_bf16.hip measured faster on every map width, by 0.07 to 0.64 ms per ResNet-18 step)
-  if (gb || g.ks != 3 || g.pad != 1 || g.transposed || g.raw3 || S != 2) return false;
-  if (H != S * Ho || W != S * Wo || g.Cs % 8 != 0 || Cout % 8 != 0 || cin_real > g.Cs) return false;
-  // (a reduction step of sixteen positions must lie inside one map row or be made of whole rows of one image)
-  if (Wo < 4 || Wo > kUnit || (Wo % 16 != 0 && 16 % Wo != 0)) return false;
-  const int R = std::min(Ho, kUnit / Wo);
-  if (Ho % R != 0 || kUnit % (R * Wo) != 0 || (R * Wo) % 16 != 0) return false;
-  const int nimg = kUnit / (R * Wo);
-  if ((nimg > 1 && R != Ho) || nimg > 15) return false;
-  const int PR = S * (R - 1) + 3, PW = S * (Wo - 1) + 3;
-  const int npatch = nimg * PR * PW;
-  if (npatch * 4 > kNX * kThreads) return false;
-  if ((long)g.rows * H * W * g.Cs >= (1L << 31) || (long)g.rows * Ho * Wo * Cout >= (1L << 31)) return false;
-  TrParams p{};
-  p.dy = dy; p.src = src; p.gw = gw; p.worker_stride = worker_stride;
-  p.Cout = Cout; p.Cin = g.Cs; p.cin_real = cin_real; p.Ho = Ho; p.Wo = Wo; p.H = H; p.W = W;
-  p.R = R; p.nimg = nimg; p.PR = PR; p.PW = PW; p.partial = partial; p.zero = g.zero;
-  const int tiles = ((Cout + kCo - 1) / kCo) * ((g.Cs + kCi - 1) / kCi);
-  const size_t max_slots = conv_wgrad_partial_floats() / kTileFloats;
-  long units[OMNI_MAX_WORKERS], total_units = 0;
-  for (int k = 0; k < seg.K; ++k) {
-    const long bk = seg.off[k + 1] - seg.off[k];
-    units[k] = nimg == 1 ? bk * (Ho / R) : (bk + nimg - 1) / nimg;
-    total_units += units[k];
-  }
-  // about 512 workgroups in all (two per compute unit), at least 8 units each
-  long want = std::max<long>(1, 512 / tiles);
-  long upc = std::max<long>((total_units + want - 1) / want, 8);
-  TrChunks ct{};
-  for (;;) {
-    int acc = 0;
-    for (int k = 0; k < seg.K; ++k) {
-      ct.first[k] = acc;
-      acc += (int)((units[k] + upc - 1) / upc);
-    }
-    ct.first[seg.K] = acc;
-    if (acc == 0) return true;   // no rows at all
-    // one chunk per worker needs no scratch; otherwise the partial tiles must fit it
-    if (acc == seg.K) break;
-    if ((size_t)tiles * acc <= max_slots && (long)tiles * acc <= std::max(512, 2 * tiles * seg.K)) break;
-    upc += std::max<long>(1, upc / 16);
-  }
-  p.upc = (int)upc;
-  const size_t lds = (size_t)kUnit * kSA + (size_t)npatch * 80;   // (80 bytes per patch position at stride 2: see the kernel)
-  const dim3 grid(tiles, ct.first[seg.K]);
-  hipLaunchKernelGGL(conv3_wgrad_tr_kernel<2>, grid, dim3(kThreads), lds, st, p, seg, ct);
-  bool chunked = false;
-  for (int k = 0; k < seg.K; ++k) chunked = chunked || ct.first[k + 1] - ct.first[k] > 1;
-  if (chunked)
-    hipLaunchKernelGGL(conv3_wgrad_tr_reduce_kernel, dim3(tiles, seg.K, 36), dim3(kThreads), 0, st, p, seg, ct);
-  return true;
-}
-
 }  // namespace omni

@@ -204,22 +204,28 @@ bool conv3s2_dgrad_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int 
 // (mask_bits: as ConvGeom::mask_bits.)
 // (addend, [M][N] or null, is added to the product before the mask: the input gradient of a layer
 // whose input also feeds a residual add takes the add's share along instead of a separate pass.)
-// Per worker k: gw_k[Cout][taps][cin_real] = dy_k^T gather(src)_k, gb_k = column sums of dy_k (gb may be null).
+// Weight gradients (conv_wgrad_bf16.hip).  Per worker k: gw_k[Cout][taps][cin_real] = dy_k^T gather(src)_k, gb_k = column
+// sums of dy_k (gb may be null).
 // With dpool and pool_code (only where conv_wgrad_pooled_supported says so: the first-layer kernel),
 // dy is not read: the layer's output gradient is taken from the gradient of the 2 x 2 max pooling
 // that follows the layer ([rows*(Hp/2)*(Wp/2)][Cout]) and the pooling's codes, so that it never has
 // to be written out at full resolution.
-void conv_wgrad_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* src, float* gw, float* gb,
-                     size_t worker_stride, int Cout, int cin_real, const ConvGeom& g, const Segments& seg,
-                     float* partial, uint32_t* counters, const bf16_t* dpool = nullptr,
-                     const uint8_t* pool_code = nullptr);
+struct ConvWgradJob {
+  const bf16_t* dy;
+  const bf16_t* src;
+  float* gw;           // worker 0's
+  float* gb;           // worker 0's, may be null
+  int Cout, cin_real;
+  ConvGeom g;          // as in the forward pass
+  const bf16_t* dpool;
+  const uint8_t* pool_code;
+};
 bool conv_wgrad_pooled_supported(int Cout, int cin_real, const ConvGeom& g);
-// Weight gradient of a 3x3 / pad-1 convolution of stride 2 (or 1) without bias from operands left in their
-// [position][channel] layout (conv3_wgrad_tr_bf16.hip); arguments as conv_wgrad_bf16.  False, with nothing
-// launched, for shapes it does not take.
-bool conv3_wgrad_tr_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* src, float* gw, float* gb,
-                         size_t worker_stride, int Cout, int cin_real, const ConvGeom& g, const Segments& seg,
-                         float* partial);
+double conv_wgrad_work(const ConvWgradJob& job);   // flop
+// All jobs share launches (first stage, second stage).  partial: conv_wgrad_partial_floats() of scratch.  head (may be
+// null): the classifier's parameter gradients and losses as well (head_wgrad_loss).
+void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+                      float* partial, const HeadWgradParams* head);
 
 // ---- bf16 pointwise kernels (pointwise_bf16.hip) ----
 // fp32 weights [cout][taps][cin_real] -> bf16 [cout][taps][cin_pad] (zero padded) and,

@@ -63,6 +63,7 @@ struct omni_net {
   size_t grads_off = 0, loss_rows_off = 0, status_off = 0;
   size_t shadow_off = 0, shadow_elems = 0, xpad_off = 0, conv_partial_off = 0, conv_counters_off = 0;
   size_t conv_partial2_off = 0;     // chunk scratch of the second side stream
+  size_t conv_partial3_off = 0;     // ... and of the main stream
   size_t bn_off = 0, bn_floats = 0, bn_partial_off = 0;
   size_t reduced_off = 0;           // g = sum_k lambda_k g_k, written only on request
   int bn_cmax = 0;
@@ -313,6 +314,7 @@ int omni_net_create(const omni_layer_desc* descs, int32_t n, int32_t in_h, int32
     net->conv_counters_off = take(omni::kZeroPageWords * sizeof(uint32_t));
     net->conv_partial_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
     net->conv_partial2_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
+    net->conv_partial3_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
     net->shadow_off = take(net->shadow_elems * 2);
     if (in_c % 8 != 0) net->xpad_off = take((size_t)B_max * in_h * in_w * ((in_c + 7) / 8 * 8) * 2);
     if (net->bn_floats) {
@@ -436,20 +438,8 @@ struct StepCtx {
   hipStream_t side;      // equals st when no side stream could be made
   hipStream_t side2;     // equals side when no second one could be made
   size_t sync_used = 0;
-  // a side stream may start once everything enqueued on the main stream so far is done
-  void fork(hipStream_t& to) {
-    if (to == st) return;
-    if (sync_used == net->sync_ev.size()) {
-      hipEvent_t e;
-      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { to = st; return; }
-      net->sync_ev.push_back(e);
-    }
-    hipEvent_t e = net->sync_ev[sync_used++];
-    (void)hipEventRecord(e, st);
-    (void)hipStreamWaitEvent(to, e, 0);
-  }
-  void fork() { fork(side); }
-  // The two halves of a fork, for when main-stream work is enqueued in between: the side stream
+  // The two halves of a fork (a side stream may start once everything enqueued on the main stream so far is done), so
+  // that main-stream work can be enqueued in between: the side stream
   // then waits only for what preceded the record, and the main stream's next kernel is not held up
   // by the host calls that set the side stream going.
   hipEvent_t fork_record() {
@@ -781,6 +771,7 @@ void step_bf16(StepCtx& c) {
 
   // ---- classifier head: logits, loss, dz (with 1/b_k), first input gradient, head parameter gradients
   std::vector<char> written(net->tensors.size(), 0);
+  omni::HeadWgradParams head_grads{};
   {
     TimedScope ts(net, st, OMNI_KERNEL_LOSS, n_layers - 1);
     const int logits = last.out;
@@ -792,15 +783,10 @@ void step_bf16(StepCtx& c) {
                               z, dz, c.loss_rows, need_dx && net->tensors[last.in0].relu,
                               need_dx ? grad(last.in0) : nullptr);
     if (need_dx) written[last.in0] = 1;
-    if (!net->linear_only) {   // (a network of fully connected layers is too short a chain to fork from)
-      c.fork();
-      c.forked = true;
-    }
-    omni::head_wgrad_loss(net->linear_only ? st : c.side, true,
-                          omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
-                                                last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
-                                                c.loss_per_worker, c.loss, c.status},
-                          c.seg);
+    head_grads = omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
+                                       last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
+                                       c.loss_per_worker, c.loss, c.status};
+    if (net->linear_only) omni::head_wgrad_loss(st, true, head_grads, c.seg);   // (else with the last weight gradients)
   }
 
   // ---- backward
@@ -813,7 +799,33 @@ void step_bf16(StepCtx& c) {
   // its own: that convolution's input-gradient kernel adds it before its ReLU mask.
   std::vector<const bf16_t*> pending_add(net->tensors.size(), nullptr);
   float* conv_partial2 = reinterpret_cast<float*>(c.ws + net->conv_partial2_off);
-  bool second = false;   // which side stream (and scratch) takes the next weight gradient
+  float* conv_partial3 = reinterpret_cast<float*>(c.ws + net->conv_partial3_off);
+  // The weight gradients feed nothing but the update.  They are collected and set going in groups, on the side
+  // streams beside the input-gradient chain, the two streams (and scratch areas) in turn; what is left when the
+  // chain has ended runs on the main stream.  A group is worth a fork (event calls: about 12 us of host time, 3 us of the
+  // main stream) from kGroupWork on: 50 us or so of an otherwise idle chip.  Small networks never reach it.
+  constexpr double kGroupWork = 40e9;
+  constexpr int kGroupJobs = 6;
+  bool second = false;
+  std::vector<omni::ConvWgradJob> group;
+  double group_work = 0.0;
+  auto start_group = [&](hipEvent_t ready, int layer) {
+    const bool use2 = second && c.side2 != c.side;
+    second = !second;
+    c.fork_wait(use2 ? c.side2 : c.side, ready);
+    c.forked = true;
+    if (use2) c.forked2 = true;
+    hipStream_t side = use2 ? c.side2 : c.side;
+    TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
+    omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
+                           nullptr);
+    group.clear();
+    group_work = 0.0;
+  };
+  // the lowest layer with an input gradient: nothing is left to overlap with below it
+  int last_dgrad = n_layers;
+  for (int i = 0; i < n_layers - 1; ++i)
+    if (!net->layers[i].fused_away && is_param_op(net->layers[i].d.op) && net->layers[i].in0 >= 0) { last_dgrad = i; break; }
   // The entry of a residual block: its input feeds a 3x3 / stride-2 convolution and the 1x1 / stride-2
   // projection of the shortcut, and nothing else.  The projection comes first in this backward walk: its
   // input gradient is not launched on its own but handed to the 3x3 convolution's, whose kernel writes
@@ -832,7 +844,7 @@ void step_bf16(StepCtx& c) {
     }
     return -1;
   };
-  std::vector<omni::LinearWgradBf16Job> linear_jobs;   // linear_only: every hidden layer's, in one launch at the end
+  std::vector<omni::LinearWgradBf16Job> linear_jobs;   // the hidden fully connected layers', in one launch at the end
   auto linear_job = [&](const Layer& L) {
     return omni::LinearWgradBf16Job{grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin,
                                     L.d.cout, L.w_off, L.b_off};
@@ -844,11 +856,19 @@ void step_bf16(StepCtx& c) {
       const omni::ConvGeom g = fwd_geom(L);
       const Tensor& to = net->tensors[L.out];
       const bool conv = L.d.op == OMNI_OP_CONV;
-      // Parameter gradients run on the side streams beside the input-gradient chain.  ALL of
-      // them do, the first layer's included.  The point they wait for is recorded first, then the
-      // input gradient goes to the main stream, and only then are the side stream's wait and
-      // launches issued: the main chain (the longer one) never waits for those host calls.
-      hipEvent_t ready = net->linear_only ? nullptr : c.fork_record();
+      // The point a group of weight gradients waits for is recorded first, then the input gradient goes to the main
+      // stream, and only then are the side stream's wait and launches issued: the main chain (the longer one)
+      // never waits for those host calls.
+      bool group_full = false;
+      if (conv) {
+        const int pl = pooled_from[i];
+        group.push_back({grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cout, L.d.cin, g,
+                         pl >= 0 ? grad(net->layers[pl].out) : nullptr,
+                         pl >= 0 ? reinterpret_cast<const uint8_t*>(c.ws + net->layers[pl].code_off) : nullptr});
+        group_work += omni::conv_wgrad_work(group.back());
+        group_full = L.in0 >= 0 && (group_work >= kGroupWork || (int)group.size() == kGroupJobs || (c.forked && i == last_dgrad));
+      }
+      hipEvent_t ready = group_full ? c.fork_record() : nullptr;
       const int takes_me = conv && L.in0 >= 0 ? entry_partner(i) : -1;
       if (takes_me >= 0) partner[takes_me] = i;   // (this projection's input gradient rides with that convolution's)
       bool dgrad_done = takes_me >= 0;
@@ -884,28 +904,8 @@ void step_bf16(StepCtx& c) {
         }
         written[L.in0] = 1;
       }
-      if (net->linear_only) {
-        linear_jobs.push_back(linear_job(L));
-      } else {
-        const bool use2 = second && c.side2 != c.side;
-        second = !second;
-        c.fork_wait(use2 ? c.side2 : c.side, ready);
-        c.forked = true;
-        if (use2) c.forked2 = true;
-        hipStream_t ws_ = use2 ? c.side2 : c.side;
-        TimedScope ts(net, ws_, conv ? OMNI_KERNEL_CONV_WGRAD : OMNI_KERNEL_LINEAR_WGRAD, i);
-        const int pl = pooled_from[i];
-        if (!conv) {
-          const omni::LinearWgradBf16Job job = linear_job(L);
-          omni::linear_wgrad_bf16(ws_, &job, 1, net->P_stride, c.seg, nullptr, nullptr);
-          continue;
-        }
-        omni::conv_wgrad_bf16(ws_, grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr,
-                              net->P_stride, L.d.cout, L.d.cin, g, c.seg, use2 ? conv_partial2 : conv_partial,
-                              conv_counters,
-                              pl >= 0 ? grad(net->layers[pl].out) : nullptr,
-                              pl >= 0 ? reinterpret_cast<const uint8_t*>(c.ws + net->layers[pl].code_off) : nullptr);
-      }
+      if (group_full) start_group(ready, i);
+      if (!conv) linear_jobs.push_back(linear_job(L));
     } else if (L.d.op == OMNI_OP_MAXPOOL2) {
       int prod = -1;   // the layer that produced the pooling's input
       for (int j = i - 1; j >= 0 && prod < 0; --j)
@@ -955,14 +955,18 @@ void step_bf16(StepCtx& c) {
       written[L.in0] = 1;
     }
   }
-  if (net->linear_only && (!linear_jobs.empty() || c.fuse_update)) {
-    TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);
+  if (!net->linear_only) {
+    TimedScope ts(net, st, OMNI_KERNEL_CONV_WGRAD, 0);
+    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3, &head_grads);
+  }
+  if (!linear_jobs.empty() || (net->linear_only && c.fuse_update)) {
+    TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);   // the hidden fully connected layers', in one launch
     const omni::SgdArgs sgd{c.params, net->velocity, c.lr, net->momentum, net->weight_decay};
     omni::LinearWgradBf16Job head{};
     head.gw = c.G + last.w_off;
     head.gb = last.has_b ? c.G + last.b_off : nullptr;
     head.cin = last.d.cin; head.cout = last.d.cout; head.w_off = last.w_off; head.b_off = last.b_off;
-    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg, &head,
+    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg, c.fuse_update ? &head : nullptr,
                             c.fuse_update ? &sgd : nullptr, ts.timer());
   }
   for (size_t t = 0; t < net->tensors.size(); ++t) {
