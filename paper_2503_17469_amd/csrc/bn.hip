@@ -46,17 +46,36 @@ __device__ inline int share_owner(const ShareTable& tb, int K, int id) {
   return lo;
 }
 
+// Mean and 1/sqrt(var) of eight consecutive channels (stats: [channel][2]).
+__device__ inline void load_stats8(const float* __restrict__ p, float (&mu)[8], float (&is)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const v4f t = *reinterpret_cast<const v4f*>(p + 4 * i);
+    mu[2 * i] = t[0]; is[2 * i] = t[1];
+    mu[2 * i + 1] = t[2]; is[2 * i + 1] = t[3];
+  }
+}
+__device__ inline void unpack8(u32x4 t, float (&v)[8]) {
+#pragma unroll
+  for (int d = 0; d < 4; ++d) { v[2 * d] = bf16_lo(t[d]); v[2 * d + 1] = bf16_hi(t[d]); }
+}
+
 // Partial sums of (a) x and x^2, or (b) dy and dy*xhat, over one split of one worker's positions.
-// grid (total splits, ceil(C/64)); block = 8 channel pieces x 32 position lanes; four
-// positions per lane in flight.  A split is `per` positions, a whole number of trips of 128: splits of
-// equal shares instead made most of them end in a trip for one to three positions (129 positions each for
-// 128 32x32 images over 1016 workgroups: two trips where one does).
+// grid (total splits, ceil(C/64)); block = 8 channel pieces x 64 position lanes; four
+// positions per lane in flight (64 or 128 KB per workgroup: a workgroup per compute unit is enough to keep
+// memory busy, and few workgroups mean few records, which the apply kernel can then sum itself).
+// A split is `per` positions, a whole number of trips: splits of equal shares instead made most of them end in a
+// trip for one to three positions.
+constexpr int kPartThreads = 512, kPartTrip = kPartThreads / 8 * 4;
 template <bool BWD>
-__global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
-                                                         const float* __restrict__ stats, int C, int hw,
-                                                         Segments seg, ShareTable tb, int per,
-                                                         double* __restrict__ partial) {
-  __shared__ double red[32][8][17];
+__global__ __launch_bounds__(kPartThreads) void bn_partial_kernel(const bf16_t* __restrict__ x,
+                                                                  const bf16_t* __restrict__ dy,
+                                                                  const float* __restrict__ stats, int C, int hw,
+                                                                  Segments seg, ShareTable tb, int per,
+                                                                  double* __restrict__ partial) {
+  constexpr int kRows = kPartThreads / 8;
+  __shared__ double red[kRows][8][9];
+  __shared__ double red2[8][64];
   const int tid = threadIdx.x;
   const int c8 = tid & 7, pl = tid >> 3;
   const int wk = share_owner(tb, seg.K, blockIdx.x);
@@ -73,49 +92,56 @@ __global__ __launch_bounds__(256) void bn_partial_kernel(const bf16_t* __restric
   float mu[8], is[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) { s1[e] = 0.0; s2[e] = 0.0; mu[e] = 0.f; is[e] = 1.f; }
-  if (BWD) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      mu[e] = stats[((size_t)wk * C + cl + e) * 2];
-      is[e] = stats[((size_t)wk * C + cl + e) * 2 + 1];
-    }
-  }
-  for (long p = sbeg + pl; p < send; p += 128) {
+  if (BWD) load_stats8(stats + ((size_t)wk * C + cl) * 2, mu, is);
+  for (long p = sbeg + pl; p < send; p += kPartTrip) {
     // loads are unconditional (a position past the end re-reads the last one and adds zero)
-    float xv[4][8], dv[4][8];
+    u32x4 xr[4], dr[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long q = min(p + 32 * u, send - 1);
-      Piece<bf16_t>::load(x + q * C + cl, xv[u]);
-      if (BWD) Piece<bf16_t>::load(dy + q * C + cl, dv[u]);
+      const long q = min(p + kRows * u, send - 1);
+      xr[u] = *reinterpret_cast<const u32x4*>(x + q * C + cl);
+      if (BWD) dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + cl);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float live = p + 32 * u < send ? 1.f : 0.f;
+      const float live = p + kRows * u < send ? 1.f : 0.f;
+      float xv[8], dv[8];
+      unpack8(xr[u], xv);
+      if (BWD) unpack8(dr[u], dv);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         if (!BWD) {
-          const float v = xv[u][e] * live;
+          const float v = xv[e] * live;
           s1[e] += (double)v;
           s2[e] += (double)v * (double)v;
         } else {
-          const float d = dv[u][e] * live;
+          const float d = dv[e] * live;
           s1[e] += (double)d;
-          s2[e] += (double)(d * ((xv[u][e] - mu[e]) * is[e]));
+          s2[e] += (double)(d * ((xv[e] - mu[e]) * is[e]));
         }
       }
     }
   }
+  // the position lanes' sums, eight rows per thread, then the eight parts: a fixed order
 #pragma unroll
-  for (int e = 0; e < 8; ++e) { red[pl][c8][e] = s1[e]; red[pl][c8][8 + e] = s2[e]; }
-  __syncthreads();
-  if (tid < 128) {
-    const int cc = tid & 63, which = tid >> 6;     // channel within the group, sum or second sum
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) red[pl][c8][e] = which ? s2[e] : s1[e];
+    __syncthreads();
+    const int cc = tid & 63, part = tid >> 6;
     double t = 0.0;
 #pragma unroll
-    for (int r = 0; r < 32; ++r) t += red[r][cc >> 3][which * 8 + (cc & 7)];
-    const int c = blockIdx.y * 64 + cc;
-    if (c < C) partial[((size_t)blockIdx.x * C + c) * 2 + which] = t;
+    for (int r = 0; r < kRows / 8; ++r) t += red[part * (kRows / 8) + r][cc >> 3][cc & 7];
+    red2[part][cc] = t;
+    __syncthreads();
+    if (tid < 64) {
+      t = 0.0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) t += red2[r][tid];
+      const int c = blockIdx.y * 64 + tid;
+      if (c < C) partial[((size_t)blockIdx.x * C + c) * 2 + which] = t;
+    }
   }
 }
 
@@ -182,6 +208,40 @@ __global__ __launch_bounds__(256) void bn_finalize_bwd_kernel(const double* __re
   means[((size_t)wk * C + c) * 2 + 1] = (float)(b / n);
 }
 
+// The forward value of eight channels: normalised, ReLU, and the residual add that follows, on the normalised value as it
+// would have been stored.
+__device__ inline void bn_normalise8(const float (&xv)[8], const float (&sk)[8], const float (&mu)[8], const float (&is)[8],
+                                     const float (&gm)[8], const float (&bt)[8], int relu, bool skip, int relu_add,
+                                     float (&o)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float y = gm[e] * ((xv[e] - mu[e]) * is[e]) + bt[e];
+    if (relu) y = y > 0.f ? y : 0.f;
+    if (skip) {
+      y = bf16_to_f32(f32_to_bf16(y)) + sk[e];
+      if (relu_add) y = y > 0.f ? y : 0.f;
+    }
+    o[e] = y;
+  }
+}
+// Stores them at element idx and, with sign_bits, "stored value > 0" as byte bidx.
+__device__ inline void bn_store8(const float (&o)[8], bf16_t* __restrict__ out, uint8_t* __restrict__ sign_bits, long idx,
+                                 long bidx) {
+  u32x4 t;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) t[d] = pack_bf16(o[2 * d], o[2 * d + 1]);
+  *reinterpret_cast<u32x4*>(out + idx) = t;
+  if (!sign_bits) return;
+  uint32_t bits = 0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const uint32_t lo = t[d] & 0xFFFFu, hi = t[d] >> 16;
+    bits |= ((lo != 0u && lo < 0x8000u) ? 1u : 0u) << (2 * d);
+    bits |= ((hi != 0u && hi < 0x8000u) ? 1u : 0u) << (2 * d + 1);
+  }
+  sign_bits[bidx] = (uint8_t)bits;
+}
+
 // Normalise (forward) or input gradient (backward).  grid (total chunks); a workgroup
 // walks one chunk of ONE worker's positions, so each thread keeps the statistics and
 // the affine parameters of its 8 channels in registers; C/8 threads cover a position,
@@ -232,38 +292,133 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict_
       const long q = p + (long)u * ppar;
       if (q >= cend) break;
       float o[8];
+      if (BWD) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float xh = (xv[u][e] - mu[e]) * is[e];
-        if (!BWD) {
-          float y = gm[e] * xh + bt[e];
-          if (relu) y = y > 0.f ? y : 0.f;
-          if (skip) {
-            // the residual add that follows, on the normalised value as it would have been stored
-            y = bf16_to_f32(f32_to_bf16(y)) + dv[u][e];
-            if (relu_add) y = y > 0.f ? y : 0.f;
-          }
-          o[e] = y;
-        } else {
+        for (int e = 0; e < 8; ++e) {
+          const float xh = (xv[u][e] - mu[e]) * is[e];
           o[e] = gm[e] * is[e] * (dv[u][e] - mn1[e] - xh * mn2[e]);
         }
-      }
-      if (!BWD && sign_bits) {
-        // (the piece is packed here rather than in Piece::store: the bits are those of the values as stored)
-        u32x4 t;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) t[d] = pack_bf16(o[2 * d], o[2 * d + 1]);
-        *reinterpret_cast<u32x4*>(out + q * C + c0) = t;
-        uint32_t bits = 0;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const uint32_t lo = t[d] & 0xFFFFu, hi = t[d] >> 16;
-          bits |= ((lo != 0u && lo < 0x8000u) ? 1u : 0u) << (2 * d);
-          bits |= ((hi != 0u && hi < 0x8000u) ? 1u : 0u) << (2 * d + 1);
-        }
-        sign_bits[q * c8n + pc] = (uint8_t)bits;
-      } else {
         Piece<bf16_t>::store(out + q * C + c0, o);
+      } else {
+        bn_normalise8(xv[u], dv[u], mu, is, gm, bt, relu, skip != nullptr, relu_add, o);
+        bn_store8(o, out, sign_bits, q * C + c0, q * c8n + pc);
+      }
+    }
+  }
+}
+
+// The same with the sums of the records in front, for layers with few records per worker and whole groups of 64
+// channels: grid (total chunks, C/64); every workgroup adds its worker's records for its 64 channels (at most 64 KB,
+// mostly from the L2, while its first positions are on their way), the worker's first chunk leaves the results
+// behind.  A launch of its own for them took 4-5 us of every batch norm, forward and backward: 180 of the 1700 us of a
+// ResNet-18 step at 128 images.
+constexpr int kFinishRecords = 64;
+template <bool BWD>
+__global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
+                                                        const double* __restrict__ partial, ShareTable rec,
+                                                        float* __restrict__ stats, const float* __restrict__ gamma,
+                                                        const float* __restrict__ beta, float* __restrict__ g_gamma,
+                                                        float* __restrict__ g_beta, size_t worker_stride, int C, int hw,
+                                                        Segments seg, ShareTable tb, int relu, bf16_t* __restrict__ out,
+                                                        const bf16_t* __restrict__ skip, int relu_add,
+                                                        uint8_t* __restrict__ sign_bits) {
+  __shared__ double red[4][64][2];
+  __shared__ float fin[64][2];
+  const int tid = threadIdx.x;
+  const int wk = share_owner(tb, seg.K, blockIdx.x);
+  const int chunk = blockIdx.x - tb.first[wk], nchunk = tb.first[wk + 1] - tb.first[wk];
+  const long pbeg = (long)seg.off[wk] * hw, pend = (long)seg.off[wk + 1] * hw;
+  const long per = (pend - pbeg + nchunk - 1) / nchunk;
+  const long cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
+  const int lp = tid >> 3, c8 = tid & 7, c0 = blockIdx.y * 64 + c8 * 8;
+  u32x4 xr[4], dr[4];   // dr: the output gradient (backward) or the residual input (forward, with skip)
+  auto fetch = [&](long p) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long q = max(min(p + 32 * u, cend - 1), pbeg);
+      xr[u] = *reinterpret_cast<const u32x4*>(x + q * C + c0);
+      if (BWD) dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + c0);
+      else if (skip) dr[u] = *reinterpret_cast<const u32x4*>(skip + q * C + c0);
+    }
+  };
+  fetch(cbeg + lp);
+  {
+    const int c = tid & 63, part = tid >> 6;
+    const int r0 = rec.first[wk], r1 = rec.first[wk + 1];
+    double a = 0.0, b = 0.0;
+    for (int r = r0 + part; r < r1; r += 32) {      // eight loads in flight, added in order
+      double2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = *reinterpret_cast<const double2*>(partial + ((size_t)min(r + 4 * u, r1 - 1) * C + blockIdx.y * 64 + c) * 2);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (r + 4 * u < r1) { a += v[u].x; b += v[u].y; }
+    }
+    red[part][c][0] = a;
+    red[part][c][1] = b;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const double a = ((red[0][tid][0] + red[1][tid][0]) + red[2][tid][0]) + red[3][tid][0];
+    const double b = ((red[0][tid][1] + red[1][tid][1]) + red[2][tid][1]) + red[3][tid][1];
+    const double n = (double)(pend - pbeg);
+    const int c = blockIdx.y * 64 + tid;
+    const double mean = a / n;
+    if (!BWD) {
+      double var = b / n - mean * mean;
+      var = var > 0.0 ? var : 0.0;
+      const float m = (float)mean, is = (float)(1.0 / sqrt(var + (double)kBnEps));
+      fin[tid][0] = m;
+      fin[tid][1] = is;
+      if (chunk == 0) {
+        stats[((size_t)wk * C + c) * 2] = m;
+        stats[((size_t)wk * C + c) * 2 + 1] = is;
+      }
+    } else {
+      fin[tid][0] = (float)mean;
+      fin[tid][1] = (float)(b / n);
+      if (chunk == 0) {
+        g_beta[(size_t)wk * worker_stride + c] = (float)a;
+        g_gamma[(size_t)wk * worker_stride + c] = (float)b;
+      }
+    }
+  }
+  float mu[8], is[8], gm[8], bt[8], mn1[8], mn2[8];
+  if (BWD) load_stats8(stats + ((size_t)wk * C + c0) * 2, mu, is);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    gm[e] = gamma[c0 + e];
+    bt[e] = BWD ? 0.f : beta[c0 + e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if (BWD) { mn1[e] = fin[c8 * 8 + e][0]; mn2[e] = fin[c8 * 8 + e][1]; }
+    else { mu[e] = fin[c8 * 8 + e][0]; is[e] = fin[c8 * 8 + e][1]; }
+  }
+  for (long p = cbeg + lp; p < cend; p += 128) {
+    u32x4 xc[4], dc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) { xc[u] = xr[u]; dc[u] = dr[u]; }
+    if (p - lp + 128 < cend) fetch(p + 128);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long q = p + 32L * u;
+      if (q >= cend) break;
+      float xv[8], dv[8], o[8];
+      unpack8(xc[u], xv);
+      if (BWD || skip) unpack8(dc[u], dv);
+      if (BWD) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float xh = (xv[e] - mu[e]) * is[e];
+          o[e] = gm[e] * is[e] * (dv[e] - mn1[e] - xh * mn2[e]);
+        }
+        Piece<bf16_t>::store(out + q * C + c0, o);
+      } else {
+        bn_normalise8(xv, dv, mu, is, gm, bt, relu, skip != nullptr, relu_add, o);
+        bn_store8(o, out, sign_bits, q * C + c0, q * (C / 8) + (c0 >> 3));
       }
     }
   }
@@ -376,15 +531,24 @@ ShareTable deal_shares(const Segments& seg, long total) {
   return tb;
 }
 
-// Splits of the statistics pass: about 2048 workgroups in all, every split `per` positions of one worker
-// (a multiple of the 128 positions of a trip), never more records than the scratch holds.
+// Splits of the statistics pass, every split `per` positions of one worker (a multiple of a trip): about 512 workgroups in
+// all and at most 64 records per worker (kFinishRecords), which the apply kernel then sums.  The largest tensors (from
+// four trips per workgroup on) are cut finer: beside weight gradients that hold most of the chip's LDS, 512
+// workgroups of 2048 images were 7 % slower than 2048, more than the launch that sums their records costs.
 ShareTable bn_splits(const Segments& seg, int C, int hw, int& per) {
   const int groups = (C + 63) / 64;
   const long positions = (long)seg.off[seg.K] * hw;
-  const long most = (long)seg.K * (kBnMaxSplits - 2);
-  long trips = std::max<long>(1, (positions * groups + 2048 * 64) / (2048L * 128));
-  while (positions / (128 * trips) + seg.K > most) ++trips;
-  per = (int)(128 * trips);
+  int bmax = 0;
+  for (int k = 0; k < seg.K; ++k) bmax = std::max(bmax, seg.off[k + 1] - seg.off[k]);
+  const long big = (long)bmax * hw;
+  long trips = std::max<long>(1, (positions * groups + 512 * kPartTrip - 1) / (512L * kPartTrip));
+  if (trips > 4) {
+    trips = std::max<long>(1, trips / 4);
+    while (positions / (kPartTrip * trips) + seg.K > (long)seg.K * (kBnMaxSplits - 2)) ++trips;
+  } else {
+    trips = std::max(trips, (big + (long)kFinishRecords * kPartTrip - 1) / ((long)kFinishRecords * kPartTrip));
+  }
+  per = (int)(kPartTrip * trips);
   ShareTable tb{};
   int acc = 0;
   for (int k = 0; k < seg.K; ++k) {
@@ -393,6 +557,19 @@ ShareTable bn_splits(const Segments& seg, int C, int hw, int& per) {
   }
   tb.first[seg.K] = acc;
   return tb;
+}
+
+bool few_records(const ShareTable& tb, int K, int C) {
+  if (C % 64 != 0) return false;
+  for (int k = 0; k < K; ++k)
+    if (tb.first[k + 1] - tb.first[k] > kFinishRecords) return false;
+  return true;
+}
+// Chunks of bn_finish_kernel: about 2048 workgroups at most, a trip of 128 positions being the least.
+ShareTable finish_chunks(const Segments& seg, int C, int hw) {
+  const long positions = (long)seg.off[seg.K] * hw;
+  const long total = std::min<long>((positions + 127) / 128, std::max(1, 2048 / (C / 64)));
+  return deal_shares(seg, std::max<long>(seg.K, total));
 }
 
 ShareTable bn_chunks(const Segments& seg, int C, int hw) {
@@ -417,8 +594,14 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
   const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
   const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
   if (!presummed)
-    hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(sp.first[seg.K], groups), dim3(256), 0, st, x, nullptr,
+    hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, nullptr,
                        nullptr, C, hw, seg, sp, per, partial);
+  if (few_records(sp, seg.K, C)) {
+    const ShareTable ch = finish_chunks(seg, C, hw);
+    hipLaunchKernelGGL(bn_finish_kernel<false>, dim3(ch.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
+                       gamma, beta, nullptr, nullptr, 0, C, hw, seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
+    return;
+  }
   hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
   const ShareTable ch = bn_chunks(seg, C, hw);
   hipLaunchKernelGGL(bn_apply_kernel<false>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, nullptr, stats, nullptr,
@@ -427,12 +610,20 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
 
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
                       const Segments& seg, const float* stats, float* means, double* partial, float* g_gamma,
-                      float* g_beta, size_t worker_stride) {
+                      float* g_beta, size_t worker_stride, const ShareTable* presummed) {
   int per = 0;
-  const ShareTable sp = bn_splits(seg, C, hw, per);
+  const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
   const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
-  hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(sp.first[seg.K], groups), dim3(256), 0, st, x, dy, stats, C, hw,
-                     seg, sp, per, partial);
+  if (!presummed)
+    hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, dy, stats, C,
+                       hw, seg, sp, per, partial);
+  if (few_records(sp, seg.K, C)) {
+    const ShareTable ch = finish_chunks(seg, C, hw);
+    hipLaunchKernelGGL(bn_finish_kernel<true>, dim3(ch.first[seg.K], groups), dim3(256), 0, st, x, dy, partial, sp,
+                       const_cast<float*>(stats), gamma, nullptr, g_gamma, g_beta, worker_stride, C, hw, seg, ch, 0, dx, nullptr,
+                       0, nullptr);
+    return;
+  }
   hipLaunchKernelGGL(bn_finalize_bwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, means,
                      g_gamma, g_beta, worker_stride);
   const ShareTable ch = bn_chunks(seg, C, hw);

@@ -66,7 +66,10 @@ struct WideParams {
   // belong to one worker).
   int gK;
   int32_t gfirst[OMNI_MAX_WORKERS + 1], ufirst[OMNI_MAX_WORKERS + 1];
-  double* stat_partial;   // STATS: [group][N][2] sums of the stored output and of its squares
+  int32_t ifirst[OMNI_MAX_WORKERS + 1];   // the entries' images
+  double* stat_partial;   // STATS: [group][N][2] sums of the stored output and of its squares (BWD: see BnStatRequest)
+  const bf16_t* stat_x;   // STATS and BWD: [rows*H*W][N]
+  const float* stat_norm; // ... [worker][N][2]
 };
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -99,13 +102,15 @@ __device__ inline void stat_exchange(float (&sv)[LEN], int j) {
 
 // MA: 32-position blocks per wavefront: 4 (a unit of 512 positions, one workgroup per compute unit) or 2 (256
 // positions, two workgroups per compute unit, whose load, store and compute phases overlap each other's).
-// STATS (forward, MA = 2, no bias, no ReLU): the per-channel sums of the group's stored outputs and of their
-// squares go to p.stat_partial, the first pass of the batch norm that follows, without reading the tensor back.
+// STATS (MA = 2, no bias, no ReLU): the per-channel sums of the group's stored outputs and of their squares go to
+// p.stat_partial, the first pass of the batch norm that follows, without reading the tensor back.  With BWD: the sums
+// of the stored gradient and of its product with the normalised input, the first pass of the batch norm's backward,
+// for one read of that input instead of two tensors (its means and factors wait in LDS).
 // BITS (input gradient): the ReLU mask is read as one bit per element, 8 bytes per position and channel tile
 // instead of 128.
 template <int MA, int NP, bool W8, bool BWD, bool STATS = false, bool BITS = false>
 __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(WideParams p) {
-  static_assert(!STATS || (MA == 2 && !BWD), "statistics come with the forward 256-position unit only");
+  static_assert(!STATS || (MA == 2 && (!BWD || BITS)), "statistics come with the 256-position unit only");
   static_assert(!BITS || BWD, "mask bits belong to the input gradient");
   constexpr int WPOS = 32 * MA;   // positions per wavefront
   extern __shared__ __attribute__((aligned(16))) unsigned char smemW[];
@@ -114,6 +119,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
   const int npatch = p.nimg * PR * PW;
   bf16_t* sP = reinterpret_cast<bf16_t*>(smemW);          // [npatch][kRow]
   bf16_t* sW = sP + (size_t)npatch * kRow;                // [9][64][kRow]
+  float* sN = reinterpret_cast<float*>(sW + 9 * kTN * kRow);   // STATS and BWD: [64][2]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 31, h = lane >> 5;
   const int tiles_n = (p.N + kTN - 1) / kTN;
@@ -172,12 +178,14 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
 
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
   u32x4 rp[NP], rw[9];
+  const int ibeg = p.ifirst[gk], iend = p.ifirst[gk + 1];
   auto unit_geom = [&](int unit, int& n0, int& r0, int& nvalid) {
+    unit -= p.ufirst[gk];
     if (p.nimg == 1) {
       const int upi = H / R, img = unit / upi;
-      n0 = img; r0 = (unit - img * upi) * R; nvalid = 1;
+      n0 = ibeg + img; r0 = (unit - img * upi) * R; nvalid = 1;
     } else {
-      n0 = unit * p.nimg; r0 = 0; nvalid = min(p.nimg, p.rows - n0);
+      n0 = ibeg + unit * p.nimg; r0 = 0; nvalid = min(p.nimg, iend - n0);
     }
   };
   // everything slice cs of `unit` needs, on its way to registers (all loads are unconditional)
@@ -206,7 +214,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
     }
   };
 
-  load_slice(min(ubeg, p.units - 1), 0);
+  if (STATS && BWD && tid < 2 * kTN) sN[tid] = p.stat_norm[((size_t)gk * p.N + col0) * 2 + tid];
+  load_slice(ubeg, 0);
   store_slice();
   __syncthreads();
 
@@ -273,7 +282,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
         const int toff = (p.flip ? (2 - u) * PW + (2 - v) : u * PW + v) * kRow;
         const int un = (tap + 1) / 3, vn = (tap + 1) - un * 3;
         const int toff_next = (p.flip ? (2 - un) * PW + (2 - vn) : un * PW + vn) * kRow;
-        if (BWD && (MA == 4 || (BITS && !W8)) && tap == 6 && last_slice) load_epi(0, 0);
+        if (BWD && (MA == 4 || (BITS && !W8 && !STATS)) && tap == 6 && last_slice) load_epi(0, 0);
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
           const int step = tap * KK + kk;
@@ -333,8 +342,17 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
         for (int e = 0; e < 4; ++e) { bias8[bq][e] = b0[e]; bias8[bq][4 + e] = b1[e]; }
       }
     }
-    if (BWD && MA == 2 && !(BITS && !W8)) load_epi(0, 0);
+    if (BWD && MA == 2 && !(BITS && !W8 && !STATS)) load_epi(0, 0);
     if (BWD && MA == 2) load_epi(1, 1);
+    u32x4 xs[MA][STATS && BWD ? 4 : 1];   // STATS and BWD: the batch norm's input at this lane's positions
+    if (STATS && BWD) {
+#pragma unroll
+      for (int a = 0; a < MA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          xs[a][STATS && BWD ? i : 0] = *reinterpret_cast<const u32x4*>(
+              ipos[a] < npos ? p.stat_x + ((size_t)(out_base + ipos[a]) * p.N + col0 + i * 16 + h * 8) : zp);
+    }
     // STATS: sv[which*32 + (b*2+q)*8 + e]: sums over this lane's positions of the stored values (which = 0) and
     // of their squares (1)
     float sv[STATS ? 64 : 1];
@@ -405,8 +423,15 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
               const int i = (b * 2 + q) * 8 + 2 * d;
               sv[STATS ? i : 0] += lo;
               sv[STATS ? i + 1 : 0] += hi;
-              sv[STATS ? 32 + i : 0] = fmaf(lo, lo, sv[STATS ? 32 + i : 0]);
-              sv[STATS ? 32 + i + 1 : 0] = fmaf(hi, hi, sv[STATS ? 32 + i + 1 : 0]);
+              float lo2 = lo, hi2 = hi;
+              if (BWD) {
+                const v4f nm = *reinterpret_cast<const v4f*>(sN + (b * 32 + q * 16 + h * 8 + 2 * d) * 2);
+                const uint32_t xw = xs[a][STATS && BWD ? b * 2 + q : 0][d];
+                lo2 = (bf16_lo(xw) - nm[0]) * nm[1];
+                hi2 = (bf16_hi(xw) - nm[2]) * nm[3];
+              }
+              sv[STATS ? 32 + i : 0] = fmaf(lo, lo2, sv[STATS ? 32 + i : 0]);
+              sv[STATS ? 32 + i + 1 : 0] = fmaf(hi, hi2, sv[STATS ? 32 + i + 1 : 0]);
             }
           }
         }
@@ -457,10 +482,13 @@ void launch_variant(hipStream_t st, const WideParams& p, dim3 grid, size_t lds) 
 template <int MA, int NP, bool W8>
 void launch_wide(hipStream_t st, const WideParams& p, dim3 grid, size_t lds, bool bwd, bool stats) {
   if (bwd) {
+    if constexpr (MA == 2) {
+      if (stats) return launch_variant<MA, NP, W8, true, true, true>(st, p, grid, lds);
+    }
     if (p.mask_bits) return launch_variant<MA, NP, W8, true, false, true>(st, p, grid, lds);
     return launch_variant<MA, NP, W8, true, false, false>(st, p, grid, lds);
   }
-  if constexpr (MA == 2 && !W8) {
+  if constexpr (MA == 2) {
     if (stats) return launch_variant<MA, NP, W8, false, true, false>(st, p, grid, lds);
   }
   launch_variant<MA, NP, W8, false, false, false>(st, p, grid, lds);
@@ -500,7 +528,7 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
     if (!unit_shape(H, W, 128 * cand, r, n)) continue;
     const int np_ = n * (r + 2) * (W + 2);
     const size_t l = ((size_t)np_ + 9 * kTN) * kRow * sizeof(bf16_t);   // patch + the nine taps' weights of a slice
-    if (l > (size_t)kLdsLimit / (cand == 2 ? 2 : 1)) continue;
+    if (l + 2 * kTN * sizeof(float) > (size_t)kLdsLimit / (cand == 2 ? 2 : 1)) continue;
     ma = cand; R = r; nimg = n; npatch = np_; lds = l;
     break;
   }
@@ -518,19 +546,23 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
   // the grid still covers the chip a few times over
   int upw = 1;
   while (upw < 8 && (long)units * tiles_n / (upw * 2) >= (ma == 2 ? 2048 : 1024)) upw *= 2;
-  // Batch-norm sums on the way out: units of one image (so a unit has one owner), no bias, no ReLU, and groups
-  // that do not cross from one worker to the next, few enough for the statistics scratch.
+  // Batch-norm sums on the way out: no bias, no ReLU, and units and groups that do not cross from one worker to the next,
+  // few enough groups for the statistics scratch.
   bool with_stats = false;
   p.gK = 1;
   p.ufirst[0] = 0; p.ufirst[1] = units;
-  if (stats && stats->partial && stats->seg && ma == 2 && nimg == 1 && !w8 && !bwd && !bias && !relu && N % kTN == 0 &&
-      stats->seg->off[stats->seg->K] == g.rows) {
+  p.ifirst[0] = 0; p.ifirst[1] = g.rows;
+  if (stats && stats->partial && stats->seg && ma == 2 && bwd == (stats->x != nullptr) && (!bwd || p.mask_bits) && !bias &&
+      !relu && N % kTN == 0 && stats->seg->off[stats->seg->K] == g.rows) {
     const Segments& seg = *stats->seg;
-    const int upi = H / R;
+    auto units_of = [&](int k) {
+      const long rows = seg.off[k + 1] - seg.off[k];
+      return nimg == 1 ? rows * (H / R) : (rows + nimg - 1) / nimg;
+    };
     int u = upw;
     auto groups_at = [&](int per) {
       long n = 0;
-      for (int k = 0; k < seg.K; ++k) n += ((long)(seg.off[k + 1] - seg.off[k]) * upi + per - 1) / per;
+      for (int k = 0; k < seg.K; ++k) n += (units_of(k) + per - 1) / per;
       return n;
     };
     while (groups_at(u) > (long)seg.K * kBnMaxSplits && u < 64) u *= 2;
@@ -538,11 +570,15 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
       with_stats = true;
       upw = u;
       p.gK = seg.K;
-      for (int k = 0; k <= seg.K; ++k) p.ufirst[k] = seg.off[k] * upi;
+      for (int k = 0; k < seg.K; ++k) p.ufirst[k + 1] = p.ufirst[k] + (int)units_of(k);
+      for (int k = 0; k <= seg.K; ++k) p.ifirst[k] = seg.off[k];
       p.stat_partial = stats->partial;
+      p.stat_x = stats->x;
+      p.stat_norm = stats->stats;
+      if (bwd) lds += 2 * kTN * sizeof(float);
     }
   }
-  p.units = units; p.upw = upw;
+  p.units = p.ufirst[p.gK]; p.upw = upw;
   p.gfirst[0] = 0;
   for (int k = 0; k < p.gK; ++k) p.gfirst[k + 1] = p.gfirst[k] + (p.ufirst[k + 1] - p.ufirst[k] + upw - 1) / upw;
   const int groups = p.gfirst[p.gK];

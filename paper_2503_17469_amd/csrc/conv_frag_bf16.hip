@@ -59,6 +59,8 @@ struct FragParams {
   bf16_t* pool;
   uint8_t* pool_code;
   double* stat_partial;   // [tile][N][2] or null
+  const bf16_t* stat_x;   // BWD: see BnStatRequest
+  const float* stat_norm;
 };
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -78,7 +80,7 @@ __device__ inline void stat_exchange(float (&sv)[LEN], int j) {
 }
 
 // KS: shares of the reduction (4: a wavefront has 64 positions and a quarter of the channels; 2: 32 positions and
-// half).  TAPS: 9 or 1.  BWD: mask / addend / accumulate instead of bias / ReLU / pooling / statistics.
+// half).  TAPS: 9 or 1.  BWD: mask / addend / accumulate instead of bias / ReLU / pooling.
 template <int KS, int TAPS, bool BWD>
 __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   constexpr int MA = KS == 4 ? 2 : 1;
@@ -243,8 +245,18 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   const int cb = min(col0 + eb * 32, p.N - 32);
   const size_t row = out_pos * p.N + cb;
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
-  u32x4 em[2], ea4[2];
+  u32x4 em[2], ea4[2], ex4[2];
+  v4f norm[2][4];                                  // BWD with statistics: (mean, 1/sqrt(var)) of this lane's channels
   uint32_t ebits = 0;
+  if (BWD && p.stat_partial) {
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq) {
+      ex4[qq] = *reinterpret_cast<const u32x4*>(row_in ? p.stat_x + row + qq * 16 + h * 8 : zp);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        norm[qq][i] = *reinterpret_cast<const v4f*>(p.stat_norm + ((size_t)gk * p.N + cb + qq * 16 + h * 8) * 2 + 4 * i);
+    }
+  }
   if (BWD) {
     const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
     if (p.mask_bits) ebits = *reinterpret_cast<const uint32_t*>(row_in ? p.mask_bits + (row >> 3) : static_cast<const uint8_t*>(p.zero));
@@ -328,10 +340,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
     for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
     if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
   }
-  if (BWD) return;
 
   if (p.stat_partial) {
-    // sums of the stored values and of their squares: fp32 over the 32 positions of a block (a fixed tree, entry
+    // sums of the stored values and of their squares (BWD: of the values times xhat): fp32 over the 32 positions of a block (a fixed tree, entry
     // which*16 + q*8 + e ends in lane j with bits which, q, e from the top), double over the two blocks
     float sv[32];
 #pragma unroll
@@ -341,8 +352,13 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
         const float lo = row_in ? bf16_lo(outp[qq][d]) : 0.f, hi = row_in ? bf16_hi(outp[qq][d]) : 0.f;
         sv[qq * 8 + 2 * d] = lo;
         sv[qq * 8 + 2 * d + 1] = hi;
-        sv[16 + qq * 8 + 2 * d] = lo * lo;
-        sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
+        if (BWD) {
+          sv[16 + qq * 8 + 2 * d] = lo * ((bf16_lo(ex4[qq][d]) - norm[qq][d][0]) * norm[qq][d][1]);
+          sv[16 + qq * 8 + 2 * d + 1] = hi * ((bf16_hi(ex4[qq][d]) - norm[qq][d][2]) * norm[qq][d][3]);
+        } else {
+          sv[16 + qq * 8 + 2 * d] = lo * lo;
+          sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
+        }
       }
     stat_exchange<16, 16>(sv, j);
     stat_exchange<8, 8>(sv, j);
@@ -359,7 +375,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
           (double)red[which * 64 + c] + (double)red[(2 + which) * 64 + c];
     }
   }
-  if (p.pool) {
+  if (!BWD && p.pool) {
     // a tile is whole rows of whole images, an even number of them: its pooled positions are a contiguous run too
     __syncthreads();
     constexpr int kRow = kTN + 8;
@@ -467,7 +483,8 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   p.mask_bits = (mask && N % 64 == 0) ? g.mask_bits : nullptr;
   if (!bwd && pool && pool_code && s.R % 2 == 0 && g.Hp % 2 == 0) { p.pool = pool; p.pool_code = pool_code; }
   // tiles; one worker's each where their batch-norm sums are wanted and there is room for one record per tile
-  const bool want = !bwd && stats && stats->partial && stats->seg && !bias && !relu && stats->seg->off[stats->seg->K] == g.rows;
+  const bool want = stats && stats->partial && stats->seg && !bias && !relu && stats->seg->off[stats->seg->K] == g.rows &&
+                    bwd == (stats->x != nullptr);
   auto tiles_of = [&](int images) { return s.upi == 1 ? (images + s.nimg - 1) / s.nimg : images * s.upi; };
   long records = 0;
   if (want)
@@ -478,6 +495,8 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
     p.gK = stats->seg->K;
     for (int k = 0; k <= p.gK; ++k) p.ifirst[k] = stats->seg->off[k];
     p.stat_partial = stats->partial;
+    p.stat_x = stats->x;
+    p.stat_norm = stats->stats;
   }
   for (int k = 0; k < p.gK; ++k) p.tfirst[k + 1] = p.tfirst[k] + tiles_of(p.ifirst[k + 1] - p.ifirst[k]);
   const int taps = g.ks * g.ks, tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;

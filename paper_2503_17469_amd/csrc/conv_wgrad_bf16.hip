@@ -1242,7 +1242,7 @@ double conv_wgrad_work(const ConvWgradJob& j) {
 }
 
 void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, const HeadWgradParams* head) {
+                      float* partial, const HeadWgradParams* head, int workgroups) {
   if (head && n == 0) {
     head_wgrad_loss(st, true, *head, seg);
     return;
@@ -1262,7 +1262,7 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
       work += pl.work;
       ++heavy;
     }
-    // Layers that share the launch share two workgroups per compute unit in proportion to the time their units take (not
+    // Layers that share the launch share its workgroups in proportion to the time their units take (not
     // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
     const size_t budget = conv_wgrad_partial_floats() / m;
     BatchTable tab{}, red{};
@@ -1270,7 +1270,7 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
     size_t lds = 0;
     for (int i = 0; i < m; ++i) {
       Plan& pl = plans[i];
-      const long aim = (i == light || heavy == 1) ? pl.alone : std::max<long>(1, (long)(512.0 * pl.work / work));
+      const long aim = (i == light || heavy == 1) ? pl.alone : std::max<long>(1, (long)(workgroups * pl.work / work));
       cut_chunks(pl, seg, aim, budget);
       set_partial(pl.job, partial + budget / 4 * 4 * i);
       pl.job.first_block = blocks;

@@ -140,12 +140,17 @@ constexpr int kZeroPageWords = 64;           // 256 bytes of zeros that loads of
 // first[k] .. first[k+1]-1 in order.
 struct ShareTable { int32_t first[OMNI_MAX_WORKERS + 1]; };
 constexpr int kBnMaxSplits = 256;  // the statistics scratch holds K * kBnMaxSplits records in all
-// A forward convolution whose output a batch norm normalises may write the first stage itself, from the
-// values it stores, instead of the batch norm reading the tensor once more: the caller fills partial and seg;
-// the kernel that takes the offer sets done and fills table (bn_forward_bf16 then skips its own first stage).
+// A convolution may write the first stage itself, from the values it stores, instead of the batch norm reading them once
+// more: forward, where a batch norm normalises its output (the sums of the values and of their squares), and input
+// gradient, where what it stores is the complete output gradient dy of a batch norm (the sums of dy and of dy * xhat;
+// x and stats are that batch norm's input and its [K][C][2] means and 1/sqrt(var + eps)).  The caller fills partial,
+// seg, x and stats; the kernel that takes the offer sets done and fills table (the batch norm then skips its own
+// first stage).
 struct BnStatRequest {
   double* partial;       // [K * kBnMaxSplits][C][2]
   const Segments* seg;
+  const bf16_t* x;       // null: forward
+  const float* stats;
   ShareTable table;
   bool done;
 };
@@ -223,9 +228,10 @@ struct ConvWgradJob {
 bool conv_wgrad_pooled_supported(int Cout, int cin_real, const ConvGeom& g);
 double conv_wgrad_work(const ConvWgradJob& job);   // flop
 // All jobs share launches (first stage, second stage).  partial: conv_wgrad_partial_floats() of scratch.  head (may be
-// null): the classifier's parameter gradients and losses as well (head_wgrad_loss).
+// null): the classifier's parameter gradients and losses as well (head_wgrad_loss).  workgroups: how many the layers of a
+// shared first stage are cut into (two fit a compute unit).
 void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, const HeadWgradParams* head);
+                      float* partial, const HeadWgradParams* head, int workgroups);
 
 // ---- bf16 pointwise kernels (pointwise_bf16.hip) ----
 // fp32 weights [cout][taps][cin_real] -> bf16 [cout][taps][cin_pad] (zero padded) and,
@@ -273,7 +279,7 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
 // means: [K][C][2] scratch; g_gamma / g_beta: worker k's entries at + k*worker_stride.
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
                       const Segments& seg, const float* stats, float* means, double* partial, float* g_gamma,
-                      float* g_beta, size_t worker_stride);
+                      float* g_beta, size_t worker_stride, const ShareTable* presummed = nullptr);
 void add_fwd_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* out, long elems, bool relu);
 // dst (+)= g, zeroed where mask <= 0 (mask may be null)
 void route_grad_bf16(hipStream_t st, const bf16_t* g, const bf16_t* mask, bf16_t* dst, long elems, bool accumulate);

@@ -726,7 +726,7 @@ void step_bf16(StepCtx& c) {
                           L.has_b ? c.params + L.b_off : nullptr, to.relu, nullptr);
         continue;
       }
-      omni::BnStatRequest offer{bn_partial, &c.seg, {}, false};
+      omni::BnStatRequest offer{bn_partial, &c.seg, nullptr, nullptr, {}, false};
       const bool pooled =
           omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g,
                                L.has_b ? c.params + L.b_off : nullptr, nullptr, to.relu, false,
@@ -818,7 +818,7 @@ void step_bf16(StepCtx& c) {
     hipStream_t side = use2 ? c.side2 : c.side;
     TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
     omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
-                           nullptr);
+                           nullptr, group_work > 2 * kGroupWork ? 512 : 256);   // (leaves room for the chain at small batches)
     group.clear();
     group_work = 0.0;
   };
@@ -849,12 +849,39 @@ void step_bf16(StepCtx& c) {
     return omni::LinearWgradBf16Job{grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin,
                                     L.d.cout, L.w_off, L.b_off};
   };
+  // The batch norm whose output gradient is complete once layer i's input gradient is stored, if it is the next one in
+  // this walk: the producer of layer i's input, or (through a residual add, which passes its gradient on to a batch
+  // norm that nothing else reads) the last batch norm before it.  Its sums are then offered to that convolution.
+  auto fed_bn = [&](int i) {
+    const int t = net->layers[i].in0;
+    auto producer = [&](int tensor, int below) {
+      for (int j = below - 1; j >= 0; --j)
+        if (!net->layers[j].fused_away && net->layers[j].out == tensor) return j;
+      return -1;
+    };
+    const int p = producer(t, i);
+    if (p < 0) return -1;
+    for (int j = p + 1; j < i; ++j)   // another reader of t, whose share is still to come
+      if (!net->layers[j].fused_away && (net->layers[j].in0 == t || net->layers[j].in1 == t)) return -1;
+    int bn = -1;
+    if (net->layers[p].d.op == OMNI_OP_BN) bn = p;
+    else if (net->layers[p].d.op == OMNI_OP_ADD)
+      for (int in : {net->layers[p].in0, net->layers[p].in1}) {
+        const int q = in < 0 ? -1 : producer(in, p);
+        if (q >= 0 && net->layers[q].d.op == OMNI_OP_BN && net->tensors[in].consumers == 1 && !net->tensors[in].relu &&
+            !written[in])
+          bn = std::max(bn, q);
+      }
+    for (int j = bn + 1; bn >= 0 && j < i; ++j)   // a batch norm in between would use the scratch first
+      if (!net->layers[j].fused_away && net->layers[j].d.op == OMNI_OP_BN) return -1;
+    return bn;
+  };
+  presummed_for = -1;
   for (int i = n_layers - 2; i >= 0; --i) {
     const Layer& L = net->layers[i];
     if (L.fused_away) continue;
     if (is_param_op(L.d.op)) {
       const omni::ConvGeom g = fwd_geom(L);
-      const Tensor& to = net->tensors[L.out];
       const bool conv = L.d.op == OMNI_OP_CONV;
       // The point a group of weight gradients waits for is recorded first, then the input gradient goes to the main
       // stream, and only then are the side stream's wait and launches issued: the main chain (the longer one)
@@ -899,8 +926,16 @@ void step_bf16(StepCtx& c) {
                             ti.relu ? act(L.in0) : nullptr);
         } else {
           d.mask_bits = (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr;
+          const int bn = conv ? fed_bn(i) : -1;
+          omni::BnStatRequest offer{bn_partial, &c.seg, nullptr, nullptr, {}, false};
+          if (bn >= 0) {
+            offer.x = act(net->layers[bn].in0);
+            offer.stats = bn_area + net->layers[bn].stat_off;
+          }
           omni::conv_gemm_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), m_rows, L.cin_pad, d, nullptr,
-                               ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend);
+                               ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend,
+                               bn >= 0 ? &offer : nullptr);
+          if (offer.done) { presummed = offer.table; presummed_for = bn; }
         }
         written[L.in0] = 1;
       }
@@ -926,7 +961,7 @@ void step_bf16(StepCtx& c) {
       float* stats = bn_area + L.stat_off;
       omni::bn_backward_bf16(st, act(L.in0), grad(L.out), grad(L.in0), c.params + L.w_off, L.ic, L.ih * L.iw, c.seg,
                              stats, stats + (size_t)net->K_max * L.ic * 2, bn_partial, c.G + L.w_off, c.G + L.b_off,
-                             net->P_stride);
+                             net->P_stride, i == presummed_for ? &presummed : nullptr);
       written[L.in0] = 1;
     } else if (L.d.op == OMNI_OP_ADD) {
       const long elems = (long)rows * L.ih * L.iw * L.ic;
@@ -957,7 +992,7 @@ void step_bf16(StepCtx& c) {
   }
   if (!net->linear_only) {
     TimedScope ts(net, st, OMNI_KERNEL_CONV_WGRAD, 0);
-    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3, &head_grads);
+    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3, &head_grads, 512);
   }
   if (!linear_jobs.empty() || (net->linear_only && c.fuse_update)) {
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);   // the hidden fully connected layers', in one launch
