@@ -14,6 +14,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "update_device.h"
+#include "xcd_tiles.h"
 
 namespace omni {
 
@@ -32,6 +33,7 @@ struct BfGemm {
   const float* bias;   // [N], may be null
   const bf16_t* mask;  // [M][N], the value passes where mask > 0, may be null
   int relu;
+  XcdTiles tiles;
 };
 
 // A workgroup owns a tile of 32 WB x 32 WB outputs; its four wavefronts split the reduction, each with the whole tile in
@@ -51,8 +53,8 @@ __global__ __launch_bounds__(256, 2) void bf16_gemm_kernel(BfGemm p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, h = lane >> 5, lrow = lane >> 3, lp = lane & 7;
   const int M = p.M, N = p.N, K = p.K;
-  const int tiles_m = (M + T - 1) / T;
-  const int tile_n = (int)blockIdx.x / tiles_m, tile_m = (int)blockIdx.x - tile_n * tiles_m;
+  int tile_m, tile_n;
+  if (!xcd_tile(p.tiles, (int)blockIdx.x, tile_m, tile_n)) return;
   const int row0 = tile_m * T, col0 = tile_n * T;
   uint32_t* la = lds + wave * kWave;
   uint32_t* lb = la + T * kLineWords;
@@ -382,13 +384,15 @@ inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * (
 
 void linear_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* c, int M, int N, int K, const float* bias,
                  bool relu, const bf16_t* mask) {
-  const BfGemm p{a, b, c, M, N, K, bias, mask, relu ? 1 : 0};
+  BfGemm p{a, b, c, M, N, K, bias, mask, relu ? 1 : 0, {}};
   // 64 x 64 tiles need half the operand traffic of 32 x 32 ones; they are taken once they cover the compute units
   const int t64 = tiles_of(M, N, 64);
-  if (t64 >= 192)
-    hipLaunchKernelGGL((bf16_gemm_kernel<2>), dim3(t64), dim3(256), 0, st, p);
+  const int T = t64 >= 192 ? 64 : 32;
+  p.tiles = xcd_tiles((M + T - 1) / T, (N + T - 1) / T);
+  if (T == 64)
+    hipLaunchKernelGGL((bf16_gemm_kernel<2>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL((bf16_gemm_kernel<1>), dim3(tiles_of(M, N, 32)), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((bf16_gemm_kernel<1>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
 }
 
 void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,

@@ -27,6 +27,7 @@
 #include "head_device.h"
 #include "kernels.h"
 #include "update_device.h"
+#include "xcd_tiles.h"
 
 namespace omni {
 
@@ -69,6 +70,7 @@ struct SmallGemm {
   const float* bias;   // forward, may be null
   const float* mask;   // dgrad, [M][N], may be null
   int relu, accumulate;
+  XcdTiles tiles;
 };
 
 // A k-contiguous operand of a chunk, 16 WB rows of 128 bytes, arrives with 8 lanes per row (whole lines per group of
@@ -128,8 +130,8 @@ __global__ __launch_bounds__(64 * NW) void small_gemm_kernel(SmallGemm p) {
   __shared__ __attribute__((aligned(16))) float lds[NW * kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int tiles_m = (p.M + T - 1) / T;
-  const int tile_n = (int)blockIdx.x / tiles_m, tile_m = (int)blockIdx.x - tile_n * tiles_m;
+  int tile_m, tile_n;
+  if (!xcd_tile(p.tiles, (int)blockIdx.x, tile_m, tile_n)) return;
   const int row0 = tile_m * T, col0 = tile_n * T;
   const int M = p.M, N = p.N, K = p.K;
   float* la = lds + wave * kWave;
@@ -539,16 +541,18 @@ namespace {
 inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * ((cols + t - 1) / t); }
 
 template <bool DGRAD>
-void small_gemm(hipStream_t st, const SmallGemm& p) {
+void small_gemm(hipStream_t st, SmallGemm p) {
   // Four wavefronts per tile (with 8 or 16 the reduction is split further, but every one of them waits for its first
   // chunk: no faster anywhere).  32 x 32 tiles need half the operand traffic, 16 x 16 tiles spread a product with few
-  // tiles over more compute units: measured, the lines cross near 160 tiles of 32 x 32 (forward) and 112 (dgrad).
+  // tiles over more compute units: measured, the lines cross near 160 tiles of 32 x 32.
   const int t32 = tiles_of(p.M, p.N, 32);
-  const bool wide = p.N >= 2 && p.K >= 256 && t32 >= (DGRAD ? 112 : 160);
+  const bool wide = p.N >= 2 && p.K >= 256 && t32 >= 160;
+  const int T = wide ? 32 : 16;
+  p.tiles = xcd_tiles((p.M + T - 1) / T, (p.N + T - 1) / T);
   if (wide)
-    hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 2, 4>), dim3(t32), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 2, 4>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 1, 4>), dim3(tiles_of(p.M, p.N, 16)), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 1, 4>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
 }
 
 template <int WB, int NW>
@@ -576,12 +580,12 @@ bool linear_f32_small(int rows, int cols, int kred) {
 
 void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows,
                           int cin, int cout, bool relu) {
-  small_gemm<false>(st, SmallGemm{x, w, y, rows, cout, cin, bias, nullptr, relu ? 1 : 0, 0});
+  small_gemm<false>(st, SmallGemm{x, w, y, rows, cout, cin, bias, nullptr, relu ? 1 : 0, 0, {}});
 }
 
 void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows,
                             int cin, int cout, bool accumulate) {
-  small_gemm<true>(st, SmallGemm{dy, w, dx, rows, cin, cout, nullptr, mask, 0, accumulate ? 1 : 0});
+  small_gemm<true>(st, SmallGemm{dy, w, dx, rows, cin, cout, nullptr, mask, 0, accumulate ? 1 : 0, {}});
 }
 
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
