@@ -12,6 +12,7 @@
 
 #include "bf16.h"
 #include "common.h"
+#include "head_device.h"
 #include "kernels.h"
 #include "update_device.h"
 #include "xcd_tiles.h"
@@ -44,17 +45,18 @@ struct BfGemm {
 constexpr int kLine = 64;          // reduction elements of a chunk: 128 bytes
 constexpr int kLineWords = 36;
 
+template <int WB> constexpr int bf16_gemm_words() { return 4 * 2 * 32 * WB * kLineWords; }
+
 template <int WB>
-__global__ __launch_bounds__(256, 2) void bf16_gemm_kernel(BfGemm p) {
+__device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint32_t* lds) {
   constexpr int T = 32 * WB, NL = 4 * WB, D = 2;     // NL: 16-byte pieces of an operand's chunk per lane
   constexpr int kWave = 2 * T * kLineWords;          // words of a wavefront's LDS block
   static_assert(kWave >= T * T, "the partial tile reuses the staging block");
-  __shared__ __attribute__((aligned(16))) uint32_t lds[4 * kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 31, h = lane >> 5, lrow = lane >> 3, lp = lane & 7;
   const int M = p.M, N = p.N, K = p.K;
   int tile_m, tile_n;
-  if (!xcd_tile(p.tiles, (int)blockIdx.x, tile_m, tile_n)) return;
+  if (!xcd_tile(p.tiles, block, tile_m, tile_n)) return;
   const int row0 = tile_m * T, col0 = tile_n * T;
   uint32_t* la = lds + wave * kWave;
   uint32_t* lb = la + T * kLineWords;
@@ -177,6 +179,22 @@ __global__ __launch_bounds__(256, 2) void bf16_gemm_kernel(BfGemm p) {
     }
     Piece<bf16_t>::store(p.C + idx, y);
   }
+}
+
+template <int WB>
+__global__ __launch_bounds__(256, 2) void bf16_gemm_kernel(BfGemm p) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[bf16_gemm_words<WB>()];
+  bf16_gemm_body<WB>(p, (int)blockIdx.x, lds);
+}
+
+// An input gradient and, in front of its tiles, the classifier's parameter gradients and losses.
+template <int WB>
+__global__ __launch_bounds__(256, 2) void bf16_dgrad_head_kernel(BfGemm p, HeadRole head, Segments seg) {
+  constexpr int kWords = bf16_gemm_words<WB>() > kHeadWgradLdsFloats ? bf16_gemm_words<WB>() : kHeadWgradLdsFloats;
+  __shared__ __attribute__((aligned(16))) uint32_t lds[kWords];
+  const int b = (int)blockIdx.x;
+  if (b < head.blocks) head_wgrad_loss_body<bf16_t>(head.p, seg, b % head.gx, b / head.gx, reinterpret_cast<float*>(lds));
+  else bf16_gemm_body<WB>(p, b - head.blocks, lds);
 }
 
 // ------------------------------------------------------------------ weight gradients
@@ -383,12 +401,19 @@ inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * (
 }  // namespace
 
 void linear_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* c, int M, int N, int K, const float* bias,
-                 bool relu, const bf16_t* mask) {
+                 bool relu, const bf16_t* mask, const HeadWgradParams* head, const Segments& seg) {
   BfGemm p{a, b, c, M, N, K, bias, mask, relu ? 1 : 0, {}};
   // 64 x 64 tiles need half the operand traffic of 32 x 32 ones; they are taken once they cover the compute units
   const int t64 = tiles_of(M, N, 64);
   const int T = t64 >= 192 ? 64 : 32;
   p.tiles = xcd_tiles((M + T - 1) / T, (N + T - 1) / T);
+  if (head) {
+    const HeadRole role = head_role(head, seg);
+    const dim3 grid(p.tiles.grid() + role.blocks);
+    if (T == 64) hipLaunchKernelGGL(bf16_dgrad_head_kernel<2>, grid, dim3(256), 0, st, p, role, seg);
+    else hipLaunchKernelGGL(bf16_dgrad_head_kernel<1>, grid, dim3(256), 0, st, p, role, seg);
+    return;
+  }
   if (T == 64)
     hipLaunchKernelGGL((bf16_gemm_kernel<2>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
   else

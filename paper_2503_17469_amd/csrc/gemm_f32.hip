@@ -433,18 +433,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f32_kernel(GemmParams p) {
   gemm_f32_body<BK, A_MC, B_MC, MODE, 0>(p, Segments{}, (int)blockIdx.x, (int)gridDim.x, lds);
 }
 
-// An input gradient and, behind its tiles, the classifier's parameter gradients and losses (see HeadWgradParams): the
-// head's workgroups wait for memory most of the time and run beside the product's.
-__global__ __launch_bounds__(kThreads, 2) void gemm_f32_dgrad_head_kernel(GemmParams p, int tiles, HeadWgradParams h,
-                                                                          int head_gx, Segments seg) {
+// An input gradient and, in front of its tiles, the classifier's parameter gradients and losses: its workgroups wait for
+// memory most of the time and run beside the product's.
+__global__ __launch_bounds__(kThreads, 4) void gemm_f32_dgrad_head_kernel(GemmParams p, int tiles, HeadRole head,
+                                                                          Segments seg) {
   constexpr int kGemm = gemm_lds_floats<32, false, true, MODE_DGRAD>();
   __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
-  if ((int)blockIdx.x < tiles) {
-    gemm_f32_body<32, false, true, MODE_DGRAD, 0>(p, seg, (int)blockIdx.x, tiles, lds);
-  } else {
-    const int hb = (int)blockIdx.x - tiles;
-    head_wgrad_loss_body<float>(h, seg, hb % head_gx, hb / head_gx, lds);
-  }
+  const int b = (int)blockIdx.x;
+  if (b < head.blocks)
+    head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, lds);
+  else
+    gemm_f32_body<32, false, true, MODE_DGRAD, 0>(p, seg, b - head.blocks, tiles, lds);
 }
 
 // Weight gradients of several layers in ONE launch: the workgroups of the problems follow each other
@@ -515,26 +514,24 @@ void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float*
   launch<false, false, MODE_FWD>(st, p);
 }
 
-bool linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
+void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
                       int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg) {
-  if (linear_dgrad_f32_direct(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg)) return head != nullptr;
+  if (linear_dgrad_f32_direct(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg)) return;
   if (linear_f32_small(rows, cin, cout)) {
-    linear_dgrad_f32_small(st, dy, w, mask, dx, rows, cin, cout, accumulate);
-    return false;
+    linear_dgrad_f32_small(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg);
+    return;
   }
   GemmParams p{};
   p.A = dy; p.B = w; p.C = dx; p.M = rows; p.N = cin; p.lda = cout; p.ldb = cin; p.ldc = cin;
   p.kred = cout; p.mask = mask; p.accumulate = accumulate ? 1 : 0;
   if (!head) {
     launch<false, true, MODE_DGRAD>(st, p);
-    return false;
+    return;
   }
   const int tiles = gemm_tiles(p.M, p.N);
   p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
-  const dim3 hg = head_wgrad_grid(head->cin, head->C, seg.K);
-  hipLaunchKernelGGL(gemm_f32_dgrad_head_kernel, dim3(tiles + hg.x * hg.y), dim3(kThreads), 0, st, p, tiles, *head,
-                     (int)hg.x, seg);
-  return true;
+  const HeadRole role = head_role(head, seg);
+  hipLaunchKernelGGL(gemm_f32_dgrad_head_kernel, dim3(tiles + role.blocks), dim3(kThreads), 0, st, p, tiles, role, seg);
 }
 
 bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows) {

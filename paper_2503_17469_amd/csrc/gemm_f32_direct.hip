@@ -262,22 +262,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_direct_kernel(DirectParams p
 
 // Two independent kernels of the fp32 backward pass in one launch: the input gradient of the layer
 // below the classifier, and the classifier's own parameter gradients with the losses (both need
-// only the head's output gradient).  The first dgrad_tiles workgroups are the product's tiles,
-// the rest the head's grid flattened row by row.  Launched one after the other, the second
-// starts when the first has drained; the product has fewer tiles than the chip has room for,
-// and the head's short workgroups run beside them.
-__global__ __launch_bounds__(256) void dgrad_and_head_wgrad_kernel(DirectParams p, int dgrad_tiles, HeadWgradParams h,
-                                                                   int head_gx, Segments seg) {
+// only the head's output gradient).  Launched one after the other, the second starts when the first has drained;
+// the product has fewer tiles than the chip has room for, and the head's short workgroups run beside them.
+__global__ __launch_bounds__(256) void dgrad_and_head_wgrad_kernel(DirectParams p, int tiles, HeadRole head, Segments seg) {
   constexpr int kFloats = direct_lds_floats<true, 4>() > kHeadWgradLdsFloats ? direct_lds_floats<true, 4>()
                                                                               : kHeadWgradLdsFloats;
   __shared__ __attribute__((aligned(16))) float smem[kFloats];
   const int b = blockIdx.x;
-  if (b < dgrad_tiles) {
-    gemm_f32_direct_body<true, 4>(p, b, dgrad_tiles, smem);
-  } else {
-    const int hb = b - dgrad_tiles;
-    head_wgrad_loss_body<float>(h, seg, hb % head_gx, hb / head_gx, smem);
-  }
+  if (b < head.blocks)
+    head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, smem);
+  else
+    gemm_f32_direct_body<true, 4>(p, b - head.blocks, tiles, smem);
 }
 
 inline bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
@@ -337,9 +332,8 @@ bool linear_dgrad_f32_direct(hipStream_t st, const float* dy, const float* w, co
   }
   const int tiles = ((p.M + 31) / 32) * ((p.N + 63) / 64);
   p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
-  const dim3 hg = head_wgrad_grid(head->cin, head->C, seg.K);
-  hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel, dim3(tiles + hg.x * hg.y), dim3(256), 0, st, p, tiles, *head,
-                     (int)hg.x, seg);
+  const HeadRole role = head_role(head, seg);
+  hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel, dim3(tiles + role.blocks), dim3(256), 0, st, p, tiles, role, seg);
   return true;
 }
 

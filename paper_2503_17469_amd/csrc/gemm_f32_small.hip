@@ -123,15 +123,17 @@ __device__ __forceinline__ void frag_clear_below(SmallFrag<WB>& f, int lo, int g
 }
 
 template <bool DGRAD, int WB, int NW>
-__global__ __launch_bounds__(64 * NW) void small_gemm_kernel(SmallGemm p) {
+constexpr int small_gemm_floats() { return NW * (DGRAD ? 1 : 2) * 16 * WB * kRowFloats; }
+
+template <bool DGRAD, int WB, int NW>
+__device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, float* lds) {
   constexpr int T = 16 * WB, D = 2;                        // D chunks on their way from memory
   constexpr int kWave = (DGRAD ? 1 : 2) * T * kRowFloats;  // floats of a wavefront's LDS block (at least its partial tile)
   static_assert(kWave >= T * T, "the partial tile reuses the staging block");
-  __shared__ __attribute__((aligned(16))) float lds[NW * kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
   int tile_m, tile_n;
-  if (!xcd_tile(p.tiles, (int)blockIdx.x, tile_m, tile_n)) return;
+  if (!xcd_tile(p.tiles, block, tile_m, tile_n)) return;
   const int row0 = tile_m * T, col0 = tile_n * T;
   const int M = p.M, N = p.N, K = p.K;
   float* la = lds + wave * kWave;
@@ -268,6 +270,22 @@ __global__ __launch_bounds__(64 * NW) void small_gemm_kernel(SmallGemm p) {
     }
     p.C[idx] = y;
   }
+}
+
+template <bool DGRAD, int WB, int NW>
+__global__ __launch_bounds__(64 * NW) void small_gemm_kernel(SmallGemm p) {
+  __shared__ __attribute__((aligned(16))) float lds[small_gemm_floats<DGRAD, WB, NW>()];
+  small_gemm_body<DGRAD, WB, NW>(p, (int)blockIdx.x, lds);
+}
+
+// An input gradient and, in front of its tiles, the classifier's parameter gradients and losses.
+template <int WB>
+__global__ __launch_bounds__(256) void small_dgrad_head_kernel(SmallGemm p, HeadRole head, Segments seg) {
+  constexpr int kGemm = small_gemm_floats<true, WB, 4>();
+  __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
+  const int b = (int)blockIdx.x;
+  if (b < head.blocks) head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, lds);
+  else small_gemm_body<true, WB, 4>(p, b - head.blocks, lds);
 }
 
 // ------------------------------------------------------------------ weight gradients
@@ -541,7 +559,7 @@ namespace {
 inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * ((cols + t - 1) / t); }
 
 template <bool DGRAD>
-void small_gemm(hipStream_t st, SmallGemm p) {
+void small_gemm(hipStream_t st, SmallGemm p, const HeadWgradParams* head, const Segments& seg) {
   // Four wavefronts per tile (with 8 or 16 the reduction is split further, but every one of them waits for its first
   // chunk: no faster anywhere).  32 x 32 tiles need half the operand traffic, 16 x 16 tiles spread a product with few
   // tiles over more compute units: measured, the lines cross near 160 tiles of 32 x 32.
@@ -549,6 +567,13 @@ void small_gemm(hipStream_t st, SmallGemm p) {
   const bool wide = p.N >= 2 && p.K >= 256 && t32 >= 160;
   const int T = wide ? 32 : 16;
   p.tiles = xcd_tiles((p.M + T - 1) / T, (p.N + T - 1) / T);
+  if (DGRAD && head) {
+    const HeadRole role = head_role(head, seg);
+    const dim3 grid(p.tiles.grid() + role.blocks);
+    if (wide) hipLaunchKernelGGL(small_dgrad_head_kernel<2>, grid, dim3(256), 0, st, p, role, seg);
+    else hipLaunchKernelGGL(small_dgrad_head_kernel<1>, grid, dim3(256), 0, st, p, role, seg);
+    return;
+  }
   if (wide)
     hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 2, 4>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
   else
@@ -580,12 +605,12 @@ bool linear_f32_small(int rows, int cols, int kred) {
 
 void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows,
                           int cin, int cout, bool relu) {
-  small_gemm<false>(st, SmallGemm{x, w, y, rows, cout, cin, bias, nullptr, relu ? 1 : 0, 0, {}});
+  small_gemm<false>(st, SmallGemm{x, w, y, rows, cout, cin, bias, nullptr, relu ? 1 : 0, 0, {}}, nullptr, Segments{});
 }
 
 void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows,
-                            int cin, int cout, bool accumulate) {
-  small_gemm<true>(st, SmallGemm{dy, w, dx, rows, cin, cout, nullptr, mask, 0, accumulate ? 1 : 0, {}});
+                            int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg) {
+  small_gemm<true>(st, SmallGemm{dy, w, dx, rows, cin, cout, nullptr, mask, 0, accumulate ? 1 : 0, {}}, head, seg);
 }
 
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,

@@ -320,6 +320,8 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
                            seg, z, dz, loss_rows, use_mask, static_cast<float*>(dx));
 }
 
+int head_wgrad_columns_for(int cin, int classes, int K) { return head_wgrad_columns(cin, classes, K); }
+
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg) {
   const dim3 grid = head_wgrad_grid(h.cin, h.C, seg.K);
   if (bf16)

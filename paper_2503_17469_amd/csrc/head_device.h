@@ -66,22 +66,30 @@ __device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Se
   }
 }
 
-constexpr int kHeadWgradLdsFloats = 16 * 16 * 17 + 256 * 16;
+// LDS: the row groups' sums of 256 / JC groups x 16 classes x JC columns (rows of JC + 1), and 256 rows of dz.
+constexpr int kHeadWgradLdsFloats = 64 * 16 * 5 + 256 * 16;
+// Input columns per workgroup: 16, or 8 or 4 where that leaves most of the chip idle (a worker's rows are walked by one
+// workgroup per 16 classes and JC columns: one worker with 4096 rows of 1024 columns took 66 us in 64 workgroups).
+inline int head_wgrad_columns(int cin, int classes, int K) {
+  const long groups = (long)K * ((classes + 15) / 16);
+  for (int jc = 16; jc > 4; jc /= 2)
+    if (groups * ((cin + jc - 1) / jc) >= 256) return jc;
+  return 4;
+}
 inline dim3 head_wgrad_grid(int cin, int classes, int K) {
-  return dim3(K * ((cin + 15) / 16) + 1, (classes + 15) / 16, 1);
+  const int jc = head_wgrad_columns(cin, classes, K);
+  return dim3(K * ((cin + jc - 1) / jc) + 1, (classes + 15) / 16, 1);
 }
 
-// Workgroup (bx, by) of a K * ceil(cin/16) + 1 by ceil(C/16) grid (head_wgrad_grid), 256 threads,
-// kHeadWgradLdsFloats floats of LDS at smem (16-byte aligned).  A workgroup is 16 input
-// columns x 16 row groups; each thread walks its share of the worker's rows.
-// The worker's dz rows (16 classes of them) are staged in LDS 256 rows at a time:
-// fetched per thread they would be 16 global loads per row, and the vector cache,
-// not the arithmetic, would set the pace.
-template <typename T>
-__device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, const Segments& seg, int bx, int by,
-                                                     float* smem) {
-  float (*red)[16][17] = reinterpret_cast<float (*)[16][17]>(smem);
-  float (*dzs)[16] = reinterpret_cast<float (*)[16]>(smem + 16 * 16 * 17);
+// One worker, JC input columns, 16 classes; 256 threads.  Each thread walks one column and every (256 / JC)-th row: of 256
+// rows at a time all its elements are on their way before the rows' dz (16 classes of them) is staged in LDS (fetched
+// per thread they would be 16 global loads per row, and the vector cache, not the arithmetic, would set the pace).
+template <typename T, int JC>
+__device__ __forceinline__ void head_wgrad_columns_body(const HeadWgradParams& h, const Segments& seg, int bx, int by,
+                                                        float* smem) {
+  constexpr int RS = 256 / JC;
+  float (*red)[16][JC + 1] = reinterpret_cast<float (*)[16][JC + 1]>(smem);
+  float (*dzs)[16] = reinterpret_cast<float (*)[16]>(smem + RS * 16 * (JC + 1));
   const float* __restrict__ dz = h.dz;
   const T* __restrict__ x = static_cast<const T*>(h.x);
   const int cin = h.cin, C = h.C;
@@ -89,17 +97,10 @@ __device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, c
   float* __restrict__ gb = h.gb;
   const size_t worker_stride = h.worker_stride;
   const int tid = threadIdx.x;
-  const int jchunks = (cin + 15) / 16;
-
-  if (bx == seg.K * jchunks) {
-    if (by == 0)
-      head_loss_body(HeadLossParams{h.labels, h.C, h.loss_rows, h.loss_per_worker, h.loss, h.status}, seg, smem);
-    return;
-  }
-
+  const int jchunks = (cin + JC - 1) / JC;
   const int wk = bx / jchunks, jc = bx % jchunks;
-  const int jl = tid & 15, rs = tid >> 4;
-  const int j = min(jc * 16 + jl, cin - 1);   // a column past the end shadows the last one and is not stored
+  const int jl = tid % JC, rs = tid / JC;
+  const int j = min(jc * JC + jl, cin - 1);   // a column past the end shadows the last one and is not stored
   const int c0 = by * 16;
   const int nc = min(16, C - c0);
   const int s_end = seg.off[wk + 1];
@@ -107,66 +108,69 @@ __device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, c
   float acc[16];
 #pragma unroll
   for (int c = 0; c < 16; ++c) acc[c] = 0.f;
-  float bsum = 0.f;   // class jl, rows rs, rs+16, ...
+  float bsum = 0.f;   // class tid % 16, rows tid / 16, + 16, ...
 
   for (int base = seg.off[wk]; base < s_end; base += 256) {
     const int n = min(256, s_end - base);
-    __syncthreads();   // the previous 256 rows have been consumed
+    // (a worker often has fewer rows than that: groups of four loads that would all lie past the end are left out)
+    const T* xb = x + (size_t)base * cin;          // (uniform bases and 32-bit offsets: half the address registers)
+    const float* dzb = dz + (size_t)base * C + c0;
+    float av[JC];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int f = tid + 256 * i, rr = f >> 4, c = f & 15;
-      const bool ok = rr < n && c < nc;
-      const float v = dz[(size_t)(base + (ok ? rr : 0)) * C + c0 + (ok ? c : 0)];
-      dzs[rr][c] = ok ? v : 0.f;
+    for (int u = 0; u < JC; ++u) {
+      if (u % 4 == 0 && RS * u >= n) break;
+      av[u] = Piece<T>::get(xb + (min(rs + RS * u, n - 1) * cin + j));   // (dz of rows past the end: 0)
+    }
+#pragma unroll
+    for (int i0 = 0; i0 < 16; i0 += 8) {          // (eight at a time: registers)
+      if (16 * i0 >= n) break;
+      float dv[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int rr = (tid >> 4) + 16 * (i0 + i), c = tid & 15;
+        const bool ok = rr < n && c < nc;
+        const float v = dzb[ok ? rr * C + c : 0];
+        dv[i] = ok ? v : 0.f;
+      }
+      if (i0 == 0) __syncthreads();               // the previous 256 rows have been consumed
+#pragma unroll
+      for (int i = 0; i < 8; ++i) dzs[(tid >> 4) + 16 * (i0 + i)][tid & 15] = dv[i];
     }
     __syncthreads();
-    const T* xb = x + (size_t)base * cin + j;
-    int sl = rs;
-    for (; sl + 112 < n; sl += 128) {        // eight rows per trip: their loads overlap
-      float av[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) av[u] = Piece<T>::get(xb + (size_t)(sl + 16 * u) * cin);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const v4f* d = reinterpret_cast<const v4f*>(&dzs[sl + 16 * u][0]);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const v4f dv = d[q];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[4 * q + e] += dv[e] * av[u];
-        }
-      }
-    }
-    for (; sl < n; sl += 16) {
-      const float a = Piece<T>::get(xb + (size_t)sl * cin);
-      const v4f* d = reinterpret_cast<const v4f*>(&dzs[sl][0]);
+    for (int u = 0; u < JC; ++u) {
+      if (u % 4 == 0 && RS * u >= n) break;
+      // (a row of the group that the staged rows do not reach is not counted)
+      const bool live = rs + RS * u < n;
+      const v4f* d = reinterpret_cast<const v4f*>(&dzs[live ? rs + RS * u : 0][0]);
+      const float a = live ? av[u] : 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const v4f dv = d[q];
+        const v4f t = d[q];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[4 * q + e] += dv[e] * a;
+        for (int e = 0; e < 4; ++e) acc[4 * q + e] += t[e] * a;
       }
     }
     if (want_bias)
-      for (int r2 = rs; r2 < n; r2 += 16) bsum += dzs[r2][jl];
+      for (int r2 = tid >> 4; r2 < n; r2 += 16) bsum += dzs[r2][tid & 15];
   }
 
 #pragma unroll
   for (int c = 0; c < 16; ++c) red[rs][c][jl] = acc[c];
   __syncthreads();
-  {
-    const int c = tid >> 4, jj = tid & 15;
+  if (tid < 16 * JC) {
+    const int c = tid / JC, jj = tid % JC;
     float t = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) t += red[r][c][jj];
-    if (c < nc && jc * 16 + jj < cin)
-      gw[(size_t)wk * worker_stride + (size_t)(c0 + c) * cin + jc * 16 + jj] = t;
+#pragma unroll 16
+    for (int r = 0; r < RS; ++r) t += red[r][c][jj];
+    if (c < nc && jc * JC + jj < cin)
+      gw[(size_t)wk * worker_stride + (size_t)(c0 + c) * cin + jc * JC + jj] = t;
   }
   if (want_bias) {
     // bias gradient: column sums of dz over the worker's rows, 16 row groups x 16 classes
     __syncthreads();
     float* r2 = &red[0][0][0];
-    r2[rs * 16 + jl] = bsum;
+    r2[(tid >> 4) * 16 + (tid & 15)] = bsum;
     __syncthreads();
     if (tid < 16 && tid < nc) {
       float u = 0.f;
@@ -176,5 +180,36 @@ __device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, c
   }
 }
 
+// Workgroup (bx, by) of a head_wgrad_grid, 256 threads, kHeadWgradLdsFloats floats of LDS at smem (16-byte aligned).  The
+// one past the last column computes the losses.
+template <typename T>
+__device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, const Segments& seg, int bx, int by,
+                                                     float* smem) {
+  const int jchunks = (h.cin + h.columns - 1) / h.columns;
+  if (bx == seg.K * jchunks) {
+    if (by == 0)
+      head_loss_body(HeadLossParams{h.labels, h.C, h.loss_rows, h.loss_per_worker, h.loss, h.status}, seg, smem);
+    return;
+  }
+  if (h.columns == 16) head_wgrad_columns_body<T, 16>(h, seg, bx, by, smem);
+  else if (h.columns == 8) head_wgrad_columns_body<T, 8>(h, seg, bx, by, smem);
+  else head_wgrad_columns_body<T, 4>(h, seg, bx, by, smem);
+}
+
+// The classifier's part of a launch it shares with a matrix product: its workgroups come first (they are short but wait for
+// memory most of the time, so they should not be left for the end).
+struct HeadRole {
+  HeadWgradParams p;
+  int gx, blocks;   // blocks = 0: no such part
+};
+inline HeadRole head_role(const HeadWgradParams* h, const Segments& seg) {
+  HeadRole r{};
+  if (!h) return r;
+  const dim3 g = head_wgrad_grid(h->cin, h->C, seg.K);
+  r.p = *h;
+  r.gx = (int)g.x;
+  r.blocks = (int)(g.x * g.y);
+  return r;
+}
 
 }  // namespace omni

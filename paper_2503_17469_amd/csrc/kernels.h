@@ -24,10 +24,10 @@ struct KernelTimer {
 void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
                     int rows, int cin, int cout, bool relu);
 // dx[rows][cin] (+)= dy[rows][cout] * w[cout][cin], zeroed where mask[rows][cin] <= 0 (mask may be null).
-// head (may be null): the classifier's parameter gradients and losses, which need nothing of this product; where the
-// kernel taken can carry them they run in the same launch and the call returns true.
+// head (may be null): the classifier's parameter gradients and losses, which need nothing of this product, in the same
+// launch.
 struct HeadWgradParams;
-bool linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
+void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
                       int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
 // Small-batch variants (gemm_f32_direct.hip): same results as the two above up to
 // summation order; return false without launching when the shape does not qualify.
@@ -78,7 +78,7 @@ bool linear_f32_small(int rows, int cols, int kred);   // the rule for forward (
 void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows,
                           int cin, int cout, bool relu);
 void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows,
-                            int cin, int cout, bool accumulate);
+                            int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
 // (loss, may be null: computed in the same launch.)
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                             const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer);
@@ -96,6 +96,7 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
 // Per worker: gw_k = dz_k^T x_k, gb_k = column sums of dz_k; plus L_k, the total
 // loss and the status word (bit 0: some label outside [0, classes)).
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg);
+int head_wgrad_columns_for(int cin, int classes, int K);   // HeadWgradParams::columns
 // Arguments of the head's parameter-gradient kernel.  x has the storage type T of the body's
 // instantiation (fp32, or bf16 words); everything else is fp32.
 struct HeadWgradParams {
@@ -110,6 +111,7 @@ struct HeadWgradParams {
   float* loss_per_worker;     // [K]
   float* loss;                // [1]
   uint32_t* status;           // [1]
+  int columns;                // head_wgrad_columns(cin, C, workers)
 };
 // ---- bf16 convolutions / fully connected layers as implicit GEMMs (conv_bf16.hip) ----
 typedef uint16_t bf16_t;   // raw bfloat16 bits
@@ -157,8 +159,9 @@ struct BnStatRequest {
 // Hidden fully connected layers (gemm_bf16.hip); widths are multiples of 8.
 // c[M][N] = a[M][K] b[N][K]^T (+bias) (ReLU), zeroed where mask <= 0 (mask may be null): forward with b = the weight copy,
 // input gradient with b = the transposed copy.
+// head (may be null): as linear_dgrad_f32.
 void linear_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* c, int M, int N, int K, const float* bias,
-                 bool relu, const bf16_t* mask);
+                 bool relu, const bf16_t* mask, const HeadWgradParams* head, const Segments& seg);
 struct LinearWgradBf16Job {
   const bf16_t* dy;      // [rows][cout]
   const bf16_t* x;       // [rows][cin]

@@ -556,16 +556,16 @@ void step_f32(StepCtx& c) {
   const bool tiled = omni::linear_wgrad_f32_tiled(jobs.data() + skip, (int)jobs.size() - skip, rows);
   const omni::HeadWgradParams head{grad(logits), act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                    last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
-                                   c.loss_per_worker, c.loss, c.status};
+                                   c.loss_per_worker, c.loss, c.status,
+                                   omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg.K)};
   bool head_pending = fused_head && tiled;
   for (int i = n_layers - 1; i >= 0; --i) {
     const Layer& L = net->layers[i];
     if (L.fused_away || L.in0 < 0 || (fused_head && i == n_layers - 1)) continue;
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_DGRAD, i);
-    if (omni::linear_dgrad_f32(st, grad(L.out), params + L.w_off, net->tensors[L.in0].relu ? act(L.in0) : nullptr,
-                               grad(L.in0), rows, L.d.cin, L.d.cout, written[L.in0] != 0, head_pending ? &head : nullptr,
-                               c.seg))
-      head_pending = false;
+    omni::linear_dgrad_f32(st, grad(L.out), params + L.w_off, net->tensors[L.in0].relu ? act(L.in0) : nullptr,
+                           grad(L.in0), rows, L.d.cin, L.d.cout, written[L.in0] != 0, head_pending ? &head : nullptr, c.seg);
+    head_pending = false;
     written[L.in0] = 1;
   }
   if (head_pending) omni::head_wgrad_loss(st, false, head, c.seg);
@@ -723,7 +723,7 @@ void step_bf16(StepCtx& c) {
                            net->layers[nx].in0 == L.out && !to.relu && !L.has_b;
       if (L.d.op == OMNI_OP_LINEAR) {
         omni::linear_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows, L.d.cout, L.d.cin,
-                          L.has_b ? c.params + L.b_off : nullptr, to.relu, nullptr);
+                          L.has_b ? c.params + L.b_off : nullptr, to.relu, nullptr, nullptr, c.seg);
         continue;
       }
       omni::BnStatRequest offer{bn_partial, &c.seg, nullptr, nullptr, {}, false};
@@ -771,7 +771,10 @@ void step_bf16(StepCtx& c) {
 
   // ---- classifier head: logits, loss, dz (with 1/b_k), first input gradient, head parameter gradients
   std::vector<char> written(net->tensors.size(), 0);
+  // the classifier's parameter gradients and losses run beside the first input gradient of a fully connected network, else
+  // with the last weight gradients
   omni::HeadWgradParams head_grads{};
+  bool head_pending = true;
   {
     TimedScope ts(net, st, OMNI_KERNEL_LOSS, n_layers - 1);
     const int logits = last.out;
@@ -785,8 +788,8 @@ void step_bf16(StepCtx& c) {
     if (need_dx) written[last.in0] = 1;
     head_grads = omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                        last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
-                                       c.loss_per_worker, c.loss, c.status};
-    if (net->linear_only) omni::head_wgrad_loss(st, true, head_grads, c.seg);   // (else with the last weight gradients)
+                                       c.loss_per_worker, c.loss, c.status,
+                                       omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg.K)};
   }
 
   // ---- backward
@@ -923,7 +926,8 @@ void step_bf16(StepCtx& c) {
         pending_add[L.in0] = nullptr;
         if (!conv && !addend && !written[L.in0]) {
           omni::linear_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), rows, L.d.cin, L.d.cout, nullptr, false,
-                            ti.relu ? act(L.in0) : nullptr);
+                            ti.relu ? act(L.in0) : nullptr, head_pending ? &head_grads : nullptr, c.seg);
+          head_pending = false;
         } else {
           d.mask_bits = (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr;
           const int bn = conv ? fed_bn(i) : -1;
@@ -992,7 +996,10 @@ void step_bf16(StepCtx& c) {
   }
   if (!net->linear_only) {
     TimedScope ts(net, st, OMNI_KERNEL_CONV_WGRAD, 0);
-    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3, &head_grads, 512);
+    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3,
+                           head_pending ? &head_grads : nullptr, 512);
+  } else if (head_pending) {
+    omni::head_wgrad_loss(st, true, head_grads, c.seg);
   }
   if (!linear_jobs.empty() || (net->linear_only && c.fuse_update)) {
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);   // the hidden fully connected layers', in one launch
