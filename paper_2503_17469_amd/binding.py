@@ -1,4 +1,5 @@
-"""ctypes binding of libomnistep.so: argument marshalling only.
+"""Binding of libomnistep.so: argument marshalling only (ctypes; the calls a training loop makes every step go through
+the _hostcall extension, which does the same in C).
 
 Every function maps one to one onto an `omni_*` entry point of
 include/omnistep.h.  Device buffers are torch tensors used purely as owners of
@@ -125,6 +126,21 @@ def _load():
 lib = _load()
 
 
+def _load_hostcall():
+    try:
+        from . import _hostcall
+    except ImportError as e:
+        raise ImportError(f"_hostcall is missing or does not load ({e}): build it first "
+                          "(python -c 'import __graft_entry__ as g; g.build()')") from e
+    _hostcall.init(*[C.cast(f, C.c_void_p) for f in (
+        lib.omni_ctl_set_throughputs, lib.omni_ctl_run, lib.omni_step, lib.omni_weighted_sgd,
+        lib.omni_weighted_sgd_momentum, lib.omni_asp_update)])
+    return _hostcall
+
+
+_host = _load_hostcall()
+
+
 def last_error() -> str:
     return lib.omni_last_error().decode()
 
@@ -163,15 +179,16 @@ def ctl_create(K: int, B: int, b_min: int = 1, b_max: int = 0):
 
 
 def ctl_set_throughputs(ctl, T: Sequence[int]):
-    arr = (C.c_uint64 * len(T))(*[int(t) for t in T])
-    _check(lib.omni_ctl_set_throughputs(ctl, arr))
+    rc = _host.ctl_set_throughputs(ctl, T)
+    if rc:
+        _check(rc)
 
 
 def ctl_run(ctl, K: int):
-    b = (C.c_int32 * K)()
-    off = (C.c_int32 * (K + 1))()
-    _check(lib.omni_ctl_run(ctl, b, off))
-    return list(b), list(off)
+    out = _host.ctl_run(ctl, K)
+    if type(out) is int:
+        _check(out)
+    return out
 
 
 def ctl_destroy(ctl):
@@ -222,10 +239,10 @@ STEP_NO_UPDATE, STEP_KEEP_REDUCED_GRAD = 1, 2
 
 
 def step(net, params, x, labels, off, b, lr, workspace, loss_per_worker, loss, flags: int = 0, stream=None):
-    K = len(b)
-    _check(lib.omni_step(net, stream if stream is not None else _stream(), _ptr(params), _ptr(x), _ptr(labels),
-                         _i32(off), _i32(b), K, float(lr), _ptr(workspace), _ptr(loss_per_worker), _ptr(loss),
-                         flags))
+    rc = _host.step(net, stream if stream is not None else _stream(), params, x, labels, off, b, lr, workspace,
+                    loss_per_worker, loss, flags)
+    if rc:
+        _check(rc)
 
 
 STATIC_WORKSPACE_BYTES = 32 << 20
@@ -313,21 +330,15 @@ def net_timing_read(net):
 
 # ------------------------------------------------------------------ single kernels
 def weighted_sgd(params, grads, b, lr, shadow_bf16=None, P=None, stream=None):
-    K = len(b)
-    stride = grads.stride(0)
-    P = params.numel() if P is None else P
-    _check(lib.omni_weighted_sgd(stream if stream is not None else _stream(), _ptr(params), _ptr(grads), stride, P,
-                                 _i32(b), K, float(lr), _ptr(shadow_bf16)))
+    _check(_host.weighted_sgd(stream if stream is not None else _stream(), params, grads, grads.stride(0),
+                              params.numel() if P is None else P, b, lr, shadow_bf16))
 
 
 def weighted_sgd_momentum(params, velocity, grads, b, lr, momentum, weight_decay, shadow_bf16=None, P=None,
                           stream=None):
-    K = len(b)
-    stride = grads.stride(0)
-    P = params.numel() if P is None else P
-    _check(lib.omni_weighted_sgd_momentum(stream if stream is not None else _stream(), _ptr(params), _ptr(velocity),
-                                          _ptr(grads), stride, P, _i32(b), K, float(lr), float(momentum),
-                                          float(weight_decay), _ptr(shadow_bf16)))
+    _check(_host.weighted_sgd_momentum(stream if stream is not None else _stream(), params, velocity, grads,
+                                       grads.stride(0), params.numel() if P is None else P, b, lr, momentum,
+                                       weight_decay, shadow_bf16))
 
 
 def net_set_momentum(net, velocity, momentum, weight_decay):
@@ -431,10 +442,8 @@ def asp_schedule(T, b, n_events):
 
 def asp_update(dst, base, grad, lr, b_k, B, lr_scaling=True, P=None, stream=None):
     """grad: a device tensor, or a raw device address (int) such as net_worker_grads returns."""
-    P = dst.numel() if P is None else P
-    g = C.c_void_p(grad) if isinstance(grad, int) else _ptr(grad)
-    _check(lib.omni_asp_update(stream if stream is not None else _stream(), _ptr(dst), _ptr(base), g, P, float(lr),
-                               int(b_k), int(B), 1 if lr_scaling else 0))
+    _check(_host.asp_update(stream if stream is not None else _stream(), dst, base, grad, dst.numel() if P is None else P,
+                            lr, b_k, B, 1 if lr_scaling else 0))
 
 
 def asp_ps_create(K, b_min, b_max, deadband):

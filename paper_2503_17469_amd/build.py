@@ -1,15 +1,17 @@
-"""Compiles the HIP sources in csrc/ into libomnistep.so (gfx950), in-tree."""
+"""Compiles the HIP sources in csrc/ into libomnistep.so (gfx950) and the host-call extension in pyext/, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libomnistep.so")
+EXT = os.path.join(HERE, "_hostcall.so")
 
 # Packed-fp32 VALU forms are switched off for every device compile.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -47,6 +49,12 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     if r.returncode != 0:
         sys.stderr.write(" ".join(cmd) + "\n" + r.stdout + r.stderr)
         raise RuntimeError("linking libomnistep.so failed")
+    cmd = [os.environ.get("CXX", "g++"), *COMMON, "-shared", "-I" + sysconfig.get_paths()["include"],
+           os.path.join(HERE, "pyext", "hostcall.cpp"), "-o", EXT]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(" ".join(cmd) + "\n" + r.stdout + r.stderr)
+        raise RuntimeError("compiling hostcall.cpp failed")
     return LIB
 
 
