@@ -308,6 +308,11 @@ struct SmallWgrad {
   size_t worker_stride;
   SmallWgradJob job[kSmallJobs];
 };
+// Many rows for few tiles: the rows are cut into shares, each of one worker (worker k has the shares first[k] .. first[k+1]-1
+// of equal length), a workgroup takes one share, and gw and gb point at [share][worker_stride] of scratch.
+struct SmallShares {
+  int32_t first[OMNI_MAX_WORKERS + 1];
+};
 
 // A chunk is 16 rows per wavefront: lane (r, g) supplies column r of dy and the WB neighbouring columns WB r .. of x of
 // rows 4 s + g.
@@ -319,26 +324,38 @@ struct WgradChunk {
 // A wavefront (NW = 1, four tiles per workgroup) or the four wavefronts of a workgroup (NW = 4) own a 16 x 16 WB tile of
 // one layer's weights and walk through all workers' rows, 16 rows each at a time; where a worker's rows end, its tile goes
 // out to G[k].  UPD: 0 gradients only, 1 / 2 the SGD / momentum update of the tile's parameters at the end.
-// The workgroup behind the last tile computes the losses.
+// The workgroup behind the last tile computes the losses.  SHARES: see SmallShares (UPD = 0; split_reduce_kernel follows).
 // The vector cache takes a load instruction of any width every 16 cycles, so with WB = 4 (one 4-byte and one 16-byte load
 // per four matrix instructions, 128 matrix cycles) it stays out of the way; 16 x 16 and 32 x 32 tiles with 4- and 8-byte
 // loads took twice the time (997-501-243-37 net, 333 rows, 7 workers: 18.6 and 18.2 us).
-template <int WB, int NW, int UPD>
+template <int WB, int NW, int UPD, bool SHARES>
 __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments seg, Lambdas lam, Optim opt,
-                                                          HeadLossParams hl) {
+                                                          HeadLossParams hl, SmallShares sh) {
+  static_assert(!SHARES || (NW == 4 && UPD == 0), "shares: four wavefronts, no update");
   constexpr int TN = 16 * WB, D = 4;
   constexpr bool MOM = UPD == 2;
   constexpr int kTileFloats = 16 * TN;
   constexpr int kOwn = (kTileFloats + 255) / 256;          // elements a thread adds up (NW = 4)
   __shared__ __attribute__((aligned(16))) float red[NW == 1 ? 1 : NW][NW == 1 ? kHeadLossLdsFloats : kTileFloats + 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int groups = NW == 1 ? (p.tiles + 3) / 4 : p.tiles;
+  const int groups = NW == 1 ? (p.tiles + 3) / 4 : SHARES ? p.tiles * sh.first[seg.K] : p.tiles;
   if ((int)blockIdx.x == groups) {
     head_loss_body(hl, seg, &red[0][0]);
     return;
   }
-  const int tile = NW == 1 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x;
+  const int share = SHARES ? (int)blockIdx.x / p.tiles : 0;
+  const int tile = NW == 1 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x - share * p.tiles;
   if (NW == 1 && tile >= p.tiles) return;   // (no barrier below with NW = 1)
+  // the rows walked: all workers' one after the other, or a share of one worker's
+  int beg0 = 0, end0 = seg.off[1];
+  const int nwork = SHARES ? 1 : seg.K;
+  if (SHARES) {
+    int k = 0;
+    while (k + 1 < seg.K && share >= sh.first[k + 1]) ++k;
+    const int at = share - sh.first[k], of = sh.first[k + 1] - sh.first[k], bk = seg.off[k + 1] - seg.off[k];
+    beg0 = seg.off[k] + (int)((long)bk * at / of);
+    end0 = seg.off[k] + (int)((long)bk * (at + 1) / of);
+  }
   int ji = 0;
   for (int i = 1; i < p.n; ++i)
     if (tile >= p.job[i].first) ji = i;
@@ -404,7 +421,8 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
 
   // the worker's rows are done: its tile goes out
   auto flush = [&](int w) {
-    float* G = J.gw + (size_t)w * p.worker_stride;
+    const int dst = SHARES ? share : w;
+    float* G = J.gw + (size_t)dst * p.worker_stride;
     const float l = UPD ? lam.v[w] : 0.f;
     if (want_bias) {
       bsum += __shfl_xor(bsum, 16, 64);
@@ -423,7 +441,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
         if (row < M) store_n<WB>(G + (size_t)row * N + js, t);
       }
       if (want_bias) {
-        if (g == 0 && i0 + r < M) J.gb[(size_t)w * p.worker_stride + i0 + r] = bsum;
+        if (g == 0 && i0 + r < M) J.gb[(size_t)dst * p.worker_stride + i0 + r] = bsum;
         if (UPD) bgsum += l * bsum;
       }
     } else {
@@ -451,7 +469,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
         float t = red[0][kTileFloats + tid];
 #pragma unroll
         for (int ww = 1; ww < NW; ++ww) t += red[ww][kTileFloats + tid];
-        if (i0 + tid < M) J.gb[(size_t)w * p.worker_stride + i0 + tid] = t;
+        if (i0 + tid < M) J.gb[(size_t)dst * p.worker_stride + i0 + tid] = t;
         if (UPD) bgsum += l * t;
       }
     }
@@ -459,21 +477,21 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
   };
 
   // stream of chunks: (worker, first row, end of its rows), D of them in flight
-  int lw = 0, lk = 0, lend = seg.off[1];       // next chunk to load
+  int lw = 0, lk = beg0, lend = end0;       // next chunk to load
   auto advance = [&](int& w, int& k, int& end) {
     k += kSuper;
     if (__builtin_expect(k >= end, 0)) {
       ++w;
-      if (w < seg.K) { k = seg.off[w]; end = seg.off[w + 1]; }
+      if (w < nwork) { k = seg.off[w]; end = seg.off[w + 1]; }
     }
   };
   WgradChunk<WB> c[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     load(c[d], lk, lend);
-    if (lw < seg.K) advance(lw, lk, lend);       // (past the last chunk: the last one again, unused)
+    if (lw < nwork) advance(lw, lk, lend);       // (past the last chunk: the last one again, unused)
   }
-  int w = 0, k = 0, end = seg.off[1];
+  int w = 0, k = beg0, end = end0;
   // (everything that does not happen in every chunk is out of line: a taken branch costs the wavefront an instruction
   // fetch, and a handful of them per chunk cost as much as its matrix instructions)
   for (bool more = true; more;) {
@@ -498,11 +516,11 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
       if (__builtin_expect(k >= end, 0)) {
         flush(w);
         ++w;
-        if (w == seg.K) { more = false; break; }
+        if (w == nwork) { more = false; break; }
         k = seg.off[w];
         end = seg.off[w + 1];
       }
-      if (__builtin_expect(lw < seg.K, 1)) advance(lw, lk, lend);
+      if (__builtin_expect(lw < nwork, 1)) advance(lw, lk, lend);
     }
   }
 
@@ -552,6 +570,36 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
   }
 }
 
+// Second stage of the shares: a worker's are added in order into G[k], and with UPD the update of all parameters follows
+// from the registers, in weighted_sgd_kernel's order (the results are the same bit for bit).
+template <int UPD>
+__global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restrict__ part, float* __restrict__ G,
+                                                           size_t stride, long P, int K, SmallShares sh, Lambdas lam,
+                                                           Optim opt, float* __restrict__ theta, float* __restrict__ vel) {
+  constexpr bool MOM = UPD == 2;
+  const long j = (long)blockIdx.x * 256 + threadIdx.x;
+  if (j >= P) return;
+  float th = UPD ? theta[j] : 0.f, ve = MOM ? vel[j] : 0.f, sum = 0.f;
+  for (int k = 0; k < K; ++k) {
+    const int s0 = sh.first[k], s1 = sh.first[k + 1];
+    float g = 0.f;
+    for (int s = s0; s < s1; s += 8) {               // eight loads in flight, added in order
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(size_t)min(s + u, s1 - 1) * stride + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) g = s + u < s1 ? g + v[u] : g;
+    }
+    G[(size_t)k * stride + j] = g;
+    if (UPD) sum += lam.v[k] * g;
+  }
+  if (UPD) {
+    apply_update<MOM>(th, ve, sum, opt);
+    theta[j] = th;
+    if (MOM) vel[j] = ve;
+  }
+}
+
 }  // namespace
 
 namespace {
@@ -584,16 +632,32 @@ template <int WB, int NW>
 void launch_wgrad(hipStream_t st, const SmallWgrad& p, const Segments& seg, const Lambdas& lam, const Optim& opt,
                   const HeadLossParams& hl, int upd, bool loss, const KernelTimer* timer) {
   const dim3 grid((NW == 1 ? (p.tiles + 3) / 4 : p.tiles) + (loss ? 1 : 0)), block(256);
-#define OMNI_SMALL_WGRAD(U)                                                                                          \
-  if (timer)                                                                                                         \
-    hipExtLaunchKernelGGL((small_wgrad_kernel<WB, NW, U>), grid, block, 0, st, timer->start, timer->stop, 0, p, seg, \
-                          lam, opt, hl);                                                                             \
-  else                                                                                                               \
-    hipLaunchKernelGGL((small_wgrad_kernel<WB, NW, U>), grid, block, 0, st, p, seg, lam, opt, hl)
+  const SmallShares none{};
+#define OMNI_SMALL_WGRAD(U)                                                                                             \
+  if (timer)                                                                                                            \
+    hipExtLaunchKernelGGL((small_wgrad_kernel<WB, NW, U, false>), grid, block, 0, st, timer->start, timer->stop, 0, p,  \
+                          seg, lam, opt, hl, none);                                                                     \
+  else                                                                                                                  \
+    hipLaunchKernelGGL((small_wgrad_kernel<WB, NW, U, false>), grid, block, 0, st, p, seg, lam, opt, hl, none)
   if (upd == 0) { OMNI_SMALL_WGRAD(0); }
   else if (upd == 1) { OMNI_SMALL_WGRAD(1); }
   else { OMNI_SMALL_WGRAD(2); }
 #undef OMNI_SMALL_WGRAD
+}
+
+// Shares of a weight gradient with `tiles` tiles: as many as give the chip four workgroups per compute unit, at least 64 rows
+// each and one per worker.  A compute unit needs about 6.5 ns per row of a tile, which only the compute units without
+// a tile can take off it, and the second launch costs about 5 us: measured with 1024 and 4096 rows, the line lies near
+// 850 rows times the idle part of the chip (64-128-10 net, 4096 rows: step 42 -> 26 us; 256-256-10, 1024 rows: 23 -> 26).
+bool wgrad_shares(long tiles, const Segments& seg, size_t scratch_rows, SmallShares& sh) {
+  const long rows = seg.off[seg.K];
+  if (rows * (256 - tiles) < 850 * 256) return false;
+  const long want = std::min<long>(std::min<long>(1024 / tiles, rows / 64), (long)scratch_rows - seg.K);
+  if (want < 2) return false;
+  sh.first[0] = 0;
+  for (int k = 0; k < seg.K; ++k)
+    sh.first[k + 1] = sh.first[k] + (int)std::max<long>(1, want * (seg.off[k + 1] - seg.off[k]) / rows);
+  return sh.first[seg.K] >= 2;
 }
 
 }  // namespace
@@ -614,7 +678,8 @@ void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, con
 }
 
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                            const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer) {
+                            const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
+                            const WgradScratch& scratch) {
   long tiles = 0;
   bool narrow = false;
   for (int i = 0; i < n; ++i) {
@@ -629,6 +694,35 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
   const Lambdas lam = lambdas_of(seg);
   const Optim opt = sgd ? Optim{sgd->lr, sgd->momentum, sgd->weight_decay} : Optim{0.f, 0.f, 0.f};
   const bool one = n <= kSmallJobs;
+  SmallShares sh{};
+  if (scratch.part && !narrow && one && wgrad_shares(tiles, seg, scratch.rows, sh)) {
+    SmallWgrad p{};
+    p.n = n;
+    p.worker_stride = worker_stride;
+    for (int i = 0; i < n; ++i) {
+      const LinearWgradJob& j = jobs[i];
+      SmallWgradJob& q = p.job[i];
+      q.dy = j.dy; q.x = j.x; q.M = j.cout; q.N = j.cin;
+      q.gw = scratch.part + j.w_off;
+      q.gb = j.gb ? scratch.part + j.b_off : nullptr;
+      q.tiles_n = (j.cin + TN - 1) / TN;
+      q.first = p.tiles;
+      p.tiles += (j.cout + 15) / 16 * q.tiles_n;
+    }
+    if (timer) (void)hipEventRecord(timer->start, st);
+    hipLaunchKernelGGL((small_wgrad_kernel<4, 4, 0, true>), dim3(p.tiles * sh.first[seg.K] + (loss ? 1 : 0)), dim3(256), 0, st,
+                       p, seg, lam, opt, loss ? *loss : HeadLossParams{}, sh);
+    const dim3 grid((unsigned)((scratch.params + 255) / 256));
+#define OMNI_REDUCE(U)                                                                                                   \
+  hipLaunchKernelGGL(split_reduce_kernel<U>, grid, dim3(256), 0, st, scratch.part, scratch.G, worker_stride,             \
+                     (long)scratch.params, seg.K, sh, lam, opt, sgd ? sgd->params : nullptr, sgd ? sgd->velocity : nullptr)
+    if (upd == 0) OMNI_REDUCE(0);
+    else if (upd == 1) OMNI_REDUCE(1);
+    else OMNI_REDUCE(2);
+#undef OMNI_REDUCE
+    if (timer) (void)hipEventRecord(timer->stop, st);
+    return;
+  }
   if (timer && !one) (void)hipEventRecord(timer->start, st);
   for (int base = 0; base < n; base += kSmallJobs) {
     SmallWgrad p{};

@@ -46,7 +46,14 @@ __device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Se
   const float invB = 1.0f / (float)rows;
   for (int k = tid >> 6; k < seg.K; k += nthreads >> 6) {
     float a = 0.f;
-    for (int s = seg.off[k] + lane; s < seg.off[k + 1]; s += 64) a += h.loss_rows[s];
+    const int end = seg.off[k + 1];
+    for (int s = seg.off[k] + lane; s < end; s += 512) {   // eight loads in flight, added in order
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = h.loss_rows[min(s + 64 * u, end - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a += s + 64 * u < end ? v[u] : 0.f;
+    }
     a = wave_sum(a);
     if (lane == 0) {
       const float bk = (float)(seg.off[k + 1] - seg.off[k]);
@@ -56,7 +63,13 @@ __device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Se
     }
   }
   int badl = 0;
-  for (int s = tid; s < rows; s += nthreads) badl |= (h.labels[s] < 0 || h.labels[s] >= h.C) ? 1 : 0;
+  for (int s = tid; s < rows; s += 4 * nthreads) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int y = h.labels[min(s + u * nthreads, rows - 1)];
+      badl |= (y < 0 || y >= h.C) ? 1 : 0;
+    }
+  }
   const int anybad = __syncthreads_or(badl);
   if (tid == 0) {
     float total = 0.f;

@@ -80,8 +80,17 @@ void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const 
 void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows,
                             int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
 // (loss, may be null: computed in the same launch.)
+// Scratch that lets the rows of a tile be shared out: `rows` rows of worker_stride floats.  (Null where the jobs do not cover
+// all `params` parameters of the net.)
+struct WgradScratch {
+  float* part;
+  size_t rows;
+  float* G;            // worker 0's gradients of all parameters
+  size_t params;
+};
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                            const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer);
+                            const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
+                            const WgradScratch& scratch);
 
 // ---- classifier head (head.hip): last fully connected layer with few outputs ----
 // `bf16` selects the storage type of x, w and dx (bf16 words) versus fp32; the

@@ -20,6 +20,7 @@
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr size_t kShareMaxParams = 1 << 19;   // (256 tiles of 16 x 64 weights are 2^18)
 constexpr size_t kNoGrad = ~(size_t)0;
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -65,6 +66,7 @@ struct omni_net {
   size_t conv_partial2_off = 0;     // chunk scratch of the second side stream
   size_t conv_partial3_off = 0;     // ... and of the main stream
   size_t bn_off = 0, bn_floats = 0, bn_partial_off = 0;
+  size_t share_off = 0, share_rows = 0;   // fp32: row shares of the weight gradients (small nets, large batches)
   size_t reduced_off = 0;           // g = sum_k lambda_k g_k, written only on request
   int bn_cmax = 0;
   // Where the last step left each tensor's gradient (byte offset into the workspace; kNoGrad: that step
@@ -310,6 +312,10 @@ int omni_net_create(const omni_layer_desc* descs, int32_t n, int32_t in_h, int32
   net->reduced_off = take(net->P_stride * sizeof(float));
   net->loss_rows_off = take((size_t)B_max * sizeof(float));
   net->status_off = take(kAlign);
+  if (!bf && B_max >= 1024 && ppos <= kShareMaxParams) {
+    net->share_rows = (size_t)K_max + 64;
+    net->share_off = take(net->share_rows * net->P_stride * sizeof(float));
+  }
   if (bf) {
     net->conv_counters_off = take(omni::kZeroPageWords * sizeof(uint32_t));
     net->conv_partial_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
@@ -580,7 +586,9 @@ void step_f32(StepCtx& c) {
     } else {
       const omni::HeadLossParams hl{c.labels, last.d.cout, c.loss_rows, c.loss_per_worker, c.loss, c.status};
       omni::linear_wgrad_f32_small(st, jobs.data(), (int)jobs.size(), net->P_stride, c.seg, fused_head ? &hl : nullptr,
-                                   upd, ts.timer());
+                                   upd, ts.timer(),
+                                   omni::WgradScratch{net->share_rows ? reinterpret_cast<float*>(c.ws + net->share_off) : nullptr,
+                                                      net->share_rows, c.G, net->P});
     }
   }
   for (size_t t = 0; t < net->tensors.size(); ++t)

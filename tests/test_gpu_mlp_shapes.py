@@ -78,3 +78,28 @@ def test_update_inside_the_weight_gradient_launch(dims, off, momentum):
             run.close()
     for a, c in zip(*out):
         assert np.array_equal(a, c)
+
+
+@pytest.mark.parametrize("dims,off", [([64, 40, 10], [0, 1, 1100]), ([33, 17, 65, 9], [0, 700, 703, 1500]),
+                                      ([6, 16, 3], [0, 1024])])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_rows_of_a_weight_gradient_shared_out(dims, off, momentum):
+    """Few weights and many rows: a worker's rows in several shares (one worker with a single row, one with three)."""
+    layers, params, x, labels = _case(dims, off, 9 + sum(dims))
+    ref = oracle_step.sgd_step(layers, params, x.reshape(-1, 1, 1, dims[0]), labels, off, 0.05)
+    run = GpuRun(layers, (1, 1, dims[0]), "f32", len(off) - 1, off[-1])
+    try:
+        import torch
+        import paper_2503_17469_amd as omni
+        if momentum:
+            vel = torch.zeros(params.size, device="cuda")
+            omni.net_set_momentum(run.net, vel, 0.9, 0.0)     # the first step's update is the plain one
+        got = run.step(params, x, labels, off, 0.05, keep_g=False)
+        again = run.step(params, x, labels, off, 0.05, keep_g=False) if not momentum else got
+        assert got["status"] == 0 and np.array_equal(got["params"], again["params"])
+        for name, s, e in param_tensor_slices(layers):
+            for k in range(len(off) - 1):
+                assert_close(got["worker_grads"][k, s:e], ref.worker_grads[k, s:e], 1e-4, f"g_{k} {name}", tol_max=5e-4)
+            assert_close(got["params"][s:e], ref.params[s:e], 1e-4, f"theta' {name}")
+    finally:
+        run.close()
