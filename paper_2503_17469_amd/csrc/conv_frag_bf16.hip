@@ -1,5 +1,5 @@
-// Convolutions of few positions in bf16 (fp32 accumulation): forward of 3x3 / pad-1 and 1x1 layers of stride 1 or 2 and
-// the input gradient of stride-1 layers, where the tiles of the large-batch kernels would leave most of the chip idle.
+// Convolutions of few positions in bf16 (fp32 accumulation): forward of 3x3 / pad-1 and 1x1 layers of stride 1 or 2,
+// the input gradient of stride-1 layers and that of a residual block's entry (3x3 and 1x1 at stride 2), where the tiles of the large-batch kernels would leave most of the chip idle.
 //
 // What bounds such a launch is not arithmetic but how few workgroups it has and how long each one's serial walk
 // over the reduction is: 128 images of the 512-channel 4x4 layers are 64 workgroups of the wide kernel, 4608
@@ -58,6 +58,7 @@ struct FragParams {
   int relu, accumulate;
   bf16_t* pool;
   uint8_t* pool_code;
+  const bf16_t *src2, *wgt2;   // stride-2 input gradient: the projection's output gradient (may be null) and weights
   double* stat_partial;   // [tile][N][2] or null
   const bf16_t* stat_x;   // BWD: see BnStatRequest
   const float* stat_norm;
@@ -76,6 +77,182 @@ __device__ inline void stat_exchange(float (&sv)[LEN], int j) {
     const float send = upper ? sv[i] : sv[N + i];
     const float recv = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), (DIST << 10) | 0x1F));
     sv[i] = keep + recv;
+  }
+}
+
+// The end of a tile: the partial tiles meet in LDS and each wavefront finishes one 32 x 32 block of it.  out_pos, pos_in: where this
+// lane's position 32 (wave / 2) + lane % 32 of the tile goes, and whether it exists; npos, out_base (pooling): the tile's
+// positions and the first one's place.
+template <int KS, bool BWD>
+__device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* smemF, v16f (&acc)[KS == 4 ? 2 : 1][2], int kg,
+                                            int pa, int wave, int lane, int gk, int tile, int col0, bool pos_in,
+                                            size_t out_pos, int npos, size_t out_base) {
+  constexpr int MA = KS == 4 ? 2 : 1;
+  const int tid = wave * 64 + lane, j = lane & 31, h = lane >> 5;
+  // this wavefront finishes positions 32 a .. and channels 32 b .. of the tile
+  const int ea = wave >> 1, eb = wave & 1;
+  const int pos = ea * 32 + j;
+  const bool row_in = pos_in && col0 + eb * 32 < p.N;          // (N is a multiple of 32)
+  const int cb = min(col0 + eb * 32, p.N - 32);
+  const size_t row = out_pos * p.N + cb;
+  const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
+  u32x4 em[2], ea4[2], ex4[2];
+  v4f norm[2][4];                                  // BWD with statistics: (mean, 1/sqrt(var)) of this lane's channels
+  uint32_t ebits = 0;
+  if (BWD && p.stat_partial) {
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq) {
+      ex4[qq] = *reinterpret_cast<const u32x4*>(row_in ? p.stat_x + row + qq * 16 + h * 8 : zp);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        norm[qq][i] = *reinterpret_cast<const v4f*>(p.stat_norm + ((size_t)gk * p.N + cb + qq * 16 + h * 8) * 2 + 4 * i);
+    }
+  }
+  if (BWD) {
+    const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
+    if (p.mask_bits) ebits = *reinterpret_cast<const uint32_t*>(row_in ? p.mask_bits + (row >> 3) : static_cast<const uint8_t*>(p.zero));
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq) {
+      const size_t idx = row + qq * 16 + h * 8;
+      em[qq] = *reinterpret_cast<const u32x4*>((row_in && p.mask && !p.mask_bits) ? p.mask + idx : zp);
+      ea4[qq] = *reinterpret_cast<const u32x4*>((row_in && other) ? other + idx : zp);
+    }
+  }
+  float bias8[2][8];
+  if (!BWD) {
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bias8[qq][e] = p.bias ? p.bias[cb + qq * 16 + h * 8 + e] : 0.f;
+  }
+  __syncthreads();                                 // nobody reads the patch any more
+  float* const ex = reinterpret_cast<float*>(smemF);   // [position block][channel block][share][v / 4][lane][4]
+#pragma unroll
+  for (int a = 0; a < MA; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        *reinterpret_cast<v4f*>(ex + (size_t)((((pa + a) * 2 + b) * KS + kg) * 4 + v) * 256 + lane * 4) =
+            v4f{acc[a][b][4 * v], acc[a][b][4 * v + 1], acc[a][b][4 * v + 2], acc[a][b][4 * v + 3]};
+  __syncthreads();
+  float s[16];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    v4f t = *reinterpret_cast<const v4f*>(ex + (size_t)((ea * 2 + eb) * KS * 4 + v) * 256 + lane * 4);
+#pragma unroll
+    for (int k = 1; k < KS; ++k)
+      t += *reinterpret_cast<const v4f*>(ex + (size_t)(((ea * 2 + eb) * KS + k) * 4 + v) * 256 + lane * 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[4 * v + e] = t[e];
+  }
+  // Register v in lane (j, h) is channel 8 (v/4) + 4 h + v%4; swapping v and v + 4 between the wavefront's halves leaves
+  // runs of eight channels (see conv3_wide_bf16.hip).
+  u32x4 outp[2];
+#pragma unroll
+  for (int qq = 0; qq < 2; ++qq) {
+    float val[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[8 * qq + e]), __float_as_uint(s[8 * qq + 4 + e]),
+                                                        false, false);
+      val[e] = __uint_as_float(sw[0]);
+      val[4 + e] = __uint_as_float(sw[1]);
+    }
+    if (BWD) {
+      const u32x4 mk = em[qq], ad = ea4[qq];
+      if (p.addend) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+      }
+      if (p.mask_bits) {
+        const uint32_t byte = ebits >> (8 * (2 * qq + h));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
+      } else if (p.mask) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
+          val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
+        }
+      }
+      if (p.accumulate) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        val[e] += bias8[qq][e];
+        if (p.relu) val[e] = val[e] > 0.f ? val[e] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
+    if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
+  }
+
+  if (p.stat_partial) {
+    // sums of the stored values and of their squares (BWD: of the values times xhat): fp32 over the 32 positions of a block (a fixed tree, entry
+    // which*16 + q*8 + e ends in lane j with bits which, q, e from the top), double over the two blocks
+    float sv[32];
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const float lo = row_in ? bf16_lo(outp[qq][d]) : 0.f, hi = row_in ? bf16_hi(outp[qq][d]) : 0.f;
+        sv[qq * 8 + 2 * d] = lo;
+        sv[qq * 8 + 2 * d + 1] = hi;
+        if (BWD) {
+          sv[16 + qq * 8 + 2 * d] = lo * ((bf16_lo(ex4[qq][d]) - norm[qq][d][0]) * norm[qq][d][1]);
+          sv[16 + qq * 8 + 2 * d + 1] = hi * ((bf16_hi(ex4[qq][d]) - norm[qq][d][2]) * norm[qq][d][3]);
+        } else {
+          sv[16 + qq * 8 + 2 * d] = lo * lo;
+          sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
+        }
+      }
+    stat_exchange<16, 16>(sv, j);
+    stat_exchange<8, 8>(sv, j);
+    stat_exchange<4, 4>(sv, j);
+    stat_exchange<2, 2>(sv, j);
+    stat_exchange<1, 1>(sv, j);
+    __syncthreads();                               // the partial tiles have been read
+    float* const red = ex;                         // [position block][which][64]
+    red[(ea * 2 + (j >> 4)) * 64 + eb * 32 + ((j >> 3) & 1) * 16 + h * 8 + (j & 7)] = sv[0];
+    __syncthreads();
+    if (tid < 128 && col0 + (tid & 63) < p.N) {
+      const int c = tid & 63, which = tid >> 6;
+      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] =
+          (double)red[which * 64 + c] + (double)red[(2 + which) * 64 + c];
+    }
+  }
+  if (!BWD && p.pool) {
+    // a tile is whole rows of whole images, an even number of them: its pooled positions are a contiguous run too
+    __syncthreads();
+    constexpr int kRow = kTN + 8;
+    bf16_t* const st = reinterpret_cast<bf16_t*>(smemF);   // [64 positions][kRow]
+#pragma unroll
+    for (int qq = 0; qq < 2; ++qq)
+      *reinterpret_cast<u32x4*>(st + pos * kRow + eb * 32 + qq * 16 + h * 8) = outp[qq];
+    __syncthreads();
+    const int pq = tid >> 3, c = (tid & 7) * 8;    // pooled position (16 of them), channel octet
+    if (pq < (npos >> 2) && col0 + c < p.N) {
+      const int whlog = p.wlog - 1;
+      const int pr = pq >> whlog, pc = pq & ((1 << whlog) - 1);
+      const bf16_t* t = st + ((2 * pr << p.wlog) + 2 * pc) * kRow + c;
+      float a[8], b[8], cc[8], d[8], m[8];
+      Piece<bf16_t>::load(t, a);
+      Piece<bf16_t>::load(t + kRow, b);
+      Piece<bf16_t>::load(t + (kRow << p.wlog), cc);
+      Piece<bf16_t>::load(t + (kRow << p.wlog) + kRow, d);
+      u32x2 code = {0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        code[e >> 2] |= pool_code_of(a[e], b[e], cc[e], d[e], p.relu != 0, m[e]) << (8 * (e & 3));
+      const size_t po = ((out_base >> 2) + pq) * p.N + col0 + c;
+      Piece<bf16_t>::store(p.pool + po, m);
+      *reinterpret_cast<u32x2*>(p.pool_code + po) = code;
+    }
   }
 }
 
@@ -237,172 +414,164 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   for (int c = 0; c + 1 < nC; ++c) sixteen_channels(std::true_type{});
   sixteen_channels(std::false_type{});
 
-  // ---- epilogue: this wavefront finishes positions 32 a .. and channels 32 b .. of the tile
-  const int ea = wave >> 1, eb = wave & 1;
-  const int pos = ea * 32 + j;
-  const size_t out_pos = (((size_t)n0 * p.Hp + r0) << p.wlog) + pos;
-  const bool row_in = pos < npos && col0 + eb * 32 < p.N;      // (N is a multiple of 32)
-  const int cb = min(col0 + eb * 32, p.N - 32);
-  const size_t row = out_pos * p.N + cb;
-  const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
-  u32x4 em[2], ea4[2], ex4[2];
-  v4f norm[2][4];                                  // BWD with statistics: (mean, 1/sqrt(var)) of this lane's channels
-  uint32_t ebits = 0;
-  if (BWD && p.stat_partial) {
+  const int epos = (wave >> 1) * 32 + j;
+  frag_finish<KS, BWD>(p, smemF, acc, kg, pa, wave, lane, gk, tile, col0, epos < npos,
+                       (((size_t)n0 * p.Hp + r0) << p.wlog) + epos, npos, ((size_t)n0 * p.Hp + r0) << p.wlog);
+}
+
+// Input gradient of a residual block's entry (see conv3s2_dgrad_bf16.hip) for few positions.  A tile is 64 positions of ONE parity
+// class (h mod 2, w mod 2) of dx, which is 64 positions (i, k) of the half-resolution grid: the class meets taps at (i, k),
+// (i, k + 1), (i + 1, k), (i + 1, k + 1) of dy, 1, 2, 2 or 4 of them, and class (0, 0) also the projection's dys at (i, k).
+// Workgroups of the class with four taps come first; within an XCD the classes follow each other.  What bounds it is the walk
+// over the reduction as above: a quarter of the channels of up to four taps per wavefront, against all of them in the large
+// kernel.  The three entries of the ResNet-18 shape (input gradients and the sums of the batch norm below, which the epilogue
+// takes along), per step: 32 images 1.09 -> 1.03 ms, 128 images 1.63 -> 1.59 ms.
+//
+// TAPS steps per sixteen channels, eight steps of weights in flight.
+template <int TAPS>
+__device__ __forceinline__ void frag_steps(const unsigned char* smemF, const int (&aaddr)[2][TAPS],
+                                           const bf16_t* const (&wt)[TAPS][2], int cofs, int nC, v16f (&acc)[2][2]) {
+  constexpr int D = 8;
+  const int total = nC * TAPS;
+  bf16x8 fb[D][2];
+  auto load = [&](int u, int st) {
+    const int c = min(st, total - 1) / TAPS;
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      ex4[qq] = *reinterpret_cast<const u32x4*>(row_in ? p.stat_x + row + qq * 16 + h * 8 : zp);
+    for (int b = 0; b < 2; ++b) fb[u][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wt[u % TAPS][b] + (size_t)c * kBlock));
+  };
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        norm[qq][i] = *reinterpret_cast<const v4f*>(p.stat_norm + ((size_t)gk * p.N + cb + qq * 16 + h * 8) * 2 + 4 * i);
+  for (int u = 0; u < D; ++u) load(u, u);
+  for (int s0 = 0; s0 < total; s0 += D) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      if (s0 + u >= total) break;
+      const int c = (s0 + u) / TAPS;
+      bf16x8 fa[2];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+        fa[a] = as_bf16x8(*reinterpret_cast<const u32x4*>(smemF + aaddr[a][u % TAPS] + cofs + c * 32));
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[u][b], fa[a], acc[a][b], 0, 0, 0);
+      load(u, s0 + u + D);
     }
   }
-  if (BWD) {
-    const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
-    if (p.mask_bits) ebits = *reinterpret_cast<const uint32_t*>(row_in ? p.mask_bits + (row >> 3) : static_cast<const uint8_t*>(p.zero));
+}
+
+__global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 31, h = lane >> 5;
+  const int tiles = p.tfirst[p.gK], tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n, per = (total + 7) / 8;
+  const int local = (int)blockIdx.x >> 3;
+  const int cls = 3 - local / per;                 // (h mod 2) * 2 + (w mod 2)
+  const int at = ((int)blockIdx.x & 7) * per + local % per;
+  if (cls < 0 || at >= total) return;
+  const int ph = cls >> 1, pw = cls & 1;
+  const int tile = p.by_channel ? at % tiles : at / tiles_n;
+  const int col0 = (p.by_channel ? at / tiles : at % tiles_n) * kTN;
+  int gk = 0;
+  while (gk + 1 < p.gK && tile >= p.tfirst[gk + 1]) ++gk;
+  const int tl = tile - p.tfirst[gk];
+  const int R = 1 << p.rlog, Wp = 1 << p.wlog;     // the half-resolution grid: Hs x Ws = Hp x Wp
+  const int n0 = p.ifirst[gk] + (p.upi == 1 ? tl * p.nimg : tl / p.upi);
+  const int r0 = p.upi == 1 ? 0 : (tl % p.upi) << p.rlog;
+  const int nvalid = min(p.nimg, p.ifirst[gk + 1] - n0);
+  const int npos = nvalid << (p.rlog + p.wlog);
+  const int oc = p.Cs >> 3, pitch = p.Cs * 2 + 16;
+  const int zrow = p.npatch * pitch;
+  const int PR = p.PR;                             // patch rows per image: R + 1, or all of them
+
+  // copies `rows_of` source rows per image from (n0, r0) on (contiguous) to the patch
+  auto stage = [&](const bf16_t* src, int rows_of) {
+    const bf16_t* base = src + ((size_t)n0 * p.Hs + r0) * p.Ws * p.Cs;
+    const int npieces = (p.upi == 1 ? p.nimg * rows_of : rows_of) * p.Ws * oc;
+    const int live = (p.upi == 1 ? nvalid * rows_of : min(rows_of, p.Hs - r0)) * p.Ws * oc;
+    int q = tid / oc, rem = tid - q * oc;
+    const int dq = kThreads / oc, dr = kThreads - dq * oc;
+    for (int x0 = 0; x0 < npieces; x0 += 8 * kThreads) {
+      u32x4 rp[8];
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const size_t idx = row + qq * 16 + h * 8;
-      em[qq] = *reinterpret_cast<const u32x4*>((row_in && p.mask && !p.mask_bits) ? p.mask + idx : zp);
-      ea4[qq] = *reinterpret_cast<const u32x4*>((row_in && other) ? other + idx : zp);
+      for (int i = 0; i < 8; ++i) rp[i] = *reinterpret_cast<const u32x4*>(base + (size_t)min(x0 + tid + i * kThreads, live - 1) * 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (x0 + tid + i * kThreads < npieces) *reinterpret_cast<u32x4*>(smemF + q * pitch + rem * 16) = rp[i];
+        q += dq;
+        rem += dr;
+        if (rem >= oc) { rem -= oc; ++q; }
+      }
     }
-  }
-  float bias8[2][8];
-  if (!BWD) {
+  };
+  // where position (i + du, k + dv) of this lane's positions lies
+  auto address = [&](int a, int du, int dv) {
+    const int pos = a * 32 + j;
+    const int w = pos & (Wp - 1), r = (pos >> p.wlog) & (R - 1), il = pos >> (p.wlog + p.rlog);
+    const bool in = r0 + r + du < p.Hs && w + dv < p.Ws;
+    return (in ? ((il * PR + r + du) * p.Ws + w + dv) * pitch : zrow) + h * 16;
+  };
+  const int c16n = p.Cs >> 4, nC = c16n / 4, cofs = wave * nC * 32;
+  const int nb32 = p.N >> 5;
+  auto weights = [&](const bf16_t* w, int taps, int tap, int b) {
+    return w + (((size_t)min((col0 >> 5) + b, nb32 - 1) * taps + tap) * c16n + wave * nC) * kBlock + lane * 8;
+  };
+
+  v16f acc[2][2];
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) bias8[qq][e] = p.bias ? p.bias[cb + qq * 16 + h * 8 + e] : 0.f;
-  }
-  __syncthreads();                                 // nobody reads the patch any more
-  float* const ex = reinterpret_cast<float*>(smemF);   // [position block][channel block][share][v / 4][lane][4]
-#pragma unroll
-  for (int a = 0; a < MA; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        *reinterpret_cast<v4f*>(ex + (size_t)((((pa + a) * 2 + b) * KS + kg) * 4 + v) * 256 + lane * 4) =
-            v4f{acc[a][b][4 * v], acc[a][b][4 * v + 1], acc[a][b][4 * v + 2], acc[a][b][4 * v + 3]};
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+  for (int i = tid; i <= oc; i += kThreads) *reinterpret_cast<u32x4*>(smemF + zrow + i * 16) = u32x4{0u, 0u, 0u, 0u};
+  stage(p.src, PR);
   __syncthreads();
-  float s[16];
+  // an even row meets filter row 1 at distance 0, an odd one row 0 at distance 1 and row 2 at distance 0 (columns alike)
+  if (cls == 3) {
+    int aaddr[2][4];
+    const bf16_t* wt[4][2];
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    v4f t = *reinterpret_cast<const v4f*>(ex + (size_t)((ea * 2 + eb) * KS * 4 + v) * 256 + lane * 4);
+    for (int t = 0; t < 4; ++t) {
+      const int du = t >> 1, dv = t & 1;
 #pragma unroll
-    for (int k = 1; k < KS; ++k)
-      t += *reinterpret_cast<const v4f*>(ex + (size_t)(((ea * 2 + eb) * KS + k) * 4 + v) * 256 + lane * 4);
+      for (int a = 0; a < 2; ++a) aaddr[a][t] = address(a, du, dv);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) s[4 * v + e] = t[e];
-  }
-  // Register v in lane (j, h) is channel 8 (v/4) + 4 h + v%4; swapping v and v + 4 between the wavefront's halves leaves
-  // runs of eight channels (see conv3_wide_bf16.hip).
-  u32x4 outp[2];
-#pragma unroll
-  for (int qq = 0; qq < 2; ++qq) {
-    float val[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(s[8 * qq + e]), __float_as_uint(s[8 * qq + 4 + e]),
-                                                        false, false);
-      val[e] = __uint_as_float(sw[0]);
-      val[4 + e] = __uint_as_float(sw[1]);
+      for (int b = 0; b < 2; ++b) wt[t][b] = weights(p.wgt, 9, (2 - 2 * du) * 3 + 2 - 2 * dv, b);
     }
-    if (BWD) {
-      const u32x4 mk = em[qq], ad = ea4[qq];
-      if (p.addend) {
+    frag_steps<4>(smemF, aaddr, wt, cofs, nC, acc);
+  } else if (cls != 0) {
+    int aaddr[2][2];
+    const bf16_t* wt[2][2];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
-      }
-      if (p.mask_bits) {
-        const uint32_t byte = ebits >> (8 * (2 * qq + h));
+    for (int t = 0; t < 2; ++t) {
+      const int du = ph ? t : 0, dv = pw ? t : 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
-      } else if (p.mask) {
+      for (int a = 0; a < 2; ++a) aaddr[a][t] = address(a, du, dv);
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
-          val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
-        }
-      }
-      if (p.accumulate) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        val[e] += bias8[qq][e];
-        if (p.relu) val[e] = val[e] > 0.f ? val[e] : 0.f;
-      }
+      for (int b = 0; b < 2; ++b) wt[t][b] = weights(p.wgt, 9, (ph ? 2 - 2 * du : 1) * 3 + (pw ? 2 - 2 * dv : 1), b);
     }
+    frag_steps<2>(smemF, aaddr, wt, cofs, nC, acc);
+  } else {
+    int aaddr[2][1];
+    const bf16_t* wt[1][2];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
-    if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
-  }
-
-  if (p.stat_partial) {
-    // sums of the stored values and of their squares (BWD: of the values times xhat): fp32 over the 32 positions of a block (a fixed tree, entry
-    // which*16 + q*8 + e ends in lane j with bits which, q, e from the top), double over the two blocks
-    float sv[32];
+    for (int a = 0; a < 2; ++a) aaddr[a][0] = address(a, 0, 0);
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq)
+    for (int b = 0; b < 2; ++b) wt[0][b] = weights(p.wgt, 9, 4, b);
+    frag_steps<1>(smemF, aaddr, wt, cofs, nC, acc);
+    if (p.src2) {
+      __syncthreads();                             // the patch has been read
+      stage(p.src2, PR);
+      __syncthreads();
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const float lo = row_in ? bf16_lo(outp[qq][d]) : 0.f, hi = row_in ? bf16_hi(outp[qq][d]) : 0.f;
-        sv[qq * 8 + 2 * d] = lo;
-        sv[qq * 8 + 2 * d + 1] = hi;
-        if (BWD) {
-          sv[16 + qq * 8 + 2 * d] = lo * ((bf16_lo(ex4[qq][d]) - norm[qq][d][0]) * norm[qq][d][1]);
-          sv[16 + qq * 8 + 2 * d + 1] = hi * ((bf16_hi(ex4[qq][d]) - norm[qq][d][2]) * norm[qq][d][3]);
-        } else {
-          sv[16 + qq * 8 + 2 * d] = lo * lo;
-          sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
-        }
-      }
-    stat_exchange<16, 16>(sv, j);
-    stat_exchange<8, 8>(sv, j);
-    stat_exchange<4, 4>(sv, j);
-    stat_exchange<2, 2>(sv, j);
-    stat_exchange<1, 1>(sv, j);
-    __syncthreads();                               // the partial tiles have been read
-    float* const red = ex;                         // [position block][which][64]
-    red[(ea * 2 + (j >> 4)) * 64 + eb * 32 + ((j >> 3) & 1) * 16 + h * 8 + (j & 7)] = sv[0];
-    __syncthreads();
-    if (tid < 128 && col0 + (tid & 63) < p.N) {
-      const int c = tid & 63, which = tid >> 6;
-      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] =
-          (double)red[which * 64 + c] + (double)red[(2 + which) * 64 + c];
+      for (int b = 0; b < 2; ++b) wt[0][b] = weights(p.wgt2, 1, 0, b);
+      frag_steps<1>(smemF, aaddr, wt, cofs, nC, acc);
     }
   }
-  if (!BWD && p.pool) {
-    // a tile is whole rows of whole images, an even number of them: its pooled positions are a contiguous run too
-    __syncthreads();
-    constexpr int kRow = kTN + 8;
-    bf16_t* const st = reinterpret_cast<bf16_t*>(smemF);   // [64 positions][kRow]
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq)
-      *reinterpret_cast<u32x4*>(st + pos * kRow + eb * 32 + qq * 16 + h * 8) = outp[qq];
-    __syncthreads();
-    const int pq = tid >> 3, c = (tid & 7) * 8;    // pooled position (16 of them), channel octet
-    if (pq < (npos >> 2) && col0 + c < p.N) {
-      const int whlog = p.wlog - 1;
-      const int pr = pq >> whlog, pc = pq & ((1 << whlog) - 1);
-      const bf16_t* t = st + ((2 * pr << p.wlog) + 2 * pc) * kRow + c;
-      float a[8], b[8], cc[8], d[8], m[8];
-      Piece<bf16_t>::load(t, a);
-      Piece<bf16_t>::load(t + kRow, b);
-      Piece<bf16_t>::load(t + (kRow << p.wlog), cc);
-      Piece<bf16_t>::load(t + (kRow << p.wlog) + kRow, d);
-      u32x2 code = {0u, 0u};
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        code[e >> 2] |= pool_code_of(a[e], b[e], cc[e], d[e], p.relu != 0, m[e]) << (8 * (e & 3));
-      const size_t po = (((((size_t)n0 * p.Hp + r0) << p.wlog) >> 2) + pq) * p.N + col0 + c;
-      Piece<bf16_t>::store(p.pool + po, m);
-      *reinterpret_cast<u32x2*>(p.pool_code + po) = code;
-    }
-  }
+  const int pos = (wave >> 1) * 32 + j;
+  const int w = pos & (Wp - 1), r = (pos >> p.wlog) & (R - 1), il = pos >> (p.wlog + p.rlog);
+  const size_t out_pos = ((size_t)(n0 + il) * 2 * p.Hs + 2 * (r0 + r) + ph) * 2 * p.Ws + 2 * w + pw;
+  frag_finish<4, true>(p, smemF, acc, wave, 0, wave, lane, gk, tile * 4 + cls, col0, pos < npos, out_pos, npos, 0);
 }
 
 int log2_exact(int v) {
@@ -432,6 +601,31 @@ bool frag_shape(const ConvGeom& g, int N, FragShape& s) {
   s.ks = g.Cs % 64 == 0 ? 4 : 2;
   s.lds = std::max((size_t)(s.npatch + 1) * (g.Cs * 2 + 16), (size_t)4 * s.ks * 4096);
   return s.lds <= kLdsLimit;
+}
+
+// The tiles: one worker's each where batch-norm sums are wanted and there is room for their records (`sets` per tile), else
+// all images in one run.
+void frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stats, bool bwd, int sets) {
+  auto tiles_of = [&](int images) { return s.upi == 1 ? (images + s.nimg - 1) / s.nimg : images * s.upi; };
+  const bool want = stats && stats->partial && stats->seg && stats->seg->off[stats->seg->K] == rows &&
+                    bwd == (stats->x != nullptr);
+  long records = 0;
+  if (want)
+    for (int k = 0; k < stats->seg->K; ++k) records += tiles_of(stats->seg->off[k + 1] - stats->seg->off[k]);
+  p.gK = 1;
+  p.ifirst[1] = rows;
+  if (want && records * sets <= (long)stats->seg->K * kBnMaxSplits) {
+    p.gK = stats->seg->K;
+    for (int k = 0; k <= p.gK; ++k) p.ifirst[k] = stats->seg->off[k];
+    p.stat_partial = stats->partial;
+    p.stat_x = stats->x;
+    p.stat_norm = stats->stats;
+  }
+  for (int k = 0; k < p.gK; ++k) p.tfirst[k + 1] = p.tfirst[k] + tiles_of(p.ifirst[k + 1] - p.ifirst[k]);
+  if (p.stat_partial) {
+    for (int k = 0; k <= p.gK; ++k) stats->table.first[k] = p.tfirst[k] * sets;
+    stats->done = true;
+  }
 }
 
 template <int KS, int TAPS, bool BWD>
@@ -482,23 +676,7 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   p.bias = bias; p.mask = mask; p.addend = addend; p.relu = relu ? 1 : 0; p.accumulate = accumulate ? 1 : 0;
   p.mask_bits = (mask && N % 64 == 0) ? g.mask_bits : nullptr;
   if (!bwd && pool && pool_code && s.R % 2 == 0 && g.Hp % 2 == 0) { p.pool = pool; p.pool_code = pool_code; }
-  // tiles; one worker's each where their batch-norm sums are wanted and there is room for one record per tile
-  const bool want = stats && stats->partial && stats->seg && !bias && !relu && stats->seg->off[stats->seg->K] == g.rows &&
-                    bwd == (stats->x != nullptr);
-  auto tiles_of = [&](int images) { return s.upi == 1 ? (images + s.nimg - 1) / s.nimg : images * s.upi; };
-  long records = 0;
-  if (want)
-    for (int k = 0; k < stats->seg->K; ++k) records += tiles_of(stats->seg->off[k + 1] - stats->seg->off[k]);
-  p.gK = 1;
-  p.ifirst[1] = g.rows;
-  if (want && records <= (long)stats->seg->K * kBnMaxSplits) {
-    p.gK = stats->seg->K;
-    for (int k = 0; k <= p.gK; ++k) p.ifirst[k] = stats->seg->off[k];
-    p.stat_partial = stats->partial;
-    p.stat_x = stats->x;
-    p.stat_norm = stats->stats;
-  }
-  for (int k = 0; k < p.gK; ++k) p.tfirst[k + 1] = p.tfirst[k] + tiles_of(p.ifirst[k + 1] - p.ifirst[k]);
+  frag_tiles(p, s, g.rows, (bias || relu) ? nullptr : stats, bwd, 1);
   const int taps = g.ks * g.ks, tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
   // an XCD's L2 sees the whole of one operand and about an eighth of the other
   p.by_channel = (long)N * taps * g.Cs > (long)g.rows * g.Hs * g.Ws * g.Cs ? 1 : 0;
@@ -507,11 +685,57 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   if (taps == 9) { if (s.ks == 4) OMNI_FRAG(4, 9) else OMNI_FRAG(2, 9) }
   else { if (s.ks == 4) OMNI_FRAG(4, 1) else OMNI_FRAG(2, 1) }
 #undef OMNI_FRAG
-  if (p.stat_partial) {
-    for (int k = 0; k <= p.gK; ++k) stats->table.first[k] = p.tfirst[k];
-    stats->done = true;
-  }
   return p.pool != nullptr;
+}
+
+// Geometry of the half-resolution grid's tiles (H, W: the map of dx).
+static bool frag_s2_shape(int rows, int H, int W, int N, int Cs, ConvGeom& g, FragShape& s) {
+  if (H % 2 != 0 || W % 2 != 0 || Cs % 64 != 0) return false;
+  g = ConvGeom{};
+  g.rows = rows; g.Hs = H / 2; g.Ws = W / 2; g.Cs = Cs; g.Hp = H / 2; g.Wp = W / 2; g.ks = 3; g.stride = 1; g.pad = 1;
+  g.transposed = 1;
+  if (!frag_shape(g, N, s)) return false;
+  s.PR = s.upi == 1 ? g.Hs : s.R + 1;
+  s.npatch = s.nimg * s.PR * g.Ws;
+  s.lds = std::max((size_t)(s.npatch + 1) * (Cs * 2 + 16), (size_t)4 * 4 * 4096);
+  return s.lds <= kLdsLimit;
+}
+
+// Up to two workgroups per compute unit and class: whole steps of the ResNet-18 shape at 128, 200 and 256 images are 2.5, 2.2 and
+// 1.6 per cent shorter with it; from 384 images on (768 tiles at the second entry) there is no difference, at 1024 the
+// large kernel is ahead by 1.4 per cent.
+bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2) {
+  ConvGeom g;
+  FragShape s;
+  if ((Cs2 != 0 && Cs2 != Cs) || !frag_s2_shape(rows, H, W, N, Cs, g, s)) return false;
+  const long tiles = (s.upi == 1 ? (rows + s.nimg - 1) / s.nimg : (long)rows * s.upi) * ((N + kTN - 1) / kTN);
+  return tiles <= 512;
+}
+
+void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cs, const bf16_t* dys, const bf16_t* wts,
+                       bf16_t* dx, int rows, int H, int W, int N, const bf16_t* mask, const uint8_t* mask_bits, bool accumulate,
+                       const bf16_t* addend, const void* zero, BnStatRequest* stats) {
+  ConvGeom g;
+  FragShape s;
+  (void)frag_s2_shape(rows, H, W, N, Cs, g, s);
+  FragParams p{};
+  p.src = dy; p.wgt = wt; p.src2 = dys; p.wgt2 = wts; p.out = dx;
+  p.rows = rows; p.Hs = g.Hs; p.Ws = g.Ws; p.Cs = Cs; p.N = N; p.Hp = g.Hp;
+  p.wlog = log2_exact(g.Wp); p.rlog = log2_exact(s.R);
+  p.nimg = s.nimg; p.upi = s.upi; p.PR = s.PR; p.npatch = s.npatch;
+  p.stride = 1; p.flip = 1; p.zero = zero;
+  p.mask = mask; p.addend = addend; p.accumulate = accumulate ? 1 : 0;
+  p.mask_bits = (mask && N % 64 == 0) ? mask_bits : nullptr;
+  frag_tiles(p, s, rows, stats, true, 4);
+  const int tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
+  p.by_channel = (long)N * 9 > (long)rows * g.Hs * g.Ws ? 1 : 0;
+  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
+  if (s.lds > configured) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_frag_s2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)s.lds);
+    configured = s.lds;
+  }
+  hipLaunchKernelGGL(conv_frag_s2_kernel, dim3((tiles * tiles_n + 7) / 8 * 8 * 4), dim3(kThreads), s.lds, st, p);
 }
 
 }  // namespace omni

@@ -203,6 +203,12 @@ bool conv_frag_takes(const ConvGeom& g, int N);
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
                     const bf16_t* addend, BnStatRequest* stats);
+// The same for the input gradient of a residual block's entry (as conv3s2_dgrad_bf16, weights in operand order; Cs2: channels of
+// dys, 0 without).
+bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2);
+void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cs, const bf16_t* dys, const bf16_t* wts,
+                       bf16_t* dx, int rows, int H, int W, int N, const bf16_t* mask, const uint8_t* mask_bits, bool accumulate,
+                       const bf16_t* addend, const void* zero, BnStatRequest* stats);
 // The wide-tile kernel for 3x3 / stride 1 / pad 1 layers (conv3_wide_bf16.hip): same arguments and result as
 // conv_gemm_bf16 without pooling; false, with nothing launched, if the shape does not qualify.
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,

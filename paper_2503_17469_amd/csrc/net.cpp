@@ -680,6 +680,34 @@ void step_bf16(StepCtx& c) {
     return L.d.op == OMNI_OP_CONV && L.need_dgrad && omni::conv_frag_takes(dgrad_geom(L), L.cin_pad) ? 1 : 0;
   };
 
+  // The entry of a residual block: its input feeds a 3x3 / stride-2 convolution and the 1x1 / stride-2
+  // projection of the shortcut, and nothing else.  The projection comes first in the backward walk: its
+  // input gradient is not launched on its own but handed to the 3x3 convolution's, whose kernel writes
+  // both contributions in one pass.  partner[m] = the projection layer whose gradient conv m takes along, rides[sc] = m.
+  // s2_frag: the 3x3 convolutions (and their projections) whose input gradient runs in the kernel for few positions.
+  std::vector<int> partner(n_layers, -1), rides(n_layers, -1);
+  std::vector<char> s2_frag(n_layers, 0);
+  for (int sc = 0; sc < n_layers; ++sc) {
+    const Layer& S = net->layers[sc];
+    if (S.fused_away || S.d.op != OMNI_OP_CONV || S.d.ksize != 1 || S.d.stride != 2 || S.d.pad != 0 || S.in0 < 0) continue;
+    if (net->tensors[S.in0].consumers != 2) continue;
+    for (int m = sc - 1; m >= 0; --m) {
+      const Layer& M = net->layers[m];
+      if (M.fused_away || M.d.op != OMNI_OP_CONV || M.in0 != S.in0) continue;
+      const bool shape = M.d.ksize == 3 && M.d.stride == 2 && M.d.pad == 1 && M.cin_pad == S.cin_pad &&
+                         net->tensors[M.out].h == net->tensors[S.out].h && net->tensors[M.out].w == net->tensors[S.out].w;
+      if (shape && omni::conv3s2_dgrad_supported(rows, M.ih, M.iw, M.cin_pad, M.d.cout, S.d.cout)) { partner[m] = sc; rides[sc] = m; }
+      break;
+    }
+  }
+  for (int m = 0; m < n_layers; ++m) {
+    const Layer& M = net->layers[m];
+    if (M.fused_away || M.d.op != OMNI_OP_CONV || M.d.ksize != 3 || M.d.stride != 2 || M.d.pad != 1 || !M.need_dgrad) continue;
+    const int sc = partner[m];
+    s2_frag[m] = omni::conv_frag_s2_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, sc >= 0 ? net->layers[sc].d.cout : 0) ? 1 : 0;
+    if (sc >= 0) s2_frag[sc] = s2_frag[m];
+  }
+
   // ---- bf16 copies of the weights (forward layout, and transposed for dgrad)
   {
     std::vector<omni::CastEntry> casts;
@@ -693,7 +721,7 @@ void step_bf16(StepCtx& c) {
       e.cin_pad = L.cin_pad;
       if (L.d.op == OMNI_OP_CONV) {
         e.frag_fwd = frag_fwd(L);
-        e.frag_t = L.need_dgrad && frag_dgrad(L);
+        e.frag_t = L.need_dgrad && (frag_dgrad(L) || s2_frag[&L - net->layers.data()]);
       }
       casts.push_back(e);
     }
@@ -837,24 +865,6 @@ void step_bf16(StepCtx& c) {
   int last_dgrad = n_layers;
   for (int i = 0; i < n_layers - 1; ++i)
     if (!net->layers[i].fused_away && is_param_op(net->layers[i].d.op) && net->layers[i].in0 >= 0) { last_dgrad = i; break; }
-  // The entry of a residual block: its input feeds a 3x3 / stride-2 convolution and the 1x1 / stride-2
-  // projection of the shortcut, and nothing else.  The projection comes first in this backward walk: its
-  // input gradient is not launched on its own but handed to the 3x3 convolution's, whose kernel writes
-  // both contributions in one pass.  partner[m] = the projection layer whose gradient conv m takes along.
-  std::vector<int> partner(n_layers, -1);
-  auto entry_partner = [&](int sc) {   // the 3x3 / stride-2 convolution beside projection layer sc, or -1
-    const Layer& S = net->layers[sc];
-    if (S.d.op != OMNI_OP_CONV || S.d.ksize != 1 || S.d.stride != 2 || S.d.pad != 0 || S.in0 < 0) return -1;
-    if (net->tensors[S.in0].consumers != 2 || written[S.in0] || pending_add[S.in0]) return -1;
-    for (int m = sc - 1; m >= 0; --m) {
-      const Layer& M = net->layers[m];
-      if (M.fused_away || M.d.op != OMNI_OP_CONV || M.in0 != S.in0) continue;
-      const bool shape = M.d.ksize == 3 && M.d.stride == 2 && M.d.pad == 1 && M.cin_pad == S.cin_pad &&
-                         net->tensors[M.out].h == net->tensors[S.out].h && net->tensors[M.out].w == net->tensors[S.out].w;
-      return shape && omni::conv3s2_dgrad_supported(rows, M.ih, M.iw, M.cin_pad, M.d.cout, S.d.cout) ? m : -1;
-    }
-    return -1;
-  };
   std::vector<omni::LinearWgradBf16Job> linear_jobs;   // the hidden fully connected layers', in one launch at the end
   auto linear_job = [&](const Layer& L) {
     return omni::LinearWgradBf16Job{grad(L.out), act(L.in0), c.G + L.w_off, L.has_b ? c.G + L.b_off : nullptr, L.d.cin,
@@ -907,22 +917,33 @@ void step_bf16(StepCtx& c) {
         group_full = L.in0 >= 0 && (group_work >= kGroupWork || (int)group.size() == kGroupJobs || (c.forked && i == last_dgrad));
       }
       hipEvent_t ready = group_full ? c.fork_record() : nullptr;
-      const int takes_me = conv && L.in0 >= 0 ? entry_partner(i) : -1;
-      if (takes_me >= 0) partner[takes_me] = i;   // (this projection's input gradient rides with that convolution's)
-      bool dgrad_done = takes_me >= 0;
+      bool dgrad_done = rides[i] >= 0;   // (this projection's input gradient comes with that convolution's)
       if (L.in0 >= 0 && !dgrad_done && conv && L.d.ksize == 3 && L.d.stride == 2 && L.d.pad == 1) {
         // a stride-2 3x3 convolution: the one-pass kernel, with the shortcut's projection if it waits for it
         TimedScope ts(net, st, OMNI_KERNEL_CONV_DGRAD, i);
         const Tensor& ti = net->tensors[L.in0];
         const int sc = partner[i];
         const bf16_t* addend = pending_add[L.in0];
-        dgrad_done = omni::conv3s2_dgrad_bf16(
+        if (s2_frag[i]) {
+          const int bn = fed_bn(i);
+          omni::BnStatRequest offer{bn_partial, &c.seg, nullptr, nullptr, {}, false};
+          if (bn >= 0) {
+            offer.x = act(net->layers[bn].in0);
+            offer.stats = bn_area + net->layers[bn].stat_off;
+          }
+          omni::conv_frag_s2_bf16(st, grad(L.out), shadow + L.wt_off, L.d.cout, sc >= 0 ? grad(net->layers[sc].out) : nullptr,
+                                  sc >= 0 ? shadow + net->layers[sc].wt_off : nullptr, grad(L.in0), rows, L.ih, L.iw, L.cin_pad,
+                                  ti.relu ? act(L.in0) : nullptr, (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr,
+                                  written[L.in0] != 0, addend, conv_counters, bn >= 0 ? &offer : nullptr);
+          if (offer.done) { presummed = offer.table; presummed_for = bn; }
+          dgrad_done = true;
+        } else dgrad_done = omni::conv3s2_dgrad_bf16(
             st, grad(L.out), shadow + L.wt_off, L.d.cout, sc >= 0 ? grad(net->layers[sc].out) : nullptr,
             sc >= 0 ? shadow + net->layers[sc].wt_off : nullptr, sc >= 0 ? net->layers[sc].d.cout : 0, grad(L.in0), rows,
             L.ih, L.iw, L.cin_pad, ti.relu ? act(L.in0) : nullptr, written[L.in0] != 0, addend, conv_counters,
             (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr);
         if (dgrad_done) { pending_add[L.in0] = nullptr; written[L.in0] = 1; }
-        // (entry_partner asked conv3s2_dgrad_supported with these very shapes: a projection is never left behind)
+        // (conv3s2_dgrad_supported was asked with these very shapes: a projection is never left behind)
       }
       if (L.in0 >= 0 && !dgrad_done) {
         TimedScope ts(net, st, conv ? OMNI_KERNEL_CONV_DGRAD : OMNI_KERNEL_LINEAR_DGRAD, i);

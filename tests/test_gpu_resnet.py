@@ -134,6 +134,20 @@ def test_block_on_maps_that_are_not_square(cin, cout, stride, h, w, B):
     _check(layers, (h, w, cin), params, x, y, cuts, 0.1, f"block {cin}->{cout} s{stride} {h}x{w}")
 
 
+@pytest.mark.parametrize("cin,cout,h,w,B", [
+    (96, 128, 8, 8, 37),      # half a channel tile at the end, workers that end inside a tile of four images
+    (32, 64, 32, 32, 9),      # 16 x 16 half-resolution map: four tiles per image, halo row
+    (256, 512, 8, 16, 35),    # 4 x 8 half-resolution map: two images per tile
+    (64, 128, 16, 8, 5),      # too little work for the projection to come along: it is accumulated onto
+])
+def test_block_entry_of_few_positions(cin, cout, h, w, B):
+    layers = _block_net(cin, cout, 2, 0)
+    params = _params(layers, cin + cout + B)
+    x, y = synth.make_batch(cin * 9 + B, B, (h, w, cin), 10, True)
+    cuts = sorted({0, B // 3 + 1, B})
+    _check(layers, (h, w, cin), params, x, y, cuts, 0.1, f"entry {cin}->{cout} {h}x{w} B={B}")
+
+
 @pytest.mark.parametrize("cin,cout,stride,hw,B", [(64, 64, 1, 32, 24), (64, 128, 2, 32, 24), (256, 512, 2, 8, 96)])
 def test_block_is_reproducible_on_a_dirty_workspace(cin, cout, stride, hw, B):
     """Real layer shapes (the kernels with statistics summed by the convolution, ReLU masks as bits, chunked
