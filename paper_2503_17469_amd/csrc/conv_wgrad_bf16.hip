@@ -17,6 +17,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "bf16.h"
 #include "common.h"
@@ -698,12 +699,14 @@ __device__ __forceinline__ void wgrad3_reduce(const Wgrad3Params& p, const Chunk
 // As a matrix product the output is tiny (Cout x 27) and the reduction (all positions) is
 // everything, so the layer is bound by reading dY and X once: what kernel C spends on a 64 x 64
 // channel tile that is 15/16 empty, and on parking and re-reading such tiles, is avoided by giving
-// the product its own shape: rows = output channels (32 per block), columns = (tap, channel)
-// pairs, 9 x 4 = 36 of them, column 36 = a channel of ones (its product is the bias gradient),
-// reduction = positions, 16 per v_mfma_f32_32x32x16_bf16.  Both operands have the reduction as
-// their SLOW index in memory ([pos][channel]); they are staged in LDS as they arrive (16-byte
-// pieces) and the transposition happens in the fragment reads: eight 2-byte reads per lane and
-// fragment, at immediate offsets.  A workgroup walks units of 4 image rows (128 positions) of one
+// the product its own shape: rows = output channels (32 per block), columns = (tap, channel) pairs and, behind
+// them, a column of ones (its product is the bias gradient): 28 of 32 for three channels, 37 of 64 for four;
+// reduction = positions, 16 per v_mfma_f32_32x32x16_bf16.  dY is staged as it arrives ([pos][channel], 16-byte pieces) and
+// transposed by the LDS read (tr_pair).  X is staged as planes, one per channel and horizontal tap, each
+// shifted by its tap: the eight positions of an operand are then one aligned 16-byte read for every tap, and the
+// shifting costs nine 2-byte writes per pixel once instead of eight 2-byte reads per operand and lane, which bound this
+// kernel: 2048 images, 32 channels, pooled, with the classifier's gradients (17 us of it) in the same launch 60 -> 40 us, 64
+// channels not pooled 97 -> 76 us (3.7 TB/s).  A workgroup walks units of 4 image rows (128 positions) of one
 // worker; its four wavefronts split the positions of a unit and keep whole accumulators, which are
 // added through LDS at the end.  Chunks of one worker are added by a second small kernel in chunk
 // order (fixed summation order; no atomics).
@@ -715,7 +718,7 @@ struct Wgrad1Params {
   size_t worker_stride;
   int Cout, cin_real, H;
   int upc;              // units per chunk
-  float* partial;       // [chunk][MB * 2 * 16 * 64] accumulator images
+  float* partial;       // [chunk][MB * NB * 16 * 64] accumulator images
   // POOLED kernels: dy is not read; it is rebuilt from the gradient of the 2 x 2 max pooling that
   // follows the layer and the pooling's codes (one byte per pooled element: which input took it)
   const bf16_t* dpool;  // [rows][H/2][16][Cout]
@@ -723,8 +726,18 @@ struct Wgrad1Params {
   int raw3;             // src is [rows][H][32][3]: a pixel is three 2-byte loads
 };
 constexpr int kG_W = 32, kG_R = 4, kG_Unit = kG_W * kG_R;        // 128 positions
-constexpr int kG_PatchCols = kG_W + 2, kG_PatchRows = kG_R + 2;
-constexpr int kG_XBytes = kG_PatchRows * kG_PatchCols * 16;
+constexpr int kG_PatchRows = kG_R + 2;
+// Bytes of a plane [patch row][32]: 32 more than the data, so that the planes' reads spread over the banks.
+constexpr int kG_Plane = kG_PatchRows * kG_W * 2 + 32;
+
+// Where channel octet oct of a position lies in the staged dY strip.  Every other pair of 128-byte rows has its halves
+// swapped: the four rows of a transposing read then fill the 64 banks once, as 64-byte rows do by themselves.
+template <int MB>
+__device__ inline int wgrad1_y_offset(int pos, int oct) {
+  return MB == 2 ? pos * 128 + ((oct * 16) ^ ((pos & 2) << 5)) : pos * 64 + oct * 16;
+}
+__host__ __device__ inline int wgrad1_col_blocks(int cin_real) { return cin_real * 9 + 1 > 32 ? 2 : 1; }
+__host__ __device__ inline int wgrad1_stage_bytes(int mb, int cin_real) { return kG_Unit * 64 * mb + 3 * cin_real * kG_Plane; }
 
 // (co, column) of accumulator register v of lane l in block (mb, nb) -> where it goes in G
 __device__ inline void wgrad1_emit(const Wgrad1Params& p, float* gw, float* gb, int mb, int nb, int v, int lane,
@@ -732,23 +745,20 @@ __device__ inline void wgrad1_emit(const Wgrad1Params& p, float* gw, float* gb, 
   const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
   const int col = nb * 32 + (lane & 31);
   if (co >= p.Cout) return;
-  if (col < 36) {
-    const int tap = col >> 2, ci = col & 3;
-    if (ci < p.cin_real) gw[((size_t)co * 9 + tap) * p.cin_real + ci] = val;
-  } else if (col == 36 && gb != nullptr) {
-    gb[co] = val;
-  }
+  if (col < 9 * p.cin_real) gw[(size_t)co * 9 * p.cin_real + col] = val;
+  else if (col == 9 * p.cin_real && gb != nullptr) gb[co] = val;
 }
 
 // POOLED: the layer's output gradient was never written.  Every position takes the gradient of its
 // pooling window where the window's code names it and zero elsewhere: 16 + 8 bytes of pooled data
-// per piece (shared by the four positions of a window, so mostly cache hits) instead of 16 bytes
-// of a full-resolution tensor that a pooling-backward pass would have had to write first.
-template <int MB, bool POOLED>
+// per two positions instead of 16 bytes of a full-resolution tensor each that a pooling-backward pass would
+// have had to write first.
+template <int MB, int NB, bool POOLED>
 __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segments& seg, const Chunk& ck,
                                             unsigned char* smemg) {
-  const int SY = p.Cout * 2 + 8;                         // bytes per position of the staged dY strip
-  const int stage_bytes = (kG_Unit * SY + kG_XBytes + 15) & ~15;
+  constexpr int SY = 64 * MB;                              // bytes per position of the staged dY strip
+  const int cin = p.cin_real;
+  const int stage_bytes = wgrad1_stage_bytes(MB, cin);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
   const int wk = ck.wk, chunk_idx = ck.idx, nchunks = ck.n;
@@ -756,161 +766,178 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
   const int units = (seg.off[wk + 1] - seg.off[wk]) * upi;
   const int ubeg = chunk_idx * p.upc, uend = min(units, ubeg + p.upc);
 
-  // zero both stages once (halo columns of the patch are never written again)
+  // zero both stages once (halo columns of the planes and absent channels of dY are never written again)
   for (int i = tid * 16; i < 2 * stage_bytes; i += kThreads * 16) *reinterpret_cast<u32x4*>(smemg + i) = u32x4{0, 0, 0, 0};
   __syncthreads();
 
-  // staging tasks of this thread: dY pieces (16 bytes = 8 channels of one position), one patch piece
+  // staging tasks of this thread: dY pieces (16 bytes = 8 channels of one position; POOLED: of a pooled position, for
+  // the two positions of one row of its window), one pixel of the patch
   const int ppp = p.Cout / 8;                              // pieces per position
-  const int ny = kG_Unit * ppp;                            // pieces per unit: 128 ... 1024
-  constexpr int kYMax = 4;                                 // Cout <= 64
-  u32x4 ry[kYMax], rx;
-  u32x2 rk[kYMax];                                          // POOLED: the codes that go with ry
+  constexpr int kY = POOLED ? MB : 2 * MB;                 // Cout <= 32 MB
+  const int ny = (POOLED ? kG_Unit / 2 : kG_Unit) * ppp;
+  // two units are on their way at a time (one ahead, a trip of the loop lasted a memory round trip: 1.9 us of 0.5)
+  u32x4 ry[2][kY];
+  u32x2 rk[2][kY];                                          // POOLED: the codes that go with ry
   // a thread's pieces are the same in every unit: where each comes from (relative to the unit) and goes
-  int ysrc[kYMax], ydst[kYMax];
-  uint32_t yslot[kYMax];
+  int ysrc[kY], ydst[kY];
+  uint32_t yslot[kY];                                       // POOLED: place in the window of the first of the two positions
 #pragma unroll
-  for (int i = 0; i < kYMax; ++i) {
+  for (int i = 0; i < kY; ++i) {
     const int q = min(tid + kThreads * i, ny - 1);         // surplus slots re-read the last piece
-    const int pos = q / ppp, oct = q - pos * ppp;
-    ydst[i] = pos * SY + oct * 16;                          // 8-byte aligned (SY is 8 mod 16)
-    // POOLED: the unit's four rows are two pooled rows of 16; the window of position (r, c) is (r/2, c/2)
-    ysrc[i] = POOLED ? (((pos >> 6) * (kG_W / 2) + ((pos & 31) >> 1)) * p.Cout + oct * 8) : q * 8;
-    yslot[i] = (uint32_t)(((pos >> 5) & 1) * 2 + (pos & 1));
+    const int at = q / ppp, oct = q - at * ppp;
+    if (POOLED) {                                           // at = row of the unit, window along it
+      const int row = at >> 4, pc = at & 15;
+      ydst[i] = wgrad1_y_offset<MB>(row * kG_W + 2 * pc, oct);
+      ysrc[i] = ((row >> 1) * (kG_W / 2) + pc) * p.Cout + oct * 8;
+      yslot[i] = (uint32_t)(row & 1) * 2;
+    } else {
+      ydst[i] = wgrad1_y_offset<MB>(at, oct);
+      ysrc[i] = q * 8;
+      yslot[i] = 0;
+    }
   }
   const bool has_x = tid < kG_PatchRows * kG_W;
   const int xr = tid / kG_W, xc = tid % kG_W;              // patch row 0..5 (image row strip*4 - 1 + xr), column
-  auto fetch = [&](int u) {
+  uint32_t rx[2][2];                                        // up to four channels of the pixel
+  auto fetch = [&](int s, int u) {
     const int img = seg.off[wk] + u / upi, row0 = (u % upi) * kG_R;
     if constexpr (POOLED) {
       const size_t ubase = ((size_t)(img * (p.H >> 1) + (row0 >> 1)) * (kG_W / 2)) * p.Cout;
 #pragma unroll
-      for (int i = 0; i < kYMax; ++i) {
-        ry[i] = *reinterpret_cast<const u32x4*>(p.dpool + ubase + ysrc[i]);
-        rk[i] = *reinterpret_cast<const u32x2*>(p.code + ubase + ysrc[i]);
+      for (int i = 0; i < kY; ++i) {
+        ry[s][i] = *reinterpret_cast<const u32x4*>(p.dpool + ubase + ysrc[i]);
+        rk[s][i] = *reinterpret_cast<const u32x2*>(p.code + ubase + ysrc[i]);
       }
     } else {
       const bf16_t* ybase = p.dy + ((size_t)(img * p.H + row0) * kG_W) * p.Cout;
 #pragma unroll
-      for (int i = 0; i < kYMax; ++i) ry[i] = *reinterpret_cast<const u32x4*>(ybase + ysrc[i]);
+      for (int i = 0; i < kY; ++i) ry[s][i] = *reinterpret_cast<const u32x4*>(ybase + ysrc[i]);
     }
     const int grow = row0 - 1 + xr;
     const bool in = has_x && grow >= 0 && grow < p.H;
     const bf16_t* xp = p.src + ((size_t)(img * p.H + (in ? grow : 0)) * kG_W + xc) * (p.raw3 ? 3 : 8);
+    if (!has_x) xp = p.src;
     if (p.raw3) {
-      const bf16_t* q = has_x ? xp : p.src;
-      rx = u32x4{(uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2], 0u, 0u};
+      rx[s][0] = (uint32_t)xp[0] | ((uint32_t)xp[1] << 16);
+      rx[s][1] = xp[2];
     } else {
-      rx = *reinterpret_cast<const u32x4*>(has_x ? xp : p.src);
+      const u32x2 t = *reinterpret_cast<const u32x2*>(xp);
+      rx[s][0] = t[0];
+      rx[s][1] = t[1];
     }
-    if (!in) rx = u32x4{0, 0, 0, 0};
-    rx[2] = (rx[2] & 0xFFFF0000u) | 0x3F80u;               // channel 4 := 1.0 (the bias column reads it)
+    if (!in) rx[s][0] = rx[s][1] = 0u;
   };
-  auto stash = [&](int stage) {
-    unsigned char* sY = smemg + stage * stage_bytes;
+  auto stash = [&](int s) {
+    unsigned char* sY = smemg + s * stage_bytes;
     unsigned char* sX = sY + kG_Unit * SY;
 #pragma unroll
-    for (int i = 0; i < kYMax; ++i) {
-      const int q = tid + kThreads * i;
-      if (q < ny) {
-        if constexpr (POOLED) {
-          // keep a channel's gradient where its code names this position's place in the window
-          const uint32_t slot = yslot[i];
+    for (int i = 0; i < kY; ++i) {
+      if (tid + kThreads * i >= ny) continue;
+      unsigned char* d = sY + ydst[i];
+      if constexpr (POOLED) {
+        // keep a channel's gradient where its code names this position's place in the window
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const uint32_t slot = yslot[i] + half;
+          u32x4 w;
 #pragma unroll
           for (int d2 = 0; d2 < 4; ++d2) {
-            const uint32_t kk = rk[i][d2 >> 1] >> (16 * (d2 & 1));
+            const uint32_t kk = rk[s][i][d2 >> 1] >> (16 * (d2 & 1));
             const uint32_t lo = (kk & 0xFFu) == slot ? 0x0000FFFFu : 0u;
             const uint32_t hi = ((kk >> 8) & 0xFFu) == slot ? 0xFFFF0000u : 0u;
-            ry[i][d2] &= lo | hi;
+            w[d2] = ry[s][i][d2] & (lo | hi);
           }
+          *reinterpret_cast<u32x4*>(d + half * SY) = w;
         }
-        unsigned char* d = sY + ydst[i];
-        *reinterpret_cast<u32x2*>(d) = u32x2{ry[i][0], ry[i][1]};
-        *reinterpret_cast<u32x2*>(d + 8) = u32x2{ry[i][2], ry[i][3]};
+      } else {
+        *reinterpret_cast<u32x4*>(d) = ry[s][i];
       }
     }
-    if (has_x) *reinterpret_cast<u32x4*>(sX + (xr * kG_PatchCols + xc + 1) * 16) = rx;
+    if (has_x) {
+      // plane v * cin + ci holds X[row][column + v - 1][ci]
+      bf16_t* d = reinterpret_cast<bf16_t*>(sX) + xr * kG_W + xc + 1;
+#pragma unroll
+      for (int ci = 0; ci < 4; ++ci) {
+        if (ci >= cin) break;
+        const bf16_t val = (bf16_t)(rx[s][ci >> 1] >> (16 * (ci & 1)));
+        if (xc < kG_W - 1) d[ci * (kG_Plane / 2)] = val;
+        d[(cin + ci) * (kG_Plane / 2) - 1] = val;
+        if (xc > 0) d[(2 * cin + ci) * (kG_Plane / 2) - 2] = val;
+      }
+    }
   };
 
-  // fragment addressing.  A: lane supplies output channel lane%32 of block mb, positions
-  // 16*kb + 8*(lane/32) + i.  B: lane supplies column lane%32 of block nb.
+  // fragment addressing.  A: see wgrad_tr_body (conv3_wgrad_tr_device.h); rows = output channels of block mb.  B: lane
+  // supplies column lane % 32 of block nb at positions 8 * (lane / 32) .. + 7 of the sixteen.
   const int kg = lane >> 5, jl = lane & 31;
-  int bbase[2];
+  const int g = lane >> 4, sl = lane & 15;
+  const int abase = (8 * (g >> 1) + (sl >> 2)) * SY + (16 * (g & 1) + 4 * (sl & 3)) * 2, aswap = MB == 2 ? (sl & 8) << 3 : 0;
+  int bbase[NB];
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb) {
+  for (int nb = 0; nb < NB; ++nb) {
     const int col = nb * 32 + jl;
-    int u = 1, v = 1, ci = 5;                              // unused columns read a zero channel
-    if (col < 36) { u = (col >> 2) / 3; v = (col >> 2) % 3; ci = col & 3; }
-    else if (col == 36) ci = 4;
-    bbase[nb] = (u * kG_PatchCols + v + 8 * kg) * 16 + ci * 2;
+    const int tap = col < 9 * cin ? col / cin : 0, ci = col < 9 * cin ? col - tap * cin : 0;   // (absent columns are not stored)
+    bbase[nb] = (tap % 3 * cin + ci) * kG_Plane + (tap / 3 * kG_W + 8 * kg) * 2;
   }
-  const int abase = 8 * kg * SY + jl * 2;
+  const int ones_nb = 9 * cin / 32;
+  const bool ones = jl == 9 * cin % 32;
 
-  v16f acc[MB][2];
+  v16f acc[MB][NB];
 #pragma unroll
   for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
+  // one unit from stage S; the next one's pieces (set 1 - S) go to the other stage, those of the one after it set out
+  auto unit = [&](auto which, int u) {
+    constexpr int S = decltype(which)::value;
+    fetch(S, min(u + 2, uend - 1));
+    const unsigned char* sY = smemg + S * stage_bytes;
+    const unsigned char* sX = sY + kG_Unit * SY;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kb = wave + 4 * h;                          // 16 positions: image row kb/2, columns (kb%2)*16 ...
+      const unsigned char* ya = sY + kb * 16 * SY + abase;
+      const unsigned char* xb = sX + ((kb >> 1) * kG_W + (kb & 1) * 16) * 2;
+      bf16x8 fa[MB], fb[NB];
+#pragma unroll
+      for (int a = 0; a < MB; ++a) fa[a] = tr_pair(ya + ((a * 64) ^ aswap), ya + ((a * 64) ^ aswap) + 4 * SY);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        u32x4 w = *reinterpret_cast<const u32x4*>(xb + bbase[b]);
+        if (b == ones_nb && ones) w = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+        fb[b] = as_bf16x8(w);
+      }
+#pragma unroll
+      for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+    }
+    stash(S ^ 1);                                           // (past the last unit: never read)
+    __syncthreads();
+  };
   if (ubeg < uend) {
-    fetch(ubeg);
+    fetch(0, ubeg);
+    fetch(1, min(ubeg + 1, uend - 1));
     stash(0);
     __syncthreads();
-    int stage = 0;
-    for (int u = ubeg; u < uend; ++u) {
-      if (u + 1 < uend) fetch(u + 1);
-      const unsigned char* sY = smemg + stage * stage_bytes;
-      const unsigned char* sX = sY + kG_Unit * SY;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int kb = wave + 4 * h;                        // 16 positions: image row kb/2, columns (kb%2)*16 ...
-        const unsigned char* ya = sY + kb * 16 * SY + abase;
-        const unsigned char* xb = sX + ((kb >> 1) * kG_PatchCols + (kb & 1) * 16) * 16;
-        bf16x8 fa[MB], fb[2];
-#pragma unroll
-        for (int a = 0; a < MB; ++a) {
-          u32x4 w;
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const uint32_t lo = *reinterpret_cast<const uint16_t*>(ya + a * 64 + (2 * d) * SY);
-            const uint32_t hi = *reinterpret_cast<const uint16_t*>(ya + a * 64 + (2 * d + 1) * SY);
-            w[d] = lo | (hi << 16);
-          }
-          fa[a] = as_bf16x8(w);
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          u32x4 w;
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const uint32_t lo = *reinterpret_cast<const uint16_t*>(xb + bbase[b] + (2 * d) * 16);
-            const uint32_t hi = *reinterpret_cast<const uint16_t*>(xb + bbase[b] + (2 * d + 1) * 16);
-            w[d] = lo | (hi << 16);
-          }
-          fb[b] = as_bf16x8(w);
-        }
-#pragma unroll
-        for (int a = 0; a < MB; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-      }
-      if (u + 1 < uend) stash(stage ^ 1);
-      __syncthreads();
-      stage ^= 1;
+    for (int u = ubeg; u < uend; u += 2) {
+      unit(std::integral_constant<int, 0>{}, u);
+      if (u + 1 < uend) unit(std::integral_constant<int, 1>{}, u + 1);
     }
   }
 
   // add the four wavefronts' accumulators (wavefront order) and write the chunk's result
-  float* red = reinterpret_cast<float*>(smemg);            // [4][MB*2*16][64] floats = 32 KB at MB = 2
-  constexpr int kImg = MB * 2 * 16 * 64;
+  float* red = reinterpret_cast<float*>(smemg);            // [4][MB*NB*16][64] floats = 64 KB at most
+  constexpr int kImg = MB * NB * 16 * 64;
 #pragma unroll
   for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave * kImg + ((a * 2 + b) * 16 + v) * 64 + lane] = acc[a][b][v];
+      for (int v = 0; v < 16; ++v) red[wave * kImg + ((a * NB + b) * 16 + v) * 64 + lane] = acc[a][b][v];
   __syncthreads();
   float* gw = p.gw + (size_t)wk * p.worker_stride;
   float* gb = p.gb ? p.gb + (size_t)wk * p.worker_stride : nullptr;
@@ -920,16 +947,17 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
       p.partial[(size_t)ck.row * kImg + e] = val;
     } else {
       const int blk = e / (16 * 64), v = (e / 64) % 16, l = e % 64;
-      wgrad1_emit(p, gw, gb, blk / 2, blk % 2, v, l, val);
+      wgrad1_emit(p, gw, gb, blk / NB, blk % NB, v, l, val);
     }
   }
 }
 
-// One workgroup per worker and 64 of the MB * 2048 accumulator elements; each of the four wavefronts adds a
+// One workgroup per worker and 64 of the MB * NB * 1024 accumulator elements; each of the four wavefronts adds a
 // quarter of the worker's chunks (in chunk order, eight loads in flight), the quarters are then
 // added in order through LDS: a fixed summation order with four times the loads in flight.
 __device__ __forceinline__ void wgrad1_reduce(const Wgrad1Params& p, const Chunk& ck, int z, float* lds) {
-  const int kImg = p.Cout > 32 ? 2 * 2 * 16 * 64 : 2 * 16 * 64;
+  const int NB = wgrad1_col_blocks(p.cin_real);
+  const int kImg = (p.Cout > 32 ? 2 : 1) * NB * 16 * 64;
   float (*part)[64] = reinterpret_cast<float (*)[64]>(lds);   // [4]
   const int wk = ck.wk, nchunks = ck.n;
   const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
@@ -954,7 +982,7 @@ __device__ __forceinline__ void wgrad1_reduce(const Wgrad1Params& p, const Chunk
   float* gw = p.gw + (size_t)wk * p.worker_stride;
   float* gb = p.gb ? p.gb + (size_t)wk * p.worker_stride : nullptr;
   const int blk = e / (16 * 64), v = (e / 64) % 16, l = e % 64;
-  wgrad1_emit(p, gw, gb, blk / 2, blk % 2, v, l, s);
+  wgrad1_emit(p, gw, gb, blk / NB, blk % NB, v, l, s);
 }
 
 // ------------------------------------------------------------------ launches of several layers
@@ -1010,7 +1038,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_batch_kernel(BatchTable tab
 // The first layer's chunks and, in front of them, the classifier's parameter gradients and the losses: both are short
 // of registers and LDS and long on memory waits, and run four workgroups to a compute unit (in the launch above
 // they would be two).
-template <int MB, bool POOLED>
+template <int MB, int NB, bool POOLED>
 __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, HeadWgradParams head, int head_x, int head_blocks,
                                                                   Segments seg) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1019,7 +1047,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, 
     head_wgrad_loss_body<bf16_t>(head, seg, b % head_x, b / head_x, reinterpret_cast<float*>(smem));
     return;
   }
-  wgrad1_body<MB, POOLED>(job.first, seg, chunk_at(job, seg.K, b - head_blocks), smem);
+  wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(job, seg.K, b - head_blocks), smem);
 }
 
 // Second stage of the layers in which some worker has more than one chunk.
@@ -1080,13 +1108,13 @@ bool plan_first(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   Wgrad1Params p{};
   p.dy = j.dy; p.src = j.src; p.gw = j.gw; p.gb = j.gb; p.worker_stride = worker_stride;
   p.Cout = j.Cout; p.cin_real = j.cin_real; p.H = g.Hs; p.dpool = j.dpool; p.code = j.pool_code; p.raw3 = g.raw3;
-  pl.job.kind = kFirst; pl.job.tiles = 1; pl.job.slots = mb * 32; pl.job.first = p;
+  const int nb = wgrad1_col_blocks(j.cin_real);
+  pl.job.kind = kFirst; pl.job.tiles = 1; pl.job.slots = mb * nb * 16; pl.job.first = p;
   count_units(pl, seg, g.Hs / kG_R, 1);
   // about four workgroups per compute unit, at least 4 units each
   pl.min_upc = 4; pl.upc_step = 1; pl.alone = std::max(64, 1024 - seg.K);
-  pl.slot_floats = (size_t)mb * 2 * 16 * 64;
-  const size_t stage = ((size_t)kG_Unit * (j.Cout * 2 + 8) + kG_XBytes + 15) & ~(size_t)15;
-  pl.lds = std::max(2 * stage, 4 * pl.slot_floats * sizeof(float));
+  pl.slot_floats = (size_t)mb * nb * 16 * 64;
+  pl.lds = std::max((size_t)2 * wgrad1_stage_bytes(mb, j.cin_real), 4 * pl.slot_floats * sizeof(float));
   return true;
 }
 
@@ -1216,18 +1244,18 @@ void set_partial(BatchJob& job, float* partial) {
   }
 }
 
-template <int MB, bool POOLED>
+template <int MB, int NB, bool POOLED>
 void launch_light(hipStream_t st, const BatchJob& job, const HeadWgradParams* head, size_t lds, const Segments& seg) {
   static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
   if (head) lds = std::max(lds, kHeadWgradLdsFloats * sizeof(float));
   if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_light_kernel<MB, POOLED>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_light_kernel<MB, NB, POOLED>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     configured = lds;
   }
   const dim3 hg = head ? head_wgrad_grid(head->cin, head->C, seg.K) : dim3(1, 0, 1);
   const int head_blocks = (int)(hg.x * hg.y);
-  hipLaunchKernelGGL((wgrad_light_kernel<MB, POOLED>), dim3(head_blocks + job.chunk[seg.K]), dim3(kThreads), lds, st, job,
+  hipLaunchKernelGGL((wgrad_light_kernel<MB, NB, POOLED>), dim3(head_blocks + job.chunk[seg.K]), dim3(kThreads), lds, st, job,
                      head ? *head : HeadWgradParams{}, (int)hg.x, head_blocks, seg);
 }
 
@@ -1299,13 +1327,15 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
     if (light >= 0) {
       const Plan& pl = plans[light];
       const bool pooled = pl.job.first.dpool != nullptr;
-      if (pl.job.first.Cout > 32) {
-        if (pooled) launch_light<2, true>(st, pl.job, h, pl.lds, seg);
-        else launch_light<2, false>(st, pl.job, h, pl.lds, seg);
-      } else {
-        if (pooled) launch_light<1, true>(st, pl.job, h, pl.lds, seg);
-        else launch_light<1, false>(st, pl.job, h, pl.lds, seg);
-      }
+      const int nb = wgrad1_col_blocks(pl.job.first.cin_real);
+#define OMNI_LIGHT(MB_, NB_)                                                \
+  {                                                                         \
+    if (pooled) launch_light<MB_, NB_, true>(st, pl.job, h, pl.lds, seg);   \
+    else launch_light<MB_, NB_, false>(st, pl.job, h, pl.lds, seg);         \
+  }
+      if (pl.job.first.Cout > 32) { if (nb == 2) OMNI_LIGHT(2, 2) else OMNI_LIGHT(2, 1) }
+      else { if (nb == 2) OMNI_LIGHT(1, 2) else OMNI_LIGHT(1, 1) }
+#undef OMNI_LIGHT
     } else if (h) {
       head_wgrad_loss(st, true, *h, seg);
     }

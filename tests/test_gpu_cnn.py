@@ -107,6 +107,25 @@ def test_cnn_patch_kernels(hw, chans, B, cuts):
     _check_step(layers, (hw, hw, 3), params, x, y, cuts, 0.05, f"cnn3-{hw}px-{chans}")
 
 
+@pytest.mark.parametrize("chans,B,cuts", [
+    ((1, 8, 32, 32), 7, [0, 1, 7]),        # 10 of 32 columns, a quarter of the output channels
+    ((3, 40, 32, 32), 9, [0, 4, 9]),       # second channel block a quarter full
+    ((4, 24, 32, 32), 8, [0, 3, 8]),       # 37 columns: the bias gradient's lies in the second block
+    ((4, 64, 32, 32), 6, [0, 5, 6]),
+    ((3, 32, 32, 32), 70, [0, 69, 70]),    # a worker of several chunks
+])
+def test_first_layer_weight_gradient(chans, B, cuts):
+    layers = synth.cnn3(num_classes=10, hw=32, chans=chans)
+    rng = np.random.default_rng(B)
+    params = synth.he_normal_params(layers, 8, True)
+    for sl in synth.param_slices(layers):
+        if "b" in sl:
+            s, e = sl["b"]
+            params[s:e] = synth.to_bf16_grid(rng.standard_normal(e - s).astype(np.float32) * 0.2)
+    x, y = synth.make_batch(40 + B, B, (32, 32, chans[0]), 10, True)
+    _check_step(layers, (32, 32, chans[0]), params, x, y, cuts, 0.05, f"first layer {chans}")
+
+
 def test_config2_cnn3():
     w = synth.workload(2)
     b, off = controller_run(w.T, w.B)
