@@ -1031,13 +1031,14 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_batch_kernel(BatchTable tab
     case kPatch16: wgrad3_body<16>(job.patch, seg, ck, tile, smem); break;
     case kPatch32: wgrad3_body<32>(job.patch, seg, ck, tile, smem); break;
     case kPatchAny: wgrad3_body<0>(job.patch, seg, ck, tile, smem); break;
-    default: wgrad_tr_body<2>(job.stride2, seg, ck, tile, smem); break;
+    case kStride2: wgrad_tr_body<2>(job.stride2, seg, ck, tile, smem); break;
+    default: break;   // (kFirst has launches of its own)
   }
 }
 
-// The first layer's chunks and, in front of them, the classifier's parameter gradients and the losses: both are short
-// of registers and LDS and long on memory waits, and run four workgroups to a compute unit (in the launch above
-// they would be two).
+// The chunks of a layer on the network input and, in front of them, the classifier's parameter gradients and the losses:
+// both are short of registers and LDS and long on memory waits, and run four workgroups to a compute unit (in the launch
+// above they would be two).
 template <int MB, int NB, bool POOLED>
 __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, HeadWgradParams head, int head_x, int head_blocks,
                                                                   Segments seg) {
@@ -1244,6 +1245,56 @@ void set_partial(BatchJob& job, float* partial) {
   }
 }
 
+// What the layers of one call (at most kBatchJobs) are launched as: a table for the shared first stage, one for the second
+// stage, and the layers on the network input, each of which has a first stage of its own.
+struct BatchPlan {
+  Plan plans[kBatchJobs];
+  BatchTable tab, red;
+  int light[kBatchJobs], lights;   // places in plans
+  int member[kBatchJobs];          // ... of the jobs of tab
+  int blocks, rblocks;
+  size_t lds, scratch_each;
+};
+
+void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_stride, const Segments& seg, float* partial,
+                int workgroups) {
+  std::memset(&bp, 0, sizeof(bp));
+  int heavy = 0;
+  double work = 0.0;
+  for (int i = 0; i < m; ++i) {
+    Plan& pl = bp.plans[i];
+    if (plan_first(pl, jobs[i], worker_stride, seg)) { bp.light[bp.lights++] = i; continue; }
+    if (!plan_patch(pl, jobs[i], worker_stride, seg) && !plan_stride2(pl, jobs[i], worker_stride, seg))
+      plan_general(pl, jobs[i], worker_stride, seg);
+    work += pl.work;
+    ++heavy;
+  }
+  // Layers that share the launch share its workgroups in proportion to the time their units take (not
+  // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
+  const size_t budget = conv_wgrad_partial_floats() / m;
+  bp.scratch_each = budget / 4 * 4;
+  for (int i = 0; i < m; ++i) {
+    Plan& pl = bp.plans[i];
+    const bool light = pl.job.kind == kFirst;
+    const long aim = light || heavy == 1 ? pl.alone : std::max<long>(1, (long)(workgroups * pl.work / work));
+    cut_chunks(pl, seg, aim, budget);
+    set_partial(pl.job, partial + bp.scratch_each * i);
+    pl.job.first_block = bp.blocks;
+    pl.job.first_reduce = bp.rblocks;
+    bool chunked = false;
+    for (int k = 0; k < seg.K; ++k) chunked = chunked || pl.job.chunk[k + 1] - pl.job.chunk[k] > 1;
+    if (chunked) {
+      bp.rblocks += pl.job.tiles * seg.K * pl.job.slots;
+      bp.red.job[bp.red.n++] = pl.job;
+    }
+    if (light) continue;
+    bp.blocks += pl.job.tiles * pl.job.chunk[seg.K];
+    bp.lds = std::max(bp.lds, pl.lds);
+    bp.member[bp.tab.n] = i;
+    bp.tab.job[bp.tab.n++] = pl.job;
+  }
+}
+
 template <int MB, int NB, bool POOLED>
 void launch_light(hipStream_t st, const BatchJob& job, const HeadWgradParams* head, size_t lds, const Segments& seg) {
   static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
@@ -1276,56 +1327,20 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
     return;
   }
   for (int base = 0; base < n; base += kBatchJobs) {
-    const int m = std::min(n - base, kBatchJobs);
-    Plan plans[kBatchJobs];
-    int heavy = 0, light = -1;
-    double work = 0.0;
-    for (int i = 0; i < m; ++i) {
-      Plan& pl = plans[i];
-      std::memset(&pl, 0, sizeof(pl));
-      const ConvWgradJob& j = jobs[base + i];
-      if (plan_first(pl, j, worker_stride, seg)) { light = i; continue; }
-      if (!plan_patch(pl, j, worker_stride, seg) && !plan_stride2(pl, j, worker_stride, seg))
-        plan_general(pl, j, worker_stride, seg);
-      work += pl.work;
-      ++heavy;
-    }
-    // Layers that share the launch share its workgroups in proportion to the time their units take (not
-    // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
-    const size_t budget = conv_wgrad_partial_floats() / m;
-    BatchTable tab{}, red{};
-    int blocks = 0, rblocks = 0;
-    size_t lds = 0;
-    for (int i = 0; i < m; ++i) {
-      Plan& pl = plans[i];
-      const long aim = (i == light || heavy == 1) ? pl.alone : std::max<long>(1, (long)(workgroups * pl.work / work));
-      cut_chunks(pl, seg, aim, budget);
-      set_partial(pl.job, partial + budget / 4 * 4 * i);
-      pl.job.first_block = blocks;
-      pl.job.first_reduce = rblocks;
-      bool chunked = false;
-      for (int k = 0; k < seg.K; ++k) chunked = chunked || pl.job.chunk[k + 1] - pl.job.chunk[k] > 1;
-      if (chunked) {
-        rblocks += pl.job.tiles * seg.K * pl.job.slots;
-        red.job[red.n++] = pl.job;
-      }
-      if (i == light) continue;
-      blocks += pl.job.tiles * pl.job.chunk[seg.K];
-      lds = std::max(lds, pl.lds);
-      tab.job[tab.n++] = pl.job;
-    }
-    if (blocks > 0) {
+    BatchPlan bp;
+    plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, workgroups);
+    if (bp.blocks > 0) {
       static bool configured = false;   // raising the dynamic LDS limit is a per-function host call
       if (!configured) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_batch_kernel),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
         configured = true;
       }
-      hipLaunchKernelGGL(wgrad_batch_kernel, dim3(blocks), dim3(kThreads), lds, st, tab, seg);
+      hipLaunchKernelGGL(wgrad_batch_kernel, dim3(bp.blocks), dim3(kThreads), bp.lds, st, bp.tab, seg);
     }
-    const HeadWgradParams* h = base == 0 ? head : nullptr;
-    if (light >= 0) {
-      const Plan& pl = plans[light];
+    const HeadWgradParams* h = base == 0 ? head : nullptr;   // rides with the first of the light launches
+    for (int i = 0; i < bp.lights; ++i) {
+      const Plan& pl = bp.plans[bp.light[i]];
       const bool pooled = pl.job.first.dpool != nullptr;
       const int nb = wgrad1_col_blocks(pl.job.first.cin_real);
 #define OMNI_LIGHT(MB_, NB_)                                                \
@@ -1336,10 +1351,36 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
       if (pl.job.first.Cout > 32) { if (nb == 2) OMNI_LIGHT(2, 2) else OMNI_LIGHT(2, 1) }
       else { if (nb == 2) OMNI_LIGHT(1, 2) else OMNI_LIGHT(1, 1) }
 #undef OMNI_LIGHT
-    } else if (h) {
-      head_wgrad_loss(st, true, *h, seg);
+      h = nullptr;
     }
-    if (rblocks > 0) hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(rblocks), dim3(kThreads), 0, st, red, seg);
+    if (h) head_wgrad_loss(st, true, *h, seg);
+    if (bp.rblocks > 0) hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(bp.rblocks), dim3(kThreads), 0, st, bp.red, seg);
+  }
+}
+
+void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, int workgroups, ConvWgradPlanned* out) {
+  int launch = 0;
+  for (int base = 0; base < n; base += kBatchJobs) {
+    BatchPlan bp;
+    const int m = std::min(n - base, kBatchJobs);
+    plan_batch(bp, jobs + base, m, 0, seg, nullptr, workgroups);
+    const int shared = launch++;
+    for (int i = 0; i < m; ++i) {
+      const BatchJob& job = bp.plans[i].job;
+      ConvWgradPlanned& o = out[base + i];
+      o = ConvWgradPlanned{};
+      o.first_layer = job.kind == kFirst;
+      o.launch = -1;
+      for (int l = 0; l < bp.lights; ++l)
+        if (bp.light[l] == i) o.launch = launch + l;
+      for (int l = 0; l < bp.tab.n; ++l)
+        if (bp.member[l] == i) o.launch = o.launch < 0 && bp.tab.job[l].kind != kFirst ? shared : -2;
+      o.workgroups = job.tiles * job.chunk[seg.K];
+      for (int k = 0; k < seg.K; ++k) o.reduced = o.reduced || job.chunk[k + 1] - job.chunk[k] > 1;
+      o.scratch_begin = bp.scratch_each * i;
+      o.scratch_end = o.scratch_begin + (o.reduced ? (size_t)o.workgroups * bp.plans[i].slot_floats : 0);
+    }
+    launch += bp.lights;
   }
 }
 

@@ -250,6 +250,15 @@ double conv_wgrad_work(const ConvWgradJob& job);   // flop
 // shared first stage are cut into (two fit a compute unit).
 void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                       float* partial, const HeadWgradParams* head, int workgroups);
+// How conv_wgrad_batch runs these layers, without a launch: for checks on the host.
+struct ConvWgradPlanned {
+  bool first_layer;    // has a first stage of its own
+  int launch;          // number of the first-stage launch it is in, negative if it is in none or in several
+  int workgroups;
+  bool reduced;        // has a second stage, and then the scratch (floats from the start of it)
+  size_t scratch_begin, scratch_end;
+};
+void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, int workgroups, ConvWgradPlanned* out);
 
 // ---- bf16 pointwise kernels (pointwise_bf16.hip) ----
 // fp32 weights [cout][taps][cin_real] -> bf16 [cout][taps][cin_pad] (zero padded) and,

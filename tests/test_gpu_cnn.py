@@ -222,3 +222,30 @@ def test_workspace_overwritten_between_steps():
                 assert again["loss"] == first["loss"] and again["status"] == 0
         finally:
             run.close()
+
+
+@pytest.mark.parametrize("c1,second,B,cuts", [
+    (8, "same", 11, [0, 1, 4, 11]),
+    (32, "same", 70, [0, 69, 70]),          # a worker of several chunks: both layers have a second stage
+    (24, "through", 21, [0, 5, 6, 21]),     # beside an ordinary convolution, and of two widths
+])
+def test_two_convolutions_on_the_network_input(c1, second, B, cuts):
+    """Both weight gradients are the first-layer kernel's, in launches of their own."""
+    conv = lambda src, cin, cout: dict(op="conv", src=src, cin=cin, cout=cout, k=3, stride=1, pad=1, bias=True)
+    if second == "same":
+        layers, c = [conv(-1, 3, c1), conv(-1, 3, c1)], c1
+        a, b = 0, 1
+    else:
+        layers, c = [conv(-1, 3, c1), conv(0, c1, 40), conv(-1, 3, 40)], 40
+        a, b = 1, 2
+    n = len(layers)
+    layers += [dict(op="add", src=a, src2=b), dict(op="relu", src=n), dict(op="maxpool2", src=n + 1),
+               dict(op="gap", src=n + 2), dict(op="linear", src=n + 3, cin=c, cout=10, bias=True)]
+    rng = np.random.default_rng(c1)
+    params = synth.he_normal_params(layers, 31, True)
+    for sl in synth.param_slices(layers):
+        if "b" in sl:
+            s, e = sl["b"]
+            params[s:e] = synth.to_bf16_grid(rng.standard_normal(e - s).astype(np.float32) * 0.2)
+    x, y = synth.make_batch(500 + B, B, (32, 32, 3), 10, True)
+    _check_step(layers, (32, 32, 3), params, x, y, cuts, 0.05, f"two first layers {second} {c1}")

@@ -1,0 +1,83 @@
+"""Which launches the weight gradients of one call become, checked on the host: the library's planning is compiled
+against its internal header and asked, nothing is launched."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2503_17469_amd import binding
+
+CSRC = os.path.join(os.path.dirname(binding.LIB_PATH), "csrc")
+
+SHIM = r"""
+#include "kernels.h"
+using namespace omni;
+// layers: n x (hw, cin, cout, stride); out: n x (first_layer, launch, workgroups, reduced, scratch_begin, scratch_end)
+extern "C" size_t describe(const int* layers, int n, const int* off, int K, int workgroups, long* out) {
+  ConvWgradJob jobs[32] = {};
+  for (int i = 0; i < n; ++i) {
+    const int hw = layers[4 * i], cin = layers[4 * i + 1], cout = layers[4 * i + 2], s = layers[4 * i + 3];
+    ConvGeom g{};
+    g.rows = off[K]; g.Hs = g.Ws = hw; g.Cs = (cin + 7) / 8 * 8; g.Hp = g.Wp = hw / s;
+    g.ks = 3; g.stride = s; g.pad = 1; g.K = 9 * g.Cs;
+    jobs[i].Cout = cout; jobs[i].cin_real = cin; jobs[i].g = g;
+  }
+  Segments seg{};
+  seg.K = K;
+  for (int k = 0; k <= K; ++k) seg.off[k] = off[k];
+  ConvWgradPlanned p[32];
+  conv_wgrad_describe(jobs, n, seg, workgroups, p);
+  for (int i = 0; i < n; ++i) {
+    const long v[6] = {p[i].first_layer, p[i].launch, p[i].workgroups, p[i].reduced, (long)p[i].scratch_begin,
+                       (long)p[i].scratch_end};
+    for (int e = 0; e < 6; ++e) out[6 * i + e] = v[e];
+  }
+  return conv_wgrad_partial_floats();
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shim")
+    (d / "shim.cpp").write_text(SHIM)
+    lib_dir = os.path.dirname(binding.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
+                    str(d / "shim.cpp"), "-o", str(d / "shim.so"), "-L" + lib_dir, "-l:libomnistep.so",
+                    "-Wl,-rpath," + lib_dir, "-Wl,--allow-shlib-undefined"], check=True)
+    lib = ctypes.CDLL(str(d / "shim.so"))
+    lib.describe.restype = ctypes.c_size_t
+    return lib
+
+
+FIRST3, FIRST4, MID, S2 = (32, 3, 32, 1), (32, 4, 64, 1), (16, 32, 64, 1), (32, 64, 128, 2)
+
+
+@pytest.mark.parametrize("layers", [
+    [FIRST3], [FIRST3, FIRST3], [FIRST3, FIRST4, MID], [MID, FIRST4, S2, FIRST3], [FIRST3] * 6, [FIRST3] * 8,
+    [MID, MID, MID, MID, MID, FIRST3, FIRST3], [MID, S2], [S2],
+])
+@pytest.mark.parametrize("off", [[0, 1], [0, 5, 6, 37], [0, 256, 512, 768, 1024], [0, 300, 2048]])
+@pytest.mark.parametrize("workgroups", [256, 512])
+def test_every_layer_is_in_one_launch_that_knows_its_kind(shim, layers, off, workgroups):
+    n = len(layers)
+    flat = (ctypes.c_int * (4 * n))(*[v for L in layers for v in L])
+    offs = (ctypes.c_int * len(off))(*off)
+    out = (ctypes.c_long * (6 * n))()
+    room = shim.describe(flat, n, offs, len(off) - 1, workgroups, out)
+    rows = [tuple(out[6 * i:6 * i + 6]) for i in range(n)]
+    for (first, launch, blocks, reduced, lo, hi), L in zip(rows, layers):
+        assert first == (L in (FIRST3, FIRST4))
+        assert launch >= 0, "in no launch, in two, or in one whose kernel does not know it"
+        assert len(off) - 1 <= blocks < 1 << 20      # at least a workgroup per worker
+        assert 0 <= lo <= hi <= room
+    # layers on the network input share a first stage with nobody
+    for i in range(n):
+        others = [j for j in range(n) if j != i and rows[j][1] == rows[i][1]]
+        assert not (rows[i][0] and others)
+        assert all(not rows[j][0] for j in others)
+    # layers of one call of six (whose second stage is one launch) keep their partial tiles apart
+    for base in range(0, n, 6):
+        spans = sorted(r[4:6] for r in rows[base:base + 6] if r[3])
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
