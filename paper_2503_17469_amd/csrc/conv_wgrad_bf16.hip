@@ -1257,7 +1257,7 @@ struct BatchPlan {
 };
 
 void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_stride, const Segments& seg, float* partial,
-                int workgroups) {
+                size_t floats, int workgroups) {
   std::memset(&bp, 0, sizeof(bp));
   int heavy = 0;
   double work = 0.0;
@@ -1271,7 +1271,7 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
   }
   // Layers that share the launch share its workgroups in proportion to the time their units take (not
   // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
-  const size_t budget = conv_wgrad_partial_floats() / m;
+  const size_t budget = std::min(floats, conv_wgrad_partial_floats()) / m;
   bp.scratch_each = budget / 4 * 4;
   for (int i = 0; i < m; ++i) {
     Plan& pl = bp.plans[i];
@@ -1321,14 +1321,14 @@ double conv_wgrad_work(const ConvWgradJob& j) {
 }
 
 void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, const HeadWgradParams* head, int workgroups) {
+                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups) {
   if (head && n == 0) {
     head_wgrad_loss(st, true, *head, seg);
     return;
   }
   for (int base = 0; base < n; base += kBatchJobs) {
     BatchPlan bp;
-    plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, workgroups);
+    plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, floats, workgroups);
     if (bp.blocks > 0) {
       static bool configured = false;   // raising the dynamic LDS limit is a per-function host call
       if (!configured) {
@@ -1363,7 +1363,7 @@ void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, i
   for (int base = 0; base < n; base += kBatchJobs) {
     BatchPlan bp;
     const int m = std::min(n - base, kBatchJobs);
-    plan_batch(bp, jobs + base, m, 0, seg, nullptr, workgroups);
+    plan_batch(bp, jobs + base, m, 0, seg, nullptr, conv_wgrad_partial_floats(), workgroups);
     const int shared = launch++;
     for (int i = 0; i < m; ++i) {
       const BatchJob& job = bp.plans[i].job;

@@ -646,18 +646,34 @@ void launch_wgrad(hipStream_t st, const SmallWgrad& p, const Segments& seg, cons
 }
 
 // Shares of a weight gradient with `tiles` tiles: as many as give the chip four workgroups per compute unit, at least 64 rows
-// each and one per worker.  A compute unit needs about 6.5 ns per row of a tile, which only the compute units without
-// a tile can take off it, and the second launch costs about 5 us: measured with 1024 and 4096 rows, the line lies near
-// 850 rows times the idle part of the chip (64-128-10 net, 4096 rows: step 42 -> 26 us; 256-256-10, 1024 rows: 23 -> 26).
+// each and one per worker, within `scratch_rows` in all.  A compute unit needs about 6.5 ns per row of a tile, which only the
+// compute units without a tile can take off it, and the second launch costs about 5 us: measured with 1024 and 4096 rows, the
+// line lies near 850 rows times the idle part of the chip (64-128-10 net, 4096 rows: step 42 -> 26 us; 256-256-10, 1024 rows:
+// 23 -> 26).
+long shares_wanted(long tiles, long rows) {
+  if (tiles < 1 || rows * (256 - tiles) < 850 * 256) return 0;
+  return std::min<long>(std::min<long>(1024 / tiles, rows / 64), 64);
+}
 bool wgrad_shares(long tiles, const Segments& seg, size_t scratch_rows, SmallShares& sh) {
   const long rows = seg.off[seg.K];
-  if (rows * (256 - tiles) < 850 * 256) return false;
-  const long want = std::min<long>(std::min<long>(1024 / tiles, rows / 64), (long)scratch_rows - seg.K);
-  if (want < 2) return false;
-  sh.first[0] = 0;
-  for (int k = 0; k < seg.K; ++k)
-    sh.first[k + 1] = sh.first[k] + (int)std::max<long>(1, want * (seg.off[k + 1] - seg.off[k]) / rows);
-  return sh.first[seg.K] >= 2;
+  for (long want = shares_wanted(tiles, rows); want >= 2; --want) {
+    sh.first[0] = 0;
+    for (int k = 0; k < seg.K; ++k)
+      sh.first[k + 1] = sh.first[k] + (int)std::max<long>(1, want * (seg.off[k + 1] - seg.off[k]) / rows);
+    if ((size_t)sh.first[seg.K] <= scratch_rows) return sh.first[seg.K] >= 2;
+  }
+  return false;
+}
+
+// 16 x 64 tiles of the jobs; narrow: some layer's rows are shorter than a vector, which takes 16 x 16 tiles and no shares
+long wgrad_tiles(const LinearWgradJob* jobs, int n, bool& narrow) {
+  long tiles = 0;
+  narrow = false;
+  for (int i = 0; i < n; ++i) {
+    tiles += (long)((jobs[i].cout + 15) / 16) * ((jobs[i].cin + 63) / 64);
+    narrow = narrow || jobs[i].cin < 4;
+  }
+  return tiles;
 }
 
 }  // namespace
@@ -677,15 +693,17 @@ void linear_dgrad_f32_small(hipStream_t st, const float* dy, const float* w, con
   small_gemm<true>(st, SmallGemm{dy, w, dx, rows, cin, cout, nullptr, mask, 0, accumulate ? 1 : 0, {}}, head, seg);
 }
 
+size_t linear_wgrad_f32_share_rows(const LinearWgradJob* jobs, int n, int K_max, int B_max) {
+  bool narrow;
+  const long want = shares_wanted(wgrad_tiles(jobs, n, narrow), B_max);
+  return narrow || n > kSmallJobs || want < 2 ? 0 : (size_t)(want + K_max - 1);
+}
+
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                             const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
                             const WgradScratch& scratch) {
-  long tiles = 0;
-  bool narrow = false;
-  for (int i = 0; i < n; ++i) {
-    tiles += (long)((jobs[i].cout + 15) / 16) * ((jobs[i].cin + 63) / 64);
-    narrow = narrow || jobs[i].cin < 4;
-  }
+  bool narrow;
+  const long tiles = wgrad_tiles(jobs, n, narrow);
   // Enough tiles for the chip's 1024 SIMDs, or few rows: one wavefront walks all rows of a tile and needs no exchange.
   // Otherwise the rows are dealt to the four wavefronts of a workgroup.
   const int nw = tiles >= 512 || seg.off[seg.K] <= 64 ? 1 : 4;

@@ -88,6 +88,8 @@ struct WgradScratch {
   float* G;            // worker 0's gradients of all parameters
   size_t params;
 };
+// The most rows a step of at most K_max workers and B_max rows would use for these jobs (their widths); 0: none.
+size_t linear_wgrad_f32_share_rows(const LinearWgradJob* jobs, int n, int K_max, int B_max);
 void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                             const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
                             const WgradScratch& scratch);
@@ -245,11 +247,12 @@ struct ConvWgradJob {
 };
 bool conv_wgrad_pooled_supported(int Cout, int cin_real, const ConvGeom& g);
 double conv_wgrad_work(const ConvWgradJob& job);   // flop
-// All jobs share launches (first stage, second stage).  partial: conv_wgrad_partial_floats() of scratch.  head (may be
+// All jobs share launches (first stage, second stage).  partial: `floats` of scratch, which bound the cutting; more than
+// conv_wgrad_partial_floats() are not used.  head (may be
 // null): the classifier's parameter gradients and losses as well (head_wgrad_loss).  workgroups: how many the layers of a
 // shared first stage are cut into (two fit a compute unit).
 void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, const HeadWgradParams* head, int workgroups);
+                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups);
 // How conv_wgrad_batch runs these layers, without a launch: for checks on the host.
 struct ConvWgradPlanned {
   bool first_layer;    // has a first stage of its own

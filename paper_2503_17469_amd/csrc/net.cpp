@@ -20,7 +20,9 @@
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr size_t kShareMaxParams = 1 << 19;   // (256 tiles of 16 x 64 weights are 2^18)
+// Scratch that only makes some launches wider is bounded: 16 MiB for the row shares of fp32 weight gradients (with more
+// workers or weights than fit, fewer shares), as much for the last bf16 weight gradients beside a running side stream.
+constexpr size_t kSmallScratchFloats = 4u << 20;
 constexpr size_t kNoGrad = ~(size_t)0;
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -64,7 +66,7 @@ struct omni_net {
   size_t grads_off = 0, loss_rows_off = 0, status_off = 0;
   size_t shadow_off = 0, shadow_elems = 0, xpad_off = 0, conv_partial_off = 0, conv_counters_off = 0;
   size_t conv_partial2_off = 0;     // chunk scratch of the second side stream
-  size_t conv_partial3_off = 0;     // ... and of the main stream
+  size_t conv_partial3_off = 0;     // ... and of the main stream while the side streams use theirs
   size_t bn_off = 0, bn_floats = 0, bn_partial_off = 0;
   size_t share_off = 0, share_rows = 0;   // fp32: row shares of the weight gradients (small nets, large batches)
   size_t reduced_off = 0;           // g = sum_k lambda_k g_k, written only on request
@@ -312,15 +314,24 @@ int omni_net_create(const omni_layer_desc* descs, int32_t n, int32_t in_h, int32
   net->reduced_off = take(net->P_stride * sizeof(float));
   net->loss_rows_off = take((size_t)B_max * sizeof(float));
   net->status_off = take(kAlign);
-  if (!bf && B_max >= 1024 && ppos <= kShareMaxParams) {
-    net->share_rows = (size_t)K_max + 64;
+  if (!bf) {
+    std::vector<omni::LinearWgradJob> widths;
+    for (const Layer& L : net->layers)
+      if (!L.fused_away) {
+        omni::LinearWgradJob j{};
+        j.cin = L.d.cin; j.cout = L.d.cout;
+        widths.push_back(j);
+      }
+    net->share_rows = std::min(omni::linear_wgrad_f32_share_rows(widths.data(), (int)widths.size(), K_max, B_max),
+                               kSmallScratchFloats / net->P_stride);
+    if (net->share_rows < 2) net->share_rows = 0;
     net->share_off = take(net->share_rows * net->P_stride * sizeof(float));
   }
   if (bf) {
     net->conv_counters_off = take(omni::kZeroPageWords * sizeof(uint32_t));
     net->conv_partial_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
     net->conv_partial2_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
-    net->conv_partial3_off = take(omni::conv_wgrad_partial_floats() * sizeof(float));
+    net->conv_partial3_off = take(kSmallScratchFloats * sizeof(float));
     net->shadow_off = take(net->shadow_elems * 2);
     if (in_c % 8 != 0) net->xpad_off = take((size_t)B_max * in_h * in_w * ((in_c + 7) / 8 * 8) * 2);
     if (net->bn_floats) {
@@ -857,7 +868,7 @@ void step_bf16(StepCtx& c) {
     hipStream_t side = use2 ? c.side2 : c.side;
     TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
     omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
-                           nullptr, group_work > 2 * kGroupWork ? 512 : 256);   // (leaves room for the chain at small batches)
+                           omni::conv_wgrad_partial_floats(), nullptr, group_work > 2 * kGroupWork ? 512 : 256);   // (leaves room for the chain at small batches)
     group.clear();
     group_work = 0.0;
   };
@@ -1025,8 +1036,9 @@ void step_bf16(StepCtx& c) {
   }
   if (!net->linear_only) {
     TimedScope ts(net, st, OMNI_KERNEL_CONV_WGRAD, 0);
-    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, conv_partial3,
-                           head_pending ? &head_grads : nullptr, 512);
+    // (where groups run beside it, what is left are layers on the network input, whose gradients are small)
+    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, c.forked ? conv_partial3 : conv_partial,
+                           c.forked ? kSmallScratchFloats : omni::conv_wgrad_partial_floats(), head_pending ? &head_grads : nullptr, 512);
   } else if (head_pending) {
     omni::head_wgrad_loss(st, true, head_grads, c.seg);
   }

@@ -103,3 +103,23 @@ def test_rows_of_a_weight_gradient_shared_out(dims, off, momentum):
             assert_close(got["params"][s:e], ref.params[s:e], 1e-4, f"theta' {name}")
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("dims,K,B", [([384, 384, 10], 24, 2100),    # as many shares as the scratch holds, fewer than wanted
+                                      ([64, 150, 12], 64, 2048),     # one share per worker and a few more
+                                      ([384, 384, 10], 64, 2100)])   # not even one per worker: no shares
+def test_rows_shared_out_within_the_scratch(dims, K, B):
+    off = [0] + [min(B, 1 + k + (k * (B - K)) // K) for k in range(1, K)] + [B]
+    assert all(a < c for a, c in zip(off, off[1:]))
+    layers, params, x, labels = _case(dims, off, K + B)
+    ref = oracle_step.sgd_step(layers, params, x.reshape(-1, 1, 1, dims[0]), labels, off, 0.05)
+    run = GpuRun(layers, (1, 1, dims[0]), "f32", K, B)
+    try:
+        got = run.step(params, x, labels, off, 0.05, keep_g=False)
+        assert got["status"] == 0
+        for name, s, e in param_tensor_slices(layers):
+            for k in range(K):
+                assert_close(got["worker_grads"][k, s:e], ref.worker_grads[k, s:e], 1e-4, f"g_{k} {name}", tol_max=5e-4)
+            assert_close(got["params"][s:e], ref.params[s:e], 1e-4, f"theta' {name}")
+    finally:
+        run.close()

@@ -82,3 +82,26 @@ def test_static_workspace_step_rejects_what_does_not_fit():
         assert torch.equal(params, before)
     finally:
         omni.net_destroy(net)
+
+
+@pytest.mark.parametrize("K,B", [(16, 1024), (8, 2048)])
+def test_static_workspace_step_of_a_small_network_with_many_rows(K, B):
+    import gc
+    import torch
+    import paper_2503_17469_amd as omni
+    dims = [200, 300, 100, 50]
+    layers = synth.mlp(dims)
+    rng = np.random.default_rng(B)
+    params = synth.he_normal_params(layers, 6, False)
+    x = rng.standard_normal((B, dims[0])).astype(np.float32)
+    y = rng.integers(0, dims[-1], B).astype(np.int32)
+    gc.collect()      # (tensors that an earlier test's exception holds must not be freed between the two readings below)
+    net = omni.net_create(layers, (1, 1, dims[0]), "f32", K, B)
+    try:
+        ws = torch.zeros(omni.net_workspace_bytes(net), dtype=torch.uint8, device="cuda")
+        off = [B * k // K for k in range(K + 1)]
+        (p0, l0, t0), (p1, l1, t1) = _both(omni, torch, net, ws, params, x, y, off, 0.05, K)
+        assert np.array_equal(p0, p1) and np.array_equal(l0, l1) and t0 == t1
+        assert not np.array_equal(p1, params)
+    finally:
+        omni.net_destroy(net)
