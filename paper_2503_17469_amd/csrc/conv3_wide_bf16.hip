@@ -32,6 +32,7 @@
 #include <algorithm>
 
 #include "bf16.h"
+#include "bn_sums_device.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -83,23 +84,6 @@ constexpr int OC = KC / 8;        // 16-byte pieces per patch position and per w
 constexpr int KK = KC / 16;       // reduction steps per tap
 static_assert(kTN * OC == kThreads, "one weight piece per thread and tap");
 
-// One step of the statistics tree: the lane keeps half of its list (the upper half if bit DIST of its index
-// is set) and adds what its partner, DIST lanes away, holds of the same half.
-template <int DIST, int N, int LEN>
-__device__ inline void stat_exchange(float (&sv)[LEN], int j) {
-  if constexpr (LEN >= 2 * N) {
-    const bool upper = (j & DIST) != 0;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float keep = upper ? sv[N + i] : sv[i];
-      const float send = upper ? sv[i] : sv[N + i];
-      // ds_swizzle in bit-mask mode (groups of 32 lanes): the value comes from lane ^ DIST
-      const float recv = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), (DIST << 10) | 0x1F));
-      sv[i] = keep + recv;
-    }
-  }
-}
-
 // MA: 32-position blocks per wavefront: 4 (a unit of 512 positions, one workgroup per compute unit) or 2 (256
 // positions, two workgroups per compute unit, whose load, store and compute phases overlap each other's).
 // STATS (MA = 2, no bias, no ReLU): the per-channel sums of the group's stored outputs and of their squares go to
@@ -119,7 +103,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
   const int npatch = p.nimg * PR * PW;
   bf16_t* sP = reinterpret_cast<bf16_t*>(smemW);          // [npatch][kRow]
   bf16_t* sW = sP + (size_t)npatch * kRow;                // [9][64][kRow]
-  float* sN = reinterpret_cast<float*>(sW + 9 * kTN * kRow);   // STATS and BWD: [64][2]
+  float* sN = reinterpret_cast<float*>(sW + 9 * kTN * kRow);   // STATS and BWD: [64] means, [64] factors
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 31, h = lane >> 5;
   const int tiles_n = (p.N + kTN - 1) / kTN;
@@ -214,12 +198,12 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
     }
   };
 
-  if (STATS && BWD && tid < 2 * kTN) sN[tid] = p.stat_norm[((size_t)gk * p.N + col0) * 2 + tid];
+  if (STATS && BWD && tid < 2 * kTN) sN[(tid & 1) * kTN + (tid >> 1)] = p.stat_norm[((size_t)gk * p.N + col0) * 2 + tid];
   load_slice(ubeg, 0);
   store_slice();
   __syncthreads();
 
-  double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's two (channel, moment) pairs over the group's units, see below
+  double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's sum of a channel of either half tile over the group's units
 
   for (int unit = ubeg; unit < uend; ++unit) {
     int n0, r0, nvalid;
@@ -241,9 +225,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
     // both block rows are fetched when the loop has ended and the other workgroup's matrix instructions cover the
     // wait; with the mask as bits a set is 18 registers instead of 32 and the first one does travel under the
     // last taps (except on 8-wide maps, where the seventh patch piece takes the room).
-    constexpr int ESETS = 2;
-    u32x4 em[ESETS][BWD && !BITS ? 4 : 1], ea[ESETS][BWD ? 4 : 1];
-    u32x2 eb[ESETS];   // BITS: the mask bits of the tile's 64 channels at this lane's position (byte b*4 + q*2 + h: piece (b, q))
+    u32x4 em[2][BWD && !BITS ? 4 : 1], ea[2][BWD ? 4 : 1];
+    u32x2 eb[2];   // BITS: the mask bits of the tile's 64 channels at this lane's position (byte b*4 + q*2 + h: piece (b, q))
     auto load_epi = [&](int a, int set) {
       if (BITS) {
         const bool in = ipos[a] < npos;
@@ -353,117 +336,89 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
           xs[a][STATS && BWD ? i : 0] = *reinterpret_cast<const u32x4*>(
               ipos[a] < npos ? p.stat_x + ((size_t)(out_base + ipos[a]) * p.N + col0 + i * 16 + h * 8) : zp);
     }
-    // STATS: sv[which*32 + (b*2+q)*8 + e]: sums over this lane's positions of the stored values (which = 0) and
-    // of their squares (1)
-    float sv[STATS ? 64 : 1];
-    if (STATS) {
+    // piece by piece: with MA = 2 a run of channels (b, q) over both block rows (with STATS only its 16 sums are then live), with
+    // MA = 4 block row by block row, as the mask and the addend arrive
+    double t[2][8], first = 0.0;
 #pragma unroll
-      for (int i = 0; i < 64; ++i) sv[STATS ? i : 0] = 0.f;
-    }
+    for (int x = 0; x < 4 * MA; ++x) {
+      const int a = MA == 2 ? x % 2 : x / 4, bq = MA == 2 ? x / 2 : x % 4, b = bq >> 1, q = bq & 1;
+      if (BWD && MA == 4 && bq == 0 && a + 1 < MA) load_epi(a + 1, (a + 1) & 1);
+      if (STATS && a == 0) {
 #pragma unroll
-    for (int a = 0; a < MA; ++a) {
-      const bool row_in = ipos[a] < npos;
-      const size_t row = (size_t)(out_base + ipos[a]) * p.N;
-      if (BWD && MA == 4 && a + 1 < MA) load_epi(a + 1, (a + 1) & 1);
-      if (BWD && ESETS == 1 && a > 0) load_epi(a, 0);
+        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
+      }
+      float val[8];
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int e = 0; e < 4; ++e) {
+        const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][b][8 * q + e]),
+                                                          __float_as_uint(acc[a][b][8 * q + 4 + e]), false, false);
+        val[e] = __uint_as_float(sw[0]);
+        val[4 + e] = __uint_as_float(sw[1]);
+      }
+      const int c = col0 + b * 32 + q * 16 + h * 8;
+      if (ipos[a] < npos && c < p.N) {   // N is a multiple of 8: a piece is wholly inside or outside
+        if (AFFINE && p.bias) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          float val[8];
+          for (int e = 0; e < 8; ++e) val[e] += bias8[AFFINE ? b * 2 + q : 0][e];
+        }
+        if (AFFINE && p.relu) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][b][8 * q + e]),
-                                                              __float_as_uint(acc[a][b][8 * q + 4 + e]), false, false);
-            val[e] = __uint_as_float(sw[0]);
-            val[4 + e] = __uint_as_float(sw[1]);
+          for (int e = 0; e < 8; ++e) val[e] = val[e] > 0.f ? val[e] : 0.f;
+        }
+        if (BWD) {
+          const u32x4 mk = em[a & 1][BITS ? 0 : b * 2 + q], ad = ea[a & 1][b * 2 + q];
+          if (p.addend) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
           }
-          const int c = col0 + b * 32 + q * 16 + h * 8;
-          if (!row_in || c >= p.N) continue;   // N is a multiple of 8: a piece is wholly inside or outside
-          if (AFFINE && p.bias) {
+          if (BITS) {
+            const uint32_t byte = eb[a & 1][b] >> (8 * (2 * q + h));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) val[e] += bias8[AFFINE ? b * 2 + q : 0][e];
-          }
-          if (AFFINE && p.relu) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) val[e] = val[e] > 0.f ? val[e] : 0.f;
-          }
-          if (BWD) {
-            const u32x4 mk = em[a & (ESETS - 1)][BITS ? 0 : b * 2 + q], ad = ea[a & (ESETS - 1)][b * 2 + q];
-            if (p.addend) {
-#pragma unroll
-              for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
-            }
-            if (BITS) {
-              const uint32_t byte = eb[a & (ESETS - 1)][b] >> (8 * (2 * q + h));
-#pragma unroll
-              for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
-            } else if (p.mask) {
-#pragma unroll
-              for (int d = 0; d < 4; ++d) {
-                val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
-                val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
-              }
-            }
-            if (p.accumulate) {
-#pragma unroll
-              for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
-            }
-          }
-          if (!STATS) {
-            Piece<bf16_t>::store(p.out + row + c, val);
-          } else {
-            u32x4 t;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) t[d] = pack_bf16(val[2 * d], val[2 * d + 1]);
-            *reinterpret_cast<u32x4*>(p.out + row + c) = t;
+            for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
+          } else if (p.mask) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-              const float lo = bf16_lo(t[d]), hi = bf16_hi(t[d]);   // the values as stored
-              const int i = (b * 2 + q) * 8 + 2 * d;
-              sv[STATS ? i : 0] += lo;
-              sv[STATS ? i + 1 : 0] += hi;
-              float lo2 = lo, hi2 = hi;
-              if (BWD) {
-                const v4f nm = *reinterpret_cast<const v4f*>(sN + (b * 32 + q * 16 + h * 8 + 2 * d) * 2);
-                const uint32_t xw = xs[a][STATS && BWD ? b * 2 + q : 0][d];
-                lo2 = (bf16_lo(xw) - nm[0]) * nm[1];
-                hi2 = (bf16_hi(xw) - nm[2]) * nm[3];
-              }
-              sv[STATS ? 32 + i : 0] = fmaf(lo, lo2, sv[STATS ? 32 + i : 0]);
-              sv[STATS ? 32 + i + 1 : 0] = fmaf(hi, hi2, sv[STATS ? 32 + i + 1 : 0]);
+              val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
+              val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
             }
           }
+          if (p.accumulate) {
+#pragma unroll
+            for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+          }
         }
-    }
-    if (STATS) {
-      // The 32 lanes of a half hold 64 sums each over different positions.  Five exchange steps (lane distance
-      // 16, 8, 4, 2, 1): a lane keeps one half of its list and adds the partner's copy of that half, so the list
-      // halves while the positions covered double: a fixed tree, 62 additions instead of 320 for 64 separate
-      // reductions.  Lane j ends with entries 2 j' and 2 j' + 1, j' = its bits in the order they were used:
-      // which = bit 4 of j, b = bit 3, q = bit 2, e = 4 * bit 1 + 2 * bit 0 (+ 1 for the second entry).
-      stat_exchange<16, 32>(sv, j);
-      stat_exchange<8, 16>(sv, j);
-      stat_exchange<4, 8>(sv, j);
-      stat_exchange<2, 4>(sv, j);
-      stat_exchange<1, 2>(sv, j);
-      stat_sum[0] += (double)sv[0];
-      stat_sum[1] += (double)sv[STATS ? 1 : 0];
+        u32x4 stored;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(val[2 * d], val[2 * d + 1]);
+        *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + ipos[a]) * p.N + c) = stored;
+        if (STATS && BWD) {
+          v4f mean[2];
+#pragma unroll
+          for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h * 8 + 4 * d);
+          bn_sums_add(t, stored, xs[a][STATS && BWD ? bq : 0], mean);
+        } else if (STATS) {
+          bn_sums_add(t, stored);
+        }
+      }
+      if (STATS && a == MA - 1) {
+        const double sum = bn_sums_tree(t, j);
+        if (q == 0) first = sum;
+        else stat_sum[b] += bn_sums_pair(first, sum, j);
+      }
     }
   }
   if (STATS) {
     // the four wavefronts' sums meet in LDS (nobody reads patch or weights any more), added in wavefront order
     double* red = reinterpret_cast<double*>(smemW);   // [4][2][64]
-    const int which = (j >> 4) & 1;
-    const int ch = ((j >> 3) & 1) * 32 + ((j >> 2) & 1) * 16 + h * 8 + ((j >> 1) & 1) * 4 + (j & 1) * 2;
-    red[(wave * 2 + which) * 64 + ch] = stat_sum[0];
-    red[(wave * 2 + which) * 64 + ch + 1] = stat_sum[1];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) red[(wave * 2 + bn_sums_which(j)) * 64 + b * 32 + bn_sums_channel(j, h)] = stat_sum[b];
     __syncthreads();
     if (tid < 128) {
       const int c = tid & 63, w = tid >> 6;
       const double tot = ((red[(0 * 2 + w) * 64 + c] + red[(1 * 2 + w) * 64 + c]) + red[(2 * 2 + w) * 64 + c]) +
                          red[(3 * 2 + w) * 64 + c];
-      if (col0 + c < p.N) p.stat_partial[((size_t)group * p.N + col0 + c) * 2 + w] = tot;
+      const double factor = BWD && w == 1 ? (double)sN[kTN + c] : 1.0;
+      if (col0 + c < p.N) p.stat_partial[((size_t)group * p.N + col0 + c) * 2 + w] = tot * factor;
     }
   }
 }

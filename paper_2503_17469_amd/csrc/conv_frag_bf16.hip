@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "bf16.h"
+#include "bn_sums_device.h"
 #include "common.h"
 #include "kernels.h"
 #include "pool_device.h"
@@ -66,20 +67,6 @@ struct FragParams {
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// One step of the statistics tree (see conv3_wide_bf16.hip): the lane keeps half of its list and adds what its
-// partner, DIST lanes away, holds of the same half.
-template <int DIST, int N, int LEN>
-__device__ inline void stat_exchange(float (&sv)[LEN], int j) {
-  const bool upper = (j & DIST) != 0;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const float keep = upper ? sv[N + i] : sv[i];
-    const float send = upper ? sv[i] : sv[N + i];
-    const float recv = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), (DIST << 10) | 0x1F));
-    sv[i] = keep + recv;
-  }
-}
-
 // The end of a tile: the partial tiles meet in LDS and each wavefront finishes one 32 x 32 block of it.  out_pos, pos_in: where this
 // lane's position 32 (wave / 2) + lane % 32 of the tile goes, and whether it exists; npos, out_base (pooling): the tile's
 // positions and the first one's place.
@@ -97,15 +84,18 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
   const size_t row = out_pos * p.N + cb;
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
   u32x4 em[2], ea4[2], ex4[2];
-  v4f norm[2][4];                                  // BWD with statistics: (mean, 1/sqrt(var)) of this lane's channels
+  v4f mean[2][2];                                  // BWD with statistics: of this lane's channels
   uint32_t ebits = 0;
   if (BWD && p.stat_partial) {
 #pragma unroll
     for (int qq = 0; qq < 2; ++qq) {
       ex4[qq] = *reinterpret_cast<const u32x4*>(row_in ? p.stat_x + row + qq * 16 + h * 8 : zp);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        norm[qq][i] = *reinterpret_cast<const v4f*>(p.stat_norm + ((size_t)gk * p.N + cb + qq * 16 + h * 8) * 2 + 4 * i);
+      for (int i = 0; i < 4; ++i) {
+        const v4f n = *reinterpret_cast<const v4f*>(p.stat_norm + ((size_t)gk * p.N + cb + qq * 16 + h * 8) * 2 + 4 * i);
+        mean[qq][i >> 1][2 * (i & 1)] = n[0];
+        mean[qq][i >> 1][2 * (i & 1) + 1] = n[2];
+      }
     }
   }
   if (BWD) {
@@ -193,37 +183,28 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
   }
 
   if (p.stat_partial) {
-    // sums of the stored values and of their squares (BWD: of the values times xhat): fp32 over the 32 positions of a block (a fixed tree, entry
-    // which*16 + q*8 + e ends in lane j with bits which, q, e from the top), double over the two blocks
-    float sv[32];
+    // sums of the stored values and of their squares (BWD: see bn_sums_add) over the 32 positions of a block, then over the
+    // two blocks
+    double half[2];
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const float lo = row_in ? bf16_lo(outp[qq][d]) : 0.f, hi = row_in ? bf16_hi(outp[qq][d]) : 0.f;
-        sv[qq * 8 + 2 * d] = lo;
-        sv[qq * 8 + 2 * d + 1] = hi;
-        if (BWD) {
-          sv[16 + qq * 8 + 2 * d] = lo * ((bf16_lo(ex4[qq][d]) - norm[qq][d][0]) * norm[qq][d][1]);
-          sv[16 + qq * 8 + 2 * d + 1] = hi * ((bf16_hi(ex4[qq][d]) - norm[qq][d][2]) * norm[qq][d][3]);
-        } else {
-          sv[16 + qq * 8 + 2 * d] = lo * lo;
-          sv[16 + qq * 8 + 2 * d + 1] = hi * hi;
-        }
+    for (int qq = 0; qq < 2; ++qq) {
+      double t[2][8] = {};
+      if (row_in) {
+        if (BWD) bn_sums_add(t, outp[qq], ex4[qq], mean[qq]);
+        else bn_sums_add(t, outp[qq]);
       }
-    stat_exchange<16, 16>(sv, j);
-    stat_exchange<8, 8>(sv, j);
-    stat_exchange<4, 4>(sv, j);
-    stat_exchange<2, 2>(sv, j);
-    stat_exchange<1, 1>(sv, j);
+      half[qq] = bn_sums_tree(t, j);
+    }
+    const double sum = bn_sums_pair(half[0], half[1], j);
     __syncthreads();                               // the partial tiles have been read
-    float* const red = ex;                         // [position block][which][64]
-    red[(ea * 2 + (j >> 4)) * 64 + eb * 32 + ((j >> 3) & 1) * 16 + h * 8 + (j & 7)] = sv[0];
+    double* const red = reinterpret_cast<double*>(smemF);   // [position block][which][64]
+    red[(ea * 2 + bn_sums_which(j)) * 64 + eb * 32 + bn_sums_channel(j, h)] = sum;
     __syncthreads();
     if (tid < 128 && col0 + (tid & 63) < p.N) {
       const int c = tid & 63, which = tid >> 6;
-      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] =
-          (double)red[which * 64 + c] + (double)red[(2 + which) * 64 + c];
+      const double sum = red[which * 64 + c] + red[(2 + which) * 64 + c];
+      const double factor = BWD && which == 1 ? (double)p.stat_norm[((size_t)gk * p.N + col0 + c) * 2 + 1] : 1.0;
+      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] = sum * factor;
     }
   }
   if (!BWD && p.pool) {

@@ -1,0 +1,124 @@
+"""The sums a batch norm takes over its positions, when the convolution beside it takes them in its epilogue: double precision,
+in both directions, in the kernels for few positions and for many.  Everything is compared with the same sums, in float64, over
+the values the library itself stored, so nothing but the sums can differ."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import layers as OL
+from gpu_util import GpuRun
+
+pytestmark = pytest.mark.gpu
+
+EPS = 1e-5
+
+
+def _conv(src, c, k=3):
+    return dict(op="conv", src=src, cin=c, cout=c, k=k, stride=1, pad=k // 2, bias=False)
+
+
+def _tail(src, c):
+    return [dict(op="gap", src=src), dict(op="linear", src=src + 1, cin=c, cout=10, bias=True)]
+
+
+def _cuts(B):
+    return [0, 1, 1 + B // 3, B]
+
+
+def _per_worker(off):
+    return [slice(off[k], off[k + 1]) for k in range(len(off) - 1)]
+
+
+# images: few take the kernel that splits the reduction (64 positions a tile), many the wide one (256)
+@pytest.mark.parametrize("hw,B,k", [(4, 37, 3), (8, 13, 3), (8, 21, 1), (16, 7, 3), (32, 5, 3), (8, 600, 3), (16, 150, 3), (32, 40, 3)])
+def test_forward_statistics_of_channels_far_from_zero(hw, B, k):
+    """Means of 100 to 400 deviations: the variance is a small difference of the sums."""
+    C = 64
+    layers = [_conv(-1, C, k), dict(op="bn", src=0, c=C)] + _tail(1, C)
+    rng = np.random.default_rng(hw * 1000 + B)
+    params = synth.he_normal_params(layers, 3, True)
+    sl = synth.param_slices(layers)
+    w = np.zeros((C, k, k, C), dtype=np.float32)      # the middle tap only: no edges, whose values would spread the channel
+    w[:, k // 2, k // 2, :] = rng.uniform(0.2, 1.0, (C, C))
+    params[sl[0]["w"][0]:sl[0]["w"][1]] = synth.to_bf16_grid(w.reshape(-1))
+    params[sl[1]["gamma"][0]:sl[1]["gamma"][1]] = 1.0
+    params[sl[1]["beta"][0]:sl[1]["beta"][1]] = 0.0
+    off = _cuts(B)
+    x = synth.to_bf16_grid((1.0 + 0.02 * rng.standard_normal((B, hw, hw, C))).astype(np.float32))
+    y = rng.integers(0, 10, B).astype(np.int32)
+    run = GpuRun(layers, (hw, hw, C), "bf16", len(off) - 1, B)
+    try:
+        assert run.step(params, x, y, off, 0.0)["status"] == 0
+        conv = run.activation(0, B).astype(np.float64).reshape(B, hw * hw, C)
+        out = run.activation(1, B).astype(np.float64).reshape(B, hw * hw, C)
+    finally:
+        run.close()
+    ratio = 0.0
+    for rows in _per_worker(off):
+        v = conv[rows].reshape(-1, C)
+        mean, var = v.mean(0), v.var(0)
+        inv = 1.0 / np.sqrt(var + EPS)
+        xhat = (v - mean) * inv
+        # the mean as stored in fp32 (2^-24 of it), the difference, the factor and the product in fp32 (2^-24 each), all
+        # doubled; what is stored is a value in that interval, rounded to bf16
+        slack = 2.0 ** -23 * (np.abs(mean) * inv + 8 * np.abs(xhat))
+        got = out[rows].reshape(-1, C)
+        outside = ((got < OL.round_bf16(xhat - slack)) | (got > OL.round_bf16(xhat + slack))).mean()
+        assert outside == 0.0, (rows, outside)
+        ratio = max(ratio, float((np.abs(mean) * inv).max()))
+    assert ratio > 100       # (the case is what it claims to be)
+
+
+@pytest.mark.parametrize("hw,B", [(4, 37), (8, 21), (16, 7), (32, 5), (8, 600), (16, 150), (32, 40)])
+def test_backward_sums(hw, B):
+    """dbeta = sum of dy, dgamma = 1 / deviation times the sum of dy (x - mean), whose terms are fp32 differences and products:
+    reproduced term by term."""
+    C = 64
+    layers = [_conv(-1, C), dict(op="bn", src=0, c=C), dict(op="relu", src=1), _conv(2, C), dict(op="bn", src=3, c=C),
+              dict(op="relu", src=4)] + _tail(5, C)
+    _check_backward(layers, (hw, hw, C), B, [1])
+
+
+@pytest.mark.parametrize("hw,B", [(8, 21), (16, 6), (32, 5)])
+def test_backward_sums_below_a_block_entry(hw, B):
+    """... from the kernel of the stride-2 convolutions' input gradient."""
+    C = 64
+    layers = [_conv(-1, C), dict(op="bn", src=0, c=C), dict(op="relu", src=1),
+              dict(op="conv", src=2, cin=C, cout=C, k=3, stride=2, pad=1, bias=False), dict(op="bn", src=3, c=C),
+              dict(op="conv", src=2, cin=C, cout=C, k=1, stride=2, pad=0, bias=False), dict(op="bn", src=5, c=C),
+              dict(op="add", src=4, src2=6), dict(op="relu", src=7)] + _tail(8, C)
+    _check_backward(layers, (hw, hw, C), B, [1])
+
+
+def _check_backward(layers, shape, B, bns):
+    import paper_2503_17469_amd as omni
+    rng = np.random.default_rng(shape[0] * 100 + B)
+    params = synth.he_normal_params(layers, 5, True)
+    off = _cuts(B)
+    x = synth.to_bf16_grid(rng.standard_normal((B,) + shape).astype(np.float32))
+    y = rng.integers(0, 10, B).astype(np.int32)
+    run = GpuRun(layers, shape, "bf16", len(off) - 1, B)
+    try:
+        got = run.step(params, x, y, off, 0.0)
+        assert got["status"] == 0
+        for bn in bns:
+            C = layers[bn]["c"]
+            xin = run.activation(layers[bn]["src"], B).reshape(B, -1, C)
+            dy = omni.net_activation_grad(run.net, run.ws, bn, B, "bf16").float().cpu().numpy().reshape(B, -1, C)
+            sl = synth.param_slices(layers)[bn]
+            for k, rows in enumerate(_per_worker(off)):
+                v, d = xin[rows].reshape(-1, C), dy[rows].reshape(-1, C)
+                mean = v.mean(0, dtype=np.float64)
+                var = (v.astype(np.float64) ** 2).mean(0) - mean ** 2
+                mu, inv = mean.astype(np.float32), (1.0 / np.sqrt(np.maximum(var, 0) + EPS)).astype(np.float32)
+                terms = (d * (v - mu)).astype(np.float64) * inv
+                assert np.abs(d).max() > 0
+                for name, t in (("beta", d.astype(np.float64)), ("gamma", terms)):
+                    s, e = sl[name]
+                    exact = t.sum(0)
+                    # the rounding of the result to fp32, twice (the factor may be one unit of fp32 off); double sums in any order
+                    bound = 2.0 ** -23 * np.abs(exact) + 1e-12 * np.abs(t).sum(0)
+                    err = np.abs(got["worker_grads"][k, s:e].astype(np.float64) - exact)
+                    assert np.all(err <= bound), (bn, name, k, float((err / bound).max()), float((err > bound).mean()))
+    finally:
+        run.close()
