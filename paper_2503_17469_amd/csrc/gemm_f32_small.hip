@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
   const bool want_bias = J.gb != nullptr && tile_n == 0;
 
   // A chunk that would run past the end of its worker's rows is moved back to end there; rows that are not its own are
-  // zeroed in one operand.  Every address is then a uniform base plus a lane offset that never changes.
+  // zeroed in both operands (they may be another worker's: 0 * infinity is no zero).  Every address is then a uniform base plus a lane offset that never changes.
   constexpr int kSuper = 16 * NW;
   const int wrow = NW == 1 ? 0 : 16 * wave;
   const int last_row = seg.off[seg.K] - 1;
@@ -500,7 +500,12 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
       if (__builtin_expect(k + wrow + 16 > end, 0)) {
         const int ks = start(k, end), lo = k + wrow - ks, hi = end - ks;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) c[d].a[s] = 4 * s + g >= lo && 4 * s + g < hi ? c[d].a[s] : 0.f;
+        for (int s = 0; s < 4; ++s) {
+          const bool own = 4 * s + g >= lo && 4 * s + g < hi;
+          c[d].a[s] = own ? c[d].a[s] : 0.f;
+#pragma unroll
+          for (int j = 0; j < WB; ++j) c[d].b[s][j] = own ? c[d].b[s][j] : 0.f;
+        }
       }
       if (want_bias) bsum += (c[d].a[0] + c[d].a[1]) + (c[d].a[2] + c[d].a[3]);
 #pragma unroll
