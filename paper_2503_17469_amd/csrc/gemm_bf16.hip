@@ -62,7 +62,7 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
   uint32_t* lb = la + T * kLineWords;
 
   // rows past the end shadow the last ones (their results are not stored); a piece past the end of a row shadows its last
-  // piece and counts zero in A
+  // piece and counts zero, in both operands (0 * infinity is no zero)
   const bf16_t* a0 = p.A + (size_t)row0 * K;
   const bf16_t* b0 = p.B + (size_t)col0 * K;
   uint32_t aoff[NL], boff[NL];
@@ -89,13 +89,16 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   auto stage = [&](int d, int ch) {
-    const bool beyond = ch * kLine + lp * 8 >= K;
+    if (__builtin_expect((ch + 1) * kLine > K, 0)) {
+      const bool beyond = ch * kLine + lp * 8 >= K;
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      u32x4 t = ga[d][i];
-      if (beyond) t = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(la + (lrow + 8 * i) * kLineWords + lp * 4) = t;
+      for (int i = 0; i < NL; ++i) {
+        ga[d][i] = beyond ? u32x4{0u, 0u, 0u, 0u} : ga[d][i];
+        gb[d][i] = beyond ? u32x4{0u, 0u, 0u, 0u} : gb[d][i];
+      }
     }
+#pragma unroll
+    for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(la + (lrow + 8 * i) * kLineWords + lp * 4) = ga[d][i];
 #pragma unroll
     for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(lb + (lrow + 8 * i) * kLineWords + lp * 4) = gb[d][i];
   };

@@ -111,7 +111,7 @@ __device__ __forceinline__ void cols_load(SmallCols<WB>& c, const float* base, u
     for (int q = 0; q < 4; ++q) load_n<WB>(base + (size_t)(16 * s + q) * N + off, c.v[s][q]);
 }
 // reduction elements below `lo` count zero (the last chunk of a row is moved back to end at K: what the chunk before
-// it covers is not counted again)
+// it covers is not counted again), in both operands: 0 * infinity is no zero
 template <int WB>
 __device__ __forceinline__ void frag_clear_below(SmallFrag<WB>& f, int lo, int g) {
 #pragma unroll
@@ -120,6 +120,16 @@ __device__ __forceinline__ void frag_clear_below(SmallFrag<WB>& f, int lo, int g
     for (int q = 0; q < 4; ++q)
 #pragma unroll
       for (int i = 0; i < WB; ++i) f.v[i][s][q] = 16 * s + 4 * g + q < lo ? 0.f : f.v[i][s][q];
+}
+
+template <int WB>
+__device__ __forceinline__ void cols_clear_below(SmallCols<WB>& c, int lo, int g) {
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < WB; ++j) c.v[s][q][j] = 16 * s + 4 * g + q < lo ? 0.f : c.v[s][q][j];
 }
 
 template <bool DGRAD, int WB, int NW>
@@ -198,7 +208,11 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
         frag_load<WB>(fa, la, r, g);
         if constexpr (!DGRAD) frag_load<WB>(fb, lb, r, g);
         const int lo = ch * kChunk - start(ch);
-        if (lo > 0) frag_clear_below<WB>(fa, lo, g);
+        if (lo > 0) {
+          frag_clear_below<WB>(fa, lo, g);
+          if constexpr (DGRAD) cols_clear_below<WB>(gc[d], lo, g);
+          else frag_clear_below<WB>(fb, lo, g);
+        }
       };
       int ch = cb;
       for (; ch + D <= ce; ch += D) {
@@ -230,9 +244,16 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
         for (int i = 0; i < WB; ++i) {
           const float t = p.A[(size_t)min(row0 + 16 * i + r, M - 1) * K + ko];
           fa.v[i][s][q] = in ? t : 0.f;
-          if constexpr (!DGRAD) fb.v[i][s][q] = p.B[(size_t)min(col0 + 16 * i + r, N - 1) * K + ko];
+          if constexpr (!DGRAD) {
+            const float u = p.B[(size_t)min(col0 + 16 * i + r, N - 1) * K + ko];
+            fb.v[i][s][q] = in ? u : 0.f;
+          }
         }
-        if constexpr (DGRAD) load_n<WB>(p.B + (size_t)ko * N + min(col0 + WB * r, N - WB), fc.v[s][q]);
+        if constexpr (DGRAD) {
+          load_n<WB>(p.B + (size_t)ko * N + min(col0 + WB * r, N - WB), fc.v[s][q]);
+#pragma unroll
+          for (int j = 0; j < WB; ++j) fc.v[s][q][j] = in ? fc.v[s][q][j] : 0.f;
+        }
       }
     mma(fa, fb, fc);
   }

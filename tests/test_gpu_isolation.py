@@ -1,5 +1,5 @@
 """A worker's rows have no part in another worker's gradient, loss or statistics: with one worker's inputs not finite, everybody
-else's come out as they do without it, bit for bit."""
+else's come out as they do without it, bit for bit.  Also a weight that is infinite stays an infinity in what it feeds."""
 import numpy as np
 import pytest
 
@@ -68,3 +68,28 @@ def test_convolutions(hw, chans, off, bad, value):
 @pytest.mark.parametrize("off,bad", [([0, 3, 4, 11], 1), ([0, 40, 75, 130], 1)])
 def test_residual_network(off, bad):
     _isolated(synth.resnet18(num_classes=10, cin=3), (32, 32, 3), "bf16", off, bad, np.nan, off[-1])
+
+
+@pytest.mark.parametrize("dtype,dims,at", [("f32", [40, 48, 10], 31), ("f32", [20, 24, 10], 0), ("bf16", [72, 104, 10], 69)])
+def test_an_infinite_weight_gives_infinities(dtype, dims, at):
+    """Widths off the kernels' chunks: what a chunk holds a second time, or in the place of what lies past a row's end (element
+    `at` among it), counts zero in both operands."""
+    layers = synth.mlp(dims)
+    B = 19
+    params = synth.he_normal_params(layers, 4, dtype == "bf16")
+    sl = synth.param_slices(layers)[0]["w"]
+    w = params[sl[0]:sl[1]].reshape(dims[1], dims[0])
+    w[5, :] = 0.0
+    w[5, at] = np.inf
+    x = np.abs(np.random.default_rng(3).standard_normal((B, dims[0]))).astype(np.float32) + 0.5
+    if dtype == "bf16":
+        x = synth.to_bf16_grid(x)
+    y = np.zeros(B, dtype=np.int32)
+    run = GpuRun(layers, (1, 1, dims[0]), dtype, 2, B)
+    try:
+        run.step(params, x, y, [0, 7, B], 0.0, keep_g=False)
+        hidden = run.activation(0, B)
+    finally:
+        run.close()
+    assert np.all(np.isposinf(hidden[:, 5])), hidden[:3, 5]
+    assert np.all(np.isfinite(np.delete(hidden, 5, axis=1)))
