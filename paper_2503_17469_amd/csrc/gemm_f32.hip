@@ -221,9 +221,8 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     }                                                     \
   }
 
-  // Two accumulator chains (even / odd reduction steps) keep consecutive MFMAs independent.  WGRAD runs four
-  // wavefronts per SIMD, which hide the dependence, and uses the second set of registers for gsum.
-  constexpr bool kTwo = MODE != MODE_WGRAD;
+  // A slab's sum (acc) and the range's (acc2), to which the slab's is added when it is complete: chains of BK products and one
+  // of slabs.  Against float64 the error is a third of that of two chains over a reduction of 3072, half over 1000.
   v16f acc, acc2;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = acc2[v] = 0.f;
@@ -242,7 +241,9 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   const int ibase = row0 + wrow + 4 * (lane >> 5);
 
   // Two register sets hold the slabs one and two steps ahead of the one being
-  // multiplied, so every global load has two MFMA sections to arrive in.
+  // multiplied, so every global load has two MFMA sections to arrive in.  WGRAD has the registers for one set only
+  // (four wavefronts per SIMD: 128); a load has one section, and the other wavefronts', to arrive in.
+  constexpr bool kOneSet = MODE == MODE_WGRAD;
   const typename SA::Pre preA = SA::prepare(p.lda, row0, p.M, tid);
   const typename SB::Pre preB = SB::prepare(p.ldb, col0, p.N, tid);
   v4f ra0[SA::kPerThread], rb0[SB::kPerThread], ra1[SA::kPerThread], rb1[SB::kPerThread];
@@ -255,8 +256,10 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   if (w1 >= nrange) { k01 = 0; kend1 = 0; }
   SA::load_fast(ra0, p.A, p.lda, OMNI_KSTART(k00, kend0), preA);
   SB::load_fast(rb0, p.B, p.ldb, OMNI_KSTART(k00, kend0), preB);
-  SA::load_fast(ra1, p.A, p.lda, OMNI_KSTART(k01, kend1), preA);
-  SB::load_fast(rb1, p.B, p.ldb, OMNI_KSTART(k01, kend1), preB);
+  if (!kOneSet) {
+    SA::load_fast(ra1, p.A, p.lda, OMNI_KSTART(k01, kend1), preA);
+    SB::load_fast(rb1, p.B, p.ldb, OMNI_KSTART(k01, kend1), preB);
+  }
 #pragma unroll
   for (int i = 0; i < SA::kPerThread; ++i) SA::store_fast(ra0, sA(0), tid, i);
 #pragma unroll
@@ -282,7 +285,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     }                                                                                                   \
     if (w2 >= nrange) { k02 = 0; kend2 = 0; }                                                           \
     {                                                                                                   \
-      const int ks2 = OMNI_KSTART(k02, kend2);                                                          \
+      const int ks2 = kOneSet ? OMNI_KSTART(k01, kend1) : OMNI_KSTART(k02, kend2);                      \
       SA::load_fast(LA, p.A, p.lda, ks2, preA);                                                         \
       SB::load_fast(LB, p.B, p.ldb, ks2, preB);                                                         \
     }                                                                                                   \
@@ -299,17 +302,20 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
           fa[(ks + 1) & 1] = SA::frag(sA(CUR), wrow, ks + 1, lane);                                     \
           fb[(ks + 1) & 1] = SB::frag(sB(CUR), wcol, ks + 1, lane);                                     \
         }                                                                                               \
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][0], fb[ks & 1][0], acc, 0, 0, 0);         \
-        if (kTwo) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][1], fb[ks & 1][1], acc2, 0, 0, 0); \
-        else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][1], fb[ks & 1][1], acc, 0, 0, 0);    \
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][2], fb[ks & 1][2], acc, 0, 0, 0);         \
-        if (kTwo) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][3], fb[ks & 1][3], acc2, 0, 0, 0); \
-        else acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][3], fb[ks & 1][3], acc, 0, 0, 0);    \
-        if (ks < SA::kPerThread) SA::store_fast(NA, sA(1 - CUR), tid, ks);                              \
+        _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                 \
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks & 1][q], fb[ks & 1][q], acc, 0, 0, 0);       \
+        }                                                                                               \
+        if (kOneSet) {                                                                                  \
+        } else if (ks < SA::kPerThread) SA::store_fast(NA, sA(1 - CUR), tid, ks);                       \
         else if (ks - SA::kPerThread < SB::kPerThread) SB::store_fast(NB, sB(1 - CUR), tid, ks - SA::kPerThread); \
         __builtin_amdgcn_sched_barrier(0);                                                              \
       }                                                                                                 \
     }                                                                                                   \
+    if (kOneSet) {                                                                                      \
+      _Pragma("unroll") for (int i = 0; i < SA::kPerThread; ++i) SA::store_fast(LA, sA(1 - CUR), tid, i); \
+      _Pragma("unroll") for (int i = 0; i < SB::kPerThread; ++i) SB::store_fast(LB, sB(1 - CUR), tid, i); \
+    }                                                                                                   \
+    _Pragma("unroll") for (int v = 0; v < 16; ++v) { acc2[v] += acc[v]; acc[v] = 0.f; }                 \
     if (w1 < nrange && k01 + BK > kend1) {                                                              \
       /* the slab just staged runs past the end of its range: it was fetched moved back; clear the */  \
       /* reduction steps that are not its own (once per range; all its pieces must have landed)     */  \
@@ -333,7 +339,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
       float* tile = sA(CUR);                                                                            \
       __syncthreads(); /* every wavefront is done reading this stage */                                 \
       _Pragma("unroll") for (int v = 0; v < 16; ++v)                                                    \
-        tile[(wrow + 4 * (lane >> 5) + 8 * (v / 4) + (v % 4)) * kFlushStride + wcol + (lane & 31)] = acc[v]; \
+        tile[(wrow + 4 * (lane >> 5) + 8 * (v / 4) + (v % 4)) * kFlushStride + wcol + (lane & 31)] = acc2[v]; \
       if (want_bias_grad) bred[wave][lane] = bsum;                                                      \
       __syncthreads();                                                                                  \
       _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                                   \
@@ -349,7 +355,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
         if (UPD) bgsum += lam->v[w0] * t;                                                               \
       }                                                                                                 \
       bsum = 0.f;                                                                                       \
-      _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[v] = 0.f;                                      \
+      _Pragma("unroll") for (int v = 0; v < 16; ++v) acc2[v] = 0.f;                                     \
     }                                                                                                   \
     if (w1 >= nrange) break;                                                                            \
     __syncthreads();                                                                                    \
@@ -357,8 +363,13 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
     w1 = w2; k01 = k02; kend1 = kend2;                                                                  \
   }
   for (;;) {
-    OMNI_STEP(0, ra0, rb0, ra1, rb1)
-    OMNI_STEP(1, ra1, rb1, ra0, rb0)
+    if (kOneSet) {
+      OMNI_STEP(0, ra0, rb0, ra0, rb0)
+      OMNI_STEP(1, ra0, rb0, ra0, rb0)
+    } else {
+      OMNI_STEP(0, ra0, rb0, ra1, rb1)
+      OMNI_STEP(1, ra1, rb1, ra0, rb0)
+    }
   }
 #undef OMNI_STEP
 #undef OMNI_NEXT_SLAB
@@ -399,7 +410,7 @@ __device__ __forceinline__ void gemm_f32_body(const GemmParams& p, const Segment
   }
   if (MODE != MODE_WGRAD) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] += acc2[v];
+    for (int v = 0; v < 16; ++v) acc[v] = acc2[v];
     // dgrad: the column that sits at this lane's place in the tile; of a piece moved back, the columns that an
     // earlier piece also holds are left to that one
     const int jt = wcol + (lane & 31);

@@ -161,13 +161,19 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
   }
   const uint32_t coff = (uint32_t)(4 * g) * (uint32_t)N + (uint32_t)min(col0 + WB * r, N - WB);   // dgrad
 
-  v4f acc[2][WB][WB];
+  // Every D chunks are summed by themselves and then added: short chains.  (One chain over a whole reduction had up to 1.8
+  // times the error against float64 of the two chains of gemm_f32.hip.)  One block: two accumulators in turn, so that
+  // consecutive instructions do not depend on each other.
+  constexpr int kChains = WB == 1 ? 2 : 1;
+  v4f sum[kChains][WB][WB], acc[WB][WB];
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int i = 0; i < WB; ++i)
 #pragma unroll
-    for (int i = 0; i < WB; ++i)
+    for (int j = 0; j < WB; ++j) {
 #pragma unroll
-      for (int j = 0; j < WB; ++j) acc[s][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+      for (int ch = 0; ch < kChains; ++ch) sum[ch][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+      acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
   auto mma = [&](const SmallFrag<WB>& a, const SmallFrag<WB>& b, const SmallCols<WB>& c) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -177,10 +183,19 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
         for (int i = 0; i < WB; ++i)
 #pragma unroll
           for (int j = 0; j < WB; ++j) {
-            // one block: two accumulators in turn, so that consecutive instructions do not depend on each other
-            v4f& d = acc[WB == 1 ? s : 0][i][j];
-            d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][s][q], DGRAD ? c.v[s][q][j] : b.v[j][s][q], d, 0, 0, 0);
+            v4f& t = sum[q % kChains][i][j];
+            t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][s][q], DGRAD ? c.v[s][q][j] : b.v[j][s][q], t, 0, 0, 0);
           }
+  };
+  auto settle = [&]() {
+#pragma unroll
+    for (int i = 0; i < WB; ++i)
+#pragma unroll
+      for (int j = 0; j < WB; ++j) {
+        acc[i][j] += WB == 1 ? sum[0][i][j] + sum[kChains - 1][i][j] : sum[0][i][j];
+#pragma unroll
+        for (int ch = 0; ch < kChains; ++ch) sum[ch][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
   };
 
   const int nc = (K + kChunk - 1) / kChunk;
@@ -223,6 +238,7 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
           if constexpr (DGRAD) cols_load<WB>(gc[d], b0 + (size_t)start(ch + d + D) * N, coff, N);
           __builtin_amdgcn_sched_barrier(0);   // the loads stay in this order, so that a wait is for the oldest only
         }
+        settle();
       }
       for (int d = 0; ch + d < ce; ++d) {   // (D = 2: at most one)
         stage(0, ch + d);
@@ -258,6 +274,7 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
     mma(fa, fb, fc);
   }
 
+  settle();
   // accumulator register v of lane (r, g): row 4 g + v of its block, column r
 #pragma unroll
   for (int i = 0; i < WB; ++i)
@@ -265,8 +282,7 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
     for (int j = 0; j < WB; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float t = WB == 1 ? acc[0][i][j][v] + acc[1][i][j][v] : acc[0][i][j][v];
-        la[(16 * i + 4 * g + v) * T + (DGRAD ? WB * r + j : 16 * j + r)] = t;
+        la[(16 * i + 4 * g + v) * T + (DGRAD ? WB * r + j : 16 * j + r)] = acc[i][j][v];
       }
   __syncthreads();
 #pragma unroll
@@ -294,14 +310,14 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
 }
 
 template <bool DGRAD, int WB, int NW>
-__global__ __launch_bounds__(64 * NW) void small_gemm_kernel(SmallGemm p) {
+__global__ __launch_bounds__(64 * NW, 3) void small_gemm_kernel(SmallGemm p) {
   __shared__ __attribute__((aligned(16))) float lds[small_gemm_floats<DGRAD, WB, NW>()];
   small_gemm_body<DGRAD, WB, NW>(p, (int)blockIdx.x, lds);
 }
 
 // An input gradient and, in front of its tiles, the classifier's parameter gradients and losses.
 template <int WB>
-__global__ __launch_bounds__(256) void small_dgrad_head_kernel(SmallGemm p, HeadRole head, Segments seg) {
+__global__ __launch_bounds__(256, 3) void small_dgrad_head_kernel(SmallGemm p, HeadRole head, Segments seg) {
   constexpr int kGemm = small_gemm_floats<true, WB, 4>();
   __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
   const int b = (int)blockIdx.x;
@@ -350,7 +366,7 @@ struct WgradChunk {
 // per four matrix instructions, 128 matrix cycles) it stays out of the way; 16 x 16 and 32 x 32 tiles with 4- and 8-byte
 // loads took twice the time (997-501-243-37 net, 333 rows, 7 workers: 18.6 and 18.2 us).
 template <int WB, int NW, int UPD, bool SHARES>
-__global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments seg, Lambdas lam, Optim opt,
+__global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segments seg, Lambdas lam, Optim opt,
                                                           HeadLossParams hl, SmallShares sh) {
   static_assert(!SHARES || (NW == 4 && UPD == 0), "shares: four wavefronts, no update");
   constexpr int TN = 16 * WB, D = 4;
@@ -412,17 +428,28 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
       load_n<WB>(xk + boff[s], c.b[s]);
     }
   };
-  constexpr int kChains = WB == 1 ? 2 : 1;   // one block: two accumulators in turn, so that no instruction waits for the last
-  v4f acc[kChains][WB];
+  // A chunk is summed by itself and added while the next one is multiplied, as above (one chain over a worker's rows had up to 3
+  // times the error of the two of gemm_f32.hip).  One block: two accumulators in turn, so that no instruction waits for the last.
+  constexpr int kChains = WB == 1 ? 2 : 1;
+  v4f sum[2][kChains][WB], acc[WB];   // (chunks in turn)
   float bsum = 0.f, bgsum = 0.f, gsum[WB][4], own[kOwn];
   auto clear = [&]() {
     bsum = 0.f;
 #pragma unroll
-    for (int ch = 0; ch < kChains; ++ch)
-#pragma unroll
-      for (int j = 0; j < WB; ++j) acc[ch][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < WB; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
   };
-  auto value = [&](int j, int v) { return WB == 1 ? acc[0][j][v] + acc[kChains - 1][j][v] : acc[0][j][v]; };
+  auto settle = [&](int set) {
+#pragma unroll
+    for (int j = 0; j < WB; ++j) {
+      acc[j] += WB == 1 ? sum[set][0][j] + sum[set][kChains - 1][j] : sum[set][0][j];
+#pragma unroll
+      for (int ch = 0; ch < kChains; ++ch) sum[set][ch][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+#pragma unroll
+  for (int ch = 0; ch < kChains; ++ch)
+#pragma unroll
+    for (int j = 0; j < WB; ++j) sum[0][ch][j] = sum[1][ch][j] = v4f{0.f, 0.f, 0.f, 0.f};
   clear();
 #pragma unroll
   for (int j = 0; j < WB; ++j)
@@ -442,6 +469,8 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
 
   // the worker's rows are done: its tile goes out
   auto flush = [&](int w) {
+    settle(0);
+    settle(1);
     const int dst = SHARES ? share : w;
     float* G = J.gw + (size_t)dst * p.worker_stride;
     const float l = UPD ? lam.v[w] : 0.f;
@@ -456,7 +485,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
         float t[WB];
 #pragma unroll
         for (int j = 0; j < WB; ++j) {
-          t[j] = value(j, v);
+          t[j] = acc[j][v];
           if (UPD) gsum[j][v] += l * t[j];
         }
         if (row < M) store_n<WB>(G + (size_t)row * N + js, t);
@@ -471,7 +500,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
       for (int v = 0; v < 4; ++v) {
         float t[WB];
 #pragma unroll
-        for (int j = 0; j < WB; ++j) t[j] = value(j, v);
+        for (int j = 0; j < WB; ++j) t[j] = acc[j][v];
         store_n<WB>(&red[wave][(4 * g + v) * TN + WB * r], t);
       }
       if (want_bias && g == 0) red[wave][kTileFloats + r] = bsum;
@@ -533,10 +562,11 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(SmallWgrad p, Segments
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int j = 0; j < WB; ++j) {
-          v4f& a = acc[WB == 1 ? s & 1 : 0][j];
+          v4f& a = sum[d & 1][s % kChains][j];
           a = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d].a[s], c[d].b[s][j], a, 0, 0, 0);
         }
       load(c[d], lk, lend);
+      settle((d + 1) & 1);
       __builtin_amdgcn_sched_barrier(0);
       k += kSuper;
       if (__builtin_expect(k >= end, 0)) {

@@ -173,9 +173,12 @@ __device__ __forceinline__ void head_wgrad_columns_body(const HeadWgradParams& h
   __syncthreads();
   if (tid < 16 * JC) {
     const int c = tid / JC, jj = tid % JC;
-    float t = 0.f;
-#pragma unroll 16
-    for (int r = 0; r < RS; ++r) t += red[r][c][jj];
+    float part[4] = {0.f, 0.f, 0.f, 0.f};   // (four short chains: smaller rounding errors, and the reads need not wait for each other)
+#pragma unroll 4
+    for (int r = 0; r < RS; r += 4)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[q] += red[r + q][c][jj];
+    const float t = (part[0] + part[1]) + (part[2] + part[3]);
     if (c < nc && jc * JC + jj < cin)
       gw[(size_t)wk * worker_stride + (size_t)(c0 + c) * cin + jc * JC + jj] = t;
   }
@@ -186,9 +189,10 @@ __device__ __forceinline__ void head_wgrad_columns_body(const HeadWgradParams& h
     r2[(tid >> 4) * 16 + (tid & 15)] = bsum;
     __syncthreads();
     if (tid < 16 && tid < nc) {
-      float u = 0.f;
-      for (int r = 0; r < 16; ++r) u += r2[r * 16 + tid];
-      gb[(size_t)wk * worker_stride + c0 + tid] = u;
+      float u[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 16; ++r) u[r & 3] += r2[r * 16 + tid];
+      gb[(size_t)wk * worker_stride + c0 + tid] = (u[0] + u[1]) + (u[2] + u[3]);
     }
   }
 }
