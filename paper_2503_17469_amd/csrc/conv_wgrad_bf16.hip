@@ -1253,7 +1253,7 @@ struct BatchPlan {
   int light[kBatchJobs], lights;   // places in plans
   int member[kBatchJobs];          // ... of the jobs of tab
   int blocks, rblocks;
-  size_t lds, scratch_each;
+  size_t lds, scratch[kBatchJobs];
 };
 
 void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_stride, const Segments& seg, float* partial,
@@ -1271,14 +1271,25 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
   }
   // Layers that share the launch share its workgroups in proportion to the time their units take (not
   // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
-  const size_t budget = std::min(floats, conv_wgrad_partial_floats()) / m;
-  bp.scratch_each = budget / 4 * 4;
+  // The scratch is shared out in proportion to what that many partial tiles take, in whole 256-byte lines (tiles that began
+  // inside a line cost the three-layer net's step 6 per cent).
+  const double room = (double)std::min(floats, conv_wgrad_partial_floats());
+  long aim[kBatchJobs];
+  double wanted = 0.0;
+  for (int i = 0; i < m; ++i) {
+    const Plan& pl = bp.plans[i];
+    aim[i] = pl.job.kind == kFirst || heavy == 1 ? pl.alone : std::max<long>(1, (long)(workgroups * pl.work / work));
+    wanted += (double)std::max<long>(aim[i], pl.job.tiles) * pl.slot_floats;
+  }
+  size_t scratch = 0;
   for (int i = 0; i < m; ++i) {
     Plan& pl = bp.plans[i];
     const bool light = pl.job.kind == kFirst;
-    const long aim = light || heavy == 1 ? pl.alone : std::max<long>(1, (long)(workgroups * pl.work / work));
-    cut_chunks(pl, seg, aim, budget);
-    set_partial(pl.job, partial + bp.scratch_each * i);
+    const size_t budget = (size_t)(room * (double)std::max<long>(aim[i], pl.job.tiles) * pl.slot_floats / wanted) / 64 * 64;
+    cut_chunks(pl, seg, aim[i], budget);
+    set_partial(pl.job, partial + scratch);
+    bp.scratch[i] = scratch;
+    scratch += budget;
     pl.job.first_block = bp.blocks;
     pl.job.first_reduce = bp.rblocks;
     bool chunked = false;
@@ -1377,7 +1388,7 @@ void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, i
         if (bp.member[l] == i) o.launch = o.launch < 0 && bp.tab.job[l].kind != kFirst ? shared : -2;
       o.workgroups = job.tiles * job.chunk[seg.K];
       for (int k = 0; k < seg.K; ++k) o.reduced = o.reduced || job.chunk[k + 1] - job.chunk[k] > 1;
-      o.scratch_begin = bp.scratch_each * i;
+      o.scratch_begin = bp.scratch[i];
       o.scratch_end = o.scratch_begin + (o.reduced ? (size_t)o.workgroups * bp.plans[i].slot_floats : 0);
     }
     launch += bp.lights;

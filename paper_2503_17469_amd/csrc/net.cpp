@@ -855,7 +855,10 @@ void step_bf16(StepCtx& c) {
   // chain has ended runs on the main stream.  A group is worth a fork (event calls: about 12 us of host time, 3 us of the
   // main stream) from kGroupWork on: 50 us or so of an otherwise idle chip.  Small networks never reach it.
   constexpr double kGroupWork = 40e9;
-  constexpr int kGroupJobs = 6;
+  // It is cut into 768 workgroups: fewer walk longer (with 256, the sums of a layer's gradient at 128 images had up to twice the
+  // error against float64 that a launch per layer gives, 4e-7 of the gradient; with 768 up to 1.3 times), more park more partial
+  // tiles (1024: 1.9 per cent of a step of 128 images).
+  constexpr int kGroupJobs = 6, kGroupWorkgroups = 768;
   bool second = false;
   std::vector<omni::ConvWgradJob> group;
   double group_work = 0.0;
@@ -868,7 +871,7 @@ void step_bf16(StepCtx& c) {
     hipStream_t side = use2 ? c.side2 : c.side;
     TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
     omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
-                           omni::conv_wgrad_partial_floats(), nullptr, group_work > 2 * kGroupWork ? 512 : 256);   // (leaves room for the chain at small batches)
+                           omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups);
     group.clear();
     group_work = 0.0;
   };
