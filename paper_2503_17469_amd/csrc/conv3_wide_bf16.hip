@@ -35,6 +35,7 @@
 #include "bn_sums_device.h"
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace omni {
 
@@ -45,7 +46,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kTN = 64;           // output channels per workgroup
-constexpr int kLdsLimit = 160 * 1024;
 
 struct WideParams {
   const bf16_t* src;   // [rows][H][W][Cs]
@@ -425,12 +425,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
 
 template <int MA, int NP, bool W8, bool BWD, bool STATS, bool BITS>
 void launch_variant(hipStream_t st, const WideParams& p, dim3 grid, size_t lds) {
-  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
-  const void* fn = reinterpret_cast<const void*>(&conv3_wide_kernel<MA, NP, W8, BWD, STATS, BITS>);
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv3_wide_kernel<MA, NP, W8, BWD, STATS, BITS>), kLdsOfComputeUnit);
   hipLaunchKernelGGL((conv3_wide_kernel<MA, NP, W8, BWD, STATS, BITS>), grid, dim3(kThreads), lds, st, p);
 }
 
@@ -483,7 +479,7 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
     if (!unit_shape(H, W, 128 * cand, r, n)) continue;
     const int np_ = n * (r + 2) * (W + 2);
     const size_t l = ((size_t)np_ + 9 * kTN) * kRow * sizeof(bf16_t);   // patch + the nine taps' weights of a slice
-    if (l + 2 * kTN * sizeof(float) > (size_t)kLdsLimit / (cand == 2 ? 2 : 1)) continue;
+    if (l + 2 * kTN * sizeof(float) > kLdsOfComputeUnit / (cand == 2 ? 2 : 1)) continue;
     ma = cand; R = r; nimg = n; npatch = np_; lds = l;
     break;
   }

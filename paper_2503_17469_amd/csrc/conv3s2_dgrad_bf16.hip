@@ -25,6 +25,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace omni {
 
@@ -330,12 +331,8 @@ bool conv3s2_dgrad_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int 
   const int groups = (units + upw - 1) / upw;
   const dim3 grid(((groups + 7) / 8) * 8 * tiles_n);
   const size_t lds = ((size_t)npatch + 9 * kTN) * kRow * sizeof(bf16_t);
-  static size_t configured = 0;
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv3s2_dgrad_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv3s2_dgrad_kernel), kLdsOfComputeUnit);
   hipLaunchKernelGGL(conv3s2_dgrad_kernel, grid, dim3(kThreads), lds, st, p);
   return true;
 }

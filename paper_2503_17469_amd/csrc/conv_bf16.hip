@@ -46,6 +46,7 @@
 #include "common.h"
 #include "conv_device.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "pool_device.h"
 
 namespace omni {
@@ -891,12 +892,8 @@ static void launch_gemm2(hipStream_t st, const ConvParams& p, int tiles) {
   constexpr int BN = 64 * TN;
   constexpr size_t kBytes =
       (size_t)2 * (BM + BN) * (BK2 + 8) * sizeof(bf16_t) + (MODE != GEN ? 0 : kMaxPieces * sizeof(int));
-  static bool configured = false;   // raising the dynamic LDS limit is a per-function, one-time host call
-  if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_gemm2_kernel<TN, MODE>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBytes);
-    configured = true;
-  }
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv_gemm2_kernel<TN, MODE>), kBytes);
   hipLaunchKernelGGL((conv_gemm2_kernel<TN, MODE>), dim3(tiles), dim3(kThreads), kBytes, st, p);
 }
 
@@ -945,15 +942,10 @@ static bool conv3_gemm(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf1
   p.units = units; p.upw = upw;
   const dim3 grid(((units + upw - 1) / upw) * tiles_n);
   const bool w8 = W == 8 && R % 8 == 0;
-  static size_t configured[2][2][2][2] = {};   // raising the dynamic LDS limit is a per-function host call
 #define OMNI_CONV3(NP_, NB_, KC_, W8_)                                                                \
   {                                                                                                   \
-    size_t& conf = configured[big][NB_ - 1][KC_ == 64 ? 0 : 1][W8_ ? 1 : 0];                          \
-    if (lds > conf) {                                                                                 \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv3_gemm_kernel<NP_, NB_, KC_, W8_>), \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                \
-      conf = lds;                                                                                     \
-    }                                                                                                 \
+    static LdsLimit limit;                                                                            \
+    limit.raise(reinterpret_cast<const void*>(&conv3_gemm_kernel<NP_, NB_, KC_, W8_>), 80 * 1024);    \
     hipLaunchKernelGGL((conv3_gemm_kernel<NP_, NB_, KC_, W8_>), grid, dim3(kThreads), lds, st, p);    \
   }
 #define OMNI_CONV3_W8(NP_, NB_, KC_) { if (w8) OMNI_CONV3(NP_, NB_, KC_, true) else OMNI_CONV3(NP_, NB_, KC_, false) }

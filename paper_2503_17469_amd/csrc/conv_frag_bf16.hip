@@ -25,6 +25,7 @@
 #include "bn_sums_device.h"
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "pool_device.h"
 
 namespace omni {
@@ -37,7 +38,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTM = 64, kTN = 64;      // positions, output channels per workgroup
 constexpr int kBlock = 64 * 8;         // elements of a weight block: one matrix operand
-constexpr size_t kLdsLimit = 160 * 1024;
 
 struct FragParams {
   const bf16_t* src;   // [rows][Hs][Ws][Cs]
@@ -581,7 +581,7 @@ bool frag_shape(const ConvGeom& g, int N, FragShape& s) {
   s.npatch = g.ks == 1 ? kTM : s.nimg * s.PR * g.Ws;
   s.ks = g.Cs % 64 == 0 ? 4 : 2;
   s.lds = std::max((size_t)(s.npatch + 1) * (g.Cs * 2 + 16), (size_t)4 * s.ks * 4096);
-  return s.lds <= kLdsLimit;
+  return s.lds <= kLdsOfComputeUnit;
 }
 
 // The tiles: one worker's each where batch-norm sums are wanted and there is room for their records (`sets` per tile), else
@@ -611,12 +611,8 @@ void frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stat
 
 template <int KS, int TAPS, bool BWD>
 void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
-  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_frag_kernel<KS, TAPS, BWD>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv_frag_kernel<KS, TAPS, BWD>), kLdsOfComputeUnit);
   hipLaunchKernelGGL((conv_frag_kernel<KS, TAPS, BWD>), dim3(grid), dim3(kThreads), lds, st, p);
 }
 
@@ -679,7 +675,7 @@ static bool frag_s2_shape(int rows, int H, int W, int N, int Cs, ConvGeom& g, Fr
   s.PR = s.upi == 1 ? g.Hs : s.R + 1;
   s.npatch = s.nimg * s.PR * g.Ws;
   s.lds = std::max((size_t)(s.npatch + 1) * (Cs * 2 + 16), (size_t)4 * 4 * 4096);
-  return s.lds <= kLdsLimit;
+  return s.lds <= kLdsOfComputeUnit;
 }
 
 // Up to two workgroups per compute unit and class: whole steps of the ResNet-18 shape at 128, 200 and 256 images are 2.5, 2.2 and
@@ -710,12 +706,8 @@ void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int C
   frag_tiles(p, s, rows, stats, true, 4);
   const int tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
   p.by_channel = (long)N * 9 > (long)rows * g.Hs * g.Ws ? 1 : 0;
-  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
-  if (s.lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_frag_s2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)s.lds);
-    configured = s.lds;
-  }
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv_frag_s2_kernel), kLdsOfComputeUnit);
   hipLaunchKernelGGL(conv_frag_s2_kernel, dim3((tiles * tiles_n + 7) / 8 * 8 * 4), dim3(kThreads), s.lds, st, p);
 }
 

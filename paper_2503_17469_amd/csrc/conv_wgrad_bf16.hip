@@ -25,6 +25,7 @@
 #include "conv_device.h"
 #include "head_device.h"
 #include "kernels.h"
+#include "lds_limit.h"
 #include "wgrad_chunk.h"
 
 namespace omni {
@@ -737,7 +738,7 @@ __device__ inline int wgrad1_y_offset(int pos, int oct) {
   return MB == 2 ? pos * 128 + ((oct * 16) ^ ((pos & 2) << 5)) : pos * 64 + oct * 16;
 }
 __host__ __device__ inline int wgrad1_col_blocks(int cin_real) { return cin_real * 9 + 1 > 32 ? 2 : 1; }
-__host__ __device__ inline int wgrad1_stage_bytes(int mb, int cin_real) { return kG_Unit * 64 * mb + 3 * cin_real * kG_Plane; }
+__host__ __device__ constexpr int wgrad1_stage_bytes(int mb, int cin_real) { return kG_Unit * 64 * mb + 3 * cin_real * kG_Plane; }
 
 // (co, column) of accumulator register v of lane l in block (mb, nb) -> where it goes in G
 __device__ inline void wgrad1_emit(const Wgrad1Params& p, float* gw, float* gb, int mb, int nb, int v, int lane,
@@ -1308,13 +1309,12 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
 
 template <int MB, int NB, bool POOLED>
 void launch_light(hipStream_t st, const BatchJob& job, const HeadWgradParams* head, size_t lds, const Segments& seg) {
-  static size_t configured = 0;   // raising the dynamic LDS limit is a per-function host call
   if (head) lds = std::max(lds, kHeadWgradLdsFloats * sizeof(float));
-  if (lds > configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_light_kernel<MB, NB, POOLED>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    configured = lds;
-  }
+  // (its most: the channels of a layer on the network input are at most 4; __syncthreads_or takes a little static LDS too)
+  constexpr size_t kMost = std::max({(size_t)2 * wgrad1_stage_bytes(MB, 4), (size_t)4 * MB * NB * 16 * 64 * sizeof(float),
+                                     kHeadWgradLdsFloats * sizeof(float)});
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&wgrad_light_kernel<MB, NB, POOLED>), kMost);
   const dim3 hg = head ? head_wgrad_grid(head->cin, head->C, seg.K) : dim3(1, 0, 1);
   const int head_blocks = (int)(hg.x * hg.y);
   hipLaunchKernelGGL((wgrad_light_kernel<MB, NB, POOLED>), dim3(head_blocks + job.chunk[seg.K]), dim3(kThreads), lds, st, job,
@@ -1341,12 +1341,8 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
     BatchPlan bp;
     plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, floats, workgroups);
     if (bp.blocks > 0) {
-      static bool configured = false;   // raising the dynamic LDS limit is a per-function host call
-      if (!configured) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&wgrad_batch_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
-        configured = true;
-      }
+      static LdsLimit limit;
+      limit.raise(reinterpret_cast<const void*>(&wgrad_batch_kernel), 80 * 1024);
       hipLaunchKernelGGL(wgrad_batch_kernel, dim3(bp.blocks), dim3(kThreads), bp.lds, st, bp.tab, seg);
     }
     const HeadWgradParams* h = base == 0 ? head : nullptr;   // rides with the first of the light launches
