@@ -1,5 +1,5 @@
 """Binding of libomnistep.so: argument marshalling only (ctypes; the calls a training loop makes every step go through
-the _hostcall extension, which does the same in C).
+the _hostcall extension, which does the same in C, where it was built for this interpreter).
 
 Every function maps one to one onto an `omni_*` entry point of
 include/omnistep.h.  Device buffers are torch tensors used purely as owners of
@@ -126,12 +126,52 @@ def _load():
 lib = _load()
 
 
+def _padded(ctype, seq, n=0):
+    """A ctypes array of the integers with zeros behind them, as long as the library may read for any number of workers."""
+    return (ctype * max(len(seq), n, MAX_WORKERS + 1))(*[int(v) for v in seq])
+
+
+class _CtypesCalls:
+    """The calls of every step through ctypes, with the extension's arguments and results (its host work per step is about
+    a third of it)."""
+
+    @staticmethod
+    def ctl_set_throughputs(ctl, T):
+        return lib.omni_ctl_set_throughputs(ctl, _padded(C.c_uint64, T))
+
+    @staticmethod
+    def ctl_run(ctl, K):
+        b, off = _padded(C.c_int32, [], K), _padded(C.c_int32, [], K + 1)
+        return lib.omni_ctl_run(ctl, b, off) or (list(b)[:K], list(off)[:K + 1])
+
+    @staticmethod
+    def step(net, stream, params, x, labels, off, b, lr, workspace, loss_per_worker, loss, flags):
+        return lib.omni_step(net, stream, _ptr(params), _ptr(x), _ptr(labels), _padded(C.c_int32, off, len(b) + 1),
+                             _padded(C.c_int32, b), len(b), float(lr), _ptr(workspace), _ptr(loss_per_worker), _ptr(loss),
+                             flags)
+
+    @staticmethod
+    def weighted_sgd(stream, params, grads, stride, P, b, lr, shadow):
+        return lib.omni_weighted_sgd(stream, _ptr(params), _ptr(grads), stride, P, _padded(C.c_int32, b), len(b), float(lr),
+                                     _ptr(shadow))
+
+    @staticmethod
+    def weighted_sgd_momentum(stream, params, velocity, grads, stride, P, b, lr, momentum, decay, shadow):
+        return lib.omni_weighted_sgd_momentum(stream, _ptr(params), _ptr(velocity), _ptr(grads), stride, P,
+                                              _padded(C.c_int32, b), len(b), float(lr), float(momentum), float(decay),
+                                              _ptr(shadow))
+
+    @staticmethod
+    def asp_update(stream, dst, base, grad, P, lr, b_k, B, lr_scaling):
+        return lib.omni_asp_update(stream, _ptr(dst), _ptr(base), grad if isinstance(grad, int) else _ptr(grad), P, float(lr),
+                                   int(b_k), int(B), lr_scaling)
+
+
 def _load_hostcall():
     try:
         from . import _hostcall
-    except ImportError as e:
-        raise ImportError(f"_hostcall is missing or does not load ({e}): build it first "
-                          "(python -c 'import __graft_entry__ as g; g.build()')") from e
+    except ImportError:       # not built here (no Python.h), or built for another interpreter
+        return _CtypesCalls
     _hostcall.init(*[C.cast(f, C.c_void_p) for f in (
         lib.omni_ctl_set_throughputs, lib.omni_ctl_run, lib.omni_step, lib.omni_weighted_sgd,
         lib.omni_weighted_sgd_momentum, lib.omni_asp_update)])

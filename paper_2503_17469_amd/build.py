@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libomnistep.so")
-EXT = os.path.join(HERE, "_hostcall.so")
+EXT = os.path.join(HERE, "_hostcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 # Packed-fp32 VALU forms are switched off for every device compile.
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -49,7 +49,14 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
     if r.returncode != 0:
         sys.stderr.write(" ".join(cmd) + "\n" + r.stdout + r.stderr)
         raise RuntimeError("linking libomnistep.so failed")
-    cmd = [os.environ.get("CXX", "g++"), *COMMON, "-shared", "-I" + sysconfig.get_paths()["include"],
+    for f in os.listdir(HERE):                       # of another interpreter, or without its tag
+        if f.startswith("_hostcall.") and f.endswith(".so"):
+            os.remove(os.path.join(HERE, f))
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        sys.stderr.write(f"no Python.h under {include}: the calls of every step marshal their arguments through ctypes\n")
+        return LIB
+    cmd = [os.environ.get("CXX", "g++"), *COMMON, "-shared", "-I" + include,
            os.path.join(HERE, "pyext", "hostcall.cpp"), "-o", EXT]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

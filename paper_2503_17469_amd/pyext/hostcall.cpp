@@ -10,6 +10,9 @@
 #include <cstdint>
 #include <cstring>
 #include <memory>
+#include <new>
+
+#include "../../include/omnistep.h"
 
 namespace {
 
@@ -66,7 +69,9 @@ bool integer(PyObject* o, uint64_t* out) {
   return !PyErr_Occurred();
 }
 
-// A sequence of integers as a zero-padded array; short ones (every realistic worker count) stay on the stack.
+// A sequence of integers as an array with zeros behind it, up to OMNI_MAX_WORKERS + 1 entries at least: a caller's list that is
+// shorter than the number of workers the library knows of reads as zeros (which it refuses).  Short ones (every number of
+// workers) stay on the stack.
 template <typename T>
 class Array {
  public:
@@ -74,8 +79,7 @@ class Array {
     PyObject* fast = PySequence_Fast(seq, "a sequence of integers is wanted");
     if (!fast) return false;
     n_ = PySequence_Fast_GET_SIZE(fast);
-    room(n_ > at_least ? n_ : at_least);
-    bool ok = true;
+    bool ok = room(n_ > at_least ? n_ : at_least);
     for (Py_ssize_t i = 0; i < n_ && ok; ++i) {
       uint64_t v = 0;
       ok = integer(PySequence_Fast_GET_ITEM(fast, i), &v);
@@ -84,18 +88,20 @@ class Array {
     Py_DECREF(fast);
     return ok;
   }
-  void room(Py_ssize_t n) {
+  bool room(Py_ssize_t n) {
     if (n > kFixed) {
-      more_.reset(new T[n]);
+      more_.reset(new (std::nothrow) T[n]);
       p_ = more_.get();
+      if (!p_) { PyErr_NoMemory(); return false; }
     }
-    std::memset(p_, 0, (n > 0 ? n : 1) * sizeof(T));
+    std::memset(p_, 0, (n > kFixed ? n : kFixed) * sizeof(T));
+    return true;
   }
   T* data() { return p_; }
   Py_ssize_t size() const { return n_; }
 
  private:
-  static constexpr Py_ssize_t kFixed = 72;
+  static constexpr Py_ssize_t kFixed = OMNI_MAX_WORKERS + 1;
   T fixed_[kFixed];
   std::unique_ptr<T[]> more_;
   T* p_ = fixed_;
@@ -165,8 +171,7 @@ PyObject* ctl_run(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return nullptr;
   }
   Array<int32_t> b, off;
-  b.room((Py_ssize_t)K);
-  off.room((Py_ssize_t)K + 1);
+  if (!b.room((Py_ssize_t)K) || !off.room((Py_ssize_t)K + 1)) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = g_run(ctl, b.data(), off.data());
