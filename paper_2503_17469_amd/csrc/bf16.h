@@ -10,6 +10,9 @@ typedef uint16_t bf16_t;   // raw bits of a bfloat16
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// Sixteen bytes of fp32 values that start at any multiple of four bytes: global loads and stores of this
+// type are single instructions on gfx950 as well.
+typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ inline float bf16_to_f32(bf16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }

@@ -24,15 +24,6 @@ namespace {
 
 constexpr float kBnEps = 1e-5f;
 
-__device__ inline int owner_of_row(const Segments& seg, int n) {
-  int lo = 0, hi = seg.K - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (n >= seg.off[mid]) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 // Work is dealt to workgroups in proportion to the workers' sizes: worker k owns the
 // splits / chunks first[k] .. first[k+1]-1 of a ShareTable, each covering an equal share of ITS
 // positions, so ragged b_k do not leave most of the chip waiting for the largest worker.

@@ -28,11 +28,10 @@
 #include "bf16.h"
 #include "common.h"
 #include "conv_device.h"
+#include "lds_transpose_device.h"
 #include "wgrad_chunk.h"
 
 namespace omni {
-
-typedef short v4s __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -57,15 +56,6 @@ struct TrParams {
   float* partial;      // [(tile * total_chunks + chunk)][144][256]
   const void* zero;    // zeros for absent pieces
 };
-
-__device__ inline bf16x8 tr_pair(const unsigned char* lds_a, const unsigned char* lds_b) {
-  typedef __attribute__((address_space(3))) v4s lds_v4s;
-  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)lds_a);
-  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)lds_b);
-  typedef short v8s __attribute__((ext_vector_type(8)));
-  const v8s both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, both);
-}
 
 // S: stride of the forward convolution.  Bytes per patch position in LDS: 64 of data + padding such that the
 // four positions one transposing read covers (S patch positions apart) start 8 banks apart.

@@ -419,7 +419,6 @@ struct Conv3Params {
 constexpr int kUnitD = 256;
 
 __device__ inline float as_stored(float v) { return bf16_to_f32(f32_to_bf16(v)); }
-constexpr int kRowD = 64 + 8;   // elements per LDS row (144 bytes): 16-byte reads land 4 banks apart
 constexpr int kMaxPatchPieces = 13;   // 16-byte pieces of the patch per thread (up to 416 patch positions)
 
 // A workgroup walks `upw` consecutive units of one channel tile: the next unit's patch
@@ -882,10 +881,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
 }
 
 }  // namespace
-
-bool conv_shape_supported(const ConvGeom& g, long positions) {
-  return g.Cs % 8 == 0 && g.K <= kMaxPieces * 8 && g.ks >= 1 && g.ks <= 15 && positions < (1L << 24);
-}
 
 template <int TN, int MODE>
 static void launch_gemm2(hipStream_t st, const ConvParams& p, int tiles) {

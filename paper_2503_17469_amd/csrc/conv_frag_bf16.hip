@@ -618,11 +618,6 @@ void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
 
 }  // namespace
 
-bool conv_frag_supported(const ConvGeom& g, int N) {
-  FragShape s;
-  return frag_shape(g, N, s);
-}
-
 // Up to two workgroups per compute unit this kernel wins everywhere (1.1-5.5x over 16-512 images of the ResNet-18 and
 // three-layer shapes); beyond, its larger share of start-up and epilogue per tile tells, the sooner the shorter
 // the reduction.  Its rivals are weak at stride 2 (general kernel) and on 4-wide maps (units of 512 positions), and a

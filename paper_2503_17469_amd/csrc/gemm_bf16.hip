@@ -14,6 +14,7 @@
 #include "common.h"
 #include "head_device.h"
 #include "kernels.h"
+#include "lds_transpose_device.h"
 #include "update_device.h"
 #include "xcd_tiles.h"
 
@@ -21,7 +22,6 @@ namespace omni {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef short v4s __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -231,17 +231,6 @@ struct BfWgrad {
   const float* head_grad;
   BfWgradJob job[kBfJobs];
 };
-
-// Eight rows of one column of a slab: the transposing LDS read of gfx950 (sixteen lanes hand in four rows x sixteen columns,
-// 8 bytes each, and receive one column at those four rows per lane).
-__device__ inline bf16x8 tr_pair(const unsigned char* a, const unsigned char* b) {
-  typedef __attribute__((address_space(3))) v4s lds_v4s;
-  const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)a);
-  const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)b);
-  typedef short v8s __attribute__((ext_vector_type(8)));
-  const v8s both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, both);
-}
 
 // A workgroup owns a 64 x 64 tile of one layer's weights and walks through all workers' rows, 64 at a time, both operands in
 // LDS as they arrive ([row][column]); where a worker's rows end the tile goes out to G[k], and with UPD (1 SGD, 2 momentum)

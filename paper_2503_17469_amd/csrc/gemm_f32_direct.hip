@@ -299,7 +299,7 @@ bool small_batch_shape(int rows, int cols, int kred) {
 
 }  // namespace
 
-bool linear_fwd_f32_direct_supported(const float* x, const float* w, int rows, int cin, int cout) {
+static bool linear_fwd_f32_direct_supported(const float* x, const float* w, int rows, int cin, int cout) {
   return small_batch_shape(rows, cout, cin) && aligned16(x) && aligned16(w);
 }
 
@@ -313,8 +313,8 @@ bool linear_fwd_f32_direct(hipStream_t st, const float* x, const float* w, const
   return true;
 }
 
-bool linear_dgrad_f32_direct_supported(const float* dy, const float* w, const float* mask, const float* dx, int rows,
-                                       int cin, int cout) {
+static bool linear_dgrad_f32_direct_supported(const float* dy, const float* w, const float* mask, const float* dx, int rows,
+                                              int cin, int cout) {
   return small_batch_shape(rows, cin, cout) && cin % 2 == 0 && aligned16(dy) && aligned16(w) && aligned16(dx) &&
          (!mask || aligned16(mask));
 }

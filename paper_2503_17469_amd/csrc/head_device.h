@@ -30,13 +30,6 @@ __device__ inline float wave_sum(float v) {
   v += dpp_move<0x140>(v);   // row_mirror
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
-__device__ inline float wave_max(float v) {
-  v = fmaxf(v, dpp_move<0xB1>(v));
-  v = fmaxf(v, dpp_move<0x4E>(v));
-  v = fmaxf(v, dpp_move<0x141>(v));
-  v = fmaxf(v, dpp_move<0x140>(v));
-  return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
-}
 // Losses and label check, one workgroup of any number of wavefronts, one wavefront per worker:
 // L_k = mean of the worker's row losses, loss = sum_k lambda_k L_k, status bit 0 if a label lies outside [0, C).
 constexpr int kHeadLossLdsFloats = OMNI_MAX_WORKERS;

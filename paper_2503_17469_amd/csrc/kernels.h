@@ -31,11 +31,8 @@ void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const flo
                       int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
 // Small-batch variants (gemm_f32_direct.hip): same results as the two above up to
 // summation order; return false without launching when the shape does not qualify.
-bool linear_fwd_f32_direct_supported(const float* x, const float* w, int rows, int cin, int cout);
 bool linear_fwd_f32_direct(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
                            int rows, int cin, int cout, bool relu);
-bool linear_dgrad_f32_direct_supported(const float* dy, const float* w, const float* mask, const float* dx, int rows,
-                                       int cin, int cout);
 bool linear_dgrad_f32_direct(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
                              int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head,
                              const Segments& seg);
@@ -185,7 +182,6 @@ struct LinearWgradBf16Job {
 void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
                        const LinearWgradBf16Job* head, const SgdArgs* sgd, const KernelTimer* timer = nullptr);
 size_t conv_wgrad_partial_floats();
-bool conv_shape_supported(const ConvGeom& g, long positions);
 // out[M][N] = gather(src)[M][K] * wgt[N][K]^T (+bias) (ReLU) (masked where mask <= 0) (+= out)
 // With pool_out and pool_code (forward of a layer that a 2 x 2 max pooling follows): the kernels that
 // hold a whole unit of output rows in LDS also write [rows*(Hp/2)*(Wp/2)][N] = the pooling of `out`
@@ -199,8 +195,7 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
                     BnStatRequest* stats = nullptr);
 // The kernel for few positions (conv_frag_bf16.hip), on weights in operand order: blocks [N/32][taps][Cs/16] of 64 lanes x
 // 8 elements, output n % 32 and channels 8 * (lane / 32) .. + 7 of the sixteen in lane n % 32 + 32 * ((c % 16) / 8).
-// conv_frag_takes tells which launches it is for, conv_frag_supported which it could make at all.
-bool conv_frag_supported(const ConvGeom& g, int N);
+// conv_frag_takes tells which launches it is for.
 bool conv_frag_takes(const ConvGeom& g, int N);
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,

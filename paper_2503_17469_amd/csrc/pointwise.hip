@@ -115,16 +115,10 @@ __device__ inline void weighted_sgd_tail(float* params, float* velocity, const f
     float g = 0.f;
     for (int k = 0; k < K; ++k) g += lam.v[k] * grads[(size_t)k * stride + j];
     if (KEEPG) gout[j] = g;
-    float th = params[j];
-    if (MOM) {
-      const float d = g + opt.weight_decay * th;
-      const float v = opt.momentum * velocity[j] + d;
-      velocity[j] = v;
-      th = th - opt.lr * v;
-    } else {
-      th = th - opt.lr * g;
-    }
+    float th = params[j], v = MOM ? velocity[j] : 0.f;
+    apply_update<MOM>(th, v, g, opt);
     params[j] = th;
+    if (MOM) velocity[j] = v;
     if (SHADOW) shadow[j] = bf16_rne(th);
   }
 }

@@ -21,7 +21,6 @@ namespace {
 // the 4.2 M of the 3072-1024-1024 MLP.
 constexpr int kCastTile = 64;
 constexpr int kCastStride = kCastTile + 2;   // halfwords; odd in words, so a column of the tile spreads over the banks
-typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));   // parameters start anywhere
 
 // Offset of the piece of eight channels that starts at c of output n in a copy laid out as matrix operands
 // (conv_frag_bf16): blocks [n/32][tap][c/16] of 64 lanes x 8 elements.

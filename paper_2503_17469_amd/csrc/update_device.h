@@ -8,10 +8,6 @@
 
 namespace omni {
 
-// Sixteen bytes of fp32 values that start at any multiple of four bytes: global loads and stores of this
-// type are single instructions on gfx950 as well.
-typedef float v4f_a4 __attribute__((ext_vector_type(4), aligned(4)));
-
 struct Lambdas {
   float v[OMNI_MAX_WORKERS];
 };
