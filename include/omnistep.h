@@ -208,8 +208,9 @@ size_t omni_net_grad_stride(const omni_net* net);
  *
  * The step allocates no device memory and never synchronises with the device.
  * The first steps of a network create what they need on the host side and keep
- * it until omni_net_destroy: two side streams (default priority) on which the
- * parameter gradients of a bf16 network run beside the input-gradient chain, a
+ * it until omni_net_destroy: two side streams (default priority) on which groups of
+ * a large convolutional network's weight gradients run beside the input-gradient
+ * chain (the last group, and everything of other networks, runs on `stream`), a
  * few events that order them with the caller's stream, and the dynamic-LDS limit
  * of the kernels that need more than the default; later steps create nothing.
  * All work of a step has been ordered back onto `stream` when the call returns.
@@ -232,8 +233,8 @@ int omni_step(omni_net* net, void* stream, float* params, const void* x,
  * its own copy until the process ends) instead of an argument.  The call allocates nothing and
  * creates nothing (no device memory, no stream, no event: a network that has not been stepped by
  * omni_step before runs entirely on `stream`).  OMNI_ECAPACITY, with nothing launched, if
- * omni_net_workspace_bytes(net) exceeds the array: in practice fp32 networks of a few layers at small
- * batch sizes (a bf16 network's weight-gradient scratch alone is larger).  The other arguments and
+ * omni_net_workspace_bytes(net) exceeds the array: in practice fp32 networks of a few layers
+ * (a bf16 network's weight-gradient scratch alone is larger).  The other arguments and
  * errors are omni_step's.  Every call on a GPU uses that GPU's one array: calls that overlap in time
  * on the same GPU (different streams, different networks, different threads) race; serialise them.
  * The per-worker gradients, activations and the status word stay inside the array and cannot be

@@ -1,43 +1,32 @@
-// bf16 convolutions and fully connected layers as implicit GEMMs on the CDNA4
-// matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
+// Forward and input gradient of bf16 convolutions as implicit GEMMs on the CDNA4
+// matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulation), and which kernel
+// takes which layer (conv_gemm_bf16).
 //
 // These are the contractions inside the per-worker gradient of Algorithm 1
 // (procedure Train, gradient line) for the convolutional networks:
 //   forward  Y[m][co]  = sum_{u,v,ci} X[n, h*s+u-p, w*s+v-p, ci] * W[co][u][v][ci]
 //   dgrad    dX[m][ci] = sum_{u,v,co} dY[n, (h+p-u)/s, (w+p-v)/s, co] * Wt[ci][u][v][co]
-//   wgrad    G_k[co][u][v][ci] = sum over worker k's rows and all positions of
-//                                dY[m][co] * X[n, h*s+u-p, w*s+v-p, ci]
-// with channels-last activations, m = (n, h, w).  Forward and dgrad see all
-// workers' rows in one launch; wgrad writes one output per worker.
+// with channels-last activations, m = (n, h, w); both see all workers' rows in one
+// launch.  The weight gradients are in conv_wgrad_bf16.hip.
 //
-// Kernel A (forward / dgrad): 128 x (64*TN) output tile per workgroup, 4
+// Kernel A (any shape): 128 x (64*TN) output tile per workgroup, 4
 // wavefronts in a 2x2 grid, each 64 x (32*TN).  The left operand is gathered
 // on the fly (no im2col buffer): a 16-byte piece holds 8 consecutive channels of
 // one filter tap, so it is contiguous in memory.  Slabs of 64 reduction
 // elements go through LDS (double buffered, next slab prefetched to registers).
-// The output width must be a multiple of 8 (16-byte output pieces).
+// The output width must be a multiple of 8 (16-byte output pieces).  It has a mode
+// for the dgrad of stride-2 layers that multiplies only the filter taps an input
+// position can meet (a quarter of a 3x3 filter).
 //
-// Kernel B (wgrad): the reduction runs over positions m, which is the SLOW index
-// of both operands, while the matrix instruction wants 8 consecutive reduction
-// elements per lane.  Each thread therefore loads 4 consecutive positions of
-// one 8-channel piece and transposes them in registers into 8 four-position
-// words before writing LDS.  Each worker's position range is cut into equal
-// chunks, one workgroup per (tile, chunk): every workgroup does the same amount
-// of work however ragged the b_k are.  Chunks of one worker park partial tiles;
-// a second kernel adds them in chunk order (bit-reproducible, no atomics).
+// Kernel D (3x3 / pad 1 / stride 1, channels a multiple of 32): 256 positions x 64 (32 for
+// narrow layers) channels per workgroup; the input patch of the positions stays in LDS, so
+// the nine taps are row offsets into it and cost no extra global loads.
 //
-// 3x3 / pad-1 / stride-1 layers (most of a residual net) have kernels of their own
-// that keep the input patch of a block of positions resident in LDS, so the nine
-// taps cost no extra global loads, transposes or LDS stores:
-//   kernel C (wgrad, 32 channels and more): 64 x 64 channels x all nine taps per
-//     workgroup; column shifts of the patch are made in registers;
-//   kernel D (forward and dgrad, channels a multiple of 64): 256 positions x 64
-//     channels per workgroup; taps are row offsets into the patch.
-// Kernel A also has a mode for the dgrad of stride-2 layers that multiplies only
-// the filter taps an input position can meet (a quarter of a 3x3 filter).
-// The first layer (3 input channels stored as 8) has two more: kernel F (forward, the
-// filter bank in registers) and kernel G (weight gradient, (tap, channel) pairs as the
-// columns of the product).
+// Kernel F (3 input channels stored as 8, forward): the filter bank in registers.
+//
+// In files of their own: few positions (conv_frag_bf16.hip, asked first), 3x3 / stride 1 with
+// more than 32 outputs (conv3_wide_bf16.hip; kernel D has what it leaves: pooling in the
+// epilogue, narrow layers), a residual block's entry (conv3s2_dgrad_bf16.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -9,11 +9,10 @@
 //
 // What bounds them is latency: a few MFLOP per layer, so a product costs its launch, the first loads, a chain of
 // steps and the drain.  Therefore
-//   * operands go from global memory straight into registers.  Four lanes of a 16 x 16 x 4 instruction that share a
-//     row read 64 consecutive bytes of it, so a fragment load is coalesced as it is; no LDS staging and no barrier in
-//     the main loop, several chunks in flight per wavefront;
+//   * a wavefront fetches its own operands, several chunks ahead, in whole 128-byte lines, and turns them into the
+//     instruction's layout through LDS of its own (weight gradients need no turning): no barrier in the main loop;
 //   * the output is cut into 16 x 16 or 32 x 32 tiles, so that a few hundred rows already give hundreds of tiles, and
-//     the reduction of a tile is split over the 4, 8 or 16 wavefronts of its workgroup and added up in wavefront order
+//     the reduction of a tile is split over the four wavefronts of its workgroup and added up in wavefront order
 //     through LDS at the end (a split over workgroups needs a second pass through memory and a device-wide release);
 //   * rows may start at any multiple of 4 bytes (16-byte loads need no more), and a piece that would run past the end of
 //     a row is moved back to end there, so odd widths take the same instructions as even ones.

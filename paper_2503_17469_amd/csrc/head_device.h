@@ -1,6 +1,7 @@
 // Device code of the classifier head that more than one kernel uses: the wavefront
 // reductions and the body of the head's parameter-gradient kernel (a kernel of its own
-// in head.hip; one role of a merged launch in gemm_f32_direct.hip).
+// in head.hip; a role of the launches of input gradients in gemm_f32*.hip and gemm_bf16.hip
+// and of the first convolution's weight gradient in conv_wgrad_bf16.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -159,12 +159,12 @@ def test_config1_unfiltered_batch():
 
 
 def test_split_reduction_is_reproducible_and_robust_to_a_dirty_workspace():
-    """Shapes whose products split their reduction across workgroups (a few output tiles, a long
-    reduction: partial tiles parked in the workspace, the last workgroup to arrive adds them up in
-    split order).  Twenty runs must agree bit for bit -- a partial tile read before it had arrived
-    would show as a different sum -- also when the caller's workspace is overwritten with 0xFF
-    between the steps (the arrival counters live there), and the result must match the oracle."""
-    dims = [512, 1024, 128, 2048, 10]      # forward of layers 0 and 1 and the input gradient of layer 2 split 4, 8 and 16 ways
+    """Shapes with a few output tiles and a long reduction, which the wavefronts of a workgroup split
+    among them (partial tiles meet in LDS, added in wavefront order).  Twenty runs must agree bit for
+    bit -- a partial tile read before it had arrived would show as a different sum -- also when the
+    caller's workspace is overwritten with 0xFF between the steps, and the result must match the
+    oracle.  (Rows shared out through the workspace: test_gpu_mlp_shapes.py.)"""
+    dims = [512, 1024, 128, 2048, 10]
     off = [0, 5, 40, 41, 96]
     layers = synth.mlp(dims)
     rng = np.random.default_rng(5150)

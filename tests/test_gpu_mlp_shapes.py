@@ -84,7 +84,8 @@ def test_update_inside_the_weight_gradient_launch(dims, off, momentum):
                                       ([6, 16, 3], [0, 1024])])
 @pytest.mark.parametrize("momentum", [False, True])
 def test_rows_of_a_weight_gradient_shared_out(dims, off, momentum):
-    """Few weights and many rows: a worker's rows in several shares (one worker with a single row, one with three)."""
+    """Few weights and many rows: a worker's rows in several shares (one worker with a single row, one with three), whose
+    partial gradients wait in the workspace; also on a workspace that holds something else."""
     layers, params, x, labels = _case(dims, off, 9 + sum(dims))
     ref = oracle_step.sgd_step(layers, params, x.reshape(-1, 1, 1, dims[0]), labels, off, 0.05)
     run = GpuRun(layers, (1, 1, dims[0]), "f32", len(off) - 1, off[-1])
@@ -95,6 +96,7 @@ def test_rows_of_a_weight_gradient_shared_out(dims, off, momentum):
             vel = torch.zeros(params.size, device="cuda")
             omni.net_set_momentum(run.net, vel, 0.9, 0.0)     # the first step's update is the plain one
         got = run.step(params, x, labels, off, 0.05, keep_g=False)
+        run.ws.fill_(0xFF)
         again = run.step(params, x, labels, off, 0.05, keep_g=False) if not momentum else got
         assert got["status"] == 0 and np.array_equal(got["params"], again["params"])
         for name, s, e in param_tensor_slices(layers):

@@ -35,7 +35,7 @@ def test_static_workspace_step_matches_the_step_with_a_caller_workspace():
     import paper_2503_17469_amd as omni
     from oracle import step as OS
     from gpu_util import assert_close
-    # a network whose products split their reduction (partial tiles and arrival counters in the workspace)
+    # a network of a few layers whose products split their reduction over the wavefronts of a workgroup
     dims = [512, 1024, 128, 10]
     layers = synth.mlp(dims)
     rng = np.random.default_rng(31)
