@@ -164,16 +164,13 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
   // times the error against float64 of the two chains of gemm_f32.hip.)  One block: two accumulators in turn, so that
   // consecutive instructions do not depend on each other.
   constexpr int kChains = WB == 1 ? 2 : 1;
+  const v4f kZero = {0.f, 0.f, 0.f, 0.f};
   v4f sum[kChains][WB][WB], acc[WB][WB];
 #pragma unroll
   for (int i = 0; i < WB; ++i)
 #pragma unroll
-    for (int j = 0; j < WB; ++j) {
-#pragma unroll
-      for (int ch = 0; ch < kChains; ++ch) sum[ch][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-      acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
-  auto mma = [&](const SmallFrag<WB>& a, const SmallFrag<WB>& b, const SmallCols<WB>& c) {
+    for (int j = 0; j < WB; ++j) acc[i][j] = kZero;
+  auto mma = [&](const SmallFrag<WB>& a, const SmallFrag<WB>& b, const SmallCols<WB>& c, bool first) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -183,18 +180,15 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
 #pragma unroll
           for (int j = 0; j < WB; ++j) {
             v4f& t = sum[q % kChains][i][j];
-            t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][s][q], DGRAD ? c.v[s][q][j] : b.v[j][s][q], t, 0, 0, 0);
+            t = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[i][s][q], DGRAD ? c.v[s][q][j] : b.v[j][s][q],
+                                                     first && s == 0 && q < kChains ? kZero : t, 0, 0, 0);
           }
   };
   auto settle = [&]() {
 #pragma unroll
     for (int i = 0; i < WB; ++i)
 #pragma unroll
-      for (int j = 0; j < WB; ++j) {
-        acc[i][j] += WB == 1 ? sum[0][i][j] + sum[kChains - 1][i][j] : sum[0][i][j];
-#pragma unroll
-        for (int ch = 0; ch < kChains; ++ch) sum[ch][i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-      }
+      for (int j = 0; j < WB; ++j) acc[i][j] += WB == 1 ? sum[0][i][j] + sum[kChains - 1][i][j] : sum[0][i][j];
   };
 
   const int nc = (K + kChunk - 1) / kChunk;
@@ -233,7 +227,7 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           stage(d, ch + d);
-          mma(fa, fb, gc[d]);
+          mma(fa, fb, gc[d], d == 0);
           if constexpr (DGRAD) cols_load<WB>(gc[d], b0 + (size_t)start(ch + d + D) * N, coff, N);
           __builtin_amdgcn_sched_barrier(0);   // the loads stay in this order, so that a wait is for the oldest only
         }
@@ -241,7 +235,8 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
       }
       for (int d = 0; ch + d < ce; ++d) {   // (D = 2: at most one)
         stage(0, ch + d);
-        mma(fa, fb, gc[0]);
+        mma(fa, fb, gc[0], true);
+        settle();
       }
     }
   } else if (ce > cb) {
@@ -270,10 +265,10 @@ __device__ __forceinline__ void small_gemm_body(const SmallGemm& p, int block, f
           for (int j = 0; j < WB; ++j) fc.v[s][q][j] = in ? fc.v[s][q][j] : 0.f;
         }
       }
-    mma(fa, fb, fc);
+    mma(fa, fb, fc, true);
+    settle();
   }
 
-  settle();
   // accumulator register v of lane (r, g): row 4 g + v of its block, column r
 #pragma unroll
   for (int i = 0; i < WB; ++i)
@@ -437,18 +432,18 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
 #pragma unroll
     for (int j = 0; j < WB; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
   };
+  const v4f kZero = {0.f, 0.f, 0.f, 0.f};
   auto settle = [&](int set) {
 #pragma unroll
-    for (int j = 0; j < WB; ++j) {
-      acc[j] += WB == 1 ? sum[set][0][j] + sum[set][kChains - 1][j] : sum[set][0][j];
-#pragma unroll
-      for (int ch = 0; ch < kChains; ++ch) sum[set][ch][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int j = 0; j < WB; ++j) acc[j] += WB == 1 ? sum[set][0][j] + sum[set][kChains - 1][j] : sum[set][0][j];
   };
+  auto settled = [&](int set) {     // nothing in it that is still to be added
 #pragma unroll
-  for (int ch = 0; ch < kChains; ++ch)
+    for (int ch = 0; ch < kChains; ++ch)
 #pragma unroll
-    for (int j = 0; j < WB; ++j) sum[0][ch][j] = sum[1][ch][j] = v4f{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < WB; ++j) sum[set][ch][j] = kZero;
+  };
+  settled(1);
   clear();
 #pragma unroll
   for (int j = 0; j < WB; ++j)
@@ -467,9 +462,9 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   };
 
   // the worker's rows are done: its tile goes out
-  auto flush = [&](int w) {
-    settle(0);
-    settle(1);
+  auto flush = [&](int w, int set) {       // (the other set has been added already)
+    settle(set);
+    settled(set);
     const int dst = SHARES ? share : w;
     float* G = J.gw + (size_t)dst * p.worker_stride;
     const float l = UPD ? lam.v[w] : 0.f;
@@ -562,14 +557,14 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
 #pragma unroll
         for (int j = 0; j < WB; ++j) {
           v4f& a = sum[d & 1][s % kChains][j];
-          a = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d].a[s], c[d].b[s][j], a, 0, 0, 0);
+          a = __builtin_amdgcn_mfma_f32_16x16x4f32(c[d].a[s], c[d].b[s][j], s < kChains ? kZero : a, 0, 0, 0);
         }
       load(c[d], lk, lend);
       settle((d + 1) & 1);
       __builtin_amdgcn_sched_barrier(0);
       k += kSuper;
       if (__builtin_expect(k >= end, 0)) {
-        flush(w);
+        flush(w, d & 1);
         ++w;
         if (w == nwork) { more = false; break; }
         k = seg.off[w];

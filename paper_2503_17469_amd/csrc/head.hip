@@ -259,8 +259,6 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   for (int ct = wave; ct < col_tiles; ct += NW) {
     const int col = column(ct);
     v4f o[EL];
-#pragma unroll
-    for (int e = 0; e < EL; ++e) o[e] = v4f{0.f, 0.f, 0.f, 0.f};
     v4f mk[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) mk[v] = xm[v];
@@ -287,7 +285,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
         for (int e = 0; e < EL; ++e) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[t0 + t], b[e], part[e], 0, 0, 0);
       }
 #pragma unroll
-      for (int e = 0; e < EL; ++e) o[e] += part[e];
+      for (int e = 0; e < EL; ++e) o[e] = t0 == 0 ? part[e] : o[e] + part[e];
     }
     if (ct + NW < col_tiles) fetch_cols(column(ct + NW));
 #pragma unroll
