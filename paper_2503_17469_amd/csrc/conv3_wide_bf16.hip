@@ -203,6 +203,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
   store_slice();
   __syncthreads();
 
+  int h8 = h * 8;   // the first channel of this lane's runs of eight
   double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's sum of a channel of either half tile over the group's units
 
   for (int unit = ubeg; unit < uend; ++unit) {
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
       for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const int c = col0 + b * 32 + q * 16 + h * 8;
+          const int c = col0 + b * 32 + q * 16 + h8;
           const bool in = ipos[a] < npos && c < p.N;
           const size_t idx = (size_t)(out_base + ipos[a]) * p.N + c;
           if (!BITS) em[set][b * 2 + q] = *reinterpret_cast<const u32x4*>((in && p.mask) ? p.mask + idx : zp);
@@ -319,33 +320,34 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
     if (AFFINE && p.bias) {
 #pragma unroll
       for (int bq = 0; bq < 4; ++bq) {
-        const int c = min(col0 + (bq >> 1) * 32 + (bq & 1) * 16 + h * 8, p.N - 8);
+        const int c = min(col0 + (bq >> 1) * 32 + (bq & 1) * 16 + h8, p.N - 8);
         const v4f b0 = *reinterpret_cast<const v4f*>(p.bias + c), b1 = *reinterpret_cast<const v4f*>(p.bias + c + 4);
 #pragma unroll
         for (int e = 0; e < 4; ++e) { bias8[bq][e] = b0[e]; bias8[bq][4 + e] = b1[e]; }
       }
     }
+    // (64-bit offsets formed from these before the units would be kept in registers all along, and do not fit)
+    if (STATS) asm("" : "+v"(ipos[0]), "+v"(ipos[1]), "+v"(h8));
     if (BWD && MA == 2 && !(BITS && !W8 && !STATS)) load_epi(0, 0);
     if (BWD && MA == 2) load_epi(1, 1);
     u32x4 xs[MA][STATS && BWD ? 4 : 1];   // STATS and BWD: the batch norm's input at this lane's positions
-    if (STATS && BWD) {
+    auto load_x = [&](int a) {
 #pragma unroll
-      for (int a = 0; a < MA; ++a)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          xs[a][STATS && BWD ? i : 0] = *reinterpret_cast<const u32x4*>(
-              ipos[a] < npos ? p.stat_x + ((size_t)(out_base + ipos[a]) * p.N + col0 + i * 16 + h * 8) : zp);
-    }
-    // piece by piece: with MA = 2 a run of channels (b, q) over both block rows (with STATS only its 16 sums are then live), with
-    // MA = 4 block row by block row, as the mask and the addend arrive
-    double t[2][8], first = 0.0;
+      for (int i = 0; i < 4; ++i)
+        xs[a][STATS && BWD ? i : 0] = *reinterpret_cast<const u32x4*>(
+            ipos[a] < npos ? p.stat_x + ((size_t)(out_base + ipos[a]) * p.N + col0 + i * 16 + h8) : zp);
+    };
+    if (STATS && BWD) load_x(0);
+    // Block row by block row, as the mask and the addend arrive: the four pieces of a position's 128 bytes leave together.  (With
+    // the sums of a piece between its store and the next, lines went to memory in parts: 358 MB written per launch of 268.)
+    u32x4 kept[STATS ? MA : 1][STATS ? 4 : 1];   // STATS: what was stored
 #pragma unroll
     for (int x = 0; x < 4 * MA; ++x) {
-      const int a = MA == 2 ? x % 2 : x / 4, bq = MA == 2 ? x / 2 : x % 4, b = bq >> 1, q = bq & 1;
+      const int a = x / 4, bq = x % 4, b = bq >> 1, q = bq & 1;
       if (BWD && MA == 4 && bq == 0 && a + 1 < MA) load_epi(a + 1, (a + 1) & 1);
-      if (STATS && a == 0) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
+      if (STATS && BWD && x == 4) {   // (both block rows' at once would spill; with the seventh patch piece of 8-wide maps, either)
+        if (W8) load_x(0);
+        load_x(1);
       }
       float val[8];
 #pragma unroll
@@ -355,8 +357,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
         val[e] = __uint_as_float(sw[0]);
         val[4 + e] = __uint_as_float(sw[1]);
       }
-      const int c = col0 + b * 32 + q * 16 + h * 8;
-      if (ipos[a] < npos && c < p.N) {   // N is a multiple of 8: a piece is wholly inside or outside
+      const int c = col0 + b * 32 + q * 16 + h8;
+      if (ipos[a] < npos && (STATS || c < p.N)) {   // N is a multiple of 8 (STATS: of 64): a piece is wholly inside or outside
         if (AFFINE && p.bias) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) val[e] += bias8[AFFINE ? b * 2 + q : 0][e];
@@ -391,16 +393,31 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : 2) void conv3_wide_kernel(W
 #pragma unroll
         for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(val[2 * d], val[2 * d + 1]);
         *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + ipos[a]) * p.N + c) = stored;
-        if (STATS && BWD) {
-          v4f mean[2];
-#pragma unroll
-          for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h * 8 + 4 * d);
-          bn_sums_add(t, stored, xs[a][STATS && BWD ? bq : 0], mean);
-        } else if (STATS) {
-          bn_sums_add(t, stored);
-        }
+        if (STATS) kept[STATS ? a : 0][STATS ? bq : 0] = stored;
       }
-      if (STATS && a == MA - 1) {
+    }
+    // the sums, a run of channels (b, q) over both block rows at a time: only its 16 are then live
+    if (STATS) {
+      __builtin_amdgcn_sched_barrier(0);   // (conversions to double drawn up into the loop above would spill)
+      double first = 0.0;
+#pragma unroll
+      for (int bq = 0; bq < 4; ++bq) {
+        const int b = bq >> 1, q = bq & 1;
+        double t[2][8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
+#pragma unroll
+        for (int a = 0; a < MA; ++a) {
+          if (ipos[a] >= npos) continue;
+          if (BWD) {
+            v4f mean[2];
+#pragma unroll
+            for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h8 + 4 * d);
+            bn_sums_add(t, kept[STATS ? a : 0][STATS ? bq : 0], xs[a][STATS && BWD ? bq : 0], mean);
+          } else {
+            bn_sums_add(t, kept[STATS ? a : 0][STATS ? bq : 0]);
+          }
+        }
         const double sum = bn_sums_tree(t, j);
         if (q == 0) first = sum;
         else stat_sum[b] += bn_sums_pair(first, sum, j);
