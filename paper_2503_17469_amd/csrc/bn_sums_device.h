@@ -1,7 +1,7 @@
 // Per-channel sums of a batch norm's first stage in the epilogues of the convolutions (conv3_wide_bf16.hip, conv_frag_bf16.hip),
 // in double throughout as in bn_partial_kernel (bn.hip).  In fp32 over the 32 or 64 positions of a wavefront, dgamma (a sum of
 // products of either sign) was off by more than its own rounding to fp32 in a third of the channels, by 900 times that where
-// the terms nearly cancel.
+// the terms nearly cancel.  (Against sums in fp32: 1.5 per cent of a step of the ResNet-18 shape, 2048 images.)
 //
 // A lane of a wavefront's half (32 lanes, a position each, lane j) adds its positions' terms for runs of eight channels; a fixed
 // tree over the lanes follows in which a lane keeps half of its list and adds what its partner holds of the same half, so that the

@@ -622,7 +622,8 @@ void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
 // three-layer shapes); beyond, its larger share of start-up and epilogue per tile tells, the sooner the shorter
 // the reduction.  Its rivals are weak at stride 2 (general kernel) and on 4-wide maps (units of 512 positions), and a
 // reduction of 2304 still breaks even at four workgroups per compute unit (8x8x256: 22.8 us against 23.9); with 4608
-// on 4-wide maps it stays ahead (2048 images: 129 us against 145, 1.2 PFLOP/s).
+// on 4-wide maps it stays ahead (2048 images, 154.6 GFLOP: 147 us with the batch norm's sums, 1.05 PFLOP/s, against 151 without
+// them and 11 for a pass of their own).
 bool conv_frag_takes(const ConvGeom& g, int N) {
   FragShape s;
   if (!frag_shape(g, N, s)) return false;

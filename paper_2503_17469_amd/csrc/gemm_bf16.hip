@@ -41,7 +41,8 @@ struct BfGemm {
 // registers, and their partial tiles are added in wavefront order at the end.  Wavefronts share no operand data, so the main
 // loop has no barrier: a chunk of 64 reduction elements arrives in 128-byte lines (8 lanes per row) and turns into the
 // instruction's layout through wavefront-private LDS (36-word rows: conflict-free both ways).
-// Bound by LDS bandwidth: WB = 2 moves 32 KB per 16 matrix instructions of 32 cycles.
+// Bound by LDS bandwidth: WB = 2 moves 32 KB per 16 matrix instructions of 32 cycles.  1024 rows, 3072 -> 1024 -> 1024: both
+// products 23.6 us, 364 TFLOP/s.
 constexpr int kLine = 64;          // reduction elements of a chunk: 128 bytes
 constexpr int kLineWords = 36;
 
@@ -235,7 +236,8 @@ struct BfWgrad {
 // A workgroup owns a 64 x 64 tile of one layer's weights and walks through all workers' rows, 64 at a time, both operands in
 // LDS as they arrive ([row][column]); where a worker's rows end the tile goes out to G[k], and with UPD (1 SGD, 2 momentum)
 // sum_k lambda_k G[k] of the pieces a thread stores stays in its registers for the update of the tile's parameters at the
-// end.  Bound by the gradient rows it writes (K x 4 bytes per weight).
+// end.  Bound by the gradient rows it writes (K x 4 bytes per weight): 3072-1024-1024, eight workers, 1024 rows, momentum: 39.4 us
+// for 201 MB, 5.1 TB/s, which is what a large copy reaches.
 template <int UPD>
 __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segments seg, Lambdas lam, Optim opt) {
   constexpr bool MOM = UPD == 2;

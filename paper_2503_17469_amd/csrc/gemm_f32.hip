@@ -43,8 +43,9 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTile = 64;
 // Weight gradients come here with this many 64 x 64 tiles in the launch (one per compute unit), whatever the rows; fewer
-// go to gemm_f32_small.hip (its time against this kernel's: 164 tiles, 333 rows 16 / 21 us; 136 tiles, 1000 rows 31 / 39;
-// 1024 tiles, 32 rows 10.6 / 9.9, 480 rows 64 / 54).
+// go to gemm_f32_small.hip (its time against this kernel's, with the update: 136 tiles, 1000 rows 34.5 / 37.0 us; 164 tiles,
+// 333 rows 19.6 / 24.1, 2000 rows 61.5 / 66.1; 256 tiles, 64 rows 12.5 / 14.4, 333 rows 26.1 / 24.1; 1024 tiles, 32 rows
+// 22.3 / 19.2, 480 rows 71.1 / 51.1).
 constexpr long kTiledWgradTiles = 256;
 
 // Staging of one operand slab: R rows x BK reduction steps.
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_f32_dgrad_head_kernel(GemmPa
 // workgroups start while another's finish.  With the update, the workgroups behind the last tile update the
 // classifier's parameters, whose gradients an earlier launch has left in G.
 // Four workgroups per compute unit: 1024 tiles (the 3072-1024-1024 net) are then resident at once; with three, the
-// last quarter of them ran by itself, one wavefront per SIMD (61 against 53 us at 480 rows).
+// last quarter of them ran by itself, one wavefront per SIMD (15 per cent slower at 480 rows).
 constexpr int kMaxBatch = 8;
 struct WgradBatch {
   int n;

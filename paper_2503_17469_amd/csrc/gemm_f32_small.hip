@@ -358,7 +358,7 @@ struct WgradChunk {
 // The workgroup behind the last tile computes the losses.  SHARES: see SmallShares (UPD = 0; split_reduce_kernel follows).
 // The vector cache takes a load instruction of any width every 16 cycles, so with WB = 4 (one 4-byte and one 16-byte load
 // per four matrix instructions, 128 matrix cycles) it stays out of the way; 16 x 16 and 32 x 32 tiles with 4- and 8-byte
-// loads took twice the time (997-501-243-37 net, 333 rows, 7 workers: 18.6 and 18.2 us).
+// loads took twice the time.  997-501-243-37 net, 333 rows, 7 workers: 19.6 us with the update, 21.2 with momentum.
 template <int WB, int NW, int UPD, bool SHARES>
 __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segments seg, Lambdas lam, Optim opt,
                                                           HeadLossParams hl, SmallShares sh) {

@@ -853,7 +853,8 @@ void step_bf16(StepCtx& c) {
   // The weight gradients feed nothing but the update.  They are collected and set going in groups, on the side
   // streams beside the input-gradient chain, the two streams (and scratch areas) in turn; what is left when the
   // chain has ended runs on the main stream.  A group is worth a fork (event calls: about 12 us of host time, 3 us of the
-  // main stream) from kGroupWork on: 50 us or so of an otherwise idle chip.  Small networks never reach it.
+  // main stream) from kGroupWork on: 50 us or so of an otherwise idle chip.  (A net with less in all, or with
+  // fewer than kGroupJobs layers, has one group, on the main stream.)
   constexpr double kGroupWork = 40e9;
   // It is cut into 768 workgroups: fewer walk longer (with 256, the sums of a layer's gradient at 128 images had up to twice the
   // error against float64 that a launch per layer gives, 4e-7 of the gradient; with 768 up to 1.3 times), more park more partial

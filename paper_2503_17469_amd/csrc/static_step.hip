@@ -2,9 +2,8 @@
 // fixed array in the library's own device image, one copy per GPU, held until the process ends.
 //
 // Same launch plan and kernels as omni_step (the step driver is shared); what differs is where the
-// scratch memory comes from (per-worker gradient rows, split-reduction partial tiles and their arrival
-// counters, activations and their gradients, the status word) and that nothing at all is created on
-// the way: no device allocation, no stream, no event.
+// scratch memory comes from (per-worker gradient rows, row shares, activations and their gradients, the
+// status word) and that nothing at all is created on the way: no device allocation, no stream, no event.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
