@@ -15,7 +15,8 @@
 // steps are staged through LDS with register prefetch of the next slab
 // (double-buffered LDS, one barrier per slab).
 //
-// Products with too few tiles to fill the chip are those of gemm_f32_direct.hip and gemm_f32_small.hip.
+// Products with too few tiles to fill the chip are those of gemm_f32_direct.hip and gemm_f32_small.hip, the largest those of
+// gemm_f32_split.hip (all are asked first).
 //
 // wgrad gives every workgroup one output tile position and lets it walk through
 // ALL workers' row ranges one after the other, flushing the accumulator into
@@ -515,6 +516,10 @@ int gemm_tiles(int rows, int cols) { return ((rows + kTile - 1) / kTile) * ((col
 
 void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
                     int rows, int cin, int cout, bool relu) {
+  if (linear_f32_split(rows, cout, cin)) {
+    linear_fwd_f32_split(st, x, w, bias, y, rows, cin, cout, relu);
+    return;
+  }
   if (linear_fwd_f32_direct(st, x, w, bias, y, rows, cin, cout, relu)) return;
   if (linear_f32_small(rows, cout, cin)) {
     linear_fwd_f32_small(st, x, w, bias, y, rows, cin, cout, relu);
@@ -528,6 +533,11 @@ void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float*
 
 void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
                       int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg) {
+  if (linear_f32_split(rows, cin, cout)) {
+    if (head) head_wgrad_loss(st, false, *head, seg);
+    linear_dgrad_f32_split(st, dy, w, mask, dx, rows, cin, cout, accumulate);
+    return;
+  }
   if (linear_dgrad_f32_direct(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg)) return;
   if (linear_f32_small(rows, cin, cout)) {
     linear_dgrad_f32_small(st, dy, w, mask, dx, rows, cin, cout, accumulate, head, seg);
@@ -559,6 +569,10 @@ bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows) {
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
                             const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
                             const KernelTimer* timer) {
+  if (linear_wgrad_f32_split_shape(jobs, n, seg.off[seg.K])) {
+    linear_wgrad_f32_split(st, jobs, n, worker_stride, seg, head, sgd, timer);
+    return;
+  }
   const int upd = sgd ? (sgd->velocity ? 2 : 1) : 0;
   const Lambdas lam = lambdas_of(seg);
   const Optim opt = sgd ? Optim{sgd->lr, sgd->momentum, sgd->weight_decay} : Optim{0.f, 0.f, 0.f};

@@ -29,6 +29,13 @@ void linear_fwd_f32(hipStream_t st, const float* x, const float* w, const float*
 struct HeadWgradParams;
 void linear_dgrad_f32(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx,
                       int rows, int cin, int cout, bool accumulate, const HeadWgradParams* head, const Segments& seg);
+// Large products on the bf16 matrix instruction, operands in three pieces (gemm_f32_split.hip); any alignment.  The rule for
+// forward (cols = cout, kred = cin) and dgrad, and for weight gradients.
+bool linear_f32_split(int rows, int cols, int kred);
+void linear_fwd_f32_split(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows, int cin,
+                          int cout, bool relu);
+void linear_dgrad_f32_split(hipStream_t st, const float* dy, const float* w, const float* mask, float* dx, int rows, int cin,
+                            int cout, bool accumulate);
 // Small-batch variants (gemm_f32_direct.hip): same results as the two above up to
 // summation order; return false without launching when the shape does not qualify.
 bool linear_fwd_f32_direct(hipStream_t st, const float* x, const float* w, const float* bias, float* y,
@@ -70,6 +77,10 @@ bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows);
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
                             const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
                             const KernelTimer* timer = nullptr);
+bool linear_wgrad_f32_split_shape(const LinearWgradJob* jobs, int n, int rows);
+void linear_wgrad_f32_split(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
+                            const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
+                            const KernelTimer* timer);
 // Products too small or too odd for the tiled kernels (gemm_f32_small.hip); any shape and 4-byte alignment.
 bool linear_f32_small(int rows, int cols, int kred);   // the rule for forward (cols = cout) and dgrad (cols = cin)
 void linear_fwd_f32_small(hipStream_t st, const float* x, const float* w, const float* bias, float* y, int rows,

@@ -1,0 +1,149 @@
+"""Large fp32 products, which run on the bf16 matrix instruction with every operand in three pieces (128 x 128 tiles, slabs of 32
+reduction elements, weight gradients in chunks of 512 rows of a worker): edges of tiles, slabs and chunks against float64, values
+that are not finite, and rows that do not depend on other rows.
+
+Bounds.  An output is the sum of n exact products in float32, whatever the order: pieces of 16 in a matrix instruction, six
+times (at most 6 x 16 roundings), n / 32 slabs, the two shares, n / 512 chunks.  A rounding is at most u = 2^-24 of the sum of the
+absolute products, and what the six of nine products leave out is below 2^-24 of each: element by element the error is within
+(100 + n / 32 + n / 512) u of that sum.  In the 2-norm the model of test_gpu_sum_errors holds: pieces of 32 (two slabs of a share)."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import GpuRun
+from test_gpu_isolation import _isolated
+from test_gpu_sum_errors import U, _limit, _rel, _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(got, a, b, n, mask=None, bias=None):
+    """got = a b, zero where the mask is; with a bias max(a b + bias, 0) (which moves no further than its argument)"""
+    want, size = a @ b, a.abs() @ b.abs()
+    if bias is not None:
+        want, size = (want + bias).clamp(min=0), size + bias.abs()
+    if mask is not None:
+        want, size = want * mask, size * mask
+    worst = float(((got - want).abs() - (100 + n / 32 + n / 512) * U * size).max())
+    assert worst <= 0, worst
+    return _rel([(got, want)])
+
+
+@pytest.mark.parametrize("rows,cin,cout", [
+    (3329, 32, 1024),      # one slab; a row tile with one row
+    (3300, 33, 1021),      # a second slab of one element, moved back; odd widths, rows off every alignment
+    (3300, 63, 1021),
+    (3300, 64, 1021),
+    (3300, 97, 1021),      # a fourth slab
+    (3328, 1024, 1024),
+])
+def test_forward(rows, cin, cout):
+    L = _run([cin, cout, 10], [0, rows], "f32")[0]
+    err = _check(L["z"], L["x"], L["w"].T, cin, bias=L["b"])
+    assert err <= _limit(32, (cin + 63) // 64, 2)
+
+
+@pytest.mark.parametrize("rows,cin,cout", [(3329, 1024, 32), (3300, 1021, 33), (3300, 1021, 70), (3300, 1021, 129)])
+def test_input_gradients(rows, cin, cout):
+    """of the layer cin -> cout: its tiles are over the cin columns"""
+    L = _run([24, cin, cout, 10], [0, rows // 3, rows], "f32")[1]
+    err = _check(L["dx"], L["dy"], L["w"], cout, (L["x"] > 0).double())
+    assert err <= _limit(32, (cout + 63) // 64, 2)
+
+
+@pytest.mark.parametrize("cin,cout,off", [
+    (3400, 1021, [0, 1, 33, 34, 66, 400]),            # workers of one row, of a slab, of a slab and one
+    (3400, 1021, [0, 511, 1023, 1536]),               # chunks of 511, 512, and 512 + 1 rows
+    (3328, 1024, [0, 1056, 1601]),                    # three chunks, two chunks
+    (1021, 3400, [0, 250, 505]),
+])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_weight_gradients(cin, cout, off, momentum):
+    import torch
+    import paper_2503_17469_amd as omni
+    layers = synth.mlp([cin, cout, 10])
+    B, K, lr, mu, wd = off[-1], len(off) - 1, 0.05, 0.9, 5e-4
+    rng = np.random.default_rng(cin + B)
+    params = synth.he_normal_params(layers, 7, False)
+    x = rng.standard_normal((B, cin)).astype(np.float32)
+    y = rng.integers(0, 10, B).astype(np.int32)
+    run = GpuRun(layers, (1, 1, cin), "f32", K, B)
+    try:
+        vel0 = rng.standard_normal(run.P).astype(np.float32) * 0.01
+        if momentum:
+            velocity = torch.from_numpy(vel0.copy()).cuda()
+            omni.net_set_momentum(run.net, velocity, mu, wd)
+        got = run.step(params, x, y, off, lr, keep_g=False)
+        dy = omni.net_activation_grad(run.net, run.ws, 0, B, "f32").double().cpu()
+        vel = velocity.cpu().numpy() if momentum else None
+    finally:
+        run.close()
+    xt = torch.from_numpy(x).double()
+    (s, e), (bs, be) = synth.param_slices(layers)[0]["w"], synth.param_slices(layers)[0]["b"]
+    pairs = []
+    for k in range(K):
+        rows = slice(off[k], off[k + 1])
+        n = off[k + 1] - off[k]
+        gw = torch.from_numpy(got["worker_grads"][k, s:e].reshape(cout, cin)).double()
+        _check(gw, dy[rows].T, xt[rows], n)
+        pairs.append((gw, dy[rows].T @ xt[rows]))
+        gb = torch.from_numpy(got["worker_grads"][k, bs:be]).double()
+        assert float(((gb - dy[rows].sum(0)).abs() - (n / 8 + 8) * U * dy[rows].abs().sum(0)).max()) <= 0
+    longest = max(off[k + 1] - off[k] for k in range(K))
+    assert _rel(pairs) <= _limit(16, (min(longest, 512) + 31) // 32, 2 + longest // 512)
+    # the update from the gradients it wrote: sums of K terms, one rounding each, and a few more
+    lam = np.diff(off) / B
+    g = (got["worker_grads"].astype(np.float64) * lam[:, None]).sum(0)
+    th = params.astype(np.float64)
+    if momentum:
+        v = mu * vel0 + (g + wd * th)
+        assert np.abs(vel - v).max() <= (K + 6) * U * (np.abs(vel0) + np.abs(g) + np.abs(th)).max()
+        g = v
+    assert np.abs(got["params"] - (th - lr * g)).max() <= (K + 6) * U * (np.abs(th) + lr * np.abs(g)).max()
+
+
+def _forward_with(x, w, dims):
+    layers = synth.mlp(dims)
+    B = len(x)
+    params = synth.he_normal_params(layers, 4, False)
+    s, e = synth.param_slices(layers)[0]["w"]
+    params[s:e] = w.reshape(-1)
+    run = GpuRun(layers, (1, 1, dims[0]), "f32", 1, B)
+    try:
+        run.step(params, x, np.zeros(B, np.int32), [0, B], 0.0, keep_g=False)
+        return run.activation(0, B)
+    finally:
+        run.close()
+
+
+@pytest.mark.parametrize("at", [0, 17, 63, 64, 69])
+def test_infinities_and_the_largest_values(at):
+    """Column 5's weights are zero but for element `at`: infinite, then so large that it rounds to an infinite bf16 value.  What
+    is not near it keeps its bits."""
+    dims, B = [70, 1024, 10], 3329
+    rng = np.random.default_rng(at)
+    x = (np.abs(rng.standard_normal((B, dims[0]))) + 0.5).astype(np.float32)
+    w = (rng.standard_normal((dims[1], dims[0])) * 0.1).astype(np.float32)
+    w[5] = 0
+    w[5, at] = 1.0
+    plain = _forward_with(x, w, dims)
+    assert np.array_equal(plain[:, 5], x[:, at])
+    w[5, at] = np.inf
+    hidden = _forward_with(x, w, dims)
+    assert np.all(np.isposinf(hidden[:, 5]))
+    assert np.array_equal(np.delete(hidden, 5, axis=1), np.delete(plain, 5, axis=1))
+    w[5, at] = np.finfo(np.float32).max
+    x[:, at] = np.minimum(x[:, at], 1.0)
+    hidden = _forward_with(x, w, dims)
+    assert np.array_equal(hidden[:, 5], w[5, at] * x[:, at])
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("dims,off,bad", [
+    ([40, 1024, 10], [0, 1000, 1003, 3329], 1),            # forward: tiles with rows of three workers
+    ([24, 1021, 40, 10], [0, 1000, 1003, 3300], 1),        # and input gradient
+    ([3400, 1021, 10], [0, 200, 203, 500], 1),             # weight gradient
+    ([3400, 1021, 10], [0, 600, 620, 700], 0),
+])
+def test_workers_do_not_depend_on_each_other(dims, off, bad, value):
+    _isolated(synth.mlp(dims), (1, 1, dims[0]), "f32", off, bad, value, sum(dims))
