@@ -16,6 +16,7 @@
 #include "common.h"
 #include "head_device.h"
 #include "kernels.h"
+#include "lds_barrier_device.h"
 #include "update_device.h"
 
 namespace omni {
@@ -24,11 +25,16 @@ namespace {
 
 constexpr int kMaxClasses = 128;
 
-__device__ inline int owner(const Segments& seg, int s) {
-  int k = 0;
-  while (k + 1 < seg.K && s >= seg.off[k + 1]) ++k;
-  return k;
-}
+struct HeadFwdParams {
+  const void *x, *w;
+  const float* bias;
+  const int32_t* labels;
+  int cin, C, rows, K, use_mask;
+  int groups;            // of sixteen rows
+  int cols_each;         // column tiles of dx per workgroup of a group
+  float *z, *dz, *loss_rows;
+  void* dx;
+};
 // T is the storage type of the input rows, the weights and the input gradient (fp32, or bf16 with fp32 arithmetic);
 // CT = 16-class tiles, at least ceil(C / 16).  Sixteen rows per workgroup:
 //   * logits: the four wavefronts split the reduction; both operands arrive in 128-byte lines (8 lanes per row) and turn
@@ -38,6 +44,11 @@ __device__ inline int owner(const Segments& seg, int s) {
 //   * dx = dz w on the fp32 matrix instruction (dz stays fp32), a wavefront taking 16 rows x 16 pieces of columns at a time.
 // One wavefront per row with a lane reduction per class took 8.7 us for 10 classes, 13 for 37 and 34 for 100 (480 rows of
 // 1024, 333 of 243, 2048 of 512 inputs), nearly all of it waiting: for the classes' weight rows and between the lanes.
+// What is left is a chain of first accesses, so nothing the loss needs of a row is fetched where it is used: labels, biases and the
+// workers' first rows set out with the operands, the two barriers wait for LDS alone, and where rows are few, several workgroups
+// form the same logits and share out the columns of dx (480 rows of 1024, 10 classes: 8.5 -> 6.9 us a launch, back to back; a line
+// of arguments that no load has touched costs 640 cycles, a search for a row's worker in it 400 a step).  Not faster: sixteen
+// wavefronts; operands straight in the instruction's layout (half lines: +0.9 us).
 // Rows may start at any multiple of the element size (bf16: 16 bytes); a piece that would run past the end of a row is moved
 // back to end there, and elements it shares with the piece before count once.
 constexpr int kLineFloats = 36;   // a 128-byte line in LDS, padded: conflict-free writes and fragment reads
@@ -100,10 +111,11 @@ __device__ inline float row16_max(float v) {
 template <int CT> constexpr int head_waves() { return CT == 1 ? 8 : 4; }
 
 template <typename T, int CT>
-__global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_kernel(
-    const T* __restrict__ x, const T* __restrict__ w, const float* __restrict__ bias,
-    const int32_t* __restrict__ labels, int cin, int C, Segments seg, float* __restrict__ z,
-    float* __restrict__ dz, float* __restrict__ loss_rows, int use_mask, T* __restrict__ dx) {
+__global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_kernel(HeadFwdParams p, Segments seg) {
+  const T* __restrict__ x = static_cast<const T*>(p.x);
+  const T* __restrict__ w = static_cast<const T*>(p.w);
+  T* __restrict__ dx = static_cast<T*>(p.dx);
+  const int cin = p.cin, C = p.C, rows = p.rows, use_mask = p.use_mask;
   typedef HeadOps<T> Ops;
   constexpr int EL = Piece<T>::EL, kLine = 8 * EL;      // elements per 16-byte piece, per 128-byte line
   constexpr int NW = head_waves<CT>(), D = CT == 1 ? 4 : 2;
@@ -114,7 +126,13 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   __shared__ float zbuf[16][kZ];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4, lrow = lane >> 3, lp = lane & 7;
-  const int rows = seg.off[seg.K], row0 = (int)blockIdx.x * 16;
+  const int split = (int)blockIdx.x / p.groups, row0 = ((int)blockIdx.x - split * p.groups) * 16;
+  // what the loss needs of a row, on its way before anything waits: lane l has the rows of worker l begin at `first`
+  const int first = seg.off[min(lane, p.K)];
+  const int loss_row = row0 + ((tid >> 4) & 15), y = p.labels[min(loss_row, rows - 1)];
+  float bv[CT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j) bv[j] = p.bias ? p.bias[min(16 * j + r, C - 1)] : 0.f;
 
   // ---- logits
   float* la = lds + wave * kWave;
@@ -169,6 +187,20 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   if (ce > cb) {
 #pragma unroll
     for (int d = 0; d < D; ++d) fetch(d, min(cb + d, ce - 1));
+  }
+  // meanwhile the worker of each of this wavefront's four rows: as many as begin at or before it
+  int bk_own = 1;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = min(row0 + ((4 * wave) & 15) + q, rows - 1);
+    const int k = __popcll(__ballot(lane < p.K && first <= row)) - 1;
+    const int end = k + 1 < p.K ? __builtin_amdgcn_readlane(first, k + 1) : rows;
+    const int bk = end - __builtin_amdgcn_readlane(first, k);
+    bk_own = g == q ? bk : bk_own;
+  }
+  const float inv_b = 1.0f / (float)bk_own;
+  __builtin_amdgcn_sched_barrier(0);
+  if (ce > cb) {
     int ch = cb;
     for (; ch + D < ce; ch += D) {
 #pragma unroll
@@ -192,18 +224,18 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 #pragma unroll
     for (int t = 0; t < 4; ++t) wt[t] = Ops::load(w + col + (size_t)min(4 * t + g, C - 1) * cin);
   };
-  if (dx != nullptr) fetch_cols(column(wave));
+  const int ct_begin = split * p.cols_each, ct_end = min(ct_begin + p.cols_each, col_tiles);
+  if (dx != nullptr) fetch_cols(column(ct_begin + wave));
 #pragma unroll
   for (int j = 0; j < CT; ++j)
 #pragma unroll
     for (int v = 0; v < 4; ++v) la[(4 * g + v) * kZ + 16 * j + r] = acc[j][v];
-  __syncthreads();
+  lds_barrier();
 
   // ---- loss and dz: lane group tid / 16 has row tid / 16, its lanes the classes lane, lane + 16, ...
   if (tid < 256) {
     const int lr = tid >> 4, row = row0 + lr, cl = tid & 15;
-    const bool live = row < rows;
-    const int rr = live ? row : rows - 1;
+    const bool live = row < rows && split == 0;           // (the workgroups of a group have the same losses)
     float zc[CT], m = -INFINITY;
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
@@ -212,12 +244,11 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 #pragma unroll
       for (int ww = 1; ww < NW; ++ww) zc[j] += lds[ww * kWave + at];
       if (c < C) {
-        if (bias) zc[j] += bias[c];
+        zc[j] += bv[j];
         m = fmaxf(m, zc[j]);
       }
     }
     m = row16_max(m);
-    const int y = labels[rr];
     const bool bad = y < 0 || y >= C;
     float s = 0.f, zy = 0.f;
 #pragma unroll
@@ -229,26 +260,24 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
     s = row16_sum(s);
     zy = row16_sum(zy);
     const float lse = logf(s);
-    const int k_own = owner(seg, rr);
-    const float inv_b = 1.0f / (float)(seg.off[k_own + 1] - seg.off[k_own]);
-    if (live && cl == 0) loss_rows[row] = bad ? 0.f : lse - (zy - m);
+    if (live && cl == 0) p.loss_rows[row] = bad ? 0.f : lse - (zy - m);
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
       const int c = 16 * j + cl;
-      float p = 0.f;
+      float d = 0.f;
       if (c < C) {
-        p = expf(zc[j] - m - lse);
-        if (c == y) p -= 1.0f;
-        p = bad ? 0.f : p * inv_b;
+        d = expf(zc[j] - m - lse);
+        if (c == y) d -= 1.0f;
+        d = bad ? 0.f : d * inv_b;
         if (live) {
-          z[(size_t)row * C + c] = zc[j];
-          dz[(size_t)row * C + c] = p;
+          p.z[(size_t)row * C + c] = zc[j];
+          p.dz[(size_t)row * C + c] = d;
         }
       }
-      zbuf[lr][c] = p;
+      zbuf[lr][c] = d;
     }
   }
-  __syncthreads();
+  lds_barrier();
   if (dx == nullptr) return;
 
   // ---- input gradient dx = dz w, masked by the folded ReLU (the input row itself)
@@ -256,7 +285,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 #pragma unroll
   for (int t = 0; t < 4 * CT; ++t) da[t] = zbuf[r][4 * t + g];
   const int nt = (C + 3) / 4;
-  for (int ct = wave; ct < col_tiles; ct += NW) {
+  for (int ct = ct_begin + wave; ct < ct_end; ct += NW) {
     const int col = column(ct);
     v4f o[EL];
     v4f mk[4];
@@ -279,6 +308,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
+        if (t > 0 && t0 + t >= nt) break;                 // (no class left)
         float b[EL];
         Ops::unpack(wt[t], b);
 #pragma unroll
@@ -287,7 +317,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 #pragma unroll
       for (int e = 0; e < EL; ++e) o[e] = t0 == 0 ? part[e] : o[e] + part[e];
     }
-    if (ct + NW < col_tiles) fetch_cols(column(ct + NW));
+    if (ct + NW < ct_end) fetch_cols(column(ct + NW));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int row = row0 + 4 * g + v;
@@ -315,30 +345,31 @@ bool head_supported(int cin, int classes, const void* x, const void* w, bool bf1
          (reinterpret_cast<uintptr_t>(w) & 15u) == 0;
 }
 
-template <typename T>
-static void launch_head_fwd(hipStream_t st, const T* x, const T* w, const float* bias, const int32_t* labels, int cin,
-                            int classes, const Segments& seg, float* z, float* dz, float* loss_rows, bool use_mask,
-                            T* dx) {
-  const dim3 grid((seg.off[seg.K] + 15) / 16);
-  const int um = use_mask ? 1 : 0;
-#define OMNI_HEAD(CT)                                                                                                 \
-  hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, CT>), grid, dim3(64 * head_waves<CT>()), 0, st, x, w, bias, labels, cin, classes, seg, z, \
-                     dz, loss_rows, um, dx)
-  if (classes <= 16) OMNI_HEAD(1);
-  else if (classes <= 48) OMNI_HEAD(3);
-  else OMNI_HEAD(8);
-#undef OMNI_HEAD
-}
-
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
                          const int32_t* labels, int cin, int classes, const Segments& seg, float* z, float* dz,
                          float* loss_rows, bool use_mask, void* dx) {
-  if (bf16)
-    launch_head_fwd<bf16_t>(st, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias, labels, cin,
-                            classes, seg, z, dz, loss_rows, use_mask, static_cast<bf16_t*>(dx));
-  else
-    launch_head_fwd<float>(st, static_cast<const float*>(x), static_cast<const float*>(w), bias, labels, cin, classes,
-                           seg, z, dz, loss_rows, use_mask, static_cast<float*>(dx));
+  const int rows = seg.off[seg.K], groups = (rows + 15) / 16;
+  // Several workgroups per sixteen rows where one each leaves half the chip idle: every one forms the logits, and the columns of dx
+  // are shared out, down to one tile per SIMD (1024 columns, 480 rows: dx 6000 of a workgroup's 15700 cycles, shared by four 2400).
+  const int tile = 16 * (bf16 ? Piece<bf16_t>::EL : Piece<float>::EL), tiles = (cin + tile - 1) / tile;
+  int splits = 1;
+  while (dx && groups * splits * 2 <= 256 && tiles >= 8 * splits) splits *= 2;
+  HeadFwdParams p{};
+  p.x = x; p.w = w; p.bias = bias; p.labels = labels; p.cin = cin; p.C = classes; p.rows = rows; p.K = seg.K; p.use_mask = use_mask ? 1 : 0;
+  p.groups = groups; p.cols_each = (tiles + splits - 1) / splits;
+  p.z = z; p.dz = dz; p.loss_rows = loss_rows; p.dx = dx;
+  const dim3 grid(groups * splits);
+#define OMNI_HEAD(T, CT) \
+  hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, CT>), grid, dim3(64 * head_waves<CT>()), 0, st, p, seg)
+#define OMNI_HEAD_CT(T)                   \
+  {                                       \
+    if (classes <= 16) OMNI_HEAD(T, 1);   \
+    else if (classes <= 48) OMNI_HEAD(T, 3); \
+    else OMNI_HEAD(T, 8);                 \
+  }
+  if (bf16) OMNI_HEAD_CT(bf16_t) else OMNI_HEAD_CT(float)
+#undef OMNI_HEAD_CT
+#undef OMNI_HEAD
 }
 
 int head_wgrad_columns_for(int cin, int classes, int K) { return head_wgrad_columns(cin, classes, K); }

@@ -1,0 +1,46 @@
+"""GPU parity of the classifier's forward kernel where the columns of its input gradient are shared out between workgroups
+(few rows, wide inputs): shares that do not divide the columns, last columns moved back, as many workers as there may be."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import GpuRun, assert_close, param_tensor_slices, rel_err
+from oracle import layers as OL
+from oracle import step as oracle_step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dims,off,dtype", [
+    ([12, 581, 10], [0, 3, 40], "f32"),                       # ten column tiles for two workgroups, the last one moved back
+    ([20, 1021, 13], list(range(65)), "f32"),                 # sixteen tiles for four; a row to each of 64 workers
+    ([20, 1100, 37], [0, 1, 17, 33], "f32"),                  # three class tiles; five tiles for each of four, three of them for the last
+    ([20, 1500, 100], [0, 30, 31], "f32"),                    # eight class tiles
+    ([24, 2040, 10], [0, 5, 47], "bf16"),                     # sixteen tiles of 128 columns, the last one moved back
+    ([16, 1032, 40], [0, 16, 32, 70], "bf16"),                # nine tiles for two
+])
+def test_columns_shared_out(dims, off, dtype):
+    bf = dtype == "bf16"
+    layers = synth.mlp(dims)
+    rng = np.random.default_rng(sum(dims))
+    params = synth.he_normal_params(layers, 3, bf)
+    x = rng.standard_normal((off[-1], dims[0])).astype(np.float32)
+    x = synth.to_bf16_grid(x) if bf else x
+    labels = rng.integers(0, dims[-1], off[-1]).astype(np.int32)
+    store = dict(store=OL.round_bf16) if bf else {}
+    ref = oracle_step.sgd_step(layers, params, x.reshape(-1, 1, 1, dims[0]), labels, off, 0.05, **store)
+    run = GpuRun(layers, (1, 1, dims[0]), dtype, len(off) - 1, off[-1])
+    try:
+        got = run.step(params, x, labels, off, 0.05)
+        # fp32: sums of at most 1500 terms; a ReLU argument within rounding of zero may move a row's share of a gradient.
+        # bf16 operands and stored values: 2^-9 each.
+        tol, tol_max = (2e-2, 6e-2) if bf else (1e-4, 5e-4)
+        assert got["status"] == 0
+        assert_close(got["loss_per_worker"], ref.loss_per_worker, tol, "L_k")
+        for name, s, e in param_tensor_slices(layers):
+            assert_close(got["grad"][s:e], ref.grad[s:e], tol, f"g {name}", tol_max=tol_max)
+            for k in range(len(off) - 1):
+                if np.abs(ref.worker_grads[k, s:e]).max() > 0:
+                    assert rel_err(got["worker_grads"][k, s:e], ref.worker_grads[k, s:e])[1] <= 2 * tol, (name, k)
+    finally:
+        run.close()
