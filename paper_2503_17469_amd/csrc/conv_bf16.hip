@@ -24,9 +24,9 @@
 //
 // Kernel F (3 input channels stored as 8, forward): the filter bank in registers.
 //
-// In files of their own: few positions (conv_frag_bf16.hip, asked first), 3x3 / stride 1 with
-// more than 32 outputs (conv3_wide_bf16.hip; kernel D has what it leaves: pooling in the
-// epilogue, narrow layers), a residual block's entry (conv3s2_dgrad_bf16.hip).
+// In files of their own: few positions (conv_frag_bf16.hip, asked first), 3x3 / stride 1
+// (conv3_wide_bf16.hip; kernel D has what it leaves: pooling without a ReLU or on maps other than 16 and 8
+// wide, narrow layers with a mask, few units), a residual block's entry (conv3s2_dgrad_bf16.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -992,11 +992,9 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   bool pooled = false;
   if (g.frag)
     return conv_frag_bf16(st, src, wgt, out, N, g, bias, mask, relu, accumulate, pool_out, pool_code, addend, stats);
-  // 3x3 / stride 1 / pad 1: the wide-tile kernel where the shape and the amount of work allow it (it has no
-  // pooling epilogue), else the 256-position one
-  if (!(pool_out && pool_code) &&
-      conv3_wide_bf16(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, addend, stats))
-    return false;
+  // 3x3 / stride 1 / pad 1: the wide-tile kernel where the shape and the amount of work allow it, else the 256-position one
+  if (conv3_wide_bf16(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, addend, pool_out, pool_code, stats))
+    return pool_out && pool_code;
   if (conv3_gemm(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled, addend))
     return pooled;
   if (!addend && conv1_fwd(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled))

@@ -218,10 +218,10 @@ void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int C
                        bf16_t* dx, int rows, int H, int W, int N, const bf16_t* mask, const uint8_t* mask_bits, bool accumulate,
                        const bf16_t* addend, const void* zero, BnStatRequest* stats);
 // The wide-tile kernel for 3x3 / stride 1 / pad 1 layers (conv3_wide_bf16.hip): same arguments and result as
-// conv_gemm_bf16 without pooling; false, with nothing launched, if the shape does not qualify.
+// conv_gemm_bf16 (with pool and pool_code both are written); false, with nothing launched, if the shape does not qualify.
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                      const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                     const bf16_t* addend, BnStatRequest* stats = nullptr);
+                     const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats);
 // Input gradient of a residual block's entry (conv3s2_dgrad_bf16.hip): dx [rows][H][W][Cin] receives the gradient
 // coming back through a 3x3 / stride-2 / pad-1 convolution (dy [rows][H/2][W/2][Cout], wt its transposed weights
 // [Cin][9][Cout]) and, if dy_sc is not null, through the 1x1 / stride-2 projection beside it (dy_sc
