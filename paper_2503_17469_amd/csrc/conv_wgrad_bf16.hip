@@ -319,6 +319,8 @@ struct Wgrad3Params {
   int Wp, prows;       // patch row length W + 16 (data starts at column 8), patch rows nimg * (R + 2)
   int SX;              // bytes between channels of X^T
   int upc;             // units per chunk
+  int nimg_log;
+  uint32_t by_r, by_patch, by_upi;   // 2^16 / R, 2^16 / (R + 2), 2^32 / (units per image), rounded up (the last 0 for one)
   float* partial;      // [(tile * total_chunks + chunk)][144][256] (+ 64 bias sums)
   const void* zero;    // page of zeros for absent pieces
 };
@@ -393,89 +395,71 @@ __device__ inline void wgrad3_taps(v16f (&acc)[9], int du, const bf16x8 fa, cons
   acc[du * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(right), acc[du * 3 + 2], 0, 0, 0);
 }
 
-template <int WM>
-__device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Segments& seg, const Chunk& ck, int tile,
-                                            unsigned char* smem3) {
+// WM: the map's width, 0: any other.  KS (at most 32 input channels): the two wavefronts of 32 output channels take the same 32 input
+// channels and half of a unit's positions each, and are added at the end.
+template <int WM, bool KS>
+__device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& ck, int tile, unsigned char* smem3) {
   constexpr bool W4 = WM == 4;
+  constexpr int XR = KS ? 32 : 64;           // channel rows of the patch
+  constexpr int XO = XR / 8, NX = KS ? 1 : 2;   // channel octets, staging tasks per thread
+  constexpr int KSTEPS = kUnit / 16 / (KS ? 2 : 1);   // reduction steps per wavefront and unit
   unsigned char* sA = smem3;                 // dY^T: 64 rows of kSA bytes
-  unsigned char* sX = smem3 + 64 * kSA + kSkewPad;   // X^T: 64 rows of p.SX bytes (both arrays: + the skew)
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned char* sX = smem3 + 64 * kSA + kSkewPad;   // X^T: XR rows of p.SX bytes (both arrays: + the skew)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 31, h = lane >> 5;
-  const int tiles_ci = (p.Cin + 63) / 64;
-  const int co0 = (tile / tiles_ci) * 64, ci0 = (tile % tiles_ci) * 64;
-  const int wco = (wave >> 1) * 32, wci = (wave & 1) * 32;
-  const int H = p.H, W = p.W, R = p.R;
+  const int tiles_ci = KS ? 1 : (p.Cin + 63) / 64;
+  const int tile_co = KS ? tile : tile / tiles_ci;
+  const int co0 = tile_co * 64, ci0 = KS ? 0 : (tile - tile_co * tiles_ci) * 64;
+  const int wco = (wave >> 1) * 32, wci = KS ? 0 : (wave & 1) * 32, kfirst = KS ? (wave & 1) * KSTEPS : 0;
+  const int H = p.H, W = WM ? WM : p.W, R = p.R;
   const int wk = ck.wk, chunk_idx = ck.idx, nchunks = ck.n;
-  const int bk = seg.off[wk + 1] - seg.off[wk];
-  const int upi = H / R;   // units per image when a unit is part of one image
-  const int units_k = p.nimg == 1 ? bk * upi : (bk + p.nimg - 1) / p.nimg;
+  const int bk = ck.end - ck.beg;
+  const int upi = p.nimg == 1 ? H / R : 1;   // units per image when a unit is part of one image
+  const int units_k = p.nimg == 1 ? bk * upi : (bk + p.nimg - 1) >> p.nimg_log;
   const int ubeg = chunk_idx * p.upc, uend = min(units_k, ubeg + p.upc);
-
-  // The halo columns of the patch are never written again: they stay zero.  So do the rows of
-  // channels past the end of the tensor (their staging tasks are skipped altogether).
-  for (int i = tid * 16; i < 64 * kSA + 64 * p.SX + 2 * kSkewPad; i += kThreads * 16)
-    *reinterpret_cast<u32x4*>(smem3 + i) = u32x4{0u, 0u, 0u, 0u};
 
   // ---- staging tasks (the same for every unit, relative to the unit's first image and row)
   // dY: 8 channel octets x 32 groups of 4 positions
+  auto over_r = [&](int rows) { return (int)(((uint32_t)rows * p.by_r) >> 16); };
   const int a_oct = tid & 7;
   int a_rel, a_il;
   {
     const int p0 = 4 * (tid >> 3), rr = p0 / W, w = p0 - rr * W;
-    a_il = rr / R;
+    a_il = over_r(rr);
     a_rel = (a_il * H + (rr - a_il * R)) * W + w;
   }
   const bool a_chan_ok = co0 + 8 * a_oct < p.Cout;
   unsigned char* a_dst = sA + (8 * a_oct) * kSA + row_skew(8 * a_oct) + 8 * (tid >> 3);
-  // X: 8 octets x (W/4 groups of 4 columns) x patch rows, two tasks per thread
+  // X: channel octets x (W/4 groups of 4 columns) x patch rows
   const int wq = W >> 2;
-  const int ntasks = p.prows * wq * 8;
-  int x_rel[2], x_il[2], x_rr[2], x_dst[2];
-  bool x_task[2];
+  const int ntasks = p.prows * wq * XO;
+  int x_rel[NX], x_il[NX], x_rr[NX], x_dst[NX];
+  bool x_task[NX];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
+  for (int t = 0; t < NX; ++t) {
     const int x = tid + t * kThreads;
     x_task[t] = x < ntasks;
     const int xx = x_task[t] ? x : 0;
-    const int oct = xx & 7, g = xx >> 3;
+    const int oct = xx % XO, g = xx / XO;
     const int pr = g / wq, wg = g - pr * wq;
-    x_il[t] = pr / (R + 2);
+    x_il[t] = (int)(((uint32_t)pr * p.by_patch) >> 16);
     x_rr[t] = pr - x_il[t] * (R + 2);                       // input row = first row + x_rr - 1
     x_rel[t] = ((x_il[t] * H + x_rr[t] - 1) * W + 4 * wg) * p.Cin + 8 * oct;
     x_dst[t] = (8 * oct) * p.SX + row_skew(8 * oct) + (pr * p.Wp + 4 * wg + (W4 ? 2 : 8)) * 2;
     x_task[t] = x_task[t] && ci0 + 8 * oct < p.Cin;   // false: no such piece, or a channel octet past the end
   }
 
-  // ---- fragment addresses: k-step ks covers positions 16 ks .. 16 ks + 15, this lane the 8 at 16 ks + 8 h
-  int offB[kUnit / 16];
-#pragma unroll
-  for (int ks = 0; ks < kUnit / 16; ++ks) {
-    const int pos = (2 * ks + h) * 8, rr = pos / W, w0 = pos - rr * W;
-    const int il = rr / R;
-    offB[ks] = ((il * (R + 2) + (rr - il * R)) * p.Wp + (W4 ? 0 : w0 + 8)) * 2;
-  }
-  const unsigned char* a_frag = sA + (wco + j) * kSA + row_skew(wco + j) + h * 16;
-  const unsigned char* x_frag = sX + (wci + j) * p.SX + row_skew(wci + j);
-  const int row_shift = p.Wp * 2;
-
-  v16f acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-  const bool want_bias = p.gb != nullptr && ci0 == 0;
-  float bsum = 0.f;
-
-  u32x4 ra[4], rx[2][4];
+  u32x4 ra[4], rx[NX][4];
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
-  auto load_unit = [&](int u) {
-    int n0, r0, nvalid;
-    if (p.nimg == 1) {
-      const int img = u / upi;
-      n0 = seg.off[wk] + img; r0 = (u - img * upi) * R; nvalid = 1;
-    } else {
-      n0 = seg.off[wk] + u * p.nimg; r0 = 0; nvalid = min(p.nimg, seg.off[wk + 1] - n0);
-    }
+  // first image and row of unit u; units are loaded one after the other
+  int img_at, row_at;
+  {
+    const int img = p.by_upi ? (int)__umulhi((uint32_t)ubeg, p.by_upi) : ubeg;
+    img_at = ck.beg + (p.nimg == 1 ? img : ubeg << p.nimg_log);
+    row_at = p.nimg == 1 ? (ubeg - img * upi) * R : 0;
+  }
+  auto load_unit = [&]() {
+    const int n0 = img_at, r0 = row_at, nvalid = p.nimg == 1 ? 1 : min(p.nimg, ck.end - n0);
     const long base_pos = ((long)n0 * H + r0) * W;
     // Loads never branch (a guarded load makes the compiler wait for each group before the
     // next): an absent piece is read from a page of zeros.
@@ -487,7 +471,7 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Segment
       for (int q = 0; q < 4; ++q) ra[q] = *reinterpret_cast<const u32x4*>(src + q * st);
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NX; ++t) {
       const int row = r0 + x_rr[t] - 1;
       const bool in = x_task[t] && x_il[t] < nvalid && row >= 0 && row < H;
       const bf16_t* src = in ? p.src + (base_pos * p.Cin + x_rel[t] + ci0) : zp;
@@ -496,25 +480,58 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Segment
       for (int q = 0; q < 4; ++q) rx[t][q] = *reinterpret_cast<const u32x4*>(src + q * st);
     }
   };
+  auto next_unit = [&]() {
+    row_at += R;
+    if (row_at >= H) {
+      row_at = 0;
+      img_at += p.nimg;
+    }
+  };
   auto store_unit = [&]() {
     if (a_chan_ok) transpose_store(ra, a_dst, kSA);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < NX; ++t) {
       if (!x_task[t]) continue;   // no such patch piece, or channels that stay zero
       if (W4) transpose_store32(rx[t], sX + x_dst[t], p.SX);
       else transpose_store(rx[t], sX + x_dst[t], p.SX);
     }
   };
+  load_unit();   // (every chunk has a unit)
 
-  load_unit(min(ubeg, max(uend - 1, 0)));
+  // The halo columns of the patch are never written again: they stay zero.  So do the rows of
+  // channels past the end of the tensor (their staging tasks are skipped altogether).
+  for (int i = tid * 16; i < 64 * kSA + XR * p.SX + 2 * kSkewPad; i += kThreads * 16)
+    *reinterpret_cast<u32x4*>(smem3 + i) = u32x4{0u, 0u, 0u, 0u};
+
+  // ---- fragment addresses: k-step ks covers positions 16 ks .. 16 ks + 15, this lane the 8 at 16 ks + 8 h
+  int offB[KSTEPS];
+#pragma unroll
+  for (int i = 0; i < KSTEPS; ++i) {
+    const int pos = (2 * (kfirst + i) + h) * 8, rr = pos / W, w0 = pos - rr * W;
+    const int il = over_r(rr);
+    offB[i] = ((il * (R + 2) + (rr - il * R)) * p.Wp + (W4 ? 0 : w0 + 8)) * 2;
+  }
+  const unsigned char* a_frag = sA + (wco + j) * kSA + row_skew(wco + j) + h * 16 + kfirst * 32;
+  const unsigned char* x_frag = sX + (wci + j) * p.SX + row_skew(wci + j);
+  const int row_shift = p.Wp * 2;
+
+  v16f acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+  const bool want_bias = p.gb != nullptr && ci0 == 0;
+  float bsum = 0.f;
+
   for (int u = ubeg; u < uend; ++u) {
     __syncthreads();   // the previous unit's fragments have been read (and, first time, the zero fill is done)
     store_unit();
     __syncthreads();
-    load_unit(min(u + 1, uend - 1));   // always issued: in flight during the MFMAs below
+    if (u + 1 < uend) next_unit();
+    load_unit();   // always issued: in flight during the MFMAs below
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int ks = 0; ks < kUnit / 16; ++ks) {
+    for (int ks = 0; ks < KSTEPS; ++ks) {
       const bf16x8 fa = as_bf16x8(*reinterpret_cast<const u32x4*>(a_frag + ks * 32));
       if constexpr (W4) {
         // patch rows r .. r+3 of this lane's image (16 bytes each) serve all nine taps
@@ -595,11 +612,33 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Segment
     __syncthreads();
     if (tid < 64) bsum = ((quarter[tid] + quarter[64 + tid]) + quarter[128 + tid]) + quarter[192 + tid];
   }
+  if constexpr (KS) {
+    // the halves of the positions meet, three taps at a time
+    float* half = reinterpret_cast<float*>(smem3) + (wave >> 1) * (48 * 64) + lane;
+#pragma unroll
+    for (int du = 0; du < 3; ++du) {
+      __syncthreads();
+      if (wave & 1) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) half[(t * 16 + v) * 64] = acc[du * 3 + t][v];
+      }
+      __syncthreads();
+      if (!(wave & 1)) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[du * 3 + t][v] += half[(t * 16 + v) * 64];
+      }
+    }
+  }
 
   const int ci = ci0 + wci + j;
+  const bool holds = ci < p.cin_real && (!KS || !(wave & 1));
   if (nchunks > 1) {
     float* mine = p.partial + ((size_t)tile * ck.total + ck.row) * kTile3Stride;
-    if (ci < p.cin_real) {   // the second stage reads the same lanes only
+    if (holds) {             // the second stage reads the same lanes only
 #pragma unroll
       for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -609,7 +648,7 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Segment
     return;
   }
   float* gw = p.gw + (size_t)wk * p.worker_stride;
-  if (ci < p.cin_real) {
+  if (holds) {
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
@@ -987,13 +1026,16 @@ __device__ __forceinline__ void wgrad1_reduce(const Wgrad1Params& p, const Chunk
 }
 
 // ------------------------------------------------------------------ launches of several layers
-enum WgradKind { kGeneral11, kGeneral12, kGeneral21, kGeneral22, kPatch4, kPatch8, kPatch16, kPatch32, kPatchAny, kStride2, kFirst };
+enum WgradKind {
+  kGeneral11, kGeneral12, kGeneral21, kGeneral22, kPatch4, kPatch8, kPatch16, kPatch32, kPatchAny, kPatch8Narrow, kPatch16Narrow,
+  kPatch32Narrow, kStride2, kFirst
+};
 
 struct BatchJob {
   int kind;
   int tiles;             // workgroups of the first stage: tiles x chunks, of the second: tiles x workers x slots
   int slots;
-  int first_block, first_reduce;
+  uint32_t by_tiles, by_workers;   // reciprocal32
   int32_t chunk[OMNI_MAX_WORKERS + 1];   // first chunk of every worker; chunk[K] = all
   union {
     WgradParams general;
@@ -1005,33 +1047,50 @@ struct BatchJob {
 constexpr int kBatchJobs = 6;   // the table travels in the kernel arguments
 struct BatchTable {
   int n;
+  int first[kBatchJobs];   // the jobs' first_block (second stage: first_reduce), in one line of the arguments
   BatchJob job[kBatchJobs];
 };
 
-__device__ inline Chunk chunk_at(const BatchJob& job, int K, int row) {
-  int wk = 0;
-  while (wk + 1 < K && row >= job.chunk[wk + 1]) ++wk;
-  return Chunk{wk, row - job.chunk[wk], job.chunk[wk + 1] - job.chunk[wk], row, job.chunk[K]};
+// (A line of arguments that nothing has touched takes 640 cycles: the lanes fetch chunks and rows of all workers at once.)
+__device__ inline Chunk chunk_at(const BatchJob& job, const Segments& seg, int row) {
+  const int lane = threadIdx.x & 63, K = seg.K, total = job.chunk[K], rows = seg.off[K];
+  const int mine = min(lane, K), chunk = job.chunk[mine], off = seg.off[mine];
+  const int wk = __popcll(__ballot(lane < K && chunk <= row)) - 1;
+  const int first = __builtin_amdgcn_readlane(chunk, wk), after = wk + 1 < K ? __builtin_amdgcn_readlane(chunk, wk + 1) : total;
+  return Chunk{wk, row - first, after - first, row, total, __builtin_amdgcn_readlane(off, wk),
+               wk + 1 < K ? __builtin_amdgcn_readlane(off, wk + 1) : rows};
 }
+__device__ inline int job_at(const BatchTable& tab, int block) {
+  int e = 0;
+#pragma unroll
+  for (int i = 1; i < kBatchJobs; ++i) e += i < tab.n && block >= tab.first[i] ? 1 : 0;
+  return e;
+}
+// n / d with by = 2^32 / d rounded up, 0 for d = 1 (exact for n below 2^20, d below 2^12)
+__device__ inline int quotient(int n, uint32_t by) { return by ? (int)__umulhi((uint32_t)n, by) : n; }
+inline uint32_t reciprocal32(int d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0; }
 
 __global__ __launch_bounds__(kThreads, 2) void wgrad_batch_kernel(BatchTable tab, Segments seg) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  int e = 0;
-  while (e + 1 < tab.n && (int)blockIdx.x >= tab.job[e + 1].first_block) ++e;
+  const int e = job_at(tab, (int)blockIdx.x);
   const BatchJob& job = tab.job[e];
-  const int local = (int)blockIdx.x - job.first_block;
-  const int tile = local % job.tiles;
-  const Chunk ck = chunk_at(job, seg.K, local / job.tiles);
+  const int local = (int)blockIdx.x - tab.first[e], row = quotient(local, job.by_tiles);
+  const int tile = local - row * job.tiles;
+  const Chunk ck = chunk_at(job, seg, row);
+  const Wgrad3Params patch = job.patch;   // (read together; and with a read per use the compiler copies the whole table into scratch)
   switch (job.kind) {
     case kGeneral11: wgrad_general_body<1, 1>(job.general, seg, ck, tile, smem); break;
     case kGeneral12: wgrad_general_body<1, 2>(job.general, seg, ck, tile, smem); break;
     case kGeneral21: wgrad_general_body<2, 1>(job.general, seg, ck, tile, smem); break;
     case kGeneral22: wgrad_general_body<2, 2>(job.general, seg, ck, tile, smem); break;
-    case kPatch4: wgrad3_body<4>(job.patch, seg, ck, tile, smem); break;
-    case kPatch8: wgrad3_body<8>(job.patch, seg, ck, tile, smem); break;
-    case kPatch16: wgrad3_body<16>(job.patch, seg, ck, tile, smem); break;
-    case kPatch32: wgrad3_body<32>(job.patch, seg, ck, tile, smem); break;
-    case kPatchAny: wgrad3_body<0>(job.patch, seg, ck, tile, smem); break;
+    case kPatch4: wgrad3_body<4, false>(patch, ck, tile, smem); break;
+    case kPatch8: wgrad3_body<8, false>(patch, ck, tile, smem); break;
+    case kPatch16: wgrad3_body<16, false>(patch, ck, tile, smem); break;
+    case kPatch32: wgrad3_body<32, false>(patch, ck, tile, smem); break;
+    case kPatchAny: wgrad3_body<0, false>(patch, ck, tile, smem); break;
+    case kPatch8Narrow: wgrad3_body<8, true>(patch, ck, tile, smem); break;
+    case kPatch16Narrow: wgrad3_body<16, true>(patch, ck, tile, smem); break;
+    case kPatch32Narrow: wgrad3_body<32, true>(patch, ck, tile, smem); break;
     case kStride2: wgrad_tr_body<2>(job.stride2, seg, ck, tile, smem); break;
     default: break;   // (kFirst has launches of its own)
   }
@@ -1049,19 +1108,18 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, 
     head_wgrad_loss_body<bf16_t>(head, seg, b % head_x, b / head_x, reinterpret_cast<float*>(smem));
     return;
   }
-  wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(job, seg.K, b - head_blocks), smem);
+  wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(job, seg, b - head_blocks), smem);
 }
 
 // Second stage of the layers in which some worker has more than one chunk.
 __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(BatchTable tab, Segments seg) {
   __shared__ __attribute__((aligned(16))) float lds[4 * kThreads];
-  int e = 0;
-  while (e + 1 < tab.n && (int)blockIdx.x >= tab.job[e + 1].first_reduce) ++e;
+  const int e = job_at(tab, (int)blockIdx.x);
   const BatchJob& job = tab.job[e];
-  const int local = (int)blockIdx.x - job.first_reduce;
-  const int tile = local % job.tiles, rest = local / job.tiles;
-  const int wk = rest % seg.K, slot = rest / seg.K;
-  const Chunk ck{wk, 0, job.chunk[wk + 1] - job.chunk[wk], job.chunk[wk], job.chunk[seg.K]};
+  const int local = (int)blockIdx.x - tab.first[e];
+  const int rest = quotient(local, job.by_tiles), tile = local - rest * job.tiles;
+  const int slot = quotient(rest, job.by_workers), wk = rest - slot * seg.K;
+  const Chunk ck{wk, 0, job.chunk[wk + 1] - job.chunk[wk], job.chunk[wk], job.chunk[seg.K], 0, 0};
   if (ck.n <= 1) return;   // written directly by the first stage
   switch (job.kind) {
     case kGeneral11: wgrad_general_reduce<1, 1>(job.general, ck, tile, slot, lds); break;
@@ -1143,9 +1201,16 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   words += (4 - words % 8 + 8) % 8;
   p.SX = words * 4;
   p.zero = g.zero;
-  pl.lds = (size_t)64 * kSA + (size_t)64 * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
+  while ((1 << p.nimg_log) < nimg) ++p.nimg_log;   // (nimg divides 128)
+  auto reciprocal16 = [](int d) { return (uint32_t)(((1 << 16) + d - 1) / d); };   // (exact: rows below 2^9, divisors up to 130)
+  p.by_r = reciprocal16(R); p.by_patch = reciprocal16(R + 2);
+  p.by_upi = nimg == 1 ? reciprocal32(H / R) : 0;
+  // at most 32 input channels: half of a 64 x 64 tile would be empty
+  const bool narrow = g.Cs <= 32 && (W == 8 || W == 16 || W == 32);
+  pl.lds = (size_t)64 * kSA + (size_t)(narrow ? 32 : 64) * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
   if (pl.lds > 80 * 1024) return false;
-  pl.job.kind = w4 ? kPatch4 : W == 8 ? kPatch8 : W == 16 ? kPatch16 : W == 32 ? kPatch32 : kPatchAny;
+  pl.job.kind = w4 ? kPatch4 : W == 8 ? (narrow ? kPatch8Narrow : kPatch8) : W == 16 ? (narrow ? kPatch16Narrow : kPatch16)
+              : W == 32 ? (narrow ? kPatch32Narrow : kPatch32) : kPatchAny;
   pl.job.tiles = ((j.Cout + 63) / 64) * ((g.Cs + 63) / 64);
   pl.job.slots = 144; pl.job.patch = p;
   count_units(pl, seg, H / R, nimg);
@@ -1153,7 +1218,7 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   // back: with 512 chunks that traffic outweighed the extra parallelism, measured -2 % on the three-layer CNN's step)
   pl.min_upc = 4; pl.upc_step = 1; pl.alone = 256;
   pl.slot_floats = kTile3Stride;
-  pl.work = (w4 ? 6.0 : 4.5) * pl.job.tiles * pl.total_units;
+  pl.work = (w4 ? 6.0 : narrow ? 3.0 : 4.5) * pl.job.tiles * pl.total_units;
   return true;
 }
 
@@ -1291,15 +1356,17 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
     set_partial(pl.job, partial + scratch);
     bp.scratch[i] = scratch;
     scratch += budget;
-    pl.job.first_block = bp.blocks;
-    pl.job.first_reduce = bp.rblocks;
+    pl.job.by_tiles = reciprocal32(pl.job.tiles);
+    pl.job.by_workers = reciprocal32(seg.K);
     bool chunked = false;
     for (int k = 0; k < seg.K; ++k) chunked = chunked || pl.job.chunk[k + 1] - pl.job.chunk[k] > 1;
     if (chunked) {
+      bp.red.first[bp.red.n] = bp.rblocks;
       bp.rblocks += pl.job.tiles * seg.K * pl.job.slots;
       bp.red.job[bp.red.n++] = pl.job;
     }
     if (light) continue;
+    bp.tab.first[bp.tab.n] = bp.blocks;
     bp.blocks += pl.job.tiles * pl.job.chunk[seg.K];
     bp.lds = std::max(bp.lds, pl.lds);
     bp.member[bp.tab.n] = i;

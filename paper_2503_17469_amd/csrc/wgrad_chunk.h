@@ -8,6 +8,7 @@ namespace omni {
 struct Chunk {
   int wk, idx, n;    // worker, chunk within the worker, the worker's chunks
   int row, total;    // chunk within the layer, the layer's chunks
+  int beg, end;      // the worker's rows
 };
 
 }  // namespace omni
