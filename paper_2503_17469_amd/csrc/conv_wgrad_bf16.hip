@@ -1105,7 +1105,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int b = (int)blockIdx.x;
   if (b < head_blocks) {
-    head_wgrad_loss_body<bf16_t>(head, seg, b % head_x, b / head_x, reinterpret_cast<float*>(smem));
+    head_wgrad_loss_body<bf16_t, 2>(head, seg, b, head_x, reinterpret_cast<float*>(smem));
     return;
   }
   wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(job, seg, b - head_blocks), smem);
@@ -1382,7 +1382,7 @@ void launch_light(hipStream_t st, const BatchJob& job, const HeadWgradParams* he
                                      kHeadWgradLdsFloats * sizeof(float)});
   static LdsLimit limit;
   limit.raise(reinterpret_cast<const void*>(&wgrad_light_kernel<MB, NB, POOLED>), kMost);
-  const dim3 hg = head ? head_wgrad_grid(head->cin, head->C, seg.K) : dim3(1, 0, 1);
+  const dim3 hg = head ? head_wgrad_grid(*head, seg) : dim3(1, 0, 1);
   const int head_blocks = (int)(hg.x * hg.y);
   hipLaunchKernelGGL((wgrad_light_kernel<MB, NB, POOLED>), dim3(head_blocks + job.chunk[seg.K]), dim3(kThreads), lds, st, job,
                      head ? *head : HeadWgradParams{}, (int)hg.x, head_blocks, seg);

@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256, 2) void bf16_dgrad_head_kernel(BfGemm p, HeadR
   constexpr int kWords = bf16_gemm_words<WB>() > kHeadWgradLdsFloats ? bf16_gemm_words<WB>() : kHeadWgradLdsFloats;
   __shared__ __attribute__((aligned(16))) uint32_t lds[kWords];
   const int b = (int)blockIdx.x;
-  if (b < head.blocks) head_wgrad_loss_body<bf16_t>(head.p, seg, b % head.gx, b / head.gx, reinterpret_cast<float*>(lds));
+  if (b < head.blocks) head_wgrad_loss_body<bf16_t, WB == 2 ? 4 : 2>(head.p, seg, b, head.gx, reinterpret_cast<float*>(lds));
   else bf16_gemm_body<WB>(p, b - head.blocks, lds);
 }
 

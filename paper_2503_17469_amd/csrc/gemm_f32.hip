@@ -454,7 +454,7 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_f32_dgrad_head_kernel(GemmPa
   __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
   const int b = (int)blockIdx.x;
   if (b < head.blocks)
-    head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, lds);
+    head_wgrad_loss_body<float, 1>(head.p, seg, b, head.gx, lds);
   else
     gemm_f32_body<32, false, true, MODE_DGRAD, 0>(p, seg, b - head.blocks, tiles, lds);
 }

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void dgrad_and_head_wgrad_kernel(DirectParams 
   __shared__ __attribute__((aligned(16))) float smem[kFloats];
   const int b = blockIdx.x;
   if (b < head.blocks)
-    head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, smem);
+    head_wgrad_loss_body<float, 2>(head.p, seg, b, head.gx, smem);
   else
     gemm_f32_direct_body<true, 4>(p, b - head.blocks, tiles, smem);
 }

@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256, 3) void small_dgrad_head_kernel(SmallGemm p, H
   constexpr int kGemm = small_gemm_floats<true, WB, 4>();
   __shared__ __attribute__((aligned(16))) float lds[kGemm > kHeadWgradLdsFloats ? kGemm : kHeadWgradLdsFloats];
   const int b = (int)blockIdx.x;
-  if (b < head.blocks) head_wgrad_loss_body<float>(head.p, seg, b % head.gx, b / head.gx, lds);
+  if (b < head.blocks) head_wgrad_loss_body<float, 2>(head.p, seg, b, head.gx, lds);
   else small_gemm_body<true, WB, 4>(p, b - head.blocks, lds);
 }
 

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 template <typename T>
 __global__ __launch_bounds__(256) void head_wgrad_loss_kernel(HeadWgradParams h, Segments seg) {
   __shared__ __attribute__((aligned(16))) float smem[kHeadWgradLdsFloats];
-  head_wgrad_loss_body<T>(h, seg, (int)blockIdx.x, (int)blockIdx.y, smem);
+  head_wgrad_loss_body<T, 4>(h, seg, (int)(blockIdx.x + blockIdx.y * gridDim.x), (int)gridDim.x, smem);
 }
 
 }  // namespace
@@ -372,10 +372,10 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
 #undef OMNI_HEAD
 }
 
-int head_wgrad_columns_for(int cin, int classes, int K) { return head_wgrad_columns(cin, classes, K); }
+int head_wgrad_columns_for(int cin, int classes, const Segments& seg) { return head_wgrad_columns(cin, classes, seg); }
 
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg) {
-  const dim3 grid = head_wgrad_grid(h.cin, h.C, seg.K);
+  const dim3 grid = head_wgrad_grid(h, seg);
   if (bf16)
     hipLaunchKernelGGL(head_wgrad_loss_kernel<bf16_t>, grid, dim3(256), 0, st, h, seg);
   else

@@ -73,138 +73,153 @@ __device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Se
   }
 }
 
-// LDS: the row groups' sums of 256 / JC groups x 16 classes x JC columns (rows of JC + 1), and 256 rows of dz.
-constexpr int kHeadWgradLdsFloats = 64 * 16 * 5 + 256 * 16;
-// Input columns per workgroup: 16, or 8 or 4 where that leaves most of the chip idle (a worker's rows are walked by one
-// workgroup per 16 classes and JC columns: one worker with 4096 rows of 1024 columns took 66 us in 64 workgroups).
-inline int head_wgrad_columns(int cin, int classes, int K) {
-  const long groups = (long)K * ((classes + 15) / 16);
-  for (int jc = 16; jc > 4; jc /= 2)
-    if (groups * ((cin + jc - 1) / jc) >= 256) return jc;
-  return 4;
+// LDS: the four wavefronts' 16 x 64 (16) tiles and their sums of dz.
+constexpr int kHeadWgradLdsFloats = 4 * (16 * 64 + 16);
+// Input columns per workgroup: 64, or 16 where a wavefront would walk many rows (24 blocks of 16 and more: 64 columns take four
+// matrix instructions per four rows) while there are fewer workgroups than compute units.
+inline int head_wgrad_columns(int cin, int classes, const Segments& seg) {
+  const long groups = (long)seg.K * ((classes + 15) / 16) * ((cin + 63) / 64);
+  return groups < 256 && seg.off[seg.K] / seg.K > 4 * 24 * 16 ? 16 : 64;
 }
-inline dim3 head_wgrad_grid(int cin, int classes, int K) {
-  const int jc = head_wgrad_columns(cin, classes, K);
-  return dim3(K * ((cin + jc - 1) / jc) + 1, (classes + 15) / 16, 1);
+inline dim3 head_wgrad_grid(const HeadWgradParams& h, const Segments& seg) {
+  return dim3(seg.K * ((h.cin + h.columns - 1) / h.columns) + 1, (h.C + 15) / 16, 1);
 }
 
-// One worker, JC input columns, 16 classes; 256 threads.  Each thread walks one column and every (256 / JC)-th row: of 256
-// rows at a time all its elements are on their way before the rows' dz (16 classes of them) is staged in LDS (fetched
-// per thread they would be 16 global loads per row, and the vector cache, not the arithmetic, would set the pace).
-template <typename T, int JC>
-__device__ __forceinline__ void head_wgrad_columns_body(const HeadWgradParams& h, const Segments& seg, int bx, int by,
-                                                        float* smem) {
-  constexpr int RS = 256 / JC;
-  float (*red)[16][JC + 1] = reinterpret_cast<float (*)[16][JC + 1]>(smem);
-  float (*dzs)[16] = reinterpret_cast<float (*)[16]>(smem + RS * 16 * (JC + 1));
-  const float* __restrict__ dz = h.dz;
-  const T* __restrict__ x = static_cast<const T*>(h.x);
-  const int cin = h.cin, C = h.C;
-  float* __restrict__ gw = h.gw;
-  float* __restrict__ gb = h.gb;
-  const size_t worker_stride = h.worker_stride;
-  const int tid = threadIdx.x;
-  const int jchunks = (cin + JC - 1) / JC;
-  const int wk = bx / jchunks, jc = bx % jchunks;
-  const int jl = tid % JC, rs = tid / JC;
-  const int j = min(jc * JC + jl, cin - 1);   // a column past the end shadows the last one and is not stored
-  const int c0 = by * 16;
-  const int nc = min(16, C - c0);
-  const int s_end = seg.off[wk + 1];
-  const bool want_bias = jc == 0 && gb != nullptr;
-  float acc[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = 0.f;
-  float bsum = 0.f;   // class tid % 16, rows tid / 16, + 16, ...
+// One worker, 16 WB input columns, 16 classes; 256 threads: gw = dz^T x on the fp32 matrix instruction (bf16 inputs are exact in
+// fp32).  The four wavefronts take blocks of 16 rows in turn, operands straight from global memory (their layout is the
+// instruction's: one class, WB columns and every fourth row per lane), DEPTH blocks in flight (as many as
+// the registers of the launch it is in allow), eight rows summed by themselves, into two or four running totals; their tiles are added in a fixed order.  A block that would run past the end of the worker's rows is moved back to end there; rows that are not its
+// own count zero in both operands.  Columns past the end are the last ones again and are not stored.
+// (A thread per column with dz staged in LDS read 64 bytes of LDS per row: 1024 rows of 2048 inputs, eight workers, 10 classes
+// in a launch of its own 7.5 -> 5.3 us, beside the first convolution's weight gradient 6.7 -> 2.3 us more.)
+template <typename T, int WB> struct HeadInputs;
+template <> struct HeadInputs<float, 4> {
+  typedef v4f raw;
+  __device__ static inline raw load(const float* p) { return *reinterpret_cast<const v4f_a4*>(p); }
+  __device__ static inline float get(const raw& v, int e) { return v[e]; }
+};
+template <> struct HeadInputs<float, 1> {
+  typedef float raw;
+  __device__ static inline raw load(const float* p) { return *p; }
+  __device__ static inline float get(raw v, int) { return v; }
+};
+template <> struct HeadInputs<bf16_t, 4> {       // (widths are multiples of 8: aligned)
+  typedef u32x2 raw;
+  __device__ static inline raw load(const bf16_t* p) { return *reinterpret_cast<const u32x2*>(p); }
+  __device__ static inline float get(const raw& v, int e) { return e & 1 ? bf16_hi(v[e >> 1]) : bf16_lo(v[e >> 1]); }
+};
+template <> struct HeadInputs<bf16_t, 1> {
+  typedef bf16_t raw;
+  __device__ static inline raw load(const bf16_t* p) { return *p; }
+  __device__ static inline float get(raw v, int) { return bf16_to_f32(v); }
+};
 
-  for (int base = seg.off[wk]; base < s_end; base += 256) {
-    const int n = min(256, s_end - base);
-    // (a worker often has fewer rows than that: groups of four loads that would all lie past the end are left out)
-    const T* xb = x + (size_t)base * cin;          // (uniform bases and 32-bit offsets: half the address registers)
-    const float* dzb = dz + (size_t)base * C + c0;
-    float av[JC];
+template <typename T, int WB, int DEPTH>
+__device__ __forceinline__ void head_wgrad_tile_body(const HeadWgradParams& h, const Segments& seg, int wk, int jc, int by, float* smem) {
+  typedef HeadInputs<T, WB> In;
+  constexpr int TN = 16 * WB, kTile = 16 * TN + 16, D = WB == 1 ? 4 : DEPTH, NS = WB == 1 ? 4 : 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const int s0 = seg.off[wk], s1 = seg.off[wk + 1], last = seg.off[seg.K] - 1;
+  const int cin = h.cin, C = h.C, c0 = by * 16, j0 = jc * TN;
+  const int col = min(j0 + WB * r, cin - WB);
+  const T* const x = static_cast<const T*>(h.x) + col;
+  const float* const dz = h.dz + min(c0 + r, C - 1);
+  const bool want_bias = jc == 0 && h.gb != nullptr;
+  const int blocks = (s1 - s0 + 63 - 16 * wave) >> 6;       // of this wavefront
+  float a[D][4];
+  typename In::raw b[D][4];
+  auto start = [&](int i) { return max(min(s0 + 16 * wave + 64 * i, s1 - 16), 0); };
+  auto load = [&](int d, int i) {
+    const int at = start(min(i, blocks - 1));
 #pragma unroll
-    for (int u = 0; u < JC; ++u) {
-      if (u % 4 == 0 && RS * u >= n) break;
-      av[u] = Piece<T>::get(xb + (min(rs + RS * u, n - 1) * cin + j));   // (dz of rows past the end: 0)
+    for (int t = 0; t < 4; ++t) {
+      const int row = min(at + 4 * t + g, last);            // (fewer than 16 rows in all)
+      a[d][t] = dz[(size_t)row * C];
+      b[d][t] = In::load(x + (size_t)row * cin);
     }
+  };
+  v4f acc[NS][WB];                                          // (in turn: short chains)
+  float bsum[NS];
 #pragma unroll
-    for (int i0 = 0; i0 < 16; i0 += 8) {          // (eight at a time: registers)
-      if (16 * i0 >= n) break;
-      float dv[8];
+  for (int d = 0; d < NS; ++d) {
+    bsum[d] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int rr = (tid >> 4) + 16 * (i0 + i), c = tid & 15;
-        const bool ok = rr < n && c < nc;
-        const float v = dzb[ok ? rr * C + c : 0];
-        dv[i] = ok ? v : 0.f;
-      }
-      if (i0 == 0) __syncthreads();               // the previous 256 rows have been consumed
-#pragma unroll
-      for (int i = 0; i < 8; ++i) dzs[(tid >> 4) + 16 * (i0 + i)][tid & 15] = dv[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < JC; ++u) {
-      if (u % 4 == 0 && RS * u >= n) break;
-      // (a row of the group that the staged rows do not reach is not counted)
-      const bool live = rs + RS * u < n;
-      const v4f* d = reinterpret_cast<const v4f*>(&dzs[live ? rs + RS * u : 0][0]);
-      const float a = live ? av[u] : 0.f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const v4f t = d[q];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[4 * q + e] += t[e] * a;
-      }
-    }
-    if (want_bias)
-      for (int r2 = tid >> 4; r2 < n; r2 += 16) bsum += dzs[r2][tid & 15];
+    for (int e = 0; e < WB; ++e) acc[d][e] = v4f{0.f, 0.f, 0.f, 0.f};
   }
-
+  if (blocks > 0) {
 #pragma unroll
-  for (int c = 0; c < 16; ++c) red[rs][c][jl] = acc[c];
-  __syncthreads();
-  if (tid < 16 * JC) {
-    const int c = tid / JC, jj = tid % JC;
-    float part[4] = {0.f, 0.f, 0.f, 0.f};   // (four short chains: smaller rounding errors, and the reads need not wait for each other)
-#pragma unroll 4
-    for (int r = 0; r < RS; r += 4)
+    for (int d = 0; d < D; ++d) load(d, d);
+    for (int i0 = 0; i0 < blocks; i0 += D) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) part[q] += red[r + q][c][jj];
-    const float t = (part[0] + part[1]) + (part[2] + part[3]);
-    if (c < nc && jc * JC + jj < cin)
-      gw[(size_t)wk * worker_stride + (size_t)(c0 + c) * cin + jc * JC + jj] = t;
+      for (int d = 0; d < D; ++d) {
+        const int i = i0 + d;
+        if (i < blocks) {
+          const int lo = s0 + 16 * wave + 64 * i, at = start(i);
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {            // eight rows by themselves
+            v4f sum[WB];
+            float bs = 0.f;
+#pragma unroll
+            for (int t = 2 * half; t < 2 * half + 2; ++t) {
+              const int row = at + 4 * t + g;
+              const bool own = row >= lo && row < s1;
+              const float av = own ? a[d][t] : 0.f;
+              bs += av;
+#pragma unroll
+              for (int e = 0; e < WB; ++e)
+                sum[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, own ? In::get(b[d][t], e) : 0.f,
+                                                              t % 2 == 0 ? v4f{0.f, 0.f, 0.f, 0.f} : sum[e], 0, 0, 0);
+            }
+            const int set = (2 * d + half) % NS;
+#pragma unroll
+            for (int e = 0; e < WB; ++e) acc[set][e] += sum[e];
+            bsum[set] += bs;
+          }
+          if (i + D < blocks) load(d, i + D);
+        }
+      }
+    }
   }
+  float* const mine = smem + wave * kTile;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int e = 0; e < WB; ++e) mine[(4 * g + v) * TN + WB * r + e] = NS == 2 ? acc[0][e][v] + acc[1][e][v] : (acc[0][e][v] + acc[1][e][v]) + (acc[NS - 2][e][v] + acc[NS - 1][e][v]);
   if (want_bias) {
-    // bias gradient: column sums of dz over the worker's rows, 16 row groups x 16 classes
-    __syncthreads();
-    float* r2 = &red[0][0][0];
-    r2[(tid >> 4) * 16 + (tid & 15)] = bsum;
-    __syncthreads();
-    if (tid < 16 && tid < nc) {
-      float u[4] = {0.f, 0.f, 0.f, 0.f};
+    float t = NS == 2 ? bsum[0] + bsum[1] : (bsum[0] + bsum[1]) + (bsum[NS - 2] + bsum[NS - 1]);
+    t += __shfl_xor(t, 16, 64);
+    t += __shfl_xor(t, 32, 64);
+    if (g == 0) mine[16 * TN + r] = t;
+  }
+  __syncthreads();
+  float* const gw = h.gw + (size_t)wk * h.worker_stride + (size_t)c0 * cin;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) u[r & 3] += r2[r * 16 + tid];
-      gb[(size_t)wk * worker_stride + c0 + tid] = (u[0] + u[1]) + (u[2] + u[3]);
-    }
+  for (int q = 0; q < WB; ++q) {
+    const int e = q * 256 + tid, c = e / TN, nom = j0 + e % TN / WB * WB, cc = min(nom, cin - WB) + e % WB;
+    const float t = (smem[e] + smem[kTile + e]) + (smem[2 * kTile + e] + smem[3 * kTile + e]);
+    if (c0 + c < C && cc >= nom) gw[(size_t)c * cin + cc] = t;   // (of a group moved back, what the group before it also holds is left to that one)
+  }
+  if (want_bias && tid < 16 && c0 + tid < C) {
+    const float* const q = smem + 16 * TN + tid;
+    h.gb[(size_t)wk * h.worker_stride + c0 + tid] = (q[0] + q[kTile]) + (q[2 * kTile] + q[3 * kTile]);
   }
 }
 
-// Workgroup (bx, by) of a head_wgrad_grid, 256 threads, kHeadWgradLdsFloats floats of LDS at smem (16-byte aligned).  The
+// Workgroup b of a head_wgrad_grid (rows of gx), 256 threads, kHeadWgradLdsFloats floats of LDS at smem (16-byte aligned).  The
 // one past the last column computes the losses.
-template <typename T>
-__device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, const Segments& seg, int bx, int by,
-                                                     float* smem) {
-  const int jchunks = (h.cin + h.columns - 1) / h.columns;
-  if (bx == seg.K * jchunks) {
+template <typename T, int DEPTH>
+__device__ __forceinline__ void head_wgrad_loss_body(const HeadWgradParams& h, const Segments& seg, int b, int gx, float* smem) {
+  int bx = b, by = 0;
+  while (bx >= gx) { bx -= gx; ++by; }
+  if (bx == gx - 1) {
     if (by == 0)
       head_loss_body(HeadLossParams{h.labels, h.C, h.loss_rows, h.loss_per_worker, h.loss, h.status}, seg, smem);
     return;
   }
-  if (h.columns == 16) head_wgrad_columns_body<T, 16>(h, seg, bx, by, smem);
-  else if (h.columns == 8) head_wgrad_columns_body<T, 8>(h, seg, bx, by, smem);
-  else head_wgrad_columns_body<T, 4>(h, seg, bx, by, smem);
+  const int chunks = (h.cin + h.columns - 1) / h.columns, wk = bx / chunks, jc = bx - wk * chunks;
+  if (h.columns == 64) head_wgrad_tile_body<T, 4, DEPTH>(h, seg, wk, jc, by, smem);
+  else head_wgrad_tile_body<T, 1, DEPTH>(h, seg, wk, jc, by, smem);
 }
 
 // The classifier's part of a launch it shares with a matrix product: its workgroups come first (they are short but wait for
@@ -216,7 +231,7 @@ struct HeadRole {
 inline HeadRole head_role(const HeadWgradParams* h, const Segments& seg) {
   HeadRole r{};
   if (!h) return r;
-  const dim3 g = head_wgrad_grid(h->cin, h->C, seg.K);
+  const dim3 g = head_wgrad_grid(*h, seg);
   r.p = *h;
   r.gx = (int)g.x;
   r.blocks = (int)(g.x * g.y);

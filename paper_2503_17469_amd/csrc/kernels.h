@@ -115,7 +115,7 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
 // Per worker: gw_k = dz_k^T x_k, gb_k = column sums of dz_k; plus L_k, the total
 // loss and the status word (bit 0: some label outside [0, classes)).
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg);
-int head_wgrad_columns_for(int cin, int classes, int K);   // HeadWgradParams::columns
+int head_wgrad_columns_for(int cin, int classes, const Segments& seg);   // HeadWgradParams::columns
 // Arguments of the head's parameter-gradient kernel.  x has the storage type T of the body's
 // instantiation (fp32, or bf16 words); everything else is fp32.
 struct HeadWgradParams {
@@ -130,7 +130,7 @@ struct HeadWgradParams {
   float* loss_per_worker;     // [K]
   float* loss;                // [1]
   uint32_t* status;           // [1]
-  int columns;                // head_wgrad_columns(cin, C, workers)
+  int columns;                // head_wgrad_columns(cin, C, the step's rows)
 };
 // ---- bf16 convolutions / fully connected layers as implicit GEMMs (conv_bf16.hip) ----
 typedef uint16_t bf16_t;   // raw bfloat16 bits

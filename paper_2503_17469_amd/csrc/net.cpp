@@ -574,7 +574,7 @@ void step_f32(StepCtx& c) {
   const omni::HeadWgradParams head{grad(logits), act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                    last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
                                    c.loss_per_worker, c.loss, c.status,
-                                   omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg.K)};
+                                   omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg)};
   bool head_pending = fused_head && tiled;
   for (int i = n_layers - 1; i >= 0; --i) {
     const Layer& L = net->layers[i];
@@ -836,7 +836,7 @@ void step_bf16(StepCtx& c) {
     head_grads = omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                        last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
                                        c.loss_per_worker, c.loss, c.status,
-                                       omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg.K)};
+                                       omni::head_wgrad_columns_for(last.d.cin, last.d.cout, c.seg)};
   }
 
   // ---- backward

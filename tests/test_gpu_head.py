@@ -1,5 +1,6 @@
-"""GPU parity of the classifier's forward kernel where the columns of its input gradient are shared out between workgroups
-(few rows, wide inputs): shares that do not divide the columns, last columns moved back, as many workers as there may be."""
+"""GPU parity of the classifier: its forward kernel where the columns of its input gradient are shared out between workgroups
+(few rows, wide inputs: shares that do not divide the columns, last columns moved back, as many workers as there may be), and
+its parameter gradients at the edges of their tiles."""
 import numpy as np
 import pytest
 
@@ -18,8 +19,10 @@ pytestmark = pytest.mark.gpu
     ([20, 1500, 100], [0, 30, 31], "f32"),                    # eight class tiles
     ([24, 2040, 10], [0, 5, 47], "bf16"),                     # sixteen tiles of 128 columns, the last one moved back
     ([16, 1032, 40], [0, 16, 32, 70], "bf16"),                # nine tiles for two
+    ([16, 104, 10], [0, 1700], "bf16"),                       # parameter gradients: 16 columns per workgroup, the last half full
+    ([16, 72, 20], [0, 5, 20, 21, 100], "bf16"),              # ... 64, workers of fewer rows than a block, two class tiles
 ])
-def test_columns_shared_out(dims, off, dtype):
+def test_classifier(dims, off, dtype):
     bf = dtype == "bf16"
     layers = synth.mlp(dims)
     rng = np.random.default_rng(sum(dims))
