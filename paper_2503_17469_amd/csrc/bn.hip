@@ -28,14 +28,28 @@ constexpr float kBnEps = 1e-5f;
 // splits / chunks first[k] .. first[k+1]-1 of a ShareTable, each covering an equal share of ITS
 // positions, so ragged b_k do not leave most of the chip waiting for the largest worker.
 
-__device__ inline int share_owner(const ShareTable& tb, int K, int id) {
-  int lo = 0, hi = K - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (id >= tb.first[mid]) lo = mid; else hi = mid - 1;
+// The worker of share `id`, its shares and its rows.  The lanes fetch both tables at once: a line of arguments that nothing has
+// touched costs 640 cycles, and a search through them paid that several times over before the first load of data (ResNet-18
+// shape at 128 images, with the divisions of 64-bit numbers that stood beside it: 1.1 of 8 us a launch).
+struct Share {
+  int wk, first, after;   // worker, its first share, the next worker's
+  int beg, end;           // rows
+};
+__device__ inline Share share_at(const ShareTable& tb, const Segments& seg, int id) {
+  const int lane = threadIdx.x & 63;
+  const int first = tb.first[lane], off = seg.off[lane], K = seg.K;   // (65 entries; what lies past the workers' is not used)
+  const int wk = __popcll(__ballot(lane < K && first <= id)) - 1;
+  Share s{wk, __builtin_amdgcn_readlane(first, wk), 0, __builtin_amdgcn_readlane(off, wk), 0};
+  if (wk + 1 < OMNI_MAX_WORKERS) {
+    s.after = __builtin_amdgcn_readlane(first, wk + 1);
+    s.end = __builtin_amdgcn_readlane(off, wk + 1);
+  } else {
+    s.after = tb.first[OMNI_MAX_WORKERS];
+    s.end = seg.off[OMNI_MAX_WORKERS];
   }
-  return lo;
+  return s;
 }
+static_assert(OMNI_MAX_WORKERS == 64, "a lane per worker");
 
 // Mean and 1/sqrt(var) of eight consecutive channels (stats: [channel][2]).
 __device__ inline void load_stats8(const float* __restrict__ p, float (&mu)[8], float (&is)[8]) {
@@ -45,6 +59,11 @@ __device__ inline void load_stats8(const float* __restrict__ p, float (&mu)[8], 
     mu[2 * i] = t[0]; is[2 * i] = t[1];
     mu[2 * i + 1] = t[2]; is[2 * i + 1] = t[3];
   }
+}
+__device__ inline void load8(const float* __restrict__ p, float (&v)[8]) {   // any multiple of 4 bytes
+  const v4f lo = *reinterpret_cast<const v4f_a4*>(p), hi = *reinterpret_cast<const v4f_a4*>(p + 4);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[4 + e] = hi[e]; }
 }
 __device__ inline void unpack8(u32x4 t, float (&v)[8]) {
 #pragma unroll
@@ -69,13 +88,14 @@ __global__ __launch_bounds__(kPartThreads) void bn_partial_kernel(const bf16_t* 
   __shared__ double red2[8][64];
   const int tid = threadIdx.x;
   const int c8 = tid & 7, pl = tid >> 3;
-  const int wk = share_owner(tb, seg.K, blockIdx.x);
-  const int split = blockIdx.x - tb.first[wk];
+  const Share sh = share_at(tb, seg, blockIdx.x);
+  const int wk = sh.wk, split = blockIdx.x - sh.first;
   const int c0 = blockIdx.y * 64 + c8 * 8;
   const bool cok = c0 < C;
   const int cl = cok ? c0 : 0;   // a piece past the last channel shadows piece 0 and is not stored
-  const long pbeg = (long)seg.off[wk] * hw, pend = (long)seg.off[wk + 1] * hw;
-  const long sbeg = pbeg + (long)split * per, send = min(pend, sbeg + per);
+  // (fewer than 2^24 positions)
+  const int pbeg = sh.beg * hw, pend = sh.end * hw;
+  const long sbeg = pbeg + split * per, send = min((long)pend, sbeg + per);
   // Sums run in double: this kernel waits on memory, and statistics good to fp32
   // rounding keep the normalised values from landing on the other side of a bf16
   // rounding boundary more often than the arithmetic forces.
@@ -241,47 +261,36 @@ template <bool BWD>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                        const float* __restrict__ stats, const float* __restrict__ means,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                       int C, int hw, Segments seg, ShareTable tb, int relu,
-                                                       bf16_t* __restrict__ out, const bf16_t* __restrict__ skip,
+                                                       int C, int hw, int ppar, uint32_t by_pieces, Segments seg, ShareTable tb,
+                                                       int relu, bf16_t* __restrict__ out, const bf16_t* __restrict__ skip,
                                                        int relu_add, uint8_t* __restrict__ sign_bits) {
-  const int c8n = C / 8;
-  const int ppar = 256 / c8n;                   // positions per trip
-  const int tid = threadIdx.x;
-  const int pc = tid % c8n, lp = tid / c8n;
+  const int c8n = C / 8, tid = threadIdx.x;
+  const int lp = (int)(((uint32_t)tid * by_pieces) >> 16), pc = tid - lp * c8n;   // of ppar positions per trip
+  const Share sh = share_at(tb, seg, blockIdx.x);
   if (lp >= ppar) return;
-  const int wk = share_owner(tb, seg.K, blockIdx.x);
-  const int chunk = blockIdx.x - tb.first[wk], nchunk = tb.first[wk + 1] - tb.first[wk];
-  const long pbeg = (long)seg.off[wk] * hw, pend = (long)seg.off[wk + 1] * hw;
-  const long per = (pend - pbeg + nchunk - 1) / nchunk;
-  const long cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
+  const int wk = sh.wk, chunk = blockIdx.x - sh.first, nchunk = sh.after - sh.first;
+  const int pbeg = sh.beg * hw, pend = sh.end * hw;   // (fewer than 2^24 positions)
+  const int per = (int)((unsigned)(pend - pbeg + nchunk - 1) / (unsigned)nchunk);
+  const int cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
   const int c0 = pc * 8;
-  float mu[8], is[8], gm[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    mu[e] = stats[((size_t)wk * C + c0 + e) * 2];
-    is[e] = stats[((size_t)wk * C + c0 + e) * 2 + 1];
-    gm[e] = gamma[c0 + e];
-  }
-  float bt[8], mn1[8], mn2[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    bt[e] = BWD ? 0.f : beta[c0 + e];
-    mn1[e] = BWD ? means[((size_t)wk * C + c0 + e) * 2] : 0.f;
-    mn2[e] = BWD ? means[((size_t)wk * C + c0 + e) * 2 + 1] : 0.f;
-  }
-  for (long p = cbeg + lp; p < cend; p += 4 * ppar) {
+  float mu[8], is[8], gm[8], bt[8], mn1[8], mn2[8];
+  load_stats8(stats + ((size_t)wk * C + c0) * 2, mu, is);
+  load8(gamma + c0, gm);
+  if (BWD) load_stats8(means + ((size_t)wk * C + c0) * 2, mn1, mn2);
+  else load8(beta + c0, bt);
+  for (int p = cbeg + lp; p < cend; p += 4 * ppar) {
     float xv[4][8], dv[4][8];   // dv: the output gradient (backward) or the residual input (forward, with skip)
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long q = min(p + (long)u * ppar, cend - 1);
+      const size_t q = min(p + u * ppar, cend - 1);
       Piece<bf16_t>::load(x + q * C + c0, xv[u]);
       if (BWD) Piece<bf16_t>::load(dy + q * C + c0, dv[u]);
       else if (skip) Piece<bf16_t>::load(skip + q * C + c0, dv[u]);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long q = p + (long)u * ppar;
-      if (q >= cend) break;
+      if (p + u * ppar >= cend) break;
+      const size_t q = p + u * ppar;
       float o[8];
       if (BWD) {
 #pragma unroll
@@ -316,26 +325,32 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
   __shared__ double red[4][64][2];
   __shared__ float fin[64][2];
   const int tid = threadIdx.x;
-  const int wk = share_owner(tb, seg.K, blockIdx.x);
-  const int chunk = blockIdx.x - tb.first[wk], nchunk = tb.first[wk + 1] - tb.first[wk];
-  const long pbeg = (long)seg.off[wk] * hw, pend = (long)seg.off[wk + 1] * hw;
-  const long per = (pend - pbeg + nchunk - 1) / nchunk;
-  const long cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
+  const int rec_first = rec.first[tid & 63];
+  const Share sh = share_at(tb, seg, blockIdx.x);
+  const int wk = sh.wk, chunk = blockIdx.x - sh.first, nchunk = sh.after - sh.first;
+  const int pbeg = sh.beg * hw, pend = sh.end * hw;   // (fewer than 2^24 positions)
+  const int per = (int)((unsigned)(pend - pbeg + nchunk - 1) / (unsigned)nchunk);
+  const int cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
   const int lp = tid >> 3, c8 = tid & 7, c0 = blockIdx.y * 64 + c8 * 8;
   u32x4 xr[4], dr[4];   // dr: the output gradient (backward) or the residual input (forward, with skip)
-  auto fetch = [&](long p) {
+  auto fetch = [&](int p) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long q = max(min(p + 32 * u, cend - 1), pbeg);
+      const size_t q = max(min(p + 32 * u, cend - 1), pbeg);
       xr[u] = *reinterpret_cast<const u32x4*>(x + q * C + c0);
       if (BWD) dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + c0);
       else if (skip) dr[u] = *reinterpret_cast<const u32x4*>(skip + q * C + c0);
     }
   };
+  float mu[8], is[8], gm[8], bt[8], mn1[8], mn2[8];
+  if (BWD) load_stats8(stats + ((size_t)wk * C + c0) * 2, mu, is);
+  load8(gamma + c0, gm);
+  if (!BWD) load8(beta + c0, bt);
   fetch(cbeg + lp);
   {
     const int c = tid & 63, part = tid >> 6;
-    const int r0 = rec.first[wk], r1 = rec.first[wk + 1];
+    const int r0 = __builtin_amdgcn_readlane(rec_first, wk);
+    const int r1 = wk + 1 < OMNI_MAX_WORKERS ? __builtin_amdgcn_readlane(rec_first, wk + 1) : rec.first[OMNI_MAX_WORKERS];
     double a = 0.0, b = 0.0;
     for (int r = r0 + part; r < r1; r += 32) {      // eight loads in flight, added in order
       double2 v[8];
@@ -375,28 +390,21 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
       }
     }
   }
-  float mu[8], is[8], gm[8], bt[8], mn1[8], mn2[8];
-  if (BWD) load_stats8(stats + ((size_t)wk * C + c0) * 2, mu, is);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    gm[e] = gamma[c0 + e];
-    bt[e] = BWD ? 0.f : beta[c0 + e];
-  }
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     if (BWD) { mn1[e] = fin[c8 * 8 + e][0]; mn2[e] = fin[c8 * 8 + e][1]; }
     else { mu[e] = fin[c8 * 8 + e][0]; is[e] = fin[c8 * 8 + e][1]; }
   }
-  for (long p = cbeg + lp; p < cend; p += 128) {
+  for (int p = cbeg + lp; p < cend; p += 128) {
     u32x4 xc[4], dc[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) { xc[u] = xr[u]; dc[u] = dr[u]; }
     if (p - lp + 128 < cend) fetch(p + 128);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const long q = p + 32L * u;
-      if (q >= cend) break;
+      if (p + 32 * u >= cend) break;
+      const size_t q = p + 32 * u;
       float xv[8], dv[8], o[8];
       unpack8(xc[u], xv);
       if (BWD || skip) unpack8(dc[u], dv);
@@ -574,6 +582,9 @@ ShareTable bn_chunks(const Segments& seg, int C, int hw) {
   return deal_shares(seg, std::max<long>(seg.K, total));
 }
 
+// 2^16 / (C / 8) rounded up: exact for a thread's number (below 2^8) by at most 2^8 pieces
+uint32_t pieces_reciprocal(int C) { return (uint32_t)((65536 + C / 8 - 1) / (C / 8)); }
+
 }  // namespace
 
 bool bn_shape_supported(int C) { return C % 8 == 0 && C >= 8 && C <= 2048; }
@@ -596,7 +607,8 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
   hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
   const ShareTable ch = bn_chunks(seg, C, hw);
   hipLaunchKernelGGL(bn_apply_kernel<false>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, nullptr, stats, nullptr,
-                     gamma, beta, C, hw, seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
+                     gamma, beta, C, hw, 256 / (C / 8), pieces_reciprocal(C), seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0,
+                     sign_bits);
 }
 
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
@@ -619,7 +631,7 @@ void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t*
                      g_gamma, g_beta, worker_stride);
   const ShareTable ch = bn_chunks(seg, C, hw);
   hipLaunchKernelGGL(bn_apply_kernel<true>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, dy, stats, means, gamma,
-                     nullptr, C, hw, seg, ch, 0, dx, nullptr, 0, nullptr);
+                     nullptr, C, hw, 256 / (C / 8), pieces_reciprocal(C), seg, ch, 0, dx, nullptr, 0, nullptr);
 }
 
 void add_fwd_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* out, long elems, bool relu) {

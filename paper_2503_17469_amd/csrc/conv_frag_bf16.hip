@@ -49,8 +49,12 @@ struct FragParams {
   int PR, npatch;      // patch rows per image, patch positions in all
   int stride, flip;    // flip: input gradient (mirrored taps)
   int by_channel;      // which operand an XCD keeps to itself, see the kernel
-  int gK;              // entries of the table below: entry k owns the tiles tfirst[k] .. and the images ifirst[k] ..
-  int32_t tfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
+  int tiles, per;      // tiles of positions; workgroups (of a parity class) per XCD
+  uint32_t by_minor;   // 2^32 / the faster counted of tiles and channel tiles, rounded up (0 for 1)
+  uint32_t by_upi;     // 2^32 / upi (0 for 1)
+  uint32_t by_oc;      // 2^16 / (Cs / 8), rounded up
+  int dq, dr;          // 256 pieces on: so many positions and octets
+  int gK;              // entries of the tables at the end
   const void* zero;
   const float* bias;
   const bf16_t* mask;
@@ -63,7 +67,29 @@ struct FragParams {
   double* stat_partial;   // [tile][N][2] or null
   const bf16_t* stat_x;   // BWD: see BnStatRequest
   const float* stat_norm;
+  // entry k owns the tiles tfirst[k] .. and the images ifirst[k] ..
+  int32_t tfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
 };
+
+// Where a tile lies.  A launch of this kernel is a chain of first accesses (a line of arguments 640 cycles, a division 150 to 200):
+// the tables are read only where there is more than one entry, all lanes at once.  (128 images of three conv layers: the four
+// launches 8.5 -> 7.4 us each.)
+__device__ inline int frag_quotient(int n, uint32_t by) { return by ? (int)__umulhi((uint32_t)n, by) : n; }
+struct FragPlace {
+  int gk, n0, r0, nvalid;   // entry, first image and row, images present
+};
+__device__ inline FragPlace frag_place(const FragParams& p, int tile) {
+  int gk = 0, tl = tile, beg = 0, end = p.rows;
+  if (p.gK > 1) {
+    const int lane = threadIdx.x & 63, t = p.tfirst[lane], i = p.ifirst[lane];   // (65 entries)
+    gk = __popcll(__ballot(lane < p.gK && t <= tile)) - 1;
+    tl = tile - __builtin_amdgcn_readlane(t, gk);
+    beg = __builtin_amdgcn_readlane(i, gk);
+    end = gk + 1 < p.gK ? __builtin_amdgcn_readlane(i, gk + 1) : p.rows;
+  }
+  const int img = p.upi == 1 ? tl * p.nimg : frag_quotient(tl, p.by_upi);
+  return FragPlace{gk, beg + img, p.upi == 1 ? 0 : (tl - img * p.upi) << p.rlog, min(p.nimg, end - beg - img)};
+}
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -113,7 +139,12 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
 #pragma unroll
     for (int qq = 0; qq < 2; ++qq)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) bias8[qq][e] = p.bias ? p.bias[cb + qq * 16 + h * 8 + e] : 0.f;
+      for (int i = 0; i < 2; ++i) {
+        const v4f t = *reinterpret_cast<const v4f_a4*>(p.bias ? p.bias + cb + qq * 16 + h * 8 + 4 * i
+                                                              : static_cast<const float*>(p.zero));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bias8[qq][4 * i + e] = t[e];
+      }
   }
   __syncthreads();                                 // nobody reads the patch any more
   float* const ex = reinterpret_cast<float*>(smemF);   // [position block][channel block][share][v / 4][lane][4]
@@ -251,19 +282,14 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   // Workgroup b runs on XCD b % 8, and every XCD has an L2 of its own: it takes a contiguous run of the tiles, counted
   // channel tile by channel tile (by_channel: its L2 then holds few channel tiles' weights and most of the source) or
   // position by position (all weights, few positions).
-  const int tiles = p.tfirst[p.gK], tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n;
-  const int per = (total + 7) / 8;
-  const int at = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
-  if (at >= total || ((int)blockIdx.x >> 3) >= per) return;
-  const int tile = p.by_channel ? at % tiles : at / tiles_n;
-  const int col0 = (p.by_channel ? at / tiles : at % tiles_n) * kTN;
-  int gk = 0;
-  while (gk + 1 < p.gK && tile >= p.tfirst[gk + 1]) ++gk;
-  const int tl = tile - p.tfirst[gk];
+  const int tiles = p.tiles, tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n;
+  const int at = ((int)blockIdx.x & 7) * p.per + ((int)blockIdx.x >> 3);
+  if (at >= total || ((int)blockIdx.x >> 3) >= p.per) return;
+  const int major = frag_quotient(at, p.by_minor), minor = at - major * (p.by_channel ? tiles : tiles_n);
+  const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
+  const FragPlace place = frag_place(p, tile);
+  const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
   const int R = 1 << p.rlog, Wp = 1 << p.wlog;
-  const int n0 = p.ifirst[gk] + (p.upi == 1 ? tl * p.nimg : tl / p.upi);
-  const int r0 = p.upi == 1 ? 0 : (tl % p.upi) << p.rlog;
-  const int nvalid = min(p.nimg, p.ifirst[gk + 1] - n0);
   const int npos = nvalid << (p.rlog + p.wlog);
   const int oc = p.Cs >> 3;
   const int pitch = p.Cs * 2 + 16;                 // bytes of a patch position: neighbours start 4 banks apart
@@ -275,8 +301,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
                                                  : ((size_t)n0 * p.Hs + s0) * p.Ws * p.Cs);
   const int npieces = p.npatch * oc;
   const int live = (p.upi == 1 ? nvalid * p.PR : min(p.PR, p.Hs - s0)) * p.Ws * oc;   // (9 taps) pieces that exist
-  int q = tid / oc, rem = tid - q * oc;            // patch position and octet of the piece
-  const int dq = kThreads / oc, dr = kThreads - dq * oc;
+  int q = (int)(((uint32_t)tid * p.by_oc) >> 16), rem = tid - q * oc;   // patch position and octet of the piece
+  const int dq = p.dq, dr = p.dr;
   int x = tid;
   u32x4 rp[8];
   int dst[8];
@@ -444,21 +470,17 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p)
   extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 31, h = lane >> 5;
-  const int tiles = p.tfirst[p.gK], tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n, per = (total + 7) / 8;
-  const int local = (int)blockIdx.x >> 3;
-  const int cls = 3 - local / per;                 // (h mod 2) * 2 + (w mod 2)
-  const int at = ((int)blockIdx.x & 7) * per + local % per;
+  const int tiles = p.tiles, tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n;
+  int local = (int)blockIdx.x >> 3, cls = 3;       // (h mod 2) * 2 + (w mod 2)
+  while (local >= p.per) { local -= p.per; --cls; }
+  const int at = ((int)blockIdx.x & 7) * p.per + local;
   if (cls < 0 || at >= total) return;
   const int ph = cls >> 1, pw = cls & 1;
-  const int tile = p.by_channel ? at % tiles : at / tiles_n;
-  const int col0 = (p.by_channel ? at / tiles : at % tiles_n) * kTN;
-  int gk = 0;
-  while (gk + 1 < p.gK && tile >= p.tfirst[gk + 1]) ++gk;
-  const int tl = tile - p.tfirst[gk];
+  const int major = frag_quotient(at, p.by_minor), minor = at - major * (p.by_channel ? tiles : tiles_n);
+  const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
+  const FragPlace place = frag_place(p, tile);
+  const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
   const int R = 1 << p.rlog, Wp = 1 << p.wlog;     // the half-resolution grid: Hs x Ws = Hp x Wp
-  const int n0 = p.ifirst[gk] + (p.upi == 1 ? tl * p.nimg : tl / p.upi);
-  const int r0 = p.upi == 1 ? 0 : (tl % p.upi) << p.rlog;
-  const int nvalid = min(p.nimg, p.ifirst[gk + 1] - n0);
   const int npos = nvalid << (p.rlog + p.wlog);
   const int oc = p.Cs >> 3, pitch = p.Cs * 2 + 16;
   const int zrow = p.npatch * pitch;
@@ -469,8 +491,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p)
     const bf16_t* base = src + ((size_t)n0 * p.Hs + r0) * p.Ws * p.Cs;
     const int npieces = (p.upi == 1 ? p.nimg * rows_of : rows_of) * p.Ws * oc;
     const int live = (p.upi == 1 ? nvalid * rows_of : min(rows_of, p.Hs - r0)) * p.Ws * oc;
-    int q = tid / oc, rem = tid - q * oc;
-    const int dq = kThreads / oc, dr = kThreads - dq * oc;
+    int q = (int)(((uint32_t)tid * p.by_oc) >> 16), rem = tid - q * oc;
+    const int dq = p.dq, dr = p.dr;
     for (int x0 = 0; x0 < npieces; x0 += 8 * kThreads) {
       u32x4 rp[8];
 #pragma unroll
@@ -609,6 +631,19 @@ void frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stat
   }
 }
 
+// What follows from the tiles, the channels and by_channel.
+void frag_counts(FragParams& p) {
+  auto reciprocal = [](int d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };   // (exact: numbers below 2^20)
+  const int tiles_n = (p.N + kTN - 1) / kTN, oc = p.Cs / 8;
+  p.tiles = p.tfirst[p.gK];
+  p.per = (p.tiles * tiles_n + 7) / 8;
+  p.by_minor = reciprocal(p.by_channel ? p.tiles : tiles_n);
+  p.by_upi = reciprocal(p.upi);
+  p.by_oc = (uint32_t)((65536 + oc - 1) / oc);   // (exact: a thread's number by at most 2^8 octets)
+  p.dq = kThreads / oc;
+  p.dr = kThreads - p.dq * oc;
+}
+
 template <int KS, int TAPS, bool BWD>
 void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
   static LdsLimit limit;
@@ -653,6 +688,7 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   const int taps = g.ks * g.ks, tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
   // an XCD's L2 sees the whole of one operand and about an eighth of the other
   p.by_channel = (long)N * taps * g.Cs > (long)g.rows * g.Hs * g.Ws * g.Cs ? 1 : 0;
+  frag_counts(p);
   const int grid = (tiles * tiles_n + 7) / 8 * 8;
 #define OMNI_FRAG(KS_, TAPS_) { if (bwd) launch<KS_, TAPS_, true>(st, p, grid, s.lds); else launch<KS_, TAPS_, false>(st, p, grid, s.lds); }
   if (taps == 9) { if (s.ks == 4) OMNI_FRAG(4, 9) else OMNI_FRAG(2, 9) }
@@ -702,6 +738,7 @@ void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int C
   frag_tiles(p, s, rows, stats, true, 4);
   const int tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
   p.by_channel = (long)N * 9 > (long)rows * g.Hs * g.Ws ? 1 : 0;
+  frag_counts(p);
   static LdsLimit limit;
   limit.raise(reinterpret_cast<const void*>(&conv_frag_s2_kernel), kLdsOfComputeUnit);
   hipLaunchKernelGGL(conv_frag_s2_kernel, dim3((tiles * tiles_n + 7) / 8 * 8 * 4), dim3(kThreads), s.lds, st, p);
