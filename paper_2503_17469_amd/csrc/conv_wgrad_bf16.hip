@@ -26,6 +26,7 @@
 #include "head_device.h"
 #include "kernels.h"
 #include "lds_limit.h"
+#include "update_device.h"
 #include "wgrad_chunk.h"
 
 namespace omni {
@@ -1132,6 +1133,185 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(BatchTable tab, 
   }
 }
 
+// ---- the second stage with the update: all workers' gradients of an element meet in one workgroup, which applies their weighted
+// sum (chunks and workers in the order of the two launches it stands for: the same bits).  For steps whose weight gradients are
+// one call; kernel C's layers and the first layer's, the parameters of all others follow from G.
+struct UpdateTo {
+  float* theta;
+  float* vel;
+  float* G;            // worker 0's gradients of all parameters
+  size_t stride;
+};
+constexpr int kRestRanges = 2 * kBatchJobs + 1;
+struct RestTable {     // parameters whose gradients are complete in G already: beg[i] .. end[i] - 1 from workgroup first[i] on
+  int n;
+  int32_t first[kRestRanges], beg[kRestRanges], end[kRestRanges];
+};
+
+template <bool MOM>
+__device__ inline void update_one(const UpdateTo& to, size_t at, float th, float ve, float g, const Optim& opt) {
+  apply_update<MOM>(th, ve, g, opt);
+  to.theta[at] = th;
+  if (MOM) to.vel[at] = ve;
+}
+
+// The sum of n values `stride` apart in the order of the second stage above: four quarters, added one after the other.
+__device__ inline float sum_quarters(const float* src, int n, size_t stride) {
+  const int per = (n + 3) >> 2;
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < per; i += 4) {               // sixteen loads in flight
+    float t[4][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t[u][q] = src[(size_t)min(q * per + i + u, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = i + u < per && q * per + i + u < n ? a[q] + t[u][q] : a[q];
+  }
+  return ((a[0] + a[1]) + a[2]) + a[3];
+}
+// ... and in one chain, as the bias gradients'.
+__device__ inline float sum_chain(const float* src, int n, size_t stride) {
+  float a = 0.f;
+  for (int c = 0; c < n; c += 8) {
+    float t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = src[(size_t)min(c + u, n - 1) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a = c + u < n ? a + t[u] : a;
+  }
+  return a;
+}
+
+// Kernel C: a workgroup has one register of one tap and tile quadrant (the pairs one wavefront of the first stage held), its
+// wavefronts take the workers in turn.  lds: 64 floats per worker.
+constexpr int kUpdateSlots3 = 9 * 16 * 4;
+template <bool MOM>
+__device__ __forceinline__ void wgrad3_update(const Wgrad3Params& p, const BatchJob& job, int tile, int z, const Segments& seg,
+                                              const Lambdas& lam, const Optim& opt, const UpdateTo& to, float* lds) {
+  const int quad = z & 3, v = (z >> 2) & 15, tap = z >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, sub = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 31, h = lane >> 5, K = seg.K;
+  const int tiles_ci = (p.Cin + 63) / 64;
+  const int co0 = (tile / tiles_ci) * 64, ci0 = (tile % tiles_ci) * 64;
+  const int wco = (quad >> 1) * 32, wci = (quad & 1) * 32, ci = ci0 + wci + j;
+  const bool with_bias = z == 0 && p.gb != nullptr && ci0 == 0;
+  if (ci0 + wci >= p.cin_real) return;             // (nothing there; quadrant 0, which has the bias, never)
+  const int my_co = co0 + wco + 8 * (v / 4) + 4 * h + (v % 4);
+  const bool in = my_co < p.Cout && ci < p.cin_real;
+  const size_t at = in ? ((size_t)my_co * 9 + tap) * p.cin_real + ci : 0, mine = (size_t)(p.gw - to.G) + at;
+  const float th = to.theta[mine], ve = MOM ? to.vel[mine] : 0.f;
+  const float* const tiles = p.partial + (size_t)tile * job.chunk[K] * kTile3Stride;
+  for (int wk = sub; wk < K; wk += kThreads / 64) {
+    const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
+    float* const gw = p.gw + (size_t)wk * p.worker_stride;
+    float s = 0.f;
+    if (n > 1) {
+      s = sum_quarters(tiles + (size_t)c0 * kTile3Stride + (size_t)(tap * 16 + v) * kThreads + quad * 64 + lane, n, kTile3Stride);
+      if (in) gw[at] = s;
+    } else if (in) {
+      s = gw[at];                                  // (written by the first stage)
+    }
+    lds[wk * 64 + lane] = s;
+  }
+  __syncthreads();
+  if (sub == 0 && in) {
+    float g = 0.f;
+    for (int k = 0; k < K; ++k) g += lam.v[k] * lds[k * 64 + lane];
+    update_one<MOM>(to, mine, th, ve, g, opt);
+  }
+  if (!with_bias) return;
+  __syncthreads();
+  const int co = min(co0 + lane, p.Cout - 1);
+  for (int wk = sub; wk < K; wk += kThreads / 64) {
+    const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
+    float* const gb = p.gb + (size_t)wk * p.worker_stride + co;
+    float s;
+    if (n > 1) {
+      s = sum_chain(tiles + (size_t)c0 * kTile3Stride + kTile3Floats + co - co0, n, kTile3Stride);
+      if (co0 + lane < p.Cout) *gb = s;
+    } else {
+      s = *gb;
+    }
+    lds[wk * 64 + lane] = s;
+  }
+  __syncthreads();
+  if (sub == 0 && co0 + lane < p.Cout) {
+    float g = 0.f;
+    for (int k = 0; k < K; ++k) g += lam.v[k] * lds[k * 64 + lane];
+    const size_t bat = (size_t)(p.gb - to.G) + co;
+    update_one<MOM>(to, bat, to.theta[bat], MOM ? to.vel[bat] : 0.f, g, opt);
+  }
+}
+
+// Kernel G: 64 accumulator elements per workgroup.
+template <bool MOM>
+__device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const BatchJob& job, int z, const Segments& seg, const Lambdas& lam,
+                                              const Optim& opt, const UpdateTo& to, float* lds) {
+  const int NB = wgrad1_col_blocks(p.cin_real), MB = p.Cout > 32 ? 2 : 1, kImg = MB * NB * 16 * 64, K = seg.K;
+  const int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int e = z * 64 + lane, blk = z >> 4, v = z & 15, mb = NB == 2 ? blk >> 1 : blk, nb = NB == 2 ? blk & 1 : 0;
+  const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4), col = nb * 32 + (lane & 31), cols = 9 * p.cin_real;
+  const bool in = co < p.Cout && (col < cols || (col == cols && p.gb));
+  float* const g0 = !in ? p.gw : col < cols ? p.gw + (size_t)co * cols + col : p.gb + co;   // worker 0's
+  const size_t at = (size_t)(g0 - to.G);
+  const float th = to.theta[at], ve = MOM ? to.vel[at] : 0.f;
+  for (int wk = sub; wk < K; wk += kThreads / 64) {
+    const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
+    float s;
+    if (n > 1) {
+      s = sum_quarters(p.partial + (size_t)c0 * kImg + e, n, kImg);
+      if (in) g0[(size_t)wk * p.worker_stride] = s;
+    } else {
+      s = g0[(size_t)wk * p.worker_stride];
+    }
+    lds[wk * 64 + lane] = s;
+  }
+  __syncthreads();
+  if (sub == 0 && in) {
+    float g = 0.f;
+    for (int k = 0; k < K; ++k) g += lam.v[k] * lds[k * 64 + lane];
+    update_one<MOM>(to, at, th, ve, g, opt);
+  }
+}
+
+// Workgroups below rest.first[0]: the table's layers, tiles x slots each; then the rest, an element per thread.
+// Measured, 3-32-64-128: 128 images, four workers, second stage and update 8.3 + 3.9 us before, 10.8 together (step 90.5 -> 88.2 us);
+// 1024 images, eight workers, 14.6 + 6.4 and 20.5 (step -0.2 per cent); 2048 images, sixteen, 23.0 + 9.7 and 26.3 (step -2.0
+// per cent).  One register per workgroup and 16 loads in flight: two registers, or 32 loads, are no faster.
+template <bool MOM>
+__global__ __launch_bounds__(kThreads) void wgrad_update_kernel(BatchTable tab, RestTable rest, Segments seg, Lambdas lam, Optim opt,
+                                                                UpdateTo to) {
+  extern __shared__ __attribute__((aligned(16))) float lds_update[];
+  const int b = (int)blockIdx.x;
+  if (b >= rest.first[0]) {
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < kRestRanges; ++k) i += k < rest.n && b >= rest.first[k] ? 1 : 0;
+    const int at = rest.beg[i] + (b - rest.first[i]) * kThreads + (int)threadIdx.x;
+    if (at >= rest.end[i]) return;
+    const float th = to.theta[at], ve = MOM ? to.vel[at] : 0.f;
+    float g = 0.f;
+    for (int k0 = 0; k0 < seg.K; k0 += 8) {        // eight loads in flight
+      float t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = to.G[(size_t)min(k0 + u, seg.K - 1) * to.stride + at];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (k0 + u < seg.K) g += lam.v[k0 + u] * t[u];
+    }
+    update_one<MOM>(to, at, th, ve, g, opt);
+    return;
+  }
+  const int e = job_at(tab, b);
+  const BatchJob& job = tab.job[e];
+  const int local = b - tab.first[e], slot = quotient(local, job.by_tiles), tile = local - slot * job.tiles;
+  if (job.kind == kFirst) wgrad1_update<MOM>(job.first, job, slot, seg, lam, opt, to, lds_update);
+  else wgrad3_update<MOM>(job.patch, job, tile, slot, seg, lam, opt, to, lds_update);
+}
+
 // ------------------------------------------------------------------ planning
 // A layer's form, and how its positions may be cut: units per worker, the fewest units a chunk should have, how much
 // scratch a (tile, chunk) takes.
@@ -1398,11 +1578,59 @@ double conv_wgrad_work(const ConvWgradJob& j) {
   return 2.0 * j.g.rows * j.g.Hp * j.g.Wp * j.Cout * j.g.K;
 }
 
-void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups) {
+namespace {
+// The second stage of all layers of a call and the update of all `params` parameters; false, with nothing launched, where some layer
+// has another second stage, or none has any.
+bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, const Segments& seg, const SgdArgs& sgd, float* G,
+                  size_t params) {
+  if (bp.red.n == 0 || params > (size_t)INT32_MAX - kThreads) return false;
+  BatchTable tab = bp.red;
+  struct Range { long beg, end; } covered[2 * kBatchJobs];
+  int m = 0, blocks = 0;
+  for (int i = 0; i < tab.n; ++i) {
+    BatchJob& job = tab.job[i];
+    const bool first = job.kind == kFirst;
+    if (!first && (job.kind < kPatch4 || job.kind > kPatch32Narrow)) return false;
+    const float* const gw = first ? job.first.gw : job.patch.gw;
+    const float* const gb = first ? job.first.gb : job.patch.gb;
+    const int Cout = first ? job.first.Cout : job.patch.Cout, cin = first ? job.first.cin_real : job.patch.cin_real;
+    covered[m++] = {gw - G, gw - G + (long)Cout * 9 * cin};
+    if (gb) covered[m++] = {gb - G, gb - G + (long)Cout};
+    tab.first[i] = blocks;
+    blocks += job.tiles * (first ? job.slots : kUpdateSlots3);
+  }
+  std::sort(covered, covered + m, [](const Range& a, const Range& b) { return a.beg < b.beg; });
+  RestTable rest{};
+  rest.first[0] = blocks;
+  long at = 0;
+  for (int i = 0; i <= m; ++i) {
+    const long end = i < m ? covered[i].beg : (long)params;
+    if (end > at) {
+      rest.first[rest.n] = blocks;
+      rest.beg[rest.n] = (int32_t)at;
+      rest.end[rest.n++] = (int32_t)end;
+      blocks += (int)((end - at + kThreads - 1) / kThreads);
+    }
+    if (i < m) at = covered[i].end;
+  }
+  const UpdateTo to{sgd.params, sgd.velocity, G, worker_stride};
+  const Lambdas lam = lambdas_of(seg);
+  const Optim opt{sgd.lr, sgd.momentum, sgd.weight_decay};
+  const size_t lds = (size_t)seg.K * 64 * sizeof(float);
+  if (sgd.velocity)
+    hipLaunchKernelGGL(wgrad_update_kernel<true>, dim3(blocks), dim3(kThreads), lds, st, tab, rest, seg, lam, opt, to);
+  else
+    hipLaunchKernelGGL(wgrad_update_kernel<false>, dim3(blocks), dim3(kThreads), lds, st, tab, rest, seg, lam, opt, to);
+  return true;
+}
+}  // namespace
+
+bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd, float* G,
+                      size_t params) {
   if (head && n == 0) {
     head_wgrad_loss(st, true, *head, seg);
-    return;
+    return false;
   }
   for (int base = 0; base < n; base += kBatchJobs) {
     BatchPlan bp;
@@ -1428,8 +1656,10 @@ void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
       h = nullptr;
     }
     if (h) head_wgrad_loss(st, true, *h, seg);
+    if (sgd && n <= kBatchJobs && update_batch(st, bp, worker_stride, seg, *sgd, G, params)) return true;
     if (bp.rblocks > 0) hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(bp.rblocks), dim3(kThreads), 0, st, bp.red, seg);
   }
+  return false;
 }
 
 void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, int workgroups, ConvWgradPlanned* out) {

@@ -256,9 +256,11 @@ double conv_wgrad_work(const ConvWgradJob& job);   // flop
 // All jobs share launches (first stage, second stage).  partial: `floats` of scratch, which bound the cutting; more than
 // conv_wgrad_partial_floats() are not used.  head (may be
 // null): the classifier's parameter gradients and losses as well (head_wgrad_loss).  workgroups: how many the layers of a
-// shared first stage are cut into (two fit a compute unit).
-void conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups);
+// shared first stage are cut into (two fit a compute unit).  sgd (may be null; only where these are the step's last gradients): the
+// update of all `params` parameters (G: worker 0's gradients of them) by the launch of the second stage, where that can (true).
+bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd = nullptr,
+                      float* G = nullptr, size_t params = 0);
 // How conv_wgrad_batch runs these layers, without a launch: for checks on the host.
 struct ConvWgradPlanned {
   bool first_layer;    // has a first stage of its own

@@ -505,7 +505,8 @@ struct StepCtx {
   float* loss_per_worker;
   float* loss;
   float lr;
-  bool fuse_update;      // fully connected networks: the weight-gradient launch applies the update
+  bool fuse_update;      // the weight-gradient launch applies the update (convolutional networks: where it can)
+  bool updated;          // convolutional networks: it has
 };
 
 // ------------------------------------------------------------------ fp32 path
@@ -1041,20 +1042,25 @@ void step_bf16(StepCtx& c) {
   if (!net->linear_only) {
     TimedScope ts(net, st, OMNI_KERNEL_CONV_WGRAD, 0);
     // (where groups run beside it, what is left are layers on the network input, whose gradients are small)
-    omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg, c.forked ? conv_partial3 : conv_partial,
-                           c.forked ? kSmallScratchFloats : omni::conv_wgrad_partial_floats(), head_pending ? &head_grads : nullptr, 512);
+    const omni::SgdArgs sgd{c.params, net->velocity, c.lr, net->momentum, net->weight_decay};
+    c.updated = omni::conv_wgrad_batch(st, group.data(), (int)group.size(), net->P_stride, c.seg,
+                                       c.forked ? conv_partial3 : conv_partial,
+                                       c.forked ? kSmallScratchFloats : omni::conv_wgrad_partial_floats(),
+                                       head_pending ? &head_grads : nullptr, 512,
+                                       c.fuse_update && !c.forked && linear_jobs.empty() ? &sgd : nullptr, c.G, net->P);
   } else if (head_pending) {
     omni::head_wgrad_loss(st, true, head_grads, c.seg);
   }
-  if (!linear_jobs.empty() || (net->linear_only && c.fuse_update)) {
+  if (!linear_jobs.empty() || (net->linear_only && c.fuse_update)) {   // (with convolutions: no update here)
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, 0, true);   // the hidden fully connected layers', in one launch
     const omni::SgdArgs sgd{c.params, net->velocity, c.lr, net->momentum, net->weight_decay};
     omni::LinearWgradBf16Job head{};
     head.gw = c.G + last.w_off;
     head.gb = last.has_b ? c.G + last.b_off : nullptr;
     head.cin = last.d.cin; head.cout = last.d.cout; head.w_off = last.w_off; head.b_off = last.b_off;
-    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg, c.fuse_update ? &head : nullptr,
-                            c.fuse_update ? &sgd : nullptr, ts.timer());
+    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg,
+                            net->linear_only && c.fuse_update ? &head : nullptr, net->linear_only && c.fuse_update ? &sgd : nullptr,
+                            ts.timer());
   }
   for (size_t t = 0; t < net->tensors.size(); ++t) {
     const bool have = (written[t] && !not_stored[t]) || (int)t == last.out;
@@ -1114,7 +1120,7 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
   c.lr = lr;
   // (a caller that times the update, or wants the aggregated gradient stored, gets it as a launch of its own:
   // the same sums in the same order, so the results are the same bit for bit)
-  c.fuse_update = net->linear_only && !(flags & (OMNI_STEP_NO_UPDATE | OMNI_STEP_KEEP_REDUCED_GRAD)) &&
+  c.fuse_update = !(flags & (OMNI_STEP_NO_UPDATE | OMNI_STEP_KEEP_REDUCED_GRAD)) &&
                   net->time_class != OMNI_KERNEL_UPDATE;
 
   // ---- a repeated step as a graph: replay, capture, or enqueue launch by launch
@@ -1175,7 +1181,7 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
 
   // ---- weighted aggregation + update
   float* reduced = (flags & OMNI_STEP_KEEP_REDUCED_GRAD) ? reinterpret_cast<float*>(c.ws + net->reduced_off) : nullptr;
-  if (c.fuse_update) {
+  if (net->linear_only ? c.fuse_update : c.updated) {
   } else if (!(flags & OMNI_STEP_NO_UPDATE)) {
     TimedScope ts(net, c.st, OMNI_KERNEL_UPDATE, -1, true);
     omni::weighted_sgd_f32(c.st, params, c.G, net->P_stride, net->P, c.seg, lr, nullptr, net->velocity,

@@ -1,0 +1,87 @@
+"""The update by the launch that adds the chunks of the convolutions' weight gradients: bit for bit the update as a launch of its own
+(which a caller that times it gets), with and without momentum, several steps on; workers of one chunk and of many, first layers
+with a kernel of their own and without, channel tiles that are not full, a layer whose second stage is another (no fusion)."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import GpuRun
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hw,chans,off", [
+    (32, (3, 32, 64, 128), [0, 8, 24, 56, 128]),
+    (32, (3, 32, 64, 128), [0, 1, 200, 203]),          # workers of one image
+    (32, (3, 64, 24, 40), [0, 5, 70]),                 # two blocks of first-layer channels, tiles part full
+    (32, (4, 40, 96, 64), [0, 33]),                    # 37 columns in the first layer, two channel tiles, one worker
+    (16, (3, 16, 96, 256), [0, 3, 4, 100]),            # the first layer in the patch kernel
+    (16, (3, 32, 64, 64), list(range(0, 130, 2))),     # 64 workers of two images
+])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_update_with_the_second_stage(hw, chans, off, momentum):
+    import torch
+    import paper_2503_17469_amd as omni
+    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
+    B, K = off[-1], len(off) - 1
+    b = [off[k + 1] - off[k] for k in range(K)]
+    params = synth.he_normal_params(layers, 6, True)
+    x, y = synth.make_batch(3, B, (hw, hw, chans[0]), 10, True)
+    out = []
+    for own_launch in (False, True):
+        run = GpuRun(layers, (hw, hw, chans[0]), "bf16", K, B)
+        try:
+            p = torch.from_numpy(params).cuda()
+            xs = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda().to(torch.bfloat16)
+            ys = torch.from_numpy(np.ascontiguousarray(y, dtype=np.int32)).cuda()
+            v = torch.zeros_like(p)
+            if momentum:
+                omni.net_set_momentum(run.net, v, 0.9, 5e-4)
+            if own_launch:
+                omni.net_timing_enable(run.net, "update", -1, 8)
+            for _ in range(3):
+                run.ws.fill_(255)                      # nothing is left over from the step before
+                omni.step(run.net, p, xs, ys, off, b, 0.002, run.ws, run.lpw, run.loss)
+            torch.cuda.synchronize()
+            if own_launch:
+                assert omni.net_timing_read(run.net)[1] == 3
+            out.append((p.cpu().numpy(), v.cpu().numpy(), omni.net_worker_grads(run.net, run.ws, K).cpu().numpy()[:, :params.size]))
+        finally:
+            run.close()
+    assert not np.array_equal(out[0][0], params)
+    for a, c in zip(*out):
+        assert np.array_equal(a, c)
+
+
+@pytest.mark.parametrize("momentum", [False, True])
+def test_update_follows_from_the_gradients(momentum):
+    """One step: parameters and velocity against the weighted sum of the very gradients that the launch left, by the update entry."""
+    import torch
+    import paper_2503_17469_amd as omni
+    hw, chans, off = 32, (3, 32, 64, 128), [0, 1, 24, 56, 128]
+    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
+    B, K = off[-1], len(off) - 1
+    b = [off[k + 1] - off[k] for k in range(K)]
+    params = synth.he_normal_params(layers, 6, True)
+    x, y = synth.make_batch(3, B, (hw, hw, 3), 10, True)
+    run = GpuRun(layers, (hw, hw, 3), "bf16", K, B)
+    try:
+        p = torch.from_numpy(params).cuda()
+        xs = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda().to(torch.bfloat16)
+        ys = torch.from_numpy(np.ascontiguousarray(y, dtype=np.int32)).cuda()
+        v = torch.randn(p.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(1)) * 0.01
+        p0, v0 = p.clone(), v.clone()
+        if momentum:
+            omni.net_set_momentum(run.net, v, 0.9, 5e-4)
+        omni.step(run.net, p, xs, ys, off, b, 0.05, run.ws, run.lpw, run.loss)
+        G = omni.net_worker_grads(run.net, run.ws, K)
+        full = torch.zeros(K, (params.size + 63) // 64 * 64, device="cuda")
+        full[:, :params.size] = G[:, :params.size]
+        if momentum:
+            omni.weighted_sgd_momentum(p0, v0, full, b, 0.05, 0.9, 5e-4, None)
+        else:
+            omni.weighted_sgd(p0, full, b, 0.05, None)
+        torch.cuda.synchronize()
+        assert torch.equal(p, p0) and torch.equal(v, v0)
+    finally:
+        run.close()
