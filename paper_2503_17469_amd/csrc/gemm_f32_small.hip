@@ -332,10 +332,11 @@ struct SmallWgradJob {
   float* vel;
   float* vel_bias;
   int M, N, tiles_n;
-  int first;         // first tile of the job
+  uint32_t by_tiles_n;   // see reciprocal()
 };
 struct SmallWgrad {
   int n, tiles;
+  int first[kSmallJobs];   // first tile of the jobs
   size_t worker_stride;
   SmallWgradJob job[kSmallJobs];
 };
@@ -358,7 +359,8 @@ struct WgradChunk {
 // The workgroup behind the last tile computes the losses.  SHARES: see SmallShares (UPD = 0; split_reduce_kernel follows).
 // The vector cache takes a load instruction of any width every 16 cycles, so with WB = 4 (one 4-byte and one 16-byte load
 // per four matrix instructions, 128 matrix cycles) it stays out of the way; 16 x 16 and 32 x 32 tiles with 4- and 8-byte
-// loads took twice the time.  997-501-243-37 net, 333 rows, 7 workers: 19.6 us with the update, 21.2 with momentum.
+// loads took twice the time.  997-501-243-37 net, 333 rows, 7 workers: 20.2 us with momentum (21.3 with the tables read
+// where they are used and the parameters at the end).
 template <int WB, int NW, int UPD, bool SHARES>
 __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segments seg, Lambdas lam, Optim opt,
                                                           HeadLossParams hl, SmallShares sh) {
@@ -369,6 +371,10 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   constexpr int kOwn = (kTileFloats + 255) / 256;          // elements a thread adds up (NW = 4)
   __shared__ __attribute__((aligned(16))) float red[NW == 1 ? 1 : NW][NW == 1 ? kHeadLossLdsFloats : kTileFloats + 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (A line of arguments that nothing has touched takes 640 cycles: the lanes fetch the workers' rows and weights at once.)
+  const int off_lane = seg.off[lane], off_last = seg.off[OMNI_MAX_WORKERS];
+  const float lam_lane = UPD ? lam.v[lane] : 0.f;
+  auto off = [&](int k) { return k < OMNI_MAX_WORKERS ? __builtin_amdgcn_readlane(off_lane, k) : off_last; };
   const int groups = NW == 1 ? (p.tiles + 3) / 4 : SHARES ? p.tiles * sh.first[seg.K] : p.tiles;
   if ((int)blockIdx.x == groups) {
     head_loss_body(hl, seg, &red[0][0]);
@@ -378,21 +384,22 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   const int tile = NW == 1 ? (int)blockIdx.x * 4 + wave : (int)blockIdx.x - share * p.tiles;
   if (NW == 1 && tile >= p.tiles) return;   // (no barrier below with NW = 1)
   // the rows walked: all workers' one after the other, or a share of one worker's
-  int beg0 = 0, end0 = seg.off[1];
+  int beg0 = 0, end0 = off(1);
   const int nwork = SHARES ? 1 : seg.K;
   if (SHARES) {
     int k = 0;
     while (k + 1 < seg.K && share >= sh.first[k + 1]) ++k;
-    const int at = share - sh.first[k], of = sh.first[k + 1] - sh.first[k], bk = seg.off[k + 1] - seg.off[k];
-    beg0 = seg.off[k] + (int)((long)bk * at / of);
-    end0 = seg.off[k] + (int)((long)bk * (at + 1) / of);
+    const int at = share - sh.first[k], of = sh.first[k + 1] - sh.first[k], bk = off(k + 1) - off(k);
+    beg0 = off(k) + (int)((long)bk * at / of);
+    end0 = off(k) + (int)((long)bk * (at + 1) / of);
   }
   int ji = 0;
-  for (int i = 1; i < p.n; ++i)
-    if (tile >= p.job[i].first) ji = i;
+#pragma unroll
+  for (int i = 1; i < kSmallJobs; ++i) ji += i < p.n && tile >= p.first[i] ? 1 : 0;
   const SmallWgradJob& J = p.job[ji];
-  const int local = tile - J.first;
-  const int tile_m = local / J.tiles_n, tile_n = local - tile_m * J.tiles_n;
+  const int local = tile - p.first[ji];
+  const int tile_m = J.tiles_n == 1 ? local : J.by_tiles_n ? (int)__umulhi((uint32_t)local, J.by_tiles_n) : local / J.tiles_n;
+  const int tile_n = local - tile_m * J.tiles_n;
   const int M = J.M, N = J.N;
   const int r = lane & 15, g = lane >> 4;
   const int i0 = tile_m * 16, is = min(i0 + r, M - 1);                  // column of dy (past the end: the last one, unused)
@@ -403,7 +410,7 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   // zeroed in both operands (they may be another worker's: 0 * infinity is no zero).  Every address is then a uniform base plus a lane offset that never changes.
   constexpr int kSuper = 16 * NW;
   const int wrow = NW == 1 ? 0 : 16 * wave;
-  const int last_row = seg.off[seg.K] - 1;
+  const int last_row = off(seg.K) - 1;
   uint32_t aoff[4], boff[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -467,7 +474,7 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
     settled(set);
     const int dst = SHARES ? share : w;
     float* G = J.gw + (size_t)dst * p.worker_stride;
-    const float l = UPD ? lam.v[w] : 0.f;
+    const float l = UPD ? lane_value(lam_lane, w) : 0.f;
     if (want_bias) {
       bsum += __shfl_xor(bsum, 16, 64);
       bsum += __shfl_xor(bsum, 32, 64);
@@ -526,7 +533,7 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
     k += kSuper;
     if (__builtin_expect(k >= end, 0)) {
       ++w;
-      if (w < nwork) { k = seg.off[w]; end = seg.off[w + 1]; }
+      if (w < nwork) { k = off(w); end = off(w + 1); }
     }
   };
   WgradChunk<WB> c[D];
@@ -534,6 +541,32 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   for (int d = 0; d < D; ++d) {
     load(c[d], lk, lend);
     if (lw < nwork) advance(lw, lk, lend);       // (past the last chunk: the last one again, unused)
+  }
+  // the parameters travel while the gradients are formed (loaded at the end, they were 2500 of a small network's 13500 cycles)
+  float th1[NW == 1 && UPD ? 4 : 1][WB], ve1[NW == 1 && UPD ? 4 : 1][WB], th4[kOwn], ve4[kOwn], thb = 0.f, veb = 0.f;
+  if constexpr (UPD != 0) {
+    if constexpr (NW == 1) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const size_t at = (size_t)min(i0 + 4 * g + v, M - 1) * N + js;
+        load_n<WB>(J.theta + at, th1[v]);
+        if (MOM) load_n<WB>(J.vel + at, ve1[v]);
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < kOwn; ++q) {
+        int row, col;
+        (void)place(q * 256 + tid, row, col);
+        const size_t at = (size_t)min(row, M - 1) * N + col;
+        th4[q] = J.theta[at];
+        ve4[q] = MOM ? J.vel[at] : 0.f;
+      }
+    }
+    if (want_bias) {
+      const int bi = min(i0 + (NW == 1 ? r : tid & 15), M - 1);
+      thb = J.theta_bias[bi];
+      veb = MOM ? J.vel_bias[bi] : 0.f;
+    }
   }
   int w = 0, k = beg0, end = end0;
   // (everything that does not happen in every chunk is out of line: a taken branch costs the wavefront an instruction
@@ -567,8 +600,8 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
         flush(w, d & 1);
         ++w;
         if (w == nwork) { more = false; break; }
-        k = seg.off[w];
-        end = seg.off[w + 1];
+        k = off(w);
+        end = off(w + 1);
       }
       if (__builtin_expect(lw < nwork, 1)) advance(lw, lk, lend);
     }
@@ -580,10 +613,8 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
       for (int v = 0; v < 4; ++v) {
         const int row = i0 + 4 * g + v;
         if (row >= M) continue;
-        float th[WB], ve[WB];
+        float (&th)[WB] = th1[v], (&ve)[WB] = ve1[v];
         const size_t at = (size_t)row * N + js;
-        load_n<WB>(J.theta + at, th);
-        if (MOM) load_n<WB>(J.vel + at, ve);
 #pragma unroll
         for (int j = 0; j < WB; ++j) apply_update<MOM>(th[j], ve[j], gsum[j][v], opt);
         if (js == j_nom) {
@@ -604,18 +635,16 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
         int row, col;
         if (!place(q * 256 + tid, row, col)) continue;
         const size_t at = (size_t)row * N + col;
-        float th = J.theta[at], ve = MOM ? J.vel[at] : 0.f;
-        apply_update<MOM>(th, ve, own[q], opt);
-        J.theta[at] = th;
-        if (MOM) J.vel[at] = ve;
+        apply_update<MOM>(th4[q], ve4[q], own[q], opt);
+        J.theta[at] = th4[q];
+        if (MOM) J.vel[at] = ve4[q];
       }
     }
     const int bi = i0 + (NW == 1 ? r : tid);
     if (want_bias && (NW == 1 ? g == 0 : tid < 16) && bi < M) {
-      float th = J.theta_bias[bi], ve = MOM ? J.vel_bias[bi] : 0.f;
-      apply_update<MOM>(th, ve, bgsum, opt);
-      J.theta_bias[bi] = th;
-      if (MOM) J.vel_bias[bi] = ve;
+      apply_update<MOM>(thb, veb, bgsum, opt);
+      J.theta_bias[bi] = thb;
+      if (MOM) J.vel_bias[bi] = veb;
     }
   }
 }
@@ -677,6 +706,9 @@ void small_gemm(hipStream_t st, SmallGemm p, const HeadWgradParams* head, const 
   else
     hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 1, 4>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
 }
+
+// 2^32 / d rounded up for the quotients n / d of n < `below`, 0 where it is not exact for all of them
+uint32_t reciprocal(int d, long below) { return d > 1 && below * d < 1l << 32 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; }
 
 template <int WB, int NW>
 void launch_wgrad(hipStream_t st, const SmallWgrad& p, const Segments& seg, const Lambdas& lam, const Optim& opt,
@@ -774,8 +806,9 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
       q.gw = scratch.part + j.w_off;
       q.gb = j.gb ? scratch.part + j.b_off : nullptr;
       q.tiles_n = (j.cin + TN - 1) / TN;
-      q.first = p.tiles;
+      p.first[i] = p.tiles;
       p.tiles += (j.cout + 15) / 16 * q.tiles_n;
+      q.by_tiles_n = reciprocal(q.tiles_n, p.tiles - p.first[i]);
     }
     if (timer) (void)hipEventRecord(timer->start, st);
     hipLaunchKernelGGL((small_wgrad_kernel<4, 4, 0, true>), dim3(p.tiles * sh.first[seg.K] + (loss ? 1 : 0)), dim3(256), 0, st,
@@ -805,8 +838,9 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
         if (sgd->velocity) { q.vel = sgd->velocity + j.w_off; q.vel_bias = sgd->velocity + j.b_off; }
       }
       q.tiles_n = (j.cin + TN - 1) / TN;
-      q.first = p.tiles;
+      p.first[i] = p.tiles;
       p.tiles += (j.cout + 15) / 16 * q.tiles_n;
+      q.by_tiles_n = reciprocal(q.tiles_n, p.tiles - p.first[i]);
     }
     const bool last = base + kSmallJobs >= n;
     const HeadLossParams hl = loss ? *loss : HeadLossParams{};
