@@ -119,6 +119,21 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
   };
+  // What the results are combined with at the end travels beside the last products.
+  constexpr int kOut = (T * T / 8 + 255) / 256;   // eight neighbouring results each of a thread, all in the same columns
+  static_assert(256 % (T / 8) == 0, "the same columns");
+  float bias[8];
+  u32x4 mask[kOut];
+  auto fetch_rest = [&]() {
+    const int col = min(col0 + tid % (T / 8) * 8, N - 8);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) bias[q] = p.bias ? p.bias[col + q] : 0.f;
+#pragma unroll
+    for (int o = 0; o < kOut; ++o)
+      mask[o] = p.mask ? *reinterpret_cast<const u32x4*>(p.mask + (size_t)min(row0 + (o * 256 + tid) / (T / 8), M - 1) * N + col)
+                       : u32x4{0u, 0u, 0u, 0u};
+  };
+  if (ce <= cb) fetch_rest();
   if (ce > cb) {
     // (a chunk past this wavefront's last one is that one again, unused: loads are never conditional)
 #pragma unroll
@@ -137,6 +152,7 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
     for (int d = 0; d < D; ++d)
       if (ch + d < ce) {
         stage(d, ch + d);
+        if (ch + d == ce - 1) fetch_rest();   // (not earlier: the chunks under way take all registers)
         multiply();
       }
   }
@@ -169,7 +185,7 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
     const size_t idx = (size_t)row * N + col;
     if (p.bias) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) y[q] += p.bias[col + q];
+      for (int q = 0; q < 8; ++q) y[q] += bias[q];
     }
     if (p.relu) {
 #pragma unroll
@@ -177,7 +193,10 @@ __device__ __forceinline__ void bf16_gemm_body(const BfGemm& p, int block, uint3
     }
     if (p.mask) {
       float m[8];
-      Piece<bf16_t>::load(p.mask + idx, m);
+      for (int q = 0; q < 4; ++q) {
+        m[2 * q] = bf16_lo(mask[e0 / 256][q]);
+        m[2 * q + 1] = bf16_hi(mask[e0 / 256][q]);
+      }
 #pragma unroll
       for (int q = 0; q < 8; ++q) y[q] = m[q] > 0.f ? y[q] : 0.f;
     }
