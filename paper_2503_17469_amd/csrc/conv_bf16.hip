@@ -30,8 +30,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "bf16.h"
+#include "cast_device.h"
 #include "common.h"
 #include "conv_device.h"
 #include "kernels.h"
@@ -702,11 +704,55 @@ struct Conv1Params {
   bf16_t* pool;        // may be null: [rows*(H/2)*(W/2)][N], the 2 x 2 max pooling of `out`
   uint8_t* pool_code;  // with pool: one byte per pooled element (see pool_code_of)
   int raw3;            // src is [rows][H][W][3]: a pixel is three 2-byte loads, channels 3-7 are zero
+  int lw, lr;          // W = 1 << lw, R = 1 << lr
+  uint32_t by_patch, by_pw, by_upi;   // 2^32 / (PR PW), / PW and / (H / R), rounded up; the last 0 where it would not be exact
 };
 
-template <int NBLK>   // 32-channel blocks of output channels: 1 or 2
-__global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
+// The copies of the other layers' weights ride in front of the units (CAST): they were 5 us as a launch of their own, most of it
+// its start and end, and nothing reads them before the next launch (32-64-128 net on 32 x 32 images: 128 rows 88.3 -> 83.1 us,
+// 1024 rows 209 -> 203 us; 11 M parameters: the same).  The layer's own weights then come from the parameters,
+// and absent pieces are zeroed in registers: the zero page is cleared by this launch.
+struct Conv1Casts {
+  const float* w;      // this layer's weights [N][9][cin]
+  int cin;
+  int blocks;          // workgroups that copy
+  const float* params;
+  bf16_t* shadow;
+  uint32_t* zero_page;
+  CastTable tab;
+};
+struct NoCasts {};
+
+// Eight channels of a tap: `cin` real ones, the rest zero.  (3 channels is what images have; otherwise no load is conditional)
+__device__ __forceinline__ u32x4 weights8(const float* w, int cin, bool in) {
+  float t[8];
+  if (cin == 3) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) t[c] = c < 3 ? w[c] : 0.f;
+  } else {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float v = w[min(c, cin - 1)];
+      t[c] = c < cin ? v : 0.f;
+    }
+  }
+  u32x4 q;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) q[d] = in ? pack_bf16(t[2 * d], t[2 * d + 1]) : 0u;
+  return q;
+}
+
+template <int NBLK, bool CAST>   // 32-channel blocks of output channels: 1 or 2
+__global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, std::conditional_t<CAST, Conv1Casts, NoCasts> casts) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
+  int block = (int)blockIdx.x;
+  if constexpr (CAST) {
+    if (block < casts.blocks) {
+      cast_weights_body(casts.tab, casts.params, casts.shadow, casts.zero_page, block, reinterpret_cast<bf16_t*>(smemF));
+      return;
+    }
+    block -= casts.blocks;
+  }
   constexpr int NT = 32 * NBLK;
   constexpr int kPitch = NT + 8;   // bf16 elements per staged output row
   const int W = p.W, H = p.H, R = p.R;
@@ -726,7 +772,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
     for (int ks = 0; ks < 5; ++ks) {
       const int tap = 2 * ks + h, co = 32 * b + j;
       const bool in = tap < 9 && co < p.N;
-      wf[b][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(in ? p.wgt + ((size_t)co * 9 + tap) * 8 : zp));
+      if constexpr (CAST) wf[b][ks] = as_bf16x8(weights8(casts.w + (in ? (co * 9 + tap) * casts.cin : 0), casts.cin, in));
+      else wf[b][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(in ? p.wgt + ((size_t)co * 9 + tap) * 8 : zp));
     }
   float bj[NBLK];
 #pragma unroll
@@ -738,8 +785,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int x = min(tid + t * kThreads, npatch - 1);
-    const int il = x / (PR * PW), rem = x - il * (PR * PW);
-    const int pr = rem / PW, pc = rem - pr * PW;
+    const int il = (int)__umulhi((uint32_t)x, p.by_patch), rem = x - il * (PR * PW);
+    const int pr = (int)__umulhi((uint32_t)rem, p.by_pw), pc = rem - pr * PW;
     pil[t] = il; ppr[t] = pr;
     pcol[t] = tid + t * kThreads < npatch && pc >= 1 && pc <= W;
     prel[t] = ((il * H + pr - 1) * W + pc - 1) * (p.raw3 ? 3 : 8);
@@ -749,8 +796,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
     const int pos = wave * 64 + a * 32 + j;
-    const int rr = pos / W, w = pos - rr * W;
-    const int il = rr / R, r = rr - il * R;
+    const int rr = pos >> p.lw, w = pos & (W - 1);
+    const int il = rr >> p.lr, r = rr & (R - 1);
     pbase[a] = (il * PR + r) * PW + w;
   }
   int toff[5];
@@ -762,7 +809,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
 
   auto unit_geom = [&](int unit, int& n0, int& r0, int& nvalid) {
     if (p.nimg == 1) {
-      const int upi = H / R, img = unit / upi;
+      const int upi = H >> p.lr;
+      const int img = upi == 1 ? unit : p.by_upi ? (int)__umulhi((uint32_t)unit, p.by_upi) : unit / upi;
       n0 = img; r0 = (unit - img * upi) * R; nvalid = 1;
     } else {
       n0 = unit * p.nimg; r0 = 0; nvalid = min(p.nimg, p.rows - n0);
@@ -777,13 +825,14 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
     for (int t = 0; t < 2; ++t) {
       const int row = r0 + ppr[t] - 1;
       const bool in = pcol[t] && pil[t] < nvalid && row >= 0 && row < H;
-      const bf16_t* q = in ? p.src + (ubase + prel[t]) : zp;
+      const bf16_t* q = in ? p.src + (ubase + prel[t]) : CAST ? p.src : zp;
       if (p.raw3) rp[t] = u32x4{(uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2], 0u, 0u};
       else rp[t] = *reinterpret_cast<const u32x4*>(q);
+      if (CAST && !in) rp[t] = u32x4{0u, 0u, 0u, 0u};
     }
   };
 
-  const int ubeg = blockIdx.x * p.upw, uend = min(p.units, ubeg + p.upw);
+  const int ubeg = block * p.upw, uend = min(p.units, ubeg + p.upw);
   load_patch(min(ubeg, p.units - 1));
   for (int unit = ubeg; unit < uend; ++unit) {
 #pragma unroll
@@ -849,9 +898,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p) {
         const int c = tid + kThreads * it;
         const int q = c / kPieces, jl = (c % kPieces) * 8;
         if (q >= npool || jl >= p.N) continue;
-        const int img = q / (Rh * Wh), rem = q - img * (Rh * Wh);
-        const int pr = rem / Wh, pw = rem - pr * Wh;
-        const bf16_t* s0 = so + ((img * R + 2 * pr) * W + 2 * pw) * kPitch + jl;
+        const int pw = q & (Wh - 1), ir = q >> (p.lw - 1);   // (an image's rows follow the image's before, halved as they are)
+        const bf16_t* s0 = so + (2 * ir * W + 2 * pw) * kPitch + jl;
         float a[8], b[8], cc[8], d[8], m[8];
         Piece<bf16_t>::load(s0, a);
         Piece<bf16_t>::load(s0 + kPitch, b);
@@ -956,9 +1004,13 @@ static bool conv1_fwd_shape(int N, const ConvGeom& g, long M) {
   return nimg * (R + 2) * (W + 2) <= 2 * kThreads;
 }
 
+static uint32_t reciprocal_below(uint32_t d, uint64_t below) {   // 2^32 / d rounded up, 0 where it is not exact for all n < below
+  return below * d < 1ull << 32 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u;
+}
+
 static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                       const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                      bf16_t* pool, uint8_t* pool_code, bool* pooled) {
+                      bf16_t* pool, uint8_t* pool_code, bool* pooled, const Conv1Casts* casts = nullptr) {
   const int H = g.Hs, W = g.Ws;
   if (mask || accumulate || !conv1_fwd_shape(N, g, M)) return false;
   const int R = std::min(H, kUnitD / W);
@@ -972,14 +1024,37 @@ static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16
   p.pool_code = pool_code;
   *pooled = p.pool != nullptr;
   p.units = nimg == 1 ? g.rows * (H / R) : (g.rows + nimg - 1) / nimg;
+  p.lw = __builtin_ctz(W); p.lr = __builtin_ctz(R);   // (both divide 256)
+  p.by_patch = reciprocal_below((R + 2) * (W + 2), 2 * kThreads);
+  p.by_pw = reciprocal_below(W + 2, 2 * kThreads);
+  p.by_upi = reciprocal_below(H / R, p.units);
   p.upw = 1;
   while (p.upw < 8 && p.units / (p.upw * 2) >= 1024) p.upw *= 2;
   const int nblk = N > 32 ? 2 : 1;
   const size_t lds = (size_t)((npatch + 3) & ~3) * 16 + (size_t)kUnitD * (32 * nblk + 8) * sizeof(bf16_t);
-  const dim3 grid((p.units + p.upw - 1) / p.upw);
-  if (nblk == 2) hipLaunchKernelGGL(conv1_fwd_kernel<2>, grid, dim3(kThreads), lds, st, p);
-  else hipLaunchKernelGGL(conv1_fwd_kernel<1>, grid, dim3(kThreads), lds, st, p);
+  static_assert(kUnitD * 40 >= kCastTile * kCastStride, "a copied tile fits the staged output");
+  const dim3 grid((p.units + p.upw - 1) / p.upw + (casts ? casts->blocks : 0)), block(kThreads);
+  if (casts) {
+    if (nblk == 2) hipLaunchKernelGGL((conv1_fwd_kernel<2, true>), grid, block, lds, st, p, *casts);
+    else hipLaunchKernelGGL((conv1_fwd_kernel<1, true>), grid, block, lds, st, p, *casts);
+  } else {
+    if (nblk == 2) hipLaunchKernelGGL((conv1_fwd_kernel<2, false>), grid, block, lds, st, p, NoCasts{});
+    else hipLaunchKernelGGL((conv1_fwd_kernel<1, false>), grid, block, lds, st, p, NoCasts{});
+  }
   return true;
+}
+
+bool conv_first_layer_takes_casts(int Cout, const ConvGeom& g, long M) { return conv1_fwd_shape(Cout, g, M); }
+
+bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, int cin_real, bf16_t* shadow,
+                                const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
+                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code) {
+  Conv1Casts c{};
+  c.w = params + w_off; c.cin = cin_real; c.params = params; c.shadow = shadow; c.zero_page = zero_page;
+  c.blocks = cast_table(c.tab, entries, n);
+  bool pooled = false;
+  conv1_fwd(st, src, nullptr, out, M, N, g, bias, nullptr, relu, false, pool, pool_code, &pooled, &c);
+  return pooled;
 }
 
 bool conv_first_layer_raw_supported(int Cout, int cin_real, const ConvGeom& g, long M) {

@@ -288,9 +288,17 @@ struct CastTable {
   int n;
   CastEntry e[kCastMaxEntries];
 };
+// The table of n <= kCastMaxEntries copies; returns the number of workgroups (256 threads) that make them.
+int cast_table(CastTable& tab, const CastEntry* entries, int n);
 // zero_page (may be null): kZeroPageWords words that the same launch sets to zero.
 void cast_weights_bf16(hipStream_t st, const float* params, bf16_t* shadow, const CastEntry* entries, int n,
                        uint32_t* zero_page = nullptr);
+// The first layer's forward pass, if it is one of three channels stored as eight or unpadded (conv_first_layer_takes_casts):
+// one launch that also makes the other layers' copies and clears the zero page.  Its own weights come from `params` at w_off.
+bool conv_first_layer_takes_casts(int Cout, const ConvGeom& g, long M);
+bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, int cin_real, bf16_t* shadow,
+                                const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
+                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code);
 void pad_channels_bf16(hipStream_t st, const bf16_t* x, bf16_t* xp, long pixels, int c_real, int c_pad);
 void maxpool2_fwd_bf16(hipStream_t st, const bf16_t* in, bf16_t* out, int rows, int H, int W, int C);
 // din = dout routed to the first maximum of each 2x2 window (scan order), zero elsewhere;

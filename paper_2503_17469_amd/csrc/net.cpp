@@ -720,11 +720,23 @@ void step_bf16(StepCtx& c) {
     if (sc >= 0) s2_frag[sc] = s2_frag[m];
   }
 
-  // ---- bf16 copies of the weights (forward layout, and transposed for dgrad)
+  // ---- bf16 copies of the weights (forward layout, and transposed for dgrad).  The forward launch of a first layer that
+  // reads the network's input takes them along and needs no copy of its own weights.
+  int first = 0;
+  while (first < n_layers - 1 && net->layers[first].fused_away) ++first;
+  const Layer& F = net->layers[first];
+  bool ridden = false;
+  std::vector<omni::CastEntry> casts;
   {
-    std::vector<omni::CastEntry> casts;
+    if (F.d.op == OMNI_OP_CONV && F.in0 < 0 && !F.need_dgrad && first < n_layers - 1 && !frag_fwd(F)) {
+      const Tensor& to = net->tensors[F.out];
+      int weights = 0;
+      for (const Layer& L : net->layers) weights += is_param_op(L.d.op) ? 1 : 0;
+      ridden = weights - 1 <= omni::kCastMaxEntries &&
+               omni::conv_first_layer_takes_casts(F.d.cout, fwd_geom(F), (long)rows * to.h * to.w);
+    }
     for (const Layer& L : net->layers) {
-      if (!is_param_op(L.d.op)) continue;
+      if (!is_param_op(L.d.op) || (ridden && &L == &F)) continue;
       omni::CastEntry e{};
       e.src = (long)L.w_off; e.dst_fwd = (long)L.wsh_off; e.dst_t = L.need_dgrad ? (long)L.wt_off : -1;
       e.cout = L.d.cout;
@@ -739,7 +751,7 @@ void step_bf16(StepCtx& c) {
     }
     // (the same launch clears the few bytes of zeros that loads of absent pieces are pointed at: the workspace
     // is the caller's memory, so nothing in it is taken to have survived since the last step)
-    omni::cast_weights_bf16(st, c.params, shadow, casts.data(), (int)casts.size(), conv_counters);
+    if (!ridden) omni::cast_weights_bf16(st, c.params, shadow, casts.data(), (int)casts.size(), conv_counters);
   }
 
   // ---- forward over the concatenated batch
@@ -775,12 +787,16 @@ void step_bf16(StepCtx& c) {
         continue;
       }
       omni::BnStatRequest offer{bn_partial, &c.seg, nullptr, nullptr, {}, false};
+      const float* bias = L.has_b ? c.params + L.b_off : nullptr;
+      bf16_t* pool = pool_next ? actw(net->layers[nx].out) : nullptr;
+      uint8_t* code = pool_next ? reinterpret_cast<uint8_t*>(c.ws + net->layers[nx].code_off) : nullptr;
       const bool pooled =
-          omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g,
-                               L.has_b ? c.params + L.b_off : nullptr, nullptr, to.relu, false,
-                               pool_next ? actw(net->layers[nx].out) : nullptr,
-                               pool_next ? reinterpret_cast<uint8_t*>(c.ws + net->layers[nx].code_off) : nullptr,
-                               nullptr, bn_next ? &offer : nullptr);
+          ridden && i == first
+              ? omni::conv_first_layer_and_casts(st, act(L.in0), c.params, L.w_off, L.d.cin, shadow, casts.data(),
+                                                 (int)casts.size(), conv_counters, actw(L.out), rows * to.h * to.w, L.d.cout,
+                                                 g, bias, to.relu, pool, code)
+              : omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g, bias,
+                                     nullptr, to.relu, false, pool, code, nullptr, bn_next ? &offer : nullptr);
       if (pooled) { pooled_layer = nx; coded[nx] = 1; }
       if (bn_next && offer.done) { presummed = offer.table; presummed_for = nx; }
     } else if (L.d.op == OMNI_OP_MAXPOOL2) {

@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "bf16.h"
+#include "cast_device.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -12,78 +13,10 @@ namespace omni {
 
 namespace {
 
-// All layers' weight copies in one launch: with a few thousand weights per layer a launch per
-// layer is pure launch latency (4 x 4.6 us at the three-layer CNN).  The table travels in the
-// kernel arguments.
-// Bound by HBM (4 bytes read, 2 or 4 written per weight).  A workgroup takes 64 x 64 weights of one filter
-// tap through LDS, so that the transposed copy leaves in 32-byte pieces of whole rows; one thread per weight
-// scattered it as 2-byte stores a row apart: 87 us for the 11.2 M weights of the ResNet-18 shape, 17 us for
-// the 4.2 M of the 3072-1024-1024 MLP.
-constexpr int kCastTile = 64;
-constexpr int kCastStride = kCastTile + 2;   // halfwords; odd in words, so a column of the tile spreads over the banks
-
-// Offset of the piece of eight channels that starts at c of output n in a copy laid out as matrix operands
-// (conv_frag_bf16): blocks [n/32][tap][c/16] of 64 lanes x 8 elements.
-__device__ inline long frag_offset(int n, int tap, int c, int taps, int channels) {
-  return (((long)(n >> 5) * taps + tap) * (channels >> 4) + (c >> 4)) * 512 + ((n & 31) + 32 * ((c >> 3) & 1)) * 8;
-}
-
 __global__ __launch_bounds__(256) void cast_weights_kernel(CastTable tab, const float* __restrict__ params,
                                                            bf16_t* __restrict__ shadow, uint32_t* __restrict__ zero_page) {
   __shared__ __attribute__((aligned(16))) bf16_t tile[kCastTile * kCastStride];
-  const int tid = threadIdx.x;
-  if (zero_page && blockIdx.x == 0 && tid < kZeroPageWords) zero_page[tid] = 0u;
-  int e = 0;
-  while (e + 1 < tab.n && (int)blockIdx.x >= tab.e[e + 1].first_block) ++e;
-  const CastEntry t = tab.e[e];
-  const int ci_tiles = (t.cin_pad + kCastTile - 1) / kCastTile;
-  int local = (int)blockIdx.x - t.first_block;
-  const int ci0 = local % ci_tiles * kCastTile;
-  local /= ci_tiles;
-  const int tap = local % t.taps, co0 = local / t.taps * kCastTile;
-
-  const int cl = (tid & 15) * 4, ci = ci0 + cl, r = tid >> 4;
-  v4f v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int co = co0 + r + 16 * i;
-    v[i] = v4f{0.f, 0.f, 0.f, 0.f};
-    if (co < t.cout) {
-      const float* src = params + t.src + ((long)co * t.taps + tap) * t.cin_real + ci;
-      if (ci + 3 < t.cin_real) {
-        v[i] = *reinterpret_cast<const v4f_a4*>(src);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (ci + q < t.cin_real) v[i][q] = src[q];
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int co = co0 + r + 16 * i;
-    const u32x2 w = {pack_bf16(v[i][0], v[i][1]), pack_bf16(v[i][2], v[i][3])};
-    if (co < t.cout && ci < t.cin_pad)
-      *reinterpret_cast<u32x2*>(shadow + t.dst_fwd +
-                                (t.frag_fwd ? frag_offset(co, tap, ci, t.taps, t.cin_pad) + (ci & 7)
-                                            : ((long)co * t.taps + tap) * t.cin_pad + ci)) = w;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      tile[(cl + q) * kCastStride + r + 16 * i] = (bf16_t)(w[q >> 1] >> (16 * (q & 1)));
-  }
-  if (t.dst_t < 0) return;
-  __syncthreads();
-  // rows of the transposed copy: output channels are a multiple of 8 wherever there is one
-  const int tr = tid >> 2, tc = (tid & 3) * 16;
-  if (ci0 + tr >= t.cin_pad) return;
-  const uint32_t* row = reinterpret_cast<const uint32_t*>(tile + tr * kCastStride + tc);
-  bf16_t* dst = shadow + t.dst_t + (t.frag_t ? frag_offset(ci0 + tr, tap, co0 + tc, t.taps, t.cout)
-                                             : ((long)(ci0 + tr) * t.taps + tap) * t.cout + co0 + tc);
-  const int second = t.frag_t ? 32 * 8 : 8;   // from one piece of eight channels to the next
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-    if (co0 + tc + 8 * h < t.cout)
-      *reinterpret_cast<u32x4*>(dst + second * h) = u32x4{row[4 * h], row[4 * h + 1], row[4 * h + 2], row[4 * h + 3]};
+  cast_weights_body(tab, params, shadow, zero_page, (int)blockIdx.x, tile);
 }
 
 __global__ __launch_bounds__(256) void pad_channels_kernel(const bf16_t* __restrict__ x, bf16_t* __restrict__ xp,
@@ -196,18 +129,23 @@ inline unsigned blocks_for(long n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
+int cast_table(CastTable& tab, const CastEntry* entries, int n) {
+  tab.n = n;
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    tab.e[i] = entries[i];
+    tab.e[i].first_block = blocks;
+    blocks += (tab.e[i].cout + kCastTile - 1) / kCastTile * tab.e[i].taps *
+              ((tab.e[i].cin_pad + kCastTile - 1) / kCastTile);
+  }
+  return blocks;
+}
+
 void cast_weights_bf16(hipStream_t st, const float* params, bf16_t* shadow, const CastEntry* entries, int n,
                        uint32_t* zero_page) {
   for (int base = 0; base < n; base += kCastMaxEntries) {
     CastTable tab{};
-    tab.n = std::min(n - base, kCastMaxEntries);
-    int blocks = 0;
-    for (int i = 0; i < tab.n; ++i) {
-      tab.e[i] = entries[base + i];
-      tab.e[i].first_block = blocks;
-      blocks += (tab.e[i].cout + kCastTile - 1) / kCastTile * tab.e[i].taps *
-                ((tab.e[i].cin_pad + kCastTile - 1) / kCastTile);
-    }
+    const int blocks = cast_table(tab, entries + base, std::min(n - base, kCastMaxEntries));
     if (blocks > 0)
       hipLaunchKernelGGL(cast_weights_kernel, dim3(blocks), dim3(256), 0, st, tab, params, shadow,
                          base == 0 ? zero_page : nullptr);
