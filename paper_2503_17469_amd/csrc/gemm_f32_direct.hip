@@ -60,16 +60,22 @@ struct DirectParams {
 constexpr int kBlk = 32 * 36;
 struct Staged { v4f a[4], b0[4], b1[4]; };   // b0/b1 unused by dgrad (row-contiguous B is loaded directly)
 
-// LDS of one workgroup, in floats: the wavefronts' staging blocks, then their partial tiles.
+// LDS of one workgroup, in floats: a wavefront's staging blocks, at the end its partial tile in their place.  (Room for two
+// workgroups in a compute unit, so that the launch bounds can cap the registers at 256: see gemm_f32_direct_kernel.)
+template <bool DGRAD>
+constexpr int direct_wave_floats() { return (DGRAD ? 1 : 3) * kBlk > 32 * 64 ? (DGRAD ? 1 : 3) * kBlk : 32 * 64; }
 template <bool DGRAD, int NW>
-constexpr int direct_lds_floats() { return NW * (DGRAD ? 1 : 3) * kBlk + NW * 32 * 64; }
+constexpr int direct_lds_floats() { return NW * direct_wave_floats<DGRAD>(); }
 
 // Workgroup `tile_index` of `n_tiles` (64 * NW threads); smem holds direct_lds_floats() floats, 16-byte aligned.
-template <bool DGRAD, int NW>
+// CHUNKS: two steps are summed by themselves, from zero, and added while the next two are multiplied (two sets in turn), as
+// the small kernels do.  One chain over the wavefront's quarter of the reduction has 2.0 (1024 elements) to 3.4 times (3072) the
+// error against float64; the sums cost 2 per cent (480 rows, 3072-1024-1024-10: step 111.3 -> 113.7 us).
+template <bool DGRAD, int NW, bool CHUNKS>
 __device__ __forceinline__ void gemm_f32_direct_body(const DirectParams& p, int tile_index, int n_tiles, float* smem) {
-  constexpr int kWave = (DGRAD ? 1 : 3) * kBlk;
+  constexpr int kWave = direct_wave_floats<DGRAD>();
   float* stage = smem;
-  float (*red)[32 * 64] = reinterpret_cast<float (*)[32 * 64]>(smem + NW * kWave);
+  float (*red)[kWave] = reinterpret_cast<float (*)[kWave]>(smem);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, h = lane >> 5;
   const int lrow = lane >> 3, lpiece = lane & 7;
@@ -98,9 +104,9 @@ __device__ __forceinline__ void gemm_f32_direct_body(const DirectParams& p, int 
   float* wl_w = wl + lrow * 36 + lpiece * 4;   // where this lane writes row lrow (+8i) of a block
   const float* wl_r = wl + r * 36 + h * 16;    // where this lane reads its 16 reduction elements of row r
 
-  v16f acc0, acc1;
+  v16f acc0, acc1, S0, S1, T0, T1, zero;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) { acc0[v] = 0.f; acc1[v] = 0.f; }
+  for (int v = 0; v < 16; ++v) { acc0[v] = 0.f; acc1[v] = 0.f; S0[v] = 0.f; S1[v] = 0.f; T0[v] = 0.f; T1[v] = 0.f; zero[v] = 0.f; }
 
   Staged G, F0, F1;
   v2f B0[16], B1[16];   // dgrad: columns (2r, 2r+1) of the lane's 16 reduction rows
@@ -131,26 +137,30 @@ __device__ __forceinline__ void gemm_f32_direct_body(const DirectParams& p, int 
     else if ((j) < 8) F.b0[(j) & 3] = *reinterpret_cast<const v4f*>(wl_r + kBlk + 4 * ((j) & 3)); \
     else F.b1[(j) & 3] = *reinterpret_cast<const v4f*>(wl_r + 2 * kBlk + 4 * ((j) & 3));        \
   }
-#define OMNI_MMA1(F, BV, e)                                                                     \
+#define OMNI_MMA1(F, BV, e, S, first)                                                                   \
   {                                                                                             \
     const float av = F.a[(e) >> 2][(e) & 3];                                                    \
     float bv0, bv1;                                                                             \
     if constexpr (DGRAD) { bv0 = BV[(e)][0]; bv1 = BV[(e)][1]; }                                \
     else { bv0 = F.b0[(e) >> 2][(e) & 3]; bv1 = F.b1[(e) >> 2][(e) & 3]; }                      \
-    acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv0, acc0, 0, 0, 0);                        \
-    acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv1, acc1, 0, 0, 0);                        \
+    S##0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv0, (e) == 0 && first ? zero : S##0, 0, 0, 0);      \
+    S##1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv1, (e) == 0 && first ? zero : S##1, 0, 0, 0);      \
   }
-  // One step: multiply (FC, BC) while the data of the next step (in G) goes
+  // One step: multiply (FC, BC) into set S (`first`: from zero, and set T is added to the rest meanwhile) while the data of the next step (in G) goes
   // through LDS into (FN), G is refilled from step `gstep`, and (dgrad) BN is
   // loaded for step `bstep`.  (A second G set, giving loads two steps to arrive,
   // measured no faster.)  Forward: 12 writes, 12 reads, 12 loads over 16
   // slots; dgrad: 4 + 4 + 4 and one B load per slot.
-#define OMNI_STEP(FC, BC, FN, BN, G, gstep, bstep)                                                 \
+#define OMNI_STEP(FC, BC, S, T, first, FN, BN, G, gstep, bstep)                                           \
   {                                                                                             \
     const int gk0 = min((gstep), nsteps - 1) * kStep;                                           \
     const float* bp = DGRAD ? bcol + (size_t)(min((bstep), nsteps - 1) * kStep) * p.ldb : nullptr; \
     _Pragma("unroll") for (int e = 0; e < 16; ++e) {                                            \
-      OMNI_MMA1(FC, BC, e)                                                                      \
+      OMNI_MMA1(FC, BC, e, S, first)                                                                   \
+      if (first && e >= 8) {                                                                             \
+        acc0[2 * e - 16] += T##0[2 * e - 16]; acc0[2 * e - 15] += T##0[2 * e - 15];             \
+        acc1[2 * e - 16] += T##1[2 * e - 16]; acc1[2 * e - 15] += T##1[2 * e - 15];             \
+      }                                                                                         \
       if constexpr (DGRAD) {                                                                    \
         BN[e] = *reinterpret_cast<const v2f*>(bp + (size_t)e * p.ldb);                          \
         if (e < 4) OMNI_LWRITE1(G, e)                                                              \
@@ -175,27 +185,61 @@ __device__ __forceinline__ void gemm_f32_direct_body(const DirectParams& p, int 
     const int k0 = min(sbeg, nsteps - 1) * kStep;
 #pragma unroll
     for (int j = 0; j < kOps; ++j) OMNI_GLOAD1(G, j, k0)
-    if constexpr (DGRAD) {
-      const float* bp = bcol + (size_t)k0 * p.ldb;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) B0[e] = *reinterpret_cast<const v2f*>(bp + (size_t)e * p.ldb);
-    }
 #pragma unroll
     for (int j = 0; j < kOps; ++j) OMNI_LWRITE1(G, j)
     const int k1 = min(sbeg + 1, nsteps - 1) * kStep;
+    // (in the order the loop has them: the first operation of a step then waits for its own loads only, not for all of them)
+    const float* bp = DGRAD ? bcol + (size_t)k0 * p.ldb : nullptr;
 #pragma unroll
-    for (int j = 0; j < kOps; ++j) OMNI_GLOAD1(G, j, k1)
+    for (int e = 0; e < 16; ++e) {
+      if constexpr (DGRAD) {
+        B0[e] = *reinterpret_cast<const v2f*>(bp + (size_t)e * p.ldb);
+        if (e >= 4 && e < 8) OMNI_GLOAD1(G, e - 4, k1)
+      } else {
+        if (e < 12) OMNI_GLOAD1(G, e, k1)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int j = 0; j < kOps; ++j) OMNI_LREAD1(F0, j)
   }
   int s = sbeg;
-  for (; s + 1 < send; s += 2) {
-    OMNI_STEP(F0, B0, F1, B1, G, s + 2, s + 1)
-    OMNI_STEP(F1, B1, F0, B0, G, s + 3, s + 2)
-  }
-  if (s < send) {
+  if constexpr (CHUNKS) {
+    for (; s + 3 < send; s += 4) {
+      OMNI_STEP(F0, B0, S, T, true, F1, B1, G, s + 2, s + 1)
+      OMNI_STEP(F1, B1, S, T, false, F0, B0, G, s + 3, s + 2)
+      OMNI_STEP(F0, B0, T, S, true, F1, B1, G, s + 4, s + 3)
+      OMNI_STEP(F1, B1, T, S, false, F0, B0, G, s + 5, s + 4)
+    }
+    asm volatile("" : "+v"(T0), "+v"(T1));   // (the compiler moved these two sums into the loop)
+    acc0 += T0;
+    acc1 += T1;
+    if (s + 1 < send) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) OMNI_MMA1(F0, B0, e)
+      for (int v = 0; v < 16; ++v) T0[v] = T1[v] = 0.f;
+      OMNI_STEP(F0, B0, S, T, true, F1, B1, G, s + 2, s + 1)
+      OMNI_STEP(F1, B1, S, T, false, F0, B0, G, s + 3, s + 2)
+      acc0 += S0;
+      acc1 += S1;
+      s += 2;
+    }
+    if (s < send) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) OMNI_MMA1(F0, B0, e, S, true)
+      acc0 += S0;
+      acc1 += S1;
+    }
+  } else {
+    for (; s + 1 < send; s += 2) {
+      OMNI_STEP(F0, B0, S, T, false, F1, B1, G, s + 2, s + 1)
+      OMNI_STEP(F1, B1, S, T, false, F0, B0, G, s + 3, s + 2)
+    }
+    if (s < send) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) OMNI_MMA1(F0, B0, e, S, false)
+    }
+    acc0 = S0;
+    acc1 = S1;
   }
 #undef OMNI_GLOAD1
 #undef OMNI_LWRITE1
@@ -254,17 +298,20 @@ __device__ __forceinline__ void gemm_f32_direct_body(const DirectParams& p, int 
   }
 }
 
-template <bool DGRAD, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_direct_kernel(DirectParams p) {
+// (Capped at 256 registers the compiler keeps the sums in ordinary ones; without, a chunk's were copied out of the
+// accumulation registers one by one in front of the next chunk.)
+template <bool DGRAD, int NW, bool CHUNKS>
+__global__ __launch_bounds__(64 * NW, 2) void gemm_f32_direct_kernel(DirectParams p) {
   __shared__ __attribute__((aligned(16))) float smem[direct_lds_floats<DGRAD, NW>()];
-  gemm_f32_direct_body<DGRAD, NW>(p, (int)blockIdx.x, (int)gridDim.x, smem);
+  gemm_f32_direct_body<DGRAD, NW, CHUNKS>(p, (int)blockIdx.x, (int)gridDim.x, smem);
 }
 
 // Two independent kernels of the fp32 backward pass in one launch: the input gradient of the layer
 // below the classifier, and the classifier's own parameter gradients with the losses (both need
 // only the head's output gradient).  Launched one after the other, the second starts when the first has drained;
 // the product has fewer tiles than the chip has room for, and the head's short workgroups run beside them.
-__global__ __launch_bounds__(256) void dgrad_and_head_wgrad_kernel(DirectParams p, int tiles, HeadRole head, Segments seg) {
+template <bool CHUNKS>
+__global__ __launch_bounds__(256, 2) void dgrad_and_head_wgrad_kernel(DirectParams p, int tiles, HeadRole head, Segments seg) {
   constexpr int kFloats = direct_lds_floats<true, 4>() > kHeadWgradLdsFloats ? direct_lds_floats<true, 4>()
                                                                               : kHeadWgradLdsFloats;
   __shared__ __attribute__((aligned(16))) float smem[kFloats];
@@ -272,27 +319,35 @@ __global__ __launch_bounds__(256) void dgrad_and_head_wgrad_kernel(DirectParams 
   if (b < head.blocks)
     head_wgrad_loss_body<float, 2>(head.p, seg, b, head.gx, smem);
   else
-    gemm_f32_direct_body<true, 4>(p, b - head.blocks, tiles, smem);
+    gemm_f32_direct_body<true, 4, CHUNKS>(p, b - head.blocks, tiles, smem);
 }
 
 inline bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
+
+// With fewer of this kernel's tiles the small kernels are the alternative, and the sums must be no worse than theirs.
+bool chunked_shape(int rows, int cols) { return (long)((rows + 31) / 32) * ((cols + 63) / 64) < 200; }
 
 template <bool DGRAD>
 void launch_direct(hipStream_t st, DirectParams& p) {
   const int tiles = ((p.M + 31) / 32) * ((p.N + 63) / 64);
   p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
   // (eight wavefronts with an eighth of the reduction each measured slower: more streams in flight than the vector cache holds)
-  hipLaunchKernelGGL((gemm_f32_direct_kernel<DGRAD, 4>), dim3(tiles), dim3(256), 0, st, p);
+  if (chunked_shape(p.M, p.N))
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<DGRAD, 4, true>), dim3(tiles), dim3(256), 0, st, p);
+  else
+    hipLaunchKernelGGL((gemm_f32_direct_kernel<DGRAD, 4, false>), dim3(tiles), dim3(256), 0, st, p);
 }
 
 // Worth it while the output has too few 64x64 tiles to fill the chip without a
 // split, and every wavefront gets at least two steps.
 bool small_batch_shape(int rows, int cols, int kred) {
   const long tiles64 = (long)((rows + 63) / 64) * ((cols + 63) / 64);
-  // with fewer than ~200 of this kernel's 32 x 64 tiles many compute units would sit idle: the small kernels spread such a
-  // product better (256 rows, 3072 -> 1024: 29.8 us here, 19.4 us there)
-  const long tiles32 = (long)((rows + 31) / 32) * ((cols + 63) / 64);
-  if (tiles32 < 200) return false;
+  // While the small kernels' 32 x 32 tiles are one round of the chip (256) they are the faster ones (256 rows, 3072 -> 1024: 29.8
+  // us here, 19.4 us there); a second round costs them as much again and these 32 x 64 tiles are still in their first.  Steps
+  // of a 3072-1024-1024-10 net, small / here: 257 rows 108 / 98 us, 320 rows 113 / 103, 384 rows 117 / 108; 1024-768-768-10: 384
+  // rows 75 / 69; 2048-384-384-10: 1000 rows 83 / 77.  (A third round of small tiles against a second one here: 178 / 175.)
+  const long tiles32 = (long)((rows + 31) / 32) * ((cols + 31) / 32);
+  if (tiles32 <= 256) return false;
   return rows >= 1 && tiles64 < 256 && kred % kStep == 0 && kred / kStep >= 8 &&
          (long)rows * kred < (1L << 30) && (long)cols * kred < (1L << 30);   // 32-bit element offsets
 }
@@ -333,7 +388,9 @@ bool linear_dgrad_f32_direct(hipStream_t st, const float* dy, const float* w, co
   const int tiles = ((p.M + 31) / 32) * ((p.N + 63) / 64);
   p.xcd_remap = tiles % 8 == 0 ? 1 : 0;
   const HeadRole role = head_role(head, seg);
-  hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel, dim3(tiles + role.blocks), dim3(256), 0, st, p, tiles, role, seg);
+  const dim3 grid(tiles + role.blocks), block(256);
+  if (chunked_shape(p.M, p.N)) hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel<true>, grid, block, 0, st, p, tiles, role, seg);
+  else hipLaunchKernelGGL(dgrad_and_head_wgrad_kernel<false>, grid, block, 0, st, p, tiles, role, seg);
   return true;
 }
 
