@@ -4,7 +4,7 @@
 //   forward   Y  = X W^T + bias,  dgrad  dX = dY W,  wgrad  G_k = dY_k^T X_k (with the update, as there)
 // where the output has enough 128 x 128 tiles to fill the chip.  The fp32 instruction's pipe is what bounds those (154 TFLOP/s; 104
 // were reached, staging instructions between); the bf16 one is sixteen times as fast.  Every operand element is taken as the
-// exact sum of three bf16 values (split_bf16_device.h), and of the nine products the six that reach 2^-24 of the whole are
+// exact sum of three bf16 values, scaled (split_bf16_device.h), and of the nine products the six that reach 2^-24 of the whole are
 // formed, exactly, and added in fp32.  What is left out is below 2^-25 of a product, with random signs.
 //
 // Measured, 3072-1024-1024-10, 4096 rows, against the fp32 instruction: forward 222 -> 149 and 75 -> 54 us, input gradient 85 -> 63,
@@ -22,8 +22,8 @@
 // The pipeline: while a slab is multiplied from registers, the next one's fragments are read from LDS, the one after that is
 // split and written where the present one lay, and the fourth is sent for.  One barrier per slab.
 //
-// Infinities and NaN, and values that round to infinity, come out of the products as infinity or NaN, never as a number; sums
-// that are not finite are formed again with the fp32 instruction, whose results then stand.
+// Infinities and NaN, and operands from 2^104 on, come out of the products as infinity or NaN, never as a number, and so do sums
+// from 2^80 on; sums that are not finite are formed again with the fp32 instruction, whose results then stand.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -373,7 +373,8 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
         for (int q = 0; q < kPieces / kParts; ++q) {
           const int idx = ft + kThreads * q, r = idx / (kTile / 4), c4 = (idx % (kTile / 4)) * 4;
           const float* o = out + r * kFlushPitch + c4;
-          const v4f g = *reinterpret_cast<const v4f*>(o) + *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch);
+          const v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale +
+                        *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
           const int row = row0 + part * kFlushRows + r;
           if (UPD) gsum[part * (kPieces / kParts) + q] += lam->v[done.w] * g;
           float* dst = C + (size_t)row * p.ldc + col0 + c4;
@@ -408,23 +409,31 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
     if (!WGRAD || s0.w >= nrange) break;
   }
 
-  // Sums that are not finite once more, from memory, in one chain; what is finite stays (a row's results do not depend on other
-  // rows).  Here, where nothing else is in registers: beside the loop it spilled, and the spills' waits were the stores'.
+  // Sums that are not finite once more, from memory, in pieces of 32 elements; what is finite stays (a row's results do not depend
+  // on other rows).  Here, where nothing else is in registers: beside the loop it spilled, and the spills' waits were the stores'.
   const int ri = wrow + 32 * share;      // 32 of the block's rows by each wavefront
   auto again = [&](int j, int kb, int ke) {
     const int ra = min(row0 + ri + r32, p.M - 1), rb = min(col0 + wcol + 32 * j + r32, p.N - 1);
-    v16f c;
+    v16f sum;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) c[v] = 0.f;
+    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+#pragma unroll 1
+    for (; kb < ke; kb += BK) {
+      v16f c;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) c[v] = 0.f;
 #pragma unroll 4
-    for (int k = kb; k < ke; k += 2) {
-      const int kk = min(k + h, ke - 1);
-      float x = A_MC ? p.A[(size_t)kk * p.lda + ra] : p.A[(size_t)ra * p.lda + kk];
-      float y = B_MC ? p.B[(size_t)kk * p.ldb + rb] : p.B[(size_t)rb * p.ldb + kk];
-      if (k + h >= ke) x = y = 0.f;
-      c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+      for (int k = kb; k < min(kb + BK, ke); k += 2) {
+        const int kk = min(k + h, ke - 1);
+        float x = A_MC ? p.A[(size_t)kk * p.lda + ra] : p.A[(size_t)ra * p.lda + kk];
+        float y = B_MC ? p.B[(size_t)kk * p.ldb + rb] : p.B[(size_t)rb * p.ldb + kk];
+        if (k + h >= ke) x = y = 0.f;
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, c, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[v] += c[v];
     }
-    return c;
+    return sum;
   };
   auto row_of = [&](int v) { return ri + 4 * h + 8 * (v >> 2) + (v & 3); };
   const bool repair = __syncthreads_or(notfinite);
@@ -509,7 +518,7 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int slot = ((wave & 3) * 64 + (share * 2 + j) * 16 + v) * 64 + lane;
-        sum[v] = out[slot] + out[slot + 4 * 64 * 64];
+        sum[v] = out[slot] * kSplitUnscale + out[slot + 4 * 64 * 64] * kSplitUnscale;   // (each: the sum may be large)
       }
       if (repair) {
         const v16f c = again(j, 0, p.kred);

@@ -118,7 +118,7 @@ def _forward_with(x, w, dims):
 
 @pytest.mark.parametrize("at", [0, 17, 63, 64, 69])
 def test_infinities_and_the_largest_values(at):
-    """Column 5's weights are zero but for element `at`: infinite, then so large that it rounds to an infinite bf16 value.  What
+    """Column 5's weights are zero but for element `at`: infinite, then so large that its pieces are no numbers.  What
     is not near it keeps its bits."""
     dims, B = [70, 1024, 10], 3329
     rng = np.random.default_rng(at)
@@ -136,6 +136,77 @@ def test_infinities_and_the_largest_values(at):
     x[:, at] = np.minimum(x[:, at], 1.0)
     hidden = _forward_with(x, w, dims)
     assert np.array_equal(hidden[:, 5], w[5, at] * x[:, at])
+
+
+# Powers of two on the two operands: down to numbers of a few bits (the smallest fp32 number is 2^-149), and up to where the pieces
+# are no numbers (2^104) or a product of the scaled pieces is none (2^80).
+RANGES = [(-124, 20), (20, -124), (-112, -30), (110, -30), (-30, 110), (60, 60)]
+
+
+@pytest.mark.parametrize("ex,ew", RANGES)
+def test_forward_of_small_and_large_operands(ex, ew):
+    import torch
+    dims, B = [97, 1021, 10], 3300
+    rng = np.random.default_rng(7)
+    x = np.ldexp(rng.standard_normal((B, dims[0])), ex).astype(np.float32)
+    w = np.ldexp(rng.standard_normal((dims[1], dims[0])), ew).astype(np.float32)
+    z = torch.from_numpy(_forward_with(x, w, dims)).double()
+    want = torch.from_numpy(x).double() @ torch.from_numpy(w).double().T
+    size = torch.from_numpy(x).double().abs() @ torch.from_numpy(w).double().abs().T
+    # (2^-149: the smallest number, for results that have fewer than 24 bits)
+    assert float(((z - want.clamp(min=0)).abs() - 110 * U * size).max()) <= 2.0 ** -149
+
+
+def _backward_with(dims, off, scale, ex):
+    """One step with x times 2^ex and layer i's weights times 2^scale[i]: what the first layers stored, float64"""
+    import torch
+    import paper_2503_17469_amd as omni
+    layers = synth.mlp(dims)
+    B, K = off[-1], len(off) - 1
+    rng = np.random.default_rng(sum(dims) + B)
+    params = synth.he_normal_params(layers, 7, False)
+    linear = [i for i, L in enumerate(layers) if L["op"] == "linear"]
+    for i, e in zip(linear, scale):
+        s, t = synth.param_slices(layers)[i]["w"]
+        params[s:t] = np.ldexp(params[s:t].astype(np.float64), e)
+    x = np.ldexp(rng.standard_normal((B, dims[0])), ex).astype(np.float32)
+    y = rng.integers(0, dims[-1], B).astype(np.int32)
+    run = GpuRun(layers, (1, 1, dims[0]), "f32", K, B)
+    try:
+        got = run.step(params, x, y, off, 0.0, keep_g=False)
+        dy = [omni.net_activation_grad(run.net, run.ws, i, B, "f32").double().cpu() for i in linear[:-1]]
+        hidden = torch.from_numpy(np.ascontiguousarray(run.activation(0, B))).double()
+    finally:
+        run.close()
+    w = []
+    for i, (o, n) in zip(linear, zip(dims[1:], dims)):
+        s, t = synth.param_slices(layers)[i]["w"]
+        w.append((torch.from_numpy(params[s:t].reshape(o, n)).double(),
+                  [torch.from_numpy(got["worker_grads"][k, s:t].reshape(o, n)).double() for k in range(K)]))
+    return torch.from_numpy(x).double(), hidden, dy, w
+
+
+@pytest.mark.parametrize("ea,eb", RANGES)
+def test_input_gradients_of_small_and_large_operands(ea, eb):
+    """output gradients (through the classifier's weights) times 2^ea, weights times 2^eb"""
+    _, hidden, dy, w = _backward_with([24, 1021, 129, 10], [0, 1100, 3300], [min(0, -ea - eb), eb, ea], 0)
+    a, b = dy[1], w[1][0]
+    assert float(a.abs().max()) > 0
+    mask = (hidden > 0).double()
+    over = (dy[0] - (a @ b) * mask).abs() - 110 * U * (a.abs() @ b.abs()) * mask
+    assert float(over.max()) <= 2.0 ** -149
+
+
+@pytest.mark.parametrize("ea,eb", RANGES)
+def test_weight_gradients_of_small_and_large_operands(ea, eb):
+    """output gradients (through the classifier's weights) times 2^ea, inputs times 2^eb"""
+    off = [0, 300, 1100]
+    x, _, dy, w = _backward_with([3400, 1021, 10], off, [min(0, -ea - eb), ea], eb)
+    assert float(dy[0].abs().max()) > 0
+    for k in range(2):
+        a, b = dy[0][off[k]:off[k + 1]].T, x[off[k]:off[k + 1]]
+        over = (w[0][1][k] - a @ b).abs() - 130 * U * (a.abs() @ b.abs())
+        assert float(over.max()) <= 2 * 2.0 ** -149      # two chunks of two shares, each rounded to a multiple of 2^-149
 
 
 @pytest.mark.parametrize("value", [np.nan, np.inf])
