@@ -8,9 +8,10 @@
 // formed, exactly, and added in fp32.  What is left out is below 2^-25 of a product, with random signs.
 //
 // Measured, 3072-1024-1024-10, 4096 rows, against the fp32 instruction: forward 222 -> 149 and 75 -> 54 us, input gradient 85 -> 63,
-// weight gradients of sixteen workers with the update 346 -> 270; 170 TFLOP/s, that is 1.03 PFLOP/s of bf16 products, where a
+// weight gradients of sixteen workers with the update 346 -> 270 (all 2.5 % longer since operands are scaled); 170 TFLOP/s, that is 1.03 PFLOP/s of bf16 products, where a
 // loop of nothing but these matrix instructions reaches 1.40 on the same data (the clock falls under the load).  Error
-// against float64 (2-norm): forward 0.80 to 0.88 of the fp32 kernel's, weight gradients 0.5 to 0.9.
+// against float64 (2-norm), as a part of the fp32 kernels': forward 0.4 to 0.7 (32 to 8192 elements), input gradients 0.5 to 0.9,
+// weight gradients 0.35 to 0.75 from 8 rows of a worker on, the same at 4, but 1.2 at 2 and 1.4 at one.
 //
 // A workgroup has a 128 x 128 tile and eight wavefronts: a 2 x 2 grid of 64 x 64 blocks, twice; the two wavefronts of a block take
 // the two halves of every slab of 32 reduction elements, and their sums are added at the end.  (Four wavefronts with the
@@ -18,6 +19,10 @@
 // half as much again from LDS per instruction.)  Elements are split once, on their way to LDS.  Smaller tiles split too often for
 // what they multiply: 64 x 64 and 64 x 32 tiles, with the reduction cut four or eight ways, were no faster than the fp32 kernels
 // at 480 to 1500 rows.
+//
+// The instruction rounds down: products that share a sum, and the sum they are added to, are cut off at 2^-24 of the largest
+// product, towards minus infinity (0.085 x 2^-24 of the absolute products' sum, all outputs alike, however long the reduction).  So
+// the second half of every slab is summed with the opposite sign, and subtracted.
 //
 // The pipeline: while a slab is multiplied from registers, the next one's fragments are read from LDS, the one after that is
 // split and written where the present one lay, and the fourth is sent for.  One barrier per slab.
@@ -79,6 +84,7 @@ struct Operand {
     const int r = min(row0 + row_of(tid), rows - 1);   // (rows past the end feed outputs that are not stored)
     ptr = base + (MC ? (size_t)(k8_of(tid) * 8) * ld + r : (size_t)r * ld + k8_of(tid) * 8);
   }
+  __device__ static __forceinline__ int share_of(int tid) { return k8_of(tid) / (BK / 8 / kShares); }
   // (16-byte loads from any multiple of 4 bytes)
   __device__ __forceinline__ void load(int ld, int ks) {
     if (!MC) {
@@ -99,10 +105,10 @@ struct Operand {
       for (int q = 0; q < 8; ++q) v[q] = (k + q >= lo && k + q < hi) ? v[q] : 0.f;
     }
   }
-  __device__ __forceinline__ void store(u32x4* lds, int tid) const {
+  __device__ __forceinline__ void store(u32x4* lds, int tid, float scale) const {
     uint32_t w[3][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) split3(v[2 * q], v[2 * q + 1], w[0][q], w[1][q], w[2][q]);
+    for (int q = 0; q < 4; ++q) split3(v[2 * q], v[2 * q + 1], scale, w[0][q], w[1][q], w[2][q]);
     u32x4* at = lds + row_piece(row_of(tid)) + k8_of(tid);
 #pragma unroll
     for (int p = 0; p < 3; ++p) at[4 * p] = u32x4{w[p][0], w[p][1], w[p][2], w[p][3]};
@@ -177,6 +183,7 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
 
   Operand<A_MC> a;
   Operand<B_MC> b;
+  const float scale_a = Operand<A_MC>::share_of(tid) == 0 ? kSplitScale : -kSplitScale;    // (the second share sums -A B)
   a.prepare(p.A, p.lda, row0, p.M, tid);
   b.prepare(p.B, p.ldb, col0, p.N, tid);
   const bool want_bias_grad = WGRAD && p.bias_grad != nullptr && tile_n == 0;
@@ -214,13 +221,13 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
   Slab s0 = first(), s1 = after(s0), s2 = after(s1);
   send(s0);
   take(s0);
-  a.store(stage(0), tid);
-  b.store(stage(0) + kOperand, tid);
+  a.store(stage(0), tid, scale_a);
+  b.store(stage(0) + kOperand, tid, kSplitScale);
   bsum = bpart;
   send(s1);
   take(live(s1));
-  a.store(stage(1), tid);
-  b.store(stage(1) + kOperand, tid);
+  a.store(stage(1), tid, scale_a);
+  b.store(stage(1) + kOperand, tid, kSplitScale);
   bnext = bpart;
   send(s2);
   if (WGRAD) { a.arrived(); b.arrived(); }      // (see the loop)
@@ -269,8 +276,8 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
               acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][pa[t]], fb[j][pb[t]], acc[i][j], 0, 0, 0);
             }
           }
-        if (t == 0) a.store(wst, tid);
-        if (t == 1) { b.store(wst + kOperand, tid); send(s3); }
+        if (t == 0) a.store(wst, tid, scale_a);
+        if (t == 1) { b.store(wst + kOperand, tid, kSplitScale); send(s3); }
         // fragments that no later product needs make room for the next slab's
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -291,8 +298,8 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
         for (int v = 0; v < 16; ++v) c[v] = 0.f;
 #pragma unroll
         for (int t = 0; t < 6; ++t) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][pa[t]], fb[j][pb[t]], c, 0, 0, 0);
-        if (blk == 0) a.store(wst, tid);
-        if (blk == 1) { b.store(wst + kOperand, tid); send(s3); }
+        if (blk == 0) a.store(wst, tid, scale_a);
+        if (blk == 1) { b.store(wst + kOperand, tid, kSplitScale); send(s3); }
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
           if (i == 1) nb[j][q] = read_b(rst, j, q);
@@ -373,7 +380,7 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
         for (int q = 0; q < kPieces / kParts; ++q) {
           const int idx = ft + kThreads * q, r = idx / (kTile / 4), c4 = (idx % (kTile / 4)) * 4;
           const float* o = out + r * kFlushPitch + c4;
-          const v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale +
+          const v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale -
                         *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
           const int row = row0 + part * kFlushRows + r;
           if (UPD) gsum[part * (kPieces / kParts) + q] += lam->v[done.w] * g;
@@ -518,7 +525,7 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int slot = ((wave & 3) * 64 + (share * 2 + j) * 16 + v) * 64 + lane;
-        sum[v] = out[slot] * kSplitUnscale + out[slot + 4 * 64 * 64] * kSplitUnscale;   // (each: the sum may be large)
+        sum[v] = out[slot] * kSplitUnscale - out[slot + 4 * 64 * 64] * kSplitUnscale;   // (each: the sum may be large)
       }
       if (repair) {
         const v16f c = again(j, 0, p.kred);
