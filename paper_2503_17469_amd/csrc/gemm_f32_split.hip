@@ -55,8 +55,8 @@ namespace {
 constexpr int kTile = 128, kThreads = 512;
 constexpr int BK = 32;              // reduction elements per slab
 constexpr int kShares = 2;          // wavefronts per 64 x 64 block
-// A weight gradient adds at most so many rows of a worker in one chain of slabs; longer ones go to G in pieces (4096 rows by
-// two workers: 0.89 instead of 1.07 times the fp32 kernel's error, for 3 us per piece).
+// A weight gradient adds at most so many rows of a worker in one chain of slabs; longer ones go to G in pieces (4096 rows of
+// one worker: 0.35 instead of 0.71 times the fp32 kernel's error, for 5 us per piece).
 constexpr int kChunkRows = 512;
 
 enum { MODE_FWD = 0, MODE_DGRAD = 1, MODE_WGRAD = 2 };
@@ -389,11 +389,17 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
           float* dst = C + (size_t)row * p.ldc + col0 + c4;
           if (whole) {
             *reinterpret_cast<v4f_a4*>(dst) = g;
-          } else {
-            if (row < p.M)
+          } else if (row < p.M) {
+            // (16 bytes at a time as well: element by element, 1021 x 3400 outputs of 32 workers took 54 us longer, and the eight
+            // pieces of a worker with 4096 rows 37)
+            if (col0 + c4 + 4 <= p.N) {
+              v4f_a4* const to = reinterpret_cast<v4f_a4*>(dst);
+              *to = cont ? *to + g : g;
+            } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
+              for (int e = 0; e < 3; ++e)
                 if (col0 + c4 + e < p.N) dst[e] = cont ? dst[e] + g[e] : g[e];
+            }
           }
         }
       }
