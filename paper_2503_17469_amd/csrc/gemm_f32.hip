@@ -569,7 +569,7 @@ bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows) {
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
                             const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
                             const KernelTimer* timer) {
-  if (linear_wgrad_f32_split_shape(jobs, n, seg.off[seg.K])) {
+  if (linear_wgrad_f32_split_shape(jobs, n, seg)) {
     linear_wgrad_f32_split(st, jobs, n, worker_stride, seg, head, sgd, timer);
     return;
   }

@@ -639,14 +639,26 @@ void linear_dgrad_f32_split(hipStream_t st, const float* dy, const float* w, con
   launch<true, MODE_DGRAD>(st, p);
 }
 
-// (Few rows are bound by the writing of G either way: 256 rows of one worker 30.3 / 30.6 us, 480 rows of four 48.3 / 49.5.)
-bool linear_wgrad_f32_split_shape(const LinearWgradJob* jobs, int n, int rows) {
+// Every worker costs a slab that its rows seldom fill and a flush through LDS with five barriers, so that it is rows per worker that
+// count, a hundred of them on average; and few rows are bound by the writing of G either way, so at least 400 in all.  Steps, split /
+// fp32, in us:
+//   3072-1024-1024-10    1 worker,   256 rows  74 /  74    512 rows 107 / 113   1024 rows 200 / 213
+//                        4 workers,  256 rows  80 /  75    400 rows 111 / 114   1024 rows 198 / 212
+//                       16 workers,  512 rows 141 / 126   1024 rows 225 / 224   2048 rows 354 / 378
+//                       32 workers, 1024 rows 275 / 259   2048 rows 405 / 411   4096 rows 603 / 644
+//   3400-1021-10         4 workers,  256 rows  70 /  64    400 rows 104 / 103   1024 rows 160 / 170
+//                       16 workers, 1024 rows 202 / 188   1536 rows 278 / 270   2048 rows 306 / 309
+// No worker of fewer than four rows: sums of one to three products are nearer to float64 on the fp32 instruction (see above).
+bool linear_wgrad_f32_split_shape(const LinearWgradJob* jobs, int n, const Segments& seg) {
+  if (seg.off[seg.K] < 100 * std::max((int)seg.K, 4)) return false;
+  for (int k = 0; k < seg.K; ++k)
+    if (seg.off[k + 1] - seg.off[k] < 4) return false;
   long tiles = 0, outputs = 0;
   for (int i = 0; i < n; ++i) {
     tiles += tiles_of(jobs[i].cout, jobs[i].cin);
     outputs += (long)jobs[i].cout * jobs[i].cin;
   }
-  return n <= kMaxBatch && rows >= 400 && fills_rounds(tiles, outputs);
+  return n <= kMaxBatch && fills_rounds(tiles, outputs);
 }
 
 void linear_wgrad_f32_split(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,

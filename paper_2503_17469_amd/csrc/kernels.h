@@ -77,7 +77,7 @@ bool linear_wgrad_f32_tiled(const LinearWgradJob* jobs, int n, int rows);
 void linear_wgrad_f32_batch(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
                             const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
                             const KernelTimer* timer = nullptr);
-bool linear_wgrad_f32_split_shape(const LinearWgradJob* jobs, int n, int rows);
+bool linear_wgrad_f32_split_shape(const LinearWgradJob* jobs, int n, const Segments& seg);
 void linear_wgrad_f32_split(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride,
                             const Segments& seg, const LinearWgradJob* head, const SgdArgs* sgd,
                             const KernelTimer* timer);

@@ -54,6 +54,7 @@ def test_input_gradients(rows, cin, cout):
 
 @pytest.mark.parametrize("cin,cout,off", [
     (3400, 1021, [0, 1, 33, 34, 66, 400]),            # workers of one row, of a slab, of a slab and one
+    (3400, 1021, [0, 4, 37, 70, 74, 700]),            # (the first of these is not split: workers of fewer than four rows)
     (3400, 1021, [0, 511, 1023, 1536]),               # chunks of 511, 512, and 512 + 1 rows
     (3328, 1024, [0, 1056, 1601]),                    # three chunks, two chunks
     (1021, 3400, [0, 250, 505]),
@@ -247,6 +248,7 @@ def test_errors_have_no_direction():
     ([24, 1021, 40, 10], [0, 1000, 1003, 3300], 1),        # and input gradient
     ([3400, 1021, 10], [0, 200, 203, 500], 1),             # weight gradient
     ([3400, 1021, 10], [0, 600, 620, 700], 0),
+    ([3400, 1021, 10], [0, 300, 304, 500], 1),
 ])
 def test_workers_do_not_depend_on_each_other(dims, off, bad, value):
     _isolated(synth.mlp(dims), (1, 1, dims[0]), "f32", off, bad, value, sum(dims))
