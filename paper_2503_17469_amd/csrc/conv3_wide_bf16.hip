@@ -39,6 +39,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "pool_device.h"
+#include "quotient.h"
 
 namespace omni {
 
@@ -60,7 +61,7 @@ struct WideParams {
   int flip;            // 1: dgrad (mirrored taps)
   int wlog;            // log2 of W
   uint32_t by_patch, by_row, by_r;   // 2^22 / d rounded up, for division of a patch position by a patch and by a patch row, and of a row by R
-  uint32_t by_units;   // 2^32 / d, for division of a unit by the units of an image
+  uint32_t by_units;   // reciprocal_below(units of an image)
   const void* zero;    // zeros for absent pieces
   const float* bias;
   const bf16_t* mask;     // [rows*H*W][N] or null: the value passes where mask > 0
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   auto unit_geom = [&](int unit, int& n0, int& r0, int& nvalid) {
     unit -= ufirst;
     if (p.nimg == 1) {
-      const int img = p.by_units ? (int)__umulhi((uint32_t)unit, p.by_units) : unit;
+      const int img = quotient(unit, p.by_units, 1);
       n0 = ibeg + img; r0 = unit * R - img * H; nvalid = 1;
     } else {
       n0 = ibeg + unit * p.nimg; r0 = 0; nvalid = min(p.nimg, iend - n0);
@@ -626,6 +627,8 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
   }
   if (!ma) return false;
   const int units = nimg == 1 ? g.rows * (H / R) : (g.rows + nimg - 1) / nimg;
+  const uint32_t by_units = reciprocal_below(H / R, units);
+  if (H > R && !by_units) return false;   // (few images of a great many rows: the other kernels divide)
   // Where 64 channels per workgroup leave a compute unit with one or none: 32, so that one's loads run under another's
   // instructions (1024 images, 128 -> 64 on 8x8, alone: 16.65 -> 15.9 us).
   if (plain && ma == 2 && (long)units * ((N + 63) / 64) <= 256) nb = 1;
@@ -683,8 +686,7 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
   p.units = p.ufirst[p.gK]; p.upw = upw;
   auto reciprocal = [](int d) { return (uint32_t)(((1 << 22) + d - 1) / d); };   // (exact: positions and divisors below 2^11)
   p.by_patch = reciprocal((R + 2) * (W + 2)); p.by_row = reciprocal(W + 2); p.by_r = reciprocal(R);
-  const int upi = H / R;
-  p.by_units = upi > 1 ? (uint32_t)(((1ull << 32) + upi - 1) / upi) : 0;   // (exact: fewer than 2^24 positions)
+  p.by_units = by_units;
   while ((1 << p.wlog) < W) ++p.wlog;
   p.gfirst[0] = 0;
   for (int k = 0; k < p.gK; ++k) p.gfirst[k + 1] = p.gfirst[k] + (p.ufirst[k + 1] - p.ufirst[k] + upw - 1) / upw;

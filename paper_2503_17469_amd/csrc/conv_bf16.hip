@@ -39,6 +39,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "pool_device.h"
+#include "quotient.h"
 
 namespace omni {
 
@@ -705,7 +706,7 @@ struct Conv1Params {
   uint8_t* pool_code;  // with pool: one byte per pooled element (see pool_code_of)
   int raw3;            // src is [rows][H][W][3]: a pixel is three 2-byte loads, channels 3-7 are zero
   int lw, lr;          // W = 1 << lw, R = 1 << lr
-  uint32_t by_patch, by_pw, by_upi;   // 2^32 / (PR PW), / PW and / (H / R), rounded up; the last 0 where it would not be exact
+  uint32_t by_patch, by_pw, by_upi;   // reciprocal_below of PR PW, PW and H / R
 };
 
 // The copies of the other layers' weights ride in front of the units (CAST): they were 5 us as a launch of their own, most of it
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, s
   auto unit_geom = [&](int unit, int& n0, int& r0, int& nvalid) {
     if (p.nimg == 1) {
       const int upi = H >> p.lr;
-      const int img = upi == 1 ? unit : p.by_upi ? (int)__umulhi((uint32_t)unit, p.by_upi) : unit / upi;
+      const int img = quotient(unit, p.by_upi, upi);
       n0 = img; r0 = (unit - img * upi) * R; nvalid = 1;
     } else {
       n0 = unit * p.nimg; r0 = 0; nvalid = min(p.nimg, p.rows - n0);
@@ -1002,10 +1003,6 @@ static bool conv1_fwd_shape(int N, const ConvGeom& g, long M) {
   const int nimg = kUnitD / (R * W);
   if (nimg > 1 && R != H) return false;
   return nimg * (R + 2) * (W + 2) <= 2 * kThreads;
-}
-
-static uint32_t reciprocal_below(uint32_t d, uint64_t below) {   // 2^32 / d rounded up, 0 where it is not exact for all n < below
-  return below * d < 1ull << 32 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u;
 }
 
 static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,

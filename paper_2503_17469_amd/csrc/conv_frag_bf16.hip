@@ -27,6 +27,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "pool_device.h"
+#include "quotient.h"
 
 namespace omni {
 
@@ -50,8 +51,8 @@ struct FragParams {
   int stride, flip;    // flip: input gradient (mirrored taps)
   int by_channel;      // which operand an XCD keeps to itself, see the kernel
   int tiles, per;      // tiles of positions; workgroups (of a parity class) per XCD
-  uint32_t by_minor;   // 2^32 / the faster counted of tiles and channel tiles, rounded up (0 for 1)
-  uint32_t by_upi;     // 2^32 / upi (0 for 1)
+  uint32_t by_minor;   // reciprocal_below(the faster counted of tiles and channel tiles)
+  uint32_t by_upi;     // reciprocal_below(upi)
   uint32_t by_oc;      // 2^16 / (Cs / 8), rounded up
   int dq, dr;          // 256 pieces on: so many positions and octets
   int gK;              // entries of the tables at the end
@@ -74,7 +75,6 @@ struct FragParams {
 // Where a tile lies.  A launch of this kernel is a chain of first accesses (a line of arguments 640 cycles, a division 150 to 200):
 // the tables are read only where there is more than one entry, all lanes at once.  (128 images of three conv layers: the four
 // launches 8.5 -> 7.4 us each.)
-__device__ inline int frag_quotient(int n, uint32_t by) { return by ? (int)__umulhi((uint32_t)n, by) : n; }
 struct FragPlace {
   int gk, n0, r0, nvalid;   // entry, first image and row, images present
 };
@@ -87,7 +87,7 @@ __device__ inline FragPlace frag_place(const FragParams& p, int tile) {
     beg = __builtin_amdgcn_readlane(i, gk);
     end = gk + 1 < p.gK ? __builtin_amdgcn_readlane(i, gk + 1) : p.rows;
   }
-  const int img = p.upi == 1 ? tl * p.nimg : frag_quotient(tl, p.by_upi);
+  const int img = p.upi == 1 ? tl * p.nimg : quotient(tl, p.by_upi, p.upi);
   return FragPlace{gk, beg + img, p.upi == 1 ? 0 : (tl - img * p.upi) << p.rlog, min(p.nimg, end - beg - img)};
 }
 
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   const int tiles = p.tiles, tiles_n = (p.N + kTN - 1) / kTN, total = tiles * tiles_n;
   const int at = ((int)blockIdx.x & 7) * p.per + ((int)blockIdx.x >> 3);
   if (at >= total || ((int)blockIdx.x >> 3) >= p.per) return;
-  const int major = frag_quotient(at, p.by_minor), minor = at - major * (p.by_channel ? tiles : tiles_n);
+  const int per_major = p.by_channel ? tiles : tiles_n, major = quotient(at, p.by_minor, per_major), minor = at - major * per_major;
   const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
   const FragPlace place = frag_place(p, tile);
   const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p)
   const int at = ((int)blockIdx.x & 7) * p.per + local;
   if (cls < 0 || at >= total) return;
   const int ph = cls >> 1, pw = cls & 1;
-  const int major = frag_quotient(at, p.by_minor), minor = at - major * (p.by_channel ? tiles : tiles_n);
+  const int per_major = p.by_channel ? tiles : tiles_n, major = quotient(at, p.by_minor, per_major), minor = at - major * per_major;
   const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
   const FragPlace place = frag_place(p, tile);
   const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
@@ -633,12 +633,11 @@ void frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stat
 
 // What follows from the tiles, the channels and by_channel.
 void frag_counts(FragParams& p) {
-  auto reciprocal = [](int d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; };   // (exact: numbers below 2^20)
   const int tiles_n = (p.N + kTN - 1) / kTN, oc = p.Cs / 8;
   p.tiles = p.tfirst[p.gK];
   p.per = (p.tiles * tiles_n + 7) / 8;
-  p.by_minor = reciprocal(p.by_channel ? p.tiles : tiles_n);
-  p.by_upi = reciprocal(p.upi);
+  p.by_minor = reciprocal_below(p.by_channel ? p.tiles : tiles_n, (uint64_t)p.tiles * tiles_n);
+  p.by_upi = reciprocal_below(p.upi, p.tiles);
   p.by_oc = (uint32_t)((65536 + oc - 1) / oc);   // (exact: a thread's number by at most 2^8 octets)
   p.dq = kThreads / oc;
   p.dr = kThreads - p.dq * oc;

@@ -27,6 +27,7 @@
 #include "kernels.h"
 #include "lds_barrier_device.h"
 #include "lds_limit.h"
+#include "quotient.h"
 #include "update_device.h"
 #include "wgrad_chunk.h"
 
@@ -322,7 +323,7 @@ struct Wgrad3Params {
   int SX;              // bytes between channels of X^T
   int upc;             // units per chunk
   int nimg_log;
-  uint32_t by_r, by_patch, by_upi;   // 2^16 / R, 2^16 / (R + 2), 2^32 / (units per image), rounded up (the last 0 for one)
+  uint32_t by_r, by_patch, by_upi;   // 2^16 / R and / (R + 2), rounded up; reciprocal_below(units per image)
   float* partial;      // [(tile * total_chunks + chunk)][144][256] (+ 64 bias sums)
   const void* zero;    // page of zeros for absent pieces
 };
@@ -456,7 +457,7 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
   // first image and row of unit u; units are loaded one after the other
   int img_at, row_at;
   {
-    const int img = p.by_upi ? (int)__umulhi((uint32_t)ubeg, p.by_upi) : ubeg;
+    const int img = quotient(ubeg, p.by_upi, upi);
     img_at = ck.beg + (p.nimg == 1 ? img : ubeg << p.nimg_log);
     row_at = p.nimg == 1 ? (ubeg - img * upi) * R : 0;
   }
@@ -766,7 +767,7 @@ struct Wgrad1Params {
   const bf16_t* dpool;  // [rows][H/2][16][Cout]
   const uint8_t* code;  // [rows][H/2][16][Cout]
   int raw3;             // src is [rows][H][32][3]: a pixel is three 2-byte loads
-  uint32_t by_ppp, by_cin, by_upi;   // 2^32 / (Cout / 8), / cin_real and / (H / 4), rounded up; the last 0 where it is not exact
+  uint32_t by_ppp, by_cin, by_upi;   // reciprocal_below of Cout / 8, cin_real and H / 4
 };
 constexpr int kG_W = 32, kG_R = 4, kG_Unit = kG_W * kG_R;        // 128 positions
 constexpr int kG_PatchRows = kG_R + 2;
@@ -827,7 +828,7 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
 #pragma unroll
   for (int i = 0; i < kY; ++i) {
     const int q = min(tid + kThreads * i, ny - 1);         // surplus slots re-read the last piece
-    const int at = ppp == 1 ? q : (int)__umulhi((uint32_t)q, p.by_ppp), oct = q - at * ppp;
+    const int at = ppp == 1 ? q : quotient(q, p.by_ppp, ppp), oct = q - at * ppp;
     if (POOLED) {                                           // at = row of the unit, window along it
       const int row = at >> 4, pc = at & 15;
       ydst[i] = wgrad1_y_offset<MB>(row * kG_W + 2 * pc, oct);
@@ -847,7 +848,7 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
   // the unit that is fetched next: its image and first row
   int fu = ubeg, fimg, frow;
   {
-    const int at = upi == 1 ? ubeg : p.by_upi ? (int)__umulhi((uint32_t)ubeg, p.by_upi) : ubeg / upi;
+    const int at = quotient(ubeg, p.by_upi, upi);
     fimg = __builtin_amdgcn_readfirstlane(ck.beg + at);
     frow = __builtin_amdgcn_readfirstlane((ubeg - at * upi) * kG_R);
   }
@@ -937,7 +938,7 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int col = nb * 32 + jl;
-    const int tap = col < 9 * cin ? (cin == 1 ? col : (int)__umulhi((uint32_t)col, p.by_cin)) : 0;
+    const int tap = col < 9 * cin ? (cin == 1 ? col : quotient(col, p.by_cin, cin)) : 0;
     const int ci = col < 9 * cin ? col - tap * cin : 0;   // (absent columns are not stored)
     bbase[nb] = (tap % 3 * cin + ci) * kG_Plane + (tap / 3 * kG_W + 8 * kg) * 2;
   }
@@ -1058,7 +1059,7 @@ struct BatchJob {
   int kind;
   int tiles;             // workgroups of the first stage: tiles x chunks, of the second: tiles x workers x slots
   int slots;
-  uint32_t by_tiles, by_workers;   // reciprocal32
+  uint32_t by_tiles, by_workers;   // reciprocal_below
   int32_t chunk[OMNI_MAX_WORKERS + 1];   // first chunk of every worker; chunk[K] = all
   union {
     WgradParams general;
@@ -1089,15 +1090,12 @@ __device__ inline int job_at(const BatchTable& tab, int block) {
   for (int i = 1; i < kBatchJobs; ++i) e += i < tab.n && block >= tab.first[i] ? 1 : 0;
   return e;
 }
-// n / d with by = 2^32 / d rounded up, 0 for d = 1 (exact for n below 2^20, d below 2^12)
-__device__ inline int quotient(int n, uint32_t by) { return by ? (int)__umulhi((uint32_t)n, by) : n; }
-inline uint32_t reciprocal32(int d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0; }
 
 __global__ __launch_bounds__(kThreads, 2) void wgrad_batch_kernel(BatchTable tab, Segments seg) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int e = job_at(tab, (int)blockIdx.x);
   const BatchJob& job = tab.job[e];
-  const int local = (int)blockIdx.x - tab.first[e], row = quotient(local, job.by_tiles);
+  const int local = (int)blockIdx.x - tab.first[e], row = quotient(local, job.by_tiles, job.tiles);
   const int tile = local - row * job.tiles;
   const Chunk ck = chunk_at(job, seg, row);
   const Wgrad3Params patch = job.patch;   // (read together; and with a read per use the compiler copies the whole table into scratch)
@@ -1140,8 +1138,8 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(BatchTable tab, 
   const int e = job_at(tab, (int)blockIdx.x);
   const BatchJob& job = tab.job[e];
   const int local = (int)blockIdx.x - tab.first[e];
-  const int rest = quotient(local, job.by_tiles), tile = local - rest * job.tiles;
-  const int slot = quotient(rest, job.by_workers), wk = rest - slot * seg.K;
+  const int rest = quotient(local, job.by_tiles, job.tiles), tile = local - rest * job.tiles;
+  const int slot = quotient(rest, job.by_workers, seg.K), wk = rest - slot * seg.K;
   const Chunk ck{wk, 0, job.chunk[wk + 1] - job.chunk[wk], job.chunk[wk], job.chunk[seg.K], 0, 0};
   if (ck.n <= 1) return;   // written directly by the first stage
   switch (job.kind) {
@@ -1329,7 +1327,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_update_kernel(BatchTable tab, 
   }
   const int e = job_at(tab, b);
   const BatchJob& job = tab.job[e];
-  const int local = b - tab.first[e], slot = quotient(local, job.by_tiles), tile = local - slot * job.tiles;
+  const int local = b - tab.first[e], slot = quotient(local, job.by_tiles, job.tiles), tile = local - slot * job.tiles;
   if (job.kind == kFirst) wgrad1_update<MOM>(job.first, job, slot, seg, lam, opt, to, lds_update);
   else wgrad3_update<MOM>(job.patch, job, tile, slot, seg, lam, opt, to, lds_update);
 }
@@ -1375,9 +1373,9 @@ bool plan_first(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   count_units(pl, seg, g.Hs / kG_R, 1);
   // about four workgroups per compute unit, at least 4 units each
   const int upi = g.Hs / kG_R;
-  pl.job.first.by_ppp = reciprocal32(j.Cout / 8);
-  pl.job.first.by_cin = reciprocal32(j.cin_real);
-  pl.job.first.by_upi = (uint64_t)seg.off[seg.K] * upi * upi < 1ull << 32 ? reciprocal32(upi) : 0u;
+  pl.job.first.by_ppp = reciprocal_below(j.Cout / 8, kG_Unit * (j.Cout / 8));   // (of a unit's pieces)
+  pl.job.first.by_cin = reciprocal_below(j.cin_real, 32 * nb);                   // (of a column)
+  pl.job.first.by_upi = reciprocal_below(upi, (uint64_t)seg.off[seg.K] * upi);
   pl.min_upc = 4; pl.upc_step = 1; pl.alone = std::max(64, 1024 - seg.K);
   pl.slot_floats = (size_t)mb * nb * 16 * 64;
   pl.lds = std::max((size_t)2 * wgrad1_stage_bytes(mb, j.cin_real), 4 * pl.slot_floats * sizeof(float));
@@ -1410,7 +1408,7 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   while ((1 << p.nimg_log) < nimg) ++p.nimg_log;   // (nimg divides 128)
   auto reciprocal16 = [](int d) { return (uint32_t)(((1 << 16) + d - 1) / d); };   // (exact: rows below 2^9, divisors up to 130)
   p.by_r = reciprocal16(R); p.by_patch = reciprocal16(R + 2);
-  p.by_upi = nimg == 1 ? reciprocal32(H / R) : 0;
+  p.by_upi = nimg == 1 ? reciprocal_below(H / R, (uint64_t)seg.off[seg.K] * (H / R)) : 0;
   // at most 32 input channels: half of a 64 x 64 tile would be empty
   const bool narrow = g.Cs <= 32 && (W == 8 || W == 16 || W == 32);
   pl.lds = (size_t)64 * kSA + (size_t)(narrow ? 32 : 64) * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
@@ -1562,10 +1560,12 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
     set_partial(pl.job, partial + scratch);
     bp.scratch[i] = scratch;
     scratch += budget;
-    pl.job.by_tiles = reciprocal32(pl.job.tiles);
-    pl.job.by_workers = reciprocal32(seg.K);
     bool chunked = false;
     for (int k = 0; k < seg.K; ++k) chunked = chunked || pl.job.chunk[k + 1] - pl.job.chunk[k] > 1;
+    long rows = pl.job.chunk[seg.K];   // workgroups per tile, in whichever launch has the most
+    if (chunked) rows = std::max<long>(rows, std::max<long>((long)seg.K * pl.job.slots, kUpdateSlots3));
+    pl.job.by_tiles = reciprocal_below(pl.job.tiles, (uint64_t)pl.job.tiles * rows);
+    pl.job.by_workers = reciprocal_below(seg.K, (uint64_t)seg.K * pl.job.slots);
     if (chunked) {
       bp.red.first[bp.red.n] = bp.rblocks;
       bp.rblocks += pl.job.tiles * seg.K * pl.job.slots;

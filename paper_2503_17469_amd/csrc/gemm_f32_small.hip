@@ -25,6 +25,7 @@
 #include "common.h"
 #include "head_device.h"
 #include "kernels.h"
+#include "quotient.h"
 #include "update_device.h"
 #include "xcd_tiles.h"
 
@@ -342,7 +343,7 @@ struct SmallWgradJob {
   float* vel;
   float* vel_bias;
   int M, N, tiles_n;
-  uint32_t by_tiles_n;   // see reciprocal()
+  uint32_t by_tiles_n;   // reciprocal_below(tiles_n)
 };
 struct SmallWgrad {
   int n, tiles;
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(256, 2) void small_wgrad_kernel(SmallWgrad p, Segme
   for (int i = 1; i < kSmallJobs; ++i) ji += i < p.n && tile >= p.first[i] ? 1 : 0;
   const SmallWgradJob& J = p.job[ji];
   const int local = tile - p.first[ji];
-  const int tile_m = J.tiles_n == 1 ? local : J.by_tiles_n ? (int)__umulhi((uint32_t)local, J.by_tiles_n) : local / J.tiles_n;
+  const int tile_m = quotient(local, J.by_tiles_n, J.tiles_n);
   const int tile_n = local - tile_m * J.tiles_n;
   const int M = J.M, N = J.N;
   const int r = lane & 15, g = lane >> 4;
@@ -717,9 +718,6 @@ void small_gemm(hipStream_t st, SmallGemm p, const HeadWgradParams* head, const 
     hipLaunchKernelGGL((small_gemm_kernel<DGRAD, 1, 4>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
 }
 
-// 2^32 / d rounded up for the quotients n / d of n < `below`, 0 where it is not exact for all of them
-uint32_t reciprocal(int d, long below) { return d > 1 && below * d < 1l << 32 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; }
-
 template <int WB, int NW>
 void launch_wgrad(hipStream_t st, const SmallWgrad& p, const Segments& seg, const Lambdas& lam, const Optim& opt,
                   const HeadLossParams& hl, int upd, bool loss, const KernelTimer* timer) {
@@ -818,7 +816,7 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
       q.tiles_n = (j.cin + TN - 1) / TN;
       p.first[i] = p.tiles;
       p.tiles += (j.cout + 15) / 16 * q.tiles_n;
-      q.by_tiles_n = reciprocal(q.tiles_n, p.tiles - p.first[i]);
+      q.by_tiles_n = reciprocal_below(q.tiles_n, p.tiles - p.first[i]);
     }
     if (timer) (void)hipEventRecord(timer->start, st);
     hipLaunchKernelGGL((small_wgrad_kernel<4, 4, 0, true>), dim3(p.tiles * sh.first[seg.K] + (loss ? 1 : 0)), dim3(256), 0, st,
@@ -850,7 +848,7 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
       q.tiles_n = (j.cin + TN - 1) / TN;
       p.first[i] = p.tiles;
       p.tiles += (j.cout + 15) / 16 * q.tiles_n;
-      q.by_tiles_n = reciprocal(q.tiles_n, p.tiles - p.first[i]);
+      q.by_tiles_n = reciprocal_below(q.tiles_n, p.tiles - p.first[i]);
     }
     const bool last = base + kSmallJobs >= n;
     const HeadLossParams hl = loss ? *loss : HeadLossParams{};

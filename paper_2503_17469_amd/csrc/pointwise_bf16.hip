@@ -8,6 +8,7 @@
 #include "cast_device.h"
 #include "common.h"
 #include "kernels.h"
+#include "quotient.h"
 
 namespace omni {
 
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(256) void maxpool2_bwd_kernel(const bf16_t* __restr
 struct UnpoolDims {
   long n_out;          // pieces of 8 channels
   int W, C;            // of the tensor that was pooled
-  uint32_t by_c8, by_wh;   // 2^32 / (C / 8) and / (W / 2), rounded up; 0: the quotients are not all exact (or the divisor is 1)
+  uint32_t by_c8, by_wh;   // reciprocal_below of C / 8 and W / 2
 };
 __global__ __launch_bounds__(256) void maxpool2_bwd_coded_kernel(const uint8_t* __restrict__ code,
                                                                  const bf16_t* __restrict__ dout,
@@ -184,9 +185,8 @@ void maxpool2_fwd_bf16(hipStream_t st, const bf16_t* in, bf16_t* out, int rows, 
 void maxpool2_bwd_coded_bf16(hipStream_t st, const uint8_t* code, const bf16_t* dout, bf16_t* din, int rows, int H,
                              int W, int C) {
   UnpoolDims d{(long)rows * (H / 2) * (W / 2) * (C / 8), W, C, 0u, 0u};
-  auto reciprocal = [](long by, long below) { return by > 1 && below * by < 1l << 32 ? (uint32_t)(((1l << 32) + by - 1) / by) : 0u; };
-  d.by_c8 = reciprocal(C / 8, d.n_out);
-  d.by_wh = reciprocal(W / 2, d.n_out / (C / 8));
+  d.by_c8 = reciprocal_below(C / 8, d.n_out);
+  d.by_wh = reciprocal_below(W / 2, d.n_out / (C / 8));
   hipLaunchKernelGGL(maxpool2_bwd_coded_kernel, dim3(blocks_for(d.n_out)), dim3(256), 0, st, code, dout, din, d);
 }
 

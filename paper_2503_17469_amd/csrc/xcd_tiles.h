@@ -7,13 +7,15 @@
 #include <algorithm>
 #include <cstdint>
 
+#include "quotient.h"
+
 namespace omni {
 
 struct XcdTiles {
   int tiles_m, tiles_n;   // all tiles
   int cm, cn;             // an XCD's rectangle
   int lsm;                // 2^lsm XCDs along m, 8 >> lsm along n
-  uint32_t by_cm;         // 2^32 / cm rounded up where that gives every quotient of the rectangle, otherwise 0
+  uint32_t by_cm;         // reciprocal_below(cm)
   int grid() const { return 8 * cm * cn; }
 };
 
@@ -26,16 +28,14 @@ inline XcdTiles xcd_tiles(int tiles_m, int tiles_n) {
     if (lsm == 0 || cm * cn < best.cm * best.cn || (cm * cn == best.cm * best.cn && cm + cn < best.cm + best.cn))
       best = XcdTiles{tiles_m, tiles_n, cm, cn, lsm, 0};
   }
-  if (best.cm > 1 && (uint64_t)best.cm * best.cm * best.cn < 1ull << 32)
-    best.by_cm = (uint32_t)(((1ull << 32) + best.cm - 1) / best.cm);
+  best.by_cm = reciprocal_below(best.cm, (uint64_t)best.cm * best.cn);
   return best;
 }
 
-// False: this workgroup has no tile.  (Row tiles fastest.  A run-time division takes 150 to 300 cycles, two of them stood
-// in front of every product's first load.)
+// False: this workgroup has no tile.  (Row tiles fastest.)
 __device__ __forceinline__ bool xcd_tile(const XcdTiles& x, int b, int& tile_m, int& tile_n) {
   const int xcd = b & 7, local = b >> 3;
-  const int ln = x.cm == 1 ? local : x.by_cm ? (int)__umulhi((uint32_t)local, x.by_cm) : local / x.cm, lm = local - ln * x.cm;
+  const int ln = quotient(local, x.by_cm, x.cm), lm = local - ln * x.cm;
   const int xn = xcd >> x.lsm, xm = xcd - (xn << x.lsm);
   tile_m = xm * x.cm + lm;
   tile_n = xn * x.cn + ln;
