@@ -663,73 +663,74 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
   if (want_bias && tid < 64 && co0 + tid < p.Cout) p.gb[(size_t)wk * p.worker_stride + co0 + tid] = bsum;
 }
 
+// ---- the order in which a worker's chunks are added, in the second stage and in the one with the update alike (their results are
+// the same bits): four quarters of the chunks, each in chunk order, one after the other; the bias gradients in one chain.
+__device__ inline int quarter_chunks(int n) { return (n + 3) >> 2; }
+__device__ inline float add_quarters(float a, float b, float c, float d) { return ((a + b) + c) + d; }
+// E sums of n values each, `stride` apart (neighbouring sums' `next` apart), eight loads of each in flight.
+template <int E>
+__device__ inline void add_chain(const float* src, int n, size_t stride, int next, float (&s)[E]) {
+  for (int c = 0; c < n; c += 8) {
+    float t[8][E];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) t[u][e] = src[(size_t)min(c + u, n - 1) * stride + e * next];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) s[e] = c + u < n ? s[e] + t[u][e] : s[e];
+  }
+}
+__device__ inline float chain_of(const float* src, int n, size_t stride) {
+  float s[1] = {0.f};
+  add_chain<1>(src, n, stride, 0, s);
+  return s[0];
+}
+
+// Kernel C's element of a tile: register v of one tap and quadrant, as lane `lane` held it.
+struct Place3 {
+  int co0, ci0, wci, co, ci;
+  size_t at;      // in the weight
+  bool in;
+};
+__device__ __forceinline__ Place3 wgrad3_place(const Wgrad3Params& p, int tile, int quad, int tap, int v, int lane) {
+  const int tiles_ci = (p.Cin + 63) / 64, row = tile / tiles_ci;
+  const int co0 = row * 64, ci0 = (tile - row * tiles_ci) * 64, wci = (quad & 1) * 32;
+  const int co = co0 + (quad >> 1) * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4), ci = ci0 + wci + (lane & 31);
+  return Place3{co0, ci0, wci, co, ci, ((size_t)co * 9 + tap) * p.cin_real + ci, co < p.Cout && ci < p.cin_real};
+}
+
 // Second stage: one workgroup per (tile, worker, 9 taps x 4 register quarters x 4 tile quadrants); it
 // owns the (output channel, input channel) pairs one wavefront of the first stage held; each of its
-// four wavefronts adds a quarter of the worker's chunks (chunk order, eight chunks in flight), the
-// quarters are then added in order through LDS: a fixed summation order with four times the loads in
+// four wavefronts adds a quarter of the worker's chunks (32 loads in flight), the quarters meet in LDS: four times the loads in
 // flight of one wavefront walking all chunks.
 __device__ __forceinline__ void wgrad3_reduce(const Wgrad3Params& p, const Chunk& ck, int tile, int z, float* lds) {
   float (*part)[4][64] = reinterpret_cast<float (*)[4][64]>(lds);   // [4]
   const int wk = ck.wk, nchunks = ck.n;
   const int quad = z & 3, vq = (z >> 2) & 3, tap = z >> 4;
   const int tid = threadIdx.x, lane = tid & 63, sub = tid >> 6;
-  const int j = lane & 31, h = lane >> 5;
-  const int tiles_ci = (p.Cin + 63) / 64;
-  const int co0 = (tile / tiles_ci) * 64, ci0 = (tile % tiles_ci) * 64;
-  const int wco = (quad >> 1) * 32, wci = (quad & 1) * 32;
   const float* all = p.partial + ((size_t)tile * ck.total + ck.row) * kTile3Stride;
   const float* mine = all + (size_t)(tap * 16 + vq * 4) * kThreads + quad * 64 + lane;
-  const int per = (nchunks + 3) / 4;
+  const int per = quarter_chunks(nchunks);
   const int c0 = min(sub * per, nchunks), c1 = min(c0 + per, nchunks);
+  const Place3 first = wgrad3_place(p, tile, quad, tap, 4 * vq, lane);
   float s[4] = {0.f, 0.f, 0.f, 0.f};
-  const int ci = ci0 + wci + j;
-  if (ci < p.cin_real) {
-    int c = c0;
-    for (; c + 8 <= c1; c += 8) {
-      float t[8][4];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) t[u][e] = mine[(size_t)(c + u) * kTile3Stride + e * kThreads];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[e] += t[u][e];
-    }
-    for (; c < c1; ++c) {
-      const float* q = mine + (size_t)c * kTile3Stride;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] += q[e * kThreads];
-    }
-  }
+  if (first.ci < p.cin_real) add_chain<4>(mine + (size_t)c0 * kTile3Stride, c1 - c0, kTile3Stride, kThreads, s);
 #pragma unroll
   for (int e = 0; e < 4; ++e) part[sub][e][lane] = s[e];
   __syncthreads();
-  if (sub == 0 && ci < p.cin_real) {
+  if (sub == 0) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float tot = ((part[0][e][lane] + part[1][e][lane]) + part[2][e][lane]) + part[3][e][lane];
-      const int v = vq * 4 + e;
-      const int co = co0 + wco + 8 * (v / 4) + 4 * h + (v % 4);
-      if (co < p.Cout) p.gw[(size_t)wk * p.worker_stride + ((size_t)co * 9 + tap) * p.cin_real + ci] = tot;
+      const Place3 pl = wgrad3_place(p, tile, quad, tap, 4 * vq + e, lane);
+      const float tot = add_quarters(part[0][e][lane], part[1][e][lane], part[2][e][lane], part[3][e][lane]);
+      if (pl.in) p.gw[(size_t)wk * p.worker_stride + pl.at] = tot;
     }
   }
-  if (z == 0 && p.gb != nullptr && ci0 == 0 && tid < 64 && co0 + tid < p.Cout) {
-    // eight loads in flight (one dependent round trip per chunk made this the kernel's long pole);
-    // the additions keep chunk order
-    float bs = 0.f;
-    const float* bsrc = all + kTile3Floats + tid;
-    int c = 0;
-    for (; c + 8 <= nchunks; c += 8) {
-      float t[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = bsrc[(size_t)(c + u) * kTile3Stride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) bs += t[u];
-    }
-    for (; c < nchunks; ++c) bs += bsrc[(size_t)c * kTile3Stride];
-    p.gb[(size_t)wk * p.worker_stride + co0 + tid] = bs;
-  }
+  const int co = first.co0 + tid;
+  if (z == 0 && p.gb != nullptr && first.ci0 == 0 && tid < 64 && co < p.Cout)
+    p.gb[(size_t)wk * p.worker_stride + co] = chain_of(all + kTile3Floats + tid, nchunks, kTile3Stride);
 }
 
 
@@ -783,14 +784,11 @@ __device__ inline int wgrad1_y_offset(int pos, int oct) {
 __host__ __device__ inline int wgrad1_col_blocks(int cin_real) { return cin_real * 9 + 1 > 32 ? 2 : 1; }
 __host__ __device__ constexpr int wgrad1_stage_bytes(int mb, int cin_real) { return kG_Unit * 64 * mb + 3 * cin_real * kG_Plane; }
 
-// (co, column) of accumulator register v of lane l in block (mb, nb) -> where it goes in G
-__device__ inline void wgrad1_emit(const Wgrad1Params& p, float* gw, float* gb, int mb, int nb, int v, int lane,
-                                   float val) {
-  const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-  const int col = nb * 32 + (lane & 31);
-  if (co >= p.Cout) return;
-  if (col < 9 * p.cin_real) gw[(size_t)co * 9 * p.cin_real + col] = val;
-  else if (col == 9 * p.cin_real && gb != nullptr) gb[co] = val;
+// Where the value of accumulator register v of lane `lane` in block (mb, nb) goes in G, null where it is none's (gw, gb: the worker's)
+__device__ inline float* wgrad1_place(const Wgrad1Params& p, float* gw, float* gb, int mb, int nb, int v, int lane) {
+  const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4), col = nb * 32 + (lane & 31), cols = 9 * p.cin_real;
+  if (co >= p.Cout) return nullptr;
+  return col < cols ? gw + (size_t)co * cols + col : col == cols && gb != nullptr ? gb + co : nullptr;
 }
 
 // POOLED: the layer's output gradient was never written.  Every position takes the gradient of its
@@ -1011,14 +1009,14 @@ __device__ __forceinline__ void wgrad1_body(const Wgrad1Params& p, const Segment
       p.partial[(size_t)ck.row * kImg + e] = val;
     } else {
       const int blk = e / (16 * 64), v = (e / 64) % 16, l = e % 64;
-      wgrad1_emit(p, gw, gb, blk / NB, blk % NB, v, l, val);
+      float* const to = wgrad1_place(p, gw, gb, blk / NB, blk % NB, v, l);
+      if (to) *to = val;
     }
   }
 }
 
 // One workgroup per worker and 64 of the MB * NB * 1024 accumulator elements; each of the four wavefronts adds a
-// quarter of the worker's chunks (in chunk order, eight loads in flight), the quarters are then
-// added in order through LDS: a fixed summation order with four times the loads in flight.
+// quarter of the worker's chunks (eight loads in flight), the quarters meet in LDS.
 __device__ __forceinline__ void wgrad1_reduce(const Wgrad1Params& p, const Chunk& ck, int z, float* lds) {
   const int NB = wgrad1_col_blocks(p.cin_real);
   const int kImg = (p.Cout > 32 ? 2 : 1) * NB * 16 * 64;
@@ -1026,27 +1024,17 @@ __device__ __forceinline__ void wgrad1_reduce(const Wgrad1Params& p, const Chunk
   const int wk = ck.wk, nchunks = ck.n;
   const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
   const int e = z * 64 + lane;
-  const int per = (nchunks + 3) / 4;
+  const int per = quarter_chunks(nchunks);
   const int c0 = min(sub * per, nchunks), c1 = min(c0 + per, nchunks);
-  const float* src = p.partial + (size_t)ck.row * kImg + e;
-  float s = 0.f;
-  int c = c0;
-  for (; c + 8 <= c1; c += 8) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(c + u) * kImg];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += t[u];
-  }
-  for (; c < c1; ++c) s += src[(size_t)c * kImg];
-  part[sub][lane] = s;
+  part[sub][lane] = chain_of(p.partial + (size_t)(ck.row + c0) * kImg + e, c1 - c0, kImg);
   __syncthreads();
   if (sub != 0) return;
-  s = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+  const float s = add_quarters(part[0][lane], part[1][lane], part[2][lane], part[3][lane]);
   float* gw = p.gw + (size_t)wk * p.worker_stride;
   float* gb = p.gb ? p.gb + (size_t)wk * p.worker_stride : nullptr;
   const int blk = e / (16 * 64), v = (e / 64) % 16, l = e % 64;
-  wgrad1_emit(p, gw, gb, blk / NB, blk % NB, v, l, s);
+  float* const to = wgrad1_place(p, gw, gb, blk / NB, blk % NB, v, l);
+  if (to) *to = s;
 }
 
 // ------------------------------------------------------------------ launches of several layers
@@ -1175,9 +1163,9 @@ __device__ inline void update_one(const UpdateTo& to, size_t at, float th, float
   if (MOM) to.vel[at] = ve;
 }
 
-// The sum of n values `stride` apart in the order of the second stage above: four quarters, added one after the other.
+// The second stage's sum of n values `stride` apart, by one wavefront: the four quarters side by side.
 __device__ inline float sum_quarters(const float* src, int n, size_t stride) {
-  const int per = (n + 3) >> 2;
+  const int per = quarter_chunks(n);
   float a[4] = {0.f, 0.f, 0.f, 0.f};
   for (int i = 0; i < per; i += 4) {               // sixteen loads in flight
     float t[4][4];
@@ -1190,19 +1178,7 @@ __device__ inline float sum_quarters(const float* src, int n, size_t stride) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) a[q] = i + u < per && q * per + i + u < n ? a[q] + t[u][q] : a[q];
   }
-  return ((a[0] + a[1]) + a[2]) + a[3];
-}
-// ... and in one chain, as the bias gradients'.
-__device__ inline float sum_chain(const float* src, int n, size_t stride) {
-  float a = 0.f;
-  for (int c = 0; c < n; c += 8) {
-    float t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = src[(size_t)min(c + u, n - 1) * stride];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) a = c + u < n ? a + t[u] : a;
-  }
-  return a;
+  return add_quarters(a[0], a[1], a[2], a[3]);
 }
 
 // Kernel C: a workgroup has one register of one tap and tile quadrant (the pairs one wavefront of the first stage held), its
@@ -1213,15 +1189,12 @@ __device__ __forceinline__ void wgrad3_update(const Wgrad3Params& p, const Batch
                                               const Lambdas& lam, const Optim& opt, const UpdateTo& to, float* lds) {
   const int quad = z & 3, v = (z >> 2) & 15, tap = z >> 6;
   const int tid = threadIdx.x, lane = tid & 63, sub = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j = lane & 31, h = lane >> 5, K = seg.K;
-  const int tiles_ci = (p.Cin + 63) / 64;
-  const int co0 = (tile / tiles_ci) * 64, ci0 = (tile % tiles_ci) * 64;
-  const int wco = (quad >> 1) * 32, wci = (quad & 1) * 32, ci = ci0 + wci + j;
-  const bool with_bias = z == 0 && p.gb != nullptr && ci0 == 0;
-  if (ci0 + wci >= p.cin_real) return;             // (nothing there; quadrant 0, which has the bias, never)
-  const int my_co = co0 + wco + 8 * (v / 4) + 4 * h + (v % 4);
-  const bool in = my_co < p.Cout && ci < p.cin_real;
-  const size_t at = in ? ((size_t)my_co * 9 + tap) * p.cin_real + ci : 0, mine = (size_t)(p.gw - to.G) + at;
+  const int K = seg.K;
+  const Place3 pl = wgrad3_place(p, tile, quad, tap, v, lane);
+  const int co0 = pl.co0;
+  const bool with_bias = z == 0 && p.gb != nullptr && pl.ci0 == 0, in = pl.in;
+  if (pl.ci0 + pl.wci >= p.cin_real) return;       // (nothing there; quadrant 0, which has the bias, never)
+  const size_t at = in ? pl.at : 0, mine = (size_t)(p.gw - to.G) + at;
   const float th = to.theta[mine], ve = MOM ? to.vel[mine] : 0.f;
   const float* const tiles = p.partial + (size_t)tile * job.chunk[K] * kTile3Stride;
   for (int wk = sub; wk < K; wk += kThreads / 64) {
@@ -1250,7 +1223,7 @@ __device__ __forceinline__ void wgrad3_update(const Wgrad3Params& p, const Batch
     float* const gb = p.gb + (size_t)wk * p.worker_stride + co;
     float s;
     if (n > 1) {
-      s = sum_chain(tiles + (size_t)c0 * kTile3Stride + kTile3Floats + co - co0, n, kTile3Stride);
+      s = chain_of(tiles + (size_t)c0 * kTile3Stride + kTile3Floats + co - co0, n, kTile3Stride);
       if (co0 + lane < p.Cout) *gb = s;
     } else {
       s = *gb;
@@ -1273,9 +1246,9 @@ __device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const Batch
   const int NB = wgrad1_col_blocks(p.cin_real), MB = p.Cout > 32 ? 2 : 1, kImg = MB * NB * 16 * 64, K = seg.K;
   const int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int e = z * 64 + lane, blk = z >> 4, v = z & 15, mb = NB == 2 ? blk >> 1 : blk, nb = NB == 2 ? blk & 1 : 0;
-  const int co = mb * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4), col = nb * 32 + (lane & 31), cols = 9 * p.cin_real;
-  const bool in = co < p.Cout && (col < cols || (col == cols && p.gb));
-  float* const g0 = !in ? p.gw : col < cols ? p.gw + (size_t)co * cols + col : p.gb + co;   // worker 0's
+  float* const place = wgrad1_place(p, p.gw, p.gb, mb, nb, v, lane);
+  const bool in = place != nullptr;
+  float* const g0 = in ? place : p.gw;             // worker 0's
   const size_t at = (size_t)(g0 - to.G);
   const float th = to.theta[at], ve = MOM ? to.vel[at] : 0.f;
   for (int wk = sub; wk < K; wk += kThreads / 64) {
