@@ -25,6 +25,21 @@ if ROOT not in sys.path:
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}
 PEAK_HBM_GBS = 8000.0
 
+# What else the launches of a class carry, so that their time has it too.
+CLASS_NOTES = {
+    "linear_dgrad": "with the classifier's parameter gradients and the losses",
+    "linear_wgrad": "with the update of all parameters; mlp3072: six bf16 products of operands in three pieces stand for an fp32 one",
+    "conv_fwd": "with the bf16 copies of the weights",
+    "conv_wgrad": "with the classifier's parameter gradients and the losses, and in the three-layer networks, whose weight "
+                  "gradients are one group, with the update of all parameters",
+}
+DTYPE_NOTES = {
+    "bf16": "bf16 operands and stored activations, fp32 accumulation, fp32 parameters, gradients, loss and update",
+    "f32": "fp32 operands, sums, parameters, gradients, loss and update",
+    "mlp3072": "fp32 operands, sums, parameters, gradients, loss and update; the hidden weight gradients are formed on the bf16 matrix "
+               "instruction, each operand as the exact sum of three bf16 values, six of the nine products (the other three are at "
+               "most 2^-24 of a product together), the rest on the fp32 instruction",
+}
 # contraction kernel classes of a step, per dtype (names of the library's timing classes)
 CLASSES = {"f32": ("linear_fwd", "linear_dgrad", "linear_wgrad"), "bf16": ("conv_fwd", "conv_dgrad", "conv_wgrad")}
 PREWARM_S = 2.0     # steps are repeated for at least this long before anything is timed (clocks settle)
@@ -228,7 +243,7 @@ class Job:
                         "unit": "TFLOP/s", "frac": ach / PEAK_TFLOPS[w.dtype],
                         "traffic": measured_traffic(w.name, cls),
                         "traffic_note": "HBM bytes of all the class's launches in a step, by counters",
-                        "flop_per_step": flops,
+                        "note": CLASS_NOTES.get(cls), "flop_per_step": flops,
                         "us_per_step": per_step_s * 1e6, "avg_launch_us": ms * 1e3 / n, "launches": int(n),
                         "steps": steps})
         return out
@@ -435,8 +450,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": w.dtype,
-        "dtype_note": ("bf16 operands and stored activations, fp32 accumulation, fp32 parameters, gradients, loss "
-                       "and update" if w.dtype == "bf16" else "fp32 throughout"),
+        "dtype_note": DTYPE_NOTES.get(w.name, DTYPE_NOTES[w.dtype]),
         "data": "synthetic",
         "config": {"workload": w.name, "K": w.K, "B": w.B, "b": job.b, "params": int(w.P),
                    "includes": "controller+offsets+fwd+loss+bwd+weighted reduce+SGD"},

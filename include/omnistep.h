@@ -166,7 +166,10 @@ typedef struct omni_net omni_net;
 
 /* Builds the launch plan for (layers, input shape, dtype, K_max, B_max).  Host
  * only: allocates no device memory and compiles nothing, now or later.
- * dtype OMNI_F32: fp32 operands and activations.  dtype OMNI_BF16: bf16
+ * dtype OMNI_F32: fp32 operands, activations and sums (products whose 128 x 128
+ * tiles fill the chip are formed from three bf16 pieces per operand, which carry
+ * all 24 bits; their error against exact arithmetic is that of the fp32
+ * instruction's products or less).  dtype OMNI_BF16: bf16
  * operands and stored activations, fp32 accumulation, fp32 master parameters,
  * gradients and loss.  OMNI_EINVAL on a malformed layer list or an unsupported
  * combination. */
@@ -303,7 +306,11 @@ int64_t omni_net_graph_replays(const omni_net* net);
  * head's own parameter gradients (with the per-worker losses) share a launch
  * with the input gradient of the layer below it where that product takes the
  * small-batch kernel: the launch counts as that layer's OMNI_KERNEL_LINEAR_DGRAD,
- * and OMNI_KERNEL_LOSS then covers the head's forward / loss / dz kernel only. */
+ * and OMNI_KERNEL_LOSS then covers the head's forward / loss / dz kernel only.
+ * Convolutional networks: OMNI_KERNEL_CONV_FWD has the bf16 copies of the weights
+ * where the first layer's launch makes them, OMNI_KERNEL_CONV_WGRAD the head's
+ * parameter gradients and, where all weight gradients are one group, the update
+ * (unless OMNI_KERNEL_UPDATE is what is timed, which takes it apart). */
 enum {
   OMNI_KERNEL_LINEAR_FWD = 0,
   OMNI_KERNEL_LINEAR_DGRAD = 1,
