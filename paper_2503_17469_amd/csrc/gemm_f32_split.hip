@@ -162,23 +162,29 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
 
   // The reduction is a stream of slabs over chunks (weight gradient: of the workers' rows; else one); w == nrange marks the end.
   // A slab that would run past the end of its chunk is moved back to end there, and what is not its own is cleared in both operands.
-  struct Slab { int c, w, k0, kend; };    // chunk, worker, first reduction element, end of the chunk
+  enum { kCont = 1, kMore = 2 };                  // the worker has chunks before this one, behind it
+  struct Slab { int c, w, k0, kend, pieces; };    // chunk, worker, first reduction element, end of the chunk, the two above
   const int nrange = WGRAD ? seg.K : 1;
-  auto first = [&]() {
-    return WGRAD ? Slab{0, 0, seg.off[0], min(seg.off[0] + kChunkRows, (int)seg.off[1])} : Slab{0, 0, 0, p.kred};
+  auto chunk = [&](Slab s) {              // its end
+    const int end = seg.off[s.w + 1];
+    s.kend = min(s.k0 + kChunkRows, end);
+    if (s.kend < end) s.pieces |= kMore;
+    return s;
   };
+  auto first = [&]() { return WGRAD ? chunk(Slab{0, 0, seg.off[0], 0, 0}) : Slab{0, 0, 0, p.kred, 0}; };
   auto after = [&](Slab s) {
     if (s.w >= nrange) return s;
-    Slab t{s.c, s.w, s.k0 + BK, s.kend};
+    Slab t{s.c, s.w, s.k0 + BK, s.kend, s.pieces};
     if (t.k0 < s.kend) return t;
     ++t.c;
     t.k0 = s.kend;
-    if (!WGRAD || s.kend >= seg.off[s.w + 1]) {
+    t.pieces = kCont;
+    if (!WGRAD || !(s.pieces & kMore)) {
       if (++t.w >= nrange) return t;
       t.k0 = seg.off[t.w];
+      t.pieces = 0;
     }
-    t.kend = min(t.k0 + kChunkRows, (int)seg.off[t.w + 1]);
-    return t;
+    return chunk(t);
   };
   auto live = [&](Slab s) { return s.w < nrange ? s : first(); };
   auto start = [&](Slab s) { return s.k0 + BK <= s.kend ? s.k0 : max(s.kend - BK, 0); };
@@ -360,10 +366,13 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
       int ft = tid;
       asm volatile("" : "+v"(ft));      // (addresses are worked out here, not kept in registers through the loop)
       float* C = p.C + (size_t)done.w * p.c_worker_stride;
-      const bool cont = done.kend > seg.off[done.w] + kChunkRows;      // added to the worker's earlier chunks
-      const bool whole = !cont && row0 + kTile <= p.M && col0 + kTile <= p.N;
       float* out = reinterpret_cast<float*>(cur == 1 ? lds + kStage : lds);
       if (want_bias_grad) bred[Operand<A_MC>::k8_of(ft)][Operand<A_MC>::row_of(ft)] = bsum;
+      const bool cont = done.pieces & kCont;       // added to the worker's earlier chunks
+      const bool whole = !cont && row0 + kTile <= p.M && col0 + kTile <= p.N;
+      // The update takes G once it is complete, as one in a launch of its own does: the same bits.
+      const bool complete = !(done.pieces & kMore);
+      const float weight = UPD ? lam->v[done.w] : 0.f;
 #pragma unroll
       for (int part = 0; part < kParts; ++part) {
         __syncthreads();
@@ -382,10 +391,9 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
         for (int q = 0; q < kPieces / kParts; ++q) {
           const int idx = ft + kThreads * q, r = idx / (kTile / 4), c4 = (idx % (kTile / 4)) * 4;
           const float* o = out + r * kFlushPitch + c4;
-          const v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale -
-                        *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
+          v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale -
+                  *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
           const int row = row0 + part * kFlushRows + r;
-          if (UPD) gsum[part * (kPieces / kParts) + q] += lam->v[done.w] * g;
           float* dst = C + (size_t)row * p.ldc + col0 + c4;
           if (whole) {
             *reinterpret_cast<v4f_a4*>(dst) = g;
@@ -394,22 +402,28 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
             // pieces of a worker with 4096 rows 37)
             if (col0 + c4 + 4 <= p.N) {
               v4f_a4* const to = reinterpret_cast<v4f_a4*>(dst);
-              *to = cont ? *to + g : g;
+              if (cont) g += *to;
+              *to = g;
             } else {
 #pragma unroll
               for (int e = 0; e < 3; ++e)
-                if (col0 + c4 + e < p.N) dst[e] = cont ? dst[e] + g[e] : g[e];
+                if (col0 + c4 + e < p.N) {
+                  if (cont) g[e] += dst[e];
+                  dst[e] = g[e];
+                }
             }
           }
+          if (UPD && complete) gsum[part * (kPieces / kParts) + q] += weight * g;
         }
       }
       if (want_bias_grad && ft < kTile) {
-        const float g = (bred[0][ft] + bred[1][ft]) + (bred[2][ft] + bred[3][ft]);
-        if (UPD) bgsum += lam->v[done.w] * g;
+        float g = (bred[0][ft] + bred[1][ft]) + (bred[2][ft] + bred[3][ft]);
         if (row0 + ft < p.M) {
           float* dst = p.bias_grad + (size_t)done.w * p.c_worker_stride + row0 + ft;
-          *dst = cont ? *dst + g : g;
+          if (cont) g += *dst;
+          *dst = g;
         }
+        if (UPD && complete) bgsum += weight * g;
       }
       __syncthreads();      // (the free stage is written again)
 #pragma unroll

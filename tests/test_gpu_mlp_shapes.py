@@ -50,7 +50,8 @@ def test_shapes(dims, off):
 
 
 @pytest.mark.parametrize("dims,off", [([61, 35, 6], [0, 9, 30]), ([257, 61, 7], [0, 300, 301, 900]),
-                                      ([1030, 1022, 5], [0, 40, 97])])
+                                      ([1030, 1022, 5], [0, 40, 97]),
+                                      ([3400, 1021, 10], [0, 600, 1300, 1400])])      # split products, workers' rows in two pieces and in one
 @pytest.mark.parametrize("momentum", [False, True])
 def test_update_inside_the_weight_gradient_launch(dims, off, momentum):
     """Bit for bit the update as a launch of its own (which a caller that times it gets), several steps on."""

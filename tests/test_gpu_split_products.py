@@ -252,3 +252,59 @@ def test_errors_have_no_direction():
 ])
 def test_workers_do_not_depend_on_each_other(dims, off, bad, value):
     _isolated(synth.mlp(dims), (1, 1, dims[0]), "f32", off, bad, value, sum(dims))
+
+
+@pytest.mark.parametrize("momentum", [False, True])
+@pytest.mark.parametrize("off", [[0, 300, 1100], [0, 600, 1300, 1400]])      # (workers of two chunks, of one)
+def test_update_of_sums_formed_again(off, momentum):
+    """Some columns of x are 2^110 in some workers' rows (their weights are zero, so that nothing else notices): the pieces of these are
+    no numbers, the sums of the whole tile's such columns are formed again on the fp32 instruction, and the update takes them.
+    Columns inside a tile, in the last one and in the same 16 bytes as others; rows of the last tile's 125.  Gradients against
+    float64, the other columns' as without them, parameters and velocity bit for bit the weighted sum of what was stored."""
+    import torch
+    import paper_2503_17469_amd as omni
+    dims, bad = [3400, 1021, 10], [0, 5, 6, 127, 128, 1030, 3398]
+    layers = synth.mlp(dims)
+    K, B = len(off) - 1, off[-1]
+    b = [off[k + 1] - off[k] for k in range(K)]
+    rng = np.random.default_rng(B)
+    params = synth.he_normal_params(layers, 7, False)
+    s, t = synth.param_slices(layers)[0]["w"]
+    params[s:t].reshape(dims[1], dims[0])[:, bad] = 0
+    x = rng.standard_normal((B, dims[0])).astype(np.float32)
+    y = rng.integers(0, dims[-1], B).astype(np.int32)
+    large = x.copy()
+    large[off[1] - 7:, bad] *= np.float32(2.0 ** 110)          # (the last rows of the first worker, and the other workers)
+    out = []
+    for xs in (x, large):
+        run = GpuRun(layers, (1, 1, dims[0]), "f32", K, B)
+        try:
+            p = torch.from_numpy(params).cuda()
+            v = torch.randn(p.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(1)) * 0.01
+            p0, v0 = p.clone(), v.clone()
+            if momentum:
+                omni.net_set_momentum(run.net, v, 0.9, 5e-4)
+            omni.step(run.net, p, torch.from_numpy(xs).cuda(), torch.from_numpy(y).cuda(), off, b, 0.05, run.ws, run.lpw, run.loss)
+            G = omni.net_worker_grads(run.net, run.ws, K)
+            full = torch.zeros(K, (params.size + 63) // 64 * 64, device="cuda")
+            full[:, :params.size] = G[:, :params.size]
+            if momentum:
+                omni.weighted_sgd_momentum(p0, v0, full, b, 0.05, 0.9, 5e-4, None)
+            else:
+                omni.weighted_sgd(p0, full, b, 0.05, None)
+            torch.cuda.synchronize()
+            assert torch.isfinite(p).all()
+            assert torch.equal(p, p0) and torch.equal(v, v0)
+            out.append((full.cpu().double().numpy(), omni.net_activation_grad(run.net, run.ws, 0, B, "f32").double().cpu().numpy()))
+        finally:
+            run.close()
+    (clean, dy), (got, dy2) = out
+    assert np.array_equal(dy, dy2)
+    clean, got = (g[:, s:t].reshape(K, dims[1], dims[0]) for g in (clean, got))
+    rest = np.setdiff1d(np.arange(dims[0]), bad)
+    assert np.array_equal(got[:, :, rest], clean[:, :, rest])
+    for k in range(K):
+        a, c = dy[off[k]:off[k + 1]].reshape(b[k], -1).T, large[off[k]:off[k + 1]][:, bad].astype(np.float64)
+        assert np.abs(a @ c).max() > 2.0 ** 90
+        # (one chain of fp32 products, two at a time)
+        assert (np.abs(got[k][:, bad] - a @ c) <= b[k] * U * (np.abs(a) @ np.abs(c))).all()
