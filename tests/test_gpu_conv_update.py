@@ -1,13 +1,42 @@
 """The update by the launch that adds the chunks of the convolutions' weight gradients: bit for bit the update as a launch of its own
 (which a caller that times it gets), with and without momentum, several steps on; workers of one chunk and of many, first layers
-with a kernel of their own and without, channel tiles that are not full, a layer whose second stage is another (no fusion)."""
+with a kernel of their own and without, channel tiles that are not full, parameters that are no convolution's.  The same of networks
+that have the update in a launch of its own: a layer whose second stage is another, hidden fully connected layers."""
 import numpy as np
 import pytest
 
 import synth
 from gpu_util import GpuRun
+from test_gpu_cnn import _check_step
 
 pytestmark = pytest.mark.gpu
+
+
+def _net(*ops):
+    """Of 16x16x3 inputs.  conv: output channels, size, stride (no bias where a batch norm follows); linear: outputs."""
+    layers, shape = [], (16, 16, 3)
+    for i, (op, *a) in enumerate(ops):
+        L = dict(op=op, src=len(layers) - 1)
+        if op == "conv":
+            L.update(cin=shape[2], cout=a[0], k=a[1], stride=a[2], pad=a[1] // 2, bias=ops[i + 1][0] != "bn")
+        elif op == "bn":
+            L.update(c=shape[2])
+        elif op == "linear":
+            L.update(cin=shape[0] * shape[1] * shape[2], cout=a[0], bias=True)
+        layers.append(L)
+        shape = synth.layer_shapes(layers, (16, 16, 3))[-1]
+    return layers
+
+
+RELU, BN, POOL, GAP = ("relu",), ("bn",), ("maxpool2",), ("gap",)
+NETS = {
+    "batch norms, 3x3 only": _net(("conv", 32, 3, 1), BN, RELU, ("conv", 64, 3, 1), BN, RELU, POOL, ("conv", 40, 3, 1), RELU, GAP,
+                                  ("linear", 10)),
+    "stride 2": _net(("conv", 32, 3, 1), RELU, ("conv", 64, 3, 2), RELU, ("conv", 64, 3, 1), RELU, GAP, ("linear", 10)),
+    "1x1": _net(("conv", 32, 3, 1), RELU, ("conv", 64, 1, 1), RELU, ("conv", 64, 3, 1), RELU, GAP, ("linear", 10)),
+    "hidden fully connected layers": _net(("conv", 32, 3, 1), RELU, POOL, ("conv", 64, 3, 1), RELU, POOL, ("linear", 256), RELU,
+                                          ("linear", 72), RELU, ("linear", 10)),
+}
 
 
 @pytest.mark.parametrize("hw,chans,off", [
@@ -20,16 +49,26 @@ pytestmark = pytest.mark.gpu
 ])
 @pytest.mark.parametrize("momentum", [False, True])
 def test_update_with_the_second_stage(hw, chans, off, momentum):
+    _same_as_own_launch(synth.cnn3(num_classes=10, hw=hw, chans=chans), (hw, hw, chans[0]), off, momentum)
+
+
+@pytest.mark.parametrize("net", list(NETS))
+@pytest.mark.parametrize("off", [[0, 1, 150, 203], [0, 2, 4, 6]])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_update_of_other_networks(net, off, momentum):
+    _same_as_own_launch(NETS[net], (16, 16, 3), off, momentum)
+
+
+def _same_as_own_launch(layers, shape, off, momentum):
     import torch
     import paper_2503_17469_amd as omni
-    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
     B, K = off[-1], len(off) - 1
     b = [off[k + 1] - off[k] for k in range(K)]
     params = synth.he_normal_params(layers, 6, True)
-    x, y = synth.make_batch(3, B, (hw, hw, chans[0]), 10, True)
+    x, y = synth.make_batch(3, B, shape, 10, True)
     out = []
     for own_launch in (False, True):
-        run = GpuRun(layers, (hw, hw, chans[0]), "bf16", K, B)
+        run = GpuRun(layers, shape, "bf16", K, B)
         try:
             p = torch.from_numpy(params).cuda()
             xs = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda().to(torch.bfloat16)
@@ -53,18 +92,19 @@ def test_update_with_the_second_stage(hw, chans, off, momentum):
         assert np.array_equal(a, c)
 
 
+@pytest.mark.parametrize("layers,shape", [(synth.cnn3(num_classes=10, hw=32, chans=(3, 32, 64, 128)), (32, 32, 3))]
+                         + [(layers, (16, 16, 3)) for layers in NETS.values()], ids=["cnn3"] + list(NETS))
 @pytest.mark.parametrize("momentum", [False, True])
-def test_update_follows_from_the_gradients(momentum):
+def test_update_follows_from_the_gradients(layers, shape, momentum):
     """One step: parameters and velocity against the weighted sum of the very gradients that the launch left, by the update entry."""
     import torch
     import paper_2503_17469_amd as omni
-    hw, chans, off = 32, (3, 32, 64, 128), [0, 1, 24, 56, 128]
-    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
+    off = [0, 1, 24, 56, 128]
     B, K = off[-1], len(off) - 1
     b = [off[k + 1] - off[k] for k in range(K)]
     params = synth.he_normal_params(layers, 6, True)
-    x, y = synth.make_batch(3, B, (hw, hw, 3), 10, True)
-    run = GpuRun(layers, (hw, hw, 3), "bf16", K, B)
+    x, y = synth.make_batch(3, B, shape, 10, True)
+    run = GpuRun(layers, shape, "bf16", K, B)
     try:
         p = torch.from_numpy(params).cuda()
         xs = torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda().to(torch.bfloat16)
@@ -85,3 +125,12 @@ def test_update_follows_from_the_gradients(momentum):
         assert torch.equal(p, p0) and torch.equal(v, v0)
     finally:
         run.close()
+
+
+@pytest.mark.parametrize("net", ["1x1", "hidden fully connected layers"])
+def test_step_of_other_networks(net):
+    """the gradients themselves, and the update, against the oracle"""
+    layers, off = NETS[net], [0, 20, 61, 150]
+    params = synth.he_normal_params(layers, 6, True)
+    x, y = synth.make_batch(3, off[-1], (16, 16, 3), 10, True)
+    _check_step(layers, (16, 16, 3), params, x, y, off, 0.05, net)
