@@ -75,11 +75,14 @@ __device__ __forceinline__ void head_loss_body(const HeadLossParams& h, const Se
 
 // LDS: the four wavefronts' 16 x 64 (16) tiles and their sums of dz.
 constexpr int kHeadWgradLdsFloats = 4 * (16 * 64 + 16);
-// Input columns per workgroup: 64, or 16 where a wavefront would walk many rows (24 blocks of 16 and more: 64 columns take four
-// matrix instructions per four rows) while there are fewer workgroups than compute units.
+// Input columns per workgroup: 64, or 16 where that leaves at most 24 workgroups, whose walk is then the launch (four matrix
+// instructions per four rows and 64 columns), or where a wavefront walks 24 blocks of 16 rows and more and there are fewer workgroups than
+// compute units.  bf16, 64 / 16 columns: step of 512-128-10 with one worker, 96 rows 20.9 / 19.9 us, 1500 rows 52.3 / 43.8; 512-512-37,
+// 1000 rows 47.1 / 41.7; with more workgroups it is the product or the convolution beside it that waits: 512-512-512-10, six workers, 3000
+// rows (48) 80.9 / 83.5, 3-32-64-64-10, three workers, 600 images (48) 132.2 / 133.5, eight workers, 512 (128) 114.3 / 116.0.
 inline int head_wgrad_columns(int cin, int classes, const Segments& seg) {
   const long groups = (long)seg.K * ((classes + 15) / 16) * ((cin + 63) / 64);
-  return groups < 256 && seg.off[seg.K] / seg.K > 4 * 24 * 16 ? 16 : 64;
+  return groups <= 24 || (groups < 256 && seg.off[seg.K] / seg.K > 4 * 24 * 16) ? 16 : 64;
 }
 inline dim3 head_wgrad_grid(const HeadWgradParams& h, const Segments& seg) {
   return dim3(seg.K * ((h.cin + h.columns - 1) / h.columns) + 1, (h.C + 15) / 16, 1);

@@ -20,7 +20,10 @@ pytestmark = pytest.mark.gpu
     ([24, 2040, 10], [0, 5, 47], "bf16"),                     # sixteen tiles of 128 columns, the last one moved back
     ([16, 1032, 40], [0, 16, 32, 70], "bf16"),                # nine tiles for two
     ([16, 104, 10], [0, 1700], "bf16"),                       # parameter gradients: 16 columns per workgroup, the last half full
-    ([16, 72, 20], [0, 5, 20, 21, 100], "bf16"),              # ... 64, workers of fewer rows than a block, two class tiles
+    ([16, 72, 20], [0, 5, 20, 21, 100], "bf16"),              # ... workers of fewer rows than a block, two class tiles
+    ([16, 72, 20], [0, 5, 20, 21, 40, 50, 66, 100], "bf16"),  # ... 64 columns, the second tile an eighth full
+    ([20, 77, 20], [0, 5, 20, 21, 40, 50, 66, 100], "f32"),   # ... and moved back
+    ([20, 581, 10], [0, 700], "f32"),                         # ... 16, the last moved back, one worker of many rows
 ])
 def test_classifier(dims, off, dtype):
     bf = dtype == "bf16"

@@ -1,0 +1,42 @@
+"""Rules on the host that choose between two forms of a launch, asked without launching anything."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2503_17469_amd import binding
+
+CSRC = os.path.join(os.path.dirname(binding.LIB_PATH), "csrc")
+
+SHIM = r"""
+#include "kernels.h"
+using namespace omni;
+extern "C" int head_columns(int cin, int classes, int rows, int K) {
+  Segments seg{};
+  seg.K = K;
+  for (int k = 0; k <= K; ++k) seg.off[k] = (int)((long)rows * k / K);
+  return head_wgrad_columns_for(cin, classes, seg);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("shim")
+    (d / "shim.cpp").write_text(SHIM)
+    lib_dir = os.path.dirname(binding.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
+                    str(d / "shim.cpp"), "-o", str(d / "shim.so"), "-L" + lib_dir, "-l:libomnistep.so",
+                    "-Wl,-rpath," + lib_dir, "-Wl,--allow-shlib-undefined"], check=True)
+    return ctypes.CDLL(str(d / "shim.so"))
+
+
+@pytest.mark.parametrize("cin,classes,rows,K,columns", [
+    (128, 10, 1500, 1, 16), (104, 14, 1548, 2, 16), (128, 29, 911, 1, 16),     # a handful of workgroups, each a long walk
+    (1024, 10, 384, 1, 16), (1536, 10, 384, 1, 16), (1537, 10, 384, 1, 64),    # 24 workgroups of 64 columns, 25
+    (2048, 10, 1024, 8, 64), (1024, 10, 480, 4, 64),
+    (2048, 10, 1536, 1, 64), (2048, 10, 1537, 1, 16), (512, 100, 40000, 8, 64),
+])
+def test_columns_of_the_classifier_gradient(shim, cin, classes, rows, K, columns):
+    assert shim.head_columns(cin, classes, rows, K) == columns
