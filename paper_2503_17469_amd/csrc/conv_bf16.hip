@@ -714,8 +714,7 @@ struct Conv1Params {
 // 1024 rows 209 -> 203 us; 11 M parameters: the same).  The layer's own weights then come from the parameters,
 // and absent pieces are zeroed in registers: the zero page is cleared by this launch.
 struct Conv1Casts {
-  const float* w;      // this layer's weights [N][9][cin]
-  int cin;
+  const float* w;      // this layer's weights [N][9][3]
   int blocks;          // workgroups that copy
   const float* params;
   bf16_t* shadow;
@@ -724,23 +723,10 @@ struct Conv1Casts {
 };
 struct NoCasts {};
 
-// Eight channels of a tap: `cin` real ones, the rest zero.  (3 channels is what images have; otherwise no load is conditional)
-__device__ __forceinline__ u32x4 weights8(const float* w, int cin, bool in) {
-  float t[8];
-  if (cin == 3) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) t[c] = c < 3 ? w[c] : 0.f;
-  } else {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const float v = w[min(c, cin - 1)];
-      t[c] = c < cin ? v : 0.f;
-    }
-  }
-  u32x4 q;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) q[d] = in ? pack_bf16(t[2 * d], t[2 * d + 1]) : 0u;
-  return q;
+// Eight channels of a tap, of which three are real.  (Cleared by a mask: with a choice the compiler makes the loads conditional.)
+__device__ __forceinline__ u32x4 weights3(const float* w, bool in) {
+  const uint32_t mask = in ? ~0u : 0u;
+  return u32x4{pack_bf16(w[0], w[1]) & mask, pack_bf16(w[2], 0.f) & mask, 0u, 0u};
 }
 
 template <int NBLK, bool CAST>   // 32-channel blocks of output channels: 1 or 2
@@ -773,7 +759,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, s
     for (int ks = 0; ks < 5; ++ks) {
       const int tap = 2 * ks + h, co = 32 * b + j;
       const bool in = tap < 9 && co < p.N;
-      if constexpr (CAST) wf[b][ks] = as_bf16x8(weights8(casts.w + (in ? (co * 9 + tap) * casts.cin : 0), casts.cin, in));
+      if constexpr (CAST) wf[b][ks] = as_bf16x8(weights3(casts.w + (in ? (co * 9 + tap) * 3 : 0), in));
       else wf[b][ks] = as_bf16x8(*reinterpret_cast<const u32x4*>(in ? p.wgt + ((size_t)co * 9 + tap) * 8 : zp));
     }
   float bj[NBLK];
@@ -1041,13 +1027,17 @@ static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16
   return true;
 }
 
-bool conv_first_layer_takes_casts(int Cout, const ConvGeom& g, long M) { return conv1_fwd_shape(Cout, g, M); }
+// (Three channels, as images have: every lane fetches its weights a row apart, and more of them cost more than the copies' launch:
+// 370 images of 32 x 32 x 8 to 64 channels 65.4 us against 23.3 and 4.9, 423 of 32 x 32 x 8 to 32 36.9 against 15.6 and 5.5.)
+bool conv_first_layer_takes_casts(int Cout, int cin_real, const ConvGeom& g, long M) {
+  return cin_real == 3 && conv1_fwd_shape(Cout, g, M);
+}
 
-bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, int cin_real, bf16_t* shadow,
+bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, bf16_t* shadow,
                                 const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
                                 const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code) {
   Conv1Casts c{};
-  c.w = params + w_off; c.cin = cin_real; c.params = params; c.shadow = shadow; c.zero_page = zero_page;
+  c.w = params + w_off; c.params = params; c.shadow = shadow; c.zero_page = zero_page;
   c.blocks = cast_table(c.tab, entries, n);
   bool pooled = false;
   conv1_fwd(st, src, nullptr, out, M, N, g, bias, nullptr, relu, false, pool, pool_code, &pooled, &c);

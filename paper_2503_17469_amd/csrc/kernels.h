@@ -295,8 +295,8 @@ void cast_weights_bf16(hipStream_t st, const float* params, bf16_t* shadow, cons
                        uint32_t* zero_page = nullptr);
 // The first layer's forward pass, if it is one of three channels stored as eight or unpadded (conv_first_layer_takes_casts):
 // one launch that also makes the other layers' copies and clears the zero page.  Its own weights come from `params` at w_off.
-bool conv_first_layer_takes_casts(int Cout, const ConvGeom& g, long M);
-bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, int cin_real, bf16_t* shadow,
+bool conv_first_layer_takes_casts(int Cout, int cin_real, const ConvGeom& g, long M);
+bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, bf16_t* shadow,
                                 const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
                                 const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code);
 void pad_channels_bf16(hipStream_t st, const bf16_t* x, bf16_t* xp, long pixels, int c_real, int c_pad);

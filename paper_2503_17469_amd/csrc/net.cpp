@@ -733,7 +733,7 @@ void step_bf16(StepCtx& c) {
       int weights = 0;
       for (const Layer& L : net->layers) weights += is_param_op(L.d.op) ? 1 : 0;
       ridden = weights - 1 <= omni::kCastMaxEntries &&
-               omni::conv_first_layer_takes_casts(F.d.cout, fwd_geom(F), (long)rows * to.h * to.w);
+               omni::conv_first_layer_takes_casts(F.d.cout, F.d.cin, fwd_geom(F), (long)rows * to.h * to.w);
     }
     for (const Layer& L : net->layers) {
       if (!is_param_op(L.d.op) || (ridden && &L == &F)) continue;
@@ -792,7 +792,7 @@ void step_bf16(StepCtx& c) {
       uint8_t* code = pool_next ? reinterpret_cast<uint8_t*>(c.ws + net->layers[nx].code_off) : nullptr;
       const bool pooled =
           ridden && i == first
-              ? omni::conv_first_layer_and_casts(st, act(L.in0), c.params, L.w_off, L.d.cin, shadow, casts.data(),
+              ? omni::conv_first_layer_and_casts(st, act(L.in0), c.params, L.w_off, shadow, casts.data(),
                                                  (int)casts.size(), conv_counters, actw(L.out), rows * to.h * to.w, L.d.cout,
                                                  g, bias, to.relu, pool, code)
               : omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g, bias,

@@ -18,6 +18,11 @@ extern "C" int head_columns(int cin, int classes, int rows, int K) {
   for (int k = 0; k <= K; ++k) seg.off[k] = (int)((long)rows * k / K);
   return head_wgrad_columns_for(cin, classes, seg);
 }
+extern "C" int takes_casts(int hw, int cin, int cout) {
+  ConvGeom g{};
+  g.rows = 10; g.Hs = g.Ws = g.Hp = g.Wp = hw; g.Cs = (cin + 7) / 8 * 8; g.ks = 3; g.stride = 1; g.pad = 1; g.K = 9 * g.Cs;
+  return conv_first_layer_takes_casts(cout, cin, g, (long)g.rows * hw * hw);
+}
 """
 
 
@@ -40,3 +45,8 @@ def shim(tmp_path_factory):
 ])
 def test_columns_of_the_classifier_gradient(shim, cin, classes, rows, K, columns):
     assert shim.head_columns(cin, classes, rows, K) == columns
+
+
+@pytest.mark.parametrize("hw,cin,cout,yes", [(32, 3, 64, 1), (16, 3, 8, 1), (32, 8, 64, 0), (32, 1, 64, 0), (32, 4, 32, 0), (32, 3, 72, 0)])
+def test_weight_copies_ride_with_layers_of_three_channels(shim, hw, cin, cout, yes):
+    assert shim.takes_casts(hw, cin, cout) == yes
