@@ -1578,11 +1578,29 @@ double conv_wgrad_work(const ConvWgradJob& j) {
 }
 
 namespace {
+// Whether the second stage with the update takes longer than one without and a launch for the update (5 us).  With it a wavefront
+// adds all chunks of a worker, sixteen on their way at a time (with fewer than four workers some wavefronts have none); without, a
+// quarter of them, eight: half a microsecond a trip either way, beside the reading of all partial tiles at 4 TB/s.  Step of one
+// 3-32 layer with pooling, one worker: 128 images 56.1 us with the update, 54.7 without; 256 69.0 / 63.8; 700 97.0 / 85.3; two workers with
+// 20 and 480 91.4 / 79.2; three layers, one worker, 384 images 130.3 / 121.7.  (More workers: eight, one of them with 665 images of
+// 700, 169.9 / 179.2, as all of that worker's workgroups of the other second stage lie on one XCD.)
+bool update_too_long(const BatchTable& tab, int K) {
+  if (K >= kThreads / 64) return false;
+  int most = 0;
+  double tiles = 0;
+  for (int i = 0; i < tab.n; ++i) {
+    const BatchJob& job = tab.job[i];
+    for (int k = 0; k < K; ++k) most = std::max(most, job.chunk[k + 1] - job.chunk[k]);
+    tiles += (double)job.tiles * job.chunk[K] * (job.kind == kFirst ? job.slots * 64 : kTile3Stride) * sizeof(float) / 4e6;
+  }
+  return std::max(0.5 * most / 16, tiles) > std::max(0.5 * most / 32, tiles) + 5;
+}
+
 // The second stage of all layers of a call and the update of all `params` parameters; false, with nothing launched, where some layer
-// has another second stage, or none has any.
+// has another second stage, or the walk in this one is long, or none has any.
 bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, const Segments& seg, const SgdArgs& sgd, float* G,
                   size_t params) {
-  if (bp.red.n == 0 || params > (size_t)INT32_MAX - kThreads) return false;
+  if (bp.red.n == 0 || params > (size_t)INT32_MAX - kThreads || update_too_long(bp.red, seg.K)) return false;
   BatchTable tab = bp.red;
   struct Range { long beg, end; } covered[2 * kBatchJobs];
   int m = 0, blocks = 0;

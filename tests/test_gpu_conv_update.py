@@ -46,6 +46,8 @@ NETS = {
     (32, (4, 40, 96, 64), [0, 33]),                    # 37 columns in the first layer, two channel tiles, one worker
     (16, (3, 16, 96, 256), [0, 3, 4, 100]),            # the first layer in the patch kernel
     (16, (3, 32, 64, 64), list(range(0, 130, 2))),     # 64 workers of two images
+    (32, (3, 32, 64, 128), list(range(16)) + [300]),   # one of sixteen with most chunks (its wavefront the last; in quarters)
+    (32, (3, 32, 64, 128), list(range(17)) + [300]),   # one of seventeen
 ])
 @pytest.mark.parametrize("momentum", [False, True])
 def test_update_with_the_second_stage(hw, chans, off, momentum):
