@@ -9,9 +9,9 @@
 // product is off by up to 2.5 x 2^-24 (0.58 in the root mean square), where the fp32 instruction rounds once (1, 0.43).
 //
 // Measured, 3072-1024-1024-10, 4096 rows, against the fp32 instruction: forward 222 -> 149 and 75 -> 54 us, input gradient 85 -> 63,
-// weight gradients of sixteen workers with the update 346 -> 270 (all of them 2.5 % longer since operands are scaled); 170 TFLOP/s,
-// that is 1.03 PFLOP/s of bf16 products, where a loop of nothing but these matrix instructions reaches 1.40 on the same data (the
-// clock falls under the load).  Error against float64 (2-norm), as a part of the fp32 kernels': forward 0.4 to 0.7 (32 to 8192
+// weight gradients of sixteen workers with the update 346 -> 270 (all of them 2.5 % longer since operands are scaled); 160 to 167
+// TFLOP/s in whole steps, that is 1.0 PFLOP/s of bf16 products, where a loop of nothing but these matrix instructions reaches 1.40 on
+// the same data (the clock falls under the load).  Error against float64 (2-norm), as a part of the fp32 kernels': forward 0.4 to 0.7 (32 to 8192
 // elements), input gradients 0.5 to 0.9, weight gradients 0.35 to 0.75 from 8 rows of a worker on, the same at 4, but 1.2 at 2 and
 // 1.4 at one.
 //
