@@ -169,7 +169,8 @@ typedef struct omni_net omni_net;
  * dtype OMNI_F32: fp32 operands, activations and sums (products whose 128 x 128
  * tiles fill the chip are formed from three bf16 pieces per operand, which carry
  * all 24 bits; their error against exact arithmetic is that of the fp32
- * instruction's products or less).  dtype OMNI_BF16: bf16
+ * instruction's products or less, but for sums in which one product stands out,
+ * which may be off by 2.5 x 2^-24 of it).  dtype OMNI_BF16: bf16
  * operands and stored activations, fp32 accumulation, fp32 master parameters,
  * gradients and loss.  OMNI_EINVAL on a malformed layer list or an unsupported
  * combination. */
@@ -310,7 +311,8 @@ int64_t omni_net_graph_replays(const omni_net* net);
  * Convolutional networks: OMNI_KERNEL_CONV_FWD has the bf16 copies of the weights
  * where the first layer's launch makes them, OMNI_KERNEL_CONV_WGRAD the head's
  * parameter gradients and, where all weight gradients are one group, the update
- * (unless OMNI_KERNEL_UPDATE is what is timed, which takes it apart). */
+ * (unless one to three workers have many rows, or OMNI_KERNEL_UPDATE is what is
+ * timed, which takes it apart). */
 enum {
   OMNI_KERNEL_LINEAR_FWD = 0,
   OMNI_KERNEL_LINEAR_DGRAD = 1,
