@@ -2,7 +2,8 @@
 //
 //   G_k[co][u][v][ci] = sum over worker k's rows and all positions of dY[m][co] * X[n, h*s+u-p, w*s+v-p, ci].
 //
-// Four forms, by shape: kernel B (any), kernel C (3x3 / stride 1 / pad 1), the transposing-read form (3x3 / stride 2,
+// Five forms, by shape: kernel B (any), the ring form (3x3 / stride 1 / pad 1 on maps 4, 8, 16 and 32 wide,
+// conv3_wgrad_ring_device.h), kernel C (the same on wider maps), the transposing-read form (3x3 / stride 2,
 // conv3_wgrad_tr_device.h) and kernel G (3 input channels).  A layer's output is small and its reduction (positions)
 // long, so each worker's positions are cut into chunks, one workgroup per (tile, chunk); a worker with several chunks
 // gets its partial tiles added by a second kernel in chunk order (bit-reproducible, no atomics).
@@ -21,6 +22,7 @@
 
 #include "bf16.h"
 #include "common.h"
+#include "conv3_wgrad_ring_device.h"
 #include "conv3_wgrad_tr_device.h"
 #include "conv_device.h"
 #include "head_device.h"
@@ -293,7 +295,8 @@ __device__ __forceinline__ void wgrad_general_reduce(const WgradParams& p, const
 
 
 // ------------------------------------------------------------------ kernel C
-// Weight gradient of 3x3, stride-1, pad-1 convolutions (most of a residual net).
+// Weight gradient of 3x3, stride-1, pad-1 convolutions on maps that the ring form does not take (64 and 128 wide, or of
+// so few positions that a step of it would hold parts of images).
 // Kernel B treats the nine filter taps as nine independent column blocks: the
 // input is fetched and transposed nine times and dY once per column tile, and at
 // 64 channels that memory traffic, not the matrix pipe, sets the pace.  Here a
@@ -310,24 +313,6 @@ __device__ __forceinline__ void wgrad_general_reduce(const WgradParams& p, const
 // Units never straddle workers; a worker's units are cut into chunks, one
 // workgroup per (tile, chunk), partial tiles are added by a second kernel in
 // chunk order (bit-reproducible, no atomics).
-struct Wgrad3Params {
-  const bf16_t* dy;    // [rows*H*W][Cout]
-  const bf16_t* src;   // [rows][H][W][Cin]
-  float* gw;           // worker w: gw + w*worker_stride, [Cout][9][Cin]
-  float* gb;           // may be null
-  size_t worker_stride;
-  int Cout, Cin, H, W;  // Cin: stored channels (a multiple of 8)
-  int cin_real;        // channels of the gradient tensor (the first layer stores 3 channels padded to 8)
-  int R, nimg;         // a unit is nimg images x R rows; nimg * R * W = 128
-  int Wp, prows;       // patch row length W + 16 (data starts at column 8), patch rows nimg * (R + 2)
-  int SX;              // bytes between channels of X^T
-  int upc;             // units per chunk
-  int nimg_log;
-  uint32_t by_r, by_patch, by_upi;   // 2^16 / R and / (R + 2), rounded up; reciprocal_below(units per image)
-  float* partial;      // [(tile * total_chunks + chunk)][144][256] (+ 64 bias sums)
-  const void* zero;    // page of zeros for absent pieces
-};
-constexpr int kUnit = 128;
 constexpr int kSA = 2 * kUnit + 16;                 // bytes between channels of dY^T
 // Channel rows 8 apart are a multiple of 32 words apart: the eight channel octets that sixteen lanes
 // of one transposing write cover would all land in the same banks (measured: 87 % of the LDS cycles
@@ -340,24 +325,8 @@ constexpr int kSA = 2 * kUnit + 16;                 // bytes between channels of
 // back (2.4e7 in all).
 constexpr int kSkewPad = 128;   // room for the skew of 64 rows (7 x 16 bytes), kept a multiple of 128
 __device__ inline int row_skew(int row) { return (row >> 3) * 16; }
-constexpr int kTile3Floats = 9 * 16 * kThreads;    // one partial tile
-constexpr int kTile3Stride = kTile3Floats + 64;
-
 // four positions x eight channels (c[q] = the 16-byte piece of position q) -> eight
 // channel rows of four positions each
-// the same for a destination that is only 4-byte aligned
-__device__ inline void transpose_store32(const u32x4 c[4], unsigned char* dst, int row_bytes) {
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    uint32_t* lo = reinterpret_cast<uint32_t*>(dst + (2 * d) * row_bytes);
-    uint32_t* hi = reinterpret_cast<uint32_t*>(dst + (2 * d + 1) * row_bytes);
-    lo[0] = (c[0][d] & 0xFFFFu) | (c[1][d] << 16);
-    lo[1] = (c[2][d] & 0xFFFFu) | (c[3][d] << 16);
-    hi[0] = (c[0][d] >> 16) | (c[1][d] & 0xFFFF0000u);
-    hi[1] = (c[2][d] >> 16) | (c[3][d] & 0xFFFF0000u);
-  }
-}
-
 __device__ inline void transpose_store(const u32x4 c[4], unsigned char* dst, int row_bytes) {
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
@@ -369,20 +338,6 @@ __device__ inline void transpose_store(const u32x4 c[4], unsigned char* dst, int
     *reinterpret_cast<u32x2*>(dst + (2 * d) * row_bytes) = lo;
     *reinterpret_cast<u32x2*>(dst + (2 * d + 1) * row_bytes) = hi;
   }
-}
-
-// WM = 4: maps four columns wide (a patch row is 8 elements = one 16-byte read, data in columns 2-5;
-// a group of 8 reduction positions is two image rows).
-// WM = 8, 16, 32: the map width is known.  The two halves of a wavefront read neighbouring windows
-// of 8 columns, so the one element to the left and to the right of a window is either the zero halo
-// or sits in a register of the partner lane in the other half: it comes over with a swap of the
-// wavefront's halves instead of two more LDS reads per tap row (4-byte reads 16-byte-aligned rows
-// apart use a quarter of the banks: measured, they were all of this kernel's read conflicts and
-// more LDS time than the fragments themselves).  WM = 0: any other width, with those reads.
-__device__ inline uint32_t from_partner(uint32_t send, bool upper) {
-  // lanes 32-63 receive what lanes 0-31 sent, and the other way round
-  const u32x2 sw = __builtin_amdgcn_permlane32_swap(send, send, false, false);
-  return upper ? sw[0] : sw[1];
 }
 
 // The three taps of one filter row: q holds the window's 8 columns (two per word), pl the word
@@ -398,23 +353,16 @@ __device__ inline void wgrad3_taps(v16f (&acc)[9], int du, const bf16x8 fa, cons
   acc[du * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(right), acc[du * 3 + 2], 0, 0, 0);
 }
 
-// WM: the map's width, 0: any other.  KS (at most 32 input channels): the two wavefronts of 32 output channels take the same 32 input
-// channels and half of a unit's positions each, and are added at the end.
-template <int WM, bool KS>
 __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& ck, int tile, unsigned char* smem3) {
-  constexpr bool W4 = WM == 4;
-  constexpr int XR = KS ? 32 : 64;           // channel rows of the patch
-  constexpr int XO = XR / 8, NX = KS ? 1 : 2;   // channel octets, staging tasks per thread
-  constexpr int KSTEPS = kUnit / 16 / (KS ? 2 : 1);   // reduction steps per wavefront and unit
+  constexpr int KSTEPS = kUnit / 16;   // reduction steps per unit
   unsigned char* sA = smem3;                 // dY^T: 64 rows of kSA bytes
-  unsigned char* sX = smem3 + 64 * kSA + kSkewPad;   // X^T: XR rows of p.SX bytes (both arrays: + the skew)
+  unsigned char* sX = smem3 + 64 * kSA + kSkewPad;   // X^T: 64 rows of p.SX bytes (both arrays: + the skew)
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 31, h = lane >> 5;
-  const int tiles_ci = KS ? 1 : (p.Cin + 63) / 64;
-  const int tile_co = KS ? tile : tile / tiles_ci;
-  const int co0 = tile_co * 64, ci0 = KS ? 0 : (tile - tile_co * tiles_ci) * 64;
-  const int wco = (wave >> 1) * 32, wci = KS ? 0 : (wave & 1) * 32, kfirst = KS ? (wave & 1) * KSTEPS : 0;
-  const int H = p.H, W = WM ? WM : p.W, R = p.R;
+  const int tiles_ci = (p.Cin + 63) / 64, tile_co = tile / tiles_ci;
+  const int co0 = tile_co * 64, ci0 = (tile - tile_co * tiles_ci) * 64;
+  const int wco = (wave >> 1) * 32, wci = (wave & 1) * 32;
+  const int H = p.H, W = p.W, R = p.R;
   const int wk = ck.wk, chunk_idx = ck.idx, nchunks = ck.n;
   const int bk = ck.end - ck.beg;
   const int upi = p.nimg == 1 ? H / R : 1;   // units per image when a unit is part of one image
@@ -435,24 +383,24 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
   unsigned char* a_dst = sA + (8 * a_oct) * kSA + row_skew(8 * a_oct) + 8 * (tid >> 3);
   // X: channel octets x (W/4 groups of 4 columns) x patch rows
   const int wq = W >> 2;
-  const int ntasks = p.prows * wq * XO;
-  int x_rel[NX], x_il[NX], x_rr[NX], x_dst[NX];
-  bool x_task[NX];
+  const int ntasks = p.prows * wq * 8;
+  int x_rel[2], x_il[2], x_rr[2], x_dst[2];
+  bool x_task[2];
 #pragma unroll
-  for (int t = 0; t < NX; ++t) {
+  for (int t = 0; t < 2; ++t) {
     const int x = tid + t * kThreads;
     x_task[t] = x < ntasks;
     const int xx = x_task[t] ? x : 0;
-    const int oct = xx % XO, g = xx / XO;
+    const int oct = xx & 7, g = xx >> 3;
     const int pr = g / wq, wg = g - pr * wq;
     x_il[t] = (int)(((uint32_t)pr * p.by_patch) >> 16);
     x_rr[t] = pr - x_il[t] * (R + 2);                       // input row = first row + x_rr - 1
     x_rel[t] = ((x_il[t] * H + x_rr[t] - 1) * W + 4 * wg) * p.Cin + 8 * oct;
-    x_dst[t] = (8 * oct) * p.SX + row_skew(8 * oct) + (pr * p.Wp + 4 * wg + (W4 ? 2 : 8)) * 2;
+    x_dst[t] = (8 * oct) * p.SX + row_skew(8 * oct) + (pr * p.Wp + 4 * wg + 8) * 2;
     x_task[t] = x_task[t] && ci0 + 8 * oct < p.Cin;   // false: no such piece, or a channel octet past the end
   }
 
-  u32x4 ra[4], rx[NX][4];
+  u32x4 ra[4], rx[2][4];
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
   // first image and row of unit u; units are loaded one after the other
   int img_at, row_at;
@@ -474,7 +422,7 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
       for (int q = 0; q < 4; ++q) ra[q] = *reinterpret_cast<const u32x4*>(src + q * st);
     }
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
+    for (int t = 0; t < 2; ++t) {
       const int row = r0 + x_rr[t] - 1;
       const bool in = x_task[t] && x_il[t] < nvalid && row >= 0 && row < H;
       const bf16_t* src = in ? p.src + (base_pos * p.Cin + x_rel[t] + ci0) : zp;
@@ -493,28 +441,25 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
   auto store_unit = [&]() {
     if (a_chan_ok) transpose_store(ra, a_dst, kSA);
 #pragma unroll
-    for (int t = 0; t < NX; ++t) {
-      if (!x_task[t]) continue;   // no such patch piece, or channels that stay zero
-      if (W4) transpose_store32(rx[t], sX + x_dst[t], p.SX);
-      else transpose_store(rx[t], sX + x_dst[t], p.SX);
-    }
+    for (int t = 0; t < 2; ++t)
+      if (x_task[t]) transpose_store(rx[t], sX + x_dst[t], p.SX);   // (else no such patch piece, or channels that stay zero)
   };
   load_unit();   // (every chunk has a unit)
 
   // The halo columns of the patch are never written again: they stay zero.  So do the rows of
   // channels past the end of the tensor (their staging tasks are skipped altogether).
-  for (int i = tid * 16; i < 64 * kSA + XR * p.SX + 2 * kSkewPad; i += kThreads * 16)
+  for (int i = tid * 16; i < 64 * kSA + 64 * p.SX + 2 * kSkewPad; i += kThreads * 16)
     *reinterpret_cast<u32x4*>(smem3 + i) = u32x4{0u, 0u, 0u, 0u};
 
   // ---- fragment addresses: k-step ks covers positions 16 ks .. 16 ks + 15, this lane the 8 at 16 ks + 8 h
   int offB[KSTEPS];
 #pragma unroll
   for (int i = 0; i < KSTEPS; ++i) {
-    const int pos = (2 * (kfirst + i) + h) * 8, rr = pos / W, w0 = pos - rr * W;
+    const int pos = (2 * i + h) * 8, rr = pos / W, w0 = pos - rr * W;
     const int il = over_r(rr);
-    offB[i] = ((il * (R + 2) + (rr - il * R)) * p.Wp + (W4 ? 0 : w0 + 8)) * 2;
+    offB[i] = ((il * (R + 2) + (rr - il * R)) * p.Wp + w0 + 8) * 2;
   }
-  const unsigned char* a_frag = sA + (wco + j) * kSA + row_skew(wco + j) + h * 16 + kfirst * 32;
+  const unsigned char* a_frag = sA + (wco + j) * kSA + row_skew(wco + j) + h * 16;
   const unsigned char* x_frag = sX + (wci + j) * p.SX + row_skew(wci + j);
   const int row_shift = p.Wp * 2;
 
@@ -536,66 +481,11 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
       const bf16x8 fa = as_bf16x8(*reinterpret_cast<const u32x4*>(a_frag + ks * 32));
-      if constexpr (W4) {
-        // patch rows r .. r+3 of this lane's image (16 bytes each) serve all nine taps
-        u32x4 row[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) row[i] = *reinterpret_cast<const u32x4*>(x_frag + offB[ks] + i * row_shift);
-        uint32_t lf[4][2], rt[4][2];   // columns 1-4 and 3-6 of every row
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t m21 = __builtin_amdgcn_alignbit(row[i][2], row[i][1], 16);
-          lf[i][0] = __builtin_amdgcn_alignbit(row[i][1], row[i][0], 16); lf[i][1] = m21;
-          rt[i][0] = m21; rt[i][1] = __builtin_amdgcn_alignbit(row[i][3], row[i][2], 16);
-        }
-#pragma unroll
-        for (int du = 0; du < 3; ++du) {
-          const u32x4 left = {lf[du][0], lf[du][1], lf[du + 1][0], lf[du + 1][1]};
-          const u32x4 mid = {row[du][1], row[du][2], row[du + 1][1], row[du + 1][2]};
-          const u32x4 right = {rt[du][0], rt[du][1], rt[du + 1][0], rt[du + 1][1]};
-          acc[du * 3 + 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(left), acc[du * 3 + 0], 0, 0, 0);
-          acc[du * 3 + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(mid), acc[du * 3 + 1], 0, 0, 0);
-          acc[du * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, as_bf16x8(right), acc[du * 3 + 2], 0, 0, 0);
-        }
-        // (keeps the next steps' patch rows from being read ahead of their turn: with them all in flight the
-        // 256 registers overflowed into scratch memory)
-        __builtin_amdgcn_sched_barrier(0);
-      } else if constexpr (WM == 32) {
-        // a map row is two reduction steps: windows A | B (this step) and C | D (the next), A and C
-        // in the lower half of the wavefront, B and D in the upper
-        if (ks & 1) continue;   // done together with the step before
-        const bf16x8 fa2 = as_bf16x8(*reinterpret_cast<const u32x4*>(a_frag + (ks + 1) * 32));
-        const bool up = h != 0;
-#pragma unroll
-        for (int du = 0; du < 3; ++du) {
-          const u32x4 q = *reinterpret_cast<const u32x4*>(x_frag + offB[ks] + du * row_shift);
-          const u32x4 q2 = *reinterpret_cast<const u32x4*>(x_frag + offB[ks + 1] + du * row_shift);
-          const uint32_t r1 = from_partner(up ? q[0] : q[3], up);    // A gets B's first, B gets A's last
-          const uint32_t r2 = from_partner(up ? q[3] : q2[0], up);   // C gets B's last, B gets C's first
-          const uint32_t r3 = from_partner(up ? q2[0] : q2[3], up);  // C gets D's first, D gets C's last
-          const uint32_t pl = up ? r1 : 0u, pn = up ? r2 : r1;
-          const uint32_t pl2 = up ? r3 : r2, pn2 = up ? 0u : r3;
-          wgrad3_taps(acc, du, fa, q, pl, pn);
-          wgrad3_taps(acc, du, fa2, q2, pl2, pn2);
-        }
-      } else {
 #pragma unroll
       for (int du = 0; du < 3; ++du) {
         const unsigned char* xb = x_frag + offB[ks] + du * row_shift;
-        const u32x4 q = *reinterpret_cast<const u32x4*>(xb);
-        uint32_t pl, pn;
-        if constexpr (WM == 8) {
-          pl = 0u; pn = 0u;                      // a window is a whole map row: halo on both sides
-        } else if constexpr (WM == 16) {
-          const bool up = h != 0;                // a map row is the two windows of this step
-          const uint32_t r = from_partner(up ? q[0] : q[3], up);
-          pl = up ? r : 0u; pn = up ? 0u : r;
-        } else {
-          pl = *reinterpret_cast<const uint32_t*>(xb - 4);
-          pn = *reinterpret_cast<const uint32_t*>(xb + 16);
-        }
-        wgrad3_taps(acc, du, fa, q, pl, pn);
-      }
+        wgrad3_taps(acc, du, fa, *reinterpret_cast<const u32x4*>(xb), *reinterpret_cast<const uint32_t*>(xb - 4),
+                    *reinterpret_cast<const uint32_t*>(xb + 16));
       }
     }
     if (want_bias) {
@@ -615,38 +505,11 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
     __syncthreads();
     if (tid < 64) bsum = ((quarter[tid] + quarter[64 + tid]) + quarter[128 + tid]) + quarter[192 + tid];
   }
-  if constexpr (KS) {
-    // the halves of the positions meet, three taps at a time
-    float* half = reinterpret_cast<float*>(smem3) + (wave >> 1) * (48 * 64) + lane;
-#pragma unroll
-    for (int du = 0; du < 3; ++du) {
-      __syncthreads();
-      if (wave & 1) {
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) half[(t * 16 + v) * 64] = acc[du * 3 + t][v];
-      }
-      __syncthreads();
-      if (!(wave & 1)) {
-#pragma unroll
-        for (int t = 0; t < 3; ++t)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[du * 3 + t][v] += half[(t * 16 + v) * 64];
-      }
-    }
-  }
-
   const int ci = ci0 + wci + j;
-  const bool holds = ci < p.cin_real && (!KS || !(wave & 1));
+  const bool holds = ci < p.cin_real;
   if (nchunks > 1) {
     float* mine = p.partial + ((size_t)tile * ck.total + ck.row) * kTile3Stride;
-    if (holds) {             // the second stage reads the same lanes only
-#pragma unroll
-      for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mine[(t * 16 + v) * kThreads + tid] = acc[t][v];
-    }
+    if (holds) park3(mine, acc, wave, lane);             // (the second stage reads the same lanes only)
     if (tid < 64) mine[kTile3Floats + tid] = bsum;
     return;
   }
@@ -666,29 +529,23 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
 // ---- the order in which a worker's chunks are added, in the second stage and in the one with the update alike (their results are
 // the same bits): four quarters of the chunks, each in chunk order, one after the other; the bias gradients in one chain.
 __device__ inline int quarter_chunks(int n) { return (n + 3) >> 2; }
-__device__ inline float add_quarters(float a, float b, float c, float d) { return ((a + b) + c) + d; }
-// E sums of n values each, `stride` apart (neighbouring sums' `next` apart), eight loads of each in flight.
-template <int E>
-__device__ inline void add_chain(const float* src, int n, size_t stride, int next, float (&s)[E]) {
+template <typename V>
+__device__ inline V add_quarters(V a, V b, V c, V d) { return ((a + b) + c) + d; }
+// The sum of n values `stride` floats apart, eight loads in flight.
+template <typename V = float>
+__device__ inline V chain_of(const float* src, int n, size_t stride) {
+  V s = {};
   for (int c = 0; c < n; c += 8) {
-    float t[8][E];
+    V t[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 8; ++u) t[u] = *reinterpret_cast<const V*>(src + (size_t)min(c + u, n - 1) * stride);
 #pragma unroll
-      for (int e = 0; e < E; ++e) t[u][e] = src[(size_t)min(c + u, n - 1) * stride + e * next];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) s[e] = c + u < n ? s[e] + t[u][e] : s[e];
+    for (int u = 0; u < 8; ++u) s = c + u < n ? s + t[u] : s;
   }
-}
-__device__ inline float chain_of(const float* src, int n, size_t stride) {
-  float s[1] = {0.f};
-  add_chain<1>(src, n, stride, 0, s);
-  return s[0];
+  return s;
 }
 
-// Kernel C's element of a tile: register v of one tap and quadrant, as lane `lane` held it.
+// Kernel C's and the ring form's element of a tile: register v of one tap and quadrant, as lane `lane` held it.
 struct Place3 {
   int co0, ci0, wci, co, ci;
   size_t at;      // in the weight
@@ -703,29 +560,27 @@ __device__ __forceinline__ Place3 wgrad3_place(const Wgrad3Params& p, int tile, 
 
 // Second stage: one workgroup per (tile, worker, 9 taps x 4 register quarters x 4 tile quadrants); it
 // owns the (output channel, input channel) pairs one wavefront of the first stage held; each of its
-// four wavefronts adds a quarter of the worker's chunks (32 loads in flight), the quarters meet in LDS: four times the loads in
-// flight of one wavefront walking all chunks.
+// four wavefronts adds a quarter of the worker's chunks (eight 16-byte loads in flight), the quarters meet in LDS.
 __device__ __forceinline__ void wgrad3_reduce(const Wgrad3Params& p, const Chunk& ck, int tile, int z, float* lds) {
-  float (*part)[4][64] = reinterpret_cast<float (*)[4][64]>(lds);   // [4]
+  v4f (*part)[64] = reinterpret_cast<v4f (*)[64]>(lds);   // [4]
   const int wk = ck.wk, nchunks = ck.n;
   const int quad = z & 3, vq = (z >> 2) & 3, tap = z >> 4;
   const int tid = threadIdx.x, lane = tid & 63, sub = tid >> 6;
   const float* all = p.partial + ((size_t)tile * ck.total + ck.row) * kTile3Stride;
-  const float* mine = all + (size_t)(tap * 16 + vq * 4) * kThreads + quad * 64 + lane;
   const int per = quarter_chunks(nchunks);
   const int c0 = min(sub * per, nchunks), c1 = min(c0 + per, nchunks);
   const Place3 first = wgrad3_place(p, tile, quad, tap, 4 * vq, lane);
-  float s[4] = {0.f, 0.f, 0.f, 0.f};
-  if (first.ci < p.cin_real) add_chain<4>(mine + (size_t)c0 * kTile3Stride, c1 - c0, kTile3Stride, kThreads, s);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) part[sub][e][lane] = s[e];
+  v4f s = {0.f, 0.f, 0.f, 0.f};
+  if (first.ci < p.cin_real)
+    s = chain_of<v4f>(all + (size_t)c0 * kTile3Stride + partial3_at(tap, vq, quad, lane), c1 - c0, kTile3Stride);
+  part[sub][lane] = s;
   __syncthreads();
   if (sub == 0) {
+    const v4f tot = add_quarters(part[0][lane], part[1][lane], part[2][lane], part[3][lane]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const Place3 pl = wgrad3_place(p, tile, quad, tap, 4 * vq + e, lane);
-      const float tot = add_quarters(part[0][e][lane], part[1][e][lane], part[2][e][lane], part[3][e][lane]);
-      if (pl.in) p.gw[(size_t)wk * p.worker_stride + pl.at] = tot;
+      if (pl.in) p.gw[(size_t)wk * p.worker_stride + pl.at] = tot[e];
     }
   }
   const int co = first.co0 + tid;
@@ -1063,14 +918,22 @@ struct BatchTable {
   BatchJob job[kBatchJobs];
 };
 
-// (A line of arguments that nothing has touched takes 640 cycles: the lanes fetch chunks and rows of all workers at once.)
-__device__ inline Chunk chunk_at(const BatchJob& job, const Segments& seg, int row) {
-  const int lane = threadIdx.x & 63, K = seg.K, total = job.chunk[K], rows = seg.off[K];
-  const int mine = min(lane, K), chunk = job.chunk[mine], off = seg.off[mine];
-  const int wk = __popcll(__ballot(lane < K && chunk <= row)) - 1;
-  const int first = __builtin_amdgcn_readlane(chunk, wk), after = wk + 1 < K ? __builtin_amdgcn_readlane(chunk, wk + 1) : total;
-  return Chunk{wk, row - first, after - first, row, total, __builtin_amdgcn_readlane(off, wk),
-               wk + 1 < K ? __builtin_amdgcn_readlane(off, wk + 1) : rows};
+// (A line of arguments that nothing has touched takes 640 cycles: the lanes fetch chunks and rows of all workers at once, before
+// anything that depends on them.)
+struct ChunkTable {
+  int chunk, off, chunk64, off64;
+};
+__device__ inline ChunkTable chunk_table(const BatchJob& job, const Segments& seg) {
+  static_assert(OMNI_MAX_WORKERS == 64, "one lane per worker");
+  const int lane = threadIdx.x & 63;
+  return ChunkTable{job.chunk[lane], seg.off[lane], job.chunk[64], seg.off[64]};
+}
+__device__ inline Chunk chunk_at(const ChunkTable& t, int K, int row) {
+  const int wk = __popcll(__ballot((int)(threadIdx.x & 63) < K && t.chunk <= row)) - 1;
+  auto chunk = [&](int k) { return k < 64 ? __builtin_amdgcn_readlane(t.chunk, k & 63) : t.chunk64; };
+  auto off = [&](int k) { return k < 64 ? __builtin_amdgcn_readlane(t.off, k & 63) : t.off64; };
+  const int first = chunk(wk);
+  return Chunk{wk, row - first, chunk(wk + 1) - first, row, chunk(K), off(wk), off(wk + 1)};
 }
 __device__ inline int job_at(const BatchTable& tab, int block) {
   int e = 0;
@@ -1083,25 +946,50 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_batch_kernel(BatchTable tab
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int e = job_at(tab, (int)blockIdx.x);
   const BatchJob& job = tab.job[e];
+  const ChunkTable table = chunk_table(job, seg);
   const int local = (int)blockIdx.x - tab.first[e], row = quotient(local, job.by_tiles, job.tiles);
   const int tile = local - row * job.tiles;
-  const Chunk ck = chunk_at(job, seg, row);
+  const Chunk ck = chunk_at(table, seg.K, row);
   const Wgrad3Params patch = job.patch;   // (read together; and with a read per use the compiler copies the whole table into scratch)
   switch (job.kind) {
     case kGeneral11: wgrad_general_body<1, 1>(job.general, seg, ck, tile, smem); break;
     case kGeneral12: wgrad_general_body<1, 2>(job.general, seg, ck, tile, smem); break;
     case kGeneral21: wgrad_general_body<2, 1>(job.general, seg, ck, tile, smem); break;
     case kGeneral22: wgrad_general_body<2, 2>(job.general, seg, ck, tile, smem); break;
-    case kPatch4: wgrad3_body<4, false>(patch, ck, tile, smem); break;
-    case kPatch8: wgrad3_body<8, false>(patch, ck, tile, smem); break;
-    case kPatch16: wgrad3_body<16, false>(patch, ck, tile, smem); break;
-    case kPatch32: wgrad3_body<32, false>(patch, ck, tile, smem); break;
-    case kPatchAny: wgrad3_body<0, false>(patch, ck, tile, smem); break;
-    case kPatch8Narrow: wgrad3_body<8, true>(patch, ck, tile, smem); break;
-    case kPatch16Narrow: wgrad3_body<16, true>(patch, ck, tile, smem); break;
-    case kPatch32Narrow: wgrad3_body<32, true>(patch, ck, tile, smem); break;
+    case kPatch4: wgrad3_ring_body<4, false, 4>(patch, ck, tile, smem); break;
+    case kPatch8: wgrad3_ring_body<8, false, 4>(patch, ck, tile, smem); break;
+    case kPatch16: wgrad3_ring_body<16, false, 4>(patch, ck, tile, smem); break;
+    case kPatch32: wgrad3_ring_body<32, false, 4>(patch, ck, tile, smem); break;
+    case kPatchAny: wgrad3_body(patch, ck, tile, smem); break;
+    case kPatch8Narrow: wgrad3_ring_body<8, true, 4>(patch, ck, tile, smem); break;
+    case kPatch16Narrow: wgrad3_ring_body<16, true, 4>(patch, ck, tile, smem); break;
+    case kPatch32Narrow: wgrad3_ring_body<32, true, 4>(patch, ck, tile, smem); break;
     case kStride2: wgrad_tr_body<2>(job.stride2, seg, ck, tile, smem); break;
     default: break;   // (kFirst has launches of its own)
+  }
+}
+
+// The same for layers of the ring form alone, with eight wavefronts to a workgroup.  Two share a block of the output and are added in
+// LDS: a compute unit is as full as with two workgroups of four, for half the partial tiles in memory.  For launches with nothing
+// beside them: these workgroups leave no registers to another kernel's.
+__global__ __launch_bounds__(2 * kThreads, 2) void wgrad_ring_kernel(BatchTable tab, Segments seg) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int e = job_at(tab, (int)blockIdx.x);
+  const BatchJob& job = tab.job[e];
+  const ChunkTable table = chunk_table(job, seg);
+  const Wgrad3Params patch = job.patch;   // (all of the arguments on their way together)
+  const int local = (int)blockIdx.x - tab.first[e], row = exact_quotient(local, job.by_tiles);
+  const int tile = local - row * job.tiles;
+  const Chunk ck = chunk_at(table, seg.K, row);
+  switch (job.kind) {
+    case kPatch4: wgrad3_ring_body<4, false, 8>(patch, ck, tile, smem); break;
+    case kPatch8: wgrad3_ring_body<8, false, 8>(patch, ck, tile, smem); break;
+    case kPatch16: wgrad3_ring_body<16, false, 8>(patch, ck, tile, smem); break;
+    case kPatch32: wgrad3_ring_body<32, false, 8>(patch, ck, tile, smem); break;
+    case kPatch8Narrow: wgrad3_ring_body<8, true, 8>(patch, ck, tile, smem); break;
+    case kPatch16Narrow: wgrad3_ring_body<16, true, 8>(patch, ck, tile, smem); break;
+    case kPatch32Narrow: wgrad3_ring_body<32, true, 8>(patch, ck, tile, smem); break;
+    default: break;
   }
 }
 
@@ -1117,7 +1005,7 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_light_kernel(BatchJob job, 
     head_wgrad_loss_body<bf16_t, 2>(head, seg, b, head_x, reinterpret_cast<float*>(smem));
     return;
   }
-  wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(job, seg, b - head_blocks), smem);
+  wgrad1_body<MB, NB, POOLED>(job.first, seg, chunk_at(chunk_table(job, seg), seg.K, b - head_blocks), smem);
 }
 
 // Second stage of the layers in which some worker has more than one chunk.
@@ -1143,7 +1031,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(BatchTable tab, 
 
 // ---- the second stage with the update: all workers' gradients of an element meet in one workgroup, which applies their weighted
 // sum (chunks and workers in the order of the two launches it stands for: the same bits).  For steps whose weight gradients are
-// one call; kernel C's layers and the first layer's, the parameters of all others follow from G.
+// one call; kernel C's and the ring form's layers and the first layer's, the parameters of all others follow from G.
 struct UpdateTo {
   float* theta;
   float* vel;
@@ -1164,83 +1052,92 @@ __device__ inline void update_one(const UpdateTo& to, size_t at, float th, float
 }
 
 // The second stage's sum of n values `stride` apart, by one wavefront: the four quarters side by side.
-__device__ inline float sum_quarters(const float* src, int n, size_t stride) {
+template <typename V = float>
+__device__ inline V sum_quarters(const float* src, int n, size_t stride) {
+  constexpr int U = 4;                             // sixteen loads in flight
   const int per = quarter_chunks(n);
-  float a[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int i = 0; i < per; i += 4) {               // sixteen loads in flight
-    float t[4][4];
+  V a[4] = {};
+  for (int i = 0; i < per; i += U) {
+    V t[U][4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) t[u][q] = src[(size_t)min(q * per + i + u, n - 1) * stride];
+      for (int q = 0; q < 4; ++q) t[u][q] = *reinterpret_cast<const V*>(src + (size_t)min(q * per + i + u, n - 1) * stride);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int q = 0; q < 4; ++q) a[q] = i + u < per && q * per + i + u < n ? a[q] + t[u][q] : a[q];
   }
   return add_quarters(a[0], a[1], a[2], a[3]);
 }
 
-// Kernel C: a workgroup has one register of one tap and tile quadrant (the pairs one wavefront of the first stage held), its
-// wavefronts take the workers in turn.  lds: 64 floats per worker.
-constexpr int kUpdateSlots3 = 9 * 16 * 4;
-template <bool MOM>
+// Kernel C and the ring form: a workgroup has four registers of one tap and tile quadrant (the pairs one wavefront of the first stage held) or, in the
+// last slot, a tile's biases; its NW wavefronts take a worker each, or take turns.  lds: 256 floats per worker.
+constexpr int kUpdateSlots3 = 9 * 4 * 4 + 1;
+template <bool MOM, int NW>
 __device__ __forceinline__ void wgrad3_update(const Wgrad3Params& p, const BatchJob& job, int tile, int z, const Segments& seg,
                                               const Lambdas& lam, const Optim& opt, const UpdateTo& to, float* lds) {
-  const int quad = z & 3, v = (z >> 2) & 15, tap = z >> 6;
+  const bool bias = z == kUpdateSlots3 - 1;
+  const int quad = bias ? 0 : z & 3, vq = bias ? 0 : (z >> 2) & 3, tap = bias ? 0 : z >> 4;
   const int tid = threadIdx.x, lane = tid & 63, sub = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = seg.K;
-  const Place3 pl = wgrad3_place(p, tile, quad, tap, v, lane);
-  const int co0 = pl.co0;
-  const bool with_bias = z == 0 && p.gb != nullptr && pl.ci0 == 0, in = pl.in;
-  if (pl.ci0 + pl.wci >= p.cin_real) return;       // (nothing there; quadrant 0, which has the bias, never)
-  const size_t at = in ? pl.at : 0, mine = (size_t)(p.gw - to.G) + at;
-  const float th = to.theta[mine], ve = MOM ? to.vel[mine] : 0.f;
+  const Place3 first = wgrad3_place(p, tile, quad, tap, 4 * vq, lane);
   const float* const tiles = p.partial + (size_t)tile * job.chunk[K] * kTile3Stride;
-  for (int wk = sub; wk < K; wk += kThreads / 64) {
-    const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
-    float* const gw = p.gw + (size_t)wk * p.worker_stride;
-    float s = 0.f;
-    if (n > 1) {
-      s = sum_quarters(tiles + (size_t)c0 * kTile3Stride + (size_t)(tap * 16 + v) * kThreads + quad * 64 + lane, n, kTile3Stride);
-      if (in) gw[at] = s;
-    } else if (in) {
-      s = gw[at];                                  // (written by the first stage)
+  if (bias) {
+    if (p.gb == nullptr || first.ci0 != 0) return;
+    const int co = min(first.co0 + lane, p.Cout - 1);
+    const bool in = first.co0 + lane < p.Cout;
+    const size_t mine = (size_t)(p.gb - to.G) + co;
+    const float th = to.theta[mine], ve = MOM ? to.vel[mine] : 0.f;
+    for (int wk = sub; wk < K; wk += NW) {
+      const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
+      float* const gb = p.gb + (size_t)wk * p.worker_stride + co;
+      float s;
+      if (n > 1) {
+        s = chain_of(tiles + (size_t)c0 * kTile3Stride + kTile3Floats + co - first.co0, n, kTile3Stride);
+        if (in) *gb = s;
+      } else {
+        s = *gb;
+      }
+      lds[wk * 64 + lane] = s;
     }
-    lds[wk * 64 + lane] = s;
-  }
-  __syncthreads();
-  if (sub == 0 && in) {
+    __syncthreads();
+    if (sub != 0 || !in) return;
     float g = 0.f;
     for (int k = 0; k < K; ++k) g += lam.v[k] * lds[k * 64 + lane];
     update_one<MOM>(to, mine, th, ve, g, opt);
+    return;
   }
-  if (!with_bias) return;
-  __syncthreads();
-  const int co = min(co0 + lane, p.Cout - 1);
-  for (int wk = sub; wk < K; wk += kThreads / 64) {
+  if (first.ci0 + first.wci >= p.cin_real) return; // (nothing there)
+  // wavefront sub < 4 applies the update of register 4 vq + sub
+  const Place3 own = wgrad3_place(p, tile, quad, tap, 4 * vq + (sub & 3), lane);
+  const size_t mine = (size_t)(p.gw - to.G) + (own.in ? own.at : 0);
+  const float th = to.theta[mine], ve = MOM ? to.vel[mine] : 0.f;
+  v4f* const sums = reinterpret_cast<v4f*>(lds);   // [worker][lane]
+  for (int wk = sub; wk < K; wk += NW) {
     const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
-    float* const gb = p.gb + (size_t)wk * p.worker_stride + co;
-    float s;
-    if (n > 1) {
-      s = chain_of(tiles + (size_t)c0 * kTile3Stride + kTile3Floats + co - co0, n, kTile3Stride);
-      if (co0 + lane < p.Cout) *gb = s;
-    } else {
-      s = *gb;
+    float* const gw = p.gw + (size_t)wk * p.worker_stride;
+    v4f s = {0.f, 0.f, 0.f, 0.f};
+    if (n > 1) s = sum_quarters<v4f>(tiles + (size_t)c0 * kTile3Stride + partial3_at(tap, vq, quad, lane), n, kTile3Stride);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const Place3 pl = wgrad3_place(p, tile, quad, tap, 4 * vq + e, lane);
+      if (!pl.in) continue;
+      if (n > 1) gw[pl.at] = s[e];
+      else s[e] = gw[pl.at];                       // (written by the first stage)
     }
-    lds[wk * 64 + lane] = s;
+    sums[wk * 64 + lane] = s;
   }
   __syncthreads();
-  if (sub == 0 && co0 + lane < p.Cout) {
+  if (sub < 4 && own.in) {
     float g = 0.f;
-    for (int k = 0; k < K; ++k) g += lam.v[k] * lds[k * 64 + lane];
-    const size_t bat = (size_t)(p.gb - to.G) + co;
-    update_one<MOM>(to, bat, to.theta[bat], MOM ? to.vel[bat] : 0.f, g, opt);
+    for (int k = 0; k < K; ++k) g += lam.v[k] * lds[(k * 64 + lane) * 4 + sub];
+    update_one<MOM>(to, mine, th, ve, g, opt);
   }
 }
 
 // Kernel G: 64 accumulator elements per workgroup.
-template <bool MOM>
+template <bool MOM, int NW>
 __device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const BatchJob& job, int z, const Segments& seg, const Lambdas& lam,
                                               const Optim& opt, const UpdateTo& to, float* lds) {
   const int NB = wgrad1_col_blocks(p.cin_real), MB = p.Cout > 32 ? 2 : 1, kImg = MB * NB * 16 * 64, K = seg.K;
@@ -1251,7 +1148,7 @@ __device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const Batch
   float* const g0 = in ? place : p.gw;             // worker 0's
   const size_t at = (size_t)(g0 - to.G);
   const float th = to.theta[at], ve = MOM ? to.vel[at] : 0.f;
-  for (int wk = sub; wk < K; wk += kThreads / 64) {
+  for (int wk = sub; wk < K; wk += NW) {
     const int c0 = job.chunk[wk], n = job.chunk[wk + 1] - c0;
     float s;
     if (n > 1) {
@@ -1270,12 +1167,12 @@ __device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const Batch
   }
 }
 
-// Workgroups below rest.first[0]: the table's layers, tiles x slots each; then the rest, an element per thread.
-// Measured, 3-32-64-128: 128 images, four workers, second stage and update 8.3 + 3.9 us before, 10.8 together (step 90.5 -> 88.2 us);
-// 1024 images, eight workers, 14.6 + 6.4 and 20.5 (step -0.2 per cent); 2048 images, sixteen, 23.0 + 9.7 and 26.3 (step -2.0
-// per cent).  One register per workgroup and 16 loads in flight: two registers, or 32 loads, are no faster.
-template <bool MOM>
-__global__ __launch_bounds__(kThreads) void wgrad_update_kernel(BatchTable tab, RestTable rest, Segments seg, Lambdas lam, Optim opt,
+// Workgroups below rest.first[0]: the table's layers, tiles x slots each; then the rest, an element per thread.  A wavefront per
+// worker up to sixteen: with four wavefronts they took turns, a round trip to memory each.
+// Measured, 3-32-64-128: 1024 images, eight workers, 20.3 us with a register per workgroup, 256 bytes a load and twice the partial
+// tiles; 17.0 with half the tiles, 13.6 with four registers and eight wavefronts.  128 images, four workers, 10.6 -> 9.7.
+template <bool MOM, int NW>
+__global__ __launch_bounds__(NW * 64) void wgrad_update_kernel(BatchTable tab, RestTable rest, Segments seg, Lambdas lam, Optim opt,
                                                                 UpdateTo to) {
   extern __shared__ __attribute__((aligned(16))) float lds_update[];
   const int b = (int)blockIdx.x;
@@ -1283,7 +1180,7 @@ __global__ __launch_bounds__(kThreads) void wgrad_update_kernel(BatchTable tab, 
     int i = 0;
 #pragma unroll
     for (int k = 1; k < kRestRanges; ++k) i += k < rest.n && b >= rest.first[k] ? 1 : 0;
-    const int at = rest.beg[i] + (b - rest.first[i]) * kThreads + (int)threadIdx.x;
+    const int at = rest.beg[i] + (b - rest.first[i]) * NW * 64 + (int)threadIdx.x;
     if (at >= rest.end[i]) return;
     const float th = to.theta[at], ve = MOM ? to.vel[at] : 0.f;
     float g = 0.f;
@@ -1301,8 +1198,8 @@ __global__ __launch_bounds__(kThreads) void wgrad_update_kernel(BatchTable tab, 
   const int e = job_at(tab, b);
   const BatchJob& job = tab.job[e];
   const int local = b - tab.first[e], slot = quotient(local, job.by_tiles, job.tiles), tile = local - slot * job.tiles;
-  if (job.kind == kFirst) wgrad1_update<MOM>(job.first, job, slot, seg, lam, opt, to, lds_update);
-  else wgrad3_update<MOM>(job.patch, job, tile, slot, seg, lam, opt, to, lds_update);
+  if (job.kind == kFirst) wgrad1_update<MOM, NW>(job.first, job, slot, seg, lam, opt, to, lds_update);
+  else wgrad3_update<MOM, NW>(job.patch, job, tile, slot, seg, lam, opt, to, lds_update);
 }
 
 // ------------------------------------------------------------------ planning
@@ -1355,7 +1252,7 @@ bool plan_first(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   return true;
 }
 
-// 3x3 / stride 1 / pad 1 and a map whose rows tile into units of 128 positions: kernel C.  (Also
+// 3x3 / stride 1 / pad 1 and a map whose rows tile into units of 128 positions: the ring form or kernel C.  (Also
 // for a first layer with 8 stored channels on maps that are not 32 wide, which kernel G does not
 // take: most of the 64-channel tile is then empty.)
 bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Segments& seg) {
@@ -1381,21 +1278,24 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   while ((1 << p.nimg_log) < nimg) ++p.nimg_log;   // (nimg divides 128)
   auto reciprocal16 = [](int d) { return (uint32_t)(((1 << 16) + d - 1) / d); };   // (exact: rows below 2^9, divisors up to 130)
   p.by_r = reciprocal16(R); p.by_patch = reciprocal16(R + 2);
-  p.by_upi = nimg == 1 ? reciprocal_below(H / R, (uint64_t)seg.off[seg.K] * (H / R)) : 0;
+  p.by_upi = nimg == 1 ? reciprocal_below(H / R, (uint64_t)seg.off[seg.K] * (H / R) + 1) : 0;
+  // the form with rings wants whole images of 32 positions (4-wide maps: a step is two images)
+  const bool ring = w4 || ((W == 8 || W == 16 || W == 32) && H * W % 32 == 0 && (p.by_upi || nimg > 1 || R == H));
   // at most 32 input channels: half of a 64 x 64 tile would be empty
-  const bool narrow = g.Cs <= 32 && (W == 8 || W == 16 || W == 32);
-  pl.lds = (size_t)64 * kSA + (size_t)(narrow ? 32 : 64) * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
-  if (pl.lds > 80 * 1024) return false;
-  pl.job.kind = w4 ? kPatch4 : W == 8 ? (narrow ? kPatch8Narrow : kPatch8) : W == 16 ? (narrow ? kPatch16Narrow : kPatch16)
+  const bool narrow = ring && !w4 && g.Cs <= 32;
+  pl.lds = ring ? ring_lds_bytes(narrow, 4) : (size_t)64 * kSA + (size_t)64 * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
+  if (!ring && pl.lds > 80 * 1024) return false;
+  pl.job.kind = !ring ? kPatchAny : w4 ? kPatch4 : W == 8 ? (narrow ? kPatch8Narrow : kPatch8) : W == 16 ? (narrow ? kPatch16Narrow : kPatch16)
               : W == 32 ? (narrow ? kPatch32Narrow : kPatch32) : kPatchAny;
   pl.job.tiles = ((j.Cout + 63) / 64) * ((g.Cs + 63) / 64);
   pl.job.slots = 144; pl.job.patch = p;
   count_units(pl, seg, H / R, nimg);
   // about one workgroup per compute unit (every chunk parks a partial tile of up to 148 KB that the second stage reads
-  // back: with 512 chunks that traffic outweighed the extra parallelism, measured -2 % on the three-layer CNN's step)
-  pl.min_upc = 4; pl.upc_step = 1; pl.alone = 256;
+  // back: with 512 chunks that traffic outweighed the extra parallelism, measured -2 % on the three-layer CNN's step).
+  // At least two units a chunk (128 images of 3-32-64-128: step 77.9 us with four, 76.6 with two)
+  pl.min_upc = 2; pl.upc_step = 1; pl.alone = 256;
   pl.slot_floats = kTile3Stride;
-  pl.work = (w4 ? 6.0 : narrow ? 3.0 : 4.5) * pl.job.tiles * pl.total_units;
+  pl.work = (ring ? (narrow ? 1.3 : 2.6) : 4.5) * pl.job.tiles * pl.total_units;
   return true;
 }
 
@@ -1496,12 +1396,14 @@ struct BatchPlan {
   int light[kBatchJobs], lights;   // places in plans
   int member[kBatchJobs];          // ... of the jobs of tab
   int blocks, rblocks;
+  bool ring8;                      // tab in wgrad_ring_kernel
   size_t lds, scratch[kBatchJobs];
 };
 
 void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_stride, const Segments& seg, float* partial,
-                size_t floats, int workgroups) {
+                size_t floats, int workgroups, bool alone) {
   std::memset(&bp, 0, sizeof(bp));
+  bp.ring8 = alone;
   int heavy = 0;
   double work = 0.0;
   for (int i = 0; i < m; ++i) {
@@ -1509,11 +1411,13 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
     if (plan_first(pl, jobs[i], worker_stride, seg)) { bp.light[bp.lights++] = i; continue; }
     if (!plan_patch(pl, jobs[i], worker_stride, seg) && !plan_stride2(pl, jobs[i], worker_stride, seg))
       plan_general(pl, jobs[i], worker_stride, seg);
+    bp.ring8 = bp.ring8 && pl.job.kind >= kPatch4 && pl.job.kind <= kPatch32Narrow && pl.job.kind != kPatchAny;
     work += pl.work;
     ++heavy;
   }
   // Layers that share the launch share its workgroups in proportion to the time their units take (not
   // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).
+  if (bp.ring8) workgroups /= 2;
   // The scratch is shared out in proportion to what that many partial tiles take, in whole 256-byte lines (tiles that began
   // inside a line cost the three-layer net's step 6 per cent).
   const double room = (double)std::min(floats, conv_wgrad_partial_floats());
@@ -1547,7 +1451,7 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
     if (light) continue;
     bp.tab.first[bp.tab.n] = bp.blocks;
     bp.blocks += pl.job.tiles * pl.job.chunk[seg.K];
-    bp.lds = std::max(bp.lds, pl.lds);
+    bp.lds = std::max(bp.lds, bp.ring8 ? ring_lds_bytes(pl.job.kind >= kPatch8Narrow, 8) : pl.lds);
     bp.member[bp.tab.n] = i;
     bp.tab.job[bp.tab.n++] = pl.job;
   }
@@ -1600,7 +1504,7 @@ bool update_too_long(const BatchTable& tab, int K) {
 // has another second stage, or the walk in this one is long, or none has any.
 bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, const Segments& seg, const SgdArgs& sgd, float* G,
                   size_t params) {
-  if (bp.red.n == 0 || params > (size_t)INT32_MAX - kThreads || update_too_long(bp.red, seg.K)) return false;
+  if (bp.red.n == 0 || params > (size_t)INT32_MAX - 1024 || update_too_long(bp.red, seg.K)) return false;
   BatchTable tab = bp.red;
   struct Range { long beg, end; } covered[2 * kBatchJobs];
   int m = 0, blocks = 0;
@@ -1616,6 +1520,7 @@ bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, con
     tab.first[i] = blocks;
     blocks += job.tiles * (first ? job.slots : kUpdateSlots3);
   }
+  const int threads = seg.K <= 4 ? 256 : seg.K <= 8 ? 512 : 1024;
   std::sort(covered, covered + m, [](const Range& a, const Range& b) { return a.beg < b.beg; });
   RestTable rest{};
   rest.first[0] = blocks;
@@ -1626,33 +1531,37 @@ bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, con
       rest.first[rest.n] = blocks;
       rest.beg[rest.n] = (int32_t)at;
       rest.end[rest.n++] = (int32_t)end;
-      blocks += (int)((end - at + kThreads - 1) / kThreads);
+      blocks += (int)((end - at + threads - 1) / threads);
     }
     if (i < m) at = covered[i].end;
   }
   const UpdateTo to{sgd.params, sgd.velocity, G, worker_stride};
   const Lambdas lam = lambdas_of(seg);
   const Optim opt{sgd.lr, sgd.momentum, sgd.weight_decay};
-  const size_t lds = (size_t)seg.K * 64 * sizeof(float);
-  if (sgd.velocity)
-    hipLaunchKernelGGL(wgrad_update_kernel<true>, dim3(blocks), dim3(kThreads), lds, st, tab, rest, seg, lam, opt, to);
-  else
-    hipLaunchKernelGGL(wgrad_update_kernel<false>, dim3(blocks), dim3(kThreads), lds, st, tab, rest, seg, lam, opt, to);
+  const size_t lds = (size_t)seg.K * 256 * sizeof(float);   // (kernel G: a quarter of it)
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), lds, st, tab, rest, seg, lam, opt, to); };
+#define OMNI_UPDATE(NW_) { if (sgd.velocity) launch(wgrad_update_kernel<true, NW_>); else launch(wgrad_update_kernel<false, NW_>); }
+  if (threads == 256) OMNI_UPDATE(4) else if (threads == 512) OMNI_UPDATE(8) else OMNI_UPDATE(16)
+#undef OMNI_UPDATE
   return true;
 }
 }  // namespace
 
 bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
-                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd, float* G,
-                      size_t params) {
+                      float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd, float* G, size_t params,
+                      bool alone) {
   if (head && n == 0) {
     head_wgrad_loss(st, true, *head, seg);
     return false;
   }
   for (int base = 0; base < n; base += kBatchJobs) {
     BatchPlan bp;
-    plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, floats, workgroups);
-    if (bp.blocks > 0) {
+    plan_batch(bp, jobs + base, std::min(n - base, kBatchJobs), worker_stride, seg, partial, floats, workgroups, alone);
+    if (bp.blocks > 0 && bp.ring8) {
+      static LdsLimit limit;
+      limit.raise(reinterpret_cast<const void*>(&wgrad_ring_kernel), std::max(ring_lds_bytes(true, 8), ring_lds_bytes(false, 8)));
+      hipLaunchKernelGGL(wgrad_ring_kernel, dim3(bp.blocks), dim3(2 * kThreads), bp.lds, st, bp.tab, seg);
+    } else if (bp.blocks > 0) {
       static LdsLimit limit;
       limit.raise(reinterpret_cast<const void*>(&wgrad_batch_kernel), 80 * 1024);
       hipLaunchKernelGGL(wgrad_batch_kernel, dim3(bp.blocks), dim3(kThreads), bp.lds, st, bp.tab, seg);
@@ -1679,12 +1588,12 @@ bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
   return false;
 }
 
-void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, int workgroups, ConvWgradPlanned* out) {
+void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, int workgroups, ConvWgradPlanned* out, bool alone) {
   int launch = 0;
   for (int base = 0; base < n; base += kBatchJobs) {
     BatchPlan bp;
     const int m = std::min(n - base, kBatchJobs);
-    plan_batch(bp, jobs + base, m, 0, seg, nullptr, conv_wgrad_partial_floats(), workgroups);
+    plan_batch(bp, jobs + base, m, 0, seg, nullptr, conv_wgrad_partial_floats(), workgroups, alone);
     const int shared = launch++;
     for (int i = 0; i < m; ++i) {
       const BatchJob& job = bp.plans[i].job;

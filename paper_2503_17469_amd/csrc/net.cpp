@@ -1063,7 +1063,7 @@ void step_bf16(StepCtx& c) {
                                        c.forked ? conv_partial3 : conv_partial,
                                        c.forked ? kSmallScratchFloats : omni::conv_wgrad_partial_floats(),
                                        head_pending ? &head_grads : nullptr, 512,
-                                       c.fuse_update && !c.forked && linear_jobs.empty() ? &sgd : nullptr, c.G, net->P);
+                                       c.fuse_update && !c.forked && linear_jobs.empty() ? &sgd : nullptr, c.G, net->P, !c.forked);
   } else if (head_pending) {
     omni::head_wgrad_loss(st, true, head_grads, c.seg);
   }

@@ -13,6 +13,9 @@ inline uint32_t reciprocal_below(uint64_t d, uint64_t below) {
   return d > 1 && d < 1ull << 32 && below <= (1ull << 32) / d ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u;
 }
 
+// By a divisor that is 1 or whose reciprocal is known not to be 0: no branch, so that loads are not held up at one.
+__host__ __device__ inline int exact_quotient(int n, uint32_t by) { return by ? (int)(((uint64_t)(uint32_t)n * by) >> 32) : n; }
+
 __host__ __device__ inline int quotient(int n, uint32_t by, int d) {
   return by ? (int)(((uint64_t)(uint32_t)n * by) >> 32) : d == 1 ? n : n / d;
 }
