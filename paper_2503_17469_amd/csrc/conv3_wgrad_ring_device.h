@@ -33,6 +33,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "conv_device.h"
+#include "lds_load_device.h"
 #include "lds_transpose_device.h"
 #include "quotient.h"
 #include "wgrad_chunk.h"
@@ -88,20 +89,6 @@ constexpr size_t ring_lds_bytes(bool ks, int waves) {
 __device__ inline uint32_t from_partner(uint32_t send, bool upper) {
   const u32x2 sw = __builtin_amdgcn_permlane32_swap(send, send, false, false);
   return upper ? sw[0] : sw[1];
-}
-
-// Sixteen bytes per lane from memory to LDS address `to` + 16 * lane (to: the same in the whole wavefront), from base + offset or
-// from an address per lane.  Counted by vmcnt like any load; the compiler does not know of it, so whoever reads the data waits
-// first.  (Through the builtin it waits for all loads under way before the next LDS read, whichever part of LDS that reads.)
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t offset, uint32_t to) {
-  uint32_t m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0) : "s"(to), "v"(offset), "s"(base) : "memory");
-}
-__device__ __forceinline__ void load_to_lds(const void* from, uint32_t to) {
-  uint32_t m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0) : "s"(to), "v"(from) : "memory");
 }
 
 typedef short v4s_t __attribute__((ext_vector_type(4)));

@@ -9,35 +9,42 @@
 // wavefront a quarter of the positions.  What limits such a product is not a unit of the machine but waiting, so:
 //
 //   * the next reduction step's fragments are read under the matrix instructions of this one (two register sets);
-//   * the reduction is staged 32 channels at a time, and a slice brings its patch AND the weights of all
-//     nine taps (9 x 64 x 32) into LDS together: no barrier and no wait inside a slice.  The memory counter retires
-//     loads in order: weight slabs requested tap by tap, in between the loads of the next patch, waited for those
-//     as well (about 1 us per tap, measured).  All loads of the next slice are issued together when a slice begins and are
-//     first needed when it ends, where two barriers separate the last fragment read from the stores that replace
-//     patch and weights;
+//   * the reduction is staged 32 channels at a time, by loads that write LDS themselves (NP = 0): no registers, no store
+//     instructions and no wait for either.  A slice's patch goes to the other of two slots while this one's is read; its
+//     weights come 16 channels at a time, one half being read while the other is filled, in the order the matrix instruction
+//     wants them, which the cast to bf16 lays out.  Two barriers per slice;
+//   * where those loads do not fit (other map widths, channel counts that are no multiple of 32, a single slice), a slice
+//     comes through registers: its patch AND the weights of all nine taps (9 x 64 x 32) into LDS together, no barrier and no
+//     wait inside a slice.  The memory counter retires loads in order: weight slabs requested tap by tap, in between the
+//     loads of the next patch, waited for those as well (about 1 us per tap, measured).  All loads of the next slice are
+//     issued together when a slice begins and are first needed when it ends, where two barriers separate the last fragment
+//     read from the stores that replace patch and weights;
 //   * the product is formed TRANSPOSED (weights as the left operand): a lane then holds, for one
 //     position, runs of four consecutive channels; one swap of the wavefront's halves per register pair
 //     turns them into runs of eight, and the lane writes 16-byte pieces of the output row itself --
 //     no staging of the output tile through LDS.
 //
-// 2048 images of the ResNet-18 shape, 154.6 GFLOP per launch, each alone: forward with the batch norm's sums 224 us at 64 channels
-// (32x32 maps; 706 MB, 3.2 TB/s), 192 at 128, 173 at 256 (0.9 PFLOP/s, matrix pipe busy 0.49); input gradient with mask, shortcut's
-// gradient and sums 298 us (1.2 GB, 4.1 TB/s), 227, 197.  At 64 channels memory and matrix pipe bind together.
+// 2048 images of the ResNet-18 shape, 154.6 GFLOP per launch, each alone, staged through registers and by loads that write LDS:
+// forward with the batch norm's sums 216 -> 187 us at 64 channels (32x32 maps; 706 MB, 3.8 TB/s), 190 -> 154 at 128, 172 -> 136 at
+// 256 (1.14 PFLOP/s, matrix pipe busy 0.63 at the 1.74 GHz that the chip then holds); input gradient with mask, shortcut's gradient
+// and sums 294 -> 261 us (1.2 GB, 4.7 TB/s), 224 -> 188, 199 -> 160.  At 64 channels memory and the epilogue's vector instructions
+// (the sums are in double) bind, at 256 the matrix pipe.  128 images: 22-24 -> 19-21 and 26-29 -> 24-26.5, a third of it the first loads.
 //
-// 1024 images of three conv layers 3-32-64-128, 32x32: forward 32 -> 64 on 16x16 with pooling 33.7 -> 20.3 us (kernel D staged fp32
-// tiles through LDS and waited for memory at every tap), 64 -> 128 on 8x8 24.6 -> 19.5, input gradients 64 -> 32 27.4 -> 21.7 and
-// 128 -> 64 18.5 -> 18.2.  Of a workgroup's 30000 cycles in the first, 6000 are the first loads, 4600 per unit the matrix pipe (two
-// workgroups on it) and 5000 the epilogue's vector instructions, two thirds of them pooling (7700 with a float comparison per
-// value and biases from memory); indexes by division were 2600.
+// 1024 images of three conv layers 3-32-64-128, 32x32: forward 32 -> 64 on 16x16 with pooling 20.3 us (one slice, through registers),
+// 64 -> 128 on 8x8 19.5 -> 17.6, input gradients 64 -> 32 21.7 -> 21.5 and 128 -> 64 18.2 -> 16.0.  Of a workgroup's 30000 cycles
+// in the first, 6000 are the first loads, 4600 per unit the matrix pipe (two workgroups on it) and 5000 the epilogue's vector
+// instructions, two thirds of them pooling; indexes by division were 2600.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "bf16.h"
 #include "bn_sums_device.h"
 #include "common.h"
 #include "kernels.h"
 #include "lds_limit.h"
+#include "lds_load_device.h"
 #include "pool_device.h"
 #include "quotient.h"
 
@@ -60,6 +67,7 @@ struct WideParams {
   int groups;          // of upw units (see below)
   int flip;            // 1: dgrad (mirrored taps)
   int wlog;            // log2 of W
+  uint32_t by_rows;    // 2^22 / (R + 2) rounded up
   uint32_t by_patch, by_row, by_r;   // 2^22 / d rounded up, for division of a patch position by a patch and by a patch row, and of a row by R
   uint32_t by_units;   // reciprocal_below(units of an image)
   const void* zero;    // zeros for absent pieces
@@ -91,6 +99,13 @@ constexpr int KC = 32;            // reduction channels per slice
 constexpr int kRow = KC + 8;      // elements per LDS row (80 bytes): sixteen 16-byte reads of consecutive rows cover all banks
 constexpr int OC = KC / 8;        // 16-byte pieces per patch position and per weight row
 constexpr int KK = KC / 16;       // reduction steps per tap
+// With loads that write LDS themselves (NP = 0): patches of 32 channels, rows of 64 bytes, no column halo, in two slots; weights of 16
+// channels, in the order the matrix instruction wants them (blocks of 64 lanes x 8 elements, see frag_offset), in two halves.  Both are
+// whole cache lines a wavefront: with patches of 16 channels, 32 bytes a position, a load took 200 cycles and bound the kernel.
+constexpr int kDmaPatch = 320;                              // positions at most
+constexpr uint32_t kDmaSlot = kDmaPatch * 64 + 64;          // (with the zeros that absent columns are read from)
+constexpr uint32_t dma_weights(int nb) { return 9 * nb * 1024; }
+constexpr uint32_t dma_lds(int nb) { return 2 * kDmaSlot + 2 * dma_weights(nb); }
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
@@ -131,6 +146,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   constexpr int kTN = 32 * NB;    // output channels per workgroup
   constexpr bool STOP = ONE;   // no loads for a unit that does not come (the other variants would spill at the branch)
   constexpr int RW = (9 * kTN * OC + kThreads - 1) / kThreads;   // weight pieces per thread and slice
+  constexpr bool DMA = NP == 0;
+  static_assert(!DMA || (MA == 2 && !ONE), "units of 256 positions");
   static_assert(!BITS || BWD, "mask bits belong to the input gradient");
   constexpr int WPOS = 32 * MA;   // positions per wavefront
   extern __shared__ __attribute__((aligned(16))) unsigned char smemW[];
@@ -139,7 +156,8 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   const int npatch = p.nimg * PR * PW;
   bf16_t* sP = reinterpret_cast<bf16_t*>(smemW);          // [npatch][kRow]
   bf16_t* sW = sP + (size_t)npatch * kRow;                // [9][64][kRow]
-  float* sN = reinterpret_cast<float*>(sW + 9 * kTN * kRow);   // STATS and BWD: [64] means, [64] factors; forward: [64] biases
+  float* sN = DMA ? reinterpret_cast<float*>(smemW + dma_lds(NB))
+                  : reinterpret_cast<float*>(sW + 9 * kTN * kRow);   // STATS and BWD: [64] means, [64] factors; forward: [64] biases
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 31, h = lane >> 5;
   const int tiles_n = (p.N + kTN - 1) / kTN;
@@ -152,20 +170,26 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   const int group = (on_xcd / tiles_n) * 8 + (blockIdx.x & 7);
   if (group >= p.groups) return;   // (the grid is rounded up to whole rounds of 8 groups)
   // (the tables lie in lines of arguments of their own, 640 cycles each at first touch: without sums there is one entry)
-  int gk = 0;
-  if (STATS)
-    while (gk + 1 < p.gK && group >= p.gfirst[gk + 1]) ++gk;
-  const int ufirst = STATS ? p.ufirst[gk] : 0, uafter = STATS ? p.ufirst[gk + 1] : p.units;
-  const int ibeg = STATS ? p.ifirst[gk] : 0, iend = STATS ? p.ifirst[gk + 1] : p.rows;
+  int gk = 0, ufirst = 0, uafter = p.units, ibeg = 0, iend = p.rows, gbeg = 0;
+  if (STATS) {                                            // (all lanes at once: entry by entry, eight workers' took 5000 cycles)
+    const int tg = p.gfirst[lane], tu = p.ufirst[lane], ti = p.ifirst[lane];   // (65 entries)
+    gk = __popcll(__ballot(lane < p.gK && tg <= group)) - 1;
+    const bool more = gk + 1 < p.gK;
+    gbeg = __builtin_amdgcn_readlane(tg, gk);
+    ufirst = __builtin_amdgcn_readlane(tu, gk);
+    ibeg = __builtin_amdgcn_readlane(ti, gk);
+    uafter = more ? __builtin_amdgcn_readlane(tu, gk + 1) : p.units;
+    iend = more ? __builtin_amdgcn_readlane(ti, gk + 1) : p.rows;
+  }
   const int col0 = tile_n * kTN;
   const int K = 9 * p.Cs;
-  const int ubeg = ufirst + (group - (STATS ? p.gfirst[gk] : 0)) * p.upw, uend = min(uafter, ubeg + p.upw);
+  const int ubeg = ufirst + (group - gbeg) * p.upw, uend = min(uafter, ubeg + p.upw);
   const int nslice = p.Cs / KC;
 
   // ---- patch staging tasks: piece x = tid + 256 t -> patch position x / OC, channel octet x % OC
-  int prel[NP];
+  int prel[NP > 0 ? NP : 1];
   uint32_t col_ok = 0, top = 0, bottom = 0;
-  uint32_t img8[(NP + 3) / 4];
+  uint32_t img8[(NP + 3) / 4 + 1];
 #pragma unroll
   for (int t = 0; t < (NP + 3) / 4; ++t) img8[t] = 0;
   const int npieces = npatch * OC;
@@ -191,19 +215,33 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   // ---- fragment addresses: this wavefront's positions wave*128 + a*32 + j
   auto row_order = [](int t) { return (t >> 1) + 4 * (t & 1); };   // t: 0..7
   int pbase[MA], ipos[MA];
+  const uint32_t lds0 = lds_address(smemW), zeros = lds0 + kDmaPatch * 64;
+  uint32_t xaddr[DMA ? 9 : 1][MA];                        // DMA: where tap t of block a's positions lies in a buffer
+  // how the four pieces of a patch position are moved (xor) so that sixteen lanes' reads cover all banks
+  auto moved = [](int at) { return W8 ? (at >> 2 & 1) | (at >> 3 & 2) : at >> 2 & 3; };
 #pragma unroll
   for (int a = 0; a < MA; ++a) {
     int pos = wave * WPOS + a * 32 + j;
-    if (W8) pos = wave * WPOS + (a >> 1) * 64 + row_order((a & 1) * 4 + (j >> 3)) * 8 + (j & 7);
+    if (W8 && !DMA) pos = wave * WPOS + (a >> 1) * 64 + row_order((a & 1) * 4 + (j >> 3)) * 8 + (j & 7);
+    // (rows 0 2 1 3: of sixteen lanes the rows are two apart, and the rows of a pooling window are lanes j and j ^ 16)
+    if (W8 && DMA) pos = wave * WPOS + a * 32 + ((j & 7) | (j & 8) << 1 | (j & 16) >> 1);
     ipos[a] = pos;
     const int rr = pos >> p.wlog, w = pos - (rr << p.wlog);
     const int il = (int)(((uint32_t)rr * p.by_r) >> 22), r = rr - il * R;
     pbase[a] = ((il * PR + r) * PW + w) * kRow + h * 8;   // patch origin is (-1, -1): tap (u, v) adds u*PW + v
+    if constexpr (DMA) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const int at = (il * PR + r + t / 3) * W + w + t % 3 - 1;
+        const bool in = (t % 3 > 0 || w > 0) && (t % 3 < 2 || w < W - 1);
+        xaddr[DMA ? t : 0][a] = in ? lds0 + at * 64 + (h ^ moved(at)) * 16 : zeros;
+      }
+    }
   }
   const bf16_t* const wfrag = sW + j * kRow + h * 8;
 
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
-  u32x4 rp[NP], rw[ONE ? 1 : RW];
+  u32x4 rp[NP > 0 ? NP : 1], rw[ONE ? 1 : RW];
   auto unit_geom = [&](int unit, int& n0, int& r0, int& nvalid) {
     unit -= ufirst;
     if (p.nimg == 1) {
@@ -252,7 +290,83 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   if (STATS && BWD && tid < 2 * kTN) sN[(tid & 1) * kTN + (tid >> 1)] = p.stat_norm[((size_t)gk * p.N + col0) * 2 + tid];
   constexpr bool AFFINE = !BWD && !STATS;   // bias and ReLU exist in the plain forward only
   const float bias = AFFINE && p.bias ? p.bias[min(col0 + (tid & (kTN - 1)), p.N - 1)] : 0.f;
-  load_slice(ubeg, 0);
+  // ---- DMA: a patch instruction of a wavefront brings 16 positions, a weight instruction a block
+  constexpr int kXI = kDmaPatch / 16 / 4;                 // patch instructions per wavefront at most
+  const bf16_t* xptr[DMA ? kXI : 1];                      // of the unit that is loaded next
+  uint32_t xstep[DMA ? kXI : 1];                          // 0 where there is nothing and a zero is loaded
+  const int nx = (p.nimg * PR * W + 15) / 16;
+  const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
+  auto load_unit = [&](int unit) {
+    if constexpr (DMA) {
+      int n0, r0, nvalid;
+      unit_geom(unit, n0, r0, nvalid);
+      int at0 = wave * 16 + (lane >> 2);
+      asm volatile("" : "+v"(at0));                       // (places and pieces kept from unit to unit would not fit the registers)
+#pragma unroll
+      for (int k = 0; k < kXI; ++k) {
+        const int at = at0 + 64 * k;
+        const int row = at >> p.wlog, w = at & (W - 1), il = (int)(((uint32_t)row * p.by_rows) >> 22), pr = row - il * PR;
+        const int hr = r0 + pr - 1;
+        const bool in = unit < uend && il < nvalid && hr >= 0 && hr < H;
+        xptr[k] = in ? p.src + (((size_t)(n0 + il) * H + hr) * W + w) * p.Cs + ((lane & 3) ^ moved(at)) * 8 : zp;
+        xstep[k] = in ? KC : 0;
+      }
+    }
+  };
+  // the patch of the next slice (unit by unit) to the next slot, and the weights of sixteen channels to either half
+  uint32_t to_slot = 0;
+  int lunit = ubeg, lslice = 0;
+  auto load_patch = [&]() {
+    if constexpr (DMA) {
+#pragma unroll
+      for (int k = 0; k < kXI; ++k) {
+        if (k == kXI - 1 && (int)wave_u + 4 * k >= nx) break;   // (more than 16 in all)
+        load_to_lds(xptr[k], lds0 + to_slot + (wave_u + 4 * k) * 1024);
+        xptr[k] += xstep[k];
+      }
+      to_slot = kDmaSlot - to_slot;
+      if (++lslice == nslice) {
+        lslice = 0;
+        load_unit(++lunit);                               // (past the last unit: images that are not there, zeros)
+      }
+    }
+  };
+  // weight instruction wave + 4 k: two of a tap's blocks (NB == 1: one), taps in turn (flip: the last one first in LDS)
+  const int c16n = p.Cs >> 4, wtap0 = NB == 2 ? wave_u >> 1 : wave_u, wblk = NB == 2 ? wave_u & 1 : 0;
+  const int wexists = col0 + 32 * wblk < p.N ? wblk : 0;  // (a tile of which only the first half exists)
+  const char* const wsrc = reinterpret_cast<const char*>(p.wgt) + ((size_t)(((col0 >> 5) + wexists) * 9 + wtap0) * c16n << 10);
+  const uint32_t wstride = (uint32_t)((NB == 2 ? 2 : 4) * c16n) << 10;
+  const uint32_t wto = lds0 + 2 * kDmaSlot + ((p.flip ? 8 - wtap0 : wtap0) * NB + wblk) * 1024;
+  const int wstep = p.flip ? -4096 : 4096;
+  auto load_weights = [&](int c16) {
+    if constexpr (DMA) {
+      constexpr int kWI = 9 * NB;
+      const char* from = wsrc + ((size_t)c16 << 10);
+      uint32_t to = wto + (c16 & 1) * dma_weights(NB);
+#pragma unroll
+      for (int k = 0; k < (kWI + 3) / 4; ++k) {
+        if (k == (kWI + 3) / 4 - 1 && (int)wave_u + 4 * k >= kWI) break;
+        load_to_lds(from, lane * 16, to);
+        from += wstride;
+        to += wstep;
+      }
+    }
+  };
+  // own weights have arrived (the patch asked for after them may be under way), then everyone's
+  const int xloads = (nx - (int)wave_u + 3) / 4;
+  auto weights_arrived = [&]() {
+    if (xloads <= 4) asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(5)\n\ts_barrier" ::: "memory");
+  };
+  if constexpr (DMA) {
+    load_unit(ubeg);
+    load_weights(0);
+    load_patch();
+    if (tid < 8)
+      *reinterpret_cast<u32x4*>(smemW + (tid >> 2) * kDmaSlot + kDmaPatch * 64 + (tid & 3) * 16) = u32x4{0u, 0u, 0u, 0u};
+  } else {
+    load_slice(ubeg, 0);
+  }
   __builtin_amdgcn_sched_barrier(0);
   if (AFFINE && tid < kTN) sN[tid] = bias;
   if constexpr (ONE) {
@@ -262,9 +376,14 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
 #pragma unroll
     for (int t = 0; t < RW; ++t) store_w(t, w1[t]);
   }
-  store_slice();
-  __syncthreads();
+  if constexpr (DMA) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  } else {
+    store_slice();
+    __syncthreads();
+  }
 
+  uint32_t to_other = kDmaSlot;   // DMA: from the slot that is read to the other
   int h8 = h * 8;   // the first channel of this lane's runs of eight
   double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's sum of a channel of either half tile over the group's units
 
@@ -310,69 +429,137 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
         }
     };
 
-    for (int cs = 0; cs < nslice; ++cs) {
-      const bool last_slice = cs + 1 == nslice, more = !STOP || !last_slice || unit + 1 < uend;
-      // the next slice (of this unit, or the first of the next unit) sets out now: it is needed when this one ends
-      if (more) load_slice(last_slice ? min(unit + 1, uend - 1) : unit, last_slice ? 0 : cs + 1);
-      bf16x8 fa[2][MA], fb[2][NB];   // two fragment sets: one feeds the matrix pipe while the other is read
-      {
-        const int toff0 = (p.flip ? 2 * PW + 2 : 0) * kRow;
+    if constexpr (DMA) {
+      // sixteen channels: nine taps, the next tap's fragments read under this one's matrix instructions
+      auto sixteen = [&](auto which) {
+        constexpr uint32_t half = decltype(which)::value;
+        const uint32_t wl = lds0 + 2 * kDmaSlot + half * dma_weights(NB) + lane * 16;
+        auto read = [](uint32_t at) {
+          typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+          return as_bf16x8(*(lds_u32x4*)(uintptr_t)at);
+        };
+        uint32_t second_half = half * 32;
+        if (half) asm volatile("" : "+s"(second_half));   // (as above)
+        auto patch_at = [&](int tap, int a) { return half ? xaddr[DMA ? tap : 0][a] ^ second_half : xaddr[DMA ? tap : 0][a]; };
+        auto tap_of = [](int t) { return 8 - t; };   // the last tap first
+        bf16x8 fa[2][MA], fb[2][NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) fb[0][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + b * 32 * kRow));
+        for (int b = 0; b < NB; ++b) fb[0][b] = read(wl + (tap_of(0) * NB + b) * 1024);
 #pragma unroll
-        for (int a = 0; a < MA; ++a) fa[0][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff0));
-      }
+        for (int a = 0; a < MA; ++a) fa[0][a] = read(patch_at(tap_of(0), a));
 #pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int u = tap / 3, v = tap - u * 3;
-        const int toff = (p.flip ? (2 - u) * PW + (2 - v) : u * PW + v) * kRow;
-        const int un = (tap + 1) / 3, vn = (tap + 1) - un * 3;
-        const int toff_next = (p.flip ? (2 - un) * PW + (2 - vn) : un * PW + vn) * kRow;
-        if (BWD && (MA == 4 || (BITS && !W8 && !STATS)) && tap == 6 && last_slice) load_epi(0, 0);
+        for (int tap = 0; tap < 9; ++tap) {
+          const int cur = tap & 1, nxt = cur ^ 1;
+          if (tap < 8) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const int step = tap * KK + kk;
-          const int cur = step & 1, nxt = cur ^ 1;
-          // (read in the order of first use: both weight fragments, then the patch fragments)
-          if (kk + 1 < KK) {
+            for (int b = 0; b < NB; ++b) fb[nxt][b] = read(wl + (tap_of(tap + 1) * NB + b) * 1024);
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-              fb[nxt][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + (tap * kTN + b * 32) * kRow + (kk + 1) * 16));
-#pragma unroll
-            for (int a = 0; a < MA; ++a)
-              fa[nxt][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff + (kk + 1) * 16));
-          } else if (tap < 8) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-              fb[nxt][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + ((tap + 1) * kTN + b * 32) * kRow));
-#pragma unroll
-            for (int a = 0; a < MA; ++a)
-              fa[nxt][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff_next));
+            for (int a = 0; a < MA; ++a) fa[nxt][a] = read(patch_at(tap_of(tap + 1), a));
           }
-          // transposed product: rows = output channels, columns = positions
 #pragma unroll
           for (int a = 0; a < MA; ++a)
 #pragma unroll
             for (int b = 0; b < NB; ++b)
               acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][b], fa[cur][a], acc[a][b], 0, 0, 0);
-          // issue order of this step: a fragment read of the next step behind each of the first matrix
-          // instructions (left to itself the scheduler reads every fragment right before its use and waits)
-          if (step + 1 < 9 * KK) {
+          if (tap < 8) {
 #pragma unroll
-            for (int i = 0; i < MA + NB; ++i) {
+            for (int i = 0; i < MA * NB; ++i) {
               __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix instruction
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+              __builtin_amdgcn_sched_group_barrier(0x100, NB == 2 ? 1 : 2, 0);   // ... and a read or two
             }
-            if (MA * NB > MA + NB) __builtin_amdgcn_sched_group_barrier(0x008, MA * NB - MA - NB, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
+      };
+      for (int cs = 0; cs < nslice; ++cs) {
+        const bool last = cs + 1 == nslice;
+        // (a unit's first slice had arrived before the last unit's results were stored)
+        if (cs == 0) asm volatile("s_barrier" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        load_weights(2 * cs + 1);
+        load_patch();
+        __builtin_amdgcn_sched_barrier(0);
+        sixteen(std::integral_constant<uint32_t, 0>{});
+        weights_arrived();
+        load_weights(last ? 0 : 2 * cs + 2);
+        if (BWD && BITS && !STATS && last) {
+          load_epi(0, 0);
+          load_epi(1, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        sixteen(std::integral_constant<uint32_t, 1>{});
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+          for (int a = 0; a < MA; ++a) xaddr[DMA ? t : 0][a] += to_other;
+        to_other = -to_other;
       }
-      // the slice is done: the next one replaces patch and weights once every wavefront has read its last fragment
-      if (more) {
-        __syncthreads();
-        store_slice();
-        __syncthreads();
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the next unit's first slice, before results are stored
+    } else {
+      for (int cs = 0; cs < nslice; ++cs) {
+        const bool last_slice = cs + 1 == nslice, more = !STOP || !last_slice || unit + 1 < uend;
+        // the next slice (of this unit, or the first of the next unit) sets out now: it is needed when this one ends
+        if (more) load_slice(last_slice ? min(unit + 1, uend - 1) : unit, last_slice ? 0 : cs + 1);
+        bf16x8 fa[2][MA], fb[2][NB];   // two fragment sets: one feeds the matrix pipe while the other is read
+        {
+          const int toff0 = (p.flip ? 2 * PW + 2 : 0) * kRow;
+#pragma unroll
+          for (int b = 0; b < NB; ++b) fb[0][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + b * 32 * kRow));
+#pragma unroll
+          for (int a = 0; a < MA; ++a) fa[0][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff0));
+        }
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+          const int u = tap / 3, v = tap - u * 3;
+          const int toff = (p.flip ? (2 - u) * PW + (2 - v) : u * PW + v) * kRow;
+          const int un = (tap + 1) / 3, vn = (tap + 1) - un * 3;
+          const int toff_next = (p.flip ? (2 - un) * PW + (2 - vn) : un * PW + vn) * kRow;
+          if (BWD && (MA == 4 || (BITS && !W8 && !STATS)) && tap == 6 && last_slice) load_epi(0, 0);
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            const int step = tap * KK + kk;
+            const int cur = step & 1, nxt = cur ^ 1;
+            // (read in the order of first use: both weight fragments, then the patch fragments)
+            if (kk + 1 < KK) {
+#pragma unroll
+              for (int b = 0; b < NB; ++b)
+                fb[nxt][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + (tap * kTN + b * 32) * kRow + (kk + 1) * 16));
+#pragma unroll
+              for (int a = 0; a < MA; ++a)
+                fa[nxt][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff + (kk + 1) * 16));
+            } else if (tap < 8) {
+#pragma unroll
+              for (int b = 0; b < NB; ++b)
+                fb[nxt][b] = as_bf16x8(*reinterpret_cast<const u32x4*>(wfrag + ((tap + 1) * kTN + b * 32) * kRow));
+#pragma unroll
+              for (int a = 0; a < MA; ++a)
+                fa[nxt][a] = as_bf16x8(*reinterpret_cast<const u32x4*>(sP + pbase[a] + toff_next));
+            }
+            // transposed product: rows = output channels, columns = positions
+#pragma unroll
+            for (int a = 0; a < MA; ++a)
+#pragma unroll
+              for (int b = 0; b < NB; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][b], fa[cur][a], acc[a][b], 0, 0, 0);
+            // issue order of this step: a fragment read of the next step behind each of the first matrix
+            // instructions (left to itself the scheduler reads every fragment right before its use and waits)
+            if (step + 1 < 9 * KK) {
+#pragma unroll
+              for (int i = 0; i < MA + NB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one matrix instruction
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+              }
+              if (MA * NB > MA + NB) __builtin_amdgcn_sched_group_barrier(0x008, MA * NB - MA - NB, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        // the slice is done: the next one replaces patch and weights once every wavefront has read its last fragment
+        if (more) {
+          __syncthreads();
+          store_slice();
+          __syncthreads();
+        }
       }
     }
 
@@ -423,8 +610,9 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
     };
     // (64-bit offsets formed from these before the units would be kept in registers all along, and do not fit)
     if (STATS || POOL) asm("" : "+v"(ipos[0]), "+v"(ipos[1]), "+v"(h8));
-    if (BWD && MA == 2 && !(BITS && !W8 && !STATS)) load_epi(0, 0);
-    if (BWD && MA == 2) load_epi(1, 1);
+    constexpr bool early = DMA ? BITS && !STATS : BITS && !W8 && !STATS;
+    if (BWD && MA == 2 && !early) load_epi(0, 0);
+    if (BWD && MA == 2 && !(DMA && early)) load_epi(1, 1);
     u32x4 xs[MA][STATS && BWD ? 4 : 1];   // STATS and BWD: the batch norm's input at this lane's positions
     auto load_x = [&](int a) {
 #pragma unroll
@@ -528,6 +716,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
       }
     }
   }
+  if constexpr (DMA) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may be on its way to LDS when it is used again
   if (STATS) {
     // the four wavefronts' sums meet in LDS (once nobody reads patch or weights any more), added in wavefront order
     __syncthreads();
@@ -555,14 +744,15 @@ void launch_variant(hipStream_t st, const WideParams& p, dim3 grid, size_t lds) 
 // without mask and sums: with pooling, on the narrow tile, with a single slice
 template <int MA, int NP, bool W8, int NB>
 void launch_plain(hipStream_t st, const WideParams& p, dim3 grid, size_t lds) {
-  const bool one = p.Cs == KC;
-  if (p.pool) {
-    if (one) launch_variant<MA, NP, W8, false, false, false, NB, true, true>(st, p, grid, lds);
-    else launch_variant<MA, NP, W8, false, false, false, NB, true, false>(st, p, grid, lds);
-  } else {
-    if (one) launch_variant<MA, NP, W8, false, false, false, NB, false, true>(st, p, grid, lds);
-    else launch_variant<MA, NP, W8, false, false, false, NB, false, false>(st, p, grid, lds);
+  auto launch = [&](auto one) {
+    constexpr bool ONE = decltype(one)::value;
+    if (p.pool) launch_variant<MA, NP, W8, false, false, false, NB, true, ONE>(st, p, grid, lds);
+    else launch_variant<MA, NP, W8, false, false, false, NB, false, ONE>(st, p, grid, lds);
+  };
+  if constexpr (NP > 0) {
+    if (p.Cs == KC) return launch(std::true_type{});
   }
+  launch(std::false_type{});
 }
 
 template <int MA, int NP, bool W8>
@@ -594,14 +784,33 @@ bool unit_shape(int H, int W, int unit, int& R, int& nimg) {
 }
 }  // namespace
 
+// Whether conv3_wide_bf16 takes the layer with weights in operand order (ConvGeom::frag = 2), staged by loads that write LDS: maps 8, 16
+// and 32 wide, whole blocks of 32 channels in and out, two slices of the reduction or more (a single one, 32 -> 64 on 16x16 with
+// pooling, 1024 images: 23.0 us, and 20.3 in the variant whose weights stay in LDS).  pooled: forward with a max pooling behind;
+// relu: after the product; share: as input gradient, a mask or another share to add.
+bool conv3_wide_takes(const ConvGeom& g, int N, bool pooled, bool relu, bool share) {
+  const int H = g.Hs, W = g.Ws;
+  if (g.raw3 || g.ks != 3 || g.stride != 1 || g.pad != 1 || g.Hp != H || g.Wp != W || (W != 8 && W != 16 && W != 32)) return false;
+  if (g.Cs % KC != 0 || g.Cs < 2 * KC || N % 32 != 0 || (long)g.rows * H * W * std::max(g.Cs, N) >= (1L << 31)) return false;
+  int R, nimg;
+  if (!unit_shape(H, W, 256, R, nimg) || nimg * (R + 2) * W > kDmaPatch) return false;
+  if (N == 32 && share) return false;
+  if (pooled && (!relu || W == 32 || H % 2 != 0 || R % 2 != 0 || (W == 8 && R % 8 != 0))) return false;
+  const long units = nimg == 1 ? (long)g.rows * (H / R) : (g.rows + nimg - 1) / nimg;
+  if (H > R && !reciprocal_below(H / R, units)) return false;
+  return units * ((N + 63) / 64) >= 32;
+}
+
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                      const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
                      const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats) {
+  const bool dma = g.frag == 2;   // (conv3_wide_takes has said yes)
   const int H = g.Hs, W = g.Ws;
   if (g.raw3 || g.ks != 3 || g.stride != 1 || g.pad != 1 || g.Hp != H || g.Wp != W) return false;
   if (g.Cs % 32 != 0 || N % 8 != 0 || (long)g.rows * H * W != M) return false;
   if ((long)M * std::max(g.Cs, N) >= (1L << 31)) return false;   // 32-bit element offsets in the kernel
   int nb = N <= 32 ? 1 : 2;
+  if (dma && nb == 1) stats = nullptr;   // (not taken: the narrow tile has no sums)
   // Units of 256 positions with two workgroups per compute unit where both fit LDS (one workgroup's loads,
   // stores and epilogue then run under the other's matrix instructions); units of 512 with one otherwise.
   // Two 256-register kernels also share a SIMD with the weight-gradient kernels of the side streams; a
@@ -619,6 +828,10 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
     if (!unit_shape(H, W, 128 * cand, r, n)) continue;
     if ((nb == 1 || pooling) && cand == 4) continue;
     if (pooling && (r % 2 != 0 || (W == 8 && r % 8 != 0))) continue;
+    if (dma) {
+      ma = 2; R = r; nimg = n;
+      break;
+    }
     const int np_ = n * (r + 2) * (W + 2);
     const size_t l = ((size_t)np_ + 9 * 64) * kRow * sizeof(bf16_t);   // patch + the nine taps' weights of a slice
     if (l + 2 * 64 * sizeof(float) > kLdsOfComputeUnit / (cand == 2 ? 2 : 1)) continue;
@@ -633,9 +846,9 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
   // instructions (1024 images, 128 -> 64 on 8x8, alone: 16.65 -> 15.9 us).
   if (plain && ma == 2 && (long)units * ((N + 63) / 64) <= 256) nb = 1;
   const int kTN = 32 * nb, tiles_n = (N + kTN - 1) / kTN;
-  const size_t lds = ((size_t)npatch + 9 * kTN) * kRow * sizeof(bf16_t) + 2 * kTN * sizeof(float);
+  const size_t lds = (dma ? dma_lds(nb) : ((size_t)npatch + 9 * kTN) * kRow * sizeof(bf16_t)) + 2 * kTN * sizeof(float);
   if ((long)units * tiles_n < 32) return false;   // too little work to fill the chip this way: the generic kernels spread it better
-  const bool w8 = W == 8 && R % 8 == 0;
+  const bool w8 = W == 8 && R % (dma ? 4 : 8) == 0;
   const int need = (npatch * OC + kThreads - 1) / kThreads;   // patch pieces per thread
   WideParams p{};
   p.src = src; p.wgt = wgt; p.out = out; p.rows = g.rows; p.H = H; p.W = W; p.Cs = g.Cs; p.N = N;
@@ -685,14 +898,22 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
   }
   p.units = p.ufirst[p.gK]; p.upw = upw;
   auto reciprocal = [](int d) { return (uint32_t)(((1 << 22) + d - 1) / d); };   // (exact: positions and divisors below 2^11)
-  p.by_patch = reciprocal((R + 2) * (W + 2)); p.by_row = reciprocal(W + 2); p.by_r = reciprocal(R);
+  p.by_patch = reciprocal((R + 2) * (W + 2)); p.by_row = reciprocal(W + 2); p.by_rows = reciprocal(R + 2); p.by_r = reciprocal(R);
   p.by_units = by_units;
   while ((1 << p.wlog) < W) ++p.wlog;
   p.gfirst[0] = 0;
   for (int k = 0; k < p.gK; ++k) p.gfirst[k + 1] = p.gfirst[k] + (p.ufirst[k + 1] - p.ufirst[k] + upw - 1) / upw;
   const int groups = p.groups = p.gfirst[p.gK];
   const dim3 grid(((groups + 7) / 8) * 8 * tiles_n);   // whole rounds of 8 groups: see the kernel's index mapping
-  if (nb == 1) {
+  if (dma) {
+    if (nb == 1) {
+      if (w8) launch_plain<2, 0, true, 1>(st, p, grid, lds);
+      else launch_plain<2, 0, false, 1>(st, p, grid, lds);
+    } else {
+      if (w8) launch_wide<2, 0, true>(st, p, grid, lds, bwd, with_stats);
+      else launch_wide<2, 0, false>(st, p, grid, lds, bwd, with_stats);
+    }
+  } else if (nb == 1) {
     if (w8 && need <= 7) launch_plain<2, 7, true, 1>(st, p, grid, lds);
     else if (!w8 && need <= 6) launch_plain<2, 6, false, 1>(st, p, grid, lds);
     else return false;

@@ -148,7 +148,8 @@ struct ConvGeom {
   const uint8_t* mask_bits;   // may be null; with a mask [M][N], N a multiple of 64: the same information at one bit
                               // per element ([M][N/8] bytes, bit e of byte c/8 set where mask[m][c - c%8 + e] > 0).
                               // Kernels that know how read it instead of the mask (a sixteenth of the bytes).
-  int frag;             // 1: the weights are laid out for conv_frag_bf16 (CastEntry), which conv_gemm_bf16 then calls
+  // The weights are laid out in operand order (CastEntry): 1 for conv_frag_bf16, 2 for conv3_wide_bf16, which conv_gemm_bf16 then calls.
+  int frag;
 };
 // True if both the forward and the weight-gradient pass of a first layer with this shape can read a
 // 3-channel source as it is, so that no padded copy of the network input has to be made.
@@ -208,6 +209,8 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
 // 8 elements, output n % 32 and channels 8 * (lane / 32) .. + 7 of the sixteen in lane n % 32 + 32 * ((c % 16) / 8).
 // conv_frag_takes tells which launches it is for.
 bool conv_frag_takes(const ConvGeom& g, int N);
+// ... and which ones conv3_wide_bf16 wants in the same order.
+bool conv3_wide_takes(const ConvGeom& g, int N, bool pooled, bool relu, bool share);
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
                     const bf16_t* addend, BnStatRequest* stats);

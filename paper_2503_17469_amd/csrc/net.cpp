@@ -687,9 +687,29 @@ void step_bf16(StepCtx& c) {
   }
 
   // Which convolutions run in the kernel for few positions, whose weights have a layout of their own
-  auto frag_fwd = [&](const Layer& L) { return L.d.op == OMNI_OP_CONV && omni::conv_frag_takes(fwd_geom(L), L.d.cout) ? 1 : 0; };
+  // (1), and which in the wide kernel with weights in the same order (2).
+  auto next_layer = [&](int i) {
+    int nx = i + 1;
+    while (nx < n_layers - 1 && net->layers[nx].fused_away) ++nx;
+    return nx;
+  };
+  auto reads_next = [&](int i, int op) {   // the next layer that runs is an `op` on layer i's output
+    const int nx = next_layer(i);
+    return nx < n_layers - 1 && net->layers[nx].d.op == op && net->layers[nx].in0 == net->layers[i].out;
+  };
+  auto frag_fwd = [&](const Layer& L) {
+    if (L.d.op != OMNI_OP_CONV) return 0;
+    const omni::ConvGeom g = fwd_geom(L);
+    if (omni::conv_frag_takes(g, L.d.cout)) return 1;
+    const bool pooled = reads_next((int)(&L - net->layers.data()), OMNI_OP_MAXPOOL2);
+    return omni::conv3_wide_takes(g, L.d.cout, pooled, net->tensors[L.out].relu, false) ? 2 : 0;
+  };
   auto frag_dgrad = [&](const Layer& L) {
-    return L.d.op == OMNI_OP_CONV && L.need_dgrad && omni::conv_frag_takes(dgrad_geom(L), L.cin_pad) ? 1 : 0;
+    if (L.d.op != OMNI_OP_CONV || !L.need_dgrad) return 0;
+    const omni::ConvGeom g = dgrad_geom(L);
+    if (omni::conv_frag_takes(g, L.cin_pad)) return 1;
+    const Tensor& ti = net->tensors[L.in0];   // (what others that read it have to add)
+    return omni::conv3_wide_takes(g, L.cin_pad, false, false, ti.relu || ti.consumers > 1) ? 2 : 0;
   };
 
   // The entry of a residual block: its input feeds a 3x3 / stride-2 convolution and the 1x1 / stride-2
@@ -744,8 +764,8 @@ void step_bf16(StepCtx& c) {
       e.cin_real = L.d.op == OMNI_OP_CONV ? L.d.cin : L.cin_pad;
       e.cin_pad = L.cin_pad;
       if (L.d.op == OMNI_OP_CONV) {
-        e.frag_fwd = frag_fwd(L);
-        e.frag_t = L.need_dgrad && (frag_dgrad(L) || s2_frag[&L - net->layers.data()]);
+        e.frag_fwd = frag_fwd(L) != 0;
+        e.frag_t = L.need_dgrad && (frag_dgrad(L) != 0 || s2_frag[&L - net->layers.data()]);
       }
       casts.push_back(e);
     }
@@ -773,14 +793,11 @@ void step_bf16(StepCtx& c) {
       g.frag = frag_fwd(L);
       const Tensor& to = net->tensors[L.out];
       // the next layer that runs, if it pools this layer's output (its only consumer then)
-      int nx = i + 1;
-      while (nx < n_layers - 1 && net->layers[nx].fused_away) ++nx;
-      const bool pool_next = L.d.op == OMNI_OP_CONV && nx < n_layers - 1 &&
-                             net->layers[nx].d.op == OMNI_OP_MAXPOOL2 && net->layers[nx].in0 == L.out;
+      const int nx = next_layer(i);
+      const bool pool_next = L.d.op == OMNI_OP_CONV && reads_next(i, OMNI_OP_MAXPOOL2);
       // ... or normalises it: the convolution is then offered the first pass of the statistics (the sums of
       // what it stores), which the kernels that hold a worker-pure group of positions take
-      const bool bn_next = L.d.op == OMNI_OP_CONV && nx < n_layers - 1 && net->layers[nx].d.op == OMNI_OP_BN &&
-                           net->layers[nx].in0 == L.out && !to.relu && !L.has_b;
+      const bool bn_next = L.d.op == OMNI_OP_CONV && reads_next(i, OMNI_OP_BN) && !to.relu && !L.has_b;
       if (L.d.op == OMNI_OP_LINEAR) {
         omni::linear_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows, L.d.cout, L.d.cin,
                           L.has_b ? c.params + L.b_off : nullptr, to.relu, nullptr, nullptr, c.seg);
