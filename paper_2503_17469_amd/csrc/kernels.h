@@ -236,6 +236,12 @@ bool conv3s2_dgrad_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int 
                         const bf16_t* mask, bool accumulate, const bf16_t* addend, const void* zero,
                         const uint8_t* mask_bits = nullptr);
 // (mask_bits: as ConvGeom::mask_bits.)
+// The same from weights in operand order (dy_sc, if any, with as many channels as dy), with the sums of a batch norm below on request;
+// conv3s2_dgrad_ring_takes tells for which shapes.
+bool conv3s2_dgrad_ring_takes(int rows, int H, int W, int Cin, int Cout, int Cout_sc);
+void conv3s2_dgrad_ring_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cout, const bf16_t* dy_sc, const bf16_t* wt_sc,
+                             bf16_t* dx, int rows, int H, int W, int Cin, const bf16_t* mask, const uint8_t* mask_bits,
+                             bool accumulate, const bf16_t* addend, const void* zero, BnStatRequest* stats);
 // (addend, [M][N] or null, is added to the product before the mask: the input gradient of a layer
 // whose input also feeds a residual add takes the add's share along instead of a separate pass.)
 // Weight gradients (conv_wgrad_bf16.hip).  Per worker k: gw_k[Cout][taps][cin_real] = dy_k^T gather(src)_k, gb_k = column

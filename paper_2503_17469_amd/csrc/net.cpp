@@ -716,7 +716,8 @@ void step_bf16(StepCtx& c) {
   // projection of the shortcut, and nothing else.  The projection comes first in the backward walk: its
   // input gradient is not launched on its own but handed to the 3x3 convolution's, whose kernel writes
   // both contributions in one pass.  partner[m] = the projection layer whose gradient conv m takes along, rides[sc] = m.
-  // s2_frag: the 3x3 convolutions (and their projections) whose input gradient runs in the kernel for few positions.
+  // s2_frag: the 3x3 convolutions (and their projections) whose input gradient takes weights in operand order, in the kernel for few
+  // positions (1) or in the large one (2).
   std::vector<int> partner(n_layers, -1), rides(n_layers, -1);
   std::vector<char> s2_frag(n_layers, 0);
   for (int sc = 0; sc < n_layers; ++sc) {
@@ -736,7 +737,10 @@ void step_bf16(StepCtx& c) {
     const Layer& M = net->layers[m];
     if (M.fused_away || M.d.op != OMNI_OP_CONV || M.d.ksize != 3 || M.d.stride != 2 || M.d.pad != 1 || !M.need_dgrad) continue;
     const int sc = partner[m];
-    s2_frag[m] = omni::conv_frag_s2_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, sc >= 0 ? net->layers[sc].d.cout : 0) ? 1 : 0;
+    const int cout_sc = sc >= 0 ? net->layers[sc].d.cout : 0;
+    s2_frag[m] = omni::conv_frag_s2_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, cout_sc)         ? 1
+                 : omni::conv3s2_dgrad_ring_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, cout_sc) ? 2
+                                                                                                  : 0;
     if (sc >= 0) s2_frag[sc] = s2_frag[m];
   }
 
@@ -980,10 +984,11 @@ void step_bf16(StepCtx& c) {
             offer.x = act(net->layers[bn].in0);
             offer.stats = bn_area + net->layers[bn].stat_off;
           }
-          omni::conv_frag_s2_bf16(st, grad(L.out), shadow + L.wt_off, L.d.cout, sc >= 0 ? grad(net->layers[sc].out) : nullptr,
-                                  sc >= 0 ? shadow + net->layers[sc].wt_off : nullptr, grad(L.in0), rows, L.ih, L.iw, L.cin_pad,
-                                  ti.relu ? act(L.in0) : nullptr, (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr,
-                                  written[L.in0] != 0, addend, conv_counters, bn >= 0 ? &offer : nullptr);
+          const auto kernel = s2_frag[i] == 1 ? omni::conv_frag_s2_bf16 : omni::conv3s2_dgrad_ring_bf16;
+          kernel(st, grad(L.out), shadow + L.wt_off, L.d.cout, sc >= 0 ? grad(net->layers[sc].out) : nullptr,
+                 sc >= 0 ? shadow + net->layers[sc].wt_off : nullptr, grad(L.in0), rows, L.ih, L.iw, L.cin_pad,
+                 ti.relu ? act(L.in0) : nullptr, (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr,
+                 written[L.in0] != 0, addend, conv_counters, bn >= 0 ? &offer : nullptr);
           if (offer.done) { presummed = offer.table; presummed_for = bn; }
           dgrad_done = true;
         } else dgrad_done = omni::conv3s2_dgrad_bf16(
