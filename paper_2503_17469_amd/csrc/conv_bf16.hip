@@ -1054,6 +1054,10 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   bool pooled = false;
   if (g.frag == 1)
     return conv_frag_bf16(st, src, wgt, out, N, g, bias, mask, relu, accumulate, pool_out, pool_code, addend, stats);
+  if (g.frag == 3) {
+    conv_gather_bf16(st, src, wgt, out, N, g, bias, relu, stats);
+    return false;
+  }
   // 3x3 / stride 1 / pad 1: the wide-tile kernel where the shape and the amount of work allow it, else the 256-position one
   if (conv3_wide_bf16(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, addend, pool_out, pool_code, stats))
     return pool_out && pool_code;

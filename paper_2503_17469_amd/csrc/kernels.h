@@ -148,7 +148,8 @@ struct ConvGeom {
   const uint8_t* mask_bits;   // may be null; with a mask [M][N], N a multiple of 64: the same information at one bit
                               // per element ([M][N/8] bytes, bit e of byte c/8 set where mask[m][c - c%8 + e] > 0).
                               // Kernels that know how read it instead of the mask (a sixteenth of the bytes).
-  // The weights are laid out in operand order (CastEntry): 1 for conv_frag_bf16, 2 for conv3_wide_bf16, which conv_gemm_bf16 then calls.
+  // The weights are laid out in operand order (CastEntry): 1 for conv_frag_bf16, 2 for conv3_wide_bf16, 3 for conv_gather_bf16, which
+  // conv_gemm_bf16 then calls.
   int frag;
 };
 // True if both the forward and the weight-gradient pass of a first layer with this shape can read a
@@ -211,6 +212,10 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
 bool conv_frag_takes(const ConvGeom& g, int N);
 // ... and which ones conv3_wide_bf16 wants in the same order.
 bool conv3_wide_takes(const ConvGeom& g, int N, bool pooled, bool relu, bool share);
+// Forward at stride 2, or with one tap (conv_gather_bf16.hip), from weights in operand order.
+bool conv_gather_takes(const ConvGeom& g, int N);
+void conv_gather_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g, const float* bias,
+                      bool relu, BnStatRequest* stats);
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
                     const bf16_t* addend, BnStatRequest* stats);

@@ -687,7 +687,7 @@ void step_bf16(StepCtx& c) {
   }
 
   // Which convolutions run in the kernel for few positions, whose weights have a layout of their own
-  // (1), and which in the wide kernel with weights in the same order (2).
+  // (1), and which in the wide kernel (2) or the gathering one (3) with weights in the same order.
   auto next_layer = [&](int i) {
     int nx = i + 1;
     while (nx < n_layers - 1 && net->layers[nx].fused_away) ++nx;
@@ -702,7 +702,8 @@ void step_bf16(StepCtx& c) {
     const omni::ConvGeom g = fwd_geom(L);
     if (omni::conv_frag_takes(g, L.d.cout)) return 1;
     const bool pooled = reads_next((int)(&L - net->layers.data()), OMNI_OP_MAXPOOL2);
-    return omni::conv3_wide_takes(g, L.d.cout, pooled, net->tensors[L.out].relu, false) ? 2 : 0;
+    if (omni::conv3_wide_takes(g, L.d.cout, pooled, net->tensors[L.out].relu, false)) return 2;
+    return omni::conv_gather_takes(g, L.d.cout) ? 3 : 0;
   };
   auto frag_dgrad = [&](const Layer& L) {
     if (L.d.op != OMNI_OP_CONV || !L.need_dgrad) return 0;
