@@ -20,20 +20,20 @@
 //     issued together when a slice begins and are first needed when it ends, where two barriers separate the last fragment
 //     read from the stores that replace patch and weights;
 //   * the product is formed TRANSPOSED (weights as the left operand): a lane then holds, for one
-//     position, runs of four consecutive channels; one swap of the wavefront's halves per register pair
-//     turns them into runs of eight, and the lane writes 16-byte pieces of the output row itself --
-//     no staging of the output tile through LDS.
+//     position, runs of four consecutive channels; exchanges within the wavefront (lines_device.h) turn that into whole
+//     lines of the output per instruction -- no staging of the output tile through LDS.
 //
-// 2048 images of the ResNet-18 shape, 154.6 GFLOP per launch, each alone, staged through registers and by loads that write LDS:
-// forward with the batch norm's sums 216 -> 187 us at 64 channels (32x32 maps; 706 MB, 3.8 TB/s), 190 -> 154 at 128, 172 -> 136 at
-// 256 (1.14 PFLOP/s, matrix pipe busy 0.63 at the 1.74 GHz that the chip then holds); input gradient with mask, shortcut's gradient
-// and sums 294 -> 261 us (1.2 GB, 4.7 TB/s), 224 -> 188, 199 -> 160.  At 64 channels memory and the epilogue's vector instructions
-// (the sums are in double) bind, at 256 the matrix pipe.  128 images: 22-24 -> 19-21 and 26-29 -> 24-26.5, a third of it the first loads.
+// 2048 images of the ResNet-18 shape, 154.6 GFLOP per launch, each alone, staged through registers / by loads that write LDS / and
+// stored in whole lines: forward with the batch norm's sums 216 / 187 / 175 us at 64 channels (32x32 maps; 706 MB, 4.0 TB/s),
+// 190 / 154 / 151 at 128, 172 / 136 / 138 at 256 (1.1 PFLOP/s, matrix pipe busy 0.66 at the 1.63 GHz that the chip then holds);
+// input gradient with mask, shortcut's gradient and sums 294 / 261 / 248 (1.2 GB, 4.9 TB/s), 224 / 188 / 183, 199 / 160 / 158.
+// At 64 channels memory and vector instructions (the sums are in double) bind, at 256 the matrix pipe.
+// 128 images: 22-24 -> 19-21 and 26-29 -> 24-26.5, a third of it the first loads.
 //
-// 1024 images of three conv layers 3-32-64-128, 32x32: forward 32 -> 64 on 16x16 with pooling 20.3 us (one slice, through registers),
-// 64 -> 128 on 8x8 19.5 -> 17.6, input gradients 64 -> 32 21.7 -> 21.5 and 128 -> 64 18.2 -> 16.0.  Of a workgroup's 30000 cycles
+// 1024 images of three conv layers 3-32-64-128, 32x32: forward 32 -> 64 on 16x16 with pooling 20.6 us (one slice, through registers),
+// 64 -> 128 on 8x8 19.5 -> 17.3, input gradients 64 -> 32 21.7 -> 20.0 and 128 -> 64 18.2 -> 15.5.  Of a workgroup's 30000 cycles
 // in the first, 6000 are the first loads, 4600 per unit the matrix pipe (two workgroups on it) and 5000 the epilogue's vector
-// instructions, two thirds of them pooling; indexes by division were 2600.
+// instructions, half of them pooling; indexes by division were 2600.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,6 +45,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "lds_load_device.h"
+#include "lines_device.h"
 #include "pool_device.h"
 #include "quotient.h"
 
@@ -122,9 +123,10 @@ __device__ inline uint32_t pool_pair(uint32_t a, uint32_t b, uint32_t c, uint32_
   return __builtin_bit_cast(uint32_t, m);
 }
 
-// v of the lane whose number differs in bit 0
+// v of the even (quad_perm [0,0,2,2], 0xA0) or the odd ([1,1,3,3], 0xF5) lane of a pair
+template <int CTRL>
 __device__ inline uint32_t beside(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
 
 // MA: 32-position blocks per wavefront: 4 (a unit of 512 positions, one workgroup per compute unit) or 2 (256
@@ -214,7 +216,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   bf16_t* const wdst = sW + wrow * kRow + woct * 8;
   // ---- fragment addresses: this wavefront's positions wave*128 + a*32 + j
   auto row_order = [](int t) { return (t >> 1) + 4 * (t & 1); };   // t: 0..7
-  int pbase[MA], ipos[MA];
+  int pbase[MA];
   const uint32_t lds0 = lds_address(smemW), zeros = lds0 + kDmaPatch * 64;
   uint32_t xaddr[DMA ? 9 : 1][MA];                        // DMA: where tap t of block a's positions lies in a buffer
   // how the four pieces of a patch position are moved (xor) so that sixteen lanes' reads cover all banks
@@ -225,7 +227,6 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
     if (W8 && !DMA) pos = wave * WPOS + (a >> 1) * 64 + row_order((a & 1) * 4 + (j >> 3)) * 8 + (j & 7);
     // (rows 0 2 1 3: of sixteen lanes the rows are two apart, and the rows of a pooling window are lanes j and j ^ 16)
     if (W8 && DMA) pos = wave * WPOS + a * 32 + ((j & 7) | (j & 8) << 1 | (j & 16) >> 1);
-    ipos[a] = pos;
     const int rr = pos >> p.wlog, w = pos - (rr << p.wlog);
     const int il = (int)(((uint32_t)rr * p.by_r) >> 22), r = rr - il * R;
     pbase[a] = ((il * PR + r) * PW + w) * kRow + h * 8;   // patch origin is (-1, -1): tap (u, v) adds u*PW + v
@@ -239,6 +240,15 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
     }
   }
   const bf16_t* const wfrag = sW + j * kRow + h * 8;
+  // ---- in the epilogue a lane has eight channels at 2 NB positions of every block (lines_device.h): position place(a, r) of the unit
+  constexpr int NR = 2 * NB;
+  int lane_pos = wave * WPOS + (lane & 7), lane_c = lines_channel<NB>(lane);
+  if (NB == 1) lane_pos += (lane >> 3 & 1) * (W8 && DMA ? 16 : W8 ? 32 : 8);
+  const int lane_pooled = POOL ? (lane_pos >> p.wlog >> 1) * (W >> 1) + ((lane_pos & (W - 1)) >> 1) : 0;
+  auto place = [](int a, int r) {
+    const int p3 = r >> 1, p4 = r & 1;   // the bits of the lane that had it
+    return W8 && DMA ? a * 32 + p3 * 16 + p4 * 8 : W8 ? (a >> 1) * 64 + (a & 1) * 16 + p4 * 8 + p3 * 32 : a * 32 + p3 * 8 + p4 * 16;
+  };
 
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
   u32x4 rp[NP > 0 ? NP : 1], rw[ONE ? 1 : RW];
@@ -384,8 +394,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   }
 
   uint32_t to_other = kDmaSlot;   // DMA: from the slot that is read to the other
-  int h8 = h * 8;   // the first channel of this lane's runs of eight
-  double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's sum of a channel of either half tile over the group's units
+  double stat_sum[2] = {0.0, 0.0};   // STATS: this lane's sums of two channels over the group's units
 
   for (int unit = ubeg; unit < uend; ++unit) {
     int n0, r0, nvalid;
@@ -401,32 +410,25 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-    // epilogue operands of the input gradient (mask; addend or the old output), one 16-byte piece per (b, half)
-    // of a block row a, in two sets.  MA = 4: the first set is fetched during the last taps, the others one
-    // block row ahead.  MA = 2 (256 registers per lane): a full set that is live inside the tap loop spills, so
-    // both block rows are fetched when the loop has ended and the other workgroup's matrix instructions cover the
-    // wait; with the mask as bits a set is 18 registers instead of 32 and the first one does travel under the
-    // last taps (except on 8-wide maps, where the seventh patch piece takes the room).
-    u32x4 em[2][BWD && !BITS ? 4 : 1], ea[2][BWD ? 4 : 1];
-    u32x2 eb[2];   // BITS: the mask bits of the tile's 64 channels at this lane's position (byte b*4 + q*2 + h: piece (b, q))
+    // epilogue operands of the input gradient (mask; addend or the old output), one 16-byte piece per position of a block row a,
+    // in two sets.  MA = 4: the first set is fetched during the last taps, the others one block row ahead.  MA = 2 (256
+    // registers per lane): a full set that is live inside the tap loop spills, so both block rows are fetched when the
+    // loop has ended and the other workgroup's matrix instructions cover the wait; with the mask as bits the first one does
+    // travel under the last taps (except on 8-wide maps, where the seventh patch piece takes the room).
+    u32x4 em[2][BWD && !BITS ? NR : 1], ea[2][BWD ? NR : 1];
+    uint8_t eb[2][NR];   // BITS: the mask bits of this lane's channels
+    // element or byte `unit's + lane's` of a tensor with `per` of them per position
+    auto lane_at = [&](int per, int c) { return (uint32_t)(lane_pos * per + c); };
     auto load_epi = [&](int a, int set) {
-      if (BITS) {
-        const bool in = ipos[a] < npos;
-        eb[set] = *reinterpret_cast<const u32x2*>(
-            in ? p.mask_bits + ((size_t)(out_base + ipos[a]) * (p.N >> 3) + (col0 >> 3))
-               : static_cast<const uint8_t*>(p.zero));
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const bool in = lane_pos + place(a, r) < npos && col0 + lane_c < p.N;
+        const size_t unit_at = (size_t)(out_base + place(a, r)) * p.N + col0;
+        if (BITS) eb[set][r] = *(in ? p.mask_bits + (unit_at >> 3) + lane_at(p.N >> 3, lane_c >> 3) : static_cast<const uint8_t*>(p.zero));
+        if (!BITS) em[set][r] = *reinterpret_cast<const u32x4*>((in && p.mask) ? p.mask + unit_at + lane_at(p.N, lane_c) : zp);
+        const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
+        ea[set][r] = *reinterpret_cast<const u32x4*>((in && other) ? other + unit_at + lane_at(p.N, lane_c) : zp);
       }
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const int c = col0 + b * 32 + q * 16 + h8;
-          const bool in = ipos[a] < npos && c < p.N;
-          const size_t idx = (size_t)(out_base + ipos[a]) * p.N + c;
-          if (!BITS) em[set][b * 2 + q] = *reinterpret_cast<const u32x4*>((in && p.mask) ? p.mask + idx : zp);
-          const bf16_t* other = p.addend ? p.addend : (p.accumulate ? p.out : nullptr);
-          ea[set][b * 2 + q] = *reinterpret_cast<const u32x4*>((in && other) ? other + idx : zp);
-        }
     };
 
     if constexpr (DMA) {
@@ -482,7 +484,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
         sixteen(std::integral_constant<uint32_t, 0>{});
         weights_arrived();
         load_weights(last ? 0 : 2 * cs + 2);
-        if (BWD && BITS && !STATS && last) {
+        if (BWD && BITS && last) {
           load_epi(0, 0);
           load_epi(1, 1);
         }
@@ -563,157 +565,136 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
       }
     }
 
-    // ---- epilogue, straight from registers.  Register v of block (a, b) in lane (j, h) is channel
-    // b*32 + 8 (v/4) + 4 h + v%4 of position ipos[a].  Swapping registers v and v + 4 between the
-    // wavefront's halves leaves lane (j, 0) with channels 0-7 (and 16-23), lane (j, 1) with 8-15 (24-31).
-    // POOL: the four positions of a 2 x 2 window are in lanes j, j ^ 1 (columns), j ^ 16 and j ^ 17 (rows; also in the order that
-    // 8-wide maps are taken in).  Each holds all the tile's channels of one position; two exchanges give each a quarter of
-    // the channels of all four: runs of eight (q by the column's lane bit), then blocks b (or, of one block, halves of a run) by the
-    // row's.  Values as stored, none negative.
-    auto pool_block = [&](int a, const u32x4(&v)[STATS || POOL ? 2 * NB : 1]) {
-      if constexpr (POOL) {
-        const bool odd = j & 1;
-        u32x4 even_c[NB], odd_c[NB];                       // of the even and of the odd column
+    // ---- epilogue, straight from registers, in whole lines (lines_device.h).  Register v of block (a, b) in lane (j, h) is channel
+    // b*32 + 8 (v/4) + 4 h + v%4 of the position that lane took; afterwards a lane has channels lane_c .. +7 of positions place(a, r).
+    // POOL: of a 2 x 2 window the rows are a lane's r and r + 1 (their lanes' bit 4, also in the orders that 8-wide maps are taken in),
+    // the columns two neighbouring lanes', of which each does half of the eight channels.  Values as stored, none negative.
+    auto pool_rows = [&](int a, int r, const u32x4& upper, const u32x4& lower) {
+      const bool odd = lane & 1;
+      // of the even and of the odd lane's column, this lane's half of the channels
+      auto left = [&](const u32x4& v, int d) {
+        const uint32_t even = beside<0xA0>(v[2 + d]);      // (all lanes take part)
+        return odd ? even : v[d];
+      };
+      auto right = [&](const u32x4& v, int d) {
+        const uint32_t other = beside<0xF5>(v[d]);
+        return odd ? v[2 + d] : other;
+      };
+      uint32_t m[2], c2[2];
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const uint32_t left = beside(v[2 * b + 1][d]), right = beside(v[2 * b][d]);
-            even_c[b][d] = odd ? left : v[2 * b][d];
-            odd_c[b][d] = odd ? v[2 * b + 1][d] : right;
-          }
-        constexpr int ND = 2 * NB;                         // pairs of channels per lane
-        uint32_t m2[ND], c2[ND];
-#pragma unroll
-        for (int d = 0; d < ND; ++d) {
-          const u32x4 x0 = even_c[0], x1 = odd_c[0], y0 = even_c[NB - 1], y1 = odd_c[NB - 1];
-          const u32x2 s0 = __builtin_amdgcn_permlane16_swap(x0[d], NB == 2 ? y0[d] : x0[(d + 2) & 3], false, false);
-          const u32x2 s1 = __builtin_amdgcn_permlane16_swap(x1[d], NB == 2 ? y1[d] : x1[(d + 2) & 3], false, false);
-          m2[d] = pool_pair(s0[0], s1[0], s0[1], s1[1], c2[d]);
-        }
-        uint32_t code[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) code[b] = __builtin_amdgcn_perm(c2[2 * b + 1], c2[2 * b], 0x06040200u);
-        const int row = (j >> 4) & 1, c = col0 + (odd ? 16 : 0) + h8 + (NB == 2 ? 32 : 4) * row;
-        if (ipos[a] < npos && c < p.N) {
-          const int rr = ipos[a] >> p.wlog, w = ipos[a] - (rr << p.wlog);
-          const size_t at = (size_t)((((long)n0 * H + r0 + rr) >> 1) * (W >> 1) + (w >> 1)) * p.N + c;
-          if constexpr (NB == 2) {
-            *reinterpret_cast<u32x4*>(p.pool + at) = u32x4{m2[0], m2[1], m2[ND - 2], m2[ND - 1]};
-            *reinterpret_cast<u32x2*>(p.pool_code + at) = u32x2{code[0], code[NB - 1]};
-          } else {
-            *reinterpret_cast<u32x2*>(p.pool + at) = u32x2{m2[0], m2[1]};
-            *reinterpret_cast<uint32_t*>(p.pool_code + at) = code[0];
-          }
-        }
+      for (int d = 0; d < 2; ++d) m[d] = pool_pair(left(upper, d), right(upper, d), left(lower, d), right(lower, d), c2[d]);
+      if (lane_pos + place(a, r) < npos && col0 + lane_c < p.N) {
+        // (a pair of rows of 8 or 16 is 4 or 8 pooled positions)
+        const int ahead = W8 ? place(a, r) / 4 : place(a, r) / 32 * 8 + place(a, r) % 32 / 2;
+        const size_t unit_at = ((((size_t)n0 * H + r0) >> 1) * (W >> 1) + ahead) * p.N + col0;
+        const uint32_t lane_to = lane_pooled * p.N + lane_c + (odd ? 4 : 0);
+        *reinterpret_cast<u32x2*>(p.pool + unit_at + lane_to) = u32x2{m[0], m[1]};
+        *reinterpret_cast<uint32_t*>(p.pool_code + unit_at + lane_to) = __builtin_amdgcn_perm(c2[1], c2[0], 0x06040200u);
       }
     };
-    // (64-bit offsets formed from these before the units would be kept in registers all along, and do not fit)
-    if (STATS || POOL) asm("" : "+v"(ipos[0]), "+v"(ipos[1]), "+v"(h8));
-    constexpr bool early = DMA ? BITS && !STATS : BITS && !W8 && !STATS;
+    // (offsets formed from these before the units would be kept in registers all along, and do not fit)
+    if (STATS || POOL) asm("" : "+v"(lane_pos), "+v"(lane_c));
+    constexpr bool early = DMA ? BITS : BITS && !W8 && !STATS;
     if (BWD && MA == 2 && !early) load_epi(0, 0);
     if (BWD && MA == 2 && !(DMA && early)) load_epi(1, 1);
-    u32x4 xs[MA][STATS && BWD ? 4 : 1];   // STATS and BWD: the batch norm's input at this lane's positions
+    u32x4 xs[MA][STATS && BWD ? NR : 1];   // STATS and BWD: the batch norm's input at this lane's positions
     auto load_x = [&](int a) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        xs[a][STATS && BWD ? i : 0] = *reinterpret_cast<const u32x4*>(
-            ipos[a] < npos ? p.stat_x + ((size_t)(out_base + ipos[a]) * p.N + col0 + i * 16 + h8) : zp);
+      for (int r = 0; r < NR; ++r)
+        xs[a][STATS && BWD ? r : 0] = *reinterpret_cast<const u32x4*>(
+            lane_pos + place(a, r) < npos ? p.stat_x + (size_t)(out_base + place(a, r)) * p.N + col0 + lane_at(p.N, lane_c) : zp);
     };
     if (STATS && BWD) load_x(0);
-    // Block row by block row, as the mask and the addend arrive: the four pieces of a position's 128 bytes leave together.  (With
-    // the sums of a piece between its store and the next, lines went to memory in parts: 358 MB written per launch of 268.)
-    u32x4 kept[STATS ? MA : 1][STATS || POOL ? 2 * NB : 1];   // STATS, POOL: what was stored
+    if (STATS && BWD && DMA) load_x(1);
+    u32x4 kept[STATS ? MA : 1][NR];   // what was stored
 #pragma unroll
-    for (int x = 0; x < 2 * NB * MA; ++x) {
-      const int a = x / (2 * NB), bq = x % (2 * NB), b = bq >> 1, q = bq & 1;
-      if (BWD && MA == 4 && bq == 0 && a + 1 < MA) load_epi(a + 1, (a + 1) & 1);
-      if (STATS && BWD && x == 4) {   // (both block rows' at once would spill; with the seventh patch piece of 8-wide maps, either)
+    for (int a = 0; a < MA; ++a) {
+      if (BWD && MA == 4 && a + 1 < MA) load_epi(a + 1, (a + 1) & 1);
+      if (STATS && BWD && !DMA && a == 1) {   // (both block rows' at once would spill; with the seventh patch piece of 8-wide maps, either)
         if (W8) load_x(0);
         load_x(1);
       }
-      float val[8];
+      u32x4(&stored)[NR] = kept[STATS ? a : 0];
+      if constexpr (BWD) {
+        float val[NR][8];
+        lines_of<NB>(acc[a], val);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][b][8 * q + e]),
-                                                          __float_as_uint(acc[a][b][8 * q + 4 + e]), false, false);
-        val[e] = __uint_as_float(sw[0]);
-        val[4 + e] = __uint_as_float(sw[1]);
-      }
-      const int c = col0 + b * 32 + q * 16 + h8;
-      if (POOL || (ipos[a] < npos && (STATS || c < p.N))) {   // N is a multiple of 8 (STATS: of 64): a piece is wholly inside or outside
-        if (AFFINE && p.bias) {
-          const v4f b0 = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h8);
-          const v4f b1 = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h8 + 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            val[e] += b0[e];
-            val[4 + e] += b1[e];
-          }
-        }
-        if (AFFINE && (POOL || p.relu)) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) val[e] = fmaxf(val[e], 0.f);   // (zero for NaN, as val > 0 ? val : 0)
-        }
-        if (BWD) {
-          const u32x4 mk = em[a & 1][BITS ? 0 : b * 2 + q], ad = ea[a & 1][b * 2 + q];
+        for (int r = 0; r < NR; ++r) {
+          const u32x4 mk = em[a & 1][BITS ? 0 : r], ad = ea[a & 1][r];
+          float(&v)[8] = val[r];
           if (p.addend) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+            for (int d = 0; d < 4; ++d) { v[2 * d] += bf16_lo(ad[d]); v[2 * d + 1] += bf16_hi(ad[d]); }
           }
           if (BITS) {
-            const uint32_t byte = eb[a & 1][b] >> (8 * (2 * q + h));
 #pragma unroll
-            for (int e = 0; e < 8; ++e) val[e] = ((byte >> e) & 1u) ? val[e] : 0.f;
+            for (int e = 0; e < 8; ++e) v[e] = ((eb[a & 1][r] >> e) & 1u) ? v[e] : 0.f;
           } else if (p.mask) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-              val[2 * d] = bf16_lo(mk[d]) > 0.f ? val[2 * d] : 0.f;
-              val[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? val[2 * d + 1] : 0.f;
+              v[2 * d] = bf16_lo(mk[d]) > 0.f ? v[2 * d] : 0.f;
+              v[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? v[2 * d + 1] : 0.f;
             }
           }
           if (p.accumulate) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) { val[2 * d] += bf16_lo(ad[d]); val[2 * d + 1] += bf16_hi(ad[d]); }
+            for (int d = 0; d < 4; ++d) { v[2 * d] += bf16_lo(ad[d]); v[2 * d + 1] += bf16_hi(ad[d]); }
           }
-        }
-        u32x4 stored;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(val[2 * d], val[2 * d + 1]);
-        if (!POOL || (ipos[a] < npos && c < p.N))
-          *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + ipos[a]) * p.N + c) = stored;
-        if (STATS || POOL) kept[STATS ? a : 0][STATS || POOL ? bq : 0] = stored;
+          for (int d = 0; d < 4; ++d) stored[r][d] = pack_bf16(v[2 * d], v[2 * d + 1]);
+        }
+      } else {
+        if (AFFINE && p.bias) {
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+              const v4f add = *reinterpret_cast<const v4f*>(sN + b * 32 + o * 8 + h * 4);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[a][b][4 * o + e] += add[e];
+            }
+        }
+        if (AFFINE && (POOL || p.relu)) {
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = fmaxf(acc[a][b][v], 0.f);   // (zero for NaN, as v > 0 ? v : 0)
+        }
+        uint32_t w[NB][8];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int d = 0; d < 8; ++d) w[b][d] = pack_bf16(acc[a][b][2 * d], acc[a][b][2 * d + 1]);
+        lines_of<NB>(w, stored);
       }
+#pragma unroll
+      for (int r = 0; r < NR; ++r)   // N is a multiple of 8 (STATS: of 64): a piece is wholly inside or outside
+        if (lane_pos + place(a, r) < npos && (STATS || col0 + lane_c < p.N))
+          *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + place(a, r)) * p.N + col0 + lane_at(p.N, lane_c)) = stored[r];
       if constexpr (POOL) {
-        if (bq == 2 * NB - 1) pool_block(a, kept[0]);
+#pragma unroll
+        for (int r = 0; r < NR; r += 2) pool_rows(a, r, stored[r], stored[r + 1]);
       }
     }
-    // the sums, a run of channels (b, q) over both block rows at a time: only its 16 are then live
-    if (STATS) {
+    if constexpr (STATS) {
       __builtin_amdgcn_sched_barrier(0);   // (conversions to double drawn up into the loop above would spill)
-      double first = 0.0;
+      double t[2][8];
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq) {
-        const int b = bq >> 1, q = bq & 1;
-        double t[2][8];
+      for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
+      v4f mean[2];
+      if (BWD) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
-#pragma unroll
-        for (int a = 0; a < MA; ++a) {
-          if (ipos[a] >= npos) continue;
-          if (BWD) {
-            v4f mean[2];
-#pragma unroll
-            for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + b * 32 + q * 16 + h8 + 4 * d);
-            bn_sums_add(t, kept[STATS ? a : 0][STATS ? bq : 0], xs[a][STATS && BWD ? bq : 0], mean);
-          } else {
-            bn_sums_add(t, kept[STATS ? a : 0][STATS ? bq : 0]);
-          }
-        }
-        const double sum = bn_sums_tree(t, j);
-        if (q == 0) first = sum;
-        else stat_sum[b] += bn_sums_pair(first, sum, j);
+        for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + lane_c + 4 * d);
       }
+#pragma unroll
+      for (int a = 0; a < MA; ++a)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          if (lane_pos + place(a, r) >= npos) continue;
+          if (BWD) bn_sums_add(t, kept[a][r], xs[a][r], mean);
+          else bn_sums_add(t, kept[a][r]);
+        }
+      lines_sums(t, lane, stat_sum);
     }
   }
   if constexpr (DMA) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may be on its way to LDS when it is used again
@@ -722,7 +703,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
     __syncthreads();
     double* red = reinterpret_cast<double*>(smemW);   // [4][2][64]
 #pragma unroll
-    for (int b = 0; b < 2; ++b) red[(wave * 2 + bn_sums_which(j)) * 64 + b * 32 + bn_sums_channel(j, h)] = stat_sum[b];
+    for (int i = 0; i < 2; ++i) red[(wave * 2 + lines_sum(lane)) * 64 + lines_sum_channel(lane) + i] = stat_sum[i];
     __syncthreads();
     if (tid < 128) {
       const int c = tid & 63, w = tid >> 6;
