@@ -28,6 +28,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "lds_load_device.h"
+#include "lines_device.h"
 #include "quotient.h"
 
 namespace omni {
@@ -462,7 +463,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv3s2_ring_kernel(S2RingParams 
   for (int unit = ubeg; unit < uend; ++unit) {
     int n0, r0, nvalid;
     unit_geom(unit, n0, r0, nvalid);
-    const bool live = qil < nvalid;
     place_reads(read_slot, r0 + R < H);
     v16f acc[4][2];
 #pragma unroll
@@ -513,24 +513,38 @@ __global__ __launch_bounds__(kThreads, 2) void conv3s2_ring_kernel(S2RingParams 
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    // what the epilogue reads: the mask's bits of the tile's 64 channels at this lane's positions (byte b*4 + q*2 + h: piece (b, q)), and
-    // for STATS the batch norm's input, two classes at a time
-    uint32_t pos0 = ((uint32_t)n0 * H + r0) * W + (qil * R + 2 * qi) * W + 2 * qj;   // of class (0, 0)
-    auto pos_of = [&](int a) { return pos0 + (a >> 1) * W + (a & 1); };
-    u32x2 eb[4];
-    u32x4 xs[2][STATS ? 4 : 1];
-    auto load_bits = [&]() {
+    // what the epilogue reads, in whole lines (lines_device.h): a lane has eight channels at four of the half-resolution positions, which
+    // for class a are dx positions pos[r] + (a >> 1) W + (a & 1): the mask's bits, and for STATS the batch norm's input
+    int lane_q = wave * 32 + lines_base<2>(lane);
+    uint32_t pos[4];
+    bool live[4];
+    auto place_results = [&]() {
+      asm volatile("" : "+v"(lane_q));                    // (nothing formed from it before)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        eb[a] = u32x2{~0u, ~0u};
-        if (p.mask_bits && live) eb[a] = *reinterpret_cast<const u32x2*>(p.mask_bits + ((size_t)pos_of(a) * (p.N >> 3) + (col0 >> 3)));
+      for (int r = 0; r < 4; ++r) {
+        const int at = lane_q + lines_position<2>(r), il = at >> (p.w2log + p.r2log);
+        pos[r] = ((uint32_t)n0 * H + r0) * W + (il * R + 2 * ((at >> p.w2log) & (R2 - 1))) * W + 2 * (at & (W2 - 1));
+        live[r] = il < nvalid;
+      }
+    };
+    auto shift_of = [&](int a) { return (a >> 1) * W + (a & 1); };
+    const int lane_c = lines_channel<2>(lane);
+    uint8_t eb[2][4];
+    u32x4 xs[2][STATS ? 4 : 1];
+    auto load_bits = [&](int a) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        eb[a & 1][r] = 255;
+        if (p.mask_bits)
+          eb[a & 1][r] = *(live[r] ? p.mask_bits + ((size_t)(shift_of(a) * (p.N >> 3) + (col0 >> 3)) + pos[r] * (p.N >> 3) + (lane_c >> 3))
+                                   : static_cast<const uint8_t*>(p.zero));
       }
     };
     auto load_x = [&](int a) {
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq)
-        xs[a & 1][STATS ? bq : 0] = *reinterpret_cast<const u32x4*>(
-            live ? p.stat_x + ((size_t)pos_of(a) * p.N + col0 + h * 8 + bq * 16) : static_cast<const bf16_t*>(p.zero));
+      for (int r = 0; r < 4; ++r)
+        xs[a & 1][STATS ? r : 0] = *reinterpret_cast<const u32x4*>(
+            live[r] ? p.stat_x + (size_t)(shift_of(a) * p.N + col0) + (pos[r] * p.N + lane_c) : static_cast<const bf16_t*>(p.zero));
     };
     for (int cs = 0; cs < nslice; ++cs) {
       const bool last = cs + 1 == nslice;
@@ -543,10 +557,6 @@ __global__ __launch_bounds__(kThreads, 2) void conv3s2_ring_kernel(S2RingParams 
       sixteen(std::integral_constant<uint32_t, 0>{});
       weights_arrived();
       load_weights(last ? 0 : 2 * cs + 2);
-      if (last) {
-        asm volatile("" : "+v"(pos0));                    // (nothing formed from it before)
-        load_bits();
-      }
       __builtin_amdgcn_sched_barrier(0);
       sixteen(std::integral_constant<uint32_t, 1>{});
       const uint32_t other_slot = slot - read_slot;
@@ -556,92 +566,75 @@ __global__ __launch_bounds__(kThreads, 2) void conv3s2_ring_kernel(S2RingParams 
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the next unit's first slice, before results are stored
 
-    // ---- epilogue, straight from registers, a class at a time: lane (j, h) holds channels b*32 + q*16 + 8h .. +7 of its position
-    u32x4 kept[2][STATS ? 4 : 1];   // STATS: what was stored
-    auto sums = [&]() {             // ... and the sums of two classes
-      double first = 0.0;
+    // ---- epilogue, straight from registers, a class at a time
+    place_results();
+    load_bits(0);
+    if (STATS) load_x(0);
+    double t[2][8];                 // STATS: this lane's sums of its channels
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq) {
-        double t[2][8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
-        if (live) {
-          v4f mean[2];
-#pragma unroll
-          for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + bq * 16 + h * 8 + 4 * d);
-#pragma unroll
-          for (int a = 0; a < 2; ++a) bn_sums_add(t, kept[a][STATS ? bq : 0], xs[a][STATS ? bq : 0], mean);
-        }
-        const double sum = bn_sums_tree(t, j);
-        if ((bq & 1) == 0) first = sum;
-        else stat_sum[bq >> 1] += bn_sums_pair(first, sum, j);
-        __builtin_amdgcn_sched_barrier(0);                // (the next run's conversions drawn up would spill)
-      }
-    };
+    for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      if (STATS && !(a & 1)) {
-        load_x(a);
-        load_x(a + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const uint32_t row = pos_of(a) * p.N + col0 + h * 8;
       float val[4][8];
+      lines_of<2>(acc[a], val);
+      u32x4 kept[4];
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][bq >> 1][8 * (bq & 1) + e]),
-                                                            __float_as_uint(acc[a][bq >> 1][8 * (bq & 1) + 4 + e]), false, false);
-          val[bq][e] = __uint_as_float(sw[0]);
-          val[bq][4 + e] = __uint_as_float(sw[1]);
-        }
-      if (live) {
-#pragma unroll
-        for (int bq = 0; bq < 4; ++bq) {
-          const int c = bq * 16;
-          if (!STATS && col0 + c + h * 8 >= p.N) continue;
-          float(&v)[8] = val[bq];
-          u32x4 ad = {0u, 0u, 0u, 0u};
-          if (SHARE && (p.addend || p.accumulate)) {
-            ad = *reinterpret_cast<const u32x4*>((p.addend ? p.addend : p.dx) + row + c);
-            if (p.addend) {
-#pragma unroll
-              for (int d = 0; d < 4; ++d) { v[2 * d] += bf16_lo(ad[d]); v[2 * d + 1] += bf16_hi(ad[d]); }
-            }
-          }
-          const uint32_t byte = eb[a][bq >> 1] >> (8 * (2 * (bq & 1) + h));
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = ((byte >> e) & 1u) ? v[e] : 0.f;
-          if (SHARE && !p.mask_bits && p.mask) {
-            const u32x4 mk = *reinterpret_cast<const u32x4*>(p.mask + row + c);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              v[2 * d] = bf16_lo(mk[d]) > 0.f ? v[2 * d] : 0.f;
-              v[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? v[2 * d + 1] : 0.f;
-            }
-          }
-          if (SHARE && p.accumulate) {
+      for (int r = 0; r < 4; ++r) {
+        if (!live[r] || (!STATS && col0 + lane_c >= p.N)) continue;
+        const size_t to = (size_t)(shift_of(a) * p.N + col0) + (pos[r] * p.N + lane_c);
+        float(&v)[8] = val[r];
+        u32x4 ad = {0u, 0u, 0u, 0u};
+        if (SHARE && (p.addend || p.accumulate)) {
+          ad = *reinterpret_cast<const u32x4*>((p.addend ? p.addend : p.dx) + to);
+          if (p.addend) {
 #pragma unroll
             for (int d = 0; d < 4; ++d) { v[2 * d] += bf16_lo(ad[d]); v[2 * d + 1] += bf16_hi(ad[d]); }
           }
-          u32x4 stored;
-#pragma unroll
-          for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(v[2 * d], v[2 * d + 1]);
-          *reinterpret_cast<u32x4*>(p.dx + row + c) = stored;
-          kept[a & 1][STATS ? bq : 0] = stored;
         }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = ((eb[a & 1][r] >> e) & 1u) ? v[e] : 0.f;
+        if (SHARE && !p.mask_bits && p.mask) {
+          const u32x4 mk = *reinterpret_cast<const u32x4*>(p.mask + to);
+#pragma unroll
+          for (int d = 0; d < 4; ++d) {
+            v[2 * d] = bf16_lo(mk[d]) > 0.f ? v[2 * d] : 0.f;
+            v[2 * d + 1] = bf16_hi(mk[d]) > 0.f ? v[2 * d + 1] : 0.f;
+          }
+        }
+        if (SHARE && p.accumulate) {
+#pragma unroll
+          for (int d = 0; d < 4; ++d) { v[2 * d] += bf16_lo(ad[d]); v[2 * d + 1] += bf16_hi(ad[d]); }
+        }
+        u32x4 stored;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(v[2 * d], v[2 * d + 1]);
+        *reinterpret_cast<u32x4*>(p.dx + to) = stored;
+        kept[r] = stored;
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (STATS && (a & 1)) sums();
+      if (a < 3) {                                        // (in the registers that have gone)
+        load_bits(a + 1);
+        if (STATS) load_x(a + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (STATS) {
+        v4f mean[2];
+#pragma unroll
+        for (int d = 0; d < 2; ++d) mean[d] = *reinterpret_cast<const v4f*>(sN + lane_c + 4 * d);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (live[r]) bn_sums_add(t, kept[r], xs[a & 1][r], mean);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if constexpr (STATS) lines_sums(t, lane, stat_sum);
   }
   if (STATS) {
     // the four wavefronts' sums meet in LDS (once nobody reads patch or weights any more), added in wavefront order
     __syncthreads();
     double* red = reinterpret_cast<double*>(smemS);       // [4][2][64]
 #pragma unroll
-    for (int b = 0; b < 2; ++b) red[(wave * 2 + bn_sums_which(j)) * 64 + b * 32 + bn_sums_channel(j, h)] = stat_sum[b];
+    for (int i = 0; i < 2; ++i) red[(wave * 2 + lines_sum(lane)) * 64 + lines_sum_channel(lane) + i] = stat_sum[i];
     __syncthreads();
     if (tid < 128) {
       const int c = tid & 63, w = tid >> 6;

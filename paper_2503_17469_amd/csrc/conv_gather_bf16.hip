@@ -24,6 +24,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "lds_load_device.h"
+#include "lines_device.h"
 #include "quotient.h"
 
 namespace omni {
@@ -200,59 +201,54 @@ __global__ __launch_bounds__(kThreads, 2) void conv_gather_kernel(GatherParams p
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the next two steps, before results are stored
     ready = 2;
 
-    // ---- epilogue, straight from registers: after the swap of the wavefront's halves lane (j, h) holds channels b*32 + q*16 + 8h .. +7
-    // of its position
-    int mlane = m0 + tile * kTM + wp * 128 + j;
+    // ---- epilogue, straight from registers, in whole lines (lines_device.h): a lane has eight channels at four positions of a block
+    int mlane = wp * 128 + lines_base<2>(lane);
     asm volatile("" : "+v"(mlane));                       // (nothing formed from it before)
-    const int c0 = col0 + wc * 64 + h * 8;
+    const int c0 = wc * 64 + lines_channel<2>(lane), m_tile = m0 + tile * kTM, live = mend - m_tile;
     u32x4 kept[STATS ? 4 : 1][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
+      if (!STATS && p.bias) {
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq) {
-        float val[8];
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[a][bq >> 1][8 * (bq & 1) + e]),
-                                                            __float_as_uint(acc[a][bq >> 1][8 * (bq & 1) + 4 + e]), false, false);
-          val[e] = __uint_as_float(sw[0]);
-          val[4 + e] = __uint_as_float(sw[1]);
-        }
-        if (!STATS && p.bias) {
-          const v4f b0 = *reinterpret_cast<const v4f*>(p.bias + c0 + bq * 16), b1 = *reinterpret_cast<const v4f*>(p.bias + c0 + bq * 16 + 4);
+          for (int o = 0; o < 4; ++o) {
+            const v4f add = *reinterpret_cast<const v4f*>(p.bias + col0 + wc * 64 + b * 32 + o * 8 + h * 4);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            val[e] += b0[e];
-            val[4 + e] += b1[e];
+            for (int e = 0; e < 4; ++e) acc[a][b][4 * o + e] += add[e];
           }
-        }
-        if (!STATS && p.relu) {
+      }
+      if (!STATS && p.relu) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) val[e] = fmaxf(val[e], 0.f);   // (zero for NaN, as val > 0 ? val : 0)
-        }
-        u32x4 stored;
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int d = 0; d < 4; ++d) stored[d] = pack_bf16(val[2 * d], val[2 * d + 1]);
-        if (mlane + a * 32 < mend) *reinterpret_cast<u32x4*>(p.out + (size_t)(mlane + a * 32) * p.N + c0 + bq * 16) = stored;
-        kept[STATS ? a : 0][bq] = stored;
+          for (int v = 0; v < 16; ++v) acc[a][b][v] = fmaxf(acc[a][b][v], 0.f);   // (zero for NaN, as v > 0 ? v : 0)
+      }
+      uint32_t w[2][8];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int d = 0; d < 8; ++d) w[b][d] = pack_bf16(acc[a][b][2 * d], acc[a][b][2 * d + 1]);
+      u32x4(&stored)[4] = kept[STATS ? a : 0];
+      lines_of<2>(w, stored);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at = a * 32 + lines_position<2>(r);
+        if (mlane + at < live)
+          *reinterpret_cast<u32x4*>(p.out + (size_t)(m_tile + at) * p.N + col0 + (uint32_t)(mlane * p.N + c0)) = stored[r];
       }
     }
-    if (STATS) {
-      __builtin_amdgcn_sched_barrier(0);
-      double first = 0.0;
+    if constexpr (STATS) {
+      __builtin_amdgcn_sched_barrier(0);                  // (conversions to double drawn up into the loop above would spill)
+      double t[2][8];
 #pragma unroll
-      for (int bq = 0; bq < 4; ++bq) {
-        double t[2][8];
+      for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) t[0][e] = t[1][e] = 0.0;
+      for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-          if (mlane + a * 32 < mend) bn_sums_add(t, kept[STATS ? a : 0][bq]);
-        const double sum = bn_sums_tree(t, j);
-        if ((bq & 1) == 0) first = sum;
-        else stat_sum[bq >> 1] += bn_sums_pair(first, sum, j);
-        __builtin_amdgcn_sched_barrier(0);                // (the next run's conversions drawn up would spill)
-      }
+        for (int r = 0; r < 4; ++r)
+          if (mlane + a * 32 + lines_position<2>(r) < live) bn_sums_add(t, kept[a][r]);
+      lines_sums(t, lane, stat_sum);
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // nothing may be on its way to LDS when the workgroup ends
@@ -260,7 +256,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_gather_kernel(GatherParams p
     // the sums of the two wavefronts that have a channel, in wavefront order
     double* red = reinterpret_cast<double*>(smemG + 3 * kStep);   // [4][2][64]
 #pragma unroll
-    for (int b = 0; b < 2; ++b) red[(wave * 2 + bn_sums_which(j)) * 64 + b * 32 + bn_sums_channel(j, h)] = stat_sum[b];
+    for (int i = 0; i < 2; ++i) red[(wave * 2 + lines_sum(lane)) * 64 + lines_sum_channel(lane) + i] = stat_sum[i];
     __syncthreads();
     const int c = tid & 127, w = tid >> 7, of = c >> 6;
     p.stat_partial[((size_t)group * p.N + col0 + c) * 2 + w] = red[(of * 4 + w) * 64 + (c & 63)] + red[(of * 4 + 2 + w) * 64 + (c & 63)];
