@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict_
 }
 
 // The same with the sums of the records in front, for layers with few records per worker and whole groups of 64
-// channels: grid (total chunks, C/64); every workgroup adds its worker's records for its 64 channels (at most 64 KB,
+// channels: grid (total chunks, C/64); every workgroup adds its worker's records for its 64 channels (64 KB, 128 in small launches,
 // mostly from the L2, while its first positions are on their way), the worker's first chunk leaves the results
 // behind.  A launch of its own for them took 4-5 us of every batch norm, forward and backward: 180 of the 1700 us of a
 // ResNet-18 step at 128 images.
@@ -567,17 +567,23 @@ ShareTable bn_splits(const Segments& seg, int C, int hw, int& per) {
   return tb;
 }
 
-bool few_records(const ShareTable& tb, int K, int C) {
-  if (C % 64 != 0) return false;
-  for (int k = 0; k < K; ++k)
-    if (tb.first[k + 1] - tb.first[k] > kFinishRecords) return false;
-  return true;
-}
 // Chunks of bn_finish_kernel: about 2048 workgroups at most, a trip of 128 positions being the least.
 ShareTable finish_chunks(const Segments& seg, int C, int hw) {
   const long positions = (long)seg.off[seg.K] * hw;
   const long total = std::min<long>((positions + 127) / 128, std::max(1, 2048 / (C / 64)));
   return deal_shares(seg, std::max<long>(seg.K, total));
+}
+
+// Whether bn_finish_kernel takes the records (in `chunks` workgroups per 64 channels): 64 of a worker, or 128 where its workgroups read at most 65,536 in all (64 MB from the
+// L2s).  Step of the ResNet-18 shape, records of 65 to 128 in their own launch / here: one worker, 32 images 998 / 977 us;
+// four, 128 images 1502 / 1479; sixteen, 700 images (2048 workgroups, 90 records each) 4567 / 4580; at most 320 records: 1553
+// with 128 images.
+bool few_records(const ShareTable& tb, const Segments& seg, int C, int hw, ShareTable& chunks) {
+  if (C % 64 != 0) return false;
+  chunks = finish_chunks(seg, C, hw);
+  int most = 0;
+  for (int k = 0; k < seg.K; ++k) most = std::max(most, tb.first[k + 1] - tb.first[k]);
+  return most <= kFinishRecords || (most <= 2 * kFinishRecords && (long)most * chunks.first[seg.K] * (C / 64) <= 65536);
 }
 
 ShareTable bn_chunks(const Segments& seg, int C, int hw) {
@@ -607,10 +613,10 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
   if (!presummed)
     hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, nullptr,
                        nullptr, C, hw, seg, sp, per, partial);
-  if (few_records(sp, seg.K, C)) {
-    const ShareTable ch = finish_chunks(seg, C, hw);
-    hipLaunchKernelGGL(bn_finish_kernel<false>, dim3(ch.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
-                       gamma, beta, nullptr, nullptr, 0, C, hw, seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
+  ShareTable fc;
+  if (few_records(sp, seg, C, hw, fc)) {
+    hipLaunchKernelGGL(bn_finish_kernel<false>, dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
+                       gamma, beta, nullptr, nullptr, 0, C, hw, seg, fc, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
     return;
   }
   hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
@@ -629,10 +635,10 @@ void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t*
   if (!presummed)
     hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, dy, stats, C,
                        hw, seg, sp, per, partial);
-  if (few_records(sp, seg.K, C)) {
-    const ShareTable ch = finish_chunks(seg, C, hw);
-    hipLaunchKernelGGL(bn_finish_kernel<true>, dim3(ch.first[seg.K], groups), dim3(256), 0, st, x, dy, partial, sp,
-                       const_cast<float*>(stats), gamma, nullptr, g_gamma, g_beta, worker_stride, C, hw, seg, ch, 0, dx, nullptr,
+  ShareTable fc;
+  if (few_records(sp, seg, C, hw, fc)) {
+    hipLaunchKernelGGL(bn_finish_kernel<true>, dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, dy, partial, sp,
+                       const_cast<float*>(stats), gamma, nullptr, g_gamma, g_beta, worker_stride, C, hw, seg, fc, 0, dx, nullptr,
                        0, nullptr);
     return;
   }

@@ -122,3 +122,17 @@ def _check_backward(layers, shape, B, bns):
                     assert np.all(err <= bound), (bn, name, k, float((err / bound).max()), float((err > bound).mean()))
     finally:
         run.close()
+
+
+# The largest worker has 66 records (tiles of 64 positions), 84, 128 and 132 (256): summed by the kernel that applies them up to 128.
+RECORDS = [(8, 100), (32, 33), (32, 49), (32, 50)]
+
+
+@pytest.mark.parametrize("hw,B", RECORDS)
+def test_forward_statistics_of_many_records(hw, B):
+    test_forward_statistics_of_channels_far_from_zero(hw, B, 3)
+
+
+@pytest.mark.parametrize("hw,B", RECORDS)
+def test_backward_sums_of_many_records(hw, B):
+    test_backward_sums(hw, B)
