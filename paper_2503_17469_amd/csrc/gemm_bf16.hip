@@ -255,9 +255,10 @@ struct BfWgrad {
 // A workgroup owns a 64 x 64 tile of one layer's weights and walks through all workers' rows, 64 at a time, both operands in
 // LDS as they arrive ([row][column]); where a worker's rows end the tile goes out to G[k], and with UPD (1 SGD, 2 momentum)
 // sum_k lambda_k G[k] of the pieces a thread stores stays in its registers for the update of the tile's parameters at the
-// end.  Bound by the gradient rows it writes (K x 4 bytes per weight): 3072-1024-1024, eight workers, 1024 rows, momentum: 39.4 us
+// end.  APART: a workgroup per tile and worker instead (UPD = 0), see wgrad_workers_apart.  Bound by the gradient rows it writes
+// (K x 4 bytes per weight), with few tiles by the walk: 3072-1024-1024, eight workers, 1024 rows, momentum: 39.4 us
 // for 201 MB, 5.1 TB/s, which is what a large copy reaches.
-template <int UPD>
+template <int UPD, bool APART>
 __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segments seg, Lambdas lam, Optim opt) {
   constexpr bool MOM = UPD == 2;
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][2 * kSlab];
@@ -274,13 +275,16 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
     if (MOM) b.head_vel[j] = ve;
     return;
   }
+  static_assert(!APART || UPD == 0, "the update needs all workers");
+  const int wbeg = APART ? (int)((unsigned)blockIdx.x / (unsigned)b.start[b.n]) : 0, wend = APART ? wbeg + 1 : seg.K;
+  const int bx = (int)blockIdx.x - wbeg * b.start[b.n];
   int ji = 0;
   for (int i = 1; i < b.n; ++i)
-    if ((int)blockIdx.x >= b.start[i]) ji = i;
+    if (bx >= b.start[i]) ji = i;
   const BfWgradJob& J = b.job[ji];
   const int M = J.M, N = J.N;
   const int tiles_n = (N + kTile - 1) / kTile;
-  const int local = (int)blockIdx.x - b.start[ji];
+  const int local = bx - b.start[ji];
   const int tile_m = local / tiles_n, tile_n = local - tile_m * tiles_n;
   const int i0 = tile_m * kTile, j0 = tile_n * kTile;
   const bool want_bias = J.gb != nullptr && tile_n == 0;
@@ -329,8 +333,8 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
   for (int q = 0; q < 4; ++q) gsum[q] = v4f{0.f, 0.f, 0.f, 0.f};
   float bsum = 0.f, bgsum = 0.f;
 
-  int w = 0, k = 0, end = seg.off[1], cur = 0;
-  fetch(0);
+  int w = wbeg, k = APART ? seg.off[wbeg] : 0, end = seg.off[wbeg + 1], cur = 0;
+  fetch(k);
   for (;;) {
     unsigned char* st = lds[cur];
     const int live = min(kRows, end - k);
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
     int w2 = w, k2 = k + kRows, end2 = end;
     if (k2 >= end) {
       ++w2;
-      if (w2 < seg.K) { k2 = seg.off[w2]; end2 = seg.off[w2 + 1]; }
+      if (w2 < wend) { k2 = seg.off[w2]; end2 = seg.off[w2 + 1]; }
     }
     fetch(min(k2, last_row));
     __syncthreads();
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
       bsum = 0.f;
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-      if (w2 >= seg.K) break;
+      if (w2 >= wend) break;
     }
     w = w2; k = k2; end = end2;
     cur ^= 1;
@@ -418,6 +422,16 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
   }
 }
 
+// Whether every worker has workgroups of its own (APART), and the update is a launch of its own behind them: the walk through the
+// workers, a microsecond and more each, against that launch (4 us and the reading of G).  Step in us, together / apart:
+//    24 tiles  2 workers,  200 rows 27.7 / 28.2   4, 480 32.1 / 29.7    16, 600 45.6 / 33.3   32, 3000 94.7 / 50.7
+//    88 tiles  2 workers,  200 rows 30.5 / 30.9   4, 480 35.4 / 33.5    16, 600 50.0 / 40.5   32, 3000 104 / 65.1
+//   160 tiles  4 workers,  480 rows 34.8 / 34.9   8,  64 35.5 / 38.6  8, 1500 57.8 / 46.8   16, 128 47.1 / 45.7   32, 3000 104 / 80.2
+//   512 tiles  8 workers, 1500 rows 70.2 / 76.0  16, 600 58.0 / 79.4
+bool wgrad_workers_apart(long tiles, const Segments& seg) {
+  return tiles <= 96 ? seg.K >= 4 : tiles <= 160 && (seg.K >= 16 || (seg.K >= 8 && seg.off[seg.K] >= 1024));
+}
+
 inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * ((cols + t - 1) / t); }
 
 }  // namespace
@@ -442,12 +456,16 @@ void linear_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* c, in
     hipLaunchKernelGGL((bf16_gemm_kernel<1>), dim3(p.tiles.grid()), dim3(256), 0, st, p);
 }
 
-void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
+bool linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
                        const LinearWgradBf16Job* head, const SgdArgs* sgd, const KernelTimer* timer) {
+  const bool one = n <= kBfJobs;
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += tiles_of(jobs[i].cout, jobs[i].cin, kTile);
+  const bool apart = one && tiles > 0 && wgrad_workers_apart(tiles, seg);
+  if (apart) sgd = nullptr;
   const int upd = sgd ? (sgd->velocity ? 2 : 1) : 0;
   const Lambdas lam = lambdas_of(seg);
   const Optim opt = sgd ? Optim{sgd->lr, sgd->momentum, sgd->weight_decay} : Optim{0.f, 0.f, 0.f};
-  const bool one = n <= kBfJobs;
   if (timer && !one) (void)hipEventRecord(timer->start, st);
   int base = 0;
   do {
@@ -470,19 +488,21 @@ void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, si
       if (sgd->velocity) p.head_vel = sgd->velocity + head->w_off;
       p.head_grad = head->gw;
     }
-    const dim3 grid(p.start[p.n] + (unsigned)((p.head_n + kThreads - 1) / kThreads)), block(kThreads);
-#define OMNI_BF_WGRAD(U)                                                                                            \
+    const dim3 grid(p.start[p.n] * (apart ? seg.K : 1) + (unsigned)((p.head_n + kThreads - 1) / kThreads)), block(kThreads);
+#define OMNI_BF_WGRAD(U, A)                                                                                         \
   if (timer && one)                                                                                                 \
-    hipExtLaunchKernelGGL((bf16_wgrad_kernel<U>), grid, block, 0, st, timer->start, timer->stop, 0, p, seg, lam, opt); \
+    hipExtLaunchKernelGGL((bf16_wgrad_kernel<U, A>), grid, block, 0, st, timer->start, timer->stop, 0, p, seg, lam, opt); \
   else                                                                                                              \
-    hipLaunchKernelGGL((bf16_wgrad_kernel<U>), grid, block, 0, st, p, seg, lam, opt)
-    if (upd == 0) { OMNI_BF_WGRAD(0); }
-    else if (upd == 1) { OMNI_BF_WGRAD(1); }
-    else { OMNI_BF_WGRAD(2); }
+    hipLaunchKernelGGL((bf16_wgrad_kernel<U, A>), grid, block, 0, st, p, seg, lam, opt)
+    if (apart) { OMNI_BF_WGRAD(0, true); }
+    else if (upd == 0) { OMNI_BF_WGRAD(0, false); }
+    else if (upd == 1) { OMNI_BF_WGRAD(1, false); }
+    else { OMNI_BF_WGRAD(2, false); }
 #undef OMNI_BF_WGRAD
     base += kBfJobs;
   } while (base < n);
   if (timer && !one) (void)hipEventRecord(timer->stop, st);
+  return sgd != nullptr;
 }
 
 }  // namespace omni

@@ -192,7 +192,8 @@ struct LinearWgradBf16Job {
   size_t w_off, b_off;   // the layer's weight and bias in the parameter vector
 };
 // As linear_wgrad_f32_batch.
-void linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
+// Returns whether the update has been applied.
+bool linear_wgrad_bf16(hipStream_t st, const LinearWgradBf16Job* jobs, int n, size_t worker_stride, const Segments& seg,
                        const LinearWgradBf16Job* head, const SgdArgs* sgd, const KernelTimer* timer = nullptr);
 size_t conv_wgrad_partial_floats();
 // out[M][N] = gather(src)[M][K] * wgt[N][K]^T (+bias) (ReLU) (masked where mask <= 0) (+= out)

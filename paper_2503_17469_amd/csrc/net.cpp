@@ -505,8 +505,8 @@ struct StepCtx {
   float* loss_per_worker;
   float* loss;
   float lr;
-  bool fuse_update;      // the weight-gradient launch applies the update (convolutional networks: where it can)
-  bool updated;          // convolutional networks: it has
+  bool fuse_update;      // the weight-gradient launch applies the update where it can
+  bool updated;          // it has
 };
 
 // ------------------------------------------------------------------ fp32 path
@@ -592,6 +592,7 @@ void step_f32(StepCtx& c) {
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, first_job_layer, true);
     const omni::SgdArgs sgd{params, net->velocity, c.lr, net->momentum, net->weight_decay};
     const omni::SgdArgs* upd = c.fuse_update ? &sgd : nullptr;
+    c.updated = upd != nullptr;
     if (tiled) {
       omni::linear_wgrad_f32_batch(st, jobs.data() + skip, (int)jobs.size() - skip, net->P_stride, c.seg,
                                    fused_head ? jobs.data() : nullptr, upd, ts.timer());
@@ -1097,9 +1098,10 @@ void step_bf16(StepCtx& c) {
     head.gw = c.G + last.w_off;
     head.gb = last.has_b ? c.G + last.b_off : nullptr;
     head.cin = last.d.cin; head.cout = last.d.cout; head.w_off = last.w_off; head.b_off = last.b_off;
-    omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg,
+    const bool updated = omni::linear_wgrad_bf16(st, linear_jobs.data(), (int)linear_jobs.size(), net->P_stride, c.seg,
                             net->linear_only && c.fuse_update ? &head : nullptr, net->linear_only && c.fuse_update ? &sgd : nullptr,
                             ts.timer());
+    if (net->linear_only) c.updated = updated;
   }
   for (size_t t = 0; t < net->tensors.size(); ++t) {
     const bool have = (written[t] && !not_stored[t]) || (int)t == last.out;
@@ -1220,7 +1222,7 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
 
   // ---- weighted aggregation + update
   float* reduced = (flags & OMNI_STEP_KEEP_REDUCED_GRAD) ? reinterpret_cast<float*>(c.ws + net->reduced_off) : nullptr;
-  if (net->linear_only ? c.fuse_update : c.updated) {
+  if (c.updated) {
   } else if (!(flags & OMNI_STEP_NO_UPDATE)) {
     TimedScope ts(net, c.st, OMNI_KERNEL_UPDATE, -1, true);
     omni::weighted_sgd_f32(c.st, params, c.G, net->P_stride, net->P, c.seg, lr, nullptr, net->velocity,
