@@ -352,7 +352,8 @@ struct SmallWgrad {
   SmallWgradJob job[kSmallJobs];
 };
 // Many rows for few tiles: the rows are cut into shares, each of one worker (worker k has the shares first[k] .. first[k+1]-1
-// of equal length), a workgroup takes one share, and gw and gb point at [share][worker_stride] of scratch.
+// of equal length), a workgroup takes one share, and gw and gb point at [share][worker_stride] of scratch.  Many workers for few tiles:
+// a share is a worker, and gw and gb point at G (wgrad_workers_apart).
 struct SmallShares {
   int32_t first[OMNI_MAX_WORKERS + 1];
 };
@@ -367,7 +368,8 @@ struct WgradChunk {
 // A wavefront (NW = 1, four tiles per workgroup) or the four wavefronts of a workgroup (NW = 4) own a 16 x 16 WB tile of
 // one layer's weights and walk through all workers' rows, 16 rows each at a time; where a worker's rows end, its tile goes
 // out to G[k].  UPD: 0 gradients only, 1 / 2 the SGD / momentum update of the tile's parameters at the end.
-// The workgroup behind the last tile computes the losses.  SHARES: see SmallShares (UPD = 0; split_reduce_kernel follows).
+// The workgroup behind the last tile computes the losses.  SHARES: see SmallShares (UPD = 0; split_reduce_kernel follows,
+// or the update where a share is a worker).
 // The vector cache takes a load instruction of any width every 16 cycles, so with WB = 4 (one 4-byte and one 16-byte load
 // per four matrix instructions, 128 matrix cycles) it stays out of the way; 16 x 16 and 32 x 32 tiles with 4- and 8-byte
 // loads took twice the time.  997-501-243-37 net, 333 rows, 7 workers: 20.2 us with momentum (21.3 with the tables read
@@ -755,6 +757,17 @@ bool wgrad_shares(long tiles, const Segments& seg, size_t scratch_rows, SmallSha
   return false;
 }
 
+// Whether every worker's rows are one share that goes straight to G, and the update is a launch of its own behind it: the walk through
+// the workers, 1.4 us each with the exchange at its end, against that launch (4 us).  Step in us, together / apart:
+//    4 tiles   8 workers,  64 rows 19.5 / 18.8   16, 600 31.2 / 21.3   32, 600 52.9 / 27.4
+//   43 tiles   8 workers,  64 rows 20.6 / 19.4   16, 600 33.8 / 23.4   32, 600 55.5 / 32.5
+//   64 tiles   8 workers,  64 rows 21.2 / 22.6    8, 333 25.4 / 23.3   32, 600 56.9 / 50.5
+//  125 tiles   8 workers, 333 rows 37.4 / 37.8   16, 600 48.7 / 51.0   32, 600 70.6 / 75.8
+// (four workers, 24 tiles: 16.2 / 16.1)
+bool wgrad_workers_apart(long tiles, const Segments& seg) {
+  return seg.K >= 8 && (tiles <= 44 || (tiles <= 64 && (seg.K >= 12 || seg.off[seg.K] >= 256)));
+}
+
 // 16 x 64 tiles of the jobs; narrow: some layer's rows are shorter than a vector, which takes 16 x 16 tiles and no shares
 long wgrad_tiles(const LinearWgradJob* jobs, int n, bool& narrow) {
   long tiles = 0;
@@ -789,7 +802,7 @@ size_t linear_wgrad_f32_share_rows(const LinearWgradJob* jobs, int n, int K_max,
   return narrow || n > kSmallJobs || want < 2 ? 0 : (size_t)(want + K_max - 1);
 }
 
-void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+bool linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                             const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
                             const WgradScratch& scratch) {
   bool narrow;
@@ -803,7 +816,11 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
   const Optim opt = sgd ? Optim{sgd->lr, sgd->momentum, sgd->weight_decay} : Optim{0.f, 0.f, 0.f};
   const bool one = n <= kSmallJobs;
   SmallShares sh{};
-  if (scratch.part && !narrow && one && wgrad_shares(tiles, seg, scratch.rows, sh)) {
+  const bool shares = scratch.part && !narrow && one && wgrad_shares(tiles, seg, scratch.rows, sh);
+  const bool apart = !shares && !narrow && one && wgrad_workers_apart(tiles, seg);
+  if (shares || apart) {
+    if (apart)
+      for (int k = 0; k <= seg.K; ++k) sh.first[k] = k;
     SmallWgrad p{};
     p.n = n;
     p.worker_stride = worker_stride;
@@ -811,8 +828,8 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
       const LinearWgradJob& j = jobs[i];
       SmallWgradJob& q = p.job[i];
       q.dy = j.dy; q.x = j.x; q.M = j.cout; q.N = j.cin;
-      q.gw = scratch.part + j.w_off;
-      q.gb = j.gb ? scratch.part + j.b_off : nullptr;
+      q.gw = apart ? j.gw : scratch.part + j.w_off;
+      q.gb = apart || !j.gb ? j.gb : scratch.part + j.b_off;
       q.tiles_n = (j.cin + TN - 1) / TN;
       p.first[i] = p.tiles;
       p.tiles += (j.cout + 15) / 16 * q.tiles_n;
@@ -821,6 +838,10 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
     if (timer) (void)hipEventRecord(timer->start, st);
     hipLaunchKernelGGL((small_wgrad_kernel<4, 4, 0, true>), dim3(p.tiles * sh.first[seg.K] + (loss ? 1 : 0)), dim3(256), 0, st,
                        p, seg, lam, opt, loss ? *loss : HeadLossParams{}, sh);
+    if (apart) {
+      if (timer) (void)hipEventRecord(timer->stop, st);
+      return false;
+    }
     const dim3 grid((unsigned)((scratch.params + 255) / 256));
 #define OMNI_REDUCE(U)                                                                                                   \
   hipLaunchKernelGGL(split_reduce_kernel<U>, grid, dim3(256), 0, st, scratch.part, scratch.G, worker_stride,             \
@@ -830,7 +851,7 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
     else OMNI_REDUCE(2);
 #undef OMNI_REDUCE
     if (timer) (void)hipEventRecord(timer->stop, st);
-    return;
+    return sgd != nullptr;
   }
   if (timer && !one) (void)hipEventRecord(timer->start, st);
   for (int base = 0; base < n; base += kSmallJobs) {
@@ -859,6 +880,7 @@ void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
     else launch_wgrad<4, 4>(st, p, seg, lam, opt, hl, upd, with_loss, tm);
   }
   if (timer && !one) (void)hipEventRecord(timer->stop, st);
+  return sgd != nullptr;
 }
 
 }  // namespace omni

@@ -98,7 +98,8 @@ struct WgradScratch {
 };
 // The most rows a step of at most K_max workers and B_max rows would use for these jobs (their widths); 0: none.
 size_t linear_wgrad_f32_share_rows(const LinearWgradJob* jobs, int n, int K_max, int B_max);
-void linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
+// Returns whether the update has been applied.
+bool linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                             const HeadLossParams* loss, const SgdArgs* sgd, const KernelTimer* timer,
                             const WgradScratch& scratch);
 

@@ -592,13 +592,13 @@ void step_f32(StepCtx& c) {
     TimedScope ts(net, st, OMNI_KERNEL_LINEAR_WGRAD, first_job_layer, true);
     const omni::SgdArgs sgd{params, net->velocity, c.lr, net->momentum, net->weight_decay};
     const omni::SgdArgs* upd = c.fuse_update ? &sgd : nullptr;
-    c.updated = upd != nullptr;
     if (tiled) {
+      c.updated = upd != nullptr;
       omni::linear_wgrad_f32_batch(st, jobs.data() + skip, (int)jobs.size() - skip, net->P_stride, c.seg,
                                    fused_head ? jobs.data() : nullptr, upd, ts.timer());
     } else {
       const omni::HeadLossParams hl{c.labels, last.d.cout, c.loss_rows, c.loss_per_worker, c.loss, c.status};
-      omni::linear_wgrad_f32_small(st, jobs.data(), (int)jobs.size(), net->P_stride, c.seg, fused_head ? &hl : nullptr,
+      c.updated = omni::linear_wgrad_f32_small(st, jobs.data(), (int)jobs.size(), net->P_stride, c.seg, fused_head ? &hl : nullptr,
                                    upd, ts.timer(),
                                    omni::WgradScratch{net->share_rows ? reinterpret_cast<float*>(c.ws + net->share_off) : nullptr,
                                                       net->share_rows, c.G, net->P});

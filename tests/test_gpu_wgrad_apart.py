@@ -11,6 +11,7 @@ from test_gpu_sum_errors import U, _limit, _run, _wgrad_error
 pytestmark = pytest.mark.gpu
 
 OFF4 = [0, 1, 64, 128, 400]
+OFF8 = [0, 1, 16, 79, 143, 207, 208, 271, 530]
 OFF16 = [0] + [3 + 17 * k for k in range(15)] + [330]
 
 
@@ -20,7 +21,10 @@ OFF16 = [0] + [3 + 17 * k for k in range(15)] + [330]
     ([648, 512, 64, 7], OFF4, "bf16", (16, 17)),            # 88 + 8 tiles: the most
     ([648, 512, 72, 7], OFF4, "bf16", (16, 17)),            # 104: together
     ([1024, 640, 8], OFF16, "bf16", (16, 6)),               # 160 tiles and sixteen workers
-    ([8, 16, 3], OFF4, "bf16", (16, 17)),
+    ([8, 16, 3], OFF8, "bf16", (16, 17)),
+    ([64, 128, 10], OFF8, "f32", (16, 5, 4)),
+    ([64, 128, 10], OFF8[:8], "f32", (16, 5, 4)),           # seven workers: together
+    ([130, 67, 33, 10], OFF16, "f32", (16, 5, 4)),
 ])
 def test_gradients(dims, off, dtype, chains):
     layers = _run(dims, off, dtype)
@@ -29,7 +33,7 @@ def test_gradients(dims, off, dtype, chains):
         assert err <= _limit(*chains), (err / U, _limit(*chains) / U)
 
 
-@pytest.mark.parametrize("dims,off,dtype", [([216, 160, 232, 10], OFF4, "bf16")])
+@pytest.mark.parametrize("dims,off,dtype", [([216, 160, 232, 10], OFF4, "bf16"), ([64, 128, 10], OFF8, "f32")])
 @pytest.mark.parametrize("momentum", [False, True])
 def test_update_of_all_parameters(dims, off, dtype, momentum):
     """theta' and the velocity from the gradients the step left, in float64: fp32 sums of at most eight terms, 1e-6; and twice
