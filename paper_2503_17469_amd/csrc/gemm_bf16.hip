@@ -425,11 +425,14 @@ __global__ __launch_bounds__(kThreads, 4) void bf16_wgrad_kernel(BfWgrad b, Segm
 // Whether every worker has workgroups of its own (APART), and the update is a launch of its own behind them: the walk through the
 // workers, a microsecond and more each, against that launch (4 us and the reading of G).  Step in us, together / apart:
 //    24 tiles  2 workers,  200 rows 27.7 / 28.2   4, 480 32.1 / 29.7    16, 600 45.6 / 33.3   32, 3000 94.7 / 50.7
+//    51 tiles  4 workers,  170 rows 42.0 / 43.1
 //    88 tiles  2 workers,  200 rows 30.5 / 30.9   4, 480 35.4 / 33.5    16, 600 50.0 / 40.5   32, 3000 104 / 65.1
 //   160 tiles  4 workers,  480 rows 34.8 / 34.9   8,  64 35.5 / 38.6  8, 1500 57.8 / 46.8   16, 128 47.1 / 45.7   32, 3000 104 / 80.2
 //   512 tiles  8 workers, 1500 rows 70.2 / 76.0  16, 600 58.0 / 79.4
 bool wgrad_workers_apart(long tiles, const Segments& seg) {
-  return tiles <= 96 ? seg.K >= 4 : tiles <= 160 && (seg.K >= 16 || (seg.K >= 8 && seg.off[seg.K] >= 1024));
+  const int rows = seg.off[seg.K];
+  if (tiles <= 96) return seg.K >= 5 || (seg.K == 4 && (tiles <= 24 || rows >= 400));
+  return tiles <= 160 && (seg.K >= 16 || (seg.K >= 8 && rows >= 1024));
 }
 
 inline int tiles_of(int rows, int cols, int t) { return ((rows + t - 1) / t) * ((cols + t - 1) / t); }

@@ -761,11 +761,11 @@ bool wgrad_shares(long tiles, const Segments& seg, size_t scratch_rows, SmallSha
 // the workers, 1.4 us each with the exchange at its end, against that launch (4 us).  Step in us, together / apart:
 //    4 tiles   8 workers,  64 rows 19.5 / 18.8   16, 600 31.2 / 21.3   32, 600 52.9 / 27.4
 //   43 tiles   8 workers,  64 rows 20.6 / 19.4   16, 600 33.8 / 23.4   32, 600 55.5 / 32.5
-//   64 tiles   8 workers,  64 rows 21.2 / 22.6    8, 333 25.4 / 23.3   32, 600 56.9 / 50.5
+//   64 tiles   8 workers,  64 rows 21.2 / 22.6    8, 333 25.4 / 23.3   12,  39 31.5 / 32.7   16, 128 34.4 / 30.3   32, 600 56.9 / 50.5
 //  125 tiles   8 workers, 333 rows 37.4 / 37.8   16, 600 48.7 / 51.0   32, 600 70.6 / 75.8
 // (four workers, 24 tiles: 16.2 / 16.1)
 bool wgrad_workers_apart(long tiles, const Segments& seg) {
-  return seg.K >= 8 && (tiles <= 44 || (tiles <= 64 && (seg.K >= 12 || seg.off[seg.K] >= 256)));
+  return seg.K >= 8 && (tiles <= 44 || (tiles <= 64 && (seg.K >= 16 || seg.off[seg.K] >= 256)));
 }
 
 // 16 x 64 tiles of the jobs; narrow: some layer's rows are shorter than a vector, which takes 16 x 16 tiles and no shares
