@@ -295,8 +295,8 @@ __device__ __forceinline__ void wgrad_general_reduce(const WgradParams& p, const
 
 
 // ------------------------------------------------------------------ kernel C
-// Weight gradient of 3x3, stride-1, pad-1 convolutions on maps that the ring form does not take (64 and 128 wide, or of
-// so few positions that a step of it would hold parts of images).
+// Weight gradient of 3x3, stride-1, pad-1 convolutions on maps that the ring form does not take: 64 and 128 wide (narrower ones where
+// units of a great many rows have no reciprocal).
 // Kernel B treats the nine filter taps as nine independent column blocks: the
 // input is fetched and transposed nine times and dY once per column tile, and at
 // 64 channels that memory traffic, not the matrix pipe, sets the pace.  Here a
@@ -381,24 +381,23 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
   }
   const bool a_chan_ok = co0 + 8 * a_oct < p.Cout;
   unsigned char* a_dst = sA + (8 * a_oct) * kSA + row_skew(8 * a_oct) + 8 * (tid >> 3);
-  // X: channel octets x (W/4 groups of 4 columns) x patch rows
+  // X: channel octets x (W/4 groups of 4 columns) x patch rows: at most two tasks a thread, three on 128-wide maps (a row of one
+  // image and its neighbours) and for one row of 64
   const int wq = W >> 2;
   const int ntasks = p.prows * wq * 8;
-  int x_rel[2], x_il[2], x_rr[2], x_dst[2];
-  bool x_task[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int x = tid + t * kThreads;
-    x_task[t] = x < ntasks;
-    const int xx = x_task[t] ? x : 0;
-    const int oct = xx & 7, g = xx >> 3;
+  struct Task {
+    int rel, il, rr, dst;
+    bool here;
+  };
+  auto task_at = [&](int x) {
+    const bool in = x < ntasks;
+    const int oct = in ? x & 7 : 0, g = in ? x >> 3 : 0;
     const int pr = g / wq, wg = g - pr * wq;
-    x_il[t] = (int)(((uint32_t)pr * p.by_patch) >> 16);
-    x_rr[t] = pr - x_il[t] * (R + 2);                       // input row = first row + x_rr - 1
-    x_rel[t] = ((x_il[t] * H + x_rr[t] - 1) * W + 4 * wg) * p.Cin + 8 * oct;
-    x_dst[t] = (8 * oct) * p.SX + row_skew(8 * oct) + (pr * p.Wp + 4 * wg + 8) * 2;
-    x_task[t] = x_task[t] && ci0 + 8 * oct < p.Cin;   // false: no such piece, or a channel octet past the end
-  }
+    const int il = (int)(((uint32_t)pr * p.by_patch) >> 16), rr = pr - il * (R + 2);   // input row = first row + rr - 1
+    return Task{((il * H + rr - 1) * W + 4 * wg) * p.Cin + 8 * oct, il, rr, (8 * oct) * p.SX + row_skew(8 * oct) + (pr * p.Wp + 4 * wg + 8) * 2,
+                in && ci0 + 8 * oct < p.Cin};   // false: no such piece, or a channel octet past the end
+  };
+  const Task task[2] = {task_at(tid), task_at(tid + kThreads)};
 
   u32x4 ra[4], rx[2][4];
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
@@ -409,11 +408,20 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
     img_at = ck.beg + (p.nimg == 1 ? img : ubeg << p.nimg_log);
     row_at = p.nimg == 1 ? (ubeg - img * upi) * R : 0;
   }
+  // Loads never branch (a guarded load makes the compiler wait for each group before the
+  // next): an absent piece is read from a page of zeros.
+  auto images = [&]() { return p.nimg == 1 ? 1 : min(p.nimg, ck.end - img_at); };
+  auto load_task = [&](const Task& t, u32x4 (&to)[4]) {
+    const int row = row_at + t.rr - 1;
+    const bool in = t.here && t.il < images() && row >= 0 && row < H;
+    const bf16_t* src = in ? p.src + (((long)img_at * H + row_at) * W * p.Cin + t.rel + ci0) : zp;
+    const int st = in ? p.Cin : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) to[q] = *reinterpret_cast<const u32x4*>(src + q * st);
+  };
   auto load_unit = [&]() {
-    const int n0 = img_at, r0 = row_at, nvalid = p.nimg == 1 ? 1 : min(p.nimg, ck.end - n0);
-    const long base_pos = ((long)n0 * H + r0) * W;
-    // Loads never branch (a guarded load makes the compiler wait for each group before the
-    // next): an absent piece is read from a page of zeros.
+    const int nvalid = images();
+    const long base_pos = ((long)img_at * H + row_at) * W;
     {
       const bool in = a_chan_ok && a_il < nvalid;
       const bf16_t* src = in ? p.dy + ((base_pos + a_rel) * p.Cout + co0 + 8 * a_oct) : zp;
@@ -422,14 +430,7 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
       for (int q = 0; q < 4; ++q) ra[q] = *reinterpret_cast<const u32x4*>(src + q * st);
     }
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int row = r0 + x_rr[t] - 1;
-      const bool in = x_task[t] && x_il[t] < nvalid && row >= 0 && row < H;
-      const bf16_t* src = in ? p.src + (base_pos * p.Cin + x_rel[t] + ci0) : zp;
-      const int st = in ? p.Cin : 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) rx[t][q] = *reinterpret_cast<const u32x4*>(src + q * st);
-    }
+    for (int t = 0; t < 2; ++t) load_task(task[t], rx[t]);
   };
   auto next_unit = [&]() {
     row_at += R;
@@ -442,7 +443,14 @@ __device__ __forceinline__ void wgrad3_body(const Wgrad3Params& p, const Chunk& 
     if (a_chan_ok) transpose_store(ra, a_dst, kSA);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-      if (x_task[t]) transpose_store(rx[t], sX + x_dst[t], p.SX);   // (else no such patch piece, or channels that stay zero)
+      if (task[t].here) transpose_store(rx[t], sX + task[t].dst, p.SX);   // (else no such patch piece, or channels that stay zero)
+    // the third task, whose pieces no registers are left for while the unit before is multiplied.  (128 images of 64 channels on 128x128,
+    // whole step: 3.13 ms, 3.15 with registers for it, of which eleven spill, and 4.10 in kernel B.)
+    if (ntasks > 2 * kThreads) {
+      const Task third = task_at(tid + 2 * kThreads);
+      load_task(third, rx[0]);
+      if (third.here) transpose_store(rx[0], sX + third.dst, p.SX);
+    }
   };
   load_unit();   // (every chunk has a unit)
 
