@@ -1175,8 +1175,8 @@ __device__ __forceinline__ void wgrad1_update(const Wgrad1Params& p, const Batch
   }
 }
 
-// Workgroups below rest.first[0]: the table's layers, tiles x slots each; then the rest, an element per thread.  A wavefront per
-// worker up to sixteen: with four wavefronts they took turns, a round trip to memory each.
+// Workgroups below rest.first[0]: the table's layers, tiles x slots each; then the rest, an element per thread.  The wavefronts take
+// the workers in turn, a round trip to memory each (update_wavefronts).
 // Measured, 3-32-64-128: 1024 images, eight workers, 20.3 us with a register per workgroup, 256 bytes a load and twice the partial
 // tiles; 17.0 with half the tiles, 13.6 with four registers and eight wavefronts.  128 images, four workers, 10.6 -> 9.7.
 template <bool MOM, int NW>
@@ -1508,6 +1508,24 @@ bool update_too_long(const BatchTable& tab, int K) {
   return std::max(0.5 * most / 16, tiles) > std::max(0.5 * most / 32, tiles) + 5;
 }
 
+// Wavefronts of a workgroup of the second stage with the update.  A compute unit holds sixteen of them (100 registers) however they are
+// grouped.  More per workgroup mean fewer turns at the workers, but a barrier at which all wait for the slowest, and registers held
+// by those that have no worker left and no part in the update: sixteen only where all of the launch (an element per thread of the other
+// parameters included) is resident at once, eight while the workgroups that add chunks are.  Step in us with 4 / 8 / 16, by those
+// workgroups and by workers (images of each in brackets):
+//    145 (3-32-64-128, 16x16)   14 (2) 68.7 / 67.1 / 66.2
+//    145 (3-16-96-128, 16x16)   48 (5) 111.3 / 105.0 / 109.9
+//    306 (3-32-128-64)          48 (2) 95.2 / 88.7 / 92.3
+//    451 (3-32-64-128)           8 (128) 179.7 / 175.9 / 180.9   16 (40) 143.0 / 137.9 / 140.8   64 (8) 147.5 / 139.6 / 142.2
+//    725 (3-32-128-64, 16x16)   12 (13) 76.4 / 79.0 / 81.1
+//    886 (3-32-128-128)          5 (40) 100.5 / 103.6 / 108.5    16 (8) 88.1 / 91.3 / 94.6       64 (8) 186.2 / 175.6 / 175.0
+//   1595 (3-16-128-256, 16x16)   9 (40) 113.4 / 115.8 / 121.8    32 (8) 117.7 / 117.0 / 119.6    64 (8) 163.0 / 151.7 / 152.3
+// Of 248 such networks 0.1 per cent slower on average than with the best of the three, 2.4 at most.
+int update_wavefronts(int K, int workgroups, long others) {
+  if (K <= 4 || (K <= 32 && workgroups > 512)) return 4;
+  return K > 8 && workgroups + (others + 1023) / 1024 <= 256 ? 16 : 8;
+}
+
 // The second stage of all layers of a call and the update of all `params` parameters; false, with nothing launched, where some layer
 // has another second stage, or the walk in this one is long, or none has any.
 bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, const Segments& seg, const SgdArgs& sgd, float* G,
@@ -1528,8 +1546,10 @@ bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, con
     tab.first[i] = blocks;
     blocks += job.tiles * (first ? job.slots : kUpdateSlots3);
   }
-  const int threads = seg.K <= 4 ? 256 : seg.K <= 8 ? 512 : 1024;
   std::sort(covered, covered + m, [](const Range& a, const Range& b) { return a.beg < b.beg; });
+  long others = (long)params;
+  for (int i = 0; i < m; ++i) others -= covered[i].end - covered[i].beg;
+  const int threads = 64 * update_wavefronts(seg.K, blocks, others);
   RestTable rest{};
   rest.first[0] = blocks;
   long at = 0;

@@ -54,6 +54,21 @@ def test_update_with_the_second_stage(hw, chans, off, momentum):
     _same_as_own_launch(synth.cnn3(num_classes=10, hw=hw, chans=chans), (hw, hw, chans[0]), off, momentum)
 
 
+# Workgroups of four wavefronts with more workers than that (1595 workgroups add chunks: more than 512) and of sixteen (145, and 30 for
+# the other parameters: all resident at once), with one worker in the last turn and with full turns; eight: above.
+@pytest.mark.parametrize("chans,off", [
+    ((3, 16, 128, 256), [0, 1, 3, 7, 33, 57, 58, 60, 90, 100]),
+    ((3, 16, 128, 256), list(range(32)) + [400]),
+    ((3, 16, 128, 256), list(range(33)) + [400]),      # (one worker too many: eight)
+    ((3, 32, 32, 64), list(range(0, 20, 2))),
+    ((3, 32, 32, 64), list(range(0, 34, 2))),
+    ((3, 32, 32, 64), [0, 1] + list(range(3, 35, 2))),
+])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_update_with_few_and_many_wavefronts(chans, off, momentum):
+    _same_as_own_launch(synth.cnn3(num_classes=10, hw=16, chans=chans), (16, 16, 3), off, momentum)
+
+
 @pytest.mark.parametrize("net", list(NETS))
 @pytest.mark.parametrize("off", [[0, 1, 150, 203], [0, 2, 4, 6]])
 @pytest.mark.parametrize("momentum", [False, True])
