@@ -1219,7 +1219,8 @@ struct Plan {
   long min_upc, upc_step;   // units per chunk: at least, and a multiple of
   int alone;                // workgroups aimed at where the layer has a launch to itself
   size_t slot_floats, lds;
-  double work;              // microseconds of one workgroup walking all of it, at two workgroups per compute unit
+  double work;              // microseconds of one workgroup walking all of it, at two workgroups per compute unit (see plan_patch)
+  double ring_work;         // ... in a launch of layers of the ring form alone
 };
 
 void count_units(Plan& pl, const Segments& seg, int per_image, int images_per_unit) {
@@ -1303,7 +1304,12 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   // At least two units a chunk (128 images of 3-32-64-128: step 77.9 us with four, 76.6 with two)
   pl.min_upc = 2; pl.upc_step = 1; pl.alone = 256;
   pl.slot_floats = kTile3Stride;
-  pl.work = (ring ? (narrow ? 1.3 : 2.6) : 4.5) * pl.job.tiles * pl.total_units;
+  // The ring form's units take 2.6 us (narrow: 1.3).  Beside layers of other forms it has the share of a launch that kernel C's 4.5
+  // (3.0; 6.0 on 4-wide maps) would give: with its own its chains were up to twice as long, and a gradient's error up to 1.17 times
+  // that of kernel C (256 channels on 8x8, 1024 images, eight workers: 5.9e-7 and 5.1e-7).  It costs the step of the ResNet-18 shape 0 to 1.5
+  // per cent (256 images 2190 us and 2223, 128, 512, 1024 and 2048 the same).
+  pl.work = (w4 ? 6.0 : narrow ? 3.0 : 4.5) * pl.job.tiles * pl.total_units;
+  pl.ring_work = (narrow ? 1.3 : 2.6) * pl.job.tiles * pl.total_units;
   return true;
 }
 
@@ -1420,8 +1426,13 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
     if (!plan_patch(pl, jobs[i], worker_stride, seg) && !plan_stride2(pl, jobs[i], worker_stride, seg))
       plan_general(pl, jobs[i], worker_stride, seg);
     bp.ring8 = bp.ring8 && pl.job.kind >= kPatch4 && pl.job.kind <= kPatch32Narrow && pl.job.kind != kPatchAny;
-    work += pl.work;
     ++heavy;
+  }
+  for (int i = 0; i < m; ++i) {
+    Plan& pl = bp.plans[i];
+    if (pl.job.kind == kFirst) continue;
+    if (bp.ring8) pl.work = pl.ring_work;
+    work += pl.work;
   }
   // Layers that share the launch share its workgroups in proportion to the time their units take (not
   // to their arithmetic: a 1x1 projection cut for its few multiply-adds walked 100 slabs, 200 us).

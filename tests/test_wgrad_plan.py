@@ -81,3 +81,19 @@ def test_every_layer_is_in_one_launch_that_knows_its_kind(shim, layers, off, wor
     for base in range(0, n, 6):
         spans = sorted(r[4:6] for r in rows[base:base + 6] if r[3])
         assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+
+
+@pytest.mark.parametrize("layers,at_least", [
+    ([(8, 256, 256, 1), (16, 128, 256, 2)], 384),
+    ([(16, 128, 128, 1), (32, 64, 128, 2)], 416),
+    ([(4, 512, 512, 1), (8, 256, 512, 2)], 512),
+    ([(16, 32, 64, 1), (32, 64, 128, 2)], 128),
+])
+def test_chains_of_stride_1_layers_beside_others(shim, layers, at_least):
+    """1024 images of eight workers in 768 workgroups: the sums of a 3x3 / stride-1 layer beside a stride-2 one run through chains no
+    longer than the workgroups that kernel C had would make them (fewer workgroups are longer chains, and larger errors)."""
+    flat = (ctypes.c_int * 8)(*[v for L in layers for v in L])
+    offs = (ctypes.c_int * 9)(*range(0, 1025, 128))
+    out = (ctypes.c_long * 12)()
+    shim.describe(flat, 2, offs, 8, 768, out)
+    assert out[1] == out[7] and out[2] >= at_least
