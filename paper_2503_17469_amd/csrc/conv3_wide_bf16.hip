@@ -60,10 +60,10 @@ constexpr int kThreads = 256;
 
 struct WideParams {
   const bf16_t* src;   // [rows][H][W][Cs]
-  const bf16_t* wgt;   // [N][9][Cs]
+  const bf16_t* wgt;   // [N][9][Cs]; staged by loads that write LDS: in operand order, blocks [N/32][9][Cs/16]
   bf16_t* out;         // [rows*H*W][N]
   int rows, H, W, Cs, N;
-  int R, nimg;         // a unit is nimg images x R rows; nimg * R * W = 512
+  int R, nimg;         // a unit is nimg images x R rows; nimg * R * W = 128 MA
   int units, upw;      // units in all, units per workgroup
   int groups;          // of upw units (see below)
   int flip;            // 1: dgrad (mirrored taps)

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv3s2_dgrad_kernel(S2Params p) 
       slice(s + 1, std::integral_constant<int, 1>{});
     }
 
-    // ---- epilogue, straight from registers : after the swap of the wavefront's halves
+    // ---- epilogue, straight from registers: after the swap of the wavefront's halves
     // lane (j, h) holds channels b*32 + q*16 + 8h .. +7 of its position of class a
     u32x4 em[2][4], ea[2][4];   // mask and addend / old dx of class a: fetched one class ahead
     u32x2 eb[2];                // the mask as bits: the 8 bytes of the tile's 64 channels at this lane's position

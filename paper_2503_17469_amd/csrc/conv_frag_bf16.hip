@@ -652,12 +652,13 @@ void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
 
 }  // namespace
 
-// Up to two workgroups per compute unit this kernel wins everywhere (1.1-5.5x over 16-512 images of the ResNet-18 and
-// three-layer shapes); beyond, its larger share of start-up and epilogue per tile tells, the sooner the shorter
-// the reduction.  Its rivals are weak at stride 2 (general kernel) and on 4-wide maps (units of 512 positions), and a
-// reduction of 2304 still breaks even at four workgroups per compute unit (8x8x256: 22.8 us against 23.9); with 4608
-// on 4-wide maps it stays ahead (2048 images, 154.6 GFLOP: 147 us with the batch norm's sums, 1.05 PFLOP/s, against 151 without
-// them and 11 for a pass of their own).
+// Up to two workgroups per compute unit this kernel wins everywhere; beyond, its larger share of start-up and epilogue per tile
+// tells, the sooner the shorter the reduction.  Its rivals are weak at stride 2 (the general kernel: conv_gather_bf16 begins at twice
+// these limits) and on 4-wide maps (units of 512 positions), and a reduction of 2304 is ahead up to four workgroups per compute unit.  The
+// wide kernel staged by loads that write LDS / this one, forward with the sums, us: 32x32x64 14.2 / 12.3 at 512 tiles, 14.5 / 16.7 at 768;
+// 16x16x128 16.8 / 14.2, 17.4 / 19.3; 8x8x256 23.8 / 18.4, 24.6 / 24.8, 33.6 / 30.5 at 1024, 35.2 / 41.2 at 1536; input gradient 16.9 / 13.5,
+// 17.8 / 18.9; 21.0 / 15.5, 21.4 / 21.6; 26.9 / 21.2, 28.0 / 27.2, 35.9 / 33.0, 38.4 / 45.1.  With 4608 on 4-wide maps it stays ahead (2048
+// images, 154.6 GFLOP: 147 us with the batch norm's sums, 1.05 PFLOP/s, against 151 without them and 11 for a pass of their own).
 bool conv_frag_takes(const ConvGeom& g, int N) {
   FragShape s;
   if (!frag_shape(g, N, s)) return false;
@@ -709,15 +710,17 @@ static bool frag_s2_shape(int rows, int H, int W, int N, int Cs, ConvGeom& g, Fr
   return s.lds <= kLdsOfComputeUnit;
 }
 
-// Up to two workgroups per compute unit and class: whole steps of the ResNet-18 shape at 128, 200 and 256 images are 2.5, 2.2 and
-// 1.6 per cent shorter with it; from 384 images on (768 tiles at the second entry) there is no difference, at 1024 the
-// large kernel is ahead by 1.4 per cent.
+// Up to two workgroups per compute unit over the four classes; up to two per class where its rival is not the kernel that is staged by loads
+// that write LDS.  That one / this one, with the projection and the sums, us: 32x32 from 64 to 128 channels 18.9 / 16.1 at 128 tiles, 19.0 / 22.6
+// at 192, 21.9 / 31.0 at 512; 16x16 from 128 to 256 22.6 / 17.1, 23.3 / 26.2, 31.7 / 43.4; 8x8 from 256 to 512 31.0 / 27.9, 31.3 / 30.9, 46.3 /
+// 62.7.  Step of the ResNet-18 shape with the line at 128 tiles and at 512: 96 images 1272 / 1288 us, 128 1473 / 1498, 256 2235 / 2249, 384
+// 2882 / 2934.  (Against the kernel staged through registers 512 was the line: steps of 128 to 256 images 2.5 to 1.6 per cent shorter.)
 bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2) {
   ConvGeom g;
   FragShape s;
   if ((Cs2 != 0 && Cs2 != Cs) || !frag_s2_shape(rows, H, W, N, Cs, g, s)) return false;
   const long tiles = (s.upi == 1 ? (rows + s.nimg - 1) / s.nimg : (long)rows * s.upi) * ((N + kTN - 1) / kTN);
-  return tiles <= 512;
+  return tiles <= (conv3s2_dgrad_ring_takes(rows, H, W, N, Cs, Cs2) ? 128 : 512);
 }
 
 void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cs, const bf16_t* dys, const bf16_t* wts,

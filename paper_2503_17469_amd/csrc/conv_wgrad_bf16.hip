@@ -1278,7 +1278,7 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   Wgrad3Params p{};
   p.dy = j.dy; p.src = j.src; p.gw = j.gw; p.gb = j.gb; p.worker_stride = worker_stride;
   p.Cout = j.Cout; p.Cin = g.Cs; p.cin_real = j.cin_real; p.H = H; p.W = W; p.R = R; p.nimg = nimg;
-  p.Wp = w4 ? 8 : W + 16; p.prows = nimg * (R + 2);
+  p.Wp = W + 16; p.prows = nimg * (R + 2);
   // channel stride of X^T in 4-byte words must be 4 mod 8: 16 lanes x 16 bytes then cover all 64 banks
   int words = p.prows * p.Wp / 2;
   words += (4 - words % 8 + 8) % 8;
@@ -1294,8 +1294,8 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   const bool narrow = ring && !w4 && g.Cs <= 32;
   pl.lds = ring ? ring_lds_bytes(narrow, 4) : (size_t)64 * kSA + (size_t)64 * p.SX + 2 * kSkewPad;   // + the row skew of both arrays
   if (!ring && pl.lds > 80 * 1024) return false;
-  pl.job.kind = !ring ? kPatchAny : w4 ? kPatch4 : W == 8 ? (narrow ? kPatch8Narrow : kPatch8) : W == 16 ? (narrow ? kPatch16Narrow : kPatch16)
-              : W == 32 ? (narrow ? kPatch32Narrow : kPatch32) : kPatchAny;
+  pl.job.kind = !ring ? kPatchAny : w4 ? kPatch4 : W == 8 ? (narrow ? kPatch8Narrow : kPatch8)
+              : W == 16 ? (narrow ? kPatch16Narrow : kPatch16) : (narrow ? kPatch32Narrow : kPatch32);
   pl.job.tiles = ((j.Cout + 63) / 64) * ((g.Cs + 63) / 64);
   pl.job.slots = 144; pl.job.patch = p;
   count_units(pl, seg, H / R, nimg);
@@ -1313,8 +1313,8 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   return true;
 }
 
-// 3x3 / stride 2 / pad 1 without bias: the transposing-read form.  (Its body takes any stride; stride-1 layers are kernel
-// C's, which measured faster on every map width, by 0.07 to 0.64 ms per ResNet-18 step.)
+// 3x3 / stride 2 / pad 1 without bias: the transposing-read form.  (Its body takes any stride; stride-1 layers have the ring form, which
+// reads its operands in the same way from streams that need no patch.)
 bool plan_stride2(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Segments& seg) {
   const ConvGeom& g = j.g;
   const int S = g.stride, Ho = g.Hp, Wo = g.Wp, H = g.Hs, W = g.Ws;
