@@ -1301,8 +1301,8 @@ bool plan_patch(Plan& pl, const ConvWgradJob& j, size_t worker_stride, const Seg
   count_units(pl, seg, H / R, nimg);
   // about one workgroup per compute unit (every chunk parks a partial tile of up to 148 KB that the second stage reads
   // back: with 512 chunks that traffic outweighed the extra parallelism, measured -2 % on the three-layer CNN's step).
-  // At least two units a chunk (128 images of 3-32-64-128: step 77.9 us with four, 76.6 with two)
-  pl.min_upc = 2; pl.upc_step = 1; pl.alone = 256;
+  // At least four units a chunk (with two, ResNet-18 shape, 20 images: second stages 33 -> 69 us, step 870 -> 925; see plan_batch).
+  pl.min_upc = 4; pl.upc_step = 1; pl.alone = 256;
   pl.slot_floats = kTile3Stride;
   // The ring form's units take 2.6 us (narrow: 1.3).  Beside layers of other forms it has the share of a launch that kernel C's 4.5
   // (3.0; 6.0 on 4-wide maps) would give: with its own its chains were up to twice as long, and a gradient's error up to 1.17 times
@@ -1431,7 +1431,8 @@ void plan_batch(BatchPlan& bp, const ConvWgradJob* jobs, int m, size_t worker_st
   for (int i = 0; i < m; ++i) {
     Plan& pl = bp.plans[i];
     if (pl.job.kind == kFirst) continue;
-    if (bp.ring8) pl.work = pl.ring_work;
+    // (where eight wavefronts share a chunk, two units: 128 images of 3-32-64-128, step 77.9 us with four, 76.6 with two)
+    if (bp.ring8) { pl.work = pl.ring_work; pl.min_upc = 2; }
     work += pl.work;
   }
   // Layers that share the launch share its workgroups in proportion to the time their units take (not

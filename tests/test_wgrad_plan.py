@@ -97,3 +97,16 @@ def test_chains_of_stride_1_layers_beside_others(shim, layers, at_least):
     out = (ctypes.c_long * 12)()
     shim.describe(flat, 2, offs, 8, 768, out)
     assert out[1] == out[7] and out[2] >= at_least
+
+
+@pytest.mark.parametrize("workers", [1, 4])
+def test_chunks_of_few_images(shim, workers):
+    """Twenty images beside a stride-2 layer: chunks of at least four units of 128 positions (smaller ones made second stages twice as
+    long as they were)."""
+    layers = [(8, 256, 256, 1), (16, 128, 256, 2)]
+    flat = (ctypes.c_int * 8)(*[v for L in layers for v in L])
+    offs = (ctypes.c_int * (workers + 1))(*[20 * k // workers for k in range(workers + 1)])
+    out = (ctypes.c_long * 12)()
+    shim.describe(flat, 2, offs, workers, 768, out)
+    units = [(offs[k + 1] - offs[k]) * 64 / 128 for k in range(workers)]
+    assert out[2] == 16 * sum(-(-u // 4) for u in units)
