@@ -710,17 +710,19 @@ static bool frag_s2_shape(int rows, int H, int W, int N, int Cs, ConvGeom& g, Fr
   return s.lds <= kLdsOfComputeUnit;
 }
 
-// Up to two workgroups per compute unit over the four classes; up to two per class where its rival is not the kernel that is staged by loads
-// that write LDS.  That one / this one, with the projection and the sums, us: 32x32 from 64 to 128 channels 18.9 / 16.1 at 128 tiles, 19.0 / 22.6
-// at 192, 21.9 / 31.0 at 512; 16x16 from 128 to 256 22.6 / 17.1, 23.3 / 26.2, 31.7 / 43.4; 8x8 from 256 to 512 31.0 / 27.9, 31.3 / 30.9, 46.3 /
-// 62.7.  Step of the ResNet-18 shape with the line at 128 tiles and at 512: 96 images 1272 / 1288 us, 128 1473 / 1498, 256 2235 / 2249, 384
-// 2882 / 2934.  (Against the kernel staged through registers 512 was the line: steps of 128 to 256 images 2.5 to 1.6 per cent shorter.)
-bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2) {
+// With the sums of a batch norm up to two workgroups per compute unit over the four classes, without up to five; up to two per class
+// where its rival is not the kernel that is staged by loads that write LDS.  That one / this one, us, with the projection and the sums: 32x32
+// from 64 to 128 channels 18.9 / 16.1 at 128 tiles, 19.0 / 22.6 at 192, 21.9 / 31.0 at 512; 16x16 from 128 to 256 22.6 / 17.1, 23.3 / 26.2, 31.7 /
+// 43.4; 8x8 from 256 to 512 31.0 / 27.9, 31.3 / 30.9, 46.3 / 62.7.  Alone without sums: 21.9 / 17.7 at 256, 22.4 / 21.4 at 320, 22.6 / 23.0 at
+// 384; 25.4 / 21.9, 26.0 / 24.8, 26.1 / 26.5; 34.1 / 25.4, 34.0 / 31.2, 34.6 / 35.1.  Step of the ResNet-18 shape with the line at 128 tiles
+// and at 512: 96 images 1272 / 1288 us, 128 1473 / 1498, 256 2235 / 2249, 384 2882 / 2934.  (Against the kernel staged through registers 512 was
+// the line: steps of 128 to 256 images 2.5 to 1.6 per cent shorter.)
+bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2, bool sums) {
   ConvGeom g;
   FragShape s;
   if ((Cs2 != 0 && Cs2 != Cs) || !frag_s2_shape(rows, H, W, N, Cs, g, s)) return false;
   const long tiles = (s.upi == 1 ? (rows + s.nimg - 1) / s.nimg : (long)rows * s.upi) * ((N + kTN - 1) / kTN);
-  return tiles <= (conv3s2_dgrad_ring_takes(rows, H, W, N, Cs, Cs2) ? 128 : 512);
+  return tiles <= (!conv3s2_dgrad_ring_takes(rows, H, W, N, Cs, Cs2) ? 512 : sums ? 128 : 320);
 }
 
 void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cs, const bf16_t* dys, const bf16_t* wts,

@@ -1523,7 +1523,8 @@ bool update_too_long(const BatchTable& tab, int K) {
 // Wavefronts of a workgroup of the second stage with the update.  A compute unit holds sixteen of them (100 registers) however they are
 // grouped.  More per workgroup mean fewer turns at the workers, but a barrier at which all wait for the slowest, and registers held
 // by those that have no worker left and no part in the update: sixteen only where all of the launch (an element per thread of the other
-// parameters included) is resident at once, eight while the workgroups that add chunks are.  Step in us with 4 / 8 / 16, by those
+// parameters included) is resident at once, eight while the workgroups that add chunks are, and the others not many more (13 workers, 887,000
+// other parameters: the launch 16.2 us with eight, 13.0 with four).  Step in us with 4 / 8 / 16, by those
 // workgroups and by workers (images of each in brackets):
 //    145 (3-32-64-128, 16x16)   14 (2) 68.7 / 67.1 / 66.2
 //    145 (3-16-96-128, 16x16)   48 (5) 111.3 / 105.0 / 109.9
@@ -1534,7 +1535,7 @@ bool update_too_long(const BatchTable& tab, int K) {
 //   1595 (3-16-128-256, 16x16)   9 (40) 113.4 / 115.8 / 121.8    32 (8) 117.7 / 117.0 / 119.6    64 (8) 163.0 / 151.7 / 152.3
 // Of 248 such networks 0.1 per cent slower on average than with the best of the three, 2.4 at most.
 int update_wavefronts(int K, int workgroups, long others) {
-  if (K <= 4 || (K <= 32 && workgroups > 512)) return 4;
+  if (K <= 4 || (K <= 32 && (workgroups > 512 || workgroups + others / 512 > 900))) return 4;
   return K > 8 && workgroups + (others + 1023) / 1024 <= 256 ? 16 : 8;
 }
 

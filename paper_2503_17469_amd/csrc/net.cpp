@@ -740,7 +740,12 @@ void step_bf16(StepCtx& c) {
     if (M.fused_away || M.d.op != OMNI_OP_CONV || M.d.ksize != 3 || M.d.stride != 2 || M.d.pad != 1 || !M.need_dgrad) continue;
     const int sc = partner[m];
     const int cout_sc = sc >= 0 ? net->layers[sc].d.cout : 0;
-    s2_frag[m] = omni::conv_frag_s2_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, cout_sc)         ? 1
+    bool sums = false;   // a batch norm below will want its sums (or, below an add, may)
+    for (int j = 0; j < m; ++j) {
+      const Layer& P = net->layers[j];
+      sums = sums || (!P.fused_away && P.out == M.in0 && (P.d.op == OMNI_OP_BN || P.d.op == OMNI_OP_ADD));
+    }
+    s2_frag[m] = omni::conv_frag_s2_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, cout_sc, sums)   ? 1
                  : omni::conv3s2_dgrad_ring_takes(rows, M.ih, M.iw, M.cin_pad, M.d.cout, cout_sc) ? 2
                                                                                                   : 0;
     if (sc >= 0) s2_frag[sc] = s2_frag[m];

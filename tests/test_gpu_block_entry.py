@@ -74,14 +74,14 @@ def test_against_float64(h, w, cin, cout, beside, off):
     assert float(((got - want).abs() - slack).max()) <= 0
 
 
-# 128 tiles of 64 positions by 64 channels, the most of the kernel for few positions, and one image more
-@pytest.mark.parametrize("h,w,cin,cout,beside,B", [(16, 16, 64, 64, "projection", 128), (16, 16, 64, 64, "projection", 129),
-                                                   (8, 8, 64, 128, "twin", 512), (8, 8, 64, 128, "twin", 513)])
+# The most tiles (64 positions by 64 channels) of the kernel for few positions, 320, and one image more; with sums 128
+@pytest.mark.parametrize("h,w,cin,cout,beside,B", [(16, 16, 64, 64, "projection", 320), (16, 16, 64, 64, "projection", 321),
+                                                   (8, 8, 64, 128, "twin", 1280), (8, 8, 64, 128, "twin", 1281)])
 def test_either_side_of_the_rule(h, w, cin, cout, beside, B):
     test_against_float64(h, w, cin, cout, beside, [0, 1, B])
 
 
-@pytest.mark.parametrize("hw,B", [(16, 128), (16, 129), (32, 33)])
+@pytest.mark.parametrize("hw,B", [(16, 128), (16, 129), (32, 32), (32, 33)])
 def test_sums_at_either_side_of_the_rule(hw, B):
     test_sums_below_a_block_entry(hw, B)
 
