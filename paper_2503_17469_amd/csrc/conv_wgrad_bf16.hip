@@ -1503,11 +1503,12 @@ double conv_wgrad_work(const ConvWgradJob& j) {
 
 namespace {
 // Whether the second stage with the update takes longer than one without and a launch for the update (5 us).  With it a wavefront
-// adds all chunks of a worker, sixteen on their way at a time (with fewer than four workers some wavefronts have none); without, a
-// quarter of them, eight: half a microsecond a trip either way, beside the reading of all partial tiles at 4 TB/s.  Step of one
-// 3-32 layer with pooling, one worker: 128 images 56.1 us with the update, 54.7 without; 256 69.0 / 63.8; 700 97.0 / 85.3; two workers with
-// 20 and 480 91.4 / 79.2; three layers, one worker, 384 images 130.3 / 121.7.  (More workers: eight, one of them with 665 images of
-// 700, 169.9 / 179.2, as all of that worker's workgroups of the other second stage lie on one XCD.)
+// adds all chunks of a worker, sixteen loads on their way at a time (with fewer than four workers some wavefronts have none); without, a
+// quarter of them, eight: half a microsecond a trip either way, beside the reading of all partial tiles at 4 TB/s.  Step in us with the
+// update / without.  One 3-32 layer with pooling, one worker: 64 images 48.6 / 48.1, 128 55.2 / 53.4, 256 68.5 / 62.9, 700 95.3 / 83.9; two
+// workers with 20 and 480 91.8 / 80.5.  3-32-64-128, one worker: 128 images 81.1 / 84.2, 256 101.7 / 98.1, 384 123.1 / 115.1, 1024 195.6 / 183.5;
+// two with 20 and 480 139.6 / 130.0.  (More workers: eight, one of them with 665 images of 700, 162.0 / 164.3, as all of that worker's
+// workgroups of the other second stage lie on one XCD; of a single layer 94.1 / 85.0.)
 bool update_too_long(const BatchTable& tab, int K) {
   if (K >= kThreads / 64) return false;
   int most = 0;

@@ -222,7 +222,7 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
                     const bf16_t* addend, BnStatRequest* stats);
 // The same for the input gradient of a residual block's entry (as conv3s2_dgrad_bf16, weights in operand order; Cs2: channels of
-// dys, 0 without).
+// dys, 0 without; sums: a batch norm below is expected to ask for its sums).
 bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2, bool sums);
 void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int Cs, const bf16_t* dys, const bf16_t* wts,
                        bf16_t* dx, int rows, int H, int W, int N, const bf16_t* mask, const uint8_t* mask_bits, bool accumulate,
