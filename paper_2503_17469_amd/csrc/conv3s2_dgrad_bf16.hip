@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kThreads, 1) void conv3s2_dgrad_kernel(S2Params p) 
 // (matrix pipe busy 0.15).  Here a slice of 32 channels of dy comes with the shortcut's, so that the projection is a tenth tap and
 // no slice of its own; two workgroups share a compute unit; rows of the patch lie as in memory; and the batch norm below
 // gets its sums here, where they took another pass over dx and its input.  2048 images of the ResNet-18 shape, the entries at 64, 128 and
-// 256 channels: 731 us together and 260 for the sums -> 254 + 168 + 127 with them (the step 12.23 -> 11.72 ms), 238 + 157 + 122 with results and
+// 256 channels: 731 us together and 260 for the sums -> 254 + 168 + 127 with them (the step 12.23 -> 11.72 ms), 233 + 153 + 120 with results and
 // what the epilogue reads in whole lines (1.0 GB, 4.2 TB/s, in the first; the epilogue's vector instructions, the sums in double, were 0.45 of
 // the time there, the matrix pipe is busy for 0.42 of the last).
 struct S2RingParams {

@@ -11,7 +11,7 @@
 // sums from the epilogue.
 //
 // 2048 images of the ResNet-18 shape, 3x3 and 1x1 together, us, from 64, 128 and 256 channels: 251, 190 and 149 in the general kernel
-// and 53, 32 and 21 for the sums' pass -> 236, 160 and 155 with them (the step 11.11 -> 10.98 ms), 225, 161 and 154 with the results in whole
+// and 53, 32 and 21 for the sums' pass -> 236, 160 and 155 with them (the step 11.11 -> 10.98 ms), 219, 157 and 152 with the results in whole
 // lines.  The address unit is busy for 0.73 of the first: a gathered half line costs as much as a whole one.
 #include <hip/hip_runtime.h>
 
