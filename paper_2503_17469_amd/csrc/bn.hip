@@ -70,6 +70,19 @@ __device__ inline void unpack8(u32x4 t, float (&v)[8]) {
   for (int d = 0; d < 4; ++d) { v[2 * d] = bf16_lo(t[d]); v[2 * d + 1] = bf16_hi(t[d]); }
 }
 
+// Sixteen bytes; STREAM: with the non-temporal hint.
+template <bool STREAM>
+__device__ inline u32x4 load16(const bf16_t* __restrict__ p) {
+  const u32x4* q = reinterpret_cast<const u32x4*>(p);
+  return STREAM ? __builtin_nontemporal_load(q) : *q;
+}
+template <bool STREAM>
+__device__ inline void store16(bf16_t* __restrict__ p, u32x4 t) {
+  u32x4* q = reinterpret_cast<u32x4*>(p);
+  if (STREAM) __builtin_nontemporal_store(t, q);
+  else *q = t;
+}
+
 // Partial sums of (a) x and x^2, or (b) dy and dy*xhat, over one split of one worker's positions.
 // grid (total splits, ceil(C/64)); block = 8 channel pieces x 64 position lanes; four
 // positions per lane in flight (64 or 128 KB per workgroup: a workgroup per compute unit is enough to keep
@@ -236,12 +249,13 @@ __device__ inline void bn_normalise8(const float (&xv)[8], const float (&sk)[8],
   }
 }
 // Stores them at element idx and, with sign_bits, "stored value > 0" as byte bidx.
+template <bool STREAM>
 __device__ inline void bn_store8(const float (&o)[8], bf16_t* __restrict__ out, uint8_t* __restrict__ sign_bits, long idx,
                                  long bidx) {
   u32x4 t;
 #pragma unroll
   for (int d = 0; d < 4; ++d) t[d] = pack_bf16(o[2 * d], o[2 * d + 1]);
-  *reinterpret_cast<u32x4*>(out + idx) = t;
+  store16<STREAM>(out + idx, t);
   if (!sign_bits) return;
   uint32_t bits = 0;
 #pragma unroll
@@ -256,8 +270,10 @@ __device__ inline void bn_store8(const float (&o)[8], bf16_t* __restrict__ out, 
 // Normalise (forward) or input gradient (backward).  grid (total chunks); a workgroup
 // walks one chunk of ONE worker's positions, so each thread keeps the statistics and
 // the affine parameters of its 8 channels in registers; C/8 threads cover a position,
-// floor(256 / (C/8)) positions are in flight per trip, four trips unrolled.
-template <bool BWD>
+// floor(256 / (C/8)) positions are in flight per trip, four trips unrolled.  Bound by memory: every byte is touched
+// once, so loads carry the non-temporal hint, and stores too (STREAM) where a tensor exceeds what the last-level cache can
+// hand to the next kernel (kBnStreamBytes).  A plain copy of 256 MiB: 107 us without hints, 90 with both.
+template <bool BWD, bool STREAM>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                        const float* __restrict__ stats, const float* __restrict__ means,
                                                        const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -283,9 +299,9 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict_
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const size_t q = min(p + u * ppar, cend - 1);
-      Piece<bf16_t>::load(x + q * C + c0, xv[u]);
-      if (BWD) Piece<bf16_t>::load(dy + q * C + c0, dv[u]);
-      else if (skip) Piece<bf16_t>::load(skip + q * C + c0, dv[u]);
+      unpack8(load16<true>(x + q * C + c0), xv[u]);
+      if (BWD) unpack8(load16<true>(dy + q * C + c0), dv[u]);
+      else if (skip) unpack8(load16<true>(skip + q * C + c0), dv[u]);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -298,10 +314,13 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict_
           const float xh = (xv[u][e] - mu[e]) * is[e];
           o[e] = gm[e] * is[e] * (dv[u][e] - mn1[e] - xh * mn2[e]);
         }
-        Piece<bf16_t>::store(out + q * C + c0, o);
+        u32x4 t;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) t[d] = pack_bf16(o[2 * d], o[2 * d + 1]);
+        store16<STREAM>(out + q * C + c0, t);
       } else {
         bn_normalise8(xv[u], dv[u], mu, is, gm, bt, relu, skip != nullptr, relu_add, o);
-        bn_store8(o, out, sign_bits, q * C + c0, q * c8n + pc);
+        bn_store8<STREAM>(o, out, sign_bits, q * C + c0, q * c8n + pc);
       }
     }
   }
@@ -417,7 +436,7 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
         Piece<bf16_t>::store(out + q * C + c0, o);
       } else {
         bn_normalise8(xv, dv, mu, is, gm, bt, relu, skip != nullptr, relu_add, o);
-        bn_store8(o, out, sign_bits, q * C + c0, q * (C / 8) + (c0 >> 3));
+        bn_store8<false>(o, out, sign_bits, q * C + c0, q * (C / 8) + (c0 >> 3));
       }
     }
   }
@@ -586,14 +605,21 @@ bool few_records(const ShareTable& tb, const Segments& seg, int C, int hw, Share
   return most <= kFinishRecords || (most <= 2 * kFinishRecords && (long)most * chunks.first[seg.K] * (C / 64) <= 65536);
 }
 
+// Tensors from this size on are stored past the last-level cache (256 MiB).  Step of the ResNet-18 shape with no hints / on loads /
+// on stores too: 2048 images (256 MiB a tensor) 10.98 / 10.78 / 10.73 ms, 1400 images 7742 / 7676 / 7723 us, 512 images
+// 3546 / 3532 / 3565.
+constexpr size_t kBnStreamBytes = (size_t)224 << 20;
+bool bn_streams(const Segments& seg, int C, int hw) { return (size_t)seg.off[seg.K] * hw * C * sizeof(bf16_t) >= kBnStreamBytes; }
+
 ShareTable bn_chunks(const Segments& seg, int C, int hw) {
   const long positions = (long)seg.off[seg.K] * hw;
   const int ppar = 256 / (C / 8);
-  // At most about 4096 workgroups with at least eight trips each (a trip is four positions per thread) where
+  // At most about 8192 workgroups with at least two trips each (a trip is four positions per thread) where
   // there is that much; a smaller tensor is spread over up to 2048 workgroups, one trip being the least (128
-  // images of 32x32x64: 1024 workgroups 6 us, 128 with eight trips each 25 us).
+  // images of 32x32x64: 1024 workgroups 6 us, 128 with eight trips each 25 us).  Step of the ResNet-18 shape, 2048
+  // images: 10.53 ms with at most 4096 workgroups of eight trips, 10.46 with 8192 of two, 10.48 with 16384 of one.
   const long trips = positions / (4L * ppar);
-  long total = std::min<long>(4096, std::max(trips / 8, std::min<long>(trips, 2048)));
+  long total = std::min<long>(8192, std::max(trips / 2, std::min<long>(trips, 2048)));
   return deal_shares(seg, std::max<long>(seg.K, total));
 }
 
@@ -621,7 +647,8 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
   }
   hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
   const ShareTable ch = bn_chunks(seg, C, hw);
-  hipLaunchKernelGGL(bn_apply_kernel<false>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, nullptr, stats, nullptr,
+  const auto apply = bn_streams(seg, C, hw) ? bn_apply_kernel<false, true> : bn_apply_kernel<false, false>;
+  hipLaunchKernelGGL(apply, dim3(ch.first[seg.K]), dim3(256), 0, st, x, nullptr, stats, nullptr,
                      gamma, beta, C, hw, 256 / (C / 8), pieces_reciprocal(C), seg, ch, relu ? 1 : 0, y, skip, relu_add ? 1 : 0,
                      sign_bits);
 }
@@ -645,7 +672,8 @@ void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t*
   hipLaunchKernelGGL(bn_finalize_bwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, means,
                      g_gamma, g_beta, worker_stride);
   const ShareTable ch = bn_chunks(seg, C, hw);
-  hipLaunchKernelGGL(bn_apply_kernel<true>, dim3(ch.first[seg.K]), dim3(256), 0, st, x, dy, stats, means, gamma,
+  const auto apply = bn_streams(seg, C, hw) ? bn_apply_kernel<true, true> : bn_apply_kernel<true, false>;
+  hipLaunchKernelGGL(apply, dim3(ch.first[seg.K]), dim3(256), 0, st, x, dy, stats, means, gamma,
                      nullptr, C, hw, 256 / (C / 8), pieces_reciprocal(C), seg, ch, 0, dx, nullptr, 0, nullptr);
 }
 
