@@ -1589,9 +1589,16 @@ bool update_batch(hipStream_t st, const BatchPlan& bp, size_t worker_stride, con
 }
 }  // namespace
 
+// LDS that a workgroup asks for beside the chain of input gradients: more than half of a compute unit's 160 KB, so that one is there at
+// a time.  Two take all of its registers (256 a lane), and the chain's next kernel then waits until some of them end: batch norms of
+// 8 us took 29 to 45.  Chunks, and with them the sums, stay as they are.  Step of the ResNet-18 shape in us, two / one at a time: one
+// worker, 32 images 890 / 890; four, 128 images 1443 / 1382; sixteen, 300 images 2588 / 2522; four, 512 images 3508 / 3448; eight, 2048 images
+// 10773 / 10748.  (With 90 KB the chain's convolutions find less room: 1405 with 128 images, 10856 with 2048.)
+constexpr size_t kBesideLds = 81 * 1024;
+
 bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                       float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd, float* G, size_t params,
-                      bool alone) {
+                      bool alone, bool beside) {
   if (head && n == 0) {
     head_wgrad_loss(st, true, *head, seg);
     return false;
@@ -1605,8 +1612,9 @@ bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t wo
       hipLaunchKernelGGL(wgrad_ring_kernel, dim3(bp.blocks), dim3(2 * kThreads), bp.lds, st, bp.tab, seg);
     } else if (bp.blocks > 0) {
       static LdsLimit limit;
-      limit.raise(reinterpret_cast<const void*>(&wgrad_batch_kernel), 80 * 1024);
-      hipLaunchKernelGGL(wgrad_batch_kernel, dim3(bp.blocks), dim3(kThreads), bp.lds, st, bp.tab, seg);
+      limit.raise(reinterpret_cast<const void*>(&wgrad_batch_kernel), kBesideLds);
+      const size_t lds = beside ? std::max(bp.lds, kBesideLds) : bp.lds;
+      hipLaunchKernelGGL(wgrad_batch_kernel, dim3(bp.blocks), dim3(kThreads), lds, st, bp.tab, seg);
     }
     const HeadWgradParams* h = base == 0 ? head : nullptr;   // rides with the first of the light launches
     for (int i = 0; i < bp.lights; ++i) {

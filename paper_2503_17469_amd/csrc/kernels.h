@@ -274,10 +274,10 @@ double conv_wgrad_work(const ConvWgradJob& job);   // flop
 // null): the classifier's parameter gradients and losses as well (head_wgrad_loss).  workgroups: how many the layers of a
 // shared first stage are cut into (two fit a compute unit).  sgd (may be null; only where these are the step's last gradients): the
 // update of all `params` parameters (G: worker 0's gradients of them) by the launch of the second stage, where that can (true).
-// alone: nothing runs beside these launches.
+// alone: nothing runs beside these launches; beside: they run beside the step's chain of launches and are to leave it room.
 bool conv_wgrad_batch(hipStream_t st, const ConvWgradJob* jobs, int n, size_t worker_stride, const Segments& seg,
                       float* partial, size_t floats, const HeadWgradParams* head, int workgroups, const SgdArgs* sgd = nullptr,
-                      float* G = nullptr, size_t params = 0, bool alone = false);
+                      float* G = nullptr, size_t params = 0, bool alone = false, bool beside = false);
 // How conv_wgrad_batch runs these layers, without a launch: for checks on the host.
 struct ConvWgradPlanned {
   bool first_layer;    // has a first stage of its own

@@ -905,6 +905,15 @@ void step_bf16(StepCtx& c) {
   // error against float64 that a launch per layer gives, 4e-7 of the gradient; with 768 up to 1.3 times), more park more partial
   // tiles (1024: 1.9 per cent of a step of 128 images).
   constexpr int kGroupJobs = 6, kGroupWorkgroups = 768;
+  // It leaves the chain room (one workgroup per compute unit) where at least two batch norms are still to come: their launches are short
+  // and wait for a place otherwise (conv_wgrad_bf16.hip has what it is worth).  A chain of a few long input gradients shares the chip
+  // as it is, and the weight gradients end last: 64-128 (stride 2)-128 without batch norms, 512 images, 416 us and 476 with room.
+  constexpr int kRoomNorms = 2;
+  auto norms_below = [&](int i) {
+    int n = 0;
+    for (int j = 0; j < i; ++j) n += !net->layers[j].fused_away && net->layers[j].d.op == OMNI_OP_BN;
+    return n;
+  };
   bool second = false;
   std::vector<omni::ConvWgradJob> group;
   double group_work = 0.0;
@@ -917,7 +926,8 @@ void step_bf16(StepCtx& c) {
     hipStream_t side = use2 ? c.side2 : c.side;
     TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
     omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
-                           omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups);
+                           omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups, nullptr, nullptr, 0, false,
+                           norms_below(layer) >= kRoomNorms);
     group.clear();
     group_work = 0.0;
   };
