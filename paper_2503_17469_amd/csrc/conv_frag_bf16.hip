@@ -37,7 +37,8 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTM = 64, kTN = 64;      // positions, output channels per workgroup
+constexpr int kTMLog = 6, kTM = 1 << kTMLog, kTN = 64;   // positions, output channels per workgroup
+constexpr int kComputeUnits = 256;
 constexpr int kBlock = 64 * 8;         // elements of a weight block: one matrix operand
 
 struct FragParams {
@@ -55,7 +56,7 @@ struct FragParams {
   uint32_t by_upi;     // reciprocal_below(upi)
   uint32_t by_oc;      // 2^16 / (Cs / 8), rounded up
   int dq, dr;          // 256 pieces on: so many positions and octets
-  int gK;              // entries of the tables at the end
+  int gK;              // workers in the tables at the end; 1 where no sums are wanted
   const void* zero;
   const float* bias;
   const bf16_t* mask;
@@ -65,30 +66,40 @@ struct FragParams {
   bf16_t* pool;
   uint8_t* pool_code;
   const bf16_t *src2, *wgt2;   // stride-2 input gradient: the projection's output gradient (may be null) and weights
-  double* stat_partial;   // [tile][N][2] or null
+  double* stat_partial;   // [record][N][2] or null
   const bf16_t* stat_x;   // BWD: see BnStatRequest
   const float* stat_norm;
-  // entry k owns the tiles tfirst[k] .. and the images ifirst[k] ..
-  int32_t tfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
+  // worker k owns the records rfirst[k] .. and the images ifirst[k] ..
+  int32_t rfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
 };
 
-// Where a tile lies.  A launch of this kernel is a chain of first accesses (a line of arguments 640 cycles, a division 150 to 200):
-// the tables are read only where there is more than one entry, all lanes at once.  (128 images of three conv layers: the four
-// launches 8.5 -> 7.4 us each.)
+// Where a tile lies, and whose images are in it (with a batch norm's sums).  MIXED: tiles follow each other through all images, one may
+// have several workers'; else each worker's begin with its first image.  A launch of this kernel is a chain of first accesses (a line
+// of arguments 640 cycles, a division 150 to 200): the tables are read only where there is more than one worker, all lanes at once.  (128
+// images of three conv layers: the four launches 8.5 -> 7.4 us each.)
 struct FragPlace {
-  int gk, n0, r0, nvalid;   // entry, first image and row, images present
+  int n0, r0, nvalid;       // first image and row, images present
+  int k0, k1;               // the first image's worker and the last one's
+  int ifirst, rfirst;       // MIXED: worker `lane`'s entries
 };
+template <bool MIXED>
 __device__ inline FragPlace frag_place(const FragParams& p, int tile) {
+  const int lane = threadIdx.x & 63;
+  if constexpr (MIXED) {
+    const int i = p.ifirst[lane], r = p.rfirst[lane], n0 = tile * p.nimg, n1 = min(n0 + p.nimg, p.rows);
+    const int k0 = __popcll(__ballot(lane < p.gK && i <= n0)) - 1, k1 = __popcll(__ballot(lane < p.gK && i < n1)) - 1;
+    return FragPlace{n0, 0, n1 - n0, k0, k1, i, r};
+  }
   int gk = 0, tl = tile, beg = 0, end = p.rows;
   if (p.gK > 1) {
-    const int lane = threadIdx.x & 63, t = p.tfirst[lane], i = p.ifirst[lane];   // (65 entries)
+    const int t = p.rfirst[lane], i = p.ifirst[lane];   // (65 entries)
     gk = __popcll(__ballot(lane < p.gK && t <= tile)) - 1;
     tl = tile - __builtin_amdgcn_readlane(t, gk);
     beg = __builtin_amdgcn_readlane(i, gk);
     end = gk + 1 < p.gK ? __builtin_amdgcn_readlane(i, gk + 1) : p.rows;
   }
   const int img = p.upi == 1 ? tl * p.nimg : quotient(tl, p.by_upi, p.upi);
-  return FragPlace{gk, beg + img, p.upi == 1 ? 0 : (tl - img * p.upi) << p.rlog, min(p.nimg, end - beg - img)};
+  return FragPlace{beg + img, p.upi == 1 ? 0 : (tl - img * p.upi) << p.rlog, min(p.nimg, end - beg - img), gk, gk, 0, 0};
 }
 
 __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -96,10 +107,10 @@ __device__ inline bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, 
 // The end of a tile: the partial tiles meet in LDS and each wavefront finishes one 32 x 32 block of it.  out_pos, pos_in: where this
 // lane's position 32 (wave / 2) + lane % 32 of the tile goes, and whether it exists; npos, out_base (pooling): the tile's
 // positions and the first one's place.
-template <int KS, bool BWD>
+template <int KS, bool BWD, bool MIXED>
 __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* smemF, v16f (&acc)[KS == 4 ? 2 : 1][2], int kg,
-                                            int pa, int wave, int lane, int gk, int tile, int col0, bool pos_in,
-                                            size_t out_pos, int npos, size_t out_base) {
+                                            int pa, int wave, int lane, const FragPlace& place, int tile, int sets, int set, int col0,
+                                            bool pos_in, size_t out_pos, int npos, size_t out_base) {
   constexpr int MA = KS == 4 ? 2 : 1;
   const int tid = wave * 64 + lane, j = lane & 31, h = lane >> 5;
   // this wavefront finishes positions 32 a .. and channels 32 b .. of the tile
@@ -109,6 +120,9 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
   const int cb = min(col0 + eb * 32, p.N - 32);
   const size_t row = out_pos * p.N + cb;
   const bf16_t* const zp = static_cast<const bf16_t*>(p.zero);
+  int gk = place.k0;                               // the worker of this lane's position
+  for (int k = place.k0 + 1; MIXED && k <= place.k1; ++k)
+    gk += place.n0 + (pos >> (p.wlog + p.rlog)) >= __builtin_amdgcn_readlane(place.ifirst, k) ? 1 : 0;
   u32x4 em[2], ea4[2], ex4[2];
   v4f mean[2][2];                                  // BWD with statistics: of this lane's channels
   uint32_t ebits = 0;
@@ -215,28 +229,37 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
 
   if (p.stat_partial) {
     // sums of the stored values and of their squares (BWD: see bn_sums_add) over the 32 positions of a block, then over the
-    // two blocks
-    double half[2];
+    // two blocks, for each worker in the tile
+    auto sums_of = [&](int k) {
+      double half[2];
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      double t[2][8] = {};
-      if (row_in) {
-        if (BWD) bn_sums_add(t, outp[qq], ex4[qq], mean[qq]);
-        else bn_sums_add(t, outp[qq]);
+      for (int qq = 0; qq < 2; ++qq) {
+        double t[2][8] = {};
+        if (row_in && (!MIXED || gk == k)) {
+          if (BWD) bn_sums_add(t, outp[qq], ex4[qq], mean[qq]);
+          else bn_sums_add(t, outp[qq]);
+        }
+        half[qq] = bn_sums_tree(t, j);
       }
-      half[qq] = bn_sums_tree(t, j);
-    }
-    const double sum = bn_sums_pair(half[0], half[1], j);
-    __syncthreads();                               // the partial tiles have been read
-    double* const red = reinterpret_cast<double*>(smemF);   // [position block][which][64]
-    red[(ea * 2 + bn_sums_which(j)) * 64 + eb * 32 + bn_sums_channel(j, h)] = sum;
-    __syncthreads();
-    if (tid < 128 && col0 + (tid & 63) < p.N) {
-      const int c = tid & 63, which = tid >> 6;
-      const double sum = red[which * 64 + c] + red[(2 + which) * 64 + c];
-      const double factor = BWD && which == 1 ? (double)p.stat_norm[((size_t)gk * p.N + col0 + c) * 2 + 1] : 1.0;
-      p.stat_partial[((size_t)tile * p.N + col0 + c) * 2 + which] = sum * factor;
-    }
+      const double sum = bn_sums_pair(half[0], half[1], j);
+      __syncthreads();                               // the partial tiles (the last worker's sums) have been read
+      double* const red = reinterpret_cast<double*>(smemF);   // [position block][which][64]
+      red[(ea * 2 + bn_sums_which(j)) * 64 + eb * 32 + bn_sums_channel(j, h)] = sum;
+      __syncthreads();
+      // (of the worker's records the first is that of the tile with its first image)
+      const int record = MIXED ? __builtin_amdgcn_readlane(place.rfirst, k) + tile -
+                                     (__builtin_amdgcn_readlane(place.ifirst, k) >> (kTMLog - p.wlog - p.rlog))
+                               : tile;
+      if (tid < 128 && col0 + (tid & 63) < p.N) {
+        const int c = tid & 63, which = tid >> 6;
+        const double sum = red[which * 64 + c] + red[(2 + which) * 64 + c];
+        const double factor = BWD && which == 1 ? (double)p.stat_norm[((size_t)k * p.N + col0 + c) * 2 + 1] : 1.0;
+        p.stat_partial[((size_t)(record * sets + set) * p.N + col0 + c) * 2 + which] = sum * factor;
+      }
+    };
+    sums_of(place.k0);
+#pragma unroll 1
+    for (int k = place.k0 + 1; MIXED && k <= place.k1; ++k) sums_of(k);
   }
   if (!BWD && p.pool) {
     // a tile is whole rows of whole images, an even number of them: its pooled positions are a contiguous run too
@@ -270,7 +293,7 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
 
 // KS: shares of the reduction (4: a wavefront has 64 positions and a quarter of the channels; 2: 32 positions and
 // half).  TAPS: 9 or 1.  BWD: mask / addend / accumulate instead of bias / ReLU / pooling.
-template <int KS, int TAPS, bool BWD>
+template <int KS, int TAPS, bool BWD, bool MIXED>
 __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   constexpr int MA = KS == 4 ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
@@ -287,8 +310,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   if (at >= total || ((int)blockIdx.x >> 3) >= p.per) return;
   const int per_major = p.by_channel ? tiles : tiles_n, major = quotient(at, p.by_minor, per_major), minor = at - major * per_major;
   const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
-  const FragPlace place = frag_place(p, tile);
-  const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
+  const FragPlace place = frag_place<MIXED>(p, tile);
+  const int n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
   const int R = 1 << p.rlog, Wp = 1 << p.wlog;
   const int npos = nvalid << (p.rlog + p.wlog);
   const int oc = p.Cs >> 3;
@@ -296,7 +319,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   // first source row of the patch; whole maps need no halo rows
   const int s0 = TAPS == 1 || p.upi == 1 ? 0 : max(r0 * p.stride - 1, 0);
 
-  // ---- the patch: pieces of 16 bytes, thread tid takes pieces tid, tid + 256, ...
+  // ---- the patch: pieces of 16 bytes, thread tid takes pieces tid, tid + 256, ...; sixteen of them on their way (512 channels on 4x4: the
+  // whole patch; with eight, every launch of a small net 0.1 us longer)
   const bf16_t* const sbase = p.src + (TAPS == 1 ? (size_t)n0 * p.Hs * p.Ws * p.Cs
                                                  : ((size_t)n0 * p.Hs + s0) * p.Ws * p.Cs);
   const int npieces = p.npatch * oc;
@@ -304,9 +328,9 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   int q = (int)(((uint32_t)tid * p.by_oc) >> 16), rem = tid - q * oc;   // patch position and octet of the piece
   const int dq = p.dq, dr = p.dr;
   int x = tid;
-  u32x4 rp[8];
-  int dst[8];
-  auto load_batch = [&]() {
+  u32x4 rp[2][8];
+  int dst[2][8];
+  auto load_batch = [&](int set) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       size_t off;
@@ -317,20 +341,21 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
       } else {
         off = (size_t)min(x, live - 1) * 8;        // (what lies past the end is never read back)
       }
-      rp[i] = *reinterpret_cast<const u32x4*>(sbase + off);
-      dst[i] = x < npieces ? q * pitch + rem * 16 : -1;
+      rp[set][i] = *reinterpret_cast<const u32x4*>(sbase + off);
+      dst[set][i] = x < npieces ? q * pitch + rem * 16 : -1;
       x += kThreads;
       q += dq;
       rem += dr;
       if (rem >= oc) { rem -= oc; ++q; }
     }
   };
-  auto store_batch = [&]() {
+  auto store_batch = [&](int set) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (dst[i] >= 0) *reinterpret_cast<u32x4*>(smemF + dst[i]) = rp[i];
+      if (dst[set][i] >= 0) *reinterpret_cast<u32x4*>(smemF + dst[set][i]) = rp[set][i];
   };
-  load_batch();
+  load_batch(0);
+  if (npieces > 8 * kThreads) load_batch(1);         // (the same for all threads)
 
   // ---- weights: the first nine taps are on their way while the patch is stored
   const int c16n = p.Cs >> 4, nC = c16n / KS;
@@ -368,10 +393,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   }
 
   for (int i = tid; i <= oc; i += kThreads) *reinterpret_cast<u32x4*>(smemF + zrow + i * 16) = u32x4{0u, 0u, 0u, 0u};
-  while (true) {
-    store_batch();
-    if (x - tid >= npieces) break;                 // (the same for all threads)
-    load_batch();
+  store_batch(0);
+  if (npieces > 8 * kThreads) store_batch(1);
+  while (x - tid < npieces) {
+    load_batch(0);
+    store_batch(0);
   }
   __syncthreads();
 
@@ -422,7 +448,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_kernel(FragParams p) {
   sixteen_channels(std::false_type{});
 
   const int epos = (wave >> 1) * 32 + j;
-  frag_finish<KS, BWD>(p, smemF, acc, kg, pa, wave, lane, gk, tile, col0, epos < npos,
+  frag_finish<KS, BWD, MIXED>(p, smemF, acc, kg, pa, wave, lane, place, tile, 1, 0, col0, epos < npos,
                        (((size_t)n0 * p.Hp + r0) << p.wlog) + epos, npos, ((size_t)n0 * p.Hp + r0) << p.wlog);
 }
 
@@ -466,6 +492,7 @@ __device__ __forceinline__ void frag_steps(const unsigned char* smemF, const int
   }
 }
 
+template <bool MIXED>
 __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -478,8 +505,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p)
   const int ph = cls >> 1, pw = cls & 1;
   const int per_major = p.by_channel ? tiles : tiles_n, major = quotient(at, p.by_minor, per_major), minor = at - major * per_major;
   const int tile = p.by_channel ? minor : major, col0 = (p.by_channel ? major : minor) * kTN;
-  const FragPlace place = frag_place(p, tile);
-  const int gk = place.gk, n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
+  const FragPlace place = frag_place<MIXED>(p, tile);
+  const int n0 = place.n0, r0 = place.r0, nvalid = place.nvalid;
   const int R = 1 << p.rlog, Wp = 1 << p.wlog;     // the half-resolution grid: Hs x Ws = Hp x Wp
   const int npos = nvalid << (p.rlog + p.wlog);
   const int oc = p.Cs >> 3, pitch = p.Cs * 2 + 16;
@@ -574,7 +601,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_frag_s2_kernel(FragParams p)
   const int pos = (wave >> 1) * 32 + j;
   const int w = pos & (Wp - 1), r = (pos >> p.wlog) & (R - 1), il = pos >> (p.wlog + p.rlog);
   const size_t out_pos = ((size_t)(n0 + il) * 2 * p.Hs + 2 * (r0 + r) + ph) * 2 * p.Ws + 2 * w + pw;
-  frag_finish<4, true>(p, smemF, acc, wave, 0, wave, lane, gk, tile * 4 + cls, col0, pos < npos, out_pos, npos, 0);
+  frag_finish<4, true, MIXED>(p, smemF, acc, wave, 0, wave, lane, place, tile, 4, cls, col0, pos < npos, out_pos, npos, 0);
 }
 
 int log2_exact(int v) {
@@ -606,35 +633,41 @@ bool frag_shape(const ConvGeom& g, int N, FragShape& s) {
   return s.lds <= kLdsOfComputeUnit;
 }
 
-// The tiles: one worker's each where batch-norm sums are wanted and there is room for their records (`sets` per tile), else
-// all images in one run.
-void frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stats, bool bwd, int sets) {
+// The tiles, and where batch-norm sums are wanted and there is room for their records (`sets` per tile and worker in it), the tables.  Of
+// several images a tile is one worker's, which leaves some images of the last ones empty, or follows the one before, with a record for
+// each worker in it (1.5 us each; true): where that saves a round of workgroups (a compute unit with one more than the others is the last by a
+// quarter of a launch or more; four workers' 128 images, 512 channels on 4x4: 272 workgroups 21.9 us, 256 18.5, input gradient
+// 23.4 / 20.1, of the block's entry 25.8 / 19.5; 64 images, step 1060 us, 1072 with tiles of several workers).
+bool frag_tiles(FragParams& p, const FragShape& s, int rows, BnStatRequest* stats, bool bwd, int sets) {
   auto tiles_of = [&](int images) { return s.upi == 1 ? (images + s.nimg - 1) / s.nimg : images * s.upi; };
-  const bool want = stats && stats->partial && stats->seg && stats->seg->off[stats->seg->K] == rows &&
-                    bwd == (stats->x != nullptr);
-  long records = 0;
-  if (want)
-    for (int k = 0; k < stats->seg->K; ++k) records += tiles_of(stats->seg->off[k + 1] - stats->seg->off[k]);
+  p.tiles = tiles_of(rows);
   p.gK = 1;
-  p.ifirst[1] = rows;
-  if (want && records * sets <= (long)stats->seg->K * kBnMaxSplits) {
-    p.gK = stats->seg->K;
-    for (int k = 0; k <= p.gK; ++k) p.ifirst[k] = stats->seg->off[k];
-    p.stat_partial = stats->partial;
-    p.stat_x = stats->x;
-    p.stat_norm = stats->stats;
+  if (!stats || !stats->partial || !stats->seg || stats->seg->off[stats->seg->K] != rows || bwd != (stats->x != nullptr)) return false;
+  const Segments& seg = *stats->seg;
+  int apart = 0;
+  for (int k = 0; k < seg.K; ++k) apart += tiles_of(seg.off[k + 1] - seg.off[k]);
+  auto rounds = [&](int tiles) { return ((long)tiles * ((p.N + kTN - 1) / kTN) * sets + kComputeUnits - 1) / kComputeUnits; };
+  const bool mixed = s.nimg > 1 && rounds(p.tiles) < rounds(apart);
+  for (int k = 0; k <= seg.K; ++k) {
+    p.ifirst[k] = seg.off[k];
+    if (k == seg.K) break;
+    const int beg = seg.off[k], end = seg.off[k + 1];
+    p.rfirst[k + 1] = p.rfirst[k] + (mixed ? (end - 1) / s.nimg + 1 - beg / s.nimg : tiles_of(end - beg));
   }
-  for (int k = 0; k < p.gK; ++k) p.tfirst[k + 1] = p.tfirst[k] + tiles_of(p.ifirst[k + 1] - p.ifirst[k]);
-  if (p.stat_partial) {
-    for (int k = 0; k <= p.gK; ++k) stats->table.first[k] = p.tfirst[k] * sets;
-    stats->done = true;
-  }
+  if ((long)p.rfirst[seg.K] * sets > (long)seg.K * kBnMaxSplits) return false;
+  if (!mixed) p.tiles = apart;
+  p.gK = seg.K;
+  p.stat_partial = stats->partial;
+  p.stat_x = stats->x;
+  p.stat_norm = stats->stats;
+  for (int k = 0; k <= seg.K; ++k) stats->table.first[k] = p.rfirst[k] * sets;
+  stats->done = true;
+  return mixed;
 }
 
 // What follows from the tiles, the channels and by_channel.
 void frag_counts(FragParams& p) {
   const int tiles_n = (p.N + kTN - 1) / kTN, oc = p.Cs / 8;
-  p.tiles = p.tfirst[p.gK];
   p.per = (p.tiles * tiles_n + 7) / 8;
   p.by_minor = reciprocal_below(p.by_channel ? p.tiles : tiles_n, (uint64_t)p.tiles * tiles_n);
   p.by_upi = reciprocal_below(p.upi, p.tiles);
@@ -643,11 +676,17 @@ void frag_counts(FragParams& p) {
   p.dr = kThreads - p.dq * oc;
 }
 
-template <int KS, int TAPS, bool BWD>
+template <int KS, int TAPS, bool BWD, bool MIXED>
 void launch(hipStream_t st, const FragParams& p, int grid, size_t lds) {
   static LdsLimit limit;
-  limit.raise(reinterpret_cast<const void*>(&conv_frag_kernel<KS, TAPS, BWD>), kLdsOfComputeUnit);
-  hipLaunchKernelGGL((conv_frag_kernel<KS, TAPS, BWD>), dim3(grid), dim3(kThreads), lds, st, p);
+  limit.raise(reinterpret_cast<const void*>(&conv_frag_kernel<KS, TAPS, BWD, MIXED>), kLdsOfComputeUnit);
+  hipLaunchKernelGGL((conv_frag_kernel<KS, TAPS, BWD, MIXED>), dim3(grid), dim3(kThreads), lds, st, p);
+}
+template <bool MIXED>
+void launch_s2(hipStream_t st, const FragParams& p, int grid, size_t lds) {
+  static LdsLimit limit;
+  limit.raise(reinterpret_cast<const void*>(&conv_frag_s2_kernel<MIXED>), kLdsOfComputeUnit);
+  hipLaunchKernelGGL(conv_frag_s2_kernel<MIXED>, dim3(grid), dim3(kThreads), lds, st, p);
 }
 
 }  // namespace
@@ -684,16 +723,18 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   p.bias = bias; p.mask = mask; p.addend = addend; p.relu = relu ? 1 : 0; p.accumulate = accumulate ? 1 : 0;
   p.mask_bits = (mask && N % 64 == 0) ? g.mask_bits : nullptr;
   if (!bwd && pool && pool_code && s.R % 2 == 0 && g.Hp % 2 == 0) { p.pool = pool; p.pool_code = pool_code; }
-  frag_tiles(p, s, g.rows, (bias || relu) ? nullptr : stats, bwd, 1);
-  const int taps = g.ks * g.ks, tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
+  const bool mixed = frag_tiles(p, s, g.rows, (bias || relu) ? nullptr : stats, bwd, 1);
+  const int taps = g.ks * g.ks, tiles = p.tiles, tiles_n = (N + kTN - 1) / kTN;
   // an XCD's L2 sees the whole of one operand and about an eighth of the other
   p.by_channel = (long)N * taps * g.Cs > (long)g.rows * g.Hs * g.Ws * g.Cs ? 1 : 0;
   frag_counts(p);
   const int grid = (tiles * tiles_n + 7) / 8 * 8;
-#define OMNI_FRAG(KS_, TAPS_) { if (bwd) launch<KS_, TAPS_, true>(st, p, grid, s.lds); else launch<KS_, TAPS_, false>(st, p, grid, s.lds); }
+#define OMNI_FRAG_(KS_, TAPS_, BWD_) { if (mixed) launch<KS_, TAPS_, BWD_, true>(st, p, grid, s.lds); else launch<KS_, TAPS_, BWD_, false>(st, p, grid, s.lds); }
+#define OMNI_FRAG(KS_, TAPS_) { if (bwd) OMNI_FRAG_(KS_, TAPS_, true) else OMNI_FRAG_(KS_, TAPS_, false) }
   if (taps == 9) { if (s.ks == 4) OMNI_FRAG(4, 9) else OMNI_FRAG(2, 9) }
   else { if (s.ks == 4) OMNI_FRAG(4, 1) else OMNI_FRAG(2, 1) }
 #undef OMNI_FRAG
+#undef OMNI_FRAG_
   return p.pool != nullptr;
 }
 
@@ -739,13 +780,12 @@ void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int C
   p.stride = 1; p.flip = 1; p.zero = zero;
   p.mask = mask; p.addend = addend; p.accumulate = accumulate ? 1 : 0;
   p.mask_bits = (mask && N % 64 == 0) ? mask_bits : nullptr;
-  frag_tiles(p, s, rows, stats, true, 4);
-  const int tiles = p.tfirst[p.gK], tiles_n = (N + kTN - 1) / kTN;
+  const bool mixed = frag_tiles(p, s, rows, stats, true, 4);
+  const int tiles = p.tiles, tiles_n = (N + kTN - 1) / kTN;
   p.by_channel = (long)N * 9 > (long)rows * g.Hs * g.Ws ? 1 : 0;
   frag_counts(p);
-  static LdsLimit limit;
-  limit.raise(reinterpret_cast<const void*>(&conv_frag_s2_kernel), kLdsOfComputeUnit);
-  hipLaunchKernelGGL(conv_frag_s2_kernel, dim3((tiles * tiles_n + 7) / 8 * 8 * 4), dim3(kThreads), s.lds, st, p);
+  const int grid = (tiles * tiles_n + 7) / 8 * 8 * 4;
+  if (mixed) launch_s2<true>(st, p, grid, s.lds); else launch_s2<false>(st, p, grid, s.lds);
 }
 
 }  // namespace omni

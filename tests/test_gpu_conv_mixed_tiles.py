@@ -1,0 +1,71 @@
+"""Convolutions of few positions on 4-wide maps whose tiles hold images of several workers (where that saves a round of workgroups): a
+batch norm's sums of every worker, in both directions, and that no worker's values reach another's.  The sums are checked as in
+test_gpu_bn_sums.py, on these workers."""
+import numpy as np
+import pytest
+
+import synth
+import test_gpu_bn_sums as sums
+from gpu_util import GpuRun
+
+pytestmark = pytest.mark.gpu
+
+# four images a tile, one tile of 64 channels each: workers of 1 to 40 images, tiles with two, three and four of them; a tile's first
+# and last image alone another worker's; the last tile not full
+MANY = [0] + sorted(np.random.default_rng(5).choice(np.arange(1, 999), 63, replace=False).tolist()) + [999]
+CUTS = [MANY, [0, 1, 2, 3, 500, 1020], [0, 1, 2, 4, 507, 1017], [0, 1023 - 4 * 40, 1023 - 3] + [1023]]
+
+
+def _mixed(off, images, sets=1):
+    """Whether the tiles of several workers are the fewer rounds of 256 workgroups."""
+    apart = sum(-(-(b - a) // images) for a, b in zip(off, off[1:]))
+    return -(-(-(-off[-1] // images) * sets) // 256) < -(-apart * sets // 256)
+
+
+@pytest.mark.parametrize("off", CUTS, ids=lambda off: "%d-%d" % (len(off) - 1, off[-1]))
+@pytest.mark.parametrize("direction", ["forward", "backward"])
+def test_sums_of_every_worker(off, direction, monkeypatch):
+    assert _mixed(off, 4)
+    monkeypatch.setattr(sums, "_cuts", lambda B: off)
+    if direction == "forward":
+        sums.test_forward_statistics_of_channels_far_from_zero(4, off[-1], 3)
+    else:
+        sums.test_backward_sums(4, off[-1])
+
+
+@pytest.mark.parametrize("off", [[0, 1, 86, 256], [0, 3, 5, 6, 255]], ids=lambda off: "%d-%d" % (len(off) - 1, off[-1]))
+def test_sums_below_a_block_entry(off, monkeypatch):
+    """Four classes of positions, a record each."""
+    assert _mixed(off, 4, 4)
+    monkeypatch.setattr(sums, "_cuts", lambda B: off)
+    sums.test_backward_sums_below_a_block_entry(8, off[-1])
+
+
+def test_workers_do_not_meet():
+    off = [0, 2, 3, 7, 510, 1019]
+    assert _mixed(off, 4)
+    C, B, K = 64, off[-1], len(off) - 1
+    layers = [sums._conv(-1, C), dict(op="bn", src=0, c=C), dict(op="relu", src=1), sums._conv(2, C), dict(op="bn", src=3, c=C),
+              dict(op="relu", src=4)] + sums._tail(5, C)
+    params = synth.he_normal_params(layers, 5, True)
+    rng = np.random.default_rng(2)
+    x = synth.to_bf16_grid(rng.standard_normal((B, 4, 4, C)).astype(np.float32))
+    y = rng.integers(0, 10, B).astype(np.int32)
+    run = GpuRun(layers, (4, 4, C), "bf16", K, B)
+    try:
+        seen = []
+        for k in [None, 1, 3]:
+            xk = x.copy()
+            if k is not None:
+                xk[off[k]:off[k + 1]] = np.nan
+            got = run.step(params, xk, y, off, 0.0)
+            seen.append((k, run.activation(1, B).copy(), got["worker_grads"].copy()))
+        for k, act, grads in seen[1:]:
+            for w in range(K):
+                if w == k:
+                    continue
+                rows = slice(off[w], off[w + 1])
+                assert np.array_equal(act[rows], seen[0][1][rows])
+                assert np.array_equal(grads[w], seen[0][2][w])
+    finally:
+        run.close()
