@@ -86,6 +86,8 @@ struct WideParams {
   int32_t ifirst[OMNI_MAX_WORKERS + 1];   // the entries' images
   bf16_t* pool;           // POOL: [rows*(H/2)*(W/2)][N], the 2 x 2 max pooling of `out`
   uint8_t* pool_code;     // ... and where its gradient goes (pool_code_of)
+  const uint8_t* unpool_code;   // plain: see UnpoolRequest
+  bf16_t* unpool;
   double* stat_partial;   // STATS: [group][N][2] sums of the stored output and of its squares (BWD: see BnStatRequest)
   const bf16_t* stat_x;   // STATS and BWD: [rows*H*W][N]
   const float* stat_norm; // ... [worker][N][2]
@@ -146,9 +148,10 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
   static_assert(NB == 2 || (!BWD && !STATS), "the narrow tile has neither mask nor sums");
   static_assert(!POOL || (!BWD && !STATS), "pooling is a forward epilogue");
   constexpr int kTN = 32 * NB;    // output channels per workgroup
+  constexpr bool DMA = NP == 0;
+  constexpr bool UNPOOL = MA == 2 && (DMA || ONE) && !BWD && !STATS && !POOL;   // may expand a pooling's gradient (the others' registers are full)
   constexpr bool STOP = ONE;   // no loads for a unit that does not come (the other variants would spill at the branch)
   constexpr int RW = (9 * kTN * OC + kThreads - 1) / kThreads;   // weight pieces per thread and slice
-  constexpr bool DMA = NP == 0;
   static_assert(!DMA || (MA == 2 && !ONE), "units of 256 positions");
   static_assert(!BITS || BWD, "mask bits belong to the input gradient");
   constexpr int WPOS = 32 * MA;   // positions per wavefront
@@ -606,6 +609,20 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
     };
     if (STATS && BWD) load_x(0);
     if (STATS && BWD && DMA) load_x(1);
+    u32x2 codes[UNPOOL ? MA : 1][NR];
+    if constexpr (UNPOOL) {
+      if (p.unpool) {
+#pragma unroll
+        for (int a = 0; a < MA; ++a)
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            const bool in = lane_pos + place(a, r) < npos && col0 + lane_c < p.N;
+            codes[a][r] = *reinterpret_cast<const u32x2*>(in ? p.unpool_code + (size_t)(out_base + place(a, r)) * p.N + col0 +
+                                                                   lane_at(p.N, lane_c)
+                                                             : static_cast<const uint8_t*>(p.zero));
+          }
+      }
+    }
     u32x4 kept[STATS ? MA : 1][NR];   // what was stored
 #pragma unroll
     for (int a = 0; a < MA; ++a) {
@@ -671,6 +688,15 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
       for (int r = 0; r < NR; ++r)   // N is a multiple of 8 (STATS: of 64): a piece is wholly inside or outside
         if (lane_pos + place(a, r) < npos && (STATS || col0 + lane_c < p.N))
           *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + place(a, r)) * p.N + col0 + lane_at(p.N, lane_c)) = stored[r];
+      if constexpr (UNPOOL) {
+        if (p.unpool) {
+#pragma unroll
+          for (int r = 0; r < NR; ++r)
+            if (lane_pos + place(a, r) < npos && col0 + lane_c < p.N)
+              unpool_store(p.unpool, (size_t)out_base + (lane_pos + place(a, r)), (lane_pos + place(a, r)) & (W - 1), W, p.N, col0 + lane_c,
+                           stored[r], codes[a][r]);
+        }
+      }
       if constexpr (POOL) {
 #pragma unroll
         for (int r = 0; r < NR; r += 2) pool_rows(a, r, stored[r], stored[r + 1]);
@@ -784,7 +810,8 @@ bool conv3_wide_takes(const ConvGeom& g, int N, bool pooled, bool relu, bool sha
 
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                      const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                     const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats) {
+                     const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats,
+                     UnpoolRequest* unpool) {
   const bool dma = g.frag == 2;   // (conv3_wide_takes has said yes)
   const int H = g.Hs, W = g.Ws;
   if (g.raw3 || g.ks != 3 || g.stride != 1 || g.pad != 1 || g.Hp != H || g.Wp != W) return false;
@@ -846,6 +873,8 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
     upw = (int)std::max(1L, ((long)units * tiles_n + resident - 1) / resident);
   }
   if (pooling) { p.pool = pool; p.pool_code = pool_code; }
+  const bool unpooling = unpool && g.transposed && ma == 2 && plain && !pooling && (dma || g.Cs == KC);
+  if (unpooling) { p.unpool = unpool->din; p.unpool_code = unpool->code; }
   // Batch-norm sums on the way out: no bias, no ReLU, and units and groups that do not cross from one worker to the next,
   // few enough groups for the statistics scratch.
   bool with_stats = false;
@@ -908,6 +937,7 @@ bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_
     else if (!w8 && need <= 18) launch_wide<4, 18, false>(st, p, grid, lds, bwd, false);
     else return false;
   }
+  if (unpooling) unpool->done = true;
   if (with_stats) {
     for (int k = 0; k <= p.gK; ++k) stats->table.first[k] = p.gfirst[k];
     stats->done = true;

@@ -1050,16 +1050,17 @@ bool conv_first_layer_raw_supported(int Cout, int cin_real, const ConvGeom& g, l
 
 bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                     const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                    bf16_t* pool_out, uint8_t* pool_code, const bf16_t* addend, BnStatRequest* stats) {
+                    bf16_t* pool_out, uint8_t* pool_code, const bf16_t* addend, BnStatRequest* stats,
+                    UnpoolRequest* unpool) {
   bool pooled = false;
   if (g.frag == 1)
-    return conv_frag_bf16(st, src, wgt, out, N, g, bias, mask, relu, accumulate, pool_out, pool_code, addend, stats);
+    return conv_frag_bf16(st, src, wgt, out, N, g, bias, mask, relu, accumulate, pool_out, pool_code, addend, stats, unpool);
   if (g.frag == 3) {
     conv_gather_bf16(st, src, wgt, out, N, g, bias, relu, stats);
     return false;
   }
   // 3x3 / stride 1 / pad 1: the wide-tile kernel where the shape and the amount of work allow it, else the 256-position one
-  if (conv3_wide_bf16(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, addend, pool_out, pool_code, stats))
+  if (conv3_wide_bf16(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, addend, pool_out, pool_code, stats, unpool))
     return pool_out && pool_code;
   if (conv3_gemm(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled, addend))
     return pooled;

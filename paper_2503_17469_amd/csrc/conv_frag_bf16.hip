@@ -65,6 +65,8 @@ struct FragParams {
   int relu, accumulate;
   bf16_t* pool;
   uint8_t* pool_code;
+  const uint8_t* unpool_code;   // BWD: see UnpoolRequest
+  bf16_t* unpool;
   const bf16_t *src2, *wgt2;   // stride-2 input gradient: the projection's output gradient (may be null) and weights
   double* stat_partial;   // [record][N][2] or null
   const bf16_t* stat_x;   // BWD: see BnStatRequest
@@ -124,6 +126,7 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
   for (int k = place.k0 + 1; MIXED && k <= place.k1; ++k)
     gk += place.n0 + (pos >> (p.wlog + p.rlog)) >= __builtin_amdgcn_readlane(place.ifirst, k) ? 1 : 0;
   u32x4 em[2], ea4[2], ex4[2];
+  u32x2 ecode[2];
   v4f mean[2][2];                                  // BWD with statistics: of this lane's channels
   uint32_t ebits = 0;
   if (BWD && p.stat_partial) {
@@ -146,6 +149,7 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
       const size_t idx = row + qq * 16 + h * 8;
       em[qq] = *reinterpret_cast<const u32x4*>((row_in && p.mask && !p.mask_bits) ? p.mask + idx : zp);
       ea4[qq] = *reinterpret_cast<const u32x4*>((row_in && other) ? other + idx : zp);
+      ecode[qq] = *reinterpret_cast<const u32x2*>((row_in && p.unpool) ? p.unpool_code + idx : static_cast<const uint8_t*>(p.zero));
     }
   }
   float bias8[2][8];
@@ -225,6 +229,8 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
 #pragma unroll
     for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
     if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
+    if (BWD && p.unpool && row_in)
+      unpool_store(p.unpool, out_pos, pos & ((1 << p.wlog) - 1), 1 << p.wlog, p.N, cb + qq * 16 + h * 8, outp[qq], ecode[qq]);
   }
 
   if (p.stat_partial) {
@@ -710,7 +716,7 @@ bool conv_frag_takes(const ConvGeom& g, int N) {
 
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
-                    const bf16_t* addend, BnStatRequest* stats) {
+                    const bf16_t* addend, BnStatRequest* stats, UnpoolRequest* unpool) {
   FragShape s;
   (void)frag_shape(g, N, s);
   const bool bwd = g.transposed != 0;
@@ -723,6 +729,11 @@ bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
   p.bias = bias; p.mask = mask; p.addend = addend; p.relu = relu ? 1 : 0; p.accumulate = accumulate ? 1 : 0;
   p.mask_bits = (mask && N % 64 == 0) ? g.mask_bits : nullptr;
   if (!bwd && pool && pool_code && s.R % 2 == 0 && g.Hp % 2 == 0) { p.pool = pool; p.pool_code = pool_code; }
+  if (bwd && unpool) {
+    p.unpool = unpool->din;
+    p.unpool_code = unpool->code;
+    unpool->done = true;
+  }
   const bool mixed = frag_tiles(p, s, g.rows, (bias || relu) ? nullptr : stats, bwd, 1);
   const int taps = g.ks * g.ks, tiles = p.tiles, tiles_n = (N + kTN - 1) / kTN;
   // an XCD's L2 sees the whole of one operand and about an eighth of the other

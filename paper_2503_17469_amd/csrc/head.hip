@@ -17,6 +17,8 @@
 #include "head_device.h"
 #include "kernels.h"
 #include "lds_barrier_device.h"
+#include "pool_device.h"
+#include "quotient.h"
 #include "update_device.h"
 
 namespace omni {
@@ -34,6 +36,10 @@ struct HeadFwdParams {
   int cols_each;         // column tiles of dx per workgroup of a group
   float *z, *dz, *loss_rows;
   void* dx;
+  const uint8_t* unpool_code;   // bf16: see UnpoolRequest
+  bf16_t* unpool;
+  int W, chan;                  // of the pooling's output
+  uint32_t by_w, by_chan;       // reciprocals of them below cin
 };
 // T is the storage type of the input rows, the weights and the input gradient (fp32, or bf16 with fp32 arithmetic);
 // CT = 16-class tiles, at least ceil(C / 16).  Sixteen rows per workgroup:
@@ -218,7 +224,13 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   const int col_tiles = (cin + 16 * EL - 1) / (16 * EL);
   auto column = [&](int ct) { return min((min(ct, col_tiles - 1) * 16 + r) * EL, cin - EL); };
   v4f xm[4], wt[4];
+  constexpr bool UNPOOL = EL == 8;
+  u32x2 code[4];
   auto fetch_cols = [&](int col) {
+    if (UNPOOL && p.unpool) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) code[v] = *reinterpret_cast<const u32x2*>(p.unpool_code + (size_t)min(row0 + 4 * g + v, rows - 1) * cin + col);
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) xm[v] = Ops::load(x + (size_t)min(row0 + 4 * g + v, rows - 1) * cin + col);
 #pragma unroll
@@ -289,8 +301,12 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
     const int col = column(ct);
     v4f o[EL];
     v4f mk[4];
+    u32x2 to[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) mk[v] = xm[v];
+    for (int v = 0; v < 4; ++v) {
+      mk[v] = xm[v];
+      if (UNPOOL) to[v] = code[v];
+    }
 #pragma unroll
     for (int t0 = 0; t0 < 4 * CT; t0 += 4) {
       if (t0 >= nt) break;
@@ -325,7 +341,17 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
       if (use_mask) Ops::unpack(mk[v], m);
 #pragma unroll
       for (int e = 0; e < EL; ++e) t[e] = !use_mask || m[e] > 0.f ? o[e][v] : 0.f;
-      if (row < rows) Ops::store(dx + (size_t)row * cin + col, t);
+      if (row >= rows) continue;
+      Ops::store(dx + (size_t)row * cin + col, t);
+      if constexpr (UNPOOL) {
+        if (p.unpool) {
+          u32x4 d;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) d[i] = pack_bf16(t[2 * i], t[2 * i + 1]);
+          const int at = quotient(col, p.by_chan, p.chan), y = quotient(at, p.by_w, p.W);   // (whole pieces of a position's channels)
+          unpool_store(p.unpool + (size_t)row * 4 * cin, at, at - y * p.W, p.W, p.chan, col - at * p.chan, d, to[v]);
+        }
+      }
     }
   }
 }
@@ -347,7 +373,7 @@ bool head_supported(int cin, int classes, const void* x, const void* w, bool bf1
 
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
                          const int32_t* labels, int cin, int classes, const Segments& seg, float* z, float* dz,
-                         float* loss_rows, bool use_mask, void* dx) {
+                         float* loss_rows, bool use_mask, void* dx, UnpoolRequest* unpool) {
   const int rows = seg.off[seg.K], groups = (rows + 15) / 16;
   // Several workgroups per sixteen rows where one each leaves half the chip idle: every one forms the logits, and the columns of dx
   // are shared out, down to one tile per SIMD (1024 columns, 480 rows: dx 6000 of a workgroup's 15700 cycles, shared by four 2400).
@@ -358,6 +384,12 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
   p.x = x; p.w = w; p.bias = bias; p.labels = labels; p.cin = cin; p.C = classes; p.rows = rows; p.K = seg.K; p.use_mask = use_mask ? 1 : 0;
   p.groups = groups; p.cols_each = (tiles + splits - 1) / splits;
   p.z = z; p.dz = dz; p.loss_rows = loss_rows; p.dx = dx;
+  if (unpool && bf16 && dx && unpool->C % Piece<bf16_t>::EL == 0) {
+    p.unpool = unpool->din; p.unpool_code = unpool->code;
+    p.W = unpool->W; p.chan = unpool->C;
+    p.by_w = reciprocal_below(p.W, cin); p.by_chan = reciprocal_below(p.chan, cin);
+    unpool->done = true;
+  }
   const dim3 grid(groups * splits);
 #define OMNI_HEAD(T, CT) \
   hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, CT>), grid, dim3(64 * head_waves<CT>()), 0, st, p, seg)

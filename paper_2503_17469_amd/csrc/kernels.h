@@ -108,11 +108,13 @@ bool linear_wgrad_f32_small(hipStream_t st, const LinearWgradJob* jobs, int n, s
 // arithmetic, logits, dz and all gradients of parameters are fp32 either way.
 // True if the fused head kernels can take this shape (else use the generic path).
 bool head_supported(int cin, int classes, const void* x, const void* w, bool bf16);
+struct UnpoolRequest;
 // z = x w^T + bias; loss_rows, dz = (softmax(z) - onehot)/b_k; optionally
-// dx = dz w, zeroed where x <= 0 if use_mask (dx may be null when the input needs no gradient).
+// dx = dz w, zeroed where x <= 0 if use_mask (dx may be null when the input needs no gradient).  unpool (bf16; may be null): x is a max
+// pooling's output, see there.
 void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w, const float* bias,
                          const int32_t* labels, int cin, int classes, const Segments& seg, float* z, float* dz,
-                         float* loss_rows, bool use_mask, void* dx);
+                         float* loss_rows, bool use_mask, void* dx, UnpoolRequest* unpool = nullptr);
 // Per worker: gw_k = dz_k^T x_k, gb_k = column sums of dz_k; plus L_k, the total
 // loss and the status word (bit 0: some label outside [0, classes)).
 void head_wgrad_loss(hipStream_t st, bool bf16, const HeadWgradParams& h, const Segments& seg);
@@ -178,6 +180,16 @@ struct BnStatRequest {
   ShareTable table;
   bool done;
 };
+// A kernel that forms the complete gradient of a 2 x 2 max pooling's output (out_grad of a tensor [rows][H][W][C]) may write the gradient of
+// its input [rows][2 H][2 W][C] beside it, from the pooling's codes, in place of maxpool2_bwd_coded_bf16; it then sets done.  What the
+// launch of its own costs beyond those bytes goes: three conv layers 3-32-64-128, 1024 images: classifier 8.2 + 6.4 us -> 12.7, 128 -> 64
+// channels on 8x8 14.8 + 8.3 -> 22.6; 128 images 7.2 + 4.6 -> 9.6 and 7.7 + 4.6 -> 9.5.
+struct UnpoolRequest {
+  const uint8_t* code;
+  bf16_t* din;
+  int W, C;
+  bool done;
+};
 // Hidden fully connected layers (gemm_bf16.hip); widths are multiples of 8.
 // c[M][N] = a[M][K] b[N][K]^T (+bias) (ReLU), zeroed where mask <= 0 (mask may be null): forward with b = the weight copy,
 // input gradient with b = the transposed copy.
@@ -207,7 +219,7 @@ size_t conv_wgrad_partial_floats();
 bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                     const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
                     bf16_t* pool_out = nullptr, uint8_t* pool_code = nullptr, const bf16_t* addend = nullptr,
-                    BnStatRequest* stats = nullptr);
+                    BnStatRequest* stats = nullptr, UnpoolRequest* unpool = nullptr);
 // The kernel for few positions (conv_frag_bf16.hip), on weights in operand order: blocks [N/32][taps][Cs/16] of 64 lanes x
 // 8 elements, output n % 32 and channels 8 * (lane / 32) .. + 7 of the sixteen in lane n % 32 + 32 * ((c % 16) / 8).
 // conv_frag_takes tells which launches it is for.
@@ -220,7 +232,7 @@ void conv_gather_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16
                       bool relu, BnStatRequest* stats);
 bool conv_frag_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int N, const ConvGeom& g,
                     const float* bias, const bf16_t* mask, bool relu, bool accumulate, bf16_t* pool, uint8_t* pool_code,
-                    const bf16_t* addend, BnStatRequest* stats);
+                    const bf16_t* addend, BnStatRequest* stats, UnpoolRequest* unpool);
 // The same for the input gradient of a residual block's entry (as conv3s2_dgrad_bf16, weights in operand order; Cs2: channels of
 // dys, 0 without; sums: a batch norm below is expected to ask for its sums).
 bool conv_frag_s2_takes(int rows, int H, int W, int N, int Cs, int Cs2, bool sums);
@@ -231,7 +243,7 @@ void conv_frag_s2_bf16(hipStream_t st, const bf16_t* dy, const bf16_t* wt, int C
 // conv_gemm_bf16 (with pool and pool_code both are written); false, with nothing launched, if the shape does not qualify.
 bool conv3_wide_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                      const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                     const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats);
+                     const bf16_t* addend, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats, UnpoolRequest* unpool);
 // Input gradient of a residual block's entry (conv3s2_dgrad_bf16.hip): dx [rows][H][W][Cin] receives the gradient
 // coming back through a 3x3 / stride-2 / pad-1 convolution (dy [rows][H/2][W/2][Cout], wt its transposed weights
 // [Cin][9][Cout]) and, if dy_sc is not null, through the 1x1 / stride-2 projection beside it (dy_sc

@@ -865,8 +865,31 @@ void step_bf16(StepCtx& c) {
     }
   }
 
-  // ---- classifier head: logits, loss, dz (with 1/b_k), first input gradient, head parameter gradients
   std::vector<char> written(net->tensors.size(), 0);
+  // The max pooling whose output is tensor t, where the next gradient written to t is the whole of it and the pooling's own backward
+  // pass would be a launch of its own from its codes: the kernel that forms that gradient is offered to write the pooling's too.
+  std::vector<char> unpooled(n_layers, 0);   // poolings whose backward pass has been done that way
+  auto producer_of = [&](int t, int below) {
+    for (int j = below - 1; j >= 0; --j)
+      if (!net->layers[j].fused_away && net->layers[j].out == t) return j;
+    return -1;
+  };
+  // (the backward pass of a pooling behind a first layer that reads the pooled gradient itself)
+  auto pooled_for_first = [&](int prod) {
+    return prod >= 0 && net->layers[prod].d.op == OMNI_OP_CONV && net->layers[prod].in0 < 0 &&
+           omni::conv_wgrad_pooled_supported(net->layers[prod].d.cout, net->layers[prod].d.cin, fwd_geom(net->layers[prod]));
+  };
+  auto unpool_at = [&](int t, omni::UnpoolRequest& r) {
+    const int pl = t < 0 || net->tensors[t].consumers != 1 || written[t] ? -1 : producer_of(t, n_layers - 1);
+    if (pl < 0 || net->layers[pl].d.op != OMNI_OP_MAXPOOL2 || !coded[pl]) return -1;
+    const Layer& P = net->layers[pl];
+    if (pooled_for_first(producer_of(P.in0, pl))) return -1;
+    r = omni::UnpoolRequest{reinterpret_cast<const uint8_t*>(c.ws + P.code_off),
+                            reinterpret_cast<bf16_t*>(c.ws + net->tensors[P.in0].grad_off), P.iw / 2, P.ic, false};
+    return pl;
+  };
+
+  // ---- classifier head: logits, loss, dz (with 1/b_k), first input gradient, head parameter gradients
   // the classifier's parameter gradients and losses run beside the first input gradient of a fully connected network, else
   // with the last weight gradients
   omni::HeadWgradParams head_grads{};
@@ -877,10 +900,13 @@ void step_bf16(StepCtx& c) {
     float* z = reinterpret_cast<float*>(c.ws + net->tensors[logits].act_off);
     float* dz = reinterpret_cast<float*>(c.ws + net->tensors[logits].grad_off);
     const bool need_dx = last.in0 >= 0;
+    omni::UnpoolRequest unpool{};
+    const int pl = unpool_at(last.in0, unpool);
     omni::head_fwd_loss_dgrad(st, true, act(last.in0), shadow + last.wsh_off,
                               last.has_b ? c.params + last.b_off : nullptr, c.labels, last.d.cin, last.d.cout, c.seg,
                               z, dz, c.loss_rows, need_dx && net->tensors[last.in0].relu,
-                              need_dx ? grad(last.in0) : nullptr);
+                              need_dx ? grad(last.in0) : nullptr, pl >= 0 ? &unpool : nullptr);
+    if (pl >= 0 && unpool.done) unpooled[pl] = 1;
     if (need_dx) written[last.in0] = 1;
     head_grads = omni::HeadWgradParams{dz, act(last.in0), c.labels, last.d.cin, last.d.cout, c.G + last.w_off,
                                        last.has_b ? c.G + last.b_off : nullptr, net->P_stride, c.loss_rows,
@@ -1040,9 +1066,12 @@ void step_bf16(StepCtx& c) {
             offer.x = act(net->layers[bn].in0);
             offer.stats = bn_area + net->layers[bn].stat_off;
           }
+          omni::UnpoolRequest unpool{};
+          const int pl = unpool_at(L.in0, unpool);
           omni::conv_gemm_bf16(st, grad(L.out), shadow + L.wt_off, grad(L.in0), m_rows, L.cin_pad, d, nullptr,
                                ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend,
-                               bn >= 0 ? &offer : nullptr);
+                               bn >= 0 ? &offer : nullptr, pl >= 0 ? &unpool : nullptr);
+          if (pl >= 0 && unpool.done) unpooled[pl] = 1;
           if (offer.done) { presummed = offer.table; presummed_for = bn; }
         }
         written[L.in0] = 1;
@@ -1050,12 +1079,10 @@ void step_bf16(StepCtx& c) {
       if (group_full) start_group(ready, i);
       if (!conv) linear_jobs.push_back(linear_job(L));
     } else if (L.d.op == OMNI_OP_MAXPOOL2) {
-      int prod = -1;   // the layer that produced the pooling's input
-      for (int j = i - 1; j >= 0 && prod < 0; --j)
-        if (!net->layers[j].fused_away && net->layers[j].out == L.in0) prod = j;
-      if (coded[i] && prod >= 0 && net->layers[prod].d.op == OMNI_OP_CONV && net->layers[prod].in0 < 0 &&
-          omni::conv_wgrad_pooled_supported(net->layers[prod].d.cout, net->layers[prod].d.cin,
-                                            fwd_geom(net->layers[prod]))) {
+      const int prod = producer_of(L.in0, i);
+      if (unpooled[i]) {
+        // (written with the gradient of its output)
+      } else if (coded[i] && pooled_for_first(prod)) {
         pooled_from[prod] = i;
         not_stored[L.in0] = 1;
       } else if (coded[i])

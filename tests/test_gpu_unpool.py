@@ -1,0 +1,48 @@
+"""The gradient of a max pooling's input, written by the kernel that forms the gradient of its output (the classifier, the kernel of few
+positions, the wide one with one slice of the reduction and several) or by a launch of its own: bit for bit the output's gradient at
+the window's first maximum, zero elsewhere and where the maximum is zero."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hw,chans,B,cuts", [
+    (32, (3, 32, 64, 128), 37, [0, 5, 37]),         # few positions everywhere; classifier: several workgroups per sixteen rows
+    (32, (3, 32, 64, 128), 1030, [0, 1, 600, 1030]),  # 8x8: wide, last unit two of four images
+    (32, (3, 64, 96, 64), 523, [0, 523]),           # 8x8: channel tiles of 64 and of 32
+    (32, (3, 64, 64, 32), 1100, [0, 3, 1100]),      # 8x8: one slice, weights kept
+    (16, (3, 32, 40, 64), 130, [0, 64, 130]),       # 40 channels: a launch of its own on 4x4
+    (32, (3, 32, 24, 72), 70, [0, 70]),             # 72 channels at the classifier, positions counted without powers of two
+])
+def test_pooling_gradients(hw, chans, B, cuts):
+    import torch
+    import paper_2503_17469_amd as omni
+    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
+    params = synth.he_normal_params(layers, 6, True)
+    x = torch.randn(B, hw, hw, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(B)).to(torch.bfloat16)
+    labels = torch.arange(B, device="cuda", dtype=torch.int32) % 10
+    K = len(cuts) - 1
+    net = omni.net_create(layers, (hw, hw, 3), "bf16", K, B)
+    ws = torch.zeros(omni.net_workspace_bytes(net), dtype=torch.uint8, device="cuda")
+    omni.step(net, torch.from_numpy(params).cuda(), x, labels, cuts, list(np.diff(cuts).tolist()), 0.0, ws, torch.zeros(K, device="cuda"),
+              torch.zeros(1, device="cuda"), omni.STEP_NO_UPDATE)
+    torch.cuda.synchronize()
+    for n, pool in enumerate([i for i, L in enumerate(layers) if L["op"] == "maxpool2"]):
+        if n == 0:
+            continue                                 # (the first layer's weight gradient reads the pooled one itself)
+        s, c = hw >> n + 1, chans[n + 1]
+
+        def windows(t):
+            return t.reshape(B, s, 2, s, 2, c).permute(0, 1, 3, 5, 2, 4).reshape(B, s, s, c, 4)
+
+        a = windows(omni.net_activation(net, ws, pool - 1, B, "bf16"))
+        got = windows(omni.net_activation_grad(net, ws, pool - 1, B, "bf16"))
+        d = omni.net_activation_grad(net, ws, pool, B, "bf16").reshape(B, s, s, c, 1)
+        m = a.max(-1, keepdim=True).values
+        first = torch.zeros_like(a).scatter_(-1, (a == m).float().argmax(-1, keepdim=True), 1.0)
+        assert d.abs().max() > 0
+        assert torch.equal(got, torch.where((first > 0) & (m > 0), d.expand_as(a), torch.zeros_like(a))), (n, s, c)
+    omni.net_destroy(net)
