@@ -374,6 +374,10 @@ void weighted_sgd_f32(hipStream_t st, float* params, const float* grads, size_t 
                       float momentum = 0.f, float weight_decay = 0.f, const KernelTimer* timer = nullptr,
                       float* gout = nullptr);
 // (gout, [P] or null, also receives the aggregated gradient sum_k lambda[k] * grads[k].)
+// The same sums and updates for some of the parameters: beg .. end - 1 of each range, beg a multiple of 4; by `workgroups` at most.
+struct ParamRange { size_t beg, end; };
+void weighted_sgd_ranges_f32(hipStream_t st, const SgdArgs& sgd, const float* grads, size_t stride, const ParamRange* ranges, int n,
+                             const Segments& seg, int workgroups);
 // The aggregation alone: gout[j] = sum_k lambda[k] * grads[k*stride + j].
 void weighted_reduce_f32(hipStream_t st, const float* grads, size_t stride, size_t P, const Segments& seg,
                          float* gout);

@@ -511,6 +511,7 @@ struct StepCtx {
   float lr;
   bool fuse_update;      // the weight-gradient launch applies the update where it can
   bool updated;          // it has
+  std::vector<omni::ParamRange> covered;   // ... or launches on the side streams have updated these parameters
 };
 
 // ------------------------------------------------------------------ fp32 path
@@ -947,6 +948,28 @@ void step_bf16(StepCtx& c) {
   bool second = false;
   std::vector<omni::ConvWgradJob> group;
   double group_work = 0.0;
+  // The update of a group's weights follows its second stage on the side stream where they are many: at the step's end nothing ran beside
+  // it (K + 2 times 4 bytes a parameter, 11.2 M in 45 us with four workers).  The forward pass and the input gradients read copies.
+  // One workgroup per compute unit: with a great many the memory is theirs and the chain's next kernel waits (a batch norm's first
+  // stage 9 -> 31 us), with few the next group on the stream does.  Step of the ResNet-18 shape in us, update at the end / here with 32 / 128 /
+  // 256 / 512 workgroups: four workers, 96 images 1223 / - / 1212 / 1208 / 1214, 128 images 1356 / 1388 / 1345 / 1342 / 1345; sixteen, 300 images 2528 / - /
+  // 2474 / 2476 / 2481; four, 512 images 3425 / - / 3410 / 3400 / 3420; eight, 2048 images 10706 / - / 10671 / 10677 / 10680; one, 32 images 872 / 875 / 869.
+  constexpr size_t kGroupUpdate = 1u << 18;   // parameters
+  constexpr int kGroupUpdateWorkgroups = 256;
+  auto update_group = [&](hipStream_t side) {
+    std::vector<omni::ParamRange> ranges;
+    size_t total = 0;
+    for (const omni::ConvWgradJob& j : group) {
+      const size_t beg = j.gw - c.G, n = (size_t)j.Cout * j.g.ks * j.g.ks * j.cin_real;
+      if (beg % 4 != 0 || n % 4 != 0) continue;   // (the rest then begins at a multiple of 4 too)
+      ranges.push_back({beg, beg + n});
+      total += n;
+    }
+    if (!c.fuse_update || total < kGroupUpdate || net->P > UINT32_MAX) return;
+    omni::weighted_sgd_ranges_f32(side, omni::SgdArgs{c.params, net->velocity, c.lr, net->momentum, net->weight_decay}, c.G, net->P_stride,
+                                  ranges.data(), (int)ranges.size(), c.seg, kGroupUpdateWorkgroups);
+    c.covered.insert(c.covered.end(), ranges.begin(), ranges.end());
+  };
   auto start_group = [&](hipEvent_t ready, int layer) {
     const bool use2 = second && c.side2 != c.side;
     second = !second;
@@ -954,10 +977,13 @@ void step_bf16(StepCtx& c) {
     c.forked = true;
     if (use2) c.forked2 = true;
     hipStream_t side = use2 ? c.side2 : c.side;
-    TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
-    omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
-                           omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups, nullptr, nullptr, 0, false,
-                           norms_below(layer) >= kRoomNorms);
+    {
+      TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
+      omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
+                             omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups, nullptr, nullptr, 0, false,
+                             norms_below(layer) >= kRoomNorms);
+    }
+    update_group(side);
     group.clear();
     group_work = 0.0;
   };
@@ -1269,6 +1295,17 @@ int omni::step_impl(omni_net* net, void* stream, float* params, const void* x, c
   // ---- weighted aggregation + update
   float* reduced = (flags & OMNI_STEP_KEEP_REDUCED_GRAD) ? reinterpret_cast<float*>(c.ws + net->reduced_off) : nullptr;
   if (c.updated) {
+  } else if (!c.covered.empty()) {   // what is left
+    std::sort(c.covered.begin(), c.covered.end(), [](const omni::ParamRange& a, const omni::ParamRange& b) { return a.beg < b.beg; });
+    std::vector<omni::ParamRange> rest;
+    size_t at = 0;
+    for (const omni::ParamRange& r : c.covered) {
+      if (r.beg > at) rest.push_back({at, r.beg});
+      at = r.end;
+    }
+    if (net->P > at) rest.push_back({at, net->P});
+    omni::weighted_sgd_ranges_f32(c.st, omni::SgdArgs{params, net->velocity, lr, net->momentum, net->weight_decay}, c.G, net->P_stride,
+                                  rest.data(), (int)rest.size(), c.seg, 2048);
   } else if (!(flags & OMNI_STEP_NO_UPDATE)) {
     TimedScope ts(net, c.st, OMNI_KERNEL_UPDATE, -1, true);
     omni::weighted_sgd_f32(c.st, params, c.G, net->P_stride, net->P, c.seg, lr, nullptr, net->velocity,

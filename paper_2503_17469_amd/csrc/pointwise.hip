@@ -235,6 +235,64 @@ __global__ __launch_bounds__(256) void weighted_sgd_few_kernel(float* __restrict
   if (blockIdx.x == 0) weighted_sgd_tail<SHADOW, MOM, KEEPG>(params, velocity, grads, stride, P, K, lam, opt, shadow, gout);
 }
 
+// The same for ranges of the parameters, 1024 columns of one range at a time; four loads of each of four workers on their way.
+constexpr int kRangesMax = 32;
+struct RangeTable {
+  int n, pieces;
+  int32_t first[kRangesMax];   // range i has the pieces first[i] on, 1024 columns each
+  uint32_t beg[kRangesMax], end[kRangesMax];
+};
+template <bool MOM>
+__global__ __launch_bounds__(256) void weighted_sgd_ranges_kernel(float* __restrict__ params, float* __restrict__ velocity,
+                                                                  const float* __restrict__ grads, size_t stride, RangeTable tab,
+                                                                  int K, Lambdas lam, Optim opt) {
+  const int lane = threadIdx.x & (kRangesMax - 1), mine = tab.first[lane];   // (all lanes at once)
+  for (int piece = blockIdx.x; piece < tab.pieces; piece += gridDim.x) {
+    const int at = __popcll(__ballot((int)(threadIdx.x & 63) < tab.n && mine <= piece)) - 1;
+    const int part = piece - __builtin_amdgcn_readlane(mine, at);
+    const size_t beg = tab.beg[at], n = tab.end[at] - beg, n4 = n / 4, c0 = (size_t)part * 1024 + threadIdx.x;
+    float* const th_at = params + beg;
+    float* const ve_at = MOM ? velocity + beg : nullptr;
+    const float* const g_at = grads + beg;
+    if (n4 > 0) {
+      size_t j[4];
+      v4f th[4], ve[4], g[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        j[u] = 4 * min(c0 + 256 * u, n4 - 1);
+        th[u] = *reinterpret_cast<const v4f*>(th_at + j[u]);
+        ve[u] = MOM ? *reinterpret_cast<const v4f*>(ve_at + j[u]) : v4f{0.f, 0.f, 0.f, 0.f};
+        g[u] = v4f{0.f, 0.f, 0.f, 0.f};
+      }
+      int k = 0;
+      for (; k + 4 <= K; k += 4) {
+        v4f a[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            a[q][u] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(g_at + (size_t)(k + q) * stride + j[u]));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) g[u] += lam.v[k + q] * a[q][u];
+      }
+      for (; k < K; ++k)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          g[u] += lam.v[k] * __builtin_nontemporal_load(reinterpret_cast<const v4f*>(g_at + (size_t)k * stride + j[u]));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (c0 + 256 * u >= n4) continue;
+        apply_update<MOM>(th[u], ve[u], g[u], opt);
+        *reinterpret_cast<v4f*>(th_at + j[u]) = th[u];
+        if (MOM) *reinterpret_cast<v4f*>(ve_at + j[u]) = ve[u];
+      }
+    }
+    if (part == 0) weighted_sgd_tail<false, MOM, false>(th_at, ve_at, g_at, stride, n, K, lam, opt, nullptr, nullptr);
+  }
+}
+
 // g = sum_k lambda_k G[k] alone (equation bspweightedgrads without the update), same summation order.
 __global__ __launch_bounds__(256) void weighted_reduce_kernel(const float* __restrict__ grads, size_t stride, size_t P,
                                                               int K, Lambdas lam, float* __restrict__ gout) {
@@ -297,6 +355,25 @@ void weighted_sgd_f32(hipStream_t st, float* params, const float* grads, size_t 
 #undef OMNI_UPD2
 #undef OMNI_UPD
 #undef OMNI_UPD_
+}
+
+void weighted_sgd_ranges_f32(hipStream_t st, const SgdArgs& sgd, const float* grads, size_t stride, const ParamRange* ranges, int n,
+                             const Segments& seg, int workgroups) {
+  const Lambdas lam = lambdas_of(seg);
+  const Optim opt{sgd.lr, sgd.momentum, sgd.weight_decay};
+  for (int base = 0; base < n; base += kRangesMax) {
+    RangeTable tab{};
+    tab.n = std::min(n - base, kRangesMax);
+    for (int i = 0; i < tab.n; ++i) {
+      const ParamRange& r = ranges[base + i];
+      tab.first[i] = tab.pieces;
+      tab.beg[i] = (uint32_t)r.beg;
+      tab.end[i] = (uint32_t)r.end;
+      tab.pieces += (int)std::max<size_t>((r.end - r.beg + 4095) / 4096, 1);
+    }
+    const auto kernel = sgd.velocity ? weighted_sgd_ranges_kernel<true> : weighted_sgd_ranges_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(std::min(tab.pieces, workgroups)), dim3(256), 0, st, sgd.params, sgd.velocity, grads, stride, tab, seg.K, lam, opt);
+  }
 }
 
 void weighted_reduce_f32(hipStream_t st, const float* grads, size_t stride, size_t P, const Segments& seg,

@@ -1,0 +1,39 @@
+"""The update of groups of weights on the side streams, and of what is left at the end: bit for bit what one launch over all
+parameters gives."""
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("widths,K,b,momentum", [
+    ((64, 128, 256, 512), 1, 5, False),
+    ((64, 128, 256, 512), 3, 7, True),
+    ((64, 128, 256, 512), 9, 3, False),
+    ((64, 128, 256, 200), 6, 4, True),      # the widest group's layers end inside pieces of 1024 columns
+])
+def test_groups_match_one_launch(widths, K, b, momentum):
+    import torch
+    import paper_2503_17469_amd as omni
+    layers, B = synth.resnet18(37, widths=widths), K * b
+    params = torch.from_numpy(synth.he_normal_params(layers, 3, True)).cuda()
+    gen = torch.Generator("cuda").manual_seed(K)
+    x = torch.randn(B, 32, 32, 3, device="cuda", generator=gen).to(torch.bfloat16)
+    labels = torch.arange(B, device="cuda", dtype=torch.int32) % 37
+    velocity = torch.randn(params.numel(), device="cuda", generator=gen) * 0.01
+    got = []
+    for flags in (0, omni.STEP_KEEP_REDUCED_GRAD):   # (which wants the update as one launch)
+        net = omni.net_create(layers, (32, 32, 3), "bf16", K, B)
+        p, v = params.clone(), velocity.clone()
+        if momentum:
+            omni.net_set_momentum(net, v, 0.9, 5e-4)
+        ws = torch.zeros(omni.net_workspace_bytes(net), dtype=torch.uint8, device="cuda")
+        for _ in range(2):
+            omni.step(net, p, x, labels, [b * k for k in range(K + 1)], [b] * K, 0.05, ws, torch.zeros(K, device="cuda"),
+                      torch.zeros(1, device="cuda"), flags)
+        torch.cuda.synchronize()
+        omni.net_destroy(net)
+        got.append((p, v))
+    assert not torch.equal(got[0][0], params)
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
