@@ -211,6 +211,7 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
 #pragma unroll
   for (int q = 0; q < (WGRAD && UPD ? kPieces : 1); ++q) gsum[q] = v4f{0.f, 0.f, 0.f, 0.f};
   float bgsum = 0.f;
+  v4f theta[WGRAD && UPD ? kPieces : 1], vel[WGRAD && UPD == 2 ? kPieces : 1];   // of those pieces
   bool notfinite = false;
 
   auto take = [&](Slab s) {       // registers of slab s made ready for LDS
@@ -333,6 +334,87 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
     s0 = s1; s1 = s2; s2 = s3;
     return ended;
   };
+  auto flush = [&](auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    // The chunk's tile goes out through the stage that is free (slab s0's, whose fragments are in registers) and the extra area.
+    a.arrived();
+    b.arrived();
+    int ft = tid;
+    asm volatile("" : "+v"(ft));      // (addresses are worked out here, not kept in registers through the loop)
+    float* C = p.C + (size_t)done.w * p.c_worker_stride;
+    float* out = reinterpret_cast<float*>(cur == 1 ? lds + kStage : lds);
+    if (want_bias_grad) bred[Operand<A_MC>::k8_of(ft)][Operand<A_MC>::row_of(ft)] = bsum;
+    const bool cont = done.pieces & kCont;       // added to the worker's earlier chunks
+    const bool whole = !cont && row0 + kTile <= p.M && col0 + kTile <= p.N;
+    // The update takes G once it is complete, as one in a launch of its own does: the same bits.
+    const bool complete = !(done.pieces & kMore);
+    const float weight = UPD ? lam->v[done.w] : 0.f;
+    // The update's parameters set out in front of the last chunk's stores: behind them they would wait for those.  Step of the 3072
+    // net in us, behind / in front: one worker, 500 rows 106 / 103; four, 480 rows 111.2 / 109.4, with momentum 118.2 / 114.0; eight, 1000 rows
+    // 213.9 / 213.4; sixteen, 4096 rows 568 / 561.  (This copy of the flush stands behind the loop: inside it they spilled.)
+    if constexpr (UPD != 0 && LAST) {
+#pragma unroll
+      for (int q = 0; q < kPieces; ++q) {
+        const int part = q / (kPieces / kParts), idx = ft + kThreads * (q % (kPieces / kParts));
+        const int row = row0 + part * kFlushRows + idx / (kTile / 4), col = col0 + (idx % (kTile / 4)) * 4;
+        const size_t e0 = row < p.M && col + 4 <= p.N ? (size_t)row * p.ldc + col : 0;
+        theta[q] = *reinterpret_cast<const v4f_a4*>(p.theta + e0);
+        if (UPD == 2) vel[UPD == 2 ? q : 0] = *reinterpret_cast<const v4f_a4*>(p.velocity + e0);
+      }
+    }
+#pragma unroll
+    for (int part = 0; part < kParts; ++part) {
+      __syncthreads();
+      if (wrow / kFlushRows == part) {
+        float* o = out + share * kFlushRows * kFlushPitch;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+              o[(32 * i + 4 * (ft >> 5 & 1) + 8 * (v / 4) + (v % 4)) * kFlushPitch + wcol + 32 * j + (ft & 31)] = tot[i][j][v];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kPieces / kParts; ++q) {
+        const int idx = ft + kThreads * q, r = idx / (kTile / 4), c4 = (idx % (kTile / 4)) * 4;
+        const float* o = out + r * kFlushPitch + c4;
+        v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale -
+                *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
+        const int row = row0 + part * kFlushRows + r;
+        float* dst = C + (size_t)row * p.ldc + col0 + c4;
+        if (whole) {
+          *reinterpret_cast<v4f_a4*>(dst) = g;
+        } else if (row < p.M) {
+          // (16 bytes at a time as well: element by element, 1021 x 3400 outputs of 32 workers took 54 us longer, and the eight
+          // pieces of a worker with 4096 rows 37)
+          if (col0 + c4 + 4 <= p.N) {
+            v4f_a4* const to = reinterpret_cast<v4f_a4*>(dst);
+            if (cont) g += *to;
+            *to = g;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+              if (col0 + c4 + e < p.N) {
+                if (cont) g[e] += dst[e];
+                dst[e] = g[e];
+              }
+          }
+        }
+        if (UPD && complete) gsum[part * (kPieces / kParts) + q] += weight * g;
+      }
+    }
+    if (want_bias_grad && ft < kTile) {
+      float g = (bred[0][ft] + bred[1][ft]) + (bred[2][ft] + bred[3][ft]);
+      if (row0 + ft < p.M) {
+        float* dst = p.bias_grad + (size_t)done.w * p.c_worker_stride + row0 + ft;
+        if (cont) g += *dst;
+        *dst = g;
+      }
+      if (UPD && complete) bgsum += weight * g;
+    }
+  };
   for (;;) {
     if constexpr (!WGRAD) {
       for (bool ended = false; !ended;) {
@@ -359,72 +441,9 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
         for (int v = 0; v < 16; ++v) bad += tot[i][j][v] * 0.f;
     notfinite = notfinite || bad != bad;
 
+    if (!WGRAD || s0.w >= nrange) break;
     if constexpr (WGRAD) {
-      // The chunk's tile goes out through the stage that is free (slab s0's, whose fragments are in registers) and the extra area.
-      a.arrived();
-      b.arrived();
-      int ft = tid;
-      asm volatile("" : "+v"(ft));      // (addresses are worked out here, not kept in registers through the loop)
-      float* C = p.C + (size_t)done.w * p.c_worker_stride;
-      float* out = reinterpret_cast<float*>(cur == 1 ? lds + kStage : lds);
-      if (want_bias_grad) bred[Operand<A_MC>::k8_of(ft)][Operand<A_MC>::row_of(ft)] = bsum;
-      const bool cont = done.pieces & kCont;       // added to the worker's earlier chunks
-      const bool whole = !cont && row0 + kTile <= p.M && col0 + kTile <= p.N;
-      // The update takes G once it is complete, as one in a launch of its own does: the same bits.
-      const bool complete = !(done.pieces & kMore);
-      const float weight = UPD ? lam->v[done.w] : 0.f;
-#pragma unroll
-      for (int part = 0; part < kParts; ++part) {
-        __syncthreads();
-        if (wrow / kFlushRows == part) {
-          float* o = out + share * kFlushRows * kFlushPitch;
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int v = 0; v < 16; ++v)
-                o[(32 * i + 4 * (ft >> 5 & 1) + 8 * (v / 4) + (v % 4)) * kFlushPitch + wcol + 32 * j + (ft & 31)] = tot[i][j][v];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kPieces / kParts; ++q) {
-          const int idx = ft + kThreads * q, r = idx / (kTile / 4), c4 = (idx % (kTile / 4)) * 4;
-          const float* o = out + r * kFlushPitch + c4;
-          v4f g = *reinterpret_cast<const v4f*>(o) * kSplitUnscale -
-                  *reinterpret_cast<const v4f*>(o + kFlushRows * kFlushPitch) * kSplitUnscale;   // (each: the sum may be large)
-          const int row = row0 + part * kFlushRows + r;
-          float* dst = C + (size_t)row * p.ldc + col0 + c4;
-          if (whole) {
-            *reinterpret_cast<v4f_a4*>(dst) = g;
-          } else if (row < p.M) {
-            // (16 bytes at a time as well: element by element, 1021 x 3400 outputs of 32 workers took 54 us longer, and the eight
-            // pieces of a worker with 4096 rows 37)
-            if (col0 + c4 + 4 <= p.N) {
-              v4f_a4* const to = reinterpret_cast<v4f_a4*>(dst);
-              if (cont) g += *to;
-              *to = g;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 3; ++e)
-                if (col0 + c4 + e < p.N) {
-                  if (cont) g[e] += dst[e];
-                  dst[e] = g[e];
-                }
-            }
-          }
-          if (UPD && complete) gsum[part * (kPieces / kParts) + q] += weight * g;
-        }
-      }
-      if (want_bias_grad && ft < kTile) {
-        float g = (bred[0][ft] + bred[1][ft]) + (bred[2][ft] + bred[3][ft]);
-        if (row0 + ft < p.M) {
-          float* dst = p.bias_grad + (size_t)done.w * p.c_worker_stride + row0 + ft;
-          if (cont) g += *dst;
-          *dst = g;
-        }
-        if (UPD && complete) bgsum += weight * g;
-      }
+      flush(std::false_type{});
       __syncthreads();      // (the free stage is written again)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -435,8 +454,8 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
       bsum = bnext;
       bnext = bpart;
     }
-    if (!WGRAD || s0.w >= nrange) break;
   }
+  if constexpr (WGRAD) flush(std::true_type{});
 
   // Sums that are not finite once more, from memory, in pieces of 32 elements; what is finite stays (a row's results do not depend
   // on other rows).  Here, where nothing else is in registers: beside the loop it spilled, and the spills' waits were the stores'.
@@ -507,28 +526,27 @@ __device__ __forceinline__ void split_body(const SplitParams& p, const Segments&
       if (row >= p.M || col >= p.N) continue;
       const size_t e0 = (size_t)row * p.ldc + col;
       if (col + 4 <= p.N) {
-        v4f th = *reinterpret_cast<const v4f_a4*>(p.theta + e0), vel = {0.f, 0.f, 0.f, 0.f};
-        if (MOM) vel = *reinterpret_cast<const v4f_a4*>(p.velocity + e0);
-        apply_update<MOM>(th, vel, gsum[q], *opt);
+        v4f th = theta[q], ve = vel[MOM ? q : 0];
+        apply_update<MOM>(th, ve, gsum[q], *opt);
         *reinterpret_cast<v4f_a4*>(p.theta + e0) = th;
-        if (MOM) *reinterpret_cast<v4f_a4*>(p.velocity + e0) = vel;
+        if (MOM) *reinterpret_cast<v4f_a4*>(p.velocity + e0) = ve;
       } else {
 #pragma unroll
         for (int e = 0; e < 3; ++e) {
           if (col + e >= p.N) continue;
-          float th = p.theta[e0 + e], vel = MOM ? p.velocity[e0 + e] : 0.f;
+          float th = p.theta[e0 + e], ve = MOM ? p.velocity[e0 + e] : 0.f;
           const float g = gsum[q][e];
-          apply_update<MOM>(th, vel, g, *opt);
+          apply_update<MOM>(th, ve, g, *opt);
           p.theta[e0 + e] = th;
-          if (MOM) p.velocity[e0 + e] = vel;
+          if (MOM) p.velocity[e0 + e] = ve;
         }
       }
     }
     if (want_bias_grad && tid < kTile && row0 + tid < p.M) {
-      float th = p.theta_bias[row0 + tid], vel = MOM ? p.velocity_bias[row0 + tid] : 0.f;
-      apply_update<MOM>(th, vel, bgsum, *opt);
+      float th = p.theta_bias[row0 + tid], ve = MOM ? p.velocity_bias[row0 + tid] : 0.f;
+      apply_update<MOM>(th, ve, bgsum, *opt);
       p.theta_bias[row0 + tid] = th;
-      if (MOM) p.velocity_bias[row0 + tid] = vel;
+      if (MOM) p.velocity_bias[row0 + tid] = ve;
     }
   }
   if constexpr (!WGRAD) {
