@@ -332,7 +332,15 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const bf16_t* __restrict_
 // behind.  A launch of its own for them took 4-5 us of every batch norm, forward and backward: 180 of the 1700 us of a
 // ResNet-18 step at 128 images.
 constexpr int kFinishRecords = 64;
-template <bool BWD>
+// TWIN (backward): the records of another batch norm's sums, one of every workgroup (BnTwinSums).  A launch of its own for them read dy again
+// (128 images of the ResNet-18 shape: 4.9 to 12.5 us in each of three blocks).  Step in us, with that launch / without: one worker, 32 images
+// 868 / 862; eight, 40 images 992 / 982; four, 64 images 1053 / 1041, 128 images 1334 / 1327, 512 images 3348 / 3334; sixteen, 300 images 2441 / 2435.
+struct TwinIn {
+  const bf16_t* x;
+  const float* stats;
+  double* partial;
+};
+template <bool BWD, bool TWIN>
 __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                         const double* __restrict__ partial, ShareTable rec,
                                                         float* __restrict__ stats, const float* __restrict__ gamma,
@@ -340,7 +348,8 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
                                                         float* __restrict__ g_beta, size_t worker_stride, int C, int hw,
                                                         Segments seg, ShareTable tb, int relu, bf16_t* __restrict__ out,
                                                         const bf16_t* __restrict__ skip, int relu_add,
-                                                        uint8_t* __restrict__ sign_bits) {
+                                                        uint8_t* __restrict__ sign_bits, TwinIn twin) {
+  static_assert(!TWIN || BWD, "sums of output gradients");
   __shared__ double red[4][64][2];
   __shared__ float fin[64][2];
   const int tid = threadIdx.x;
@@ -351,11 +360,12 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
   const int per = (int)((unsigned)(pend - pbeg + nchunk - 1) / (unsigned)nchunk);
   const int cbeg = pbeg + chunk * per, cend = min(pend, cbeg + per);
   const int lp = tid >> 3, c8 = tid & 7, c0 = blockIdx.y * 64 + c8 * 8;
-  u32x4 xr[4], dr[4];   // dr: the output gradient (backward) or the residual input (forward, with skip)
+  u32x4 xr[4], dr[4], tr[TWIN ? 4 : 1];   // dr: the output gradient (backward) or the residual input (forward, with skip)
   auto fetch = [&](int p) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const size_t q = max(min(p + 32 * u, cend - 1), pbeg);
+      if (TWIN) tr[TWIN ? u : 0] = *reinterpret_cast<const u32x4*>(twin.x + q * C + c0);
       xr[u] = *reinterpret_cast<const u32x4*>(x + q * C + c0);
       if (BWD) dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + c0);
       else if (skip) dr[u] = *reinterpret_cast<const u32x4*>(skip + q * C + c0);
@@ -415,10 +425,22 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
     if (BWD) { mn1[e] = fin[c8 * 8 + e][0]; mn2[e] = fin[c8 * 8 + e][1]; }
     else { mu[e] = fin[c8 * 8 + e][0]; is[e] = fin[c8 * 8 + e][1]; }
   }
-  for (int p = cbeg + lp; p < cend; p += 128) {
-    u32x4 xc[4], dc[4];
+  double t1[TWIN ? 8 : 1], t2[TWIN ? 8 : 1];
+  float tmu[8];
+  if constexpr (TWIN) {
+    float unused[8];
+    load_stats8(twin.stats + ((size_t)wk * C + c0) * 2, tmu, unused);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) { xc[u] = xr[u]; dc[u] = dr[u]; }
+    for (int e = 0; e < 8; ++e) t1[e] = t2[e] = 0.0;
+  }
+  for (int p = cbeg + lp; p < cend; p += 128) {
+    u32x4 xc[4], dc[4], tc[TWIN ? 4 : 1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      xc[u] = xr[u];
+      dc[u] = dr[u];
+      if (TWIN) tc[TWIN ? u : 0] = tr[TWIN ? u : 0];
+    }
     if (p - lp + 128 < cend) fetch(p + 128);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -434,10 +456,42 @@ __global__ __launch_bounds__(256) void bn_finish_kernel(const bf16_t* __restrict
           o[e] = gm[e] * is[e] * (dv[e] - mn1[e] - xh * mn2[e]);
         }
         Piece<bf16_t>::store(out + q * C + c0, o);
+        if constexpr (TWIN) {
+          float tv[8];
+          unpack8(tc[u], tv);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            t1[e] += (double)dv[e];
+            t2[e] += (double)(dv[e] * (tv[e] - tmu[e]));   // (1 / deviation multiplies the sum: see bn_sums_add)
+          }
+        }
       } else {
         bn_normalise8(xv, dv, mu, is, gm, bt, relu, skip != nullptr, relu_add, o);
         bn_store8<false>(o, out, sign_bits, q * C + c0, q * (C / 8) + (c0 >> 3));
       }
+    }
+  }
+  if constexpr (TWIN) {
+    // the 32 position lanes' sums, eight rows per thread, then the four parts: a fixed order
+    __shared__ double rows[32][8][9];
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rows[lp][c8][e] = which ? t2[e] : t1[e];
+      __syncthreads();
+      const int cc = tid & 63, part = tid >> 6;
+      double t = 0.0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) t += rows[part * 8 + r][cc >> 3][cc & 7];
+      red[part][cc][which] = t;
+    }
+    __syncthreads();
+    if (tid < 128) {
+      const int cc = tid & 63, which = tid >> 6;
+      const int c = blockIdx.y * 64 + cc;
+      const double sum = ((red[0][cc][which] + red[1][cc][which]) + red[2][cc][which]) + red[3][cc][which];
+      twin.partial[((size_t)blockIdx.x * C + c) * 2 + which] = which ? sum * (double)twin.stats[((size_t)wk * C + c) * 2 + 1] : sum;
     }
   }
 }
@@ -641,8 +695,8 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
                        nullptr, C, hw, seg, sp, per, partial);
   ShareTable fc;
   if (few_records(sp, seg, C, hw, fc)) {
-    hipLaunchKernelGGL(bn_finish_kernel<false>, dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
-                       gamma, beta, nullptr, nullptr, 0, C, hw, seg, fc, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits);
+    hipLaunchKernelGGL((bn_finish_kernel<false, false>), dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
+                       gamma, beta, nullptr, nullptr, 0, C, hw, seg, fc, relu ? 1 : 0, y, skip, relu_add ? 1 : 0, sign_bits, TwinIn{});
     return;
   }
   hipLaunchKernelGGL(bn_finalize_fwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, stats);
@@ -655,7 +709,7 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
 
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
                       const Segments& seg, const float* stats, float* means, double* partial, float* g_gamma,
-                      float* g_beta, size_t worker_stride, const ShareTable* presummed) {
+                      float* g_beta, size_t worker_stride, const ShareTable* presummed, BnTwinSums* twin) {
   int per = 0;
   const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
   const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
@@ -664,9 +718,19 @@ void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t*
                        hw, seg, sp, per, partial);
   ShareTable fc;
   if (few_records(sp, seg, C, hw, fc)) {
-    hipLaunchKernelGGL(bn_finish_kernel<true>, dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, dy, partial, sp,
+    // (the workgroups are the other batch norm's records: no more of them than its own launch takes, and room behind these)
+    ShareTable tc;
+    if (twin && few_records(fc, seg, C, hw, tc) && sp.first[seg.K] + fc.first[seg.K] <= seg.K * kBnMaxSplits) {
+      twin->partial = partial + (size_t)sp.first[seg.K] * C * 2;
+      twin->table = fc;
+      twin->done = true;
+    } else {
+      twin = nullptr;
+    }
+    const auto finish = twin ? bn_finish_kernel<true, true> : bn_finish_kernel<true, false>;
+    hipLaunchKernelGGL(finish, dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, dy, partial, sp,
                        const_cast<float*>(stats), gamma, nullptr, g_gamma, g_beta, worker_stride, C, hw, seg, fc, 0, dx, nullptr,
-                       0, nullptr);
+                       0, nullptr, twin ? TwinIn{twin->x, twin->stats, twin->partial} : TwinIn{});
     return;
   }
   hipLaunchKernelGGL(bn_finalize_bwd_kernel, dim3(seg.K, fin), dim3(256), 0, st, partial, C, hw, seg, sp, means,

@@ -352,10 +352,20 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
                      bool relu_add = false, const ShareTable* presummed = nullptr, uint8_t* sign_bits = nullptr);
 // (sign_bits, [positions][C/8] bytes or null: one bit per element of y, set where the stored value is positive:
 // what the input-gradient kernels need of a ReLU's output.)
+// A second batch norm of the same output gradient and shape (of a residual block's two branches, whose add hands both the same): the
+// kernel that forms the first one's input gradient may take the records of the second one's sums along; it then sets done, partial
+// (behind the first one's records) and table.
+struct BnTwinSums {
+  const bf16_t* x;       // the second one's input
+  const float* stats;    // ... and its [K][C][2] means and 1/sqrt(var + eps)
+  double* partial;
+  ShareTable table;
+  bool done;
+};
 // means: [K][C][2] scratch; g_gamma / g_beta: worker k's entries at + k*worker_stride.
 void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t* dx, const float* gamma, int C, int hw,
                       const Segments& seg, const float* stats, float* means, double* partial, float* g_gamma,
-                      float* g_beta, size_t worker_stride, const ShareTable* presummed = nullptr);
+                      float* g_beta, size_t worker_stride, const ShareTable* presummed = nullptr, BnTwinSums* twin = nullptr);
 void add_fwd_bf16(hipStream_t st, const bf16_t* a, const bf16_t* b, bf16_t* out, long elems, bool relu);
 // dst (+)= g, zeroed where mask <= 0 (mask may be null)
 void route_grad_bf16(hipStream_t st, const bf16_t* g, const bf16_t* mask, bf16_t* dst, long elems, bool accumulate);

@@ -1024,6 +1024,7 @@ void step_bf16(StepCtx& c) {
     return bn;
   };
   presummed_for = -1;
+  double* presummed_at = bn_partial;   // where those records are
   for (int i = n_layers - 2; i >= 0; --i) {
     const Layer& L = net->layers[i];
     if (L.fused_away) continue;
@@ -1062,7 +1063,7 @@ void step_bf16(StepCtx& c) {
                  sc >= 0 ? shadow + net->layers[sc].wt_off : nullptr, grad(L.in0), rows, L.ih, L.iw, L.cin_pad,
                  ti.relu ? act(L.in0) : nullptr, (ti.relu && bits_written[L.in0]) ? sign_bits(L.in0) : nullptr,
                  written[L.in0] != 0, addend, conv_counters, bn >= 0 ? &offer : nullptr);
-          if (offer.done) { presummed = offer.table; presummed_for = bn; }
+          if (offer.done) { presummed = offer.table; presummed_for = bn; presummed_at = bn_partial; }
           dgrad_done = true;
         } else dgrad_done = omni::conv3s2_dgrad_bf16(
             st, grad(L.out), shadow + L.wt_off, L.d.cout, sc >= 0 ? grad(net->layers[sc].out) : nullptr,
@@ -1098,7 +1099,7 @@ void step_bf16(StepCtx& c) {
                                ti.relu ? act(L.in0) : nullptr, false, written[L.in0] != 0, nullptr, nullptr, addend,
                                bn >= 0 ? &offer : nullptr, pl >= 0 ? &unpool : nullptr);
           if (pl >= 0 && unpool.done) unpooled[pl] = 1;
-          if (offer.done) { presummed = offer.table; presummed_for = bn; }
+          if (offer.done) { presummed = offer.table; presummed_for = bn; presummed_at = bn_partial; }
         }
         written[L.in0] = 1;
       }
@@ -1120,9 +1121,22 @@ void step_bf16(StepCtx& c) {
       written[L.in0] = 1;
     } else if (L.d.op == OMNI_OP_BN) {
       float* stats = bn_area + L.stat_off;
+      // the next batch norm of the walk, where a residual add has handed both the same gradient
+      int second_bn = i - 1;
+      while (second_bn >= 0 && (net->layers[second_bn].fused_away || net->layers[second_bn].d.op != OMNI_OP_BN)) --second_bn;
+      omni::BnTwinSums twin{};
+      if (second_bn >= 0) {
+        const Layer& S = net->layers[second_bn];
+        if (S.ic == L.ic && S.ih * S.iw == L.ih * L.iw && grad_alias[S.out] && grad(S.out) == grad(L.out)) {
+          twin.x = act(S.in0);
+          twin.stats = bn_area + S.stat_off;
+        }
+      }
+      const bool summed = i == presummed_for;
       omni::bn_backward_bf16(st, act(L.in0), grad(L.out), grad(L.in0), c.params + L.w_off, L.ic, L.ih * L.iw, c.seg,
-                             stats, stats + (size_t)net->K_max * L.ic * 2, bn_partial, c.G + L.w_off, c.G + L.b_off,
-                             net->P_stride, i == presummed_for ? &presummed : nullptr);
+                             stats, stats + (size_t)net->K_max * L.ic * 2, summed ? presummed_at : bn_partial, c.G + L.w_off,
+                             c.G + L.b_off, net->P_stride, summed ? &presummed : nullptr, twin.x ? &twin : nullptr);
+      if (twin.done) { presummed = twin.table; presummed_for = second_bn; presummed_at = twin.partial; }
       written[L.in0] = 1;
     } else if (L.d.op == OMNI_OP_ADD) {
       const long elems = (long)rows * L.ih * L.iw * L.ic;
