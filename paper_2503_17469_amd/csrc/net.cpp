@@ -926,9 +926,8 @@ void step_bf16(StepCtx& c) {
   std::vector<const bf16_t*> pending_add(net->tensors.size(), nullptr);
   float* conv_partial2 = reinterpret_cast<float*>(c.ws + net->conv_partial2_off);
   float* conv_partial3 = reinterpret_cast<float*>(c.ws + net->conv_partial3_off);
-  // The weight gradients feed nothing but the update.  They are collected and set going in groups, on the side
-  // streams beside the input-gradient chain, the two streams (and scratch areas) in turn; what is left when the
-  // chain has ended runs on the main stream.  A group is worth a fork (event calls: about 12 us of host time, 3 us of the
+  // The weight gradients feed nothing but the update.  They are collected and set going in groups, on a side
+  // stream beside the input-gradient chain; what is left when the chain has ended runs on the main stream.  A group is worth a fork (event calls: about 12 us of host time, 3 us of the
   // main stream) from kGroupWork on: 50 us or so of an otherwise idle chip.  (A net with less in all, or with
   // fewer than kGroupJobs layers, has one group, on the main stream.)
   constexpr double kGroupWork = 40e9;
@@ -939,6 +938,11 @@ void step_bf16(StepCtx& c) {
   // It leaves the chain room (one workgroup per compute unit) where at least two batch norms are still to come: their launches are short
   // and wait for a place otherwise (conv_wgrad_bf16.hip has what it is worth).  A chain of a few long input gradients shares the chip
   // as it is, and the weight gradients end last: 64-128 (stride 2)-128 without batch norms, 512 images, 416 us and 476 with room.
+  // Groups with room follow each other on one stream: two at a time crowd the chain's kernels, whose launches are most of the step.  The
+  // others take the two streams (and scratch areas) in turn, as the chain ends before they do.  Step in us, every group in turn / as it is:
+  // ResNet-18 shape, one worker, 32 images 859 / 831; two, 64 images 1068 / 1056; four, 160 images 1629 / 1614, 400 images 2838 / 2811, 512 images
+  // 3315 / 3281; eight, 1400 images 7327 / 7264; two, 2048 images 10457 / 10351; 128 images 1324 / 1323.  All groups on one stream: 64-128 (stride 2)-128
+  // without batch norms, 2048 images, 1386 and 1402.
   constexpr int kRoomNorms = 2;
   auto norms_below = [&](int i) {
     int n = 0;
@@ -971,8 +975,8 @@ void step_bf16(StepCtx& c) {
     c.covered.insert(c.covered.end(), ranges.begin(), ranges.end());
   };
   auto start_group = [&](hipEvent_t ready, int layer) {
-    const bool use2 = second && c.side2 != c.side;
-    second = !second;
+    const bool room = norms_below(layer) >= kRoomNorms, use2 = !room && second && c.side2 != c.side;
+    if (!room) second = !second;
     c.fork_wait(use2 ? c.side2 : c.side, ready);
     c.forked = true;
     if (use2) c.forked2 = true;
@@ -981,7 +985,7 @@ void step_bf16(StepCtx& c) {
       TimedScope ts(net, side, OMNI_KERNEL_CONV_WGRAD, layer);   // (reported under the lowest layer it covers)
       omni::conv_wgrad_batch(side, group.data(), (int)group.size(), net->P_stride, c.seg, use2 ? conv_partial2 : conv_partial,
                              omni::conv_wgrad_partial_floats(), nullptr, kGroupWorkgroups, nullptr, nullptr, 0, false,
-                             norms_below(layer) >= kRoomNorms);
+                             room);
     }
     update_group(side);
     group.clear();
