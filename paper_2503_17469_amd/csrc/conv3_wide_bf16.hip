@@ -693,7 +693,7 @@ __global__ __launch_bounds__(kThreads, MA == 4 ? 1 : NB == 1 ? 3 : 2) void conv3
 #pragma unroll
           for (int r = 0; r < NR; ++r)
             if (lane_pos + place(a, r) < npos && col0 + lane_c < p.N)
-              unpool_store(p.unpool, (size_t)out_base + (lane_pos + place(a, r)), (lane_pos + place(a, r)) & (W - 1), W, p.N, col0 + lane_c,
+              unpool_store<4>(p.unpool, (size_t)out_base + (lane_pos + place(a, r)), (lane_pos + place(a, r)) & (W - 1), W, p.N, col0 + lane_c,
                            stored[r], codes[a][r]);
         }
       }

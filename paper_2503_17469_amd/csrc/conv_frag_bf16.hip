@@ -230,7 +230,7 @@ __device__ __forceinline__ void frag_finish(const FragParams& p, unsigned char* 
     for (int d = 0; d < 4; ++d) outp[qq][d] = pack_bf16(val[2 * d], val[2 * d + 1]);
     if (row_in) *reinterpret_cast<u32x4*>(p.out + row + qq * 16 + h * 8) = outp[qq];
     if (BWD && p.unpool && row_in)
-      unpool_store(p.unpool, out_pos, pos & ((1 << p.wlog) - 1), 1 << p.wlog, p.N, cb + qq * 16 + h * 8, outp[qq], ecode[qq]);
+      unpool_store<4>(p.unpool, out_pos, pos & ((1 << p.wlog) - 1), 1 << p.wlog, p.N, cb + qq * 16 + h * 8, outp[qq], ecode[qq]);
   }
 
   if (p.stat_partial) {

@@ -12,6 +12,8 @@
 //      extra workgroup) L_k, the lambda-weighted total loss and the label check.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bf16.h"
 #include "common.h"
 #include "head_device.h"
@@ -32,7 +34,6 @@ struct HeadFwdParams {
   const float* bias;
   const int32_t* labels;
   int cin, C, rows, K, use_mask;
-  int groups;            // of sixteen rows
   int cols_each;         // column tiles of dx per workgroup of a group
   float *z, *dz, *loss_rows;
   void* dx;
@@ -55,6 +56,10 @@ struct HeadFwdParams {
 // form the same logits and share out the columns of dx (480 rows of 1024, 10 classes: 8.5 -> 6.9 us a launch, back to back; a line
 // of arguments that no load has touched costs 640 cycles, a search for a row's worker in it 400 a step).  Not faster: sixteen
 // wavefronts; operands straight in the instruction's layout (half lines: +0.9 us).
+// Nothing branches between the loads either: absent biases and classes are selected away (eight exponentials behind a branch each wait
+// for one another), offsets are 32 bits from a common beginning, and the weights dx needs are all under way during the loss (they
+// cost a round trip per sixteen classes).  Step in us before / after: 64-128-10 fp32 13.45 / 13.30, 997-501-243-37 47.3 / 46.8, 3072 net 110.3 / 109.9,
+// three conv layers, 128 images 74.7 / 74.4; ResNet-18 shape with 100 classes, 128 images 1354 / 1350 (this launch 19.2 / 16.0).
 // Rows may start at any multiple of the element size (bf16: 16 bytes); a piece that would run past the end of a row is moved
 // back to end there, and elements it shares with the piece before count once.
 constexpr int kLineFloats = 36;   // a 128-byte line in LDS, padded: conflict-free writes and fragment reads
@@ -99,6 +104,29 @@ template <> struct HeadOps<bf16_t> {
   __device__ static inline void store(bf16_t* p, const float (&v)[8]) { Piece<bf16_t>::store(p, v); }
 };
 
+// CE neighbouring columns of a row, as they are stored: what a lane has of dx and of its operands.
+template <typename T, int CE> struct HeadCols {
+  static_assert(CE == Piece<T>::EL, "a whole piece");
+  typedef v4f Raw;
+  __device__ static inline Raw load(const T* p) { return HeadOps<T>::load(p); }
+  __device__ static inline void unpack(Raw t, float (&v)[CE]) { HeadOps<T>::unpack(t, v); }
+  __device__ static inline void store(T* p, const float (&v)[CE]) { HeadOps<T>::store(p, v); }
+};
+template <> struct HeadCols<bf16_t, 4> {
+  typedef u32x2 Raw;
+  __device__ static inline Raw load(const bf16_t* p) { return *reinterpret_cast<const u32x2*>(p); }
+  __device__ static inline void unpack(Raw t, float (&v)[4]) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      v[2 * d] = bf16_lo(t[d]);
+      v[2 * d + 1] = bf16_hi(t[d]);
+    }
+  }
+  __device__ static inline void store(bf16_t* p, const float (&v)[4]) {
+    *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  }
+};
+
 // sums and maxima over the 16 lanes of a row, left in every one of them
 __device__ inline float row16_sum(float v) {
   v += dpp_move<0xB1>(v);
@@ -113,8 +141,16 @@ __device__ inline float row16_max(float v) {
   return fmaxf(v, dpp_move<0x140>(v));
 }
 
+// Element i of what begins at a wavefront's common address: the address stays in scalar registers.
+template <typename T> __device__ inline const T* element(const T* p, uint32_t i) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)(i * sizeof(T)));
+}
+
 // Few classes: eight wavefronts and four chunks in flight, since all of it is waiting; more classes fill the registers.
 template <int CT> constexpr int head_waves() { return CT == 1 ? 8 : 4; }
+// Columns of dx a lane has at a time: a piece.  Half a piece in bf16 with many classes, so that twice as many wavefronts share the
+// walk over the classes, and all its weights fit the registers.
+template <typename T, int CT> constexpr int head_cols() { return sizeof(T) == 2 && CT == 8 ? 4 : Piece<T>::EL; }
 
 template <typename T, int CT>
 __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_kernel(HeadFwdParams p, Segments seg) {
@@ -124,6 +160,8 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   const int cin = p.cin, C = p.C, rows = p.rows, use_mask = p.use_mask;
   typedef HeadOps<T> Ops;
   constexpr int EL = Piece<T>::EL, kLine = 8 * EL;      // elements per 16-byte piece, per 128-byte line
+  constexpr int CE = head_cols<T, CT>();
+  typedef HeadCols<T, CE> Cols;
   constexpr int NW = head_waves<CT>(), D = CT == 1 ? 4 : 2;
   constexpr int kClasses = 16 * CT, kZ = kClasses + 1;
   constexpr int kWave = (16 + kClasses) * kLineFloats;  // a wavefront's staging block
@@ -132,23 +170,27 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   __shared__ float zbuf[16][kZ];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4, lrow = lane >> 3, lp = lane & 7;
-  const int split = (int)blockIdx.x / p.groups, row0 = ((int)blockIdx.x - split * p.groups) * 16;
+  const int split = blockIdx.y, row0 = (int)blockIdx.x * 16;
+  // sixteen rows of x and the weights lie within 32 bits of their beginnings
+  const T* const xg = x + (size_t)row0 * cin;
+  const int last = min(15, rows - 1 - row0);
   // what the loss needs of a row, on its way before anything waits: lane l has the rows of worker l begin at `first`
   const int first = seg.off[min(lane, p.K)];
-  const int loss_row = row0 + ((tid >> 4) & 15), y = p.labels[min(loss_row, rows - 1)];
+  const int y = (p.labels + row0)[min(tid >> 4 & 15, last)];
+  const bool biased = p.bias != nullptr;
+  const float* const bias = biased ? p.bias : static_cast<const float*>(p.w);
   float bv[CT];
 #pragma unroll
-  for (int j = 0; j < CT; ++j) bv[j] = p.bias ? p.bias[min(16 * j + r, C - 1)] : 0.f;
+  for (int j = 0; j < CT; ++j) bv[j] = bias[biased ? min(16 * j + r, C - 1) : 0];
 
   // ---- logits
   float* la = lds + wave * kWave;
   float* lb = la + 16 * kLineFloats;
-  const T* xrow[2];
-  const T* wrow[2 * CT];
+  uint32_t xrow[2], wrow[2 * CT];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) xrow[i] = x + (size_t)min(row0 + lrow + 8 * i, rows - 1) * cin;
+  for (int i = 0; i < 2; ++i) xrow[i] = min(lrow * cin + 8 * i * cin, last * cin);
 #pragma unroll
-  for (int i = 0; i < 2 * CT; ++i) wrow[i] = w + (size_t)min(lrow + 8 * i, C - 1) * cin;
+  for (int i = 0; i < 2 * CT; ++i) wrow[i] = min(lrow * cin + 8 * i * cin, (C - 1) * cin);
   v4f acc[CT];
 #pragma unroll
   for (int j = 0; j < CT; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -156,13 +198,13 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   const int cb = wave * nc / NW, ce = (wave + 1) * nc / NW;
   v4f xa[D][2], wa[D][2 * CT];
   auto fetch = [&](int set, int ch) {
-    const int k = min(min(ch, nc - 1) * kLine + lp * EL, cin - EL);
+    const uint32_t k = min(min(ch, nc - 1) * kLine + lp * EL, cin - EL);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) xa[set][i] = Ops::load(xrow[i] + k);
+    for (int i = 0; i < 2; ++i) xa[set][i] = Ops::load(element(xg, xrow[i] + k));
 #pragma unroll
-    for (int i = 0; i < 2 * CT; ++i) wa[set][i] = Ops::load(wrow[i] + k);
+    for (int i = 0; i < 2 * CT; ++i) wa[set][i] = Ops::load(element(w, wrow[i] + k));
   };
-  auto multiply = [&](int set, int ch) {
+  auto multiply = [&](int set, int ch, auto whole) {   // (whole: a line that no row ends in)
 #pragma unroll
     for (int i = 0; i < 2; ++i) *reinterpret_cast<v4f*>(la + (lrow + 8 * i) * kLineFloats + lp * 4) = xa[set][i];
 #pragma unroll
@@ -176,7 +218,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
       a[s] = *reinterpret_cast<const v4f*>(la + r * kLineFloats + 16 * s + 4 * g);
       const int k = ch * kLine + (4 * s + g) * EL;       // first element of this lane's piece, before it was moved back
       lo[s] = k >= cin ? EL : k - min(k, cin - EL);
-      if ((ch + 1) * kLine > cin) Ops::zero_below(a[s], lo[s]);
+      if (!whole && (ch + 1) * kLine > cin) Ops::zero_below(a[s], lo[s]);
     }
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
@@ -184,7 +226,7 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         v4f b = *reinterpret_cast<const v4f*>(lb + (16 * j + r) * kLineFloats + 16 * s + 4 * g);
-        if ((ch + 1) * kLine > cin) Ops::zero_below(b, lo[s]);
+        if (!whole && (ch + 1) * kLine > cin) Ops::zero_below(b, lo[s]);
         sum[s] = Ops::mma(a[s], b, v4f{0.f, 0.f, 0.f, 0.f});
       }
       acc[j] += sum[0] + sum[1];
@@ -206,35 +248,56 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   }
   const float inv_b = 1.0f / (float)bk_own;
   __builtin_amdgcn_sched_barrier(0);
-  if (ce > cb) {
+  if constexpr (CT == 8) {
+    // one copy of the code for the whole lines: it is fetched from memory as it goes, once a launch
+    int ch = cb;
+#pragma unroll 1
+    for (const int end = min(ce, cin / kLine); ch < end; ++ch) {
+      multiply(0, ch, std::true_type{});
+#pragma unroll
+      for (int i = 0; i < 2; ++i) xa[0][i] = xa[1][i];
+#pragma unroll
+      for (int i = 0; i < 2 * CT; ++i) wa[0][i] = wa[1][i];
+      if (ch + 2 < ce) fetch(1, ch + 2);
+    }
+    if (ch < ce) multiply(0, ch, std::false_type{});
+  } else if (ce > cb) {
     int ch = cb;
     for (; ch + D < ce; ch += D) {
 #pragma unroll
       for (int d = 0; d < D; ++d) {
-        multiply(d, ch + d);
+        multiply(d, ch + d, std::false_type{});
         fetch(d, min(ch + d + D, ce - 1));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
     for (int d = 0; d < D; ++d)
-      if (ch + d < ce) multiply(d, ch + d);
+      if (ch + d < ce) multiply(d, ch + d, std::false_type{});
   }
   // what the input gradient of this wavefront's first columns needs travels while the loss is computed
-  const int col_tiles = (cin + 16 * EL - 1) / (16 * EL);
-  auto column = [&](int ct) { return min((min(ct, col_tiles - 1) * 16 + r) * EL, cin - EL); };
-  v4f xm[4], wt[4];
-  constexpr bool UNPOOL = EL == 8;
-  u32x2 code[4];
+  // (the weights of PD times sixteen classes: loaded where they are used, each sixteen held the walk up for a round trip)
+  constexpr int PD = CT * (int)sizeof(typename Cols::Raw) <= 64 ? CT : 4;
+  const int col_tiles = (cin + 16 * CE - 1) / (16 * CE);
+  auto column = [&](int ct) { return min((min(ct, col_tiles - 1) * 16 + r) * CE, cin - CE); };
+  typename Cols::Raw xm[4], wt[PD][4];
+  constexpr bool UNPOOL = sizeof(T) == 2;
+  typedef uint32_t Codes __attribute__((ext_vector_type(CE == 8 ? 2 : 1)));
+  Codes code[4];
+  auto fetch_weights = [&](int col, int j) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) wt[j % PD][t] = Cols::load(element(w, (uint32_t)(min(g * cin + (16 * j + 4 * t) * cin, (C - 1) * cin) + col)));
+  };
   auto fetch_cols = [&](int col) {
     if (UNPOOL && p.unpool) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) code[v] = *reinterpret_cast<const u32x2*>(p.unpool_code + (size_t)min(row0 + 4 * g + v, rows - 1) * cin + col);
+      for (int v = 0; v < 4; ++v)
+        code[v] = *reinterpret_cast<const Codes*>(element(p.unpool_code + (size_t)row0 * cin, (uint32_t)(min(4 * g + v, last) * cin + col)));
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) xm[v] = Ops::load(x + (size_t)min(row0 + 4 * g + v, rows - 1) * cin + col);
+    for (int v = 0; v < 4; ++v) xm[v] = Cols::load(element(xg, (uint32_t)(min(4 * g + v, last) * cin + col)));
 #pragma unroll
-    for (int t = 0; t < 4; ++t) wt[t] = Ops::load(w + col + (size_t)min(4 * t + g, C - 1) * cin);
+    for (int j = 0; j < PD; ++j) fetch_weights(col, j);
   };
   const int ct_begin = split * p.cols_each, ct_end = min(ct_begin + p.cols_each, col_tiles);
   if (dx != nullptr) fetch_cols(column(ct_begin + wave));
@@ -255,38 +318,38 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
       zc[j] = lds[at];
 #pragma unroll
       for (int ww = 1; ww < NW; ++ww) zc[j] += lds[ww * kWave + at];
-      if (c < C) {
-        zc[j] += bv[j];
-        m = fmaxf(m, zc[j]);
-      }
+      zc[j] = c < C ? zc[j] + (biased ? bv[j] : 0.f) : -INFINITY;
+      m = fmaxf(m, zc[j]);
     }
     m = row16_max(m);
     const bool bad = y < 0 || y >= C;
     float s = 0.f, zy = 0.f;
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
-      const int c = 16 * j + cl;
-      if (c < C) s += expf(zc[j] - m);
-      zy += c == y ? zc[j] : 0.f;
+      s += expf(zc[j] - m);                               // (an absent class: 0, or NaN where the others are)
+      zy += 16 * j + cl == y ? zc[j] : 0.f;
     }
     s = row16_sum(s);
     zy = row16_sum(zy);
     const float lse = logf(s);
     if (live && cl == 0) p.loss_rows[row] = bad ? 0.f : lse - (zy - m);
+    float d[CT];
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
       const int c = 16 * j + cl;
-      float d = 0.f;
-      if (c < C) {
-        d = expf(zc[j] - m - lse);
-        if (c == y) d -= 1.0f;
-        d = bad ? 0.f : d * inv_b;
-        if (live) {
-          p.z[(size_t)row * C + c] = zc[j];
-          p.dz[(size_t)row * C + c] = d;
-        }
-      }
-      zbuf[lr][c] = d;
+      d[j] = expf(zc[j] - m - lse);
+      if (c == y) d[j] -= 1.0f;
+      d[j] = bad || c >= C ? 0.f : d[j] * inv_b;
+      zbuf[lr][c] = d[j];
+    }
+    float* const zo = p.z + (size_t)row * C;
+    float* const dzo = p.dz + (size_t)row * C;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int c = 16 * j + cl;
+      if (!live || c >= C) continue;
+      zo[c] = zc[j];
+      dzo[c] = d[j];
     }
   }
   lds_barrier();
@@ -299,57 +362,58 @@ __global__ __launch_bounds__(64 * head_waves<CT>(), 2) void head_fwd_loss_dgrad_
   const int nt = (C + 3) / 4;
   for (int ct = ct_begin + wave; ct < ct_end; ct += NW) {
     const int col = column(ct);
-    v4f o[EL];
-    v4f mk[4];
-    u32x2 to[4];
+    int cls = g;
+    asm volatile("" : "+v"(cls));                         // (else 32 masks of absent classes are made in front of the loop, and spill)
+    v4f o[CE];
+    typename Cols::Raw mk[4];
+    Codes to[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       mk[v] = xm[v];
       if (UNPOOL) to[v] = code[v];
     }
 #pragma unroll
-    for (int t0 = 0; t0 < 4 * CT; t0 += 4) {
+    for (int j = 0; j < CT; ++j) {
+      const int t0 = 4 * j;
       if (t0 >= nt) break;
-      if (t0 > 0) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) wt[t] = Ops::load(w + col + (size_t)min(4 * (t0 + t) + g, C - 1) * cin);
-      }
       // (sixteen classes by themselves, then added: short chains)
-      v4f part[EL];
+      v4f part[CE];
 #pragma unroll
-      for (int e = 0; e < EL; ++e) part[e] = v4f{0.f, 0.f, 0.f, 0.f};
-      if (4 * (t0 + 4) > C) {                             // an absent class counts zero in both operands
+      for (int e = 0; e < CE; ++e) part[e] = v4f{0.f, 0.f, 0.f, 0.f};
+      if (16 * (j + 1) > C) {                             // an absent class counts zero in both operands
 #pragma unroll
-        for (int t = 0; t < 4; ++t) wt[t] = 4 * (t0 + t) + g < C ? wt[t] : v4f{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 4; ++t) wt[j % PD][t] = 4 * (t0 + t) + cls < C ? wt[j % PD][t] : typename Cols::Raw{};
       }
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if (t > 0 && t0 + t >= nt) break;                 // (no class left)
-        float b[EL];
-        Ops::unpack(wt[t], b);
+        float b[CE];
+        Cols::unpack(wt[j % PD][t], b);
 #pragma unroll
-        for (int e = 0; e < EL; ++e) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[t0 + t], b[e], part[e], 0, 0, 0);
+        for (int e = 0; e < CE; ++e) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(da[t0 + t], b[e], part[e], 0, 0, 0);
       }
+      if (j + PD < CT) fetch_weights(col, j + PD);
 #pragma unroll
-      for (int e = 0; e < EL; ++e) o[e] = t0 == 0 ? part[e] : o[e] + part[e];
+      for (int e = 0; e < CE; ++e) o[e] = j == 0 ? part[e] : o[e] + part[e];
     }
     if (ct + NW < ct_end) fetch_cols(column(ct + NW));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int row = row0 + 4 * g + v;
-      float t[EL], m[EL];
-      if (use_mask) Ops::unpack(mk[v], m);
+      float t[CE], m[CE];
+      if (use_mask) Cols::unpack(mk[v], m);
 #pragma unroll
-      for (int e = 0; e < EL; ++e) t[e] = !use_mask || m[e] > 0.f ? o[e][v] : 0.f;
+      for (int e = 0; e < CE; ++e) t[e] = !use_mask || m[e] > 0.f ? o[e][v] : 0.f;
       if (row >= rows) continue;
-      Ops::store(dx + (size_t)row * cin + col, t);
+      Cols::store(dx + (size_t)row * cin + col, t);
       if constexpr (UNPOOL) {
         if (p.unpool) {
-          u32x4 d;
+          typedef uint32_t Grad __attribute__((ext_vector_type(CE / 2)));
+          Grad d;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) d[i] = pack_bf16(t[2 * i], t[2 * i + 1]);
+          for (int i = 0; i < CE / 2; ++i) d[i] = pack_bf16(t[2 * i], t[2 * i + 1]);
           const int at = quotient(col, p.by_chan, p.chan), y = quotient(at, p.by_w, p.W);   // (whole pieces of a position's channels)
-          unpool_store(p.unpool + (size_t)row * 4 * cin, at, at - y * p.W, p.W, p.chan, col - at * p.chan, d, to[v]);
+          unpool_store<CE / 2>(p.unpool + (size_t)row * 4 * cin, at, at - y * p.W, p.W, p.chan, col - at * p.chan, d, to[v]);
         }
       }
     }
@@ -377,12 +441,12 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
   const int rows = seg.off[seg.K], groups = (rows + 15) / 16;
   // Several workgroups per sixteen rows where one each leaves half the chip idle: every one forms the logits, and the columns of dx
   // are shared out, down to one tile per SIMD (1024 columns, 480 rows: dx 6000 of a workgroup's 15700 cycles, shared by four 2400).
-  const int tile = 16 * (bf16 ? Piece<bf16_t>::EL : Piece<float>::EL), tiles = (cin + tile - 1) / tile;
+  const int tile = 16 * (bf16 ? classes > 48 ? head_cols<bf16_t, 8>() : Piece<bf16_t>::EL : Piece<float>::EL), tiles = (cin + tile - 1) / tile;
   int splits = 1;
   while (dx && groups * splits * 2 <= 256 && tiles >= 8 * splits) splits *= 2;
   HeadFwdParams p{};
   p.x = x; p.w = w; p.bias = bias; p.labels = labels; p.cin = cin; p.C = classes; p.rows = rows; p.K = seg.K; p.use_mask = use_mask ? 1 : 0;
-  p.groups = groups; p.cols_each = (tiles + splits - 1) / splits;
+  p.cols_each = (tiles + splits - 1) / splits;
   p.z = z; p.dz = dz; p.loss_rows = loss_rows; p.dx = dx;
   if (unpool && bf16 && dx && unpool->C % Piece<bf16_t>::EL == 0) {
     p.unpool = unpool->din; p.unpool_code = unpool->code;
@@ -390,7 +454,7 @@ void head_fwd_loss_dgrad(hipStream_t st, bool bf16, const void* x, const void* w
     p.by_w = reciprocal_below(p.W, cin); p.by_chan = reciprocal_below(p.chan, cin);
     unpool->done = true;
   }
-  const dim3 grid(groups * splits);
+  const dim3 grid(groups, splits);
 #define OMNI_HEAD(T, CT) \
   hipLaunchKernelGGL((head_fwd_loss_dgrad_kernel<T, CT>), grid, dim3(64 * head_waves<CT>()), 0, st, p, seg)
 #define OMNI_HEAD_CT(T)                   \

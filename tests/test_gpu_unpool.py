@@ -9,21 +9,22 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("hw,chans,B,cuts", [
-    (32, (3, 32, 64, 128), 37, [0, 5, 37]),         # few positions everywhere; classifier: several workgroups per sixteen rows
-    (32, (3, 32, 64, 128), 1030, [0, 1, 600, 1030]),  # 8x8: wide, last unit two of four images
-    (32, (3, 64, 96, 64), 523, [0, 523]),           # 8x8: channel tiles of 64 and of 32
-    (32, (3, 64, 64, 32), 1100, [0, 3, 1100]),      # 8x8: one slice, weights kept
-    (16, (3, 32, 40, 64), 130, [0, 64, 130]),       # 40 channels: a launch of its own on 4x4
-    (32, (3, 32, 24, 72), 70, [0, 70]),             # 72 channels at the classifier, positions counted without powers of two
+@pytest.mark.parametrize("hw,chans,B,cuts,classes", [
+    (32, (3, 32, 64, 128), 37, [0, 5, 37], 10),         # few positions everywhere; classifier: several workgroups per sixteen rows
+    (32, (3, 32, 64, 128), 1030, [0, 1, 600, 1030], 10),  # 8x8: wide, last unit two of four images
+    (32, (3, 64, 96, 64), 523, [0, 523], 10),           # 8x8: channel tiles of 64 and of 32
+    (32, (3, 64, 64, 32), 1100, [0, 3, 1100], 10),      # 8x8: one slice, weights kept
+    (16, (3, 32, 40, 64), 130, [0, 64, 130], 10),       # 40 channels: a launch of its own on 4x4
+    (32, (3, 32, 24, 72), 70, [0, 70], 100),            # ... and with half a piece at a time
+    (32, (3, 32, 24, 72), 70, [0, 70], 10),             # 72 channels at the classifier, positions counted without powers of two
 ])
-def test_pooling_gradients(hw, chans, B, cuts):
+def test_pooling_gradients(hw, chans, B, cuts, classes):
     import torch
     import paper_2503_17469_amd as omni
-    layers = synth.cnn3(num_classes=10, hw=hw, chans=chans)
+    layers = synth.cnn3(num_classes=classes, hw=hw, chans=chans)
     params = synth.he_normal_params(layers, 6, True)
     x = torch.randn(B, hw, hw, 3, device="cuda", generator=torch.Generator("cuda").manual_seed(B)).to(torch.bfloat16)
-    labels = torch.arange(B, device="cuda", dtype=torch.int32) % 10
+    labels = torch.arange(B, device="cuda", dtype=torch.int32) % classes
     K = len(cuts) - 1
     net = omni.net_create(layers, (hw, hw, 3), "bf16", K, B)
     ws = torch.zeros(omni.net_workspace_bytes(net), dtype=torch.uint8, device="cuda")
