@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "bf16.h"
+#include "bn_sums_device.h"
 #include "cast_device.h"
 #include "common.h"
 #include "conv_device.h"
@@ -723,14 +724,27 @@ struct Conv1Casts {
 };
 struct NoCasts {};
 
+// The sums of a batch norm behind the layer (STAT): one record of every workgroup, whose units are all of one worker's images, in place of a
+// launch that reads the output back.  In double, from the pieces that the lanes store.
+// Step of the ResNet-18 shape in us, that launch / these sums: two workers, 64 images 1075 / 1071; four, 128 images 1334 / 1330; eight, 2048 images 10520 /
+// 10501; two, 2048 images 10345 / 10328 (the launch took 7.8 us with 128 images and 53 with 2048).
+struct Conv1Sums {
+  double* partial;     // [workgroup][N][2]
+  int K;
+  // worker k has the workgroups gfirst[k] .. and the images ifirst[k] ..
+  int32_t gfirst[OMNI_MAX_WORKERS + 1], ifirst[OMNI_MAX_WORKERS + 1];
+};
+struct NoSums {};
+
 // Eight channels of a tap, of which three are real.  (Cleared by a mask: with a choice the compiler makes the loads conditional.)
 __device__ __forceinline__ u32x4 weights3(const float* w, bool in) {
   const uint32_t mask = in ? ~0u : 0u;
   return u32x4{pack_bf16(w[0], w[1]) & mask, pack_bf16(w[2], 0.f) & mask, 0u, 0u};
 }
 
-template <int NBLK, bool CAST>   // 32-channel blocks of output channels: 1 or 2
-__global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, std::conditional_t<CAST, Conv1Casts, NoCasts> casts) {
+template <int NBLK, bool CAST, bool STAT>   // NBLK: 32-channel blocks of output channels, 1 or 2
+__global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, std::conditional_t<CAST, Conv1Casts, NoCasts> casts,
+                                                                std::conditional_t<STAT, Conv1Sums, NoSums> sums) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smemF[];
   int block = (int)blockIdx.x;
   if constexpr (CAST) {
@@ -819,7 +833,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, s
     }
   };
 
-  const int ubeg = block * p.upw, uend = min(p.units, ubeg + p.upw);
+  int ubeg = block * p.upw, uend = min(p.units, ubeg + p.upw);
+  if constexpr (STAT) {
+    const int g = sums.gfirst[lane], i = sums.ifirst[lane];   // (65 entries, all lanes at once)
+    const int k = __popcll(__ballot(lane < sums.K && g <= block)) - 1, upi = H >> p.lr;
+    const int after = k + 1 < sums.K ? __builtin_amdgcn_readlane(i, k + 1) : p.rows;
+    ubeg = __builtin_amdgcn_readlane(i, k) * upi + (block - __builtin_amdgcn_readlane(g, k)) * p.upw;
+    uend = min(after * upi, ubeg + p.upw);
+  }
+  double t[2][8] = {};   // STAT: this lane's sums of eight channels
   load_patch(min(ubeg, p.units - 1));
   for (int unit = ubeg; unit < uend; ++unit) {
 #pragma unroll
@@ -870,11 +892,13 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, s
     for (int it = 0; it < kUnitD * kPieces / kThreads; ++it) {
       const int c = tid + kThreads * it;
       const int il = c / kPieces, jl = (c % kPieces) * 8;
-      if (il < npos && jl < p.N)   // N is a multiple of 8
-        *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + il) * p.N + jl) =
-            *reinterpret_cast<const u32x4*>(so + il * kPitch + jl);
+      if (il < npos && jl < p.N) {   // N is a multiple of 8
+        const u32x4 piece = *reinterpret_cast<const u32x4*>(so + il * kPitch + jl);
+        *reinterpret_cast<u32x4*>(p.out + (size_t)(out_base + il) * p.N + jl) = piece;
+        if constexpr (STAT) bn_sums_add(t, piece);
+      }
     }
-    if (p.pool) {
+    if (!STAT && p.pool) {
       // 2 x 2 max pooling of the unit from the staged rows (a unit is whole rows of whole images: its
       // pooled positions are a contiguous run of the pooled tensor)
       const int Wh = W >> 1, Rh = R >> 1;
@@ -901,6 +925,33 @@ __global__ __launch_bounds__(kThreads, 2) void conv1_fwd_kernel(Conv1Params p, s
       }
     }
     // (the next iteration's patch store touches sP only; `so` is rewritten after the next barrier)
+  }
+  if constexpr (STAT) {
+    // the position lanes' sums of a channel, eight at a time, then the parts: a fixed order
+    constexpr int kPieces = NT / 8, kLanes = kThreads / kPieces, kParts = kThreads / NT;
+    double (*const rows)[kPieces][9] = reinterpret_cast<double (*)[kPieces][9]>(so);   // [kLanes]
+    double (*const part_sum)[NT] = reinterpret_cast<double (*)[NT]>(so + sizeof(double) / sizeof(bf16_t) * kLanes * kPieces * 9);
+    static_assert((kLanes * kPieces * 9 + kParts * NT) * sizeof(double) <= (size_t)kUnitD * kPitch * sizeof(bf16_t), "they take the staged output's place");
+    static_assert(kLanes / kParts == 8, "eight lanes to a part");
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rows[tid / kPieces][tid % kPieces][e] = t[which][e];
+      __syncthreads();
+      const int c = tid % NT, part = tid / NT;
+      double sum = 0.0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) sum += rows[part * 8 + r][c >> 3][c & 7];
+      part_sum[part][c] = sum;
+      __syncthreads();
+      if (tid < p.N) {
+        sum = part_sum[0][tid];
+#pragma unroll
+        for (int q = 1; q < kParts; ++q) sum += part_sum[q][tid];
+        sums.partial[((size_t)block * p.N + tid) * 2 + which] = sum;
+      }
+    }
   }
 }
 
@@ -993,7 +1044,7 @@ static bool conv1_fwd_shape(int N, const ConvGeom& g, long M) {
 
 static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t* out, int M, int N,
                       const ConvGeom& g, const float* bias, const bf16_t* mask, bool relu, bool accumulate,
-                      bf16_t* pool, uint8_t* pool_code, bool* pooled, const Conv1Casts* casts = nullptr) {
+                      bf16_t* pool, uint8_t* pool_code, bool* pooled, BnStatRequest* stats, const Conv1Casts* casts = nullptr) {
   const int H = g.Hs, W = g.Ws;
   if (mask || accumulate || !conv1_fwd_shape(N, g, M)) return false;
   const int R = std::min(H, kUnitD / W);
@@ -1016,14 +1067,44 @@ static bool conv1_fwd(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16
   const int nblk = N > 32 ? 2 : 1;
   const size_t lds = (size_t)((npatch + 3) & ~3) * 16 + (size_t)kUnitD * (32 * nblk + 8) * sizeof(bf16_t);
   static_assert(kUnitD * 40 >= kCastTile * kCastStride, "a copied tile fits the staged output");
-  const dim3 grid((p.units + p.upw - 1) / p.upw + (casts ? casts->blocks : 0)), block(kThreads);
-  if (casts) {
-    if (nblk == 2) hipLaunchKernelGGL((conv1_fwd_kernel<2, true>), grid, block, lds, st, p, *casts);
-    else hipLaunchKernelGGL((conv1_fwd_kernel<1, true>), grid, block, lds, st, p, *casts);
-  } else {
-    if (nblk == 2) hipLaunchKernelGGL((conv1_fwd_kernel<2, false>), grid, block, lds, st, p, NoCasts{});
-    else hipLaunchKernelGGL((conv1_fwd_kernel<1, false>), grid, block, lds, st, p, NoCasts{});
+  int groups = (p.units + p.upw - 1) / p.upw;
+  Conv1Sums sums{};
+  if (stats && stats->partial && stats->seg && !stats->x && stats->seg->off[stats->seg->K] == g.rows && !bias && !relu && !p.pool && nimg == 1) {
+    const Segments& seg = *stats->seg;
+    const int upi = H / R;
+    auto groups_of = [&](int k, int u) { return ((long)(seg.off[k + 1] - seg.off[k]) * upi + u - 1) / u; };
+    auto groups_at = [&](int u) {
+      long n = 0;
+      for (int k = 0; k < seg.K; ++k) n += groups_of(k, u);
+      return n;
+    };
+    // more units to a workgroup where there is no room for the records, but no fewer than two workgroups per compute unit (one worker, 600
+    // images, 150 workgroups: step 4131 -> 4160 us; 2048 images, 256: 10352 -> 10501)
+    int u = p.upw;
+    while (groups_at(u) > (long)seg.K * kBnMaxSplits && u < 64) u *= 2;
+    if (groups_at(u) <= (long)seg.K * kBnMaxSplits && (u == p.upw || groups_at(u) >= 512)) {
+      p.upw = u;
+      sums.partial = stats->partial;
+      sums.K = seg.K;
+      for (int k = 0; k <= seg.K; ++k) {
+        sums.ifirst[k] = seg.off[k];
+        if (k < seg.K) sums.gfirst[k + 1] = sums.gfirst[k] + (int)groups_of(k, u);
+        stats->table.first[k] = sums.gfirst[k];
+      }
+      groups = sums.gfirst[seg.K];
+      stats->done = true;
+    }
   }
+  const dim3 grid(groups + (casts ? casts->blocks : 0)), block(kThreads);
+#define OMNI_CONV1_(NBLK_, CAST_, ARG_)                                                                                                \
+  {                                                                                                                                    \
+    if (sums.partial) hipLaunchKernelGGL((conv1_fwd_kernel<NBLK_, CAST_, true>), grid, block, lds, st, p, ARG_, sums);                 \
+    else hipLaunchKernelGGL((conv1_fwd_kernel<NBLK_, CAST_, false>), grid, block, lds, st, p, ARG_, NoSums{});                         \
+  }
+#define OMNI_CONV1(NBLK_) { if (casts) OMNI_CONV1_(NBLK_, true, *casts) else OMNI_CONV1_(NBLK_, false, NoCasts{}) }
+  if (nblk == 2) OMNI_CONV1(2) else OMNI_CONV1(1)
+#undef OMNI_CONV1
+#undef OMNI_CONV1_
   return true;
 }
 
@@ -1035,12 +1116,12 @@ bool conv_first_layer_takes_casts(int Cout, int cin_real, const ConvGeom& g, lon
 
 bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, bf16_t* shadow,
                                 const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
-                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code) {
+                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats) {
   Conv1Casts c{};
   c.w = params + w_off; c.params = params; c.shadow = shadow; c.zero_page = zero_page;
   c.blocks = cast_table(c.tab, entries, n);
   bool pooled = false;
-  conv1_fwd(st, src, nullptr, out, M, N, g, bias, nullptr, relu, false, pool, pool_code, &pooled, &c);
+  conv1_fwd(st, src, nullptr, out, M, N, g, bias, nullptr, relu, false, pool, pool_code, &pooled, stats, &c);
   return pooled;
 }
 
@@ -1064,7 +1145,7 @@ bool conv_gemm_bf16(hipStream_t st, const bf16_t* src, const bf16_t* wgt, bf16_t
     return pool_out && pool_code;
   if (conv3_gemm(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled, addend))
     return pooled;
-  if (!addend && conv1_fwd(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled))
+  if (!addend && conv1_fwd(st, src, wgt, out, M, N, g, bias, mask, relu, accumulate, pool_out, pool_code, &pooled, stats))
     return pooled;
   if (g.raw3) return false;   // (callers ask conv_first_layer_raw_supported first: nothing else reads a 3-channel source)
   ConvParams p{};

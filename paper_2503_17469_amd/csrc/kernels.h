@@ -310,7 +310,7 @@ void conv_wgrad_describe(const ConvWgradJob* jobs, int n, const Segments& seg, i
 struct CastEntry {
   long src, dst_fwd, dst_t;
   int cout, taps, cin_real, cin_pad;
-  int frag_fwd, frag_t;
+  int16_t frag_fwd, frag_t;
   int first_block;   // filled by the launcher
 };
 constexpr int kCastMaxEntries = 64;
@@ -328,7 +328,7 @@ void cast_weights_bf16(hipStream_t st, const float* params, bf16_t* shadow, cons
 bool conv_first_layer_takes_casts(int Cout, int cin_real, const ConvGeom& g, long M);
 bool conv_first_layer_and_casts(hipStream_t st, const bf16_t* src, const float* params, size_t w_off, bf16_t* shadow,
                                 const CastEntry* entries, int n, uint32_t* zero_page, bf16_t* out, int M, int N,
-                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code);
+                                const ConvGeom& g, const float* bias, bool relu, bf16_t* pool, uint8_t* pool_code, BnStatRequest* stats);
 void pad_channels_bf16(hipStream_t st, const bf16_t* x, bf16_t* xp, long pixels, int c_real, int c_pad);
 void maxpool2_fwd_bf16(hipStream_t st, const bf16_t* in, bf16_t* out, int rows, int H, int W, int C);
 // din = dout routed to the first maximum of each 2x2 window (scan order), zero elsewhere;

@@ -827,7 +827,7 @@ void step_bf16(StepCtx& c) {
           ridden && i == first
               ? omni::conv_first_layer_and_casts(st, act(L.in0), c.params, L.w_off, shadow, casts.data(),
                                                  (int)casts.size(), conv_counters, actw(L.out), rows * to.h * to.w, L.d.cout,
-                                                 g, bias, to.relu, pool, code)
+                                                 g, bias, to.relu, pool, code, bn_next ? &offer : nullptr)
               : omni::conv_gemm_bf16(st, act(L.in0), shadow + L.wsh_off, actw(L.out), rows * to.h * to.w, L.d.cout, g, bias,
                                      nullptr, to.relu, false, pool, code, nullptr, bn_next ? &offer : nullptr);
       if (pooled) { pooled_layer = nx; coded[nx] = 1; }

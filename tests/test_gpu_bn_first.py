@@ -1,0 +1,53 @@
+"""The sums of the batch norm behind a first layer, taken along by that layer's kernel: units of several workgroups and several units
+of one, workers of one image, channels that fill no block; with the other layers' weight copies in the same launch (three input
+channels) and without (eight).  Compared in float64 over the values the library stored."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import layers as OL
+from gpu_util import GpuRun
+from test_gpu_bn_sums import EPS, _cuts, _per_worker, _tail
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hw,B,cin,C", [
+    (32, 5, 3, 64),      # four units to an image
+    (32, 530, 3, 64),    # more records than there is room for with two units to a workgroup: four
+    (32, 270, 3, 64),    # ... two
+    (32, 400, 3, 64),    # ... too few workgroups with four: a launch of its own
+    (16, 41, 3, 32),     # an image to a unit
+    (32, 6, 8, 24),      # eight stored channels, a block of outputs three quarters full
+    (64, 3, 3, 40),      # sixteen units to an image, the second block a quarter full
+])
+def test_statistics_behind_the_first_layer(hw, B, cin, C):
+    layers = [dict(op="conv", src=-1, cin=cin, cout=C, k=3, stride=1, pad=1, bias=False), dict(op="bn", src=0, c=C)] + _tail(1, C)
+    rng = np.random.default_rng(hw * 1000 + B)
+    params = synth.he_normal_params(layers, 3, True)
+    sl = synth.param_slices(layers)
+    w = np.zeros((C, 3, 3, cin), dtype=np.float32)    # the middle tap only: means of many deviations
+    w[:, 1, 1, :] = rng.uniform(0.2, 1.0, (C, cin))
+    params[sl[0]["w"][0]:sl[0]["w"][1]] = synth.to_bf16_grid(w.reshape(-1))
+    params[sl[1]["gamma"][0]:sl[1]["gamma"][1]] = 1.0
+    params[sl[1]["beta"][0]:sl[1]["beta"][1]] = 0.0
+    off = _cuts(B)
+    x = synth.to_bf16_grid((1.0 + 0.02 * rng.standard_normal((B, hw, hw, cin))).astype(np.float32))
+    run = GpuRun(layers, (hw, hw, cin), "bf16", len(off) - 1, B)
+    try:
+        for _ in range(2):                            # (the second step finds the first one's records in the workspace)
+            assert run.step(params, x, rng.integers(0, 10, B).astype(np.int32), off, 0.0)["status"] == 0
+        conv = run.activation(0, B).astype(np.float64).reshape(B, hw * hw, C)
+        out = run.activation(1, B).astype(np.float64).reshape(B, hw * hw, C)
+    finally:
+        run.close()
+    for rows in _per_worker(off):
+        v = conv[rows].reshape(-1, C)
+        mean, inv = v.mean(0), 1.0 / np.sqrt(v.var(0) + EPS)
+        xhat = (v - mean) * inv
+        # the mean as stored in fp32 (2^-24 of it), the difference, the factor and the product in fp32 (2^-24 each), all
+        # doubled; what is stored is a value in that interval, rounded to bf16
+        slack = 2.0 ** -23 * (np.abs(mean) * inv + 8 * np.abs(xhat))
+        got = out[rows].reshape(-1, C)
+        assert ((got >= OL.round_bf16(xhat - slack)) & (got <= OL.round_bf16(xhat + slack))).all(), rows
+        assert (np.abs(mean) * inv).max() > 10        # (the case is what it claims to be)
