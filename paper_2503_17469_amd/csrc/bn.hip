@@ -17,6 +17,7 @@
 #include "bf16.h"
 #include "common.h"
 #include "kernels.h"
+#include "quotient.h"
 
 namespace omni {
 
@@ -89,13 +90,22 @@ __device__ inline void store16(bf16_t* __restrict__ p, u32x4 t) {
 // memory busy, and few workgroups mean few records, which the apply kernel can then sum itself).
 // A split is `per` positions, a whole number of trips: splits of equal shares instead made most of them end in a
 // trip for one to three positions.
+// GAP (backward): dy is formed here, the gradient of a global average pooling's input from its output's, and stored: a launch less, and
+// this one reads no dy.  Step of the ResNet-18 shape in us, two launches / one: one worker, 32 images 878.6 / 876.6; two, 64 images
+// 1082.9 / 1078.5; four, 128 images 1354.9 / 1352.9; from 300 images on the same.
 constexpr int kPartThreads = 512, kPartTrip = kPartThreads / 8 * 4;
-template <bool BWD>
+struct GapIn {
+  const bf16_t *dout, *mask;   // gradient of the output [rows][C]; the input, where a ReLU is folded into it (else null)
+  bf16_t* din;
+  uint32_t by_hw;              // reciprocal_below(hw, positions)
+};
+template <bool BWD, bool GAP>
 __global__ __launch_bounds__(kPartThreads) void bn_partial_kernel(const bf16_t* __restrict__ x,
                                                                   const bf16_t* __restrict__ dy,
                                                                   const float* __restrict__ stats, int C, int hw,
                                                                   Segments seg, ShareTable tb, int per,
-                                                                  double* __restrict__ partial) {
+                                                                  double* __restrict__ partial, GapIn gap) {
+  static_assert(!GAP || BWD, "output gradients");
   constexpr int kRows = kPartThreads / 8;
   __shared__ double red[kRows][8][9];
   __shared__ double red2[8][64];
@@ -117,14 +127,34 @@ __global__ __launch_bounds__(kPartThreads) void bn_partial_kernel(const bf16_t* 
 #pragma unroll
   for (int e = 0; e < 8; ++e) { s1[e] = 0.0; s2[e] = 0.0; mu[e] = 0.f; is[e] = 1.f; }
   if (BWD) load_stats8(stats + ((size_t)wk * C + cl) * 2, mu, is);
+  const float inv_hw = 1.0f / (float)hw;
   for (long p = sbeg + pl; p < send; p += kPartTrip) {
     // loads are unconditional (a position past the end re-reads the last one and adds zero)
-    u32x4 xr[4], dr[4];
+    u32x4 xr[4], dr[4], mr[GAP ? 4 : 1];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const long q = min(p + kRows * u, send - 1);
       xr[u] = *reinterpret_cast<const u32x4*>(x + q * C + cl);
-      if (BWD) dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + cl);
+      if (GAP) {
+        dr[u] = *reinterpret_cast<const u32x4*>(gap.dout + (size_t)quotient((int)q, gap.by_hw, hw) * C + cl);
+        mr[GAP ? u : 0] = *reinterpret_cast<const u32x4*>(gap.mask ? gap.mask + q * C + cl : x + q * C + cl);
+      } else if (BWD) {
+        dr[u] = *reinterpret_cast<const u32x4*>(dy + q * C + cl);
+      }
+    }
+    if (GAP) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float g[8], m[8];
+        unpack8(dr[u], g);
+        unpack8(mr[GAP ? u : 0], m);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) g[e] = !gap.mask || m[e] > 0.f ? g[e] * inv_hw : 0.f;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) dr[u][d] = pack_bf16(g[2 * d], g[2 * d + 1]);
+        const long q = p + kRows * u;
+        if (cok && q < send) *reinterpret_cast<u32x4*>(gap.din + q * C + cl) = dr[u];
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -691,8 +721,8 @@ void bn_forward_bf16(hipStream_t st, const bf16_t* x, bf16_t* y, const float* ga
   const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
   const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
   if (!presummed)
-    hipLaunchKernelGGL(bn_partial_kernel<false>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, nullptr,
-                       nullptr, C, hw, seg, sp, per, partial);
+    hipLaunchKernelGGL((bn_partial_kernel<false, false>), dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, nullptr,
+                       nullptr, C, hw, seg, sp, per, partial, GapIn{});
   ShareTable fc;
   if (few_records(sp, seg, C, hw, fc)) {
     hipLaunchKernelGGL((bn_finish_kernel<false, false>), dim3(fc.first[seg.K], groups), dim3(256), 0, st, x, nullptr, partial, sp, stats,
@@ -714,8 +744,8 @@ void bn_backward_bf16(hipStream_t st, const bf16_t* x, const bf16_t* dy, bf16_t*
   const ShareTable sp = presummed ? *presummed : bn_splits(seg, C, hw, per);
   const int groups = (C + 63) / 64, fin = (C + kFinChannels - 1) / kFinChannels;
   if (!presummed)
-    hipLaunchKernelGGL(bn_partial_kernel<true>, dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, dy, stats, C,
-                       hw, seg, sp, per, partial);
+    hipLaunchKernelGGL((bn_partial_kernel<true, false>), dim3(sp.first[seg.K], groups), dim3(kPartThreads), 0, st, x, dy, stats, C,
+                       hw, seg, sp, per, partial, GapIn{});
   ShareTable fc;
   if (few_records(sp, seg, C, hw, fc)) {
     // (the workgroups are the other batch norm's records: no more of them than its own launch takes, and room behind these)
@@ -753,6 +783,16 @@ void route_grad_bf16(hipStream_t st, const bf16_t* g, const bf16_t* mask, bf16_t
 void gap_fwd_bf16(hipStream_t st, const bf16_t* in, bf16_t* out, int rows, int hw, int C) {
   const long pieces = (long)rows * (C / 8);
   hipLaunchKernelGGL(gap_fwd_kernel, dim3(blocks_for(pieces)), dim3(256), 0, st, in, out, C, hw, pieces);
+}
+
+ShareTable gap_bwd_and_bn_sums(hipStream_t st, const bf16_t* dout, const bf16_t* mask, bf16_t* din, int hw, int C, const Segments& seg,
+                               const bf16_t* x, const float* stats, double* partial) {
+  int per = 0;
+  const ShareTable sp = bn_splits(seg, C, hw, per);
+  const GapIn gap{dout, mask, din, reciprocal_below(hw, (uint64_t)seg.off[seg.K] * hw)};
+  hipLaunchKernelGGL((bn_partial_kernel<true, true>), dim3(sp.first[seg.K], (C + 63) / 64), dim3(kPartThreads), 0, st, x, nullptr, stats, C,
+                     hw, seg, sp, per, partial, gap);
+  return sp;
 }
 
 void gap_bwd_bf16(hipStream_t st, const bf16_t* dout, const bf16_t* mask, bf16_t* din, int rows, int hw, int C,

@@ -1164,8 +1164,27 @@ void step_bf16(StepCtx& c) {
         written[t] = 1;
       }
     } else if (L.d.op == OMNI_OP_GAP) {
-      omni::gap_bwd_bf16(st, grad(L.out), net->tensors[L.in0].relu ? act(L.in0) : nullptr, grad(L.in0), rows,
-                         L.ih * L.iw, L.ic, written[L.in0] != 0);
+      // the next batch norm of the walk, where what is written here is its whole output gradient (a residual add between hands it on)
+      const Tensor& ti = net->tensors[L.in0];
+      int below = i - 1, add = -1;
+      for (; below >= 0 && (net->layers[below].fused_away || (net->layers[below].d.op == OMNI_OP_ADD && add < 0)); --below)
+        if (!net->layers[below].fused_away) add = below;
+      bool whole = below >= 0 && net->layers[below].d.op == OMNI_OP_BN && ti.consumers == 1 && !written[L.in0];
+      if (whole && add < 0) whole = net->layers[below].out == L.in0;
+      else if (whole) {
+        const int t = net->layers[below].out;
+        whole = net->layers[add].out == L.in0 && (net->layers[add].in0 == t || net->layers[add].in1 == t) && !net->tensors[t].relu &&
+                net->tensors[t].consumers == 1 && !written[t];
+      }
+      if (whole) {
+        const Layer& N = net->layers[below];
+        presummed = omni::gap_bwd_and_bn_sums(st, grad(L.out), ti.relu ? act(L.in0) : nullptr, grad(L.in0), L.ih * L.iw, L.ic, c.seg,
+                                              act(N.in0), bn_area + N.stat_off, bn_partial);
+        presummed_for = below;
+        presummed_at = bn_partial;
+      } else {
+        omni::gap_bwd_bf16(st, grad(L.out), ti.relu ? act(L.in0) : nullptr, grad(L.in0), rows, L.ih * L.iw, L.ic, written[L.in0] != 0);
+      }
       written[L.in0] = 1;
     }
   }

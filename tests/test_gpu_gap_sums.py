@@ -1,0 +1,60 @@
+"""The gradient of a global average pooling's input, formed by the kernel that takes the backward sums of the batch norm below it: with a
+ReLU between, without one, behind a residual add; channels that fill no group of 64, maps that are no power of two, many images."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import layers as OL
+from gpu_util import GpuRun
+from test_gpu_bn_sums import EPS, _conv, _cuts, _per_worker, _tail
+
+pytestmark = pytest.mark.gpu
+
+
+def _net(kind, C):
+    layers = [_conv(-1, C), dict(op="bn", src=0, c=C)]
+    if kind == "plain":
+        return layers + _tail(1, C), 1
+    layers.append(dict(op="relu", src=1))
+    if kind == "relu":
+        return layers + _tail(2, C), 1
+    layers += [_conv(2, C), dict(op="bn", src=3, c=C), dict(op="add", src=4, src2=2), dict(op="relu", src=5)]
+    return layers + _tail(6, C), 4
+
+
+@pytest.mark.parametrize("kind,hw,B,C", [("plain", 4, 5, 64), ("relu", 6, 13, 72), ("block", 4, 37, 64), ("block", 8, 300, 128),
+                                         ("block", 4, 1500, 64), ("relu", 4, 3, 8)])
+def test_pooling_gradient_and_sums(kind, hw, B, C):
+    import paper_2503_17469_amd as omni
+    layers, bn = _net(kind, C)
+    params = synth.he_normal_params(layers, 5, True)
+    rng = np.random.default_rng(B)
+    off = _cuts(B)
+    x = synth.to_bf16_grid(rng.standard_normal((B, hw, hw, C)).astype(np.float32))
+    run = GpuRun(layers, (hw, hw, C), "bf16", len(off) - 1, B)
+    try:
+        got = run.step(params, x, rng.integers(0, 10, B).astype(np.int32), off, 0.0)
+        assert got["status"] == 0
+        gap = len(layers) - 2
+
+        def grad(i):
+            return omni.net_activation_grad(run.net, run.ws, i, B, "bf16").float().cpu().numpy().reshape(B, -1, C)
+
+        want = np.broadcast_to(grad(gap) * np.float32(1.0 / (hw * hw)), (B, hw * hw, C))
+        if kind != "plain":
+            want = np.where(run.activation(gap - 1, B).reshape(B, -1, C) > 0, want, 0)
+        assert np.abs(want).max() > 0
+        dy = grad(gap - 1)
+        assert np.array_equal(dy, OL.round_bf16(want).astype(np.float32))
+        xin = run.activation(layers[bn]["src"], B).astype(np.float64).reshape(B, -1, C)
+        for k, rows in enumerate(_per_worker(off)):
+            v, d = xin[rows].reshape(-1, C), dy[rows].reshape(-1, C).astype(np.float64)
+            mean, inv = v.mean(0), 1.0 / np.sqrt(v.var(0) + EPS)
+            size = np.abs(d) * (np.abs(v) + np.abs(mean)) * inv
+            # the mean and the factor in fp32 (a unit each), a difference and two products (half a unit each), of `size` at most
+            for name, t, bound in (("beta", d, 2.0 ** -23 * np.abs(d.sum(0)) + 1e-12 * np.abs(d).sum(0)),
+                                   ("gamma", d * (v - mean) * inv, 4 * 2.0 ** -23 * size.sum(0))):
+                s, e = synth.param_slices(layers)[bn][name]
+                assert np.all(np.abs(got["worker_grads"][k, s:e] - t.sum(0)) <= bound), (name, k)
+    finally:
+        run.close()
